@@ -40,6 +40,7 @@ constexpr int kTile = 256;       // GEMM output tile edge in unpacked rows (both
 constexpr int kChunk = 64;       // physical rows the GEMM epilogue holds at a time; no source row straddles a chunk
 constexpr int kKPad = 128;       // every exponent group is padded to a multiple of this many columns
 constexpr int kMaxGroups = 64;   // distinct diagonal entries of S the planner supports
+constexpr int kMaxItems = 1024;  // products of a batch that are planned together
 constexpr int kMaxRuns = 128;    // stretches of consecutive k-tiles that read consecutive blocks of the A store
 constexpr uint32_t kNever = 0xFFFFFFFFu;  // split time of a row/column that is never split
 
@@ -72,7 +73,7 @@ struct PlanHeader {
     int32_t run_kt0[kMaxRuns];
     int32_t run_blk0[kMaxRuns];
     int32_t run_grp[kMaxRuns];       // the group the run belongs to
-    int32_t edgesA, edgesB, obcount; // OB entry lists built for UnpackBoth
+    int32_t edgesA, edgesB;          // OB entry lists built for UnpackBoth
     int32_t nobA, nobB;              // OB entries of A / B kept for the scatter (UnpackBoth operands)
     int32_t overflow;                // bit set: which capacity was too small
     int32_t need[10];                // size that would have been needed, per capacity
@@ -119,7 +120,7 @@ struct RowLayout {
 // stored.  The A store holds every column of A_u once, level by level (level 0 = the d original
 // columns in order, level a = the columns appended by a-fold splits, ordered by original column), each
 // level padded to whole blocks of 128, plus a few blocks of gathered copies for exponent groups that
-// use only a small part of a level; the GEMM reads A's k-tile t from block ktile_ablk[t] of the store.
+// use only a small part of a level; the GEMM walks it run by run (PlanHeader::run_*).
 struct ColLayout {
     int32_t *pcol_slot;   // [Kp] column slot of the second unpacking in this column of B_eu, -1 = zero column
     int32_t *col_phys;    // [d'] column of B_eu of every column slot of the second unpacking
@@ -137,7 +138,43 @@ struct ColLayout {
                                   // entry of it weighs in the row norm behind the accumulator bound)
     int4 *unitA;          // [KA/16] as unitB (w = level only)
     unsigned long long *unitA_w;  // [KA/16] the weight of the unit's columns if they share one
-    int32_t *ktile_ablk;  // [Kp/128] block of the A store that GEMM k-tile t reads
+};
+
+// ---- batches.  The items of a batch (products of one shape) are planned, unpacked and multiplied by the
+// same launches: every device array of item i lies i * stride bytes behind that of item 0 (the headers lie
+// side by side in an array of their own), and a kernel moves the pointers it was given to its item.
+// (Byte-pointer arithmetic, not integers: through an integer the compiler loses that these are global
+// addresses and every access becomes a flat one: 82 -> 99 us for the scatter of a 4096 x 4096 and a 11008 x 4096
+// operand.)
+template <class T>
+__host__ __device__ __forceinline__ T *item_at(T *p, int64_t off) {
+    return p ? (T *)((const char *)p + off) : p;
+}
+__host__ __device__ __forceinline__ void move_to_item(SlotSet &s, int64_t off) {
+    s.root = item_at(s.root, off); s.exp = item_at(s.exp, off); s.time = item_at(s.time, off);
+    s.child = item_at(s.child, off); s.key = item_at(s.key, off);
+}
+__host__ __device__ __forceinline__ void move_to_item(RowLayout &l, int64_t off) {
+    l.prow_slot = item_at(l.prow_slot, off); l.prow_src = item_at(l.prow_src, off); l.prow_exp = item_at(l.prow_exp, off);
+    l.row_phys = item_at(l.row_phys, off); l.src_pstart = item_at(l.src_pstart, off); l.src_nlev = item_at(l.src_nlev, off);
+    l.tile_src0 = item_at(l.tile_src0, off); l.chunk_src0 = item_at(l.chunk_src0, off); l.tile_flat = item_at(l.tile_flat, off);
+    l.rowsum = item_at(l.rowsum, off); l.wavesum = item_at(l.wavesum, off);
+}
+__host__ __device__ __forceinline__ void move_to_item(ColLayout &c, int64_t off) {
+    c.pcol_slot = item_at(c.pcol_slot, off); c.col_phys = item_at(c.col_phys, off); c.colB_k = item_at(c.colB_k, off);
+    c.colB_e = item_at(c.colB_e, off); c.col_sexp = item_at(c.col_sexp, off); c.unitB = item_at(c.unitB, off);
+    c.acol_phys = item_at(c.acol_phys, off); c.apos = item_at(c.apos, off); c.colA_k = item_at(c.colA_k, off);
+    c.colA_e = item_at(c.colA_e, off); c.colA_w = item_at(c.colA_w, off); c.unitA = item_at(c.unitA, off);
+    c.unitA_w = item_at(c.unitA_w, off);
+}
+
+// What the quantize pass needs to know of a batch: strides in bytes from item to item of the two inputs and of everything that belongs
+// to an item (integers, statistics, lists, steps on the device).  flag: if set, `status` is not used and
+// what goes wrong in any item is ORed into *flag, which the caller has cleared.
+struct QuantBatch {
+    int nitems = 1;
+    int64_t a_stride = 0, b_stride = 0, out_stride = 0;
+    int32_t *flag = nullptr;
 };
 
 // ---- wave-wide reductions and scans on the vector ALU's data-parallel-primitive moves (shifts within a
@@ -206,9 +243,14 @@ struct imunpack_plan {
     // capacities (grow on overflow)
     int32_t cap[10];
     // views into the arena (valid after a successful imunpack_plan)
-    imu::PlanHeader *d_hdr;
-    imu::PlanHeader hdr;          // host mirror
-    imu::PlanHeader *pin_hdr;     // pinned staging copy of the header (device-to-host copies land here)
+    imu::PlanHeader *d_hdr;       // one per item
+    imu::PlanHeader hdr;          // host mirror (of item 0)
+    imu::PlanHeader *pin_hdr;     // pinned copies of the headers (device-to-host copies land here)
+    int pin_items;                // ... how many of them fit
+    // batch: the plans of `nitems` products of one shape, made by the same launches (1: a plan of its own)
+    int nitems;
+    int64_t item_bytes;           // from the arrays of one item in the arena to those of the next
+    int64_t op_stride;            // from item to item: the integer operands, their statistics and OB lists
     hipEvent_t ready;             // recorded after such a copy; the host polls it
     hipStream_t side;             // carries the copy of the accumulator bounds, so that the caller's stream
                                   // can already hold the GEMM while the host waits for them
@@ -225,14 +267,13 @@ struct imunpack_plan {
     int32_t *rcnt, *ccnt;
     int32_t *extraRows;               // per row of B: how many of those extra edges it has
     int32_t *obcopyA, *obcopyB;       // OB entries of an UnpackBoth operand, kept for the scatter: [3][cap[CAP_EDGEx]]
-    int32_t *ob;                      // own OB entry list [3][cap[CAP_OB]] when the caller gave none
+    int32_t *ob, *obcnt;              // own OB entry list [3][cap[CAP_OB]] when the caller gave none, and its length
     int32_t *tmpL, *tmpCur, *tmpPA, *tmpPB, *tmpE, *tmpK, *tmpR, *tmpOff;
     int ignore_listA, ignore_listB;   // a caller's OB list overflowed: scan the operand ourselves
     int bothA, bothB;                 // slot numbering of the set needs the export-time sort
     // canonical (paper-order) numbering, built lazily by the export / test paths
     int canon_valid;
     int32_t *canon_rowphysA, *canon_rowphysB, *canon_colphys, *canon_acolphys;   // device, indexed by canonical slot
-    int32_t *tmpApos;
     int fusable;      // set by imunpack_unpack
     int unpacked;
     int valid;
@@ -250,17 +291,40 @@ struct imunpack_plan {
 namespace imu {
 using Plan = struct ::imunpack_plan;  // the C function imunpack_plan() hides the bare struct name
 
-// Copies bytes [offset, offset + bytes) of the device header into the host mirror and waits for it.
-// The wait polls an event instead of blocking in the driver: the wake-up of a blocking wait costs
+// Copies the device headers to the host and waits for them.  The wait polls an event instead of blocking in the driver: the wake-up of a blocking wait costs
 // tens of microseconds during which the GPU idles between two stages of the path.
-int fetch_header(Plan *p, size_t offset, size_t bytes, hipStream_t st);
+int fetch_headers(Plan *p, hipStream_t st);
+// The entry points' inner forms, which also serve the items of a batch (p->nitems of them).
+int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t *B, int64_t h, int64_t ldb, int b,
+              int strategy_A, int strategy_B, const imunpack_stats_t *stats_A, const imunpack_stats_t *stats_B,
+              imunpack_plan_t **plan, int nitems, int64_t op_stride, hipStream_t st);
+Plan item_view(const Plan &batch, int i);
+int unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const int32_t *B, int64_t ldb, int8_t *A_ue,
+                int64_t a_stride, int8_t *B_eu, int64_t b_stride, hipStream_t st);
+int quantize_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float scale_A, const float *scale_A_dev,
+                  int32_t *QA, int64_t ldqa, const imunpack_stats_t *stA, const float *B, int64_t h, int64_t sb_r,
+                  int64_t sb_c, float scale_B, const float *scale_B_dev, int32_t *QB, int64_t ldqb,
+                  const imunpack_stats_t *stB, int64_t d, int b, int32_t *status, const QuantBatch &bt, hipStream_t stream);
+int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *workspace, int64_t *C_int,
+              float *C_fp, int64_t ldc, float scale_A, float scale_B, const float *scale_a_dev,
+              const float *scale_b_dev, int fuse, hipStream_t stream);
+// The fused launch for every item of a batch.  An item whose accumulator bound is too large for it writes
+// nothing and sets refused[item] (device, cleared by the caller).
+int gemm_batch(imunpack_plan_t *p, const int8_t *A_ue, int64_t a_stride, const int8_t *B_eu, int64_t b_stride, float *C_fp,
+               int64_t c_stride, int64_t ldc, const float *scale_a_dev, const float *scale_b_dev, int64_t scale_stride,
+               int32_t *refused, hipStream_t stream);
+// The RTN steps of the items of a batch (percentile.hip).
+int rtn_steps(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p, float beta, float *step,
+              int32_t *status_flag, void *workspace, int nitems, int64_t x_stride, int64_t out_stride, int32_t *flag,
+              hipStream_t st);
 // Waits for the bounds that imunpack_unpack left in flight and sets p->fusable.
 int resolve_bound(Plan *p);
 // Bytes from one physical row to the next of the A store (op 0) / of B_eu (op 1) in the digit format in
 // effect.  6-bit digits: 96 bytes per k-tile of 128 columns, the same rule against power-of-two pitches.
-inline int64_t store_pitch(const Plan *p, int op) {
-    if (!p->fp6) return op ? p->hdr.ldB : p->hdr.ldA;
-    const int bytes = (op ? p->hdr.Kp : p->hdr.KA) / 4 * 3;
+__host__ __device__ inline int header_pitch(const PlanHeader &h, int fp6, int op) {
+    if (!fp6) return op ? h.ldB : h.ldA;
+    const int bytes = (op ? h.Kp : h.KA) / 4 * 3;
     return bytes >= 2048 ? (((bytes + 255) / 256) | 1) * 256 : bytes;
 }
+inline int64_t store_pitch(const Plan *p, int op) { return header_pitch(p->hdr, p->fp6, op); }
 }

@@ -49,7 +49,6 @@ struct GemmArgs {
     int seg_delta[kMaxGroups + 1];
     // fused epilogue
     RowLayout layA, layB;
-    const int32_t *flatA, *flatB;   // per tile: 1 if every source row of the tile has a single level
     int sh, final_shift;
     int64_t *C_int;
     float *C_fp;
@@ -65,6 +64,11 @@ struct GemmArgs {
     const unsigned long long *guard;
     int guard_mul;            // s - 1
     int fold_f64;             // no int64 output wanted and every sum over digit levels is exact in binary64
+    // batch (blockIdx.y is the item): everything above that the plan decides comes from the item's header;
+    // an item that may not be fused writes nothing and sets refused[item]
+    const PlanHeader *hdr;    // nullptr: not a batch
+    int64_t a_stride, b_stride, c_stride, plan_stride, scale_stride;  // bytes from item to item
+    int32_t *refused;
     // benchmark reporting: if set, workgroup 0 writes {shader clock ticks, 100 MHz wall ticks} of its K loop
     unsigned long long *clock_probe;
 };
@@ -112,23 +116,40 @@ __device__ __forceinline__ const int8_t *uniform_ptr(const int8_t *p) {
 // with 96 the rows that a wave reads together would share banks two by two); a lane's fragment of
 // v_mfma_f32_32x32x64_f8f6f4 is one 16-byte and one 8-byte read (see fp6_dword); a k-tile is two k-steps
 // of 16 matrix instructions; the accumulators are binary32 and hold integers below 2^24, exactly.
-template <int MODE, bool FP6>  // MODE 0: fused epilogue, 1: int64 segment into C_u
+//
+// BATCH: the items of a batch (blockIdx.y) in one launch; what the plan decides comes from the item's header.  A
+// variant of its own: read through a run-time choice, those values cost the one-product kernel its last
+// registers (101 spilled; 348 -> 460 us on a 4096 x 8228 x 11013 unpacked product).
+template <int MODE, bool FP6, bool BATCH = false>  // MODE 0: fused epilogue, 1: int64 segment into C_u
 __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     constexpr int kRowB = FP6 ? 96 : BK;           // bytes of a row of the operand per k-tile
     constexpr int kPitch = FP6 ? 112 : BK;         // bytes from row to row in LDS
     constexpr int kHalfBytes = BM * kPitch;        // the A tile or the B tile of one k-tile in LDS
     constexpr int kLoads = FP6 ? 7 : 8;            // direct-to-LDS loads per wave and half-stage
     constexpr int kWaveBytes = 64 * kPitch;        // a wave's 64 rows of a half-stage
-    if (MODE == 0 && g.guard) {
-        const unsigned long long b0 = g.guard[0], b1 = g.guard[1];
-        const unsigned long long m = b0 < b1 ? b0 : b1;
-        if (!(m < (1ull << 40) && m * (unsigned long long)g.guard_mul < (1ull << (FP6 ? 24 : 31)))) return;
-    }
     const int tid = threadIdx.x, lane = tid & 63;
+    const PlanHeader *hdr = BATCH ? g.hdr + blockIdx.y : nullptr;
+    int mtiles = g.mtiles, ntiles = g.ntiles, ldA = g.ldA, ldB = g.ldB, kt0 = g.kt0, kt1 = g.kt1, nbound = g.nbound;
+    if constexpr (BATCH) {
+        mtiles = hdr->mtiles; ntiles = hdr->ntiles;
+        if ((int)blockIdx.x >= mtiles * ntiles) return;  // the grid covers the largest item
+        ldA = header_pitch(*hdr, FP6, 0); ldB = header_pitch(*hdr, FP6, 1);
+        kt0 = 0; kt1 = hdr->Kp / BK;
+        nbound = hdr->nruns - 1;
+    }
+    if (MODE == 0 && (BATCH || g.guard)) {
+        const unsigned long long *guard = BATCH ? hdr->bound : g.guard;
+        const unsigned long long b0 = guard[0], b1 = guard[1];
+        const unsigned long long m = b0 < b1 ? b0 : b1;
+        if (!(m < (1ull << 40) && m * (unsigned long long)g.guard_mul < (1ull << (FP6 ? 24 : 31))) || (BATCH && nbound >= 63)) {
+            if (g.refused && blockIdx.x == 0 && tid == 0) g.refused[blockIdx.y] = 1;
+            return;
+        }
+    }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     int tm, tn;
-    tile_of(blockIdx.x, g.mtiles, g.ntiles, tm, tn);
+    tile_of(blockIdx.x, mtiles, ntiles, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const unsigned lds0 = (unsigned)(size_t)smem;
 
@@ -143,24 +164,35 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             const int slot = u * 64 + lane;
             const int r = slot / 7, piece = min(slot - 7 * r, 5);
             const int row = 64 * wave + r;
-            voffA[u] = (unsigned)row * (unsigned)g.ldA + (unsigned)(piece * 16);
-            voffB[u] = (unsigned)row * (unsigned)g.ldB + (unsigned)(piece * 16);
+            voffA[u] = (unsigned)row * (unsigned)ldA + (unsigned)(piece * 16);
+            voffB[u] = (unsigned)row * (unsigned)ldB + (unsigned)(piece * 16);
         } else {
             const int row = 64 * wave + 8 * u + (lane >> 3);
             const int kc = (lane & 7) ^ ((row >> 1) & 7);
-            voffA[u] = (unsigned)row * (unsigned)g.ldA + (unsigned)(kc * 16);
-            voffB[u] = (unsigned)row * (unsigned)g.ldB + (unsigned)(kc * 16);
+            voffA[u] = (unsigned)row * (unsigned)ldA + (unsigned)(kc * 16);
+            voffB[u] = (unsigned)row * (unsigned)ldB + (unsigned)(kc * 16);
         }
     }
-    const int8_t *gA = g.A + (int64_t)m0 * g.ldA, *gB = g.B + (int64_t)n0 * g.ldB;
+    const int8_t *gA = g.A + (int64_t)m0 * ldA, *gB = g.B + (int64_t)n0 * ldB;
+    if constexpr (BATCH) {
+        gA += blockIdx.y * g.a_stride;
+        gB += blockIdx.y * g.b_stride;
+    }
     // Loads past the end of the range are clamped to the last k-tile: they land in a free slot and
     // are never read, which keeps the count of outstanding loads the same in every iteration.
-    const int kt0 = g.kt0, kt1 = g.kt1;
     // The loads run two k-tiles ahead of the arithmetic and so cross into the next segment earlier: they
-    // keep a segment pointer of their own.  Lane i holds the end and the block offset of segment i, so
-    // that moving on to the next segment is two lane reads and no memory access inside the loop.
-    const int v_end = lane < g.nbound ? g.bound_kt[lane] + 1 : kt1;
-    const int v_delta = g.seg_delta[min(lane, g.nbound)];
+    // keep a segment pointer of their own.  Lane i holds the end of segment i, its block offset and the shift
+    // behind it, so that moving on to the next segment is two lane reads and no memory access inside the loop.
+    int v_end, v_delta, v_shift = 0;
+    if constexpr (BATCH) {
+        const int r = min(lane, nbound), r1 = min(r + 1, nbound);
+        v_end = lane < nbound ? hdr->run_kt0[r1] : kt1;
+        v_delta = hdr->run_blk0[r] - hdr->run_kt0[r];
+        v_shift = g.sh * (hdr->grp_exp[hdr->run_grp[r]] - hdr->grp_exp[hdr->run_grp[r1]]);
+    } else {
+        v_end = lane < nbound ? g.bound_kt[lane] + 1 : kt1;
+        v_delta = g.seg_delta[min(lane, nbound)];
+    }
     int la_seg = 0, la_end = __builtin_amdgcn_readlane(v_end, 0), la_delta = __builtin_amdgcn_readlane(v_delta, 0);
     auto ring = [](int slot, int k) { slot += k; return slot >= kRing ? slot - kRing : slot; };
     const int8_t *pg = nullptr;
@@ -281,12 +313,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     // loads); past the barrier that holds for all waves, so step 4 may prefetch fragments of k-tile
     // kt+1 and stream B(kt+2) into the slot of A(kt).
     int kt = kt0;
-    for (int seg = 0; seg <= g.nbound; ++seg) {
-        if (seg > 0 && g.bound_sh[seg - 1] != 0) {  // start of the next exponent group: Horner step
+    for (int seg = 0; seg <= nbound; ++seg) {
+        const int shv = seg == 0 ? 0 : BATCH ? __builtin_amdgcn_readlane(v_shift, seg - 1) : g.bound_sh[seg - 1];
+        if (shv != 0) {  // start of the next exponent group: Horner step
             // The accumulators fill the whole accumulation register file (a0..a255), so shifting every
             // one of those registers shifts every accumulator, whichever block sits where.  Written
             // out by hand: left to the compiler, this step spills three blocks to scratch memory.
-            const int shv = g.bound_sh[seg - 1];
             int t0, t1, t2, t3;
             if constexpr (FP6) {  // binary32 accumulators: times 2^shift, exact
                 asm volatile(
@@ -335,7 +367,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                   "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
                 : [sh] "s"(shv));
         }
-        const int kend = seg < g.nbound ? g.bound_kt[seg] + 1 : kt1;
+        const int kend = BATCH ? __builtin_amdgcn_readlane(v_end, seg) : seg < nbound ? g.bound_kt[seg] + 1 : kt1;
         for (; kt < kend; ++kt) {
             const int8_t *stA = smem + sa * kHalfBytes, *stB = smem + ring(sa, 1) * kHalfBytes;
             const int8_t *stA1 = smem + ring(sa, 2) * kHalfBytes, *stB1 = smem + ring(sa, 3) * kHalfBytes;
@@ -404,23 +436,36 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     // row-contiguous and the digit levels of a source row (which the planner keeps inside one chunk)
     // and of a source column (inside one tile) can be added up:
     // C_int[i,j] = sum_{levels a of i, c of j} s^(a+c) * acc[row(i,a)][col(j,c)].
-    const int jsrc0 = g.layB.tile_src0[tn], nsrcB = g.layB.tile_src0[tn + 1] - jsrc0;
-    const bool flatA = g.flatA[tm] != 0, flatB = g.flatB[tn] != 0;
+    RowLayout layA = g.layA, layB = g.layB;
+    float *C_fp = g.C_fp;
+    int final_shift = g.final_shift, fold_f64 = g.fold_f64;
+    const float *scale_a_dev = g.scale_a_dev, *scale_b_dev = g.scale_b_dev;
+    if constexpr (BATCH) {
+        move_to_item(layA, blockIdx.y * g.plan_stride);
+        move_to_item(layB, blockIdx.y * g.plan_stride);
+        C_fp = item_at(C_fp, blockIdx.y * g.c_stride);
+        final_shift = hdr->ngroups ? g.sh * hdr->grp_exp[hdr->ngroups - 1] : 0;
+        fold_f64 = 31 + g.sh * ((hdr->lmaxA - 1) + (hdr->lmaxB - 1)) <= 52;
+        scale_a_dev = item_at(scale_a_dev, blockIdx.y * g.scale_stride);
+        scale_b_dev = item_at(scale_b_dev, blockIdx.y * g.scale_stride);
+    }
+    const int jsrc0 = layB.tile_src0[tn], nsrcB = layB.tile_src0[tn + 1] - jsrc0;
+    const bool flatA = layA.tile_flat[tm] != 0, flatB = layB.tile_flat[tn] != 0;
     constexpr int FLD = 260;
     int32_t *foldbuf = reinterpret_cast<int32_t *>(smem);  // two regions of [64][FLD]
     // behind the staging buffer: per source row of the tile its first physical row (relative to the
     // tile) | levels << 16; the same per source column; the first source row of each chunk
     int32_t *rowmeta = foldbuf + 2 * kChunk * FLD, *colmeta = rowmeta + kTile, *chunk0 = colmeta + kTile;
     // scale * 2^final_shift is exact: one multiplication in binary64, one rounding to fp32
-    const double scale2 = (g.scale_a_dev ? (double)*g.scale_a_dev * (double)*g.scale_b_dev : g.scale) *
-                          (double)(1ull << g.final_shift);
+    const double scale2 = (scale_a_dev ? (double)*scale_a_dev * (double)*scale_b_dev : g.scale) *
+                          (double)(1ull << final_shift);
     {
-        const int isrc0 = g.layA.tile_src0[tm], nsrcA = g.layA.tile_src0[tm + 1] - isrc0;
+        const int isrc0 = layA.tile_src0[tm], nsrcA = layA.tile_src0[tm + 1] - isrc0;
         if (!flatA && tid < nsrcA)
-            rowmeta[tid] = (g.layA.src_pstart[isrc0 + tid] - m0) | (g.layA.src_nlev[isrc0 + tid] << 16);
+            rowmeta[tid] = (layA.src_pstart[isrc0 + tid] - m0) | (layA.src_nlev[isrc0 + tid] << 16);
         if (!flatB && tid < nsrcB)
-            colmeta[tid] = (g.layB.src_pstart[jsrc0 + tid] - n0) | (g.layB.src_nlev[jsrc0 + tid] << 16);
-        if (tid <= kTile / kChunk) chunk0[tid] = g.layA.chunk_src0[tm * (kTile / kChunk) + tid];
+            colmeta[tid] = (layB.src_pstart[jsrc0 + tid] - n0) | (layB.src_nlev[jsrc0 + tid] << 16);
+        if (tid <= kTile / kChunk) chunk0[tid] = layA.chunk_src0[tm * (kTile / kChunk) + tid];
     }  // published by the first barrier below
     // Four results of one output row leave as 16 bytes of fp32 and / or 32 bytes of int64 (any element
     // boundary will do: a wave still writes a contiguous kilobyte), fewer than four at the ragged end of
@@ -431,17 +476,17 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             if (cols_left >= 4) {
                 v4f_u x;
                 x[0] = f[0]; x[1] = f[1]; x[2] = f[2]; x[3] = f[3];
-                __builtin_nontemporal_store(x, reinterpret_cast<v4f_u *>(g.C_fp + o));
+                __builtin_nontemporal_store(x, reinterpret_cast<v4f_u *>(C_fp + o));
             } else {
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    if (k < cols_left) g.C_fp[o + k] = f[k];
+                    if (k < cols_left) C_fp[o + k] = f[k];
             }
             return;
         }
         const int64_t w[4] = {(int64_t)v0, (int64_t)v1, (int64_t)v2, (int64_t)v3};
         float f[4];
-        if (g.C_fp) {
+        if (C_fp) {
             if constexpr (sizeof(v0) == 4) {
                 f[0] = (float)((double)v0 * scale2); f[1] = (float)((double)v1 * scale2);
                 f[2] = (float)((double)v2 * scale2); f[3] = (float)((double)v3 * scale2);
@@ -451,15 +496,15 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             }
         }
         if (cols_left >= 4) {
-            if (g.C_fp) {
+            if (C_fp) {
                 v4f_u x;
                 x[0] = f[0]; x[1] = f[1]; x[2] = f[2]; x[3] = f[3];
-                __builtin_nontemporal_store(x, reinterpret_cast<v4f_u *>(g.C_fp + o));
+                __builtin_nontemporal_store(x, reinterpret_cast<v4f_u *>(C_fp + o));
             }
             if (g.C_int) {
                 v2l_u lo, hi;
-                lo[0] = w[0] << g.final_shift; lo[1] = w[1] << g.final_shift;
-                hi[0] = w[2] << g.final_shift; hi[1] = w[3] << g.final_shift;
+                lo[0] = w[0] << final_shift; lo[1] = w[1] << final_shift;
+                hi[0] = w[2] << final_shift; hi[1] = w[3] << final_shift;
                 __builtin_nontemporal_store(lo, reinterpret_cast<v2l_u *>(g.C_int + o));
                 __builtin_nontemporal_store(hi, reinterpret_cast<v2l_u *>(g.C_int + o + 2));
             }
@@ -467,8 +512,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 if (k < cols_left) {
-                    if (g.C_fp) g.C_fp[o + k] = f[k];
-                    if (g.C_int) g.C_int[o + k] = w[k] << g.final_shift;
+                    if (C_fp) C_fp[o + k] = f[k];
+                    if (g.C_int) g.C_int[o + k] = w[k] << final_shift;
                 }
         }
     };
@@ -548,7 +593,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                                            v[u][1], v[u][2], v[u][3]);
                         }
                     };
-                    if (g.fold_f64) fold_rows(0.0);
+                    if (fold_f64) fold_rows(0.0);
                     else fold_rows((int64_t)0);
                 }
             } else {
@@ -655,6 +700,12 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_i8_kernel(const GemmArgs
     gemm_body<MODE, false>(g, smem);
 }
 
+template <bool FP6>
+__global__ __launch_bounds__(kGemmThreads, 1) void gemm_batch_kernel(const GemmArgs g) {
+    extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
+    gemm_body<0, FP6, true>(g, smem);
+}
+
 template <int MODE>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_f6_kernel(const GemmArgs g) {
     extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
@@ -724,6 +775,8 @@ static int gemm_lds_opt_in() {
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_i8_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_f6_kernel<0>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_f6_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_batch_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_batch_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         done.store(1, std::memory_order_release);
     }
     return IMUNPACK_OK;
@@ -757,12 +810,34 @@ extern "C" int imunpack_recombine(const imunpack_plan_t *p, const void *workspac
 }
 
 namespace imu {
+// What the fused launch of one plan takes from its header.
+static void fused_args(GemmArgs &g, const Plan *p) {
+    const PlanHeader &h = p->hdr;
+    g.ldA = (int)store_pitch(p, 0); g.ldB = (int)store_pitch(p, 1); g.Kp = h.Kp; g.mtiles = h.mtiles; g.ntiles = h.ntiles;
+    g.layA = p->layA; g.layB = p->layB;
+    g.sh = p->sh;
+    g.Np = h.Np;
+    g.guard_mul = p->s - 1;
+    g.kt0 = 0; g.kt1 = h.Kp / BK;
+    g.nbound = 0;
+    for (int r = 0; r < h.nruns; ++r) {
+        g.seg_delta[r] = h.run_blk0[r] - h.run_kt0[r];
+        if (r + 1 < h.nruns) {
+            g.bound_kt[g.nbound] = h.run_kt0[r + 1] - 1;
+            g.bound_sh[g.nbound] = p->sh * (h.grp_exp[h.run_grp[r]] - h.grp_exp[h.run_grp[r + 1]]);
+            ++g.nbound;
+        }
+    }
+    g.final_shift = h.ngroups ? p->sh * h.grp_exp[h.ngroups - 1] : 0;
+    // |accumulator| < 2^31, weights up to s^(levels of a row - 1 + levels of a column - 1)
+    g.fold_f64 = 31 + p->sh * ((h.lmaxA - 1) + (h.lmaxB - 1)) <= 52;
+}
+
 int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *workspace, int64_t *C_int,
               float *C_fp, int64_t ldc, float scale_A, float scale_B, const float *scale_a_dev,
-              const float *scale_b_dev, int fuse, imunpack_stream_t stream) {
+              const float *scale_b_dev, int fuse, hipStream_t st) {
     if (!p || !p->valid || !p->unpacked || !A_ue || !B_eu || (scale_a_dev == nullptr) != (scale_b_dev == nullptr))
         return IMUNPACK_EINVAL;
-    hipStream_t st = (hipStream_t)stream;
     const PlanHeader &h = p->hdr;
     if (h.mtiles <= 0 || h.ntiles <= 0) return IMUNPACK_OK;
     IMU_TRY(check_shifts(p));
@@ -772,7 +847,6 @@ int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *
     g.A = A_ue; g.B = B_eu;
     g.ldA = (int)store_pitch(p, 0); g.ldB = (int)store_pitch(p, 1); g.Kp = h.Kp; g.mtiles = h.mtiles; g.ntiles = h.ntiles;
     g.layA = p->layA; g.layB = p->layB;
-    g.flatA = p->layA.tile_flat; g.flatB = p->layB.tile_flat;
     g.sh = p->sh;
     g.Np = h.Np;
     const int grid = h.mtiles * h.ntiles;
@@ -796,25 +870,13 @@ int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *
     }
     if (fused) {
         if ((!C_int && !C_fp) || ldc < p->h) return IMUNPACK_EINVAL;
+        fused_args(g, p);
         g.guard = speculate ? p->d_hdr->bound : nullptr;
-        g.guard_mul = p->s - 1;
-        g.kt0 = 0; g.kt1 = h.Kp / BK;
-        g.nbound = 0;
-        for (int r = 0; r < h.nruns; ++r) {
-            g.seg_delta[r] = h.run_blk0[r] - h.run_kt0[r];
-            if (r + 1 < h.nruns) {
-                g.bound_kt[g.nbound] = h.run_kt0[r + 1] - 1;
-                g.bound_sh[g.nbound] = p->sh * (h.grp_exp[h.run_grp[r]] - h.grp_exp[h.run_grp[r + 1]]);
-                ++g.nbound;
-            }
-        }
-        g.final_shift = h.ngroups ? p->sh * h.grp_exp[h.ngroups - 1] : 0;
         g.C_int = C_int; g.C_fp = C_fp; g.ldc = ldc;
         g.scale = (double)scale_A * (double)scale_B;
         g.scale_a_dev = scale_a_dev; g.scale_b_dev = scale_b_dev;
         g.clock_probe = g_clock_probe.load(std::memory_order_relaxed);
-        // |accumulator| < 2^31, weights up to s^(levels of a row - 1 + levels of a column - 1)
-        g.fold_f64 = !C_int && 31 + p->sh * ((h.lmaxA - 1) + (h.lmaxB - 1)) <= 52;
+        g.fold_f64 = g.fold_f64 && !C_int;
         if (p->fp6) hipLaunchKernelGGL(gemm_f6_kernel<0>, dim3(grid), dim3(kGemmThreads), kGemmLds, st, g);
         else hipLaunchKernelGGL(gemm_i8_kernel<0>, dim3(grid), dim3(kGemmThreads), kGemmLds, st, g);
         IMU_TRY(launch_status());
@@ -841,12 +903,50 @@ int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *
         return recombine_impl(p, workspace, scale_A, scale_B, scale_a_dev, scale_b_dev, C_int, C_fp, ldc, st);
     return IMUNPACK_OK;
 }
+
+int gemm_batch(imunpack_plan_t *p, const int8_t *A_ue, int64_t a_stride, const int8_t *B_eu, int64_t b_stride, float *C_fp,
+               int64_t c_stride, int64_t ldc, const float *scale_a_dev, const float *scale_b_dev, int64_t scale_stride,
+               int32_t *refused, hipStream_t st) {
+    if (!p || !p->valid || !p->unpacked || !A_ue || !B_eu || !C_fp || ldc < p->h || !scale_a_dev || !scale_b_dev || !refused)
+        return IMUNPACK_EINVAL;
+    IMU_TRY(gemm_lds_opt_in());
+    int grid = 0;
+    for (int i = 0; i < p->nitems; ++i) {
+        const PlanHeader &h = p->pin_hdr[i];
+        const int maxexp = (h.lmaxA - 1) + (h.lmaxB - 1) + (h.ngroups ? h.grp_exp[0] : 0);
+        if (maxexp * p->sh > 62) return IMUNPACK_ERANGE;
+        grid = std::max(grid, h.mtiles * h.ntiles);
+    }
+    GemmArgs g;
+    memset(&g, 0, sizeof(g));
+    g.A = A_ue; g.B = B_eu;
+    g.C_fp = C_fp; g.ldc = ldc;
+    g.scale_a_dev = scale_a_dev; g.scale_b_dev = scale_b_dev;
+    g.refused = refused;
+    if (p->nitems == 1 && p->pin_hdr[0].nruns <= 63) {  // a batch of one: the one-product kernel, its tables in the launch
+        fused_args(g, p);
+        g.guard = p->d_hdr->bound;
+        if (p->fp6) hipLaunchKernelGGL(gemm_f6_kernel<0>, dim3(grid), dim3(kGemmThreads), kGemmLds, st, g);
+        else hipLaunchKernelGGL(gemm_i8_kernel<0>, dim3(grid), dim3(kGemmThreads), kGemmLds, st, g);
+        return launch_status();
+    }
+    g.layA = p->layA; g.layB = p->layB;
+    g.sh = p->sh;
+    g.guard_mul = p->s - 1;
+    g.hdr = p->d_hdr;
+    g.a_stride = a_stride; g.b_stride = b_stride; g.c_stride = c_stride; g.plan_stride = p->item_bytes;
+    g.scale_stride = scale_stride;
+    const dim3 blocks((unsigned)grid, (unsigned)p->nitems);
+    if (p->fp6) hipLaunchKernelGGL(gemm_batch_kernel<true>, blocks, dim3(kGemmThreads), kGemmLds, st, g);
+    else hipLaunchKernelGGL(gemm_batch_kernel<false>, blocks, dim3(kGemmThreads), kGemmLds, st, g);
+    return launch_status();
+}
 }  // namespace imu
 
 extern "C" int imunpack_gemm(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu,
                              void *workspace, int64_t *C_int, float *C_fp, int64_t ldc, float scale_A,
                              float scale_B, int fuse, imunpack_stream_t stream) {
-    return gemm_impl(p, A_ue, B_eu, workspace, C_int, C_fp, ldc, scale_A, scale_B, nullptr, nullptr, fuse, stream);
+    return gemm_impl(p, A_ue, B_eu, workspace, C_int, C_fp, ldc, scale_A, scale_B, nullptr, nullptr, fuse, (hipStream_t)stream);
 }
 
 extern "C" int imunpack_diag_clock_probe(uint64_t *ticks) {

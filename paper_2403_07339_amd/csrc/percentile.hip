@@ -35,7 +35,10 @@ __device__ __forceinline__ SelState *sel_state(void *ws) {
     return reinterpret_cast<SelState *>(reinterpret_cast<unsigned *>(ws) + kSelBins);
 }
 
-__global__ void select_init_kernel(void *ws, unsigned long long k, int32_t *status) {
+// blockIdx.y is the item of a batch in every kernel here: its matrix lies x_stride bytes behind that of the item
+// before, its workspace and its result out_stride bytes.
+__global__ void select_init_kernel(void *ws, unsigned long long k, int32_t *status, int64_t out_stride) {
+    ws = item_at(ws, blockIdx.y * out_stride);
     unsigned *hist = sel_hist(ws);
     for (int i = threadIdx.x; i < kSelBins; i += blockDim.x) hist[i] = 0;
     if (threadIdx.x == 0) {
@@ -51,10 +54,13 @@ __global__ void select_init_kernel(void *ws, unsigned long long k, int32_t *stat
 // The matrix as nslow lines of nfast entries: entry (l, f) at X[l * stride_slow + f * stride_fast].
 // VEC: stride_fast == 1, nfast % 4 == 0, lines 16-byte aligned.
 template <bool VEC>
-__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *__restrict__ X, int64_t nslow,
+__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *X, int64_t nslow,
                                                                    int64_t nfast, int64_t stride_slow,
                                                                    int64_t stride_fast, void *ws, int shift,
-                                                                   int nbins, int32_t *status) {
+                                                                   int nbins, int32_t *status, int64_t x_stride,
+                                                                   int64_t out_stride) {
+    X = item_at(X, blockIdx.y * x_stride);
+    ws = item_at(ws, blockIdx.y * out_stride);
     __shared__ unsigned lh[kSelBins];
     for (int i = threadIdx.x; i < nbins; i += kSelThreads) lh[i] = 0;
     __syncthreads();
@@ -121,14 +127,18 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *
 // alpha_p / (0.5 beta), formed once in binary32.  A matrix whose p-th percentile is 0 (mostly zeros)
 // falls back to its largest magnitude, an all-zero (or non-finite) one to 1.  *step holds alpha_p on
 // entry (the selection's last pass wrote it there) and the step on exit.
-__global__ void rtn_step_kernel(void *ws, float half_beta, float *step) {
+__global__ void rtn_step_kernel(void *ws, float half_beta, float *step, int64_t out_stride) {
+    ws = item_at(ws, blockIdx.y * out_stride);
+    step = item_at(step, blockIdx.y * out_stride);
     float a = *step;
     if (!(a > 0.0f)) a = __uint_as_float(sel_state(ws)->maxbits);
     *step = (a > 0.0f && a < __uint_as_float(0x7f800000u)) ? __fdiv_rn(a, half_beta) : 1.0f;
 }
 
 // One workgroup: the bin whose cumulative count reaches k becomes the next digit.
-__global__ __launch_bounds__(1024) void select_pick_kernel(void *ws, int shift, int nbins, float *alpha) {
+__global__ __launch_bounds__(1024) void select_pick_kernel(void *ws, int shift, int nbins, float *alpha, int64_t out_stride) {
+    ws = item_at(ws, blockIdx.y * out_stride);
+    alpha = item_at(alpha, blockIdx.y * out_stride);
     __shared__ unsigned long long part[1024];
     __shared__ int s_bin;
     __shared__ unsigned long long s_below;
@@ -181,7 +191,8 @@ __global__ __launch_bounds__(1024) void select_pick_kernel(void *ws, int shift, 
 using namespace imu;
 
 static int run_percentile(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p,
-                          float *alpha, int32_t *status_flag, void *workspace, hipStream_t st) {
+                          float *alpha, int32_t *status_flag, void *workspace, int nitems, int64_t x_stride,
+                          int64_t out_stride, int32_t *flag, hipStream_t st) {
     static_assert(IMUNPACK_PERCENTILE_WORKSPACE_BYTES >= kSelBins * sizeof(unsigned) + sizeof(SelState), "workspace");
     const int64_t N = rows * cols;
     double kd = std::ceil(p * (double)N / 100.0);
@@ -191,22 +202,27 @@ static int run_percentile(const float *X, int64_t rows, int64_t cols, int64_t sx
     // the unit-stride axis, if there is one, runs fastest
     int64_t nslow = rows, nfast = cols, sslow = sx_r, sfast = sx_c;
     if (sx_c != 1 && sx_r == 1) { nslow = cols; nfast = rows; sslow = sx_c; sfast = 1; }
-    const bool vec = sfast == 1 && (nfast % 4) == 0 && (sslow % 4) == 0 && ((uintptr_t)X % 16) == 0;
+    const bool vec = sfast == 1 && (nfast % 4) == 0 && (sslow % 4) == 0 && ((uintptr_t)X % 16) == 0 && (x_stride % 16) == 0;
     const int64_t items = nslow * (vec ? nfast / 4 : nfast);
     int64_t blocks = (items + (int64_t)kSelThreads * kSelItems - 1) / ((int64_t)kSelThreads * kSelItems);
     if (blocks > 1024) blocks = 1024;  // four per CU: every workgroup merges its histogram with atomics on the same few counters
     if (blocks < 1) blocks = 1;
     // the init kernel clears the counters and the state: whatever an earlier call left in the workspace is gone
-    hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(256), 0, st, workspace, k, status_flag);
+    hipLaunchKernelGGL(select_init_kernel, dim3(1, nitems), dim3(256), 0, st, workspace, k, flag ? nullptr : status_flag,
+                       out_stride);
+    if (flag) status_flag = flag;  // a batch ORs what goes wrong into one flag that its caller has cleared
     const int shifts[3] = {20, 10, 0}, bins[3] = {2048, 1024, 1024};
     for (int pass = 0; pass < 3; ++pass) {
         if (vec)
-            hipLaunchKernelGGL(select_count_kernel<true>, dim3((unsigned)blocks), dim3(kSelThreads), 0, st, X, nslow, nfast,
-                               sslow, sfast, workspace, shifts[pass], bins[pass], pass == 0 ? status_flag : nullptr);
+            hipLaunchKernelGGL(select_count_kernel<true>, dim3((unsigned)blocks, nitems), dim3(kSelThreads), 0, st, X, nslow, nfast,
+                               sslow, sfast, workspace, shifts[pass], bins[pass], pass == 0 ? status_flag : nullptr,
+                               x_stride, out_stride);
         else
-            hipLaunchKernelGGL(select_count_kernel<false>, dim3((unsigned)blocks), dim3(kSelThreads), 0, st, X, nslow, nfast,
-                               sslow, sfast, workspace, shifts[pass], bins[pass], pass == 0 ? status_flag : nullptr);
-        hipLaunchKernelGGL(select_pick_kernel, dim3(1), dim3(1024), 0, st, workspace, shifts[pass], bins[pass], alpha);
+            hipLaunchKernelGGL(select_count_kernel<false>, dim3((unsigned)blocks, nitems), dim3(kSelThreads), 0, st, X, nslow, nfast,
+                               sslow, sfast, workspace, shifts[pass], bins[pass], pass == 0 ? status_flag : nullptr,
+                               x_stride, out_stride);
+        hipLaunchKernelGGL(select_pick_kernel, dim3(1, nitems), dim3(1024), 0, st, workspace, shifts[pass], bins[pass], alpha,
+                           out_stride);
     }
     return launch_status();
 }
@@ -217,19 +233,27 @@ extern "C" int imunpack_percentile(const float *X, int64_t rows, int64_t cols, i
     if (!X || !alpha || !workspace || rows <= 0 || cols <= 0 || sx_r < 1 || sx_c < 1 || !(p > 0.0) || !(p <= 100.0))
         return IMUNPACK_EINVAL;
     if (rows > (int64_t)1 << 31 || cols > (int64_t)1 << 31 || rows * cols >= (int64_t)1 << 32) return IMUNPACK_EINVAL;
-    return run_percentile(X, rows, cols, sx_r, sx_c, p, alpha, status_flag, workspace, (hipStream_t)stream);
+    return run_percentile(X, rows, cols, sx_r, sx_c, p, alpha, status_flag, workspace, 1, 0, 0, nullptr,
+                          (hipStream_t)stream);
+}
+
+// The steps of the items of a batch (see QuantBatch): X, and with it step and workspace, item by item.
+int imu::rtn_steps(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p, float beta,
+                   float *step, int32_t *status_flag, void *workspace, int nitems, int64_t x_stride, int64_t out_stride,
+                   int32_t *flag, hipStream_t st) {
+    if (!X || !step || !workspace || rows <= 0 || cols <= 0 || sx_r < 1 || sx_c < 1 || !(p > 0.0) || !(p <= 100.0) ||
+        !(beta > 0.0f) || !(beta < 3.0e38f))
+        return IMUNPACK_EINVAL;
+    if (rows > (int64_t)1 << 31 || cols > (int64_t)1 << 31 || rows * cols >= (int64_t)1 << 32) return IMUNPACK_EINVAL;
+    IMU_TRY(run_percentile(X, rows, cols, sx_r, sx_c, p, step, status_flag, workspace, nitems, x_stride, out_stride, flag, st));
+    hipLaunchKernelGGL(rtn_step_kernel, dim3(1, nitems), dim3(1), 0, st, workspace, (float)(0.5 * (double)beta), step, out_stride);
+    return launch_status();
 }
 
 extern "C" int imunpack_rtn_step(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p,
                                  float beta, float *step, int32_t *status_flag, void *workspace,
                                  imunpack_stream_t stream) {
-    if (!X || !step || !workspace || rows <= 0 || cols <= 0 || sx_r < 1 || sx_c < 1 || !(p > 0.0) || !(p <= 100.0) ||
-        !(beta > 0.0f) || !(beta < 3.0e38f))
-        return IMUNPACK_EINVAL;
-    if (rows > (int64_t)1 << 31 || cols > (int64_t)1 << 31 || rows * cols >= (int64_t)1 << 32) return IMUNPACK_EINVAL;
-    IMU_TRY(run_percentile(X, rows, cols, sx_r, sx_c, p, step, status_flag, workspace, (hipStream_t)stream));
-    hipLaunchKernelGGL(rtn_step_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, workspace, (float)(0.5 * (double)beta), step);
-    return launch_status();
+    return rtn_steps(X, rows, cols, sx_r, sx_c, p, beta, step, status_flag, workspace, 1, 0, 0, nullptr, (hipStream_t)stream);
 }
 
 // ---- the same selection for callers that cannot allocate ------------------------------------------
@@ -263,5 +287,5 @@ extern "C" int imunpack_percentile_static(const float *X, int64_t rows, int64_t 
         }
         ws = g_scratch_ptr[dev];
     }
-    return run_percentile(X, rows, cols, sx_r, sx_c, p, alpha, status_flag, ws, (hipStream_t)stream);
+    return run_percentile(X, rows, cols, sx_r, sx_c, p, alpha, status_flag, ws, 1, 0, 0, nullptr, (hipStream_t)stream);
 }

@@ -142,53 +142,76 @@ __device__ __forceinline__ void identity_slot(const SlotSet &set, int x) {
     set.child[x] = -1;
 }
 
-// Clears the header and makes the first na / nb / nc slots of three sets unsplit originals (a count
-// of 0 skips a set).  The counts are known to the host, which has sized the sets for them.
-__global__ void setup_kernel(PlanHeader *hdr, SlotSet a, int na, int32_t *count_a, SlotSet b, int nb,
-                             int32_t *count_b, SlotSet c, int nc, int32_t *count_c, int32_t *zeroed, int nzeroed,
-                             int32_t *zeroed2, int nzeroed2, KeepState *ks) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        if (ks) ks->diff = ks->same = 0;
+// Clears the header and makes the first na / nb / nc slots of three sets (row slots of A and of B, column
+// slots of A's unpacking) unsplit originals (a count of 0 skips a set).  The counts are known to the host,
+// which has sized the sets for them.  blockIdx.y is the item of the batch, as in every planner kernel.
+__global__ void setup_kernel(PlanHeader *hdr, SlotSet a, int na, SlotSet c, int nc, SlotSet b, int nb, int32_t *zeroed,
+                             int nzeroed, int32_t *zeroed2, int nzeroed2, KeepState *ks, int64_t stride) {
+    hdr += blockIdx.y;
+    const int64_t off = blockIdx.y * stride;
+    move_to_item(a, off);
+    move_to_item(b, off);
+    move_to_item(c, off);
+    zeroed = item_at(zeroed, off);
+    zeroed2 = item_at(zeroed2, off);
+    if (blockIdx.x == 0) {
         static_assert(sizeof(PlanHeader) % sizeof(int32_t) == 0, "header is cleared word by word");
-        for (size_t i = 0; i < sizeof(PlanHeader) / sizeof(int32_t); ++i) reinterpret_cast<int32_t *>(hdr)[i] = 0;
-        if (na) *count_a = na;
-        if (nb) *count_b = nb;
-        if (nc) *count_c = nc;
+        for (size_t i = threadIdx.x; i < sizeof(PlanHeader) / sizeof(int32_t); i += blockDim.x)
+            reinterpret_cast<int32_t *>(hdr)[i] = 0;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (ks) ks->diff = ks->same = 0;
+            if (na) hdr->n_u = na;
+            if (nb) hdr->h_u = nb;
+            if (nc) hdr->d1 = nc;
+        }
     }
-    const int stride = gridDim.x * blockDim.x;
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < na; x += stride) identity_slot(a, x);
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nb; x += stride) identity_slot(b, x);
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nc; x += stride) identity_slot(c, x);
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nzeroed; x += stride) zeroed[x] = 0;
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nzeroed2; x += stride) zeroed2[x] = 0;
+    const int step = gridDim.x * blockDim.x;
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < na; x += step) identity_slot(a, x);
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nb; x += step) identity_slot(b, x);
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nc; x += step) identity_slot(c, x);
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nzeroed; x += step) zeroed[x] = 0;
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nzeroed2; x += step) zeroed2[x] = 0;
 }
 
-// slots 0..N-1 become unsplit originals, N read from the device
-__global__ void identity_slots_kernel(SlotSet set, const int32_t *n_dev, int32_t *count_out, PlanHeader *hdr,
-                                      int which, const int32_t *skip) {
+// UnpackRow on the second operand splits no column: its column slots are those that A's unpacking left.
+__global__ void identity_slots_kernel(SlotSet set, PlanHeader *hdr, const int32_t *skip, int64_t stride) {
+    hdr += blockIdx.y;
+    move_to_item(set, blockIdx.y * stride);
     if (hdr->overflow) return;
     if (skip && *skip) return;  // keep-weights mode: this set is taken over as it stands
-    const int N = *n_dev;
+    const int N = hdr->d1;
     if (N > set.cap) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) flag_overflow(hdr, which, N);
+        if (blockIdx.x == 0 && threadIdx.x == 0) flag_overflow(hdr, CAP_C2, N);
         return;
     }
     for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < N; x += gridDim.x * blockDim.x) identity_slot(set, x);
-    if (count_out && blockIdx.x == 0 && threadIdx.x == 0) *count_out = N;
+    if (blockIdx.x == 0 && threadIdx.x == 0) hdr->d_u = N;
 }
 
 // ---------------------------------------------------------------------------------------------
 // UnpackRow / UnpackColumn in closed form (Alg. 1 / Alg. 2)
 // ---------------------------------------------------------------------------------------------
-// Base items x = 0..N-1 with largest magnitude maxabs[via ? via[x] : x]; every level l >= 1 appends
-// the items that still have a digit there, in ascending x.
+// Base items x = 0..N-1 with largest magnitude maxabs[via ? via[x] : x] (via: the columns that A's unpacking
+// left, N read from the header); every level l >= 1 appends the items that still have a digit there, in
+// ascending x.  `which` names the set.
 __global__ __launch_bounds__(kPlanThreads) void level_major_kernel(
-    SlotSet set, const int32_t *maxabs, const int32_t *via, int n_host, const int32_t *n_dev, int sh,
-    int32_t *tmpL, int32_t *tmpCur, int32_t *count_out, PlanHeader *hdr, int which, const int32_t *skip) {
+    SlotSet set, const int32_t *maxabs, const int32_t *via, int n_host, int sh, int32_t *tmpL, int32_t *tmpCur,
+    PlanHeader *hdr, int which, const int32_t *skip, int64_t stride, int64_t stats_stride) {
     __shared__ int lds[40];
+    hdr += blockIdx.y;
+    {
+        const int64_t off = blockIdx.y * stride;
+        move_to_item(set, off);
+        via = item_at(via, off);
+        tmpL = item_at(tmpL, off);
+        tmpCur = item_at(tmpCur, off);
+        maxabs = item_at(maxabs, blockIdx.y * stats_stride);
+    }
     if (hdr->overflow) return;
     if (skip && *skip) return;  // keep-weights mode: this set is taken over as it stands
-    const int N = n_dev ? *n_dev : n_host;
+    const int N = via ? hdr->d1 : n_host;
+    int32_t *count_out = which == CAP_ROWA ? &hdr->n_u : which == CAP_ROWB ? &hdr->h_u : which == CAP_C1 ? &hdr->d1 : &hdr->d_u;
     if (N > set.cap) {
         if (threadIdx.x == 0) flag_overflow(hdr, which, N);
         return;
@@ -231,23 +254,20 @@ __global__ __launch_bounds__(kPlanThreads) void level_major_kernel(
 // ---------------------------------------------------------------------------------------------
 struct GreedyArgs {
     SlotSet rows, cols;
-    const int32_t *cols_init;      // second operand: number of column slots to start from (columns after
-                                   // unpacking A), made unsplit originals here; nullptr for the first
+    int second;                    // second operand: starts from the column slots that unpacking A left, which are
+                                   // made unsplit originals here
     const int32_t *chain_child;    // second operand: child links of the column slots of A's unpacking
     const int32_t *chain_root;     // second operand: original column of each of those slots
     const int32_t *rowcnt, *colcnt, *rowmax;  // the operand's heavy-hitter statistics
-    const int32_t *ob;             // OB entries of the operand: [3][ob_cap] rows | columns | values
-    int ob_cap;
+    int ob_cap;                    // entries the OB list can hold
     const int32_t *ob_count;
     int which_list;
     unsigned long long *edges;     // two lists of ecap packed edges
     int ecap;
-    int32_t *ob_keep_count;        // header field: the number of OB entries kept for the scatter
     const int32_t *extra_rows;     // second operand: extra edges per row (repeated columns), else null
     int32_t *rcnt, *ccnt;          // live OB count per row / column slot when LDS cannot hold them
-    int32_t *nr_io, *nc_io;        // slot counts (header fields)
-    int32_t *ecount_out;
     PlanHeader *hdr;
+    int64_t stride, stats_stride, list_stride;  // from item to item: the plan's arrays, the statistics, the OB list
     int whichR, whichC, whichE;
     int s, sh;
     const int32_t *skip;           // keep-weights mode: non-zero there = nothing to do
@@ -294,21 +314,33 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g)
     __shared__ int s_found[kPlanWaves], s_positive[kPlanWaves];
     __shared__ int lds[40];
     __shared__ int s_count;
-    PlanHeader *hdr = g.hdr;
+    PlanHeader *hdr = g.hdr + blockIdx.y;
+    {
+        const int64_t off = blockIdx.y * g.stride, soff = blockIdx.y * g.stats_stride;
+        move_to_item(g.rows, off);
+        move_to_item(g.cols, off);
+        g.chain_child = item_at(g.chain_child, off);
+        g.chain_root = item_at(g.chain_root, off);
+        g.edges = item_at(g.edges, off);
+        g.extra_rows = item_at(g.extra_rows, off);
+        g.rcnt = item_at(g.rcnt, off);
+        g.ccnt = item_at(g.ccnt, off);
+        g.rowcnt = item_at(g.rowcnt, soff);
+        g.colcnt = item_at(g.colcnt, soff);
+        g.rowmax = item_at(g.rowmax, soff);
+        g.ob_count = item_at(g.ob_count, blockIdx.y * g.list_stride);
+    }
     if (hdr->overflow) return;
     if (g.skip && *g.skip) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const unsigned long long below = (1ull << lane) - 1ull;
-    int nr = *g.nr_io, nc;
-    if (g.cols_init) {
-        nc = *g.cols_init;
+    int nr = g.second ? hdr->h_u : hdr->n_u, nc = hdr->d1;
+    if (g.second) {
         if (nc > g.cols.cap) {
             if (threadIdx.x == 0) flag_overflow(hdr, g.whichC, nc);
             return;
         }
         for (int x = threadIdx.x; x < nc; x += kPlanThreads) identity_slot(g.cols, x);
-    } else {
-        nc = *g.nc_io;
     }
     const int nob = *g.ob_count;
     if (nob > g.ob_cap) {
@@ -342,8 +374,8 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g)
     const int extras = s_count;
     const long long Etotal = (long long)nob + extras;
     if (threadIdx.x == 0) {
-        *g.ecount_out = (int)min(Etotal, 2147483647ll);
-        *g.ob_keep_count = nob;
+        *(g.second ? &hdr->edgesB : &hdr->edgesA) = (int)min(Etotal, 2147483647ll);
+        *(g.second ? &hdr->nobB : &hdr->nobA) = nob;  // the OB entries kept for the scatter
     }
     if (Etotal > g.ecap) {
         if (threadIdx.x == 0) flag_overflow(hdr, g.whichE, (int)min(Etotal, 1ll << 30));
@@ -675,8 +707,8 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g)
         if (isrow) nr += nb; else nc += nb;
     }
     if (threadIdx.x == 0) {
-        *g.nr_io = nr;
-        *g.nc_io = nc;
+        *(g.second ? &hdr->h_u : &hdr->n_u) = nr;
+        *(g.second ? &hdr->d_u : &hdr->d1) = nc;
     }
 }
 
@@ -1024,16 +1056,8 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
             cols.colB_e[q] = 0;
             cols.col_sexp[q] = e;
         }
-        // k-tile table: shared levels walk their stored blocks, gathered k-tiles get blocks of their own
-        for (int a = 0; a < kMaxLevelsA; ++a) {
-            const int kb = kbase[e * kMaxLevelsA + a];
-            if (kb < 0) continue;
-            const int nt = (cntA[a] + kKPad - 1) / kKPad;
-            for (int j = threadIdx.x; j < nt; j += kPlanThreads) cols.ktile_ablk[kb / kKPad + j] = lvlbase[a] / kKPad + j;
-        }
         const int cbase = s_cbase[e], ccount = s_ccount[e], xcol0 = ka_levels + s_xbase[e] * kKPad;
         const int ctiles = (ccount + kKPad - 1) / kKPad;
-        for (int j = threadIdx.x; j < ctiles; j += kPlanThreads) cols.ktile_ablk[cbase / kKPad + j] = xcol0 / kKPad + j;
         for (int q = threadIdx.x; q < ctiles * kKPad; q += kPlanThreads) {
             cols.colA_k[xcol0 + q] = -1;
             cols.colA_e[xcol0 + q] = 0;
@@ -1215,9 +1239,27 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
 __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     SlotSet rowA, int n, RowLayout layA, int cap_physA, int32_t *tmpPA, SlotSet rowB, int h, RowLayout layB,
     int cap_physB, int32_t *tmpPB, SlotSet c1, SlotSet c2, ColLayout cols, int d, int cap_physC, int s, int sh,
-    int32_t *tmpE, int32_t *tmpK, int32_t *tmpR, int32_t *tmpOff, PlanHeader *hdr, int fast_lds, const int32_t *skipB) {
+    int32_t *tmpE, int32_t *tmpK, int32_t *tmpR, int32_t *tmpOff, PlanHeader *hdr, int fast_lds, const int32_t *skipB,
+    int64_t stride) {
     __shared__ int lds[40];
     extern __shared__ __attribute__((aligned(16))) int32_t fast_rows[];  // 2 * max(n, h) ints, if the launch gave them
+    hdr += blockIdx.y;
+    {
+        const int64_t off = blockIdx.y * stride;
+        move_to_item(rowA, off);
+        move_to_item(layA, off);
+        move_to_item(rowB, off);
+        move_to_item(layB, off);
+        move_to_item(c1, off);
+        move_to_item(c2, off);
+        move_to_item(cols, off);
+        tmpPA = item_at(tmpPA, off);
+        tmpPB = item_at(tmpPB, off);
+        tmpE = item_at(tmpE, off);
+        tmpK = item_at(tmpK, off);
+        tmpR = item_at(tmpR, off);
+        tmpOff = item_at(tmpOff, off);
+    }
     if (hdr->overflow) return;
     if (blockIdx.x >= 1 && skipB && *skipB) return;  // keep-weights mode: these layouts stand as they are
     // rows of A: the GEMM epilogue folds them chunk by chunk; rows of B (columns of C): tile by tile
@@ -1265,8 +1307,8 @@ __global__ void clear_sums_kernel(unsigned long long *p, int count) {
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
-int scan_i32(const int32_t *Q, int64_t rows, int64_t cols, int64_t ldq, int b,
-             const imunpack_stats_t *st, hipStream_t stream);
+int scan_i32(const int32_t *Q, int64_t rows, int64_t cols, int64_t ldq, int b, const imunpack_stats_t *st, int nitems,
+             int64_t q_stride, int64_t out_stride, hipStream_t stream);
 
 struct Carver {
     char *base;
@@ -1292,11 +1334,14 @@ static void carve_slots(Carver &cv, SlotSet &s, int cap) {
 static inline int phys_cap_rows(int cap) { return (int)((int64_t)cap * kChunk / (kChunk - 8) + 2 * kTile); }
 static inline int phys_cap_cols(int cap) { return cap + kMaxGroups * kKPad; }
 
-// Lays every device array out in the arena for the current capacities; returns the bytes needed.
+// Lays every device array out in the arena for the current capacities: the headers of all items, then the
+// arrays of item 0, those of item 1 (p->item_bytes further), and so on.  Returns the bytes needed.
 static size_t carve(Plan *p, char *base, bool own_statsA, bool own_statsB) {
     Carver cv{base, 0};
     const int n = (int)p->n, d = (int)p->d, h = (int)p->h;
-    p->d_hdr = cv.take<PlanHeader>(1);
+    p->d_hdr = cv.take<PlanHeader>(p->nitems);
+    cv.off = (cv.off + 255) & ~(size_t)255;
+    const size_t item0 = cv.off;
     carve_slots(cv, p->rowA, p->cap[CAP_ROWA]);
     carve_slots(cv, p->rowB, p->cap[CAP_ROWB]);
     carve_slots(cv, p->c1, p->cap[CAP_C1]);
@@ -1332,7 +1377,6 @@ static size_t carve(Plan *p, char *base, bool own_statsA, bool own_statsB) {
         p->cols.colA_w = cv.take<unsigned long long>(kc);
         p->cols.unitA = cv.take<int4>(kc / 16 + 1);
         p->cols.unitA_w = cv.take<unsigned long long>(kc / 16 + 1);
-        p->cols.ktile_ablk = cv.take<int32_t>(kc / kKPad + 1);
         p->tmpE = cv.take<int32_t>(p->cap[CAP_C2]);
         p->tmpK = cv.take<int32_t>(p->cap[CAP_C2]);
         p->tmpR = cv.take<int32_t>(p->cap[CAP_C2]);
@@ -1364,15 +1408,17 @@ static size_t carve(Plan *p, char *base, bool own_statsA, bool own_statsB) {
         p->edge_cap = ecap;
         const int rcap = std::max(p->cap[CAP_ROWA], p->cap[CAP_ROWB]), ccap = std::max(p->cap[CAP_C1], p->cap[CAP_C2]);
         p->rcnt = cv.take<int32_t>(rcap + 8);
-    p->extraRows = cv.take<int32_t>(p->sB == IMUNPACK_BOTH ? (size_t)h + 1 : 0);
+        p->extraRows = cv.take<int32_t>(p->sB == IMUNPACK_BOTH ? (size_t)h + 1 : 0);
         p->ccnt = cv.take<int32_t>(ccap + 8);
         p->ob = cv.take<int32_t>((size_t)3 * p->cap[CAP_OB]);
+        p->obcnt = cv.take<int32_t>(1);
     }
     p->snapRoot = cv.take<int32_t>(p->cap[CAP_C1]);
     p->snapExp = cv.take<int32_t>(p->cap[CAP_C1]);
     p->snapChild = cv.take<int32_t>(p->cap[CAP_C1]);
     p->d_keep = cv.take<KeepState>(1);
-    return cv.off + 256;
+    p->item_bytes = (int64_t)((cv.off - item0 + 255) & ~(size_t)255);
+    return item0 + (size_t)p->nitems * (size_t)p->item_bytes + 256;
 }
 
 static inline int grid_for(int64_t items, int threads, int maxblocks = 2048) {
@@ -1391,8 +1437,19 @@ static inline int grid_for(int64_t items, int threads, int maxblocks = 2048) {
 __global__ __launch_bounds__(256) void ob_copy_kernel(const int32_t *__restrict__ ob, int ob_cap,
                                                       const int32_t *ob_count, int32_t *__restrict__ keep, int keep_cap,
                                                       const int32_t *chain_child, unsigned long long *edges, int ecap,
-                                                      int32_t *extras, int32_t *extra_rows, int sh, const int32_t *skip) {
+                                                      PlanHeader *hdr, int32_t *extra_rows, int sh, const int32_t *skip,
+                                                      int64_t stride, int64_t list_stride) {
     if (skip && *skip) return;  // keep-weights mode: this operand's unpacking is taken over as it stands
+    {
+        const int64_t off = blockIdx.y * stride, loff = blockIdx.y * list_stride;
+        ob = item_at(ob, loff);
+        ob_count = item_at(ob_count, loff);
+        keep = item_at(keep, off);
+        chain_child = item_at(chain_child, off);
+        edges = item_at(edges, off);
+        extra_rows = item_at(extra_rows, off);
+    }
+    int32_t *extras = &hdr[blockIdx.y].extras;
     const int n = min(*ob_count, ob_cap);
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
         const int j = ob[t], k = ob[ob_cap + t], v = ob[2 * (size_t)ob_cap + t];
@@ -1487,7 +1544,7 @@ static constexpr int kGreedyLdsMax = 136 * 1024;  // dynamic LDS the greedy may 
 static constexpr int kLayoutLdsMax = 128 * 1024;  // dynamic LDS the layouts kernel may use (its static tables take about 12 KiB)
 
 // ob: the operand's OB entry list ([3][ob_cap], count on the device)
-static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const int32_t *ob_count,
+static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const int32_t *ob_count, int64_t list_stride,
                       int which_list, hipStream_t st, const int32_t *skip = nullptr) {
     PlanHeader *hdr = p->d_hdr;
     const bool first = phase == 1;
@@ -1495,20 +1552,17 @@ static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const i
     SlotSet &cols = first ? p->c1 : p->c2;
     GreedyArgs g;
     g.rows = rows; g.cols = cols;
-    g.cols_init = first ? nullptr : &hdr->d1;
+    g.second = !first;
     g.chain_child = first ? nullptr : p->c1.child;
     g.chain_root = first ? nullptr : p->c1.root;
     int32_t **stats = first ? p->statsA : p->statsB;
     g.rowcnt = stats[0]; g.colcnt = stats[1]; g.rowmax = stats[2];
-    g.ob = ob; g.ob_cap = ob_cap; g.ob_count = ob_count; g.which_list = which_list;
+    g.ob_cap = ob_cap; g.ob_count = ob_count; g.which_list = which_list;
+    g.stride = p->item_bytes; g.stats_stride = p->op_stride; g.list_stride = list_stride;
     g.edges = p->edges;
     g.ecap = std::min(p->cap[first ? CAP_EDGEA : CAP_EDGEB], p->edge_cap);
     g.rcnt = p->rcnt; g.ccnt = p->ccnt;
-    g.ob_keep_count = first ? &hdr->nobA : &hdr->nobB;
     g.extra_rows = first ? nullptr : p->extraRows;
-    g.nr_io = first ? &hdr->n_u : &hdr->h_u;
-    g.nc_io = first ? &hdr->d1 : &hdr->d_u;
-    g.ecount_out = first ? &hdr->edgesA : &hdr->edgesB;
     g.hdr = hdr;
     g.whichR = first ? CAP_ROWA : CAP_ROWB;
     g.whichC = first ? CAP_C1 : CAP_C2;
@@ -1523,13 +1577,14 @@ static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const i
         opted_in.store(1, std::memory_order_release);
     }
     const int keep_cap = p->cap[first ? CAP_EDGEA : CAP_EDGEB];  // the stride the fix-up pass reads with
-    hipLaunchKernelGGL(ob_copy_kernel, dim3(grid_for(ob_cap, 256, 128)), dim3(256), 0, st, ob, ob_cap, ob_count,
+    const unsigned items = (unsigned)p->nitems;
+    hipLaunchKernelGGL(ob_copy_kernel, dim3(grid_for(ob_cap, 256, 128), items), dim3(256), 0, st, ob, ob_cap, ob_count,
                        first ? p->obcopyA : p->obcopyB, keep_cap, (const int32_t *)g.chain_child, g.edges, g.ecap,
-                       &hdr->extras, p->extraRows, p->sh, skip);
+                       hdr, p->extraRows, p->sh, skip, p->item_bytes, list_stride);
     if (lds_bytes <= (size_t)kGreedyLdsMax)
-        hipLaunchKernelGGL(greedy_both_kernel<true>, dim3(1), dim3(kPlanThreads), lds_bytes, st, g);
+        hipLaunchKernelGGL(greedy_both_kernel<true>, dim3(1, items), dim3(kPlanThreads), lds_bytes, st, g);
     else
-        hipLaunchKernelGGL(greedy_both_kernel<false>, dim3(1), dim3(kPlanThreads), 0, st, g);
+        hipLaunchKernelGGL(greedy_both_kernel<false>, dim3(1, items), dim3(kPlanThreads), 0, st, g);
     return launch_status();
 }
 
@@ -1547,10 +1602,12 @@ static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B
     // keep-weights mode (UnpackBoth on the second operand): its rows are set up only once it is known that its
     // unpacking has to be redone
     const bool keep = p->keep_B != 0;
-    hipLaunchKernelGGL(setup_kernel, dim3(grid_for(std::max(std::max(idA, idC1), std::max(idB, kcA)), 256, 64)),
-                       dim3(256), 0, st, hdr, p->rowA, idA, &hdr->n_u, p->c1, idC1, &hdr->d1, p->rowB, keep ? 0 : idB,
-                       &hdr->h_u, p->extraRows, (p->sB == IMUNPACK_BOTH && !keep) ? h : 0,
-                       reinterpret_cast<int32_t *>(p->cols.colA_w), keep ? 0 : 2 * kcA, keep ? p->d_keep : nullptr);
+    const unsigned items = (unsigned)p->nitems;
+    const int64_t stride = p->item_bytes, sstride = p->op_stride;
+    hipLaunchKernelGGL(setup_kernel, dim3(grid_for(std::max(std::max(idA, idC1), std::max(idB, kcA)), 256, 64), items),
+                       dim3(256), 0, st, hdr, p->rowA, idA, p->c1, idC1, p->rowB, keep ? 0 : idB,
+                       p->extraRows, (p->sB == IMUNPACK_BOTH && !keep) ? h : 0,
+                       reinterpret_cast<int32_t *>(p->cols.colA_w), keep ? 0 : 2 * kcA, keep ? p->d_keep : nullptr, stride);
     // OB entry lists for UnpackBoth: the caller's (from the fused quantize pass) if complete, else
     // this call's own scan produces one.  The two operands are planned one after the other, so one
     // own buffer serves both.
@@ -1559,26 +1616,24 @@ static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B
     const bool callerB = listB && stB && stB->ob && stB->ob_count && stB->ob_cap > 0 && !p->ignore_listB;
     const bool scanA = own_statsA || (listA && !callerA), scanB = own_statsB || (listB && !callerB);
     auto scan_operand = [&](const int32_t *M, int rows, int64_t ld, int32_t **own, bool own_stats, bool list) {
+        if (items > 1 && own_stats) return (int)IMUNPACK_EINVAL;  // a batch brings its statistics
         imunpack_stats_t sx;
         memset(&sx, 0, sizeof(sx));
         if (own_stats) { sx.rowcnt = own[0]; sx.colcnt = own[1]; sx.rowmax = own[2]; sx.colmax = own[3]; }
-        if (list) { sx.ob = p->ob; sx.ob_cap = p->cap[CAP_OB]; sx.ob_count = &hdr->obcount; }
-        return scan_i32(M, rows, d, ld, p->b, &sx, st);
+        if (list) { sx.ob = p->ob; sx.ob_cap = p->cap[CAP_OB]; sx.ob_count = p->obcnt; }
+        return scan_i32(M, rows, d, ld, p->b, &sx, p->nitems, sstride, stride, st);
     };
     if (scanA) IMU_TRY(scan_operand(A, n, lda, p->statsA, own_statsA, listA && !callerA));
     // ---- phase 1: Unpack(A, B, I, b, strategy_A)
-    if (p->sA == IMUNPACK_ROW) {
-        hipLaunchKernelGGL(level_major_kernel, dim3(1), dim3(kPlanThreads), 0, st, p->rowA, p->statsA[2],
-                           (const int32_t *)nullptr, n, (const int32_t *)nullptr, p->sh, p->tmpL, p->tmpCur,
-                           &hdr->n_u, hdr, (int)CAP_ROWA, (const int32_t *)nullptr);
-    } else if (p->sA == IMUNPACK_COL) {
-        hipLaunchKernelGGL(level_major_kernel, dim3(1), dim3(kPlanThreads), 0, st, p->c1, p->statsA[3],
-                           (const int32_t *)nullptr, d, (const int32_t *)nullptr, p->sh, p->tmpL, p->tmpCur,
-                           &hdr->d1, hdr, (int)CAP_C1, (const int32_t *)nullptr);
-    } else {
-        if (callerA) IMU_TRY(run_greedy(p, 1, stA->ob, (int)stA->ob_cap, stA->ob_count, CAP_LISTA, st));
-        else IMU_TRY(run_greedy(p, 1, p->ob, p->cap[CAP_OB], &hdr->obcount, CAP_OB, st));
-    }
+    auto closed_form = [&](const SlotSet &set, const int32_t *maxabs, const int32_t *via, int count, int which,
+                           const int32_t *skip) {
+        hipLaunchKernelGGL(level_major_kernel, dim3(1, items), dim3(kPlanThreads), 0, st, set, maxabs, via, count, p->sh,
+                           p->tmpL, p->tmpCur, hdr, which, skip, stride, sstride);
+    };
+    if (p->sA == IMUNPACK_ROW) closed_form(p->rowA, p->statsA[2], nullptr, n, CAP_ROWA, nullptr);
+    else if (p->sA == IMUNPACK_COL) closed_form(p->c1, p->statsA[3], nullptr, d, CAP_C1, nullptr);
+    else if (callerA) IMU_TRY(run_greedy(p, 1, stA->ob, (int)stA->ob_cap, stA->ob_count, sstride, CAP_LISTA, st));
+    else IMU_TRY(run_greedy(p, 1, p->ob, p->cap[CAP_OB], p->obcnt, stride, CAP_OB, st));
     if (scanB) IMU_TRY(scan_operand(B, h, ldb, p->statsB, own_statsB, listB && !callerB));
     // ---- phase 2: Unpack(B_e, A_u, S_u, b, strategy_B); B_e has d1 columns
     const int32_t *skip = nullptr;
@@ -1590,18 +1645,15 @@ static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B
         skip = &p->d_keep->same;
     }
     if (p->sB == IMUNPACK_ROW) {
-        hipLaunchKernelGGL(level_major_kernel, dim3(1), dim3(kPlanThreads), 0, st, p->rowB, p->statsB[2],
-                           (const int32_t *)nullptr, h, (const int32_t *)nullptr, p->sh, p->tmpL, p->tmpCur,
-                           &hdr->h_u, hdr, (int)CAP_ROWB, skip);
-        hipLaunchKernelGGL(identity_slots_kernel, dim3(grid_for(p->cap[CAP_C2], 256, 64)), dim3(256), 0, st,
-                           p->c2, (const int32_t *)&hdr->d1, &hdr->d_u, hdr, (int)CAP_C2, skip);
+        closed_form(p->rowB, p->statsB[2], nullptr, h, CAP_ROWB, skip);
+        hipLaunchKernelGGL(identity_slots_kernel, dim3(grid_for(p->cap[CAP_C2], 256, 64), items), dim3(256), 0, st,
+                           p->c2, hdr, skip, stride);
     } else if (p->sB == IMUNPACK_COL) {
-        hipLaunchKernelGGL(level_major_kernel, dim3(1), dim3(kPlanThreads), 0, st, p->c2, p->statsB[3],
-                           (const int32_t *)p->c1.root, 0, (const int32_t *)&hdr->d1, p->sh, p->tmpL,
-                           p->tmpCur, &hdr->d_u, hdr, (int)CAP_C2, skip);
+        closed_form(p->c2, p->statsB[3], p->c1.root, 0, CAP_C2, skip);
+    } else if (callerB) {
+        IMU_TRY(run_greedy(p, 2, stB->ob, (int)stB->ob_cap, stB->ob_count, sstride, CAP_LISTB, st, skip));
     } else {
-        if (callerB) IMU_TRY(run_greedy(p, 2, stB->ob, (int)stB->ob_cap, stB->ob_count, CAP_LISTB, st, skip));
-        else IMU_TRY(run_greedy(p, 2, p->ob, p->cap[CAP_OB], &hdr->obcount, CAP_OB, st, skip));
+        IMU_TRY(run_greedy(p, 2, p->ob, p->cap[CAP_OB], p->obcnt, stride, CAP_OB, st, skip));
     }
     // ---- physical layouts
     // the row layouts keep two ints per source row in LDS when that fits beside the column layout's tables
@@ -1612,15 +1664,22 @@ static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B
         IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
         layouts_opted_in.store(1, std::memory_order_release);
     }
-    hipLaunchKernelGGL(layouts_kernel, dim3(2 + kColBlocks), dim3(kPlanThreads), fast_lds ? fast_bytes : 0, st, p->rowA, n, p->layA,
+    hipLaunchKernelGGL(layouts_kernel, dim3(2 + kColBlocks, items), dim3(kPlanThreads), fast_lds ? fast_bytes : 0, st, p->rowA, n, p->layA,
                        phys_cap_rows(p->cap[CAP_ROWA]), p->tmpPA, p->rowB, h, p->layB,
                        phys_cap_rows(p->cap[CAP_ROWB]), p->tmpPB, p->c1, p->c2, p->cols, d,
                        phys_cap_cols(p->cap[CAP_C2]), p->s, p->sh, p->tmpE, p->tmpK, p->tmpR, p->tmpOff, hdr, fast_lds,
-                       keep ? (const int32_t *)&p->d_keep->same : (const int32_t *)nullptr);
+                       keep ? (const int32_t *)&p->d_keep->same : (const int32_t *)nullptr, stride);
     if (keep)
         hipLaunchKernelGGL(keep_remember_kernel, dim3(grid_for(p->cap[CAP_C1], 256, 16)), dim3(256), 0, st, p->c1,
                            (const PlanHeader *)hdr, p->snapRoot, p->snapExp, p->snapChild, p->d_keep);
     return launch_status();
+}
+
+static void destroy_handles(Plan *p) {
+    if (p->side) (void)hipStreamDestroy(p->side);
+    if (p->scattered) (void)hipEventDestroy(p->scattered);
+    if (p->ready) (void)hipEventDestroy(p->ready);
+    if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
 }
 
 int poll_ready(Plan *p) {
@@ -1638,56 +1697,49 @@ int poll_ready(Plan *p) {
     return IMUNPACK_OK;
 }
 
-int fetch_header(Plan *p, size_t offset, size_t bytes, hipStream_t st) {
-    if (!p->pin_hdr || offset + bytes > sizeof(PlanHeader)) return IMUNPACK_EINVAL;
-    char *pin = reinterpret_cast<char *>(p->pin_hdr) + offset;
-    IMU_HIP(hipMemcpyAsync(pin, reinterpret_cast<const char *>(p->d_hdr) + offset, bytes, hipMemcpyDeviceToHost, st));
+int fetch_headers(Plan *p, hipStream_t st) {
+    IMU_HIP(hipMemcpyAsync(p->pin_hdr, p->d_hdr, (size_t)p->nitems * sizeof(PlanHeader), hipMemcpyDeviceToHost, st));
     IMU_HIP(hipEventRecord(p->ready, st));
     IMU_TRY(poll_ready(p));
-    memcpy(reinterpret_cast<char *>(&p->hdr) + offset, pin, bytes);
+    p->hdr = p->pin_hdr[0];
     return IMUNPACK_OK;
 }
 
-}  // namespace imu
-
-using namespace imu;
-
-extern "C" int imunpack_plan(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t *B,
-                             int64_t h, int64_t ldb, int b, int strategy_A, int strategy_B,
-                             const imunpack_stats_t *stats_A, const imunpack_stats_t *stats_B,
-                             imunpack_plan_t **plan, imunpack_stream_t stream) {
-    if (!A || !B || !plan || n <= 0 || d <= 0 || h <= 0 || lda < d || ldb < d || b < 2 || b > 8)
+// The plan of one product (nitems = 1), or of every product of a batch of one shape: A, B, the statistics and
+// the OB lists of item i lie i * op_stride bytes behind those of item 0.
+int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t *B, int64_t h, int64_t ldb, int b,
+              int strategy_A, int strategy_B, const imunpack_stats_t *stats_A, const imunpack_stats_t *stats_B,
+              imunpack_plan_t **plan, int nitems, int64_t op_stride, hipStream_t st) {
+    if (!A || !B || !plan || n <= 0 || d <= 0 || h <= 0 || lda < d || ldb < d || b < 2 || b > 8 || nitems < 1 ||
+        nitems > kMaxItems)
         return IMUNPACK_EINVAL;
     if (strategy_A < 0 || strategy_A > 2 || strategy_B < 0 || strategy_B > 2) return IMUNPACK_EINVAL;
     if (n > (1 << 24) || d > (1 << 24) || h > (1 << 24)) return IMUNPACK_EINVAL;
-    hipStream_t st = (hipStream_t)stream;
     Plan *p = *plan;
     if (!p) {
         p = new (std::nothrow) Plan();
         if (!p) return IMUNPACK_ENOMEM;
         memset(p, 0, sizeof(*p));
-        if (hipHostMalloc((void **)&p->pin_hdr, sizeof(PlanHeader), hipHostMallocDefault) != hipSuccess ||
-            hipEventCreateWithFlags(&p->ready, hipEventDisableTiming) != hipSuccess ||
+        if (hipEventCreateWithFlags(&p->ready, hipEventDisableTiming) != hipSuccess ||
             hipEventCreateWithFlags(&p->scattered, hipEventDisableTiming) != hipSuccess ||
             hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking) != hipSuccess) {
             (void)hipGetLastError();
-            if (p->side) (void)hipStreamDestroy(p->side);
-            if (p->scattered) (void)hipEventDestroy(p->scattered);
-            if (p->ready) (void)hipEventDestroy(p->ready);
-            if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
+            destroy_handles(p);
             delete p;
             return IMUNPACK_ENOMEM;
         }
         p->guess_fusable = 1;
     }
     if (p->bound_pending) (void)resolve_bound(p);  // a copy into the header mirror is still in flight
-    const bool same = p->valid && p->n == n && p->d == d && p->h == h && p->b == b && p->sA == strategy_A &&
+    const bool same = p->valid && p->nitems == nitems && p->n == n && p->d == d && p->h == h && p->b == b && p->sA == strategy_A &&
                       p->sB == strategy_B;
     p->valid = 0;
     p->unpacked = 0;
     p->n = n; p->d = d; p->h = h; p->b = b; p->sA = strategy_A; p->sB = strategy_B;
     p->s = 1 << (b - 1); p->sh = b - 1;
     p->stream = st;
+    p->nitems = nitems;
+    p->op_stride = op_stride;
     if (!same) {
         // first guesses; every one of them is grown after a run that reports it too small
         p->cap[CAP_ROWA] = std::max(p->cap[CAP_ROWA], (int)(strategy_A == IMUNPACK_COL ? n : 2 * n + 256));
@@ -1702,7 +1754,19 @@ extern "C" int imunpack_plan(const int32_t *A, int64_t n, int64_t d, int64_t lda
     const bool ownA = !(stats_A && stats_A->rowcnt && stats_A->colcnt && stats_A->rowmax && stats_A->colmax);
     const bool ownB = !(stats_B && stats_B->rowcnt && stats_B->colcnt && stats_B->rowmax && stats_B->colmax);
     int rc = IMUNPACK_OK;
-    for (int attempt = 0; attempt < 24; ++attempt) {
+    if (p->pin_items < nitems) {  // the pinned copy of the headers
+        if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
+        p->pin_hdr = nullptr;
+        p->pin_items = 0;
+        if (hipHostMalloc((void **)&p->pin_hdr, (size_t)nitems * sizeof(PlanHeader), hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            p->pin_hdr = nullptr;
+            rc = IMUNPACK_ENOMEM;
+        } else {
+            p->pin_items = nitems;
+        }
+    }
+    for (int attempt = 0; rc == IMUNPACK_OK && attempt < 24; ++attempt) {
         const size_t need = carve(p, nullptr, ownA, ownB);
         if (need > p->arena_bytes) {
             if (p->arena) {
@@ -1729,10 +1793,18 @@ extern "C" int imunpack_plan(const int32_t *A, int64_t n, int64_t d, int64_t lda
         if (!ownB) { p->statsB[0] = stats_B->rowcnt; p->statsB[1] = stats_B->colcnt; p->statsB[2] = stats_B->rowmax; p->statsB[3] = stats_B->colmax; }
         rc = enqueue_plan(p, A, lda, B, ldb, stats_A, stats_B, ownA, ownB, st);
         if (rc != IMUNPACK_OK) break;
-        rc = fetch_header(p, 0, sizeof(PlanHeader), st);
+        rc = fetch_headers(p, st);
         if (rc != IMUNPACK_OK) break;
-        if (p->hdr.err) { rc = p->hdr.err; p->keep_valid = 0; break; }
-        if (!p->hdr.overflow) {
+        int err = 0, overflow = 0, needed[10] = {};
+        for (int i = 0; i < nitems; ++i) {
+            const PlanHeader &hi = p->pin_hdr[i];
+            err = std::min(err, (int)hi.err);
+            overflow |= hi.overflow;
+            for (int c = 0; c <= CAP_OB; ++c)
+                if (hi.overflow & (1 << c)) needed[c] = std::max(needed[c], (int)hi.need[c]);
+        }
+        if (err) { rc = err; p->keep_valid = 0; break; }
+        if (!overflow) {
             p->valid = 1;
             p->canon_valid = 0;
             p->keep_valid = p->keep_B;
@@ -1743,30 +1815,56 @@ extern "C" int imunpack_plan(const int32_t *A, int64_t n, int64_t d, int64_t lda
             break;
         }
         p->keep_valid = 0;
-        if (p->hdr.overflow & (1 << CAP_LISTA)) p->ignore_listA = 1;
-        if (p->hdr.overflow & (1 << CAP_LISTB)) p->ignore_listB = 1;
+        if (overflow & (1 << CAP_LISTA)) p->ignore_listA = 1;
+        if (overflow & (1 << CAP_LISTB)) p->ignore_listB = 1;
         for (int c = 0; c <= CAP_OB; ++c)
-            if (p->hdr.overflow & (1 << c)) {
-                int64_t nv = std::max<int64_t>((int64_t)p->hdr.need[c] + p->hdr.need[c] / 8 + 256, (int64_t)p->cap[c] * 2);
+            if (overflow & (1 << c)) {
+                int64_t nv = std::max<int64_t>((int64_t)needed[c] + needed[c] / 8 + 256, (int64_t)p->cap[c] * 2);
                 if (nv > (1ll << 30)) { rc = IMUNPACK_ENOMEM; break; }
                 p->cap[c] = (int)nv;
             }
-        if (rc != IMUNPACK_OK) break;
-        rc = IMUNPACK_ENOMEM;  // stays if the attempts run out
     }
+    if (rc == IMUNPACK_OK && !p->valid) rc = IMUNPACK_ENOMEM;  // the attempts ran out
     if (rc != IMUNPACK_OK && !p->valid) {
         if (!*plan) {
             if (p->arena) (void)hipFree(p->arena);
-            (void)hipStreamDestroy(p->side);
-            (void)hipEventDestroy(p->scattered);
-            (void)hipEventDestroy(p->ready);
-            (void)hipHostFree(p->pin_hdr);
+            destroy_handles(p);
             delete p;
         }
         return rc;
     }
     *plan = p;
     return IMUNPACK_OK;
+}
+
+// Item i of a batch's plan as a plan of its own: a copy that borrows the arena (never destroyed).
+Plan item_view(const Plan &batch, int i) {
+    Plan v = batch;
+    const int64_t off = (int64_t)i * batch.item_bytes;
+    v.nitems = 1;
+    v.d_hdr += i;
+    v.hdr = batch.pin_hdr[i];
+    v.pin_hdr = batch.pin_hdr + i;
+    move_to_item(v.rowA, off);
+    move_to_item(v.rowB, off);
+    move_to_item(v.c1, off);
+    move_to_item(v.c2, off);
+    move_to_item(v.layA, off);
+    move_to_item(v.layB, off);
+    move_to_item(v.cols, off);
+    v.bound_pending = 0;
+    return v;
+}
+
+}  // namespace imu
+
+using namespace imu;
+
+extern "C" int imunpack_plan(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t *B,
+                             int64_t h, int64_t ldb, int b, int strategy_A, int strategy_B,
+                             const imunpack_stats_t *stats_A, const imunpack_stats_t *stats_B,
+                             imunpack_plan_t **plan, imunpack_stream_t stream) {
+    return plan_impl(A, n, d, lda, B, h, ldb, b, strategy_A, strategy_B, stats_A, stats_B, plan, 1, 0, (hipStream_t)stream);
 }
 
 extern "C" int imunpack_plan_dims(const imunpack_plan_t *p, int64_t *n_u, int64_t *d_u, int64_t *h_u,
@@ -1970,10 +2068,7 @@ extern "C" int imunpack_plan_destroy(imunpack_plan_t *p) {
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = IMUNPACK_EHIP; }
     }
     if (p->bound_pending) (void)resolve_bound(p);
-    if (p->side) (void)hipStreamDestroy(p->side);
-    if (p->scattered) (void)hipEventDestroy(p->scattered);
-    if (p->ready) (void)hipEventDestroy(p->ready);
-    if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
+    destroy_handles(p);
     delete p;
     return rc;
 }

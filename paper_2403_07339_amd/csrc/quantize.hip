@@ -121,7 +121,17 @@ struct VecOperand {
     int32_t *ob_count;
     int rows_per_wg;
     int row_blocks;  // workgroups along the rows
+    // from item to item of a batch (blockIdx.z), in bytes: the input, and everything else but `status`
+    int64_t x_stride, out_stride;
 };
+
+template <class... P>
+__device__ __forceinline__ void to_item(int64_t off, P *&...p) { ((p = item_at(p, off)), ...); }
+
+__device__ __forceinline__ void move_to_item(VecOperand &a) {
+    a.X = item_at(a.X, blockIdx.z * a.x_stride);
+    to_item(blockIdx.z * a.out_stride, a.scale_ptr, a.Q, a.rowcnt, a.colcnt, a.rowmax, a.colmax, a.ob, a.ob_count);
+}
 
 template <bool FROM_FLOAT>
 __device__ __forceinline__ void qscan_vec_body(const VecOperand &a, int64_t cols, int s, int by, int *lds, ObStage &stage) {
@@ -210,6 +220,7 @@ template <bool FROM_FLOAT>
 __global__ __launch_bounds__(256) void qscan_vec_kernel(VecOperand a, int64_t cols, int s) {
     __shared__ int lds[2 * 4 * 256];
     __shared__ ObStage stage;
+    move_to_item(a);
     qscan_vec_body<FROM_FLOAT>(a, cols, s, blockIdx.y, lds, stage);
 }
 
@@ -219,21 +230,28 @@ __global__ __launch_bounds__(256) void qscan_vec_pair_kernel(VecOperand a, VecOp
     __shared__ int lds[2 * 4 * 256];
     __shared__ ObStage stage;
     const int by = blockIdx.y;
-    if (by < a.row_blocks) qscan_vec_body<true>(a, cols, s, by, lds, stage);
-    else qscan_vec_body<true>(b, cols, s, by - a.row_blocks, lds, stage);
+    if (by < a.row_blocks) {
+        move_to_item(a);
+        qscan_vec_body<true>(a, cols, s, by, lds, stage);
+    } else {
+        move_to_item(b);
+        qscan_vec_body<true>(b, cols, s, by - a.row_blocks, lds, stage);
+    }
 }
 
 // General path: any strides.  Workgroup = 64 x 64 tile staged through LDS so that reads follow the
 // input's unit-stride axis (if it has one) and writes follow the rows of Q.
 template <bool FROM_FLOAT>
-__global__ __launch_bounds__(256) void qscan_tile_kernel(const void *__restrict__ Xv, int64_t rows,
+__global__ __launch_bounds__(256) void qscan_tile_kernel(const void *Xv, int64_t rows,
                                                          int64_t cols, int64_t sx_r, int64_t sx_c,
                                                          float scale_val, const float *scale_ptr, int s,
-                                                         int32_t *__restrict__ Q,
+                                                         int32_t *Q,
                                                          int64_t ldq, int32_t *rowcnt, int32_t *colcnt,
                                                          int32_t *rowmax, int32_t *colmax,
                                                          int32_t *status, int32_t *ob, int ob_cap,
-                                                         int32_t *ob_count) {
+                                                         int32_t *ob_count, int64_t x_stride, int64_t out_stride) {
+    Xv = item_at(Xv, blockIdx.z * x_stride);
+    to_item(blockIdx.z * out_stride, scale_ptr, Q, rowcnt, colcnt, rowmax, colmax, ob, ob_count);
     __shared__ int32_t tile[64][65];
     __shared__ int lds[2 * 4 * 64];
     __shared__ ObStage stage;
@@ -298,12 +316,14 @@ constexpr int kTrThreads = 1024, kTrWaves = kTrThreads / 64;  // LDS admits two 
 constexpr int kTrPerWave = kTrTile / kTrWaves;               // columns (then rows) of the tile per wave, two per instruction
 
 template <bool FROM_FLOAT>
-__global__ __launch_bounds__(kTrThreads) void qscan_tr_kernel(const void *__restrict__ Xv, int64_t rows, int64_t cols,
+__global__ __launch_bounds__(kTrThreads) void qscan_tr_kernel(const void *Xv, int64_t rows, int64_t cols,
                                                        int64_t sx_c, float scale_val, const float *scale_ptr,
-                                                       int s, int32_t *__restrict__ Q, int64_t ldq, int32_t *rowcnt,
+                                                       int s, int32_t *Q, int64_t ldq, int32_t *rowcnt,
                                                        int32_t *colcnt, int32_t *rowmax, int32_t *colmax,
                                                        int32_t *status, int32_t *ob, int ob_cap,
-                                                       int32_t *ob_count) {
+                                                       int32_t *ob_count, int64_t x_stride, int64_t out_stride) {
+    Xv = item_at(Xv, blockIdx.z * x_stride);
+    to_item(blockIdx.z * out_stride, scale_ptr, Q, rowcnt, colcnt, rowmax, colmax, ob, ob_count);
     __shared__ int32_t tile[kTrTile * kTrPitch];  // [column][row]
     __shared__ ObStage stage;
     const float scale = step_of(scale_val, scale_ptr);
@@ -426,11 +446,12 @@ constexpr int kZeroArrays = 12;
 struct ZeroList {
     int32_t *p[kZeroArrays];
     int64_t len[kZeroArrays];
+    int64_t stride;   // bytes from item to item of a batch (blockIdx.y)
 };
 __global__ void zero_lists_kernel(ZeroList z) {
 #pragma unroll
     for (int i = 0; i < kZeroArrays; ++i) {
-        int32_t *p = z.p[i];
+        int32_t *p = item_at(z.p[i], blockIdx.y * z.stride);
         const int64_t len = z.len[i];
         if (!p) continue;
         for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < len; x += (int64_t)gridDim.x * blockDim.x)
@@ -453,27 +474,29 @@ static int64_t list_stats(ZeroList &z, int at, const imunpack_stats_t *st, int64
     return longest;
 }
 
-static int zero_listed(const ZeroList &z, int64_t longest, hipStream_t stream) {
+static int zero_listed(const ZeroList &z, int64_t longest, int nitems, hipStream_t stream) {
     if (longest == 0) return IMUNPACK_OK;
     int blocks = (int)((longest + 255) / 256);
     if (blocks > 256) blocks = 256;
-    hipLaunchKernelGGL(zero_lists_kernel, dim3(blocks), dim3(256), 0, stream, z);
+    hipLaunchKernelGGL(zero_lists_kernel, dim3(blocks, nitems), dim3(256), 0, stream, z);
     return launch_status();
 }
 
-static int zero_stats(const imunpack_stats_t *st, int64_t rows, int64_t cols, int32_t *status,
+static int zero_stats(const imunpack_stats_t *st, int64_t rows, int64_t cols, int32_t *status, const QuantBatch &bt,
                       hipStream_t stream) {
     ZeroList z;
+    z.stride = bt.out_stride;
     for (int i = 0; i < kZeroArrays; ++i) { z.p[i] = nullptr; z.len[i] = 0; }
-    return zero_listed(z, list_stats(z, 0, st, rows, cols, status), stream);
+    return zero_listed(z, list_stats(z, 0, st, rows, cols, bt.flag ? nullptr : status), bt.nitems, stream);
 }
 
 // The operand's description for the fast path, if it qualifies (unit column stride, rows and pointers
 // aligned to 16 bytes).
 template <bool FROM_FLOAT>
 static bool vec_operand(VecOperand &o, const void *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, float scale,
-                        const float *scale_dev, int32_t *Q, int64_t ldq, const imunpack_stats_t *st, int32_t *status) {
-    const bool vec = sx_c == 1 && (cols % 4) == 0 && (sx_r % 4) == 0 && ((uintptr_t)X % 16) == 0 &&
+                        const float *scale_dev, int32_t *Q, int64_t ldq, const imunpack_stats_t *st, int32_t *status,
+                        int64_t x_stride, const QuantBatch &bt) {
+    const bool vec = sx_c == 1 && (cols % 4) == 0 && (sx_r % 4) == 0 && ((uintptr_t)X % 16) == 0 && (x_stride % 16) == 0 &&
                      (!FROM_FLOAT || ((ldq % 4) == 0 && ((uintptr_t)Q % 16) == 0));
     if (!vec) return false;
     int64_t rpw = 64;  // 16, 32 and 128 rows per workgroup were all slower
@@ -481,7 +504,8 @@ static bool vec_operand(VecOperand &o, const void *X, int64_t rows, int64_t cols
     int32_t *ob = (st && st->ob && st->ob_count && st->ob_cap > 0) ? st->ob : nullptr;
     o = VecOperand{X, rows, sx_r, scale, scale_dev, Q, ldq,
                    st ? st->rowcnt : nullptr, st ? st->colcnt : nullptr, st ? st->rowmax : nullptr, st ? st->colmax : nullptr,
-                   status, ob, ob ? (int)st->ob_cap : 0, ob ? st->ob_count : nullptr, (int)rpw, (int)((rows + rpw - 1) / rpw)};
+                   bt.flag ? bt.flag : status, ob, ob ? (int)st->ob_cap : 0, ob ? st->ob_count : nullptr, (int)rpw,
+                   (int)((rows + rpw - 1) / rpw), x_stride, bt.out_stride};
     return true;
 }
 
@@ -498,10 +522,12 @@ static int check_qscan_args(const void *X, int64_t rows, int64_t cols, int64_t s
 template <bool FROM_FLOAT>
 int run_qscan(const void *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, float scale,
               const float *scale_dev, int b, int32_t *Q, int64_t ldq, const imunpack_stats_t *st, int32_t *status,
-              hipStream_t stream) {
+              int64_t x_stride, const QuantBatch &bt, hipStream_t stream) {
     IMU_TRY(check_qscan_args<FROM_FLOAT>(X, rows, cols, sx_r, sx_c, scale, scale_dev, b, Q, ldq, st));
-    IMU_TRY(zero_stats(st, rows, cols, FROM_FLOAT ? status : nullptr, stream));
+    IMU_TRY(zero_stats(st, rows, cols, FROM_FLOAT ? status : nullptr, bt, stream));
     if (rows == 0 || cols == 0) return IMUNPACK_OK;
+    const unsigned items = (unsigned)bt.nitems;
+    if (bt.flag) status = bt.flag;
     const int s = 1 << (b - 1);
     int32_t *rowcnt = st ? st->rowcnt : nullptr, *colcnt = st ? st->colcnt : nullptr;
     int32_t *rowmax = st ? st->rowmax : nullptr, *colmax = st ? st->colmax : nullptr;
@@ -510,18 +536,19 @@ int run_qscan(const void *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t s
     const int ob_cap = ob ? (int)st->ob_cap : 0;
     if (!FROM_FLOAT && !rowcnt && !colcnt && !rowmax && !colmax && !ob) return IMUNPACK_OK;
     VecOperand vo;
-    if (vec_operand<FROM_FLOAT>(vo, X, rows, cols, sx_r, sx_c, scale, scale_dev, Q, ldq, st, status)) {
-        dim3 grid((unsigned)((cols + 255) / 256), (unsigned)vo.row_blocks);
+    if (vec_operand<FROM_FLOAT>(vo, X, rows, cols, sx_r, sx_c, scale, scale_dev, Q, ldq, st, status, x_stride, bt)) {
+        dim3 grid((unsigned)((cols + 255) / 256), (unsigned)vo.row_blocks, items);
         hipLaunchKernelGGL(qscan_vec_kernel<FROM_FLOAT>, grid, dim3(256), 0, stream, vo, cols, s);
-    } else if (sx_r == 1 && (rows % 4) == 0 && (cols % 4) == 0 && (sx_c % 4) == 0 && ((uintptr_t)X % 16) == 0 &&
+    } else if (sx_r == 1 && (rows % 4) == 0 && (cols % 4) == 0 && (sx_c % 4) == 0 && ((uintptr_t)X % 16) == 0 && (x_stride % 16) == 0 &&
                (!FROM_FLOAT || ((ldq % 4) == 0 && ((uintptr_t)Q % 16) == 0)) && (cols + kTrTile - 1) / kTrTile <= 65535) {
-        dim3 grid((unsigned)((rows + kTrTile - 1) / kTrTile), (unsigned)((cols + kTrTile - 1) / kTrTile));
+        dim3 grid((unsigned)((rows + kTrTile - 1) / kTrTile), (unsigned)((cols + kTrTile - 1) / kTrTile), items);
         hipLaunchKernelGGL(qscan_tr_kernel<FROM_FLOAT>, grid, dim3(kTrThreads), 0, stream, X, rows, cols, sx_c, scale, scale_dev, s, Q,
-                           ldq, rowcnt, colcnt, rowmax, colmax, status, ob, ob_cap, ob_count);
+                           ldq, rowcnt, colcnt, rowmax, colmax, status, ob, ob_cap, ob_count, x_stride, bt.out_stride);
     } else {
-        dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64));
+        dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64), items);
         hipLaunchKernelGGL(qscan_tile_kernel<FROM_FLOAT>, grid, dim3(256), 0, stream, X, rows, cols, sx_r,
-                           sx_c, scale, scale_dev, s, Q, ldq, rowcnt, colcnt, rowmax, colmax, status, ob, ob_cap, ob_count);
+                           sx_c, scale, scale_dev, s, Q, ldq, rowcnt, colcnt, rowmax, colmax, status, ob, ob_cap, ob_count,
+                           x_stride, bt.out_stride);
     }
     return launch_status();
 }
@@ -532,31 +559,38 @@ int run_qscan(const void *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t s
 int quantize_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float scale_A, const float *scale_A_dev,
                   int32_t *QA, int64_t ldqa, const imunpack_stats_t *stA, const float *B, int64_t h, int64_t sb_r,
                   int64_t sb_c, float scale_B, const float *scale_B_dev, int32_t *QB, int64_t ldqb,
-                  const imunpack_stats_t *stB, int64_t d, int b, int32_t *status, hipStream_t stream) {
+                  const imunpack_stats_t *stB, int64_t d, int b, int32_t *status, const QuantBatch &bt, hipStream_t stream) {
     int32_t *stat_a = status, *stat_b = status ? status + 1 : nullptr;
     IMU_TRY(check_qscan_args<true>(A, n, d, sa_r, sa_c, scale_A, scale_A_dev, b, QA, ldqa, stA));
     IMU_TRY(check_qscan_args<true>(B, h, d, sb_r, sb_c, scale_B, scale_B_dev, b, QB, ldqb, stB));
     VecOperand va, vb;
     const bool paired = n > 0 && h > 0 && d > 0 &&
-                        vec_operand<true>(va, A, n, d, sa_r, sa_c, scale_A, scale_A_dev, QA, ldqa, stA, stat_a) &&
-                        vec_operand<true>(vb, B, h, d, sb_r, sb_c, scale_B, scale_B_dev, QB, ldqb, stB, stat_b);
+                        vec_operand<true>(va, A, n, d, sa_r, sa_c, scale_A, scale_A_dev, QA, ldqa, stA, stat_a, bt.a_stride, bt) &&
+                        vec_operand<true>(vb, B, h, d, sb_r, sb_c, scale_B, scale_B_dev, QB, ldqb, stB, stat_b, bt.b_stride, bt);
     if (!paired) {
-        IMU_TRY(run_qscan<true>(A, n, d, sa_r, sa_c, scale_A, scale_A_dev, b, QA, ldqa, stA, stat_a, stream));
-        return run_qscan<true>(B, h, d, sb_r, sb_c, scale_B, scale_B_dev, b, QB, ldqb, stB, stat_b, stream);
+        IMU_TRY(run_qscan<true>(A, n, d, sa_r, sa_c, scale_A, scale_A_dev, b, QA, ldqa, stA, stat_a, bt.a_stride, bt, stream));
+        return run_qscan<true>(B, h, d, sb_r, sb_c, scale_B, scale_B_dev, b, QB, ldqb, stB, stat_b, bt.b_stride, bt, stream);
     }
     ZeroList z;
+    z.stride = bt.out_stride;
+    if (bt.flag) stat_a = stat_b = nullptr;
     const int64_t la = list_stats(z, 0, stA, n, d, stat_a), lb = list_stats(z, 6, stB, h, d, stat_b);
-    IMU_TRY(zero_listed(z, std::max(la, lb), stream));
+    IMU_TRY(zero_listed(z, std::max(la, lb), bt.nitems, stream));
     const bool b_first = vb.row_blocks > va.row_blocks;  // the longer operand first: the shorter one fills its tail
     const VecOperand &first = b_first ? vb : va, &second = b_first ? va : vb;
-    dim3 grid((unsigned)((d + 255) / 256), (unsigned)(first.row_blocks + second.row_blocks));
+    dim3 grid((unsigned)((d + 255) / 256), (unsigned)(first.row_blocks + second.row_blocks), (unsigned)bt.nitems);
     hipLaunchKernelGGL(qscan_vec_pair_kernel, grid, dim3(256), 0, stream, first, second, d, 1 << (b - 1));
     return launch_status();
 }
 
-int scan_i32(const int32_t *Q, int64_t rows, int64_t cols, int64_t ldq, int b,
-             const imunpack_stats_t *st, hipStream_t stream) {
-    return run_qscan<false>(Q, rows, cols, ldq, 1, 1.0f, nullptr, b, nullptr, 0, st, nullptr, stream);
+// (of `nitems` operands of one shape: Q of item i lies i * q_stride bytes behind that of item 0, its results
+// i * out_stride)
+int scan_i32(const int32_t *Q, int64_t rows, int64_t cols, int64_t ldq, int b, const imunpack_stats_t *st, int nitems,
+             int64_t q_stride, int64_t out_stride, hipStream_t stream) {
+    QuantBatch bt;
+    bt.nitems = nitems;
+    bt.out_stride = out_stride;
+    return run_qscan<false>(Q, rows, cols, ldq, 1, 1.0f, nullptr, b, nullptr, 0, st, nullptr, q_stride, bt, stream);
 }
 
 }  // namespace imu
@@ -565,8 +599,8 @@ extern "C" int imunpack_quantize(const float *X, int64_t rows, int64_t cols, int
                                  float scale, int b, int32_t *Q, int64_t ldq,
                                  const imunpack_stats_t *stats, int32_t *status,
                                  imunpack_stream_t stream) {
-    return imu::run_qscan<true>(X, rows, cols, sx_r, sx_c, scale, nullptr, b, Q, ldq, stats, status,
-                                (hipStream_t)stream);
+    return imu::run_qscan<true>(X, rows, cols, sx_r, sx_c, scale, nullptr, b, Q, ldq, stats, status, 0,
+                                imu::QuantBatch(), (hipStream_t)stream);
 }
 
 extern "C" int imunpack_quantize_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float scale_A, int32_t *QA,
@@ -575,13 +609,13 @@ extern "C" int imunpack_quantize_pair(const float *A, int64_t n, int64_t sa_r, i
                                       const imunpack_stats_t *stats_B, int64_t d, int b, int32_t *status,
                                       imunpack_stream_t stream) {
     return imu::quantize_pair(A, n, sa_r, sa_c, scale_A, nullptr, QA, ldqa, stats_A, B, h, sb_r, sb_c, scale_B, nullptr, QB,
-                              ldqb, stats_B, d, b, status, (hipStream_t)stream);
+                              ldqb, stats_B, d, b, status, imu::QuantBatch(), (hipStream_t)stream);
 }
 
 extern "C" int imunpack_scan(const int32_t *Q, int64_t rows, int64_t cols, int64_t ldq, int b,
                              const imunpack_stats_t *stats, imunpack_stream_t stream) {
     if (!Q || ldq < cols) return IMUNPACK_EINVAL;
-    return imu::scan_i32(Q, rows, cols, ldq, b, stats, (hipStream_t)stream);
+    return imu::scan_i32(Q, rows, cols, ldq, b, stats, 1, 0, 0, (hipStream_t)stream);
 }
 
 extern "C" int imunpack_diag_copy(const void *src, void *dst, int64_t bytes, imunpack_stream_t stream) {

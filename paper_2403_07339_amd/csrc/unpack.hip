@@ -53,7 +53,24 @@ struct ScatterArgs {
     int items;                   // waves that serve this operand: (rows / kBandRows) * nwin
     int8_t *out;
     unsigned long long *wavesum; // [rows][nwin]: every wave leaves its part of the row norm
+    // batch (blockIdx.y is the item): the sizes above differ from item to item and come from its header
+    const PlanHeader *hdr;
+    int op;                      // 0: A, 1: B
+    int64_t m_stride, stride, out_stride;  // bytes from item to item: M, the plan's arrays, `out`
 };
+
+__device__ __forceinline__ void sizes_of_item(ScatterArgs &a) {
+    if (!a.out) {  // nothing to do for this operand
+        a.items = 0;
+        return;
+    }
+    const PlanHeader &h = a.hdr[blockIdx.y];
+    a.rows = a.op ? h.Np : h.Mp;
+    a.W = a.op ? h.Kp : h.KA;
+    a.ld = header_pitch(h, a.fp6, a.op);
+    a.nwin = (a.W + 1023) / 1024;
+    a.items = (a.rows / kBandRows) * a.nwin;
+}
 
 typedef int v4i_u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any int boundary
 
@@ -113,16 +130,9 @@ __device__ __forceinline__ unsigned long long sat44(unsigned long long m, unsign
     return t < (1ull << 44) ? t : (1ull << 44);
 }
 
-// Two operands in one launch when they take the same variant: waves below a0.items serve a0, the rest a1.
+// One wave's work: band and window `item` of operand a.
 template <bool DENSE>
-__global__ __launch_bounds__(kScatterThreads) void scatter_kernel(ScatterArgs a0, ScatterArgs a1) {
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = (int)(threadIdx.x & 63);
-    int item = (int)blockIdx.x * kScatterWaves + wave;
-    const bool second = item >= a0.items;
-    const ScatterArgs &a = second ? a1 : a0;
-    if (second) item -= a0.items;
-    if (item >= a.items) return;  // uniform per wave; no barriers anywhere
+__device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int lane) {
     const int band = item / a.nwin, win = item - band * a.nwin;
     const int nunits = a.W >> 4;
     const int upos = win * 64 + lane;
@@ -262,6 +272,40 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_kernel(ScatterArgs a0
     }
 }
 
+// Two operands in one launch when they take the same variant: waves below a0.items serve a0, the rest a1.
+template <bool DENSE>
+__global__ __launch_bounds__(kScatterThreads) void scatter_kernel(ScatterArgs a0, ScatterArgs a1) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int item = (int)blockIdx.x * kScatterWaves + wave;
+    const bool second = item >= a0.items;
+    const ScatterArgs &a = second ? a1 : a0;
+    if (second) item -= a0.items;
+    if (item >= a.items) return;  // uniform per wave; no barriers anywhere
+    scatter_item<DENSE>(a, item, (int)(threadIdx.x & 63));
+}
+
+// The same for the items of a batch, whose sizes come from their headers (a kernel of its own: the waves are too
+// short to hide a further dependent read where it is not needed).
+template <bool DENSE>
+__global__ __launch_bounds__(kScatterThreads) void scatter_batch_kernel(ScatterArgs a0, ScatterArgs a1) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int item = (int)blockIdx.x * kScatterWaves + wave;
+    sizes_of_item(a0);
+    sizes_of_item(a1);
+    const bool second = item >= a0.items;
+    ScatterArgs a = second ? a1 : a0;
+    if (second) item -= a0.items;
+    if (item >= a.items) return;
+    const int64_t off = blockIdx.y * a.stride;
+    a.M = item_at(a.M, blockIdx.y * a.m_stride);
+    a.prow_slot = item_at(a.prow_slot, off); a.prow_src = item_at(a.prow_src, off); a.prow_exp = item_at(a.prow_exp, off);
+    a.col_k = item_at(a.col_k, off); a.col_e = item_at(a.col_e, off); a.col_w = item_at(a.col_w, off);
+    a.unit = item_at(a.unit, off); a.unit_w = item_at(a.unit_w, off);
+    a.out = item_at(a.out, blockIdx.y * a.out_stride);
+    a.wavesum = item_at(a.wavesum, off);
+    scatter_item<DENSE>(a, item, (int)(threadIdx.x & 63));
+}
+
 // Places the digits above digit 0 of the listed OB entries of an operand unpacked by UnpackBoth.
 // The remainder floor(|v| / s) of an entry at (R, C) moves to the child of whichever of R and C was
 // split first (Alg. 4 lines 7-9 / 11-14) and leaves its own digit 0 there.
@@ -274,7 +318,9 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_kernel(ScatterArgs a0
 struct FixupArgs {
     const int32_t *ob;          // [3][ob_cap] rows | columns | values
     int ob_cap;
-    const int32_t *ob_count;
+    const PlanHeader *hdr;      // holds their number
+    int batch;                  // blockIdx.y is the item of a batch: W comes from its header
+    int64_t stride, out_stride; // bytes from item to item: the plan's arrays, `out`
     int second;
     SlotSet rows, cset;         // the operand's row slots and the column slots of its own unpacking
     const int32_t *c1_child;    // second == 1: child links among the column slots of A's unpacking
@@ -330,10 +376,23 @@ __device__ __forceinline__ void add_to_row(unsigned long long *rowsum, int p, un
 // half its run time).
 __global__ void fixup_kernel(FixupArgs fa, FixupArgs fb, int blocks_a, int blocks_b) {
     const bool first = (int)blockIdx.x < blocks_a;
-    const FixupArgs &f = first ? fa : fb;
+    FixupArgs f = first ? fa : fb;
     const int block = first ? blockIdx.x : blockIdx.x - blocks_a;
     const int nblocks = first ? blocks_a : blocks_b;
-    const int n = min(*f.ob_count, f.ob_cap);
+    f.hdr += blockIdx.y;
+    if (f.batch) {
+        const int64_t off = blockIdx.y * f.stride;
+        f.ob = item_at(f.ob, off);
+        move_to_item(f.rows, off);
+        move_to_item(f.cset, off);
+        f.c1_child = item_at(f.c1_child, off); f.c2_child = item_at(f.c2_child, off);
+        f.row_phys = item_at(f.row_phys, off); f.out_col = item_at(f.out_col, off);
+        f.col_phys = item_at(f.col_phys, off); f.col_sexp = item_at(f.col_sexp, off);
+        f.rowsum = item_at(f.rowsum, off);
+        f.out = item_at(f.out, blockIdx.y * f.out_stride);
+        f.W = header_pitch(*f.hdr, f.fp6, f.second);
+    }
+    const int n = min(f.second ? f.hdr->nobB : f.hdr->nobA, f.ob_cap);
     const unsigned mask = (unsigned)(f.s - 1);
     for (int t = block * blockDim.x + threadIdx.x; t < n; t += nblocks * blockDim.x) {
         const int i = f.ob[t], k = f.ob[f.ob_cap + t], v = f.ob[2 * (size_t)f.ob_cap + t];
@@ -379,8 +438,17 @@ __global__ void fixup_kernel(FixupArgs fa, FixupArgs fb, int blocks_a, int block
 __global__ void bound_kernel(const unsigned long long *rowsum_a, const unsigned long long *wavesum_a, int rows_a,
                              unsigned long long *bound_a, const unsigned long long *rowsum_b,
                              const unsigned long long *wavesum_b, int rows_b, unsigned long long *bound_b, int wpr_a,
-                             int wpr_b) {
+                             int wpr_b, const PlanHeader *hdr /* batch: the sizes come from the item's header */,
+                             int64_t stride) {
     unsigned long long ma = 0, mb = 0;
+    if (hdr) {
+        hdr += blockIdx.y;
+        const int64_t off = blockIdx.y * stride, hoff = blockIdx.y * (int64_t)sizeof(PlanHeader);
+        rowsum_a = item_at(rowsum_a, off); wavesum_a = item_at(wavesum_a, off); bound_a = item_at(bound_a, hoff);
+        rowsum_b = item_at(rowsum_b, off); wavesum_b = item_at(wavesum_b, off); bound_b = item_at(bound_b, hoff);
+        rows_a = hdr->Mp; rows_b = hdr->Np;
+        wpr_a = (hdr->KA + 1023) / 1024; wpr_b = (hdr->Kp + 1023) / 1024;
+    }
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < rows_a + rows_b; t += gridDim.x * blockDim.x) {
         if (t < rows_a) ma = max(ma, row_norm(wavesum_a, wpr_a, t, rowsum_a[t]));
         else mb = max(mb, row_norm(wavesum_b, wpr_b, t - rows_a, rowsum_b[t - rows_a]));
@@ -467,28 +535,32 @@ extern "C" int imunpack_plan_layout(const imunpack_plan_t *p, int64_t *shape) {
     return IMUNPACK_OK;
 }
 
-extern "C" int imunpack_unpack(imunpack_plan_t *p, const int32_t *A, int64_t lda, const int32_t *B,
-                               int64_t ldb, int8_t *A_ue, int8_t *B_eu, imunpack_stream_t stream) {
+// The scatter of one plan, or of every item of a batch (nitems > 1: the stores of item i lie i * a_stride and
+// i * b_stride bytes behind those of item 0).  With a_stride != 0 the bounds stay on the device, where
+// gemm_batch checks them.
+int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const int32_t *B, int64_t ldb, int8_t *A_ue,
+                     int64_t a_stride, int8_t *B_eu, int64_t b_stride, hipStream_t st) {
     if (!p || !p->valid || !A || !B || !A_ue || !B_eu || lda < p->d || ldb < p->d) return IMUNPACK_EINVAL;
-    hipStream_t st = (hipStream_t)stream;
     const PlanHeader &h = p->hdr;
+    const bool batch = p->nitems > 1;
+    const unsigned nitems = (unsigned)p->nitems;
     if (p->bound_pending) IMU_TRY(resolve_bound(p));  // of an earlier unpack of this plan
     // the planner leaves the bounds and the row norms cleared; a repeated unpack of the same plan clears them again
-    if (p->unpacked)
+    if (p->unpacked) {
+        if (batch) return IMUNPACK_EINVAL;
         hipLaunchKernelGGL(reset_bound_kernel, dim3(64), dim3(256), 0, st, p->d_hdr, p->layA.rowsum, h.Mp,
                            p->layB.rowsum, h.Np);
+    }
     FixupArgs fx[2] = {};
     int fblocks[2] = {0, 0};
     ScatterArgs sc[2];
     memset(sc, 0, sizeof(sc));
     bool launch[2] = {false, false}, dense[2] = {false, false};
+    int most_rows = 0;  // physical rows of both operands, in the largest item
     // keep-weights mode: the plan took the second operand's unpacking over, and the caller's buffer still holds
     // what the unpack before wrote for exactly that unpacking (same buffer, same format, row norms in place)
     const bool keepB = p->keep_B && h.reusedB && !p->unpacked && p->kept_Beu == B_eu && p->kept_Beu_fp6 == p->fp6;
     for (int op = 0; op < 2; ++op) {
-        const int rowsP = op ? h.Np : h.Mp;
-        const int W = op ? h.Kp : h.KA;
-        if (rowsP <= 0 || W <= 0) continue;
         const RowLayout &lay = op ? p->layB : p->layA;
         const bool both = (op ? p->sB : p->sA) == IMUNPACK_BOTH;
         ScatterArgs &a = sc[op];
@@ -499,19 +571,29 @@ extern "C" int imunpack_unpack(imunpack_plan_t *p, const int32_t *A, int64_t lda
         a.col_w = op ? nullptr : p->cols.colA_w;
         a.unit = op ? p->cols.unitB : p->cols.unitA;
         a.unit_w = op ? nullptr : p->cols.unitA_w;
-        a.rows = rowsP; a.W = W; a.ld = (int)store_pitch(p, op); a.s = p->s; a.sh = p->sh; a.fp6 = p->fp6;
-        a.nwin = (W + 1023) / 1024;
-        a.items = (rowsP / kBandRows) * a.nwin;
+        a.s = p->s; a.sh = p->sh; a.fp6 = p->fp6;
+        a.op = op;
+        a.hdr = batch ? p->d_hdr : nullptr;
+        a.m_stride = p->op_stride; a.stride = p->item_bytes; a.out_stride = op ? b_stride : a_stride;
+        a.rows = op ? h.Np : h.Mp; a.W = op ? h.Kp : h.KA; a.ld = (int)store_pitch(p, op);
+        a.nwin = (a.W + 1023) / 1024;
+        int nob = 0;
+        for (unsigned i = 0; i < nitems; ++i) {  // the launch covers the largest item
+            const PlanHeader &hi = batch ? p->pin_hdr[i] : h;
+            a.items = std::max(a.items, ((op ? hi.Np : hi.Mp) / kBandRows) * (((op ? hi.Kp : hi.KA) + 1023) / 1024));
+            nob = std::max(nob, (int)(op ? hi.nobB : hi.nobA));
+            most_rows = std::max(most_rows, hi.Mp + hi.Np);
+        }
         a.out = op ? B_eu : A_ue;
         a.wavesum = lay.wavesum;
-        launch[op] = !(op == 1 && keepB);
+        launch[op] = a.items > 0 && !(op == 1 && keepB);
         dense[op] = !both;
-        const int nob = op ? h.nobB : h.nobA;
         if (both && nob > 0 && launch[op]) {
             FixupArgs &f = fx[op];
             f.ob = op ? p->obcopyB : p->obcopyA;
             f.ob_cap = p->cap[op ? CAP_EDGEB : CAP_EDGEA];
-            f.ob_count = op ? &p->d_hdr->nobB : &p->d_hdr->nobA;
+            f.hdr = p->d_hdr;
+            f.batch = batch; f.stride = p->item_bytes; f.out_stride = a.out_stride;
             f.second = op;
             f.rows = op ? p->rowB : p->rowA;
             f.cset = op ? p->c2 : p->c1;
@@ -520,14 +602,16 @@ extern "C" int imunpack_unpack(imunpack_plan_t *p, const int32_t *A, int64_t lda
             f.row_phys = lay.row_phys;
             f.out_col = op ? p->cols.col_phys : p->cols.acol_phys;
             f.col_phys = p->cols.col_phys; f.col_sexp = p->cols.col_sexp;
-            f.W = (int)store_pitch(p, op); f.s = p->s; f.sh = p->sh; f.fp6 = p->fp6;
+            f.W = a.ld; f.s = p->s; f.sh = p->sh; f.fp6 = p->fp6;
             f.out = a.out; f.rowsum = lay.rowsum;
             fblocks[op] = (nob + 255) / 256;
         }
     }
     auto scatter = [&](const ScatterArgs &x, const ScatterArgs &y, int items, bool dns) {
-        const dim3 grid((unsigned)((items + kScatterWaves - 1) / kScatterWaves));
-        if (dns) hipLaunchKernelGGL(scatter_kernel<true>, grid, dim3(kScatterThreads), 0, st, x, y);
+        const dim3 grid((unsigned)((items + kScatterWaves - 1) / kScatterWaves), nitems);
+        if (batch && dns) hipLaunchKernelGGL(scatter_batch_kernel<true>, grid, dim3(kScatterThreads), 0, st, x, y);
+        else if (batch) hipLaunchKernelGGL(scatter_batch_kernel<false>, grid, dim3(kScatterThreads), 0, st, x, y);
+        else if (dns) hipLaunchKernelGGL(scatter_kernel<true>, grid, dim3(kScatterThreads), 0, st, x, y);
         else hipLaunchKernelGGL(scatter_kernel<false>, grid, dim3(kScatterThreads), 0, st, x, y);
     };
     ScatterArgs none;
@@ -538,20 +622,22 @@ extern "C" int imunpack_unpack(imunpack_plan_t *p, const int32_t *A, int64_t lda
         for (int op = 0; op < 2; ++op)
             if (launch[op]) scatter(sc[op], none, sc[op].items, dense[op]);
     }
-    if (h.Kp > 0 && h.Mp + h.Np > 0) {
+    if (most_rows > 0) {
         // after both scatters: the fix-up overwrites zeros they wrote; then the bounds from the row norms
         if (fblocks[0] + fblocks[1] > 0) {
             if (!fblocks[0]) fx[0] = fx[1];  // never dereferenced, but keep the argument well-formed
             if (!fblocks[1]) fx[1] = fx[0];
-            hipLaunchKernelGGL(fixup_kernel, dim3(fblocks[0] + fblocks[1]), dim3(256), 0, st, fx[0], fx[1], fblocks[0],
+            hipLaunchKernelGGL(fixup_kernel, dim3(fblocks[0] + fblocks[1], nitems), dim3(256), 0, st, fx[0], fx[1], fblocks[0],
                                fblocks[1]);
         }
-        const int nscan = std::min(256, (h.Mp + h.Np + 255) / 256);
-        hipLaunchKernelGGL(bound_kernel, dim3(nscan), dim3(256), 0, st, p->layA.rowsum, p->layA.wavesum, h.Mp,
+        const int nscan = std::min(256, (most_rows + 255) / 256);
+        hipLaunchKernelGGL(bound_kernel, dim3(nscan, nitems), dim3(256), 0, st, p->layA.rowsum, p->layA.wavesum, h.Mp,
                            &p->d_hdr->bound[0], p->layB.rowsum, p->layB.wavesum, h.Np, &p->d_hdr->bound[1],
-                           sc[0].nwin, sc[1].nwin);
+                           sc[0].nwin, sc[1].nwin, batch ? p->d_hdr : nullptr, p->item_bytes);
     }
     IMU_TRY(launch_status());
+    p->unpacked = 1;
+    if (a_stride) return IMUNPACK_OK;
     // The bounds travel to the host on the plan's side stream, behind the scatter: the caller's stream is
     // free to take the GEMM at once (imunpack_gemm launches it guarded and then waits for the bounds).
     IMU_HIP(hipEventRecord(p->scattered, st));
@@ -561,10 +647,14 @@ extern "C" int imunpack_unpack(imunpack_plan_t *p, const int32_t *A, int64_t lda
                            sizeof(p->hdr.bound), hipMemcpyDeviceToHost, p->side));
     IMU_HIP(hipEventRecord(p->ready, p->side));
     p->bound_pending = 1;
-    p->unpacked = 1;
     p->kept_Beu = p->keep_B ? B_eu : nullptr;
     p->kept_Beu_fp6 = p->fp6;
     return IMUNPACK_OK;
+}
+
+extern "C" int imunpack_unpack(imunpack_plan_t *p, const int32_t *A, int64_t lda, const int32_t *B,
+                               int64_t ldb, int8_t *A_ue, int8_t *B_eu, imunpack_stream_t stream) {
+    return unpack_impl(p, A, lda, B, ldb, A_ue, 0, B_eu, 0, (hipStream_t)stream);
 }
 
 namespace imu {

@@ -836,3 +836,38 @@ def test_gemm_batched_matches_the_oracle_chain_per_item(imu, b, strategies):
         bad[1, 2, 3] = float("nan")
         imu.imunpack_gemm_batched(dev(bad), B_d, 95.0, 31.0, 63.0, b, strategies[0], strategies[1], ctx=ctx)
     ctx.destroy()
+
+
+@pytest.mark.parametrize("b,strategies", [(8, (BOTH, BOTH)), (4, (ROW, COL)), (8, (COL, ROW))])
+def test_batched_items_that_differ(imu, b, strategies):
+    """The items of one batch share their launches but not their plans: items without heavy hitters beside items
+    with many (an OB list that overflows its first capacity), with three and more digits, and with an accumulator
+    bound that only the un-fused path can take; operands at odd offsets; each item against the oracle chain."""
+    g = torch.Generator().manual_seed(900 + b)
+    batch, n, d, h = 6, 70, 129, 65
+    a = torch.randn((batch, n, d), generator=g)
+    bt = torch.randn((batch, h, d), generator=g)
+    a[1][torch.rand((n, d), generator=g) < 0.04] *= 200.0          # many heavy hitters
+    a[2, :, 7] *= 3.0e4                                            # deep columns in both operands: large bounds
+    bt[2, :, 7] *= 3.0e4
+    a[3, 5, :] *= 500.0                                            # one heavy row
+    bt[4][torch.rand((h, d), generator=g) < 0.002] *= 1.0e5        # a few entries of many digits
+    ctx = imu.BatchContext()
+    for _ in range(2):                                             # the second call on the grown buffers
+        out = imu.imunpack_gemm_batched(dev(a), dev(bt), 95.0, 63.0, 63.0, b, strategies[0], strategies[1], ctx=ctx)
+        got = out.cpu().numpy().astype(np.float64)
+        for i in range(batch):
+            want = _oracle_matmul(a[i].numpy(), bt[i].numpy(), 95.0, 63.0, 63.0)
+            assert (np.abs(got[i] - want) <= REL_TOL * np.abs(want)).all(), i
+    ctx.destroy()
+
+
+def test_batched_more_items_than_one_group(imu):
+    """A batch of more items than share one set of launches, of the smallest shapes."""
+    g = torch.Generator().manual_seed(31)
+    batch, n, d, h = 1030, 3, 8, 2
+    a, bt = torch.randn((batch, n, d), generator=g), torch.randn((batch, h, d), generator=g)
+    out = imu.imunpack_gemm_batched(dev(a), dev(bt), 95.0, 31.0, 31.0, 8, ROW, COL, ctx=imu.BatchContext()).cpu().numpy()
+    for i in (0, 1, 511, 1023, 1024, 1029):
+        want = _oracle_matmul(a[i].numpy(), bt[i].numpy(), 95.0, 31.0, 31.0)
+        assert (np.abs(out[i] - want) <= REL_TOL * np.abs(want)).all(), i
