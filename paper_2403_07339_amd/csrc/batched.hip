@@ -98,7 +98,7 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
     const size_t oSa = take((size_t)2 * (n + d) * 4), oSb = take((size_t)2 * (h + d) * 4);
     const size_t oLa = take((size_t)3 * capA * 4), oLb = take((size_t)3 * capB * 4);
     const size_t oSmall = take(256);   // steps (2 floats), OB counts (2)
-    const size_t oWs = take(IMUNPACK_PERCENTILE_WORKSPACE_BYTES);
+    const size_t oWs = take(2 * IMUNPACK_PERCENTILE_WORKSPACE_BYTES);
     const size_t item = off;
     // Items that go through together: all of them while their operands and what is unpacked from them stay small
     // beside the memory of the GPU (a group of large products fills the chip by itself).
@@ -129,8 +129,7 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
         bt.flag = flags;
         hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(256), 0, st, flags, 1 + items);
         // the steps stay on the device: percentile -> step -> division in the quantizer -> product in the epilogue
-        IMU_TRY(rtn_steps(Ai, n, d, sa_r, sa_c, p, beta_A, steps, nullptr, pws, items, bt.a_stride, bt.out_stride, flags, st));
-        IMU_TRY(rtn_steps(Bi, h, d, sb_r, sb_c, p, beta_B, steps + 1, nullptr, pws, items, bt.b_stride, bt.out_stride, flags, st));
+        IMU_TRY(rtn_step_pair(Ai, n, sa_r, sa_c, beta_A, Bi, h, sb_r, sb_c, beta_B, d, p, steps, pws, bt, st));
         IMU_TRY(quantize_pair(Ai, n, sa_r, sa_c, 1.0f, steps, Qa, d, &stA, Bi, h, sb_r, sb_c, 1.0f, steps + 1, Qb, d, &stB, d,
                               b, nullptr, bt, st));
         IMU_TRY(plan_impl(Qa, n, d, d, Qb, h, d, b, strategy_A, strategy_B, &stA, &stB, &c->plan, items, (int64_t)item, st));

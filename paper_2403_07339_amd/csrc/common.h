@@ -313,10 +313,9 @@ int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *
 int gemm_batch(imunpack_plan_t *p, const int8_t *A_ue, int64_t a_stride, const int8_t *B_eu, int64_t b_stride, float *C_fp,
                int64_t c_stride, int64_t ldc, const float *scale_a_dev, const float *scale_b_dev, int64_t scale_stride,
                int32_t *refused, hipStream_t stream);
-// The RTN steps of the items of a batch (percentile.hip).
-int rtn_steps(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p, float beta, float *step,
-              int32_t *status_flag, void *workspace, int nitems, int64_t x_stride, int64_t out_stride, int32_t *flag,
-              hipStream_t st);
+// The RTN steps of both operands of every item of a batch (percentile.hip); ws: two workspaces side by side.
+int rtn_step_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float beta_A, const float *B, int64_t h, int64_t sb_r,
+                  int64_t sb_c, float beta_B, int64_t d, double p, float *steps, void *ws, const QuantBatch &bt, hipStream_t st);
 // Waits for the bounds that imunpack_unpack left in flight and sets p->fusable.
 int resolve_bound(Plan *p);
 // Bytes from one physical row to the next of the A store (op 0) / of B_eu (op 1) in the digit format in

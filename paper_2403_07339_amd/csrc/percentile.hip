@@ -3,186 +3,399 @@
 // That is an order statistic: the k-th smallest |x| with k = ceil(p N / 100).
 //
 // The magnitude of a binary32 number, read as a 31-bit unsigned integer, orders like the magnitude
-// itself, so the k-th smallest is found by a radix select over those integers, most significant
-// digit first: three passes over the matrix (11 + 10 + 10 bits).  A pass counts, per value of its
-// digit, the entries that agree with the digits fixed so far (a histogram in LDS per workgroup, merged
-// with one atomic per non-empty bin); a single workgroup then picks the digit value whose cumulative
-// count reaches k, fixes it and lowers k by the count below it.  HBM-bound: 12 bytes read per entry,
-// nothing written but 8 KiB of counters.  Everything stays on the stream; the caller reads *alpha
-// when it needs the number.
+// itself, so the k-th smallest is found by a radix select over those integers.
+//
+// Up to kSmall entries: one workgroup holds the whole matrix in registers and selects there, one launch.
+//
+// More: one workgroup first selects two ranks of a random sample that enclose the wanted one (five standard
+// deviations of the sample's rank and a little to either side), which leaves a window of about 1 % of the
+// entries.  Two passes over the matrix then count the entries below the window and, per value of the
+// next 11 (10) bits inside it, the entries in it (a histogram in LDS per workgroup, merged with one atomic per
+// non-empty bin); a workgroup finds the bin that the pass before it narrowed the window to by itself, from the
+// merged histogram.  A window of more than 2^21 values takes a third pass; a window that missed (the sample was
+// that unlucky) is left to one workgroup's own radix select over the whole matrix.
+// The passes are bound by reading the matrix: with the window, one entry in a hundred goes to the histogram.  Three
+// passes with a histogram of every entry, each followed by a launch that picked the bin, took 53 us each
+// on 11008 x 4096 (180 MB), 3.4 TB/s, 175 us in all; now 16 us for the sample, 35 and 31 us
+// for the passes and 6 us for the launch that closes: 88.  1576 x 768 and 3072 x 768 together: 150 -> 35 us.  Everything stays on the stream; the caller reads *alpha when it
+// needs the number.
 #include "common.h"
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
 namespace imu {
 
-constexpr int kSelBins = 2048;      // bins of the widest pass
-constexpr int kSelThreads = 256;
-constexpr int kSelItems = 4;        // 16-byte pieces per thread and step, loaded side by side
+constexpr int kSelThreads = 1024;
+constexpr int kSelWaves = kSelThreads / 64;
+constexpr int kHold = 48;                          // entries a thread of the one-workgroup selection holds, at most
+constexpr int64_t kSmall = kSelThreads * kHold;
+constexpr int kSample = 4096;                      // entries of the sample
+constexpr int kItems = 8;                          // 16-byte pieces per thread and step, loaded side by side
+constexpr int kBins0 = 2048, kBins1 = 1024, kBins2 = 512;  // of the three passes
+constexpr unsigned kInf = 0x7f800000u;             // above it: NaN
 
+// What the launches of one selection leave each other, behind the three histograms in the workspace.
 struct SelState {
-    unsigned prefix;           // digits fixed so far (in place)
-    unsigned prefix_mask;      // which bits those are
-    unsigned long long k;      // rank wanted among the entries that agree with the prefix (1-based)
-    unsigned maxbits;          // largest magnitude seen (as its bit pattern), gathered by the first pass
-    unsigned pad_;
+    unsigned lo, top, shift0;     // the window [lo, lo + top], the first pass's bin width 1 << shift0
+    unsigned below;               // entries below it (first pass)
+    unsigned maxbits, nan;        // largest magnitude (as its bit pattern); whether there is a NaN
+    unsigned base1, k1, shift1;   // the second pass's window, the rank wanted inside it, its bin width
+    unsigned found, missed;       // after the first pass: base1 is the answer / the rank was outside the window
+    unsigned arrived;             // workgroups of the third pass that are done
+};
+static_assert(IMUNPACK_PERCENTILE_WORKSPACE_BYTES >= (kBins0 + kBins1 + kBins2) * sizeof(unsigned) + sizeof(SelState),
+              "workspace");
+
+// One matrix: nslow lines of nfast entries, entry (l, f) at X[l * sslow + f * sfast].
+struct SelOperand {
+    const float *X;
+    int64_t sslow, sfast;
+    unsigned N, nfast;
+    unsigned long long magic;     // e / nfast = mulhi(e, magic) (nfast > 1)
+    int kind;                     // 0: contiguous, 1: contiguous lines of a multiple of four entries, 2: any
+    unsigned k;                   // rank wanted (1-based)
+    unsigned m, rlo, rhi;         // sample size and the ranks in it that enclose the wanted one (0 / > m: open end)
+    void *ws;
+    float *out;                   // alpha, or
+    float half_beta;              // > 0: the RTN step alpha / half_beta
+    int32_t *status;              // set to 1 if there is a NaN ...
+    int clear_status;             // ... and to 0 if not (otherwise only ever set)
+    int64_t x_stride;             // bytes from item to item of a batch
+};
+// blockIdx.y: the items of the first matrix's batch, then those of the second's.
+struct SelArgs {
+    SelOperand op[2];
+    int nitems;
+    int64_t out_stride;           // bytes from item to item: workspace and result
 };
 
-// Workspace layout: kSelBins counters, then the state.
+__device__ __forceinline__ SelOperand sel_operand(const SelArgs &a) {
+    const bool second = (int)blockIdx.y >= a.nitems;
+    SelOperand o = second ? a.op[1] : a.op[0];
+    const int64_t item = (int)blockIdx.y - (second ? a.nitems : 0);
+    o.X = item_at(o.X, item * o.x_stride);
+    o.ws = item_at(o.ws, item * a.out_stride);
+    o.out = item_at(o.out, item * a.out_stride);
+    return o;
+}
 __device__ __forceinline__ unsigned *sel_hist(void *ws) { return reinterpret_cast<unsigned *>(ws); }
 __device__ __forceinline__ SelState *sel_state(void *ws) {
-    return reinterpret_cast<SelState *>(reinterpret_cast<unsigned *>(ws) + kSelBins);
+    return reinterpret_cast<SelState *>(reinterpret_cast<unsigned *>(ws) + kBins0 + kBins1 + kBins2);
+}
+__device__ __forceinline__ unsigned sel_line(const SelOperand &o, unsigned e) {
+    return o.nfast > 1 ? (unsigned)__umul64hi(e, o.magic) : e;
+}
+__device__ __forceinline__ float sel_entry(const SelOperand &o, unsigned e) {
+    if (o.kind == 0) return o.X[e];
+    const unsigned l = sel_line(o, e);
+    return o.X[(int64_t)l * o.sslow + (int64_t)(e - l * o.nfast) * o.sfast];
 }
 
-// blockIdx.y is the item of a batch in every kernel here: its matrix lies x_stride bytes behind that of the item
-// before, its workspace and its result out_stride bytes.
-__global__ void select_init_kernel(void *ws, unsigned long long k, int32_t *status, int64_t out_stride) {
-    ws = item_at(ws, blockIdx.y * out_stride);
-    unsigned *hist = sel_hist(ws);
-    for (int i = threadIdx.x; i < kSelBins; i += blockDim.x) hist[i] = 0;
-    if (threadIdx.x == 0) {
-        SelState *st = sel_state(ws);
-        st->prefix = 0;
-        st->prefix_mask = 0;
-        st->k = k;
-        st->maxbits = 0;
-        if (status) *status = 0;
+// Workgroup-wide: the bin of hist[0..nbins) in which the cumulative count reaches k (1-based) and the count
+// before it.  Returns false (for every thread) if the total is below k or k is 0.  lds: 20 words.
+__device__ __forceinline__ bool sel_pick(const unsigned *hist, int nbins, unsigned k, unsigned &bin, unsigned &before,
+                                         unsigned *lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int b0 = 2 * (int)threadIdx.x;  // two bins per thread
+    const unsigned c0 = b0 < nbins ? hist[b0] : 0u, c1 = b0 + 1 < nbins ? hist[b0 + 1] : 0u;
+    const unsigned incl = (unsigned)wave_inclusive_sum((int)(c0 + c1));
+    __syncthreads();  // earlier uses of lds
+    if (lane == 63) lds[wave] = incl;
+    if (threadIdx.x == 0) lds[16] = 0xffffffffu;
+    __syncthreads();
+    unsigned run = incl - (c0 + c1);
+    for (int w = 0; w < wave; ++w) run += lds[w];
+    if (k > run && k <= run + c0 + c1) {  // at most one thread
+        const bool first = k <= run + c0;
+        lds[16] = (unsigned)b0 + (first ? 0u : 1u);
+        lds[17] = first ? run : run + c0;
+    }
+    __syncthreads();
+    bin = lds[16];
+    before = lds[17];
+    return bin != 0xffffffffu;
+}
+
+// The result: alpha, or the RTN step of Eq. (quantized_A) formed once in binary32: beta integers cover
+// [-alpha_p, alpha_p], so one step is alpha_p / (0.5 beta).  A matrix whose p-th percentile is 0 (mostly
+// zeros) falls back to its largest magnitude, an all-zero (or non-finite) one to 1.
+__device__ __forceinline__ void sel_result(const SelOperand &o, unsigned alpha_bits, unsigned maxbits) {
+    float a = __uint_as_float(alpha_bits);
+    if (o.half_beta > 0.0f) {
+        if (!(a > 0.0f)) a = __uint_as_float(maxbits);
+        a = (a > 0.0f && a < __uint_as_float(kInf)) ? __fdiv_rn(a, o.half_beta) : 1.0f;
+    }
+    *o.out = a;
+}
+
+// ---- one workgroup: the whole matrix if it is small, else the sample -------------------------------------
+// HOLD entries per thread, loaded in one straight line: with a branch (on the count, on the strides) around every
+// load the compiler waits for each before the next, 20 us for the 13 of a 197 x 64 matrix
+// (96 of them side by side: 27 -> 12 us for the whole kernel).
+template <int HOLD>
+__global__ __launch_bounds__(kSelThreads) void select_small_kernel(SelArgs args) {
+    __shared__ unsigned hist[2][2048];
+    __shared__ unsigned lds[20], s_max, s_nan;
+    const SelOperand o = sel_operand(args);
+    const bool whole = o.N <= (unsigned)kSmall;
+    const unsigned count = whole ? o.N : o.m;
+    unsigned u[HOLD];
+    unsigned umax = 0;
+    auto entry = [&](int j) {
+        unsigned i = min(threadIdx.x + (unsigned)(j * kSelThreads), count - 1u);
+        // a random entry per sample (a multiplicative hash of its number, so that no row or column pitch can
+        // line up with the choice)
+        unsigned x = i * 0x9e3779b1u + 0x7f4a7c15u;
+        x = (x ^ (x >> 15)) * 0x85ebca77u;
+        x = (x ^ (x >> 13)) * 0xc2b2ae3du;
+        return whole ? i : __umulhi(x ^ (x >> 16), o.N);
+    };
+    if (o.kind == 0) {
+#pragma unroll
+        for (int j = 0; j < HOLD; ++j) u[j] = __float_as_uint(o.X[entry(j)]);
+    } else {
+        const unsigned long long magic = o.nfast > 1 ? o.magic : 0ull;
+        const unsigned one = o.nfast > 1 ? 0u : 0xffffffffu;  // lines of one entry: the line is the entry's number
+#pragma unroll
+        for (int j = 0; j < HOLD; ++j) {
+            const unsigned e = entry(j), l = (unsigned)__umul64hi(e, magic) | (e & one);
+            u[j] = __float_as_uint(o.X[(int64_t)l * o.sslow + (int64_t)(e - l * o.nfast) * o.sfast]);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < HOLD; ++j) {
+        if (threadIdx.x + (unsigned)(j * kSelThreads) < count) {
+            u[j] &= 0x7fffffffu;
+            umax = max(umax, u[j]);
+        } else {
+            u[j] = 0xffffffffu;  // absent
+        }
+    }
+    for (int i = threadIdx.x; i < 2 * 2048; i += kSelThreads) (&hist[0][0])[i] = 0;
+    if (threadIdx.x == 0) s_max = 0;
+    if (!whole) {  // a clean workspace for the passes
+        unsigned *w = sel_hist(o.ws);
+        for (int i = threadIdx.x; i < kBins0 + kBins1 + kBins2 + (int)(sizeof(SelState) / 4); i += kSelThreads) w[i] = 0;
+        if (threadIdx.x == 0 && o.status && o.clear_status) *o.status = 0;
+    }
+    __syncthreads();
+    umax = (unsigned)wave_max_nonneg_lane63((int)umax);
+    if ((threadIdx.x & 63) == 63) atomicMax(&s_max, umax);
+    // digits of 11, 10 and 10 bits, most significant first; ranks r[0] (and, for the sample, r[1]).  The sample's
+    // window ends need no last digit.
+    unsigned r[2] = {whole ? o.k : o.rlo, whole ? o.k : o.rhi}, prefix[2] = {0, 0};
+    const int passes = whole ? 3 : 2;
+    bool ok[2] = {true, !whole};
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = pass == 0 ? 20 : pass == 1 ? 10 : 0, nbins = pass == 0 ? 2048 : 1024;
+        const unsigned bmask = (unsigned)nbins - 1u, pmask = pass == 0 ? 0u : 0xffffffffu << (shift + 10);
+#pragma unroll
+        for (int j = 0; j < HOLD; ++j) {
+            if (u[j] == 0xffffffffu) continue;
+            if ((u[j] & pmask) == prefix[0]) atomicAdd(&hist[0][(u[j] >> shift) & bmask], 1u);
+            if (!whole && pass > 0 && (u[j] & pmask) == prefix[1]) atomicAdd(&hist[1][(u[j] >> shift) & bmask], 1u);
+        }
+        __syncthreads();
+        const unsigned p0 = prefix[0], p1 = prefix[1];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (q == 1 && whole) continue;
+            unsigned bin, before;
+            const bool got = sel_pick(hist[pass > 0 ? q : 0], nbins, r[q], bin, before, lds);
+            ok[q] = ok[q] && got;
+            if (ok[q]) {
+                r[q] -= before;
+                prefix[q] = (q ? p1 : p0) | (bin << shift);
+            }
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < 2 * 2048; i += kSelThreads) (&hist[0][0])[i] = 0;
+        __syncthreads();
+    }
+    if (threadIdx.x != 0) return;
+    const unsigned maxbits = s_max;
+    if (whole) {
+        sel_result(o, prefix[0], maxbits);
+        if (o.status && (o.clear_status || maxbits > kInf)) {
+            if (o.clear_status) *o.status = maxbits > kInf ? 1 : 0;
+            else atomicOr(o.status, 1);
+        }
+        return;
+    }
+    SelState *st = sel_state(o.ws);
+    const unsigned lo = ok[0] ? min(prefix[0], kInf) : 0u, hi = ok[1] ? min(prefix[1] | 0x3ffu, kInf) : kInf;
+    st->lo = lo;
+    st->top = hi - lo;
+    st->shift0 = hi - lo >= (unsigned)kBins0 ? 32 - __clz(hi - lo) - 11 : 0;
+}
+
+// Calls take(bits of the magnitude) for every entry that this workgroup of `blocks` is responsible for.
+typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
+template <int ITEMS = kItems, class T>
+__device__ __forceinline__ void sel_stream(const SelOperand &o, unsigned block, unsigned blocks, T take) {
+    auto bits = [](float x) { return __float_as_uint(x) & 0x7fffffffu; };
+    // a workgroup's pieces of one step lie side by side
+    const unsigned long long step = (unsigned long long)blocks * (kSelThreads * ITEMS);
+    const unsigned long long first = (unsigned long long)block * (kSelThreads * ITEMS) + threadIdx.x;
+    if (o.kind <= 1) {
+        const unsigned quads = o.N / 4;
+        const unsigned qline = o.nfast / 4;
+        auto run = [&](auto load) {
+            for (unsigned long long q0 = first; q0 < quads; q0 += step) {
+                v4f_a4 v[ITEMS];
+#pragma unroll
+                for (int i = 0; i < ITEMS; ++i) {
+                    const unsigned long long q = q0 + (unsigned)(i * kSelThreads);
+                    if (q < quads) {
+                        const float *src = o.X + 4 * q;
+                        if (o.kind == 1) {
+                            const unsigned l = sel_line(o, (unsigned)(4 * q));
+                            src = o.X + (int64_t)l * o.sslow + 4 * (int64_t)((unsigned)q - l * qline);
+                        }
+                        v[i] = load(reinterpret_cast<const v4f_a4 *>(src));
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < ITEMS; ++i)
+                    if (q0 + (unsigned)(i * kSelThreads) < quads) {
+                        take(bits(v[i][0])); take(bits(v[i][1])); take(bits(v[i][2])); take(bits(v[i][3]));
+                    }
+            }
+        };
+        // A matrix that the L2 caches cannot hold for the next pass anyway is read non-temporally (first pass over
+        // 180 MB: 50 -> 35 us, 5.2 TB/s); one that they can, is not (second pass over 20 MB: 9 -> 6 us).
+        if (o.N > (8u << 20)) run([](const v4f_a4 *p) { return __builtin_nontemporal_load(p); });
+        else run([](const v4f_a4 *p) { return *p; });
+        if (block == 0 && threadIdx.x < (o.N & 3u)) take(bits(o.X[(o.N & ~3u) + threadIdx.x]));  // contiguous only
+    } else {
+        for (unsigned long long e0 = first; e0 < o.N; e0 += step) {
+            float v[ITEMS];
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                const unsigned long long e = e0 + (unsigned)(i * kSelThreads);
+                v[i] = e < o.N ? sel_entry(o, (unsigned)e) : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i)
+                if (e0 + (unsigned)(i * kSelThreads) < o.N) take(bits(v[i]));
+        }
     }
 }
 
-// The matrix as nslow lines of nfast entries: entry (l, f) at X[l * stride_slow + f * stride_fast].
-// VEC: stride_fast == 1, nfast % 4 == 0, lines 16-byte aligned.
-template <bool VEC>
-__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const float *X, int64_t nslow,
-                                                                   int64_t nfast, int64_t stride_slow,
-                                                                   int64_t stride_fast, void *ws, int shift,
-                                                                   int nbins, int32_t *status, int64_t x_stride,
-                                                                   int64_t out_stride) {
-    X = item_at(X, blockIdx.y * x_stride);
-    ws = item_at(ws, blockIdx.y * out_stride);
-    __shared__ unsigned lh[kSelBins];
+// The rank k inside the window [base, base + top], by one workgroup on its own: a radix select of 11 bits per
+// pass over the whole matrix.  (A window that missed, or the last bit of one of more than 2^30 values: the
+// passes below resolve everything else.)
+__device__ __forceinline__ unsigned sel_alone(const SelOperand &o, unsigned base, unsigned top, unsigned k, unsigned *lh,
+                                              unsigned *lds) {
+    for (;;) {  // the window shrinks by eleven bits a pass
+        const int shift = top >= 2048u ? 32 - __clz(top) - 11 : 0;
+        for (int i = threadIdx.x; i < 2048; i += kSelThreads) lh[i] = 0;
+        __syncthreads();
+        sel_stream<2>(o, 0, 1, [&](unsigned u) {
+            if (u - base <= top) atomicAdd(&lh[(u - base) >> shift], 1u);
+        });
+        __syncthreads();
+        unsigned bin, before;
+        if (!sel_pick(lh, 2048, k, bin, before, lds)) return 0x7fffffffu;  // fewer entries than k: NaNs are not counted
+        base += bin << shift;
+        k -= before;
+        if (shift == 0) return base;
+        top = (1u << shift) - 1u;
+        __syncthreads();
+    }
+}
+
+// ---- a pass over the matrix (PASS 0, 1, 2) -----------------------------------------------------------------
+template <int PASS>
+__global__ __launch_bounds__(kSelThreads) void select_count_kernel(SelArgs args) {
+    __shared__ unsigned lh[kBins0];
+    __shared__ unsigned lds[20], s_below, s_max, s_last;
+    const SelOperand o = sel_operand(args);
+    if (o.N <= (unsigned)kSmall) return;  // the one-workgroup launch has done it
+    SelState *st = sel_state(o.ws);
+    unsigned *hist = sel_hist(o.ws) + (PASS == 0 ? 0 : PASS == 1 ? kBins0 : kBins0 + kBins1);
+    const bool lead = blockIdx.x == 0;
+    unsigned base = st->lo, top = st->top, shift = st->shift0, k = o.k, bin, before;
+    if (PASS == 1) {  // what the first pass has narrowed the window to
+        const unsigned below = st->below, kw = k > below ? k - below : 0u;
+        const bool got = sel_pick(sel_hist(o.ws), kBins0, kw, bin, before, lds);
+        const unsigned nshift = shift > 10 ? shift - 10 : 0;
+        if (lead && threadIdx.x == 0) {
+            st->missed = !got;
+            st->found = got && shift == 0;
+            st->base1 = base + (bin << shift);
+            st->k1 = kw - before;
+            st->shift1 = nshift;
+        }
+        if (!got || shift == 0) return;
+        base += bin << shift;
+        top = (1u << shift) - 1u;
+        shift = nshift;
+    } else if (PASS == 2) {
+        if (st->missed) {
+            if (!lead) return;
+            const unsigned a = st->nan ? 0x7fffffffu : sel_alone(o, 0, kInf, k, lh, lds);
+            if (threadIdx.x == 0) sel_result(o, a, st->maxbits);
+            return;
+        }
+        base = st->base1;
+        if (!st->found) {
+            shift = st->shift1;
+            if (!sel_pick(sel_hist(o.ws) + kBins0, kBins1, st->k1, bin, before, lds)) return;  // cannot be: counted before
+            base += bin << shift;
+            k = st->k1 - before;
+        }
+        if (st->found || shift == 0) {
+            if (lead && threadIdx.x == 0) sel_result(o, base, st->maxbits);
+            return;
+        }
+        top = (1u << shift) - 1u;
+        shift = shift > 9 ? shift - 9 : 0;
+    }
+    const int nbins = PASS == 0 ? kBins0 : PASS == 1 ? kBins1 : kBins2;
     for (int i = threadIdx.x; i < nbins; i += kSelThreads) lh[i] = 0;
+    if (threadIdx.x == 0) s_below = s_max = 0;
     __syncthreads();
-    const SelState st = *sel_state(ws);
-    const unsigned bmask = (unsigned)nbins - 1u;
-    bool nan = false;
-    unsigned umax = 0;
-    auto take = [&](float x) {
-        const unsigned u = __float_as_uint(x) & 0x7fffffffu;
-        nan = nan || u > 0x7f800000u;
-        umax = max(umax, u);
-        if ((u & st.prefix_mask) == st.prefix) atomicAdd(&lh[(u >> shift) & bmask], 1u);
-    };
-    const int64_t per_line = VEC ? nfast / 4 : nfast;
-    const int64_t items = nslow * per_line;
-    const int64_t stride = (int64_t)gridDim.x * kSelThreads;
-    for (int64_t base = (int64_t)blockIdx.x * kSelThreads + threadIdx.x; base < items; base += stride * kSelItems) {
-        if (VEC) {
-            float4 v[kSelItems];
-#pragma unroll
-            for (int u = 0; u < kSelItems; ++u) {
-                const int64_t it = base + u * stride;
-                v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (it < items) {
-                    const int64_t l = it / per_line, f = it - l * per_line;
-                    v[u] = *reinterpret_cast<const float4 *>(X + l * stride_slow + 4 * f);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kSelItems; ++u) {
-                if (base + u * stride < items) {
-                    take(v[u].x); take(v[u].y); take(v[u].z); take(v[u].w);
-                }
-            }
-        } else {
-            float v[kSelItems];
-#pragma unroll
-            for (int u = 0; u < kSelItems; ++u) {
-                const int64_t it = base + u * stride;
-                v[u] = 0.f;
-                if (it < items) {
-                    const int64_t l = it / per_line, f = it - l * per_line;
-                    v[u] = X[l * stride_slow + f * stride_fast];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kSelItems; ++u)
-                if (base + u * stride < items) take(v[u]);
+    unsigned below = 0, umax = 0;
+    sel_stream(o, blockIdx.x, gridDim.x, [&](unsigned u) {
+        if (PASS == 0) {
+            below += u < base ? 1u : 0u;
+            umax = max(umax, u);
+        }
+        if (u - base <= top) atomicAdd(&lh[(u - base) >> shift], 1u);
+    });
+    if (PASS == 0) {
+        below = wave_sum_lane63(below);
+        umax = (unsigned)wave_max_nonneg_lane63((int)umax);
+        if ((threadIdx.x & 63) == 63) {
+            if (below) atomicAdd(&s_below, below);
+            atomicMax(&s_max, umax);
         }
     }
     __syncthreads();
-    unsigned *hist = sel_hist(ws);
     for (int i = threadIdx.x; i < nbins; i += kSelThreads)
         if (lh[i]) atomicAdd(&hist[i], lh[i]);
-    if (status && __ballot(nan) && (threadIdx.x & 63) == 0) atomicOr(status, 1);
-    if (shift == 20) {  // first pass: the largest magnitude, for the step's fall-back
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) umax = max(umax, (unsigned)__shfl_xor((int)umax, off, 64));
-        if ((threadIdx.x & 63) == 0 && umax) atomicMax(&sel_state(ws)->maxbits, umax);
-    }
-}
-
-// The RTN step of Eq. (quantized_A): beta integers cover [-alpha_p, alpha_p], so one step is
-// alpha_p / (0.5 beta), formed once in binary32.  A matrix whose p-th percentile is 0 (mostly zeros)
-// falls back to its largest magnitude, an all-zero (or non-finite) one to 1.  *step holds alpha_p on
-// entry (the selection's last pass wrote it there) and the step on exit.
-__global__ void rtn_step_kernel(void *ws, float half_beta, float *step, int64_t out_stride) {
-    ws = item_at(ws, blockIdx.y * out_stride);
-    step = item_at(step, blockIdx.y * out_stride);
-    float a = *step;
-    if (!(a > 0.0f)) a = __uint_as_float(sel_state(ws)->maxbits);
-    *step = (a > 0.0f && a < __uint_as_float(0x7f800000u)) ? __fdiv_rn(a, half_beta) : 1.0f;
-}
-
-// One workgroup: the bin whose cumulative count reaches k becomes the next digit.
-__global__ __launch_bounds__(1024) void select_pick_kernel(void *ws, int shift, int nbins, float *alpha, int64_t out_stride) {
-    ws = item_at(ws, blockIdx.y * out_stride);
-    alpha = item_at(alpha, blockIdx.y * out_stride);
-    __shared__ unsigned long long part[1024];
-    __shared__ int s_bin;
-    __shared__ unsigned long long s_below;
-    unsigned *hist = sel_hist(ws);
-    SelState *st = sel_state(ws);
-    const unsigned long long k = st->k;
-    // thread t owns bins [t * per, t * per + per)
-    const int per = (nbins + 1023) / 1024;
-    unsigned long long mine = 0;
-    for (int j = 0; j < per; ++j) {
-        const int b = threadIdx.x * per + j;
-        if (b < nbins) mine += hist[b];
-    }
-    part[threadIdx.x] = mine;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {  // inclusive scan
-        const unsigned long long add = threadIdx.x >= (unsigned)off ? part[threadIdx.x - off] : 0ull;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
-    }
-    const unsigned long long incl = part[threadIdx.x], excl = incl - mine;
-    if (excl < k && k <= incl) {  // exactly one thread, as 1 <= k <= the total count
-        unsigned long long run = excl;
-        for (int j = 0; j < per; ++j) {
-            const int b = threadIdx.x * per + j;
-            if (b >= nbins) break;
-            const unsigned c = hist[b];
-            if (k <= run + c) {
-                s_bin = b;
-                s_below = run;
-                break;
-            }
-            run += c;
+    if (PASS == 0 && threadIdx.x == 0) {
+        if (s_below) atomicAdd(&st->below, s_below);
+        atomicMax(&st->maxbits, s_max);
+        if (s_max > kInf) {
+            st->nan = 1;
+            if (o.status) atomicOr(o.status, 1);
         }
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < nbins; i += 1024) hist[i] = 0;  // ready for the next pass (and the next call)
-    if (threadIdx.x == 0) {
-        const unsigned prefix = st->prefix | ((unsigned)s_bin << shift);
-        st->prefix = prefix;
-        st->prefix_mask |= ((unsigned)nbins - 1u) << shift;
-        st->k = k - s_below;
-        if (shift == 0) *alpha = __uint_as_float(prefix);
+    if (PASS == 2) {  // rare: the workgroup that finishes last picks
+        __threadfence();
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = atomicAdd(&st->arrived, 1u) == gridDim.x - 1u;
+        __syncthreads();
+        if (!s_last) return;
+        __threadfence();
+        if (!sel_pick(hist, kBins2, k, bin, before, lds)) return;
+        base += bin << shift;
+        if (shift) base = sel_alone(o, base, (1u << shift) - 1u, k - before, lh, lds);
+        if (threadIdx.x == 0) sel_result(o, base, st->maxbits);
     }
 }
 
@@ -190,41 +403,62 @@ __global__ __launch_bounds__(1024) void select_pick_kernel(void *ws, int shift, 
 
 using namespace imu;
 
-static int run_percentile(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p,
-                          float *alpha, int32_t *status_flag, void *workspace, int nitems, int64_t x_stride,
-                          int64_t out_stride, int32_t *flag, hipStream_t st) {
-    static_assert(IMUNPACK_PERCENTILE_WORKSPACE_BYTES >= kSelBins * sizeof(unsigned) + sizeof(SelState), "workspace");
+static SelOperand sel_describe(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p, float *out,
+                               float half_beta, int32_t *status, void *ws) {
+    SelOperand o = {};
     const int64_t N = rows * cols;
     double kd = std::ceil(p * (double)N / 100.0);
     if (kd < 1.0) kd = 1.0;
     if (kd > (double)N) kd = (double)N;
-    const unsigned long long k = (unsigned long long)kd;
     // the unit-stride axis, if there is one, runs fastest
     int64_t nslow = rows, nfast = cols, sslow = sx_r, sfast = sx_c;
     if (sx_c != 1 && sx_r == 1) { nslow = cols; nfast = rows; sslow = sx_c; sfast = 1; }
-    const bool vec = sfast == 1 && (nfast % 4) == 0 && (sslow % 4) == 0 && ((uintptr_t)X % 16) == 0 && (x_stride % 16) == 0;
-    const int64_t items = nslow * (vec ? nfast / 4 : nfast);
-    int64_t blocks = (items + (int64_t)kSelThreads * kSelItems - 1) / ((int64_t)kSelThreads * kSelItems);
-    if (blocks > 1024) blocks = 1024;  // four per CU: every workgroup merges its histogram with atomics on the same few counters
-    if (blocks < 1) blocks = 1;
-    // the init kernel clears the counters and the state: whatever an earlier call left in the workspace is gone
-    hipLaunchKernelGGL(select_init_kernel, dim3(1, nitems), dim3(256), 0, st, workspace, k, flag ? nullptr : status_flag,
-                       out_stride);
-    if (flag) status_flag = flag;  // a batch ORs what goes wrong into one flag that its caller has cleared
-    const int shifts[3] = {20, 10, 0}, bins[3] = {2048, 1024, 1024};
-    for (int pass = 0; pass < 3; ++pass) {
-        if (vec)
-            hipLaunchKernelGGL(select_count_kernel<true>, dim3((unsigned)blocks, nitems), dim3(kSelThreads), 0, st, X, nslow, nfast,
-                               sslow, sfast, workspace, shifts[pass], bins[pass], pass == 0 ? status_flag : nullptr,
-                               x_stride, out_stride);
-        else
-            hipLaunchKernelGGL(select_count_kernel<false>, dim3((unsigned)blocks, nitems), dim3(kSelThreads), 0, st, X, nslow, nfast,
-                               sslow, sfast, workspace, shifts[pass], bins[pass], pass == 0 ? status_flag : nullptr,
-                               x_stride, out_stride);
-        hipLaunchKernelGGL(select_pick_kernel, dim3(1, nitems), dim3(1024), 0, st, workspace, shifts[pass], bins[pass], alpha,
-                           out_stride);
+    o.X = X;
+    o.sslow = sslow; o.sfast = sfast;
+    o.N = (unsigned)N; o.nfast = (unsigned)nfast;
+    o.magic = nfast > 1 ? ~0ull / (unsigned long long)nfast + 1ull : 0ull;
+    o.kind = sfast == 1 && (sslow == nfast || nslow == 1) ? 0 : sfast == 1 && nfast % 4 == 0 ? 1 : 2;
+    o.k = (unsigned)kd;
+    o.m = kSample;
+    const double q = kd / (double)N, r = q * kSample, dr = 5.0 * std::sqrt(kSample * q * (1.0 - q)) + 4.0;
+    o.rlo = r - dr < 1.0 ? 0u : (unsigned)(r - dr);
+    o.rhi = (unsigned)std::ceil(r + dr);  // beyond the sample: no upper end
+    o.ws = ws;
+    o.out = out;
+    o.half_beta = half_beta;
+    o.status = status;
+    o.clear_status = 1;
+    return o;
+}
+
+// nops matrices (1 or 2), each the first of a batch of nitems
+static int sel_launch(const SelArgs &a, int nops, hipStream_t st) {
+    const unsigned y = (unsigned)(nops * a.nitems);
+    unsigned most = a.op[0].N, held = 0;
+    if (nops > 1) most = std::max(most, a.op[1].N);
+    for (int q = 0; q < nops; ++q) held = std::max(held, a.op[q].N <= (unsigned)kSmall ? a.op[q].N : (unsigned)kSample);
+    auto small = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1, y), dim3(kSelThreads), 0, st, a); };
+    if (held <= 4 * kSelThreads) small(select_small_kernel<4>);
+    else if (held <= 8 * kSelThreads) small(select_small_kernel<8>);
+    else if (held <= 16 * kSelThreads) small(select_small_kernel<16>);
+    else if (held <= 32 * kSelThreads) small(select_small_kernel<32>);
+    else small(select_small_kernel<kHold>);
+    if (most > (unsigned)kSmall) {
+        // one workgroup per CU at most (every workgroup merges its histogram with atomics on the same counters)
+        const unsigned blocks = std::min(256u, (most / 4 + kSelThreads * kItems - 1) / (kSelThreads * kItems));
+        hipLaunchKernelGGL(select_count_kernel<0>, dim3(blocks, y), dim3(kSelThreads), 0, st, a);
+        hipLaunchKernelGGL(select_count_kernel<1>, dim3(blocks, y), dim3(kSelThreads), 0, st, a);
+        hipLaunchKernelGGL(select_count_kernel<2>, dim3(blocks, y), dim3(kSelThreads), 0, st, a);
     }
     return launch_status();
+}
+
+static int run_percentile(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p, float *out,
+                          float half_beta, int32_t *status, void *ws, hipStream_t st) {
+    SelArgs a = {};
+    a.op[0] = sel_describe(X, rows, cols, sx_r, sx_c, p, out, half_beta, status, ws);
+    a.nitems = 1;
+    return sel_launch(a, 1, st);
 }
 
 extern "C" int imunpack_percentile(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c,
@@ -233,27 +467,38 @@ extern "C" int imunpack_percentile(const float *X, int64_t rows, int64_t cols, i
     if (!X || !alpha || !workspace || rows <= 0 || cols <= 0 || sx_r < 1 || sx_c < 1 || !(p > 0.0) || !(p <= 100.0))
         return IMUNPACK_EINVAL;
     if (rows > (int64_t)1 << 31 || cols > (int64_t)1 << 31 || rows * cols >= (int64_t)1 << 32) return IMUNPACK_EINVAL;
-    return run_percentile(X, rows, cols, sx_r, sx_c, p, alpha, status_flag, workspace, 1, 0, 0, nullptr,
-                          (hipStream_t)stream);
+    return run_percentile(X, rows, cols, sx_r, sx_c, p, alpha, 0.0f, status_flag, workspace, (hipStream_t)stream);
 }
 
-// The steps of the items of a batch (see QuantBatch): X, and with it step and workspace, item by item.
-int imu::rtn_steps(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p, float beta,
-                   float *step, int32_t *status_flag, void *workspace, int nitems, int64_t x_stride, int64_t out_stride,
-                   int32_t *flag, hipStream_t st) {
-    if (!X || !step || !workspace || rows <= 0 || cols <= 0 || sx_r < 1 || sx_c < 1 || !(p > 0.0) || !(p <= 100.0) ||
-        !(beta > 0.0f) || !(beta < 3.0e38f))
-        return IMUNPACK_EINVAL;
-    if (rows > (int64_t)1 << 31 || cols > (int64_t)1 << 31 || rows * cols >= (int64_t)1 << 32) return IMUNPACK_EINVAL;
-    IMU_TRY(run_percentile(X, rows, cols, sx_r, sx_c, p, step, status_flag, workspace, nitems, x_stride, out_stride, flag, st));
-    hipLaunchKernelGGL(rtn_step_kernel, dim3(1, nitems), dim3(1), 0, st, workspace, (float)(0.5 * (double)beta), step, out_stride);
-    return launch_status();
+static bool step_args_ok(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p, float beta) {
+    return X && rows > 0 && cols > 0 && sx_r >= 1 && sx_c >= 1 && p > 0.0 && p <= 100.0 && beta > 0.0f && beta < 3.0e38f &&
+           rows <= (int64_t)1 << 31 && cols <= (int64_t)1 << 31 && rows * cols < (int64_t)1 << 32;
+}
+
+// The steps of both operands of every item of a batch (bt: see QuantBatch), by the same launches: steps[0] for A
+// (n x d), steps[1] for B (h x d); two workspaces side by side at ws.
+int imu::rtn_step_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float beta_A, const float *B, int64_t h,
+                       int64_t sb_r, int64_t sb_c, float beta_B, int64_t d, double p, float *steps, void *ws,
+                       const QuantBatch &bt, hipStream_t st) {
+    if (!step_args_ok(A, n, d, sa_r, sa_c, p, beta_A) || !step_args_ok(B, h, d, sb_r, sb_c, p, beta_B)) return IMUNPACK_EINVAL;
+    SelArgs a = {};
+    a.op[0] = sel_describe(A, n, d, sa_r, sa_c, p, steps, (float)(0.5 * (double)beta_A), bt.flag, ws);
+    a.op[1] = sel_describe(B, h, d, sb_r, sb_c, p, steps + 1, (float)(0.5 * (double)beta_B), bt.flag,
+                           static_cast<char *>(ws) + IMUNPACK_PERCENTILE_WORKSPACE_BYTES);
+    a.op[0].x_stride = bt.a_stride;
+    a.op[1].x_stride = bt.b_stride;
+    a.op[0].clear_status = a.op[1].clear_status = 0;
+    a.nitems = bt.nitems;
+    a.out_stride = bt.out_stride;
+    return sel_launch(a, 2, st);
 }
 
 extern "C" int imunpack_rtn_step(const float *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, double p,
                                  float beta, float *step, int32_t *status_flag, void *workspace,
                                  imunpack_stream_t stream) {
-    return rtn_steps(X, rows, cols, sx_r, sx_c, p, beta, step, status_flag, workspace, 1, 0, 0, nullptr, (hipStream_t)stream);
+    if (!step || !workspace || !step_args_ok(X, rows, cols, sx_r, sx_c, p, beta)) return IMUNPACK_EINVAL;
+    return run_percentile(X, rows, cols, sx_r, sx_c, p, step, (float)(0.5 * (double)beta), status_flag, workspace,
+                          (hipStream_t)stream);
 }
 
 // ---- the same selection for callers that cannot allocate ------------------------------------------
@@ -287,5 +532,5 @@ extern "C" int imunpack_percentile_static(const float *X, int64_t rows, int64_t 
         }
         ws = g_scratch_ptr[dev];
     }
-    return run_percentile(X, rows, cols, sx_r, sx_c, p, alpha, status_flag, ws, 1, 0, 0, nullptr, (hipStream_t)stream);
+    return run_percentile(X, rows, cols, sx_r, sx_c, p, alpha, 0.0f, status_flag, ws, (hipStream_t)stream);
 }

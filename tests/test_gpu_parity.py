@@ -871,3 +871,47 @@ def test_batched_more_items_than_one_group(imu):
     for i in (0, 1, 511, 1023, 1024, 1029):
         want = _oracle_matmul(a[i].numpy(), bt[i].numpy(), 95.0, 31.0, 31.0)
         assert (np.abs(out[i] - want) <= REL_TOL * np.abs(want)).all(), i
+
+
+def _sampled_entries(total, count=4096):
+    """The entries of a matrix that the percentile's sample looks at (a hash of the sample number)."""
+    x = np.arange(count, dtype=np.uint64)
+    m = np.uint64(0xffffffff)
+    x = (x * np.uint64(0x9e3779b1) + np.uint64(0x7f4a7c15)) & m
+    x = ((x ^ (x >> np.uint64(15))) * np.uint64(0x85ebca77)) & m
+    x = ((x ^ (x >> np.uint64(13))) * np.uint64(0xc2b2ae3d)) & m
+    x = x ^ (x >> np.uint64(16))
+    return (x * np.uint64(total)) >> np.uint64(32)
+
+
+@pytest.mark.parametrize("rows,cols", [(256, 192), (1, 49153), (257, 1031), (1024, 768)])
+@pytest.mark.parametrize("kind", ["normal", "ties", "gap", "sparse", "misled"])
+def test_percentile_windows(imu, rows, cols, kind):
+    """Around the size where the selection leaves one workgroup, and what its window can meet: ties (values of eight
+    significant bits), two far modes with the rank at the edge between them (the third pass), mostly zeros, and a
+    sample that shows something else than the matrix (the window misses).  Contiguous, transposed and strided."""
+    rng = np.random.default_rng(rows * 31 + cols)
+    x = rng.standard_normal((rows, cols)).astype(np.float32)
+    flat = x.reshape(-1)
+    if kind == "ties":
+        flat[:] = (flat.view(np.uint32) & np.uint32(0xffff0000)).view(np.float32)
+    elif kind == "gap":
+        flat[rng.random(flat.size) < 0.05] *= np.float32(1e12)
+    elif kind == "sparse":
+        flat[rng.random(flat.size) < 0.9995] = 0.0
+    elif kind == "misled":
+        flat[_sampled_entries(flat.size).astype(np.int64)] = np.float32(1e6)
+    xt = torch.from_numpy(x)
+    wide = torch.zeros((rows, cols + 4), device="cuda")
+    wide[:, :cols] = xt.to("cuda")
+    apart = torch.zeros((rows, 2 * cols + 1), device="cuda")
+    apart[:, 0:2 * cols:2] = xt.to("cuda")
+    for p in (0.01, 50.0, 95.0, 99.99, 100.0):
+        want = oracle.percentile_alpha(x, p)
+        for view in (xt.to("cuda"), xt.t().contiguous().to("cuda").t(), wide[:, :cols], apart[:, 0:2 * cols:2]):
+            alpha, status = imu.imunpack_percentile(view, p)
+            assert int(status.item()) == 0
+            assert alpha.cpu().numpy()[0] == want, (p, tuple(view.stride()))
+    x[rows // 2, cols // 3] = np.float32("nan")
+    _, status = imu.imunpack_percentile(torch.from_numpy(x).to("cuda"), 95.0)
+    assert int(status.item()) == 1
