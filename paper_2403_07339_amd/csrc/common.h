@@ -251,6 +251,7 @@ struct imunpack_plan {
     int nitems;
     int64_t item_bytes;           // from the arrays of one item in the arena to those of the next
     int64_t op_stride;            // from item to item: the integer operands, their statistics and OB lists
+    int chunkB;                   // no source row of B straddles that many physical rows: kTile, or kChunk for small products
     hipEvent_t ready;             // recorded after such a copy; the host polls it
     hipStream_t side;             // carries the copy of the accumulator bounds, so that the caller's stream
                                   // can already hold the GEMM while the host waits for them
@@ -290,6 +291,12 @@ struct imunpack_plan {
 
 namespace imu {
 using Plan = struct ::imunpack_plan;  // the C function imunpack_plan() hides the bare struct name
+
+// Products that the small-tile GEMM may be the better one for (gemm.hip decides once the unpacked sizes are known: never
+// above about 120 tiles of unpacked rows).
+inline bool small_tiles_possible(int64_t n, int64_t h, int nitems) {
+    return ((n + kTile - 1) / kTile) * ((h + kTile - 1) / kTile) * nitems <= 128;
+}
 
 // Copies the device headers to the host and waits for them.  The wait polls an event instead of blocking in the driver: the wake-up of a blocking wait costs
 // tens of microseconds during which the GPU idles between two stages of the path.

@@ -69,6 +69,8 @@ struct GemmArgs {
     const PlanHeader *hdr;    // nullptr: not a batch
     int64_t a_stride, b_stride, c_stride, plan_stride, scale_stride;  // bytes from item to item
     int32_t *refused;
+    int lmaxA;                // largest number of digit levels of a row of A
+    int kwaves;               // gemm_small_kernel: waves that share the contraction
     // benchmark reporting: if set, workgroup 0 writes {shader clock ticks, 100 MHz wall ticks} of its K loop
     unsigned long long *clock_probe;
 };
@@ -712,6 +714,258 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_f6_kernel(const GemmArgs
     gemm_body<MODE, true>(g, smem);
 }
 
+// ---- products of few tiles.  With 256 x 256 tiles a small product occupies a handful of CUs, each of which walks the whole
+// contraction and then spends longer in its epilogue than in the walk.  Here a workgroup owns one 64 x 64 chunk pair of the
+// layouts and its waves share the contraction: wave w of g.kwaves takes k-tiles w, w + kwaves, ... through one stage of LDS of
+// its own (nothing is shared between the waves: no barrier in the loop; the stage is filled again as soon as it has been read
+// into registers) and adds its 64 x 64 sums to one buffer in LDS.  Bound by the latency of a k-tile's loads; two workgroups
+// per CU cover it better than two stages per wave and one workgroup (21 -> 13 us at 1000 x 1031 x 777, b = 6), and fragments
+// loaded straight into registers, 64 bytes per lane and row, took twice as long (every load touches 64 lines).
+// 256 x 256 x 256: 90 -> 10 us; 16 rows against 11008 x 4096 weights 83 -> 35; 1000 x 1031 x 777, b = 6: 75 -> 14.
+// The planner lays rows of B out in chunks of 64 for products that may come here (Plan::chunkB).
+constexpr int kSmallWaves = 4, kSmallThreads = 64 * kSmallWaves;
+constexpr int kChunkPairs = (kTile / kChunk) * (kTile / kChunk);  // 64 x 64 tiles in one of 256 x 256
+constexpr int kSmallPitch = 72;  // the two half-waves of an accumulator register sit four rows apart: 32 banks
+constexpr int kSmallMeta = 2 * kChunk * (int)sizeof(int32_t);  // a word per source row and per source column of the chunk pair
+constexpr int kSmallFold = kChunk * kSmallPitch * (int)sizeof(int32_t);
+__host__ __device__ constexpr int small_stage_bytes(bool fp6) { return 2 * kChunk * (fp6 ? 112 : BK); }
+
+template <bool FP6, bool BATCH>
+__global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const GemmArgs g) {
+    constexpr int kRowB = FP6 ? 96 : BK, kPitch = FP6 ? 112 : BK, kLoads = FP6 ? 7 : 8;  // as in gemm_body
+    constexpr int kSteps = FP6 ? 2 : 4;                                                  // matrix instructions along a k-tile
+    extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
+    int32_t *rowmeta = reinterpret_cast<int32_t *>(smem), *colmeta = rowmeta + kChunk;
+    int8_t *stages = smem + kSmallMeta;
+    int32_t *fold = reinterpret_cast<int32_t *>(stages);  // takes the place of the stages once they have been read
+    const int tid = threadIdx.x, lane = tid & 63;
+    const PlanHeader *hdr = BATCH ? g.hdr + blockIdx.y : nullptr;
+    int mtiles = g.mtiles, ntiles = g.ntiles, ldA = g.ldA, ldB = g.ldB, kt1 = g.kt1, nbound = g.nbound;
+    if constexpr (BATCH) {
+        mtiles = hdr->mtiles; ntiles = hdr->ntiles;
+        ldA = header_pitch(*hdr, FP6, 0); ldB = header_pitch(*hdr, FP6, 1);
+        kt1 = hdr->Kp / BK;
+        nbound = hdr->nruns - 1;
+    }
+    constexpr int kPer = kTile / kChunk;
+    if (BATCH && (int)blockIdx.x >= mtiles * ntiles * kPer * kPer) return;  // the grid covers the largest item
+    RowLayout layA = g.layA, layB = g.layB;
+    if constexpr (BATCH) {
+        move_to_item(layA, blockIdx.y * g.plan_stride);
+        move_to_item(layB, blockIdx.y * g.plan_stride);
+    }
+    int cm, cn;
+    tile_of(blockIdx.x, mtiles * kPer, ntiles * kPer, cm, cn);
+    const int isrc0 = layA.chunk_src0[cm], ns = layA.chunk_src0[cm + 1] - isrc0;
+    const int jsrc0 = layB.chunk_src0[cn], nc = layB.chunk_src0[cn + 1] - jsrc0;
+    if (BATCH || g.guard) {
+        const unsigned long long *guard = BATCH ? hdr->bound : g.guard;
+        const unsigned long long b0 = guard[0], b1 = guard[1];
+        const unsigned long long m = b0 < b1 ? b0 : b1;
+        if (!(m < (1ull << 40) && m * (unsigned long long)g.guard_mul < (1ull << (FP6 ? 24 : 31))) || (BATCH && nbound >= 63)) {
+            if (g.refused && blockIdx.x == 0 && tid == 0) g.refused[blockIdx.y] = 1;
+            return;
+        }
+    }
+    if (ns <= 0 || nc <= 0) return;  // a chunk of nothing but padding (uniform)
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = cm * kChunk, n0 = cn * kChunk;
+
+    // lane i holds the end of segment i, its block offset and the shift behind it
+    int v_end, v_delta, v_shift;
+    if constexpr (BATCH) {
+        const int r = min(lane, nbound), r1 = min(r + 1, nbound);
+        v_end = lane < nbound ? hdr->run_kt0[r1] : kt1;
+        v_delta = hdr->run_blk0[r] - hdr->run_kt0[r];
+        v_shift = g.sh * (hdr->grp_exp[hdr->run_grp[r]] - hdr->grp_exp[hdr->run_grp[r1]]);
+    } else {
+        v_end = lane < nbound ? g.bound_kt[lane] + 1 : kt1;
+        v_delta = g.seg_delta[min(lane, nbound)];
+        v_shift = lane < nbound ? g.bound_sh[lane] : 0;
+    }
+    // ---- memory -> the wave's own stage: 8 rows x 128 B per load (see gemm_body for the order inside a stage)
+    const int8_t *gA = g.A + (int64_t)m0 * ldA, *gB = g.B + (int64_t)n0 * ldB;
+    if constexpr (BATCH) {
+        gA += blockIdx.y * g.a_stride;
+        gB += blockIdx.y * g.b_stride;
+    }
+    unsigned voffA[kLoads], voffB[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+        int row, byte;
+        if (FP6) {
+            const int slot = u * 64 + lane;
+            row = slot / 7;
+            byte = min(slot - 7 * row, 5) * 16;
+        } else {
+            row = 8 * u + (lane >> 3);
+            byte = ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+        }
+        voffA[u] = (unsigned)row * (unsigned)ldA + (unsigned)byte;
+        voffB[u] = (unsigned)row * (unsigned)ldB + (unsigned)byte;
+    }
+    const int8_t *sa = stages + wave * small_stage_bytes(FP6), *sb = sa + kChunk * kPitch;  // the wave's stage
+    const int step = g.kwaves;
+    const bool busy = wave < step && wave < kt1;
+    using FragT = std::conditional_t<FP6, v8i, v4i>;
+    using AccT = std::conditional_t<FP6, v16f, v16i>;
+    const int lrow = lane & 31, lhalf = lane >> 5;
+    AccT acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+    int seg = 0;  // follows the loads
+    unsigned long long probe_c = 0, probe_w = 0;
+    const bool probing = !BATCH && g.clock_probe != nullptr && blockIdx.x == 0;
+    if (probing) {
+        probe_c = __builtin_readcyclecounter();
+        probe_w = wall_clock64();
+    }
+    // The wave's share of the contraction.  RA: 32-row halves of the A chunk that hold source rows (a batch of up to 32
+    // decoded tokens fills one).
+    auto contract = [&](auto ra_c) {
+        constexpr int RA = decltype(ra_c)::value;
+        constexpr int kLoadsA = RA == 2 ? kLoads : 4;
+        // starts the loads of k-tile kt; returns the Horner shift between the wave's k-tile before and this one
+        auto fetch = [&](int kt) {
+            int sh = 0;
+            while (seg < nbound && kt >= __builtin_amdgcn_readlane(v_end, seg)) {
+                sh += __builtin_amdgcn_readlane(v_shift, seg);
+                ++seg;
+            }
+            const int8_t *pa = uniform_ptr(gA + (int64_t)(kt + __builtin_amdgcn_readlane(v_delta, seg)) * kRowB);
+            const int8_t *pb = uniform_ptr(gB + (int64_t)kt * kRowB);
+            const unsigned dst = __builtin_amdgcn_readfirstlane((unsigned)(size_t)sa);
+#pragma unroll
+            for (int u = 0; u < kLoadsA; ++u) dma16(dst + u * 1024, voffA[u], pa);
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) dma16(dst + kChunk * kPitch + u * 1024, voffB[u], pb);
+            return sh;
+        };
+        fetch(wave);  // nothing summed up yet: nothing to shift
+        for (int kt = wave, sh_now = 0;; kt += step) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            FragT fa[RA][kSteps], fb[2][kSteps];
+            auto load_frag = [&](const int8_t *half, int k) {
+                const int8_t *row = half + lrow * kPitch;
+                if constexpr (FP6) {
+                    const v4i lo = *reinterpret_cast<const v4i *>(row + 48 * k + 16 * lhalf);
+                    const v2i hi = *reinterpret_cast<const v2i *>(row + 48 * k + 32 + 8 * (lhalf ^ ((lrow >> 4) & 1)));
+                    return v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], 0, 0};
+                } else {
+                    return *reinterpret_cast<const v4i *>(row + (((2 * k + lhalf) ^ ((lrow >> 1) & 7)) << 4));
+                }
+            };
+#pragma unroll
+            for (int k = 0; k < kSteps; ++k) {
+#pragma unroll
+                for (int i = 0; i < RA; ++i) fa[i][k] = load_frag(sa + i * 32 * kPitch, k);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) fb[j][k] = load_frag(sb + j * 32 * kPitch, k);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the stage has been read: it may be filled again
+            const bool more = kt + step < kt1;
+            const int sh_next = more ? fetch(kt + step) : 0;
+            if (sh_now != 0) {
+#pragma unroll
+                for (int i = 0; i < RA; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            if constexpr (FP6) acc[i][j][r] = ldexpf(acc[i][j][r], sh_now);
+                            else acc[i][j][r] <<= sh_now;
+                        }
+            }
+#pragma unroll
+            for (int k = 0; k < kSteps; ++k)
+#pragma unroll
+                for (int i = 0; i < RA; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        if constexpr (FP6) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i][k], fb[j][k], acc[i][j], 2, 2, 0, 0, 0, 0);
+                        else acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i][k], fb[j][k], acc[i][j], 0, 0, 0);
+                    }
+            if (!more) break;
+            sh_now = sh_next;
+        }
+    };
+    const bool half_rows = ns * (BATCH ? hdr->lmaxA : g.lmaxA) <= 32;  // uniform; the rows of a chunk start at its first
+    if (busy) {
+        if (half_rows) contract(std::integral_constant<int, 1>{});
+        else contract(std::integral_constant<int, 2>{});
+    }
+    if (tid < ns) rowmeta[tid] = (layA.src_pstart[isrc0 + tid] - m0) | (layA.src_nlev[isrc0 + tid] << 16);
+    if (tid >= 64 && tid - 64 < nc) colmeta[tid - 64] = (layB.src_pstart[jsrc0 + tid - 64] - n0) | (layB.src_nlev[jsrc0 + tid - 64] << 16);
+    __syncthreads();  // every stage has been read
+    // the shifts behind the wave's last segment: then every wave counts in units of the lowest group
+    int rest = 0;
+    for (; seg < nbound; ++seg) rest += __builtin_amdgcn_readlane(v_shift, seg);
+    auto each = [&](auto put) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (i == 1 && half_rows) break;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    put(&fold[(i * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3)) * kSmallPitch + j * 32 + lrow], (int32_t)acc[i][j][r] << rest);
+        }
+    };
+    if (wave == 0) each([](int32_t *p, int32_t x) { *p = x; });  // (wave 0 always has a k-tile)
+    __syncthreads();
+    if (wave != 0 && busy) each([](int32_t *p, int32_t x) { atomicAdd(p, x); });
+    if (probing && tid == 0) {
+        g.clock_probe[0] = __builtin_readcyclecounter() - probe_c;
+        g.clock_probe[1] = wall_clock64() - probe_w;
+    }
+    float *C_fp = g.C_fp;
+    int final_shift = g.final_shift;
+    const float *scale_a_dev = g.scale_a_dev, *scale_b_dev = g.scale_b_dev;
+    if constexpr (BATCH) {
+        C_fp = item_at(C_fp, blockIdx.y * g.c_stride);
+        final_shift = hdr->ngroups ? g.sh * hdr->grp_exp[hdr->ngroups - 1] : 0;
+        scale_a_dev = item_at(scale_a_dev, blockIdx.y * g.scale_stride);
+        scale_b_dev = item_at(scale_b_dev, blockIdx.y * g.scale_stride);
+    }
+    const double scale2 = (scale_a_dev ? (double)*scale_a_dev * (double)*scale_b_dev : g.scale) * (double)(1ull << final_shift);
+    __syncthreads();
+    // C_int[i,j] = sum_{levels a of i, c of j} s^(a+c) * fold[row(i,a)][col(j,c)]: a lane owns a source column, a wave works
+    // on four source rows at a time so that their LDS reads are in flight together
+    if (lane >= nc) return;
+    const int q0 = colmeta[lane] & 0xFFFF, lj = colmeta[lane] >> 16;
+    constexpr int U = 4;
+    for (int r0 = wave; r0 < ns; r0 += U * kSmallWaves) {
+        int nl[U], nlmax = 0;
+        const int32_t *row[U];
+        int64_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * kSmallWaves;
+            const int m = r < ns ? rowmeta[r] : 0;
+            row[u] = fold + (m & 0xFFFF) * kSmallPitch + q0;
+            nl[u] = m >> 16;  // 0 past the chunk's last source row
+            nlmax = max(nlmax, nl[u]);
+            v[u] = 0;
+        }
+        for (int a = 0; a < nlmax; ++a)
+            for (int c = 0; c < lj; ++c)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (a < nl[u]) v[u] += (int64_t)row[u][a * kSmallPitch + c] << (g.sh * (a + c));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (nl[u]) {
+                const int64_t o = (int64_t)(isrc0 + r0 + u * kSmallWaves) * g.ldc + jsrc0 + lane;
+                if (C_fp) C_fp[o] = (float)((double)v[u] * scale2);
+                if (g.C_int) g.C_int[o] = v[u] << final_shift;
+            }
+    }
+}
+
 // C_int = Pi_A C_u Pi_B^T from the int64 unpacked product, then dequantise.
 __global__ __launch_bounds__(256) void recombine_kernel(const int64_t *__restrict__ C_u, int Np, RowLayout layA,
                                                         RowLayout layB, int n, int h, int sh,
@@ -777,6 +1031,11 @@ static int gemm_lds_opt_in() {
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_f6_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_batch_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_batch_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        constexpr int kSmallLds = kSmallMeta + kSmallWaves * small_stage_bytes(false);
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
         done.store(1, std::memory_order_release);
     }
     return IMUNPACK_OK;
@@ -817,6 +1076,7 @@ static void fused_args(GemmArgs &g, const Plan *p) {
     g.layA = p->layA; g.layB = p->layB;
     g.sh = p->sh;
     g.Np = h.Np;
+    g.lmaxA = h.lmaxA;
     g.guard_mul = p->s - 1;
     g.kt0 = 0; g.kt1 = h.Kp / BK;
     g.nbound = 0;
@@ -831,6 +1091,45 @@ static void fused_args(GemmArgs &g, const Plan *p) {
     g.final_shift = h.ngroups ? p->sh * h.grp_exp[h.ngroups - 1] : 0;
     // |accumulator| < 2^31, weights up to s^(levels of a row - 1 + levels of a column - 1)
     g.fold_f64 = 31 + p->sh * ((h.lmaxA - 1) + (h.lmaxB - 1)) <= 52;
+}
+
+// Whether 64 x 64 tiles are the better ones for `tiles` tiles of 256 x 256, of which `pairs` chunk pairs hold anything, with
+// `ktiles` k-tiles each, from what either kernel measured (nanoseconds): a 256 x 256 tile takes 12 us and 1.2 us per k-tile, 256
+// of them at a time; the small tiles take 0.2 us and 10 ns per k-tile for each sixteen of them, and no less than 0.3 us per
+// k-tile.  (1024 x 6528 by 2304 rows, 36 tiles: 70 and 38 us; 2048 x 1920 by 4352, 136 tiles: 34 and 51;
+// 2048 x 1152 by 2048, 64 tiles: 32 and 24; 2048 x 15104 by 2048: 142 and 101.)
+static bool small_tiles(const Plan *p, int64_t tiles, int64_t pairs, int64_t ktiles) {
+    if (p->chunkB != kChunk) return false;
+    const int64_t small = 6000 + std::max(300 * ktiles, pairs * (200 + 10 * ktiles) / kChunkPairs);
+    const int64_t large = (tiles + 255) / 256 * (12000 + 1200 * ktiles);
+    return small < large;
+}
+// The chunk pairs of an unpacked product that hold source rows.
+static int64_t chunk_pairs(const PlanHeader &h) {
+    auto chunks = [](int rows, int lmax) { return (rows + kChunk - lmax) / (kChunk - lmax + 1); };
+    return (int64_t)chunks(h.n_u, h.lmaxA) * chunks(h.h_u, h.lmaxB);
+}
+
+// The launch of the small-tile kernel: as many stages as the (longest) contraction has k-tiles for, so that short
+// contractions leave LDS to more workgroups of a CU.
+static int launch_small(const Plan *p, GemmArgs g, int chunks, int ktiles, bool batch, hipStream_t st) {
+    g.kwaves = std::max(1, std::min(ktiles, kSmallWaves));
+    const int lds = kSmallMeta + std::max(g.kwaves * small_stage_bytes(p->fp6), kSmallFold);
+    const dim3 grid((unsigned)chunks, batch ? (unsigned)p->nitems : 1u), threads(kSmallThreads);
+    if (batch && p->fp6) hipLaunchKernelGGL((gemm_small_kernel<true, true>), grid, threads, lds, st, g);
+    else if (batch) hipLaunchKernelGGL((gemm_small_kernel<false, true>), grid, threads, lds, st, g);
+    else if (p->fp6) hipLaunchKernelGGL((gemm_small_kernel<true, false>), grid, threads, lds, st, g);
+    else hipLaunchKernelGGL((gemm_small_kernel<false, false>), grid, threads, lds, st, g);
+    return launch_status();
+}
+
+// The fused launch of one product.
+static int launch_fused(const Plan *p, const GemmArgs &g, hipStream_t st) {
+    const int tiles = g.mtiles * g.ntiles;
+    if (small_tiles(p, tiles, chunk_pairs(p->hdr), g.kt1)) return launch_small(p, g, tiles * kChunkPairs, g.kt1, false, st);
+    if (p->fp6) hipLaunchKernelGGL(gemm_f6_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
+    else hipLaunchKernelGGL(gemm_i8_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
+    return launch_status();
 }
 
 int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *workspace, int64_t *C_int,
@@ -877,9 +1176,7 @@ int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *
         g.scale_a_dev = scale_a_dev; g.scale_b_dev = scale_b_dev;
         g.clock_probe = g_clock_probe.load(std::memory_order_relaxed);
         g.fold_f64 = g.fold_f64 && !C_int;
-        if (p->fp6) hipLaunchKernelGGL(gemm_f6_kernel<0>, dim3(grid), dim3(kGemmThreads), kGemmLds, st, g);
-        else hipLaunchKernelGGL(gemm_i8_kernel<0>, dim3(grid), dim3(kGemmThreads), kGemmLds, st, g);
-        IMU_TRY(launch_status());
+        IMU_TRY(launch_fused(p, g, st));
         if (!speculate) return IMUNPACK_OK;
         IMU_TRY(resolve_bound(p));
         if (p->fusable) return IMUNPACK_OK;
@@ -911,11 +1208,15 @@ int gemm_batch(imunpack_plan_t *p, const int8_t *A_ue, int64_t a_stride, const i
         return IMUNPACK_EINVAL;
     IMU_TRY(gemm_lds_opt_in());
     int grid = 0;
+    int64_t tiles = 0, pairs = 0, ktiles = 0;
     for (int i = 0; i < p->nitems; ++i) {
         const PlanHeader &h = p->pin_hdr[i];
         const int maxexp = (h.lmaxA - 1) + (h.lmaxB - 1) + (h.ngroups ? h.grp_exp[0] : 0);
         if (maxexp * p->sh > 62) return IMUNPACK_ERANGE;
         grid = std::max(grid, h.mtiles * h.ntiles);
+        tiles += h.mtiles * h.ntiles;
+        pairs += chunk_pairs(h);
+        ktiles = std::max<int64_t>(ktiles, h.Kp / BK);
     }
     GemmArgs g;
     memset(&g, 0, sizeof(g));
@@ -926,9 +1227,7 @@ int gemm_batch(imunpack_plan_t *p, const int8_t *A_ue, int64_t a_stride, const i
     if (p->nitems == 1 && p->pin_hdr[0].nruns <= 63) {  // a batch of one: the one-product kernel, its tables in the launch
         fused_args(g, p);
         g.guard = p->d_hdr->bound;
-        if (p->fp6) hipLaunchKernelGGL(gemm_f6_kernel<0>, dim3(grid), dim3(kGemmThreads), kGemmLds, st, g);
-        else hipLaunchKernelGGL(gemm_i8_kernel<0>, dim3(grid), dim3(kGemmThreads), kGemmLds, st, g);
-        return launch_status();
+        return launch_fused(p, g, st);
     }
     g.layA = p->layA; g.layB = p->layB;
     g.sh = p->sh;
@@ -936,6 +1235,7 @@ int gemm_batch(imunpack_plan_t *p, const int8_t *A_ue, int64_t a_stride, const i
     g.hdr = p->d_hdr;
     g.a_stride = a_stride; g.b_stride = b_stride; g.c_stride = c_stride; g.plan_stride = p->item_bytes;
     g.scale_stride = scale_stride;
+    if (small_tiles(p, tiles, pairs, ktiles)) return launch_small(p, g, grid * kChunkPairs, (int)ktiles, true, st);
     const dim3 blocks((unsigned)grid, (unsigned)p->nitems);
     if (p->fp6) hipLaunchKernelGGL(gemm_batch_kernel<true>, blocks, dim3(kGemmThreads), kGemmLds, st, g);
     else hipLaunchKernelGGL(gemm_batch_kernel<false>, blocks, dim3(kGemmThreads), kGemmLds, st, g);

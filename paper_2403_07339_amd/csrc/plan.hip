@@ -718,7 +718,7 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g)
 // Rows: source-major (all digit levels of a source row adjacent, level ascending), and no source
 // row straddles a chunk of `chunk` physical rows: kChunk for A (four chunks per GEMM tile), so that Pi_A
 // can be applied on the 64 rows the tile's epilogue holds in LDS at a time; kTile for B, whose levels
-// are folded along the columns of a tile.  Source row i with unpadded start P_i
+// are folded along the columns of a tile (kChunk there too if the 64 x 64 tiles of the small-tile GEMM may run).  Source row i with unpadded start P_i
 // goes to chunk floor(P_i / (kChunk - (Lmax-1))): a closed form, and the rows of a chunk never exceed
 // kChunk.
 __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count_dev, const RowLayout &lay,
@@ -794,7 +794,8 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
     for (int t = threadIdx.x; t < ntiles; t += kPlanThreads) {
         const int a = lay.tile_src0[t], e = lay.tile_src0[t + 1];
         const int slots = (e < nbase ? tmpP[e] : base) - tmpP[a];
-        lay.tile_flat[t] = (slots == e - a) ? 1 : 0;
+        // (rows of B in chunks: the tile's columns of C are read as one run, which gaps between the chunks break)
+        lay.tile_flat[t] = (slots == e - a && (operand == 0 || chunk == kTile || lmax == 1)) ? 1 : 0;
     }
     for (int p = threadIdx.x; p < Mp; p += kPlanThreads) {
         lay.prow_slot[p] = -1;
@@ -1240,7 +1241,7 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     SlotSet rowA, int n, RowLayout layA, int cap_physA, int32_t *tmpPA, SlotSet rowB, int h, RowLayout layB,
     int cap_physB, int32_t *tmpPB, SlotSet c1, SlotSet c2, ColLayout cols, int d, int cap_physC, int s, int sh,
     int32_t *tmpE, int32_t *tmpK, int32_t *tmpR, int32_t *tmpOff, PlanHeader *hdr, int fast_lds, const int32_t *skipB,
-    int64_t stride) {
+    int64_t stride, int chunkB) {
     __shared__ int lds[40];
     extern __shared__ __attribute__((aligned(16))) int32_t fast_rows[];  // 2 * max(n, h) ints, if the launch gave them
     hdr += blockIdx.y;
@@ -1262,11 +1263,12 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     }
     if (hdr->overflow) return;
     if (blockIdx.x >= 1 && skipB && *skipB) return;  // keep-weights mode: these layouts stand as they are
-    // rows of A: the GEMM epilogue folds them chunk by chunk; rows of B (columns of C): tile by tile
+    // rows of A: the GEMM epilogue folds them chunk by chunk; rows of B (columns of C): tile by tile, or chunk by chunk
+    // where the small-tile GEMM may be the one to run
     if (blockIdx.x == 0)
         rows_layout(rowA, n, &hdr->n_u, layA, cap_physA, cap_physA / kTile + 2, tmpPA, hdr, 0, kChunk, lds, fast_lds ? fast_rows : nullptr);
     else if (blockIdx.x == 1)
-        rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, kTile, lds, fast_lds ? fast_rows : nullptr);
+        rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr);
     else {
         cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, (int)blockIdx.x - 2);
         if (blockIdx.x == 2 && threadIdx.x == 0) hdr->bound[0] = hdr->bound[1] = 0;
@@ -1668,7 +1670,7 @@ static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B
                        phys_cap_rows(p->cap[CAP_ROWA]), p->tmpPA, p->rowB, h, p->layB,
                        phys_cap_rows(p->cap[CAP_ROWB]), p->tmpPB, p->c1, p->c2, p->cols, d,
                        phys_cap_cols(p->cap[CAP_C2]), p->s, p->sh, p->tmpE, p->tmpK, p->tmpR, p->tmpOff, hdr, fast_lds,
-                       keep ? (const int32_t *)&p->d_keep->same : (const int32_t *)nullptr, stride);
+                       keep ? (const int32_t *)&p->d_keep->same : (const int32_t *)nullptr, stride, p->chunkB);
     if (keep)
         hipLaunchKernelGGL(keep_remember_kernel, dim3(grid_for(p->cap[CAP_C1], 256, 16)), dim3(256), 0, st, p->c1,
                            (const PlanHeader *)hdr, p->snapRoot, p->snapExp, p->snapChild, p->d_keep);
@@ -1740,6 +1742,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
     p->stream = st;
     p->nitems = nitems;
     p->op_stride = op_stride;
+    p->chunkB = small_tiles_possible(n, h, nitems) ? kChunk : kTile;
     if (!same) {
         // first guesses; every one of them is grown after a run that reports it too small
         p->cap[CAP_ROWA] = std::max(p->cap[CAP_ROWA], (int)(strategy_A == IMUNPACK_COL ? n : 2 * n + 256));

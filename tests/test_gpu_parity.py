@@ -915,3 +915,40 @@ def test_percentile_windows(imu, rows, cols, kind):
     x[rows // 2, cols // 3] = np.float32("nan")
     _, status = imu.imunpack_percentile(torch.from_numpy(x).to("cuda"), 95.0)
     assert int(status.item()) == 1
+
+
+@pytest.mark.parametrize("b,strategies", [(8, (ROW, ROW)), (8, (COL, BOTH)), (4, (ROW, COL)), (3, (COL, ROW)), (8, (BOTH, BOTH))])
+@pytest.mark.parametrize("n,d,h", [(1, 1, 1), (33, 127, 65), (64, 513, 64), (257, 640, 31), (300, 1500, 250), (2050, 130, 1990)])
+def test_gemm_tiles_of_either_size(imu, n, d, h, b, strategies):
+    """Around the edges of a 64 x 64 tile, with contractions of one k-tile to more than the waves of a workgroup share,
+    several exponent groups inside one wave's share, and a product that the 256 x 256 tiles take although rows of B are
+    laid out in chunks of 64 (some of its tiles unsplit but with gaps): both outputs, both digit formats."""
+    s = 1 << (b - 1)
+    rng = np.random.default_rng(n * 7 + d * 3 + h + b)
+
+    def draw(rows, few):
+        q = rng.integers(-(s - 1), s, size=(rows, d))
+        if few:  # a few heavy hitters (UnpackBoth), all in the first rows
+            for _ in range(min(40, rows * d // 3)):
+                q[rng.integers(0, min(rows, 300)), rng.integers(0, d)] = rng.integers(-s * s * s, s * s * s)
+        else:
+            q[:, rng.integers(0, d, size=max(1, d // 40))] *= s
+            q[: min(rows, 150)] *= rng.choice([1, 1, 1, s], size=(min(rows, 150), 1))
+        return q.astype(np.int32)
+
+    Aq, Bq = draw(n, strategies[0] == BOTH), draw(h, strategies[1] == BOTH)
+    want = oracle.int_gemm(Aq, Bq)
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    for fp6 in ([False, True] if b <= 4 else [False]):
+        plan = imu.imunpack_plan(Qa, Qb, b, *strategies)
+        if fp6:
+            plan.set_digits(imu.DIGITS_FP6)
+        A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+        bw = plan.unpacked_bytes()[2]
+        C_int = torch.full(want.shape, -1, dtype=torch.int64, device="cuda")
+        C_fp = torch.full(want.shape, -1.0, device="cuda")
+        ws = torch.empty(bw // 8, dtype=torch.int64, device="cuda")
+        imu.imunpack_gemm(plan, A_ue, B_eu, 0.5, 0.25, C_int, C_fp, ws, fuse=True)
+        assert np.array_equal(C_int.cpu().numpy(), want)
+        ref = want.astype(np.float64) * 0.125
+        assert (np.abs(C_fp.cpu().numpy() - ref) <= REL_TOL * np.abs(ref)).all()
