@@ -42,6 +42,7 @@ constexpr int kKPad = 128;       // every exponent group is padded to a multiple
 constexpr int kMaxGroups = 64;   // distinct diagonal entries of S the planner supports
 constexpr int kMaxItems = 1024;  // products of a batch that are planned together
 constexpr int kMaxRuns = 128;    // stretches of consecutive k-tiles that read consecutive blocks of the A store
+constexpr int kProwLevel = 24;   // dimensions are at most 2^24, digit levels fewer than 64
 constexpr uint32_t kNever = 0xFFFFFFFFu;  // split time of a row/column that is never split
 
 // One set of growing row (or column) slots: what Pi (or S) needs per slot, plus the split
@@ -99,9 +100,7 @@ enum CapIndex { CAP_ROWA = 0, CAP_ROWB = 1, CAP_C1 = 2, CAP_C2 = 3, CAP_EDGEA = 
 
 // Physical-row description used by scatter and by the GEMM epilogue.
 struct RowLayout {
-    int32_t *prow_slot;   // [Mp]  canonical slot of physical row, -1 = padding
-    int32_t *prow_src;    // [Mp]  source row, -1 = padding
-    int32_t *prow_exp;    // [Mp]  digit level of the row
+    int32_t *prow;        // [Mp]  source row of physical row | its digit level << kProwLevel, -1 = padding
     int32_t *row_phys;    // [n']  physical row of canonical slot
     int32_t *src_pstart;  // [n]   first physical row of source row i
     int32_t *src_nlev;    // [n]   number of levels of source row i
@@ -127,8 +126,8 @@ struct ColLayout {
     int32_t *colB_k;      // [Kp] original column (-1 = zero column)
     int32_t *colB_e;      // [Kp] digit level along the columns of B_e
     int32_t *col_sexp;    // [Kp] exponent of the diagonal entry of S
-    int4 *unitB;          // [Kp/16] per 16-column unit: x, y = lowest and highest original column (-1: nothing to
-                          // read), z bit 0: 16 consecutive original columns, bit 1: one digit level for all of
+    int4 *unitB;          // [Kp/16] per 16-column unit: x = first original column, y >= 0 if there is one (-1:
+                          // nothing to read), z bit 0: 16 consecutive original columns, bit 1: one digit level for all of
                           // them, bit 2: one weight for all of them; w = that level | exponent of S << 16
     int32_t *acol_phys;   // [d'] stored column of A that every column slot of the second unpacking reads
     int32_t *apos;        // [columns of A_u] stored column of every column slot of A's unpacking
@@ -155,7 +154,7 @@ __host__ __device__ __forceinline__ void move_to_item(SlotSet &s, int64_t off) {
     s.child = item_at(s.child, off); s.key = item_at(s.key, off);
 }
 __host__ __device__ __forceinline__ void move_to_item(RowLayout &l, int64_t off) {
-    l.prow_slot = item_at(l.prow_slot, off); l.prow_src = item_at(l.prow_src, off); l.prow_exp = item_at(l.prow_exp, off);
+    l.prow = item_at(l.prow, off);
     l.row_phys = item_at(l.row_phys, off); l.src_pstart = item_at(l.src_pstart, off); l.src_nlev = item_at(l.src_nlev, off);
     l.tile_src0 = item_at(l.tile_src0, off); l.chunk_src0 = item_at(l.chunk_src0, off); l.tile_flat = item_at(l.tile_flat, off);
     l.rowsum = item_at(l.rowsum, off); l.wavesum = item_at(l.wavesum, off);

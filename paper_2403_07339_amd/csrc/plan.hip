@@ -216,6 +216,86 @@ __global__ __launch_bounds__(kPlanThreads) void level_major_kernel(
         if (threadIdx.x == 0) flag_overflow(hdr, which, N);
         return;
     }
+    // Up to kLevelItems items per thread: their levels and latest slots stay in registers (a wave owns a contiguous segment, as
+    // in ordered_select), so that a level is ballots and stores.  12608 rows: 23 -> 16 us.
+    constexpr int kLevelItems = 16;
+    if (N <= kLevelItems * kPlanThreads) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const int seg = ((N + kPlanWaves - 1) / kPlanWaves + 63) & ~63, x0 = wave * seg + lane;
+        const int hi = min(N, (wave + 1) * seg);
+        int L[kLevelItems], last[kLevelItems], lm = 1;
+#pragma unroll
+        for (int u = 0; u < kLevelItems; ++u) {
+            const int x = x0 + 64 * u;
+            last[u] = 64 * u < seg && x < hi ? (via ? via[x] : x) : -1;  // (uniform first: most operands fill a few)
+        }
+#pragma unroll
+        for (int u = 0; u < kLevelItems; ++u) {
+            if (64 * u >= seg) break;
+            L[u] = last[u] >= 0 ? maxabs[last[u]] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kLevelItems; ++u) {
+            if (64 * u >= seg) break;
+            if (last[u] < 0) continue;
+            const int x = x0 + 64 * u;
+            last[u] = x;
+            L[u] = digit_levels(L[u], sh);
+            lm = max(lm, L[u]);
+            set.root[x] = x;
+            set.exp[x] = 0;
+            if (L[u] == 1) {
+                set.time[x] = kNever;
+                set.child[x] = -1;
+            }
+        }
+        const int lmax = block_max(lm, lds);
+        const unsigned long long below = (1ull << lane) - 1ull;
+        int base = N;
+        for (int l = 1; l < lmax; ++l) {
+            int cnt = 0;
+#pragma unroll
+            for (int u = 0; u < kLevelItems; ++u) {
+                if (64 * u >= seg) break;
+                cnt += __popcll(__ballot(last[u] >= 0 && L[u] > l));
+            }
+            if (lane == 0) lds[wave] = cnt;
+            __syncthreads();
+            int run = base;
+#pragma unroll
+            for (int w = 0; w < kPlanWaves; ++w) {
+                const int c = lds[w];
+                if (w < wave) run += c;
+                base += c;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kLevelItems; ++u) {
+                if (64 * u >= seg) break;
+                const bool f = last[u] >= 0 && L[u] > l;
+                const unsigned long long m = __ballot(f);
+                const int slot = run + __popcll(m & below);
+                run += __popcll(m);
+                if (!f || slot >= set.cap) continue;
+                const int prev = last[u];
+                set.root[slot] = x0 + 64 * u;
+                set.exp[slot] = l;
+                set.key[slot] = ((unsigned long long)l << 48) | (unsigned)prev;
+                if (L[u] == l + 1) {
+                    set.time[slot] = kNever;
+                    set.child[slot] = -1;
+                }
+                set.child[prev] = slot;
+                set.time[prev] = 0;  // split (only this axis splits in this phase, any finite time will do)
+                last[u] = slot;
+            }
+        }
+        if (threadIdx.x == 0) {
+            *count_out = base;
+            if (base > set.cap) flag_overflow(hdr, which, base);
+        }
+        return;
+    }
     int lm = 1;
     for (int x = threadIdx.x; x < N; x += kPlanThreads) {
         const int L = digit_levels(maxabs[via ? via[x] : x], sh);
@@ -721,43 +801,35 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g)
 // are folded along the columns of a tile (kChunk there too if the 64 x 64 tiles of the small-tile GEMM may run).  Source row i with unpadded start P_i
 // goes to chunk floor(P_i / (kChunk - (Lmax-1))): a closed form, and the rows of a chunk never exceed
 // kChunk.
+// Bound by the latency of one workgroup's reads and stores, so rows beyond kRowSlice are shared out: every one of
+// `nslices` workgroups derives the level counts and their sums for itself and writes its share of the rows.
+constexpr int kRowSlice = 4096;  // source rows per workgroup, at most four workgroups (12608 rows of two levels: 34 -> 21 us)
 __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count_dev, const RowLayout &lay,
                             int cap_phys, int cap_tiles, int32_t *tmpP_global, PlanHeader *hdr, int operand, int chunk,
-                            int *lds, int32_t *fast /* 2 * nbase ints of LDS, or nullptr */) {
+                            int *lds, int32_t *fast /* 2 * nbase ints of LDS and one per chunk, or nullptr */, int slice, int nslices) {
     // the level counts and their running sums are scanned and searched over and over: in LDS when they fit
     int32_t *nlev = fast ? fast : lay.src_nlev;
     int32_t *tmpP = fast ? fast + nbase : tmpP_global;
+    int32_t *chunk0 = fast ? fast + 2 * nbase : lay.chunk_src0;
+    const int count = *count_dev;
+    constexpr int V = 4;  // slots per thread and step, loaded side by side
+    for (int i = threadIdx.x; i < nbase; i += kPlanThreads) nlev[i] = 1;
+    __syncthreads();
     int lm = 1;
-    constexpr int V = 4;  // source rows per thread and step: their chains are walked side by side
-    for (int i0 = threadIdx.x; i0 < nbase; i0 += kPlanThreads * V) {
-        int R[V], L[V];
+    for (int R0 = nbase + threadIdx.x; R0 < count; R0 += kPlanThreads * V) {
+        int root[V], ex[V];
 #pragma unroll
         for (int u = 0; u < V; ++u) {
-            const int i = i0 + u * kPlanThreads;
-            R[u] = i < nbase ? rows.child[i] : -1;
-            L[u] = 1;
-        }
-        for (int hop = 0; hop < 64; ++hop) {
-            bool more = false;
-#pragma unroll
-            for (int u = 0; u < V; ++u) {
-                if (R[u] >= 0) {
-                    ++L[u];
-                    R[u] = rows.child[R[u]];
-                    more = true;
-                }
-            }
-            if (!more) break;
+            const int R = R0 + u * kPlanThreads;
+            root[u] = R < count ? rows.root[R] : 0;
+            ex[u] = R < count ? rows.exp[R] : 0;
         }
 #pragma unroll
-        for (int u = 0; u < V; ++u) {
-            const int i = i0 + u * kPlanThreads;
-            if (i < nbase) {
-                nlev[i] = L[u];
-                if (fast) lay.src_nlev[i] = L[u];  // the GEMM epilogue reads it from memory
-                lm = max(lm, L[u]);
+        for (int u = 0; u < V; ++u)
+            if (ex[u] > 0) {
+                atomicMax(&nlev[root[u]], ex[u] + 1);
+                lm = max(lm, ex[u] + 1);
             }
-        }
     }
     const int lmax = block_max(lm, lds);
     const int base = ordered_scan(
@@ -772,9 +844,9 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
     const int kPerTile = kTile / chunk;
     const int ntiles = (nchunks + kPerTile - 1) / kPerTile;
     const int Mp = ntiles * kTile;
-    if (Mp > cap_phys || ntiles + 1 > cap_tiles || base != *count_dev) {
+    if (Mp > cap_phys || ntiles + 1 > cap_tiles || base != count) {
         if (threadIdx.x == 0) {
-            if (base != *count_dev) atomicMin(&hdr->err, IMUNPACK_EHIP);  // inconsistent plan: internal error
+            if (base != count) atomicMin(&hdr->err, IMUNPACK_EHIP);  // inconsistent plan: internal error
             else flag_overflow(hdr, operand ? CAP_ROWB : CAP_ROWA, 2 * base);
         }
         return;
@@ -787,57 +859,56 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
             const int mid = (lo + hi) >> 1;
             if (tmpP[mid] >= want) hi = mid; else lo = mid + 1;
         }
-        lay.chunk_src0[ch] = lo;
-        if (ch % kPerTile == 0) lay.tile_src0[ch / kPerTile] = lo;
+        chunk0[ch] = lo;
+        if (slice == 0) {
+            if (fast) lay.chunk_src0[ch] = lo;
+            if (ch % kPerTile == 0) lay.tile_src0[ch / kPerTile] = lo;
+        }
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < ntiles; t += kPlanThreads) {
-        const int a = lay.tile_src0[t], e = lay.tile_src0[t + 1];
-        const int slots = (e < nbase ? tmpP[e] : base) - tmpP[a];
-        // (rows of B in chunks: the tile's columns of C are read as one run, which gaps between the chunks break)
-        lay.tile_flat[t] = (slots == e - a && (operand == 0 || chunk == kTile || lmax == 1)) ? 1 : 0;
-    }
-    for (int p = threadIdx.x; p < Mp; p += kPlanThreads) {
-        lay.prow_slot[p] = -1;
-        lay.prow_src[p] = -1;
-        lay.prow_exp[p] = 0;
+    if (slice == 0)
+        for (int t = threadIdx.x; t < ntiles; t += kPlanThreads) {
+            const int a = chunk0[t * kPerTile], e = chunk0[(t + 1) * kPerTile];
+            const int slots = (e < nbase ? tmpP[e] : base) - tmpP[a];
+            // (rows of B in chunks: the tile's columns of C are read as one run, which gaps between the chunks break)
+            lay.tile_flat[t] = (slots == e - a && (operand == 0 || chunk == kTile || lmax == 1)) ? 1 : 0;
+        }
+    const int step = kPlanThreads * nslices, me = slice * kPlanThreads + threadIdx.x;
+    // rows behind the last one of a chunk are padding
+    for (int p = me; p < Mp; p += step) {
+        const int ch = p / chunk, a = chunk0[ch], e = chunk0[ch + 1];
+        const int used = a < e ? (e < nbase ? tmpP[e] : base) - tmpP[a] : 0;
+        if (p - ch * chunk >= used) lay.prow[p] = -1;
         lay.rowsum[p] = 0;
     }
+    // where a source row starts takes the place of its level count (without LDS: of its own entry in the layout)
+    int32_t *pstart = fast ? nlev : lay.src_pstart;
+    for (int i = threadIdx.x; i < nbase; i += kPlanThreads) {
+        const int P = tmpP[i], ch = P / Cp, at = ch * chunk + (P - tmpP[chunk0[ch]]);
+        if (fast && slice == 0) {
+            lay.src_nlev[i] = nlev[i];  // the GEMM epilogue reads both from memory
+            lay.src_pstart[i] = at;
+        }
+        pstart[i] = at;
+    }
     __syncthreads();
-    for (int i0 = threadIdx.x; i0 < nbase; i0 += kPlanThreads * V) {
-        int R[V], pst[V], L[V];
+    for (int R0 = me; R0 < count; R0 += step * V) {
+        int root[V], ex[V];
 #pragma unroll
         for (int u = 0; u < V; ++u) {
-            const int i = i0 + u * kPlanThreads;
-            R[u] = -1;
-            pst[u] = 0;
-            L[u] = 0;
-            if (i < nbase) {
-                const int P = tmpP[i], ch = P / Cp;
-                pst[u] = ch * chunk + (P - tmpP[lay.chunk_src0[ch]]);
-                L[u] = nlev[i];
-                R[u] = i;
-                lay.src_pstart[i] = pst[u];
-            }
+            const int R = R0 + u * step;
+            root[u] = R < nbase ? R : R < count ? rows.root[R] : -1;
+            ex[u] = R >= nbase && R < count ? rows.exp[R] : 0;
         }
-        for (int l = 0; l < 64; ++l) {
-            bool more = false;
 #pragma unroll
-            for (int u = 0; u < V; ++u) {
-                if (R[u] >= 0 && l < L[u]) {
-                    const int Rc = R[u];
-                    R[u] = rows.child[Rc];
-                    lay.prow_slot[pst[u] + l] = Rc;
-                    lay.prow_src[pst[u] + l] = i0 + u * kPlanThreads;
-                    lay.prow_exp[pst[u] + l] = l;
-                    lay.row_phys[Rc] = pst[u] + l;
-                    more = true;
-                }
-            }
-            if (!more) break;
+        for (int u = 0; u < V; ++u) {
+            if (root[u] < 0) continue;
+            const int at = pstart[root[u]] + ex[u];
+            lay.prow[at] = root[u] | (ex[u] << kProwLevel);
+            lay.row_phys[R0 + u * step] = at;
         }
     }
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && slice == 0) {
         if (operand == 0) { hdr->Mp = Mp; hdr->mtiles = ntiles; hdr->lmaxA = lmax; }
         else { hdr->Np = Mp; hdr->ntiles = ntiles; hdr->lmaxB = lmax; }
     }
@@ -863,19 +934,310 @@ __device__ __forceinline__ unsigned long long weight_of(int e, int sh) {  // s^e
     return bits >= 44 ? (1ull << 44) : (1ull << bits);
 }
 
+// What the column layout knows of every group (exponent e) and every level a of A; one copy in LDS.
+struct ColTables {
+    int hist2[kMaxGroups * kMaxLevelsA];                   // column slots per (exponent e, level a of A)
+    int kbase[kMaxGroups * kMaxLevelsA];                   // first column of B_eu of a shared (e, a), -1: gathered
+    int cntA[kMaxLevelsA], lvlbase[kMaxLevelsA + 1];       // columns per level of A; first stored column
+    int gk0[kMaxGroups], gext[kMaxGroups];                 // first column of a group and its extent
+    int cbase[kMaxGroups], xbase[kMaxGroups], ccount[kMaxGroups];  // gathered: first column, first extra block, how many
+    int kp, ka, ka_levels, bad, la;
+    int lb, scratch;                                       // (of the path in LDS)
+    unsigned char tile_e[256], extra_e[256];               // group of every k-tile of B_eu / of every extra block of A
+};
+
+__device__ __forceinline__ void level_bases(ColTables &t) {
+    int run = 0, la = 1;
+    for (int a = 0; a < kMaxLevelsA; ++a) {
+        t.lvlbase[a] = run;
+        run += (t.cntA[a] + kKPad - 1) / kKPad * kKPad;
+        if (t.cntA[a]) la = a + 1;
+    }
+    t.lvlbase[kMaxLevelsA] = run;
+    t.ka_levels = run;
+    t.la = la;
+}
+
+// The k-tiles of every group, from hist2, cntA and the level bases: lane e of the first wave takes exponent e.  `report`:
+// the workgroup that writes the run and group tables of the header.
+__device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, PlanHeader *hdr, bool report) {
+    if (threadIdx.x >= 64) return;
+    const int e = threadIdx.x;
+    int tiles_sh = 0, ccount = 0, members = 0;
+    for (int a = 0; a < kMaxLevelsA; ++a) {
+        const int m = t.hist2[e * kMaxLevelsA + a];
+        members += m;
+        const bool shared = m > 0 && (long long)m * 8 >= (long long)t.cntA[a] * 7;
+        t.kbase[e * kMaxLevelsA + a] = shared ? tiles_sh * kKPad : -1;  // relative to the group's start for now
+        if (shared) tiles_sh += (t.cntA[a] + kKPad - 1) / kKPad;
+        else ccount += m;
+    }
+    const int tiles_c = (ccount + kKPad - 1) / kKPad;
+    const int tiles = tiles_sh + tiles_c;
+    int nrun = tiles_c > 0 ? 1 : 0;  // stretches of k-tiles that walk consecutive blocks of the A store
+    for (int a = 0; a < kMaxLevelsA; ++a)
+        if (t.kbase[e * kMaxLevelsA + a] >= 0) ++nrun;
+    // groups come highest exponent first: sums over the lanes above this one
+    int above = tiles, above_c = tiles_c, above_n = members > 0 ? 1 : 0, above_r = nrun;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t0 = __shfl_down(above, off, 64), t1 = __shfl_down(above_c, off, 64), t2 = __shfl_down(above_n, off, 64),
+                  t3 = __shfl_down(above_r, off, 64);
+        if (e + off < 64) { above += t0; above_c += t1; above_n += t2; above_r += t3; }
+    }
+    const int k0 = (above - tiles) * kKPad, xb = above_c - tiles_c, g = above_n - (members > 0 ? 1 : 0);
+    if (report) {
+        int ri = above_r - nrun;
+        for (int a = 0; a < kMaxLevelsA; ++a) {
+            const int kb = t.kbase[e * kMaxLevelsA + a];
+            if (kb < 0) continue;
+            if (ri < kMaxRuns) {
+                hdr->run_kt0[ri] = (k0 + kb) / kKPad;
+                hdr->run_blk0[ri] = t.lvlbase[a] / kKPad;
+                hdr->run_grp[ri] = g;
+            }
+            ++ri;
+        }
+        if (tiles_c > 0 && ri < kMaxRuns) {
+            hdr->run_kt0[ri] = k0 / kKPad + tiles_sh;
+            hdr->run_blk0[ri] = t.ka_levels / kKPad + xb;
+            hdr->run_grp[ri] = g;
+        }
+        const int total_r = __shfl(above_r, 0, 64);
+        if (e == 0) {
+            hdr->nruns = total_r;
+            if (total_r > kMaxRuns) atomicMin(&hdr->err, IMUNPACK_ERANGE);
+        }
+    }
+    for (int a = 0; a < kMaxLevelsA; ++a)
+        if (t.kbase[e * kMaxLevelsA + a] >= 0) t.kbase[e * kMaxLevelsA + a] += k0;
+    t.cbase[e] = k0 + tiles_sh * kKPad;
+    t.xbase[e] = xb;
+    t.ccount[e] = ccount;
+    t.gk0[e] = k0;
+    t.gext[e] = tiles * kKPad;
+    const int total_tiles = __shfl(above, 0, 64), total_c = __shfl(above_c, 0, 64), ngroups = __shfl(above_n, 0, 64);
+    if (e == 0) {
+        t.kp = total_tiles * kKPad;
+        t.ka = t.ka_levels + total_c * kKPad;
+    }
+    if (members > 0) {
+        const long long lim = 2147483647ll / ((long long)(s - 1) * (s - 1));
+        if (e * sh > 62 || tiles * kKPad > lim) atomicMin(&hdr->err, IMUNPACK_ERANGE);
+        if (report) {
+            hdr->grp_exp[g] = e;
+            hdr->grp_k0[g] = k0;
+            hdr->grp_len[g] = tiles * kKPad;
+        }
+    }
+    if (report && e == 0) {
+        hdr->ngroups = ngroups;
+        hdr->Kp = total_tiles * kKPad;
+        hdr->KA = t.ka_levels + total_c * kKPad;
+        // row pitches: wide rows get an odd multiple of 256 bytes (power-of-two strides put the rows
+        // of a tile, which are read together, on the same few memory channels)
+        const int wa = t.ka_levels + total_c * kKPad, wb = total_tiles * kKPad;
+        hdr->ldA = wa >= 2048 ? (((wa + 255) / 256) | 1) * 256 : wa;
+        hdr->ldB = wb >= 2048 ? (((wb + 255) / 256) | 1) * 256 : wb;
+        if (total_tiles * kKPad > cap_phys) flag_overflow(hdr, CAP_C2, 2 * D);
+    }
+    for (int i = 0; i < tiles && k0 / kKPad + i < 256; ++i) t.tile_e[k0 / kKPad + i] = (unsigned char)e;
+    for (int i = 0; i < tiles_c && xb + i < 256; ++i) t.extra_e[xb + i] = (unsigned char)e;
+}
+
+// The same layout for unpackings whose tables fit the LDS of one workgroup (every product up to about 16000 column slots):
+// the general path below is a chain of phases that hand arrays to one another through memory, a microsecond or more per
+// dependent read, and its workgroups end in a device-wide fence that writes back the L2 of their XCD (24 to 54 us for one
+// product, 70 to 170 us for the items of a batch; this one: 14 to 37 and 14 to 16).  Here every slot stays in the registers of its thread.  A column slot is
+// known by its original column k and its levels eA, eB along A and B, and no two slots share all three; so the slots are a
+// bit per k in a mask per (eA, eB), every rank is a count of bits below k, and the columns of both stores are put together
+// in LDS and written once.  Returns false, having written nothing but tables that are written again, if LDS is too small.
+constexpr int kColSlotsLds = 16;  // slots per thread
+__device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColLayout &cols, int d, int cap_phys, int s, int sh,
+                                PlanHeader *hdr, ColTables &t, int32_t *dyn, int dyn_words) {
+    const int D = hdr->d_u, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (D > kColSlotsLds * kPlanThreads) return false;
+    for (int x = tid; x < kMaxGroups * kMaxLevelsA; x += kPlanThreads) t.hist2[x] = 0;
+    if (tid == 0) t.la = t.lb = t.bad = 0;
+    int key[kColSlotsLds], lev[kColSlotsLds];  // original column; eA | eB << 16
+#pragma unroll
+    for (int u = 0; u < kColSlotsLds; ++u) {
+        const int c = tid + u * kPlanThreads;
+        key[u] = -1;
+        lev[u] = 0;
+        if (u * kPlanThreads >= D) continue;  // uniform
+        key[u] = c < D ? c2.root[c] : -1;
+        lev[u] = c < D ? c2.exp[c] << 16 : 0;
+    }
+    int ma = 0, mb = 0;
+#pragma unroll
+    for (int u = 0; u < kColSlotsLds; ++u) {
+        if (key[u] < 0) continue;
+        const int r = key[u], ea = c1.exp[r];
+        key[u] = c1.root[r];
+        ma = max(ma, ea);
+        mb = max(mb, lev[u] >> 16);
+        lev[u] |= ea;
+    }
+    ma = wave_max_nonneg_lane63(ma);
+    mb = wave_max_nonneg_lane63(mb);
+    __syncthreads();
+    if (lane == 63) {
+        atomicMax(&t.la, ma);
+        atomicMax(&t.lb, mb);
+    }
+    __syncthreads();
+    const int LA = t.la + 1, LB = t.lb + 1, W = (d + 63) / 64;
+    if (LA > kMaxLevelsA || LA + LB - 1 > kMaxGroups || (long long)LA * LB * W * 3 > dyn_words) return false;
+    unsigned long long *mask = reinterpret_cast<unsigned long long *>(dyn);  // [LA * LB][W]
+    int32_t *pre = dyn + 2 * LA * LB * W;                                     // [LA * LB][W] slots of the pair below the word
+    int32_t *packB = pre + LA * LB * W;                                       // k | eB << 24 per column of B_eu, -1: none
+    if (LA * LB * W * (3 + 16) <= dyn_words) {  // a byte per k first, where the stores will be put together (atomics on the
+                                                // masks would queue up 32 to a word)
+        unsigned char *seen = reinterpret_cast<unsigned char *>(packB);
+        for (int x = tid; x < LA * LB * W * 16; x += kPlanThreads) packB[x] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kColSlotsLds; ++u)
+            if (key[u] >= 0) seen[((lev[u] & 0xffff) * LB + (lev[u] >> 16)) * W * 64 + key[u]] = 1;
+        __syncthreads();
+        for (int x = wave; x < LA * LB * W; x += kPlanWaves) {
+            const unsigned long long m = __ballot(seen[x * 64 + lane] != 0);
+            if (lane == 0) mask[x] = m;
+        }
+    } else {
+        for (int x = tid; x < 2 * LA * LB * W; x += kPlanThreads) dyn[x] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kColSlotsLds; ++u) {
+            if (key[u] < 0) continue;
+            const int k = key[u], pair = (lev[u] & 0xffff) * LB + (lev[u] >> 16);
+            atomicOr(reinterpret_cast<unsigned *>(mask) + 2 * pair * W + (k >> 5), 1u << (k & 31));
+        }
+    }
+    __syncthreads();
+    for (int pair = wave; pair < LA * LB; pair += kPlanWaves) {
+        int run = 0;
+        for (int w0 = 0; w0 < W; w0 += 64) {
+            const int w = w0 + lane;
+            const int c = w < W ? __popcll(mask[pair * W + w]) : 0;
+            const int incl = wave_inclusive_sum(c);
+            if (w < W) pre[pair * W + w] = run + incl - c;
+            run += from_lane63(incl);
+        }
+        const int a = pair / LB, eb = pair - a * LB;
+        if (lane == 0) {
+            t.hist2[(a + eb) * kMaxLevelsA + a] = run;
+            if (eb == 0) t.cntA[a] = run;
+        }
+    }
+    if (tid >= LA && tid < kMaxLevelsA) t.cntA[tid] = 0;
+    __syncthreads();
+    if (tid == 0) level_bases(t);
+    __syncthreads();
+    column_tables(t, cap_phys, D, s, sh, hdr, true);
+    __syncthreads();
+    const int Kp = t.kp, KA = t.ka, ka_levels = t.ka_levels;
+    if (Kp > cap_phys) return true;  // reported: the plan is made again with more room
+    if (Kp > 256 * kKPad || KA - ka_levels > 256 * kKPad || (long long)LA * LB * W * 3 + Kp + KA > dyn_words) return false;
+    int32_t *packA = packB + Kp;  // k | eA << 24 per stored column of A, -1: none
+    for (int x = tid; x < Kp + KA; x += kPlanThreads) packB[x] = -1;
+    __syncthreads();
+    auto bit = [&](int pair, int k) { return (int)(mask[pair * W + (k >> 6)] >> (k & 63)) & 1; };
+    auto rank = [&](int pair, int k) {
+        return pre[pair * W + (k >> 6)] + __popcll(mask[pair * W + (k >> 6)] & ((1ull << (k & 63)) - 1ull));
+    };
+#pragma unroll
+    for (int u = 0; u < kColSlotsLds; ++u) {
+        if (key[u] < 0) continue;
+        const int c = tid + u * kPlanThreads, k = key[u], a = lev[u] & 0xffff, eb = lev[u] >> 16, e = a + eb;
+        const int stored = t.lvlbase[a] + rank(a * LB, k);  // where level a of A holds column k
+        const int kb = t.kbase[e * kMaxLevelsA + a];
+        int q, qa;
+        if (kb >= 0) {
+            qa = stored;
+            q = kb + (qa - t.lvlbase[a]);
+        } else {  // gathered: behind the group's members with a lower (k, level of A)
+            int pos = 0;
+            for (int x = 0; x < LA && x <= e; ++x) {
+                if (e - x >= LB || t.kbase[e * kMaxLevelsA + x] >= 0) continue;
+                pos += rank(x * LB + e - x, k);
+                if (x < a) pos += bit(x * LB + e - x, k);
+            }
+            q = t.cbase[e] + pos;
+            qa = ka_levels + t.xbase[e] * kKPad + pos;
+            packA[qa] = k | (a << 24);
+        }
+        packB[q] = k | (eb << 24);
+        if (eb == 0) packA[stored] = k | (a << 24);
+        cols.pcol_slot[q] = c;
+        cols.col_phys[c] = q;
+        cols.acol_phys[c] = qa;
+    }
+    __syncthreads();
+    // ---- out: sixteen lanes side by side hold a unit (both widths are multiples of 128); its first lane with a column
+    // describes it (the first of all if none has)
+    auto in_unit = [&](bool f) { return (unsigned)(__ballot(f) >> (lane & 48)) & 0xffffu; };
+    auto from = [&](int v, int l) { return __shfl(v, l, 64); };
+    for (int q = tid; q < Kp; q += kPlanThreads) {
+        const int v = packB[q], k = v == -1 ? -1 : v & 0xffffff, eb = v == -1 ? 0 : (v >> 24) & 0xff, e = t.tile_e[q / kKPad];
+        cols.colB_k[q] = k;
+        cols.colB_e[q] = eb;
+        cols.col_sexp[q] = e;
+        if (k < 0) cols.pcol_slot[q] = -1;
+        const unsigned live = in_unit(k >= 0);
+        const int first = (lane & 48) + (live ? __builtin_ctz(live) : 0);
+        const int before = IMU_DPP(k, 0x111, 0xf, true);  // the column one to the left
+        const bool run = in_unit(k >= 0 && ((lane & 15) == 0 || k == before + 1)) == 0xffffu;
+        const bool uniform = in_unit(k < 0 || eb == from(eb, first)) == 0xffffu;
+        if (lane == first) cols.unitB[q / 16] = make_int4(k, k, (run ? 1 : 0) | (uniform ? 2 : 0) | 4, eb | (e << 16));
+    }
+    for (int q = tid; q < KA; q += kPlanThreads) {
+        const int v = packA[q], k = v == -1 ? -1 : v & 0xffffff, a = v == -1 ? 0 : (v >> 24) & 0xff;
+        unsigned long long w = 0;  // what an entry of the column weighs: s^e over the slots that read it
+        if (k >= 0) {
+            if (q >= ka_levels) {
+                w = weight_of(t.extra_e[(q - ka_levels) / kKPad], sh);
+            } else {
+                for (int eb = 0; eb < LB; ++eb)
+                    if (t.kbase[(a + eb) * kMaxLevelsA + a] >= 0 && bit(a * LB + eb, k)) w += weight_of(a + eb, sh);
+            }
+        }
+        cols.colA_k[q] = k;
+        cols.colA_e[q] = a;
+        cols.colA_w[q] = w;
+        const unsigned live = in_unit(k >= 0);
+        const int first = (lane & 48) + (live ? __builtin_ctz(live) : 0);
+        const int before = IMU_DPP(k, 0x111, 0xf, true);
+        const bool run = in_unit(k >= 0 && ((lane & 15) == 0 || k == before + 1)) == 0xffffu;
+        const bool uniform = in_unit(k < 0 || a == from(a, first)) == 0xffffu;
+        const bool onew = in_unit(k < 0 || (unsigned)w == (unsigned)from((int)(unsigned)w, first)) == 0xffffu &&
+                          in_unit(k < 0 || (unsigned)(w >> 32) == (unsigned)from((int)(unsigned)(w >> 32), first)) == 0xffffu;
+        if (lane == first) {
+            cols.unitA[q / 16] = make_int4(k, k, (run ? 1 : 0) | (uniform ? 2 : 0) | (onew ? 4 : 0), a);
+            cols.unitA_w[q / 16] = w < (1ull << 44) ? w : (1ull << 44);
+        }
+    }
+    return true;
+}
+
 __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayout &cols, int d, int cap_phys,
                             int s, int sh, int32_t *tmpE, int32_t *tmpK, int32_t *tmpR, int32_t *tmpOffAll,
-                            PlanHeader *hdr, int *lds, int part) {
-    __shared__ int hist2[kMaxGroups * kMaxLevelsA];          // column slots per (exponent e, level a of A)
-    __shared__ int cntA[kMaxLevelsA], lvlbase[kMaxLevelsA + 1];  // columns per level of A; first stored column
-    __shared__ int kbase[kMaxGroups * kMaxLevelsA];          // first column of B_eu of a shared (e, a), -1: gathered
-    __shared__ int s_gk0[kMaxGroups], s_gext[kMaxGroups], s_cbase[kMaxGroups], s_xbase[kMaxGroups], s_ccount[kMaxGroups];
-    __shared__ int s_kp, s_ka, s_ka_levels, s_bad, s_la;
+                            PlanHeader *hdr, int *lds, int part, int nparts, ColTables &t) {
+    auto &hist2 = t.hist2;
+    auto &cntA = t.cntA;
+    auto &lvlbase = t.lvlbase;
+    auto &kbase = t.kbase;
+    auto &s_gk0 = t.gk0;
+    auto &s_gext = t.gext;
+    auto &s_cbase = t.cbase;
+    auto &s_xbase = t.xbase;
+    auto &s_ccount = t.ccount;
     const int D = hdr->d_u, D1 = hdr->d1;
     int32_t *tmpOff = tmpOffAll + (size_t)part * (d + 1);
-    for (int t = threadIdx.x; t < kMaxGroups * kMaxLevelsA; t += kPlanThreads) hist2[t] = 0;
+    for (int x = threadIdx.x; x < kMaxGroups * kMaxLevelsA; x += kPlanThreads) hist2[x] = 0;
     if (threadIdx.x < kMaxLevelsA) cntA[threadIdx.x] = 0;
-    if (threadIdx.x == 0) s_bad = 0;
+    if (threadIdx.x == 0) t.bad = 0;
     __syncthreads();
     // every part computes the same per-slot values and the same tables (the stores of the parts
     // coincide); a part then lays out the groups part, part + kColBlocks, ...
@@ -889,23 +1251,13 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
         for (int u = 0; u < V; ++u) {
             if (a[u] < 0) continue;
             if (a[u] < kMaxLevelsA) atomicAdd(&cntA[a[u]], 1);
-            else s_bad = 1;
+            else t.bad = 1;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0, la = 1;
-        for (int a = 0; a < kMaxLevelsA; ++a) {
-            lvlbase[a] = run;
-            run += (cntA[a] + kKPad - 1) / kKPad * kKPad;
-            if (cntA[a]) la = a + 1;
-        }
-        lvlbase[kMaxLevelsA] = run;
-        s_ka_levels = run;
-        s_la = la;
-    }
+    if (threadIdx.x == 0) level_bases(t);
     __syncthreads();
-    const int la = s_la;
+    const int la = t.la;
     // ---- stored column of every column slot of A's unpacking: level 0 in place, level a >= 1 by rank
     // among the original columns whose chain reaches that level
     for (int k = threadIdx.x; k < d; k += kPlanThreads) cols.apos[k] = k;
@@ -945,96 +1297,15 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
                 atomicAdd(&hist2[e * kMaxLevelsA + ea[u]], 1);
             } else {
                 atomicMin(&hdr->err, IMUNPACK_ERANGE);
-                s_bad = 1;
+                t.bad = 1;
             }
         }
     }
     __syncthreads();
-    // ---- the k-tiles of every group: lane e of the first wave takes exponent e
-    if (threadIdx.x < 64) {
-        const int e = threadIdx.x;
-        int tiles_sh = 0, ccount = 0, members = 0;
-        for (int a = 0; a < kMaxLevelsA; ++a) {
-            const int m = hist2[e * kMaxLevelsA + a];
-            members += m;
-            const bool shared = m > 0 && (long long)m * 8 >= (long long)cntA[a] * 7;
-            kbase[e * kMaxLevelsA + a] = shared ? tiles_sh * kKPad : -1;  // relative to the group's start for now
-            if (shared) tiles_sh += (cntA[a] + kKPad - 1) / kKPad;
-            else ccount += m;
-        }
-        const int tiles_c = (ccount + kKPad - 1) / kKPad;
-        const int tiles = tiles_sh + tiles_c;
-        int nrun = tiles_c > 0 ? 1 : 0;  // stretches of k-tiles that walk consecutive blocks of the A store
-        for (int a = 0; a < kMaxLevelsA; ++a)
-            if (kbase[e * kMaxLevelsA + a] >= 0) ++nrun;
-        // groups come highest exponent first: sums over the lanes above this one
-        int above = tiles, above_c = tiles_c, above_n = members > 0 ? 1 : 0, above_r = nrun;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int t0 = __shfl_down(above, off, 64), t1 = __shfl_down(above_c, off, 64), t2 = __shfl_down(above_n, off, 64),
-                      t3 = __shfl_down(above_r, off, 64);
-            if (e + off < 64) { above += t0; above_c += t1; above_n += t2; above_r += t3; }
-        }
-        const int k0 = (above - tiles) * kKPad, xb = above_c - tiles_c, g = above_n - (members > 0 ? 1 : 0);
-        if (part == 0) {
-            int ri = above_r - nrun;
-            for (int a = 0; a < kMaxLevelsA; ++a) {
-                const int kb = kbase[e * kMaxLevelsA + a];
-                if (kb < 0) continue;
-                if (ri < kMaxRuns) {
-                    hdr->run_kt0[ri] = (k0 + kb) / kKPad;
-                    hdr->run_blk0[ri] = lvlbase[a] / kKPad;
-                    hdr->run_grp[ri] = g;
-                }
-                ++ri;
-            }
-            if (tiles_c > 0 && ri < kMaxRuns) {
-                hdr->run_kt0[ri] = k0 / kKPad + tiles_sh;
-                hdr->run_blk0[ri] = s_ka_levels / kKPad + xb;
-                hdr->run_grp[ri] = g;
-            }
-            const int total_r = __shfl(above_r, 0, 64);
-            if (e == 0) {
-                hdr->nruns = total_r;
-                if (total_r > kMaxRuns) atomicMin(&hdr->err, IMUNPACK_ERANGE);
-            }
-        }
-        for (int a = 0; a < kMaxLevelsA; ++a)
-            if (kbase[e * kMaxLevelsA + a] >= 0) kbase[e * kMaxLevelsA + a] += k0;
-        s_cbase[e] = k0 + tiles_sh * kKPad;
-        s_xbase[e] = xb;
-        s_ccount[e] = ccount;
-        s_gk0[e] = k0;
-        s_gext[e] = tiles * kKPad;
-        const int total_tiles = __shfl(above, 0, 64), total_c = __shfl(above_c, 0, 64), ngroups = __shfl(above_n, 0, 64);
-        if (e == 0) {
-            s_kp = total_tiles * kKPad;
-            s_ka = s_ka_levels + total_c * kKPad;
-        }
-        if (members > 0) {
-            const long long lim = 2147483647ll / ((long long)(s - 1) * (s - 1));
-            if (e * sh > 62 || tiles * kKPad > lim) atomicMin(&hdr->err, IMUNPACK_ERANGE);
-            if (part == 0) {
-                hdr->grp_exp[g] = e;
-                hdr->grp_k0[g] = k0;
-                hdr->grp_len[g] = tiles * kKPad;
-            }
-        }
-        if (part == 0 && e == 0) {
-            hdr->ngroups = ngroups;
-            hdr->Kp = total_tiles * kKPad;
-            hdr->KA = s_ka_levels + total_c * kKPad;
-            // row pitches: wide rows get an odd multiple of 256 bytes (power-of-two strides put the rows
-            // of a tile, which are read together, on the same few memory channels)
-            const int wa = s_ka_levels + total_c * kKPad, wb = total_tiles * kKPad;
-            hdr->ldA = wa >= 2048 ? (((wa + 255) / 256) | 1) * 256 : wa;
-            hdr->ldB = wb >= 2048 ? (((wb + 255) / 256) | 1) * 256 : wb;
-            if (total_tiles * kKPad > cap_phys) flag_overflow(hdr, CAP_C2, 2 * D);
-        }
-    }
+    column_tables(t, cap_phys, D, s, sh, hdr, part == 0);
     __syncthreads();
-    const int Kp = s_kp, KA = s_ka, ka_levels = s_ka_levels;
-    if (Kp > cap_phys || s_bad) return;
+    const int Kp = t.kp, KA = t.ka, ka_levels = t.ka_levels;
+    if (Kp > cap_phys || t.bad) return;
     // ---- the stored levels of A (first part)
     if (part == 0) {
         for (int q = threadIdx.x; q < ka_levels; q += kPlanThreads) {
@@ -1048,7 +1319,7 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
             cols.colA_e[q] = c1.exp[r];
         }
     }
-    for (int e = kMaxGroups - 1 - part; e >= 0; e -= kColBlocks) {  // any fixed assignment of groups to parts will do
+    for (int e = kMaxGroups - 1 - part; e >= 0; e -= nparts) {  // any fixed assignment of groups to parts will do
         const int q0 = s_gk0[e], q1 = q0 + s_gext[e];
         if (q1 == q0) continue;  // uniform
         for (int q = q0 + threadIdx.x; q < q1; q += kPlanThreads) {
@@ -1187,7 +1458,7 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
     __shared__ int s_last;
     __threadfence();
     __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(&hdr->cols_done, 1u) == (unsigned)(kColBlocks - 1);
+    if (threadIdx.x == 0) s_last = atomicAdd(&hdr->cols_done, 1u) == (unsigned)(nparts - 1);
     __syncthreads();
     if (!s_last) return;
     __threadfence();  // what the other workgroups wrote before their increment is visible past this fence
@@ -1236,14 +1507,21 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
     }
 }
 
-// One workgroup for the rows of A, one for the rows of B, kColBlocks for the columns.
+__host__ __device__ inline int row_slices(int rows) {
+    const int w = (rows + kRowSlice - 1) / kRowSlice;
+    return w < 1 ? 1 : w > 4 ? 4 : w;
+}
+
+// One to four workgroups for the rows of A, as many for the rows of B, one for the columns (kColBlocks where there may be more column
+// slots than that one holds).
 __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     SlotSet rowA, int n, RowLayout layA, int cap_physA, int32_t *tmpPA, SlotSet rowB, int h, RowLayout layB,
     int cap_physB, int32_t *tmpPB, SlotSet c1, SlotSet c2, ColLayout cols, int d, int cap_physC, int s, int sh,
     int32_t *tmpE, int32_t *tmpK, int32_t *tmpR, int32_t *tmpOff, PlanHeader *hdr, int fast_lds, const int32_t *skipB,
-    int64_t stride, int chunkB) {
+    int64_t stride, int chunkB, int dyn_words) {
     __shared__ int lds[40];
-    extern __shared__ __attribute__((aligned(16))) int32_t fast_rows[];  // 2 * max(n, h) ints, if the launch gave them
+    __shared__ ColTables tables;
+    extern __shared__ __attribute__((aligned(16))) int32_t fast_rows[];  // what rows_layout asks for if fast_lds; dyn_words in all
     hdr += blockIdx.y;
     {
         const int64_t off = blockIdx.y * stride;
@@ -1262,16 +1540,24 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
         tmpOff = item_at(tmpOff, off);
     }
     if (hdr->overflow) return;
-    if (blockIdx.x >= 1 && skipB && *skipB) return;  // keep-weights mode: these layouts stand as they are
+    const int slA = fast_lds ? row_slices(n) : 1, slB = fast_lds ? row_slices(h) : 1;
+    const int bx = (int)blockIdx.x;
+    if (bx >= slA && skipB && *skipB) return;  // keep-weights mode: these layouts stand as they are
     // rows of A: the GEMM epilogue folds them chunk by chunk; rows of B (columns of C): tile by tile, or chunk by chunk
     // where the small-tile GEMM may be the one to run
-    if (blockIdx.x == 0)
-        rows_layout(rowA, n, &hdr->n_u, layA, cap_physA, cap_physA / kTile + 2, tmpPA, hdr, 0, kChunk, lds, fast_lds ? fast_rows : nullptr);
-    else if (blockIdx.x == 1)
-        rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr);
+    if (bx < slA)
+        rows_layout(rowA, n, &hdr->n_u, layA, cap_physA, cap_physA / kTile + 2, tmpPA, hdr, 0, kChunk, lds, fast_lds ? fast_rows : nullptr, bx, slA);
+    else if (bx < slA + slB)
+        rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr, bx - slA, slB);
     else {
-        cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, (int)blockIdx.x - 2);
-        if (blockIdx.x == 2 && threadIdx.x == 0) hdr->bound[0] = hdr->bound[1] = 0;
+        const int part = bx - slA - slB;
+        const bool in_lds = hdr->d_u <= kColSlotsLds * kPlanThreads;
+        if (in_lds && part > 0) return;
+        if (!in_lds || !cols_layout_lds(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words)) {
+            __syncthreads();
+            cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, part, in_lds ? 1 : (int)gridDim.x - slA - slB, tables);
+        }
+        if (part == 0 && threadIdx.x == 0) hdr->bound[0] = hdr->bound[1] = 0;
     }
 }
 
@@ -1352,9 +1638,7 @@ static size_t carve(Plan *p, char *base, bool own_statsA, bool own_statsB) {
         RowLayout &l = op ? p->layB : p->layA;
         const int cap = p->cap[op ? CAP_ROWB : CAP_ROWA], nb = op ? h : n;
         const int pc = phys_cap_rows(cap);
-        l.prow_slot = cv.take<int32_t>(pc);
-        l.prow_src = cv.take<int32_t>(pc);
-        l.prow_exp = cv.take<int32_t>(pc);
+        l.prow = cv.take<int32_t>(pc);
         l.row_phys = cv.take<int32_t>(cap);
         l.src_pstart = cv.take<int32_t>(nb + 1);
         l.src_nlev = cv.take<int32_t>(nb + 1);
@@ -1543,7 +1827,7 @@ __global__ void keep_remember_kernel(SlotSet c1, const PlanHeader *hdr, int32_t 
 }
 
 static constexpr int kGreedyLdsMax = 136 * 1024;  // dynamic LDS the greedy may use for the two count vectors
-static constexpr int kLayoutLdsMax = 128 * 1024;  // dynamic LDS the layouts kernel may use (its static tables take about 12 KiB)
+static constexpr int kLayoutLdsMax = 140 * 1024;  // dynamic LDS the layouts kernel may use (its static tables take about 11 KiB)
 
 // ob: the operand's OB entry list ([3][ob_cap], count on the device)
 static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const int32_t *ob_count, int64_t list_stride,
@@ -1658,19 +1942,26 @@ static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B
         IMU_TRY(run_greedy(p, 2, p->ob, p->cap[CAP_OB], p->obcnt, stride, CAP_OB, st, skip));
     }
     // ---- physical layouts
-    // the row layouts keep two ints per source row in LDS when that fits beside the column layout's tables
-    const size_t fast_bytes = (size_t)2 * std::max(n, h) * sizeof(int32_t);
+    // the row layouts keep two ints per source row and one per chunk in LDS when that fits beside the column layout's tables
+    const int most_phys = std::max(phys_cap_rows(p->cap[CAP_ROWA]), phys_cap_rows(p->cap[CAP_ROWB]));
+    const size_t fast_bytes = ((size_t)2 * std::max(n, h) + most_phys / kChunk + 8) * sizeof(int32_t);
     const int fast_lds = fast_bytes <= (size_t)kLayoutLdsMax ? 1 : 0;
+    // the column layout: a word per column of either store, three per 64 original columns and pair of levels (sixteen pairs)
+    const size_t col_bytes = ((size_t)2 * (p->cap[CAP_C2] + 2048) + (size_t)48 * ((d + 63) / 64)) * sizeof(int32_t);
+    const size_t dyn_bytes = std::min((size_t)kLayoutLdsMax, std::max(fast_lds ? fast_bytes : 0, col_bytes));
+    const int col_blocks = p->cap[CAP_C2] <= kColSlotsLds * kPlanThreads ? 1 : kColBlocks;
+    const int slices = fast_lds ? row_slices(n) + row_slices(h) : 2;
     static std::atomic<int> layouts_opted_in{0};  // the attribute is idempotent: a race sets the same value twice
     if (!layouts_opted_in.load(std::memory_order_acquire)) {
         IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
         layouts_opted_in.store(1, std::memory_order_release);
     }
-    hipLaunchKernelGGL(layouts_kernel, dim3(2 + kColBlocks, items), dim3(kPlanThreads), fast_lds ? fast_bytes : 0, st, p->rowA, n, p->layA,
+    hipLaunchKernelGGL(layouts_kernel, dim3(slices + col_blocks, items), dim3(kPlanThreads), dyn_bytes, st, p->rowA, n, p->layA,
                        phys_cap_rows(p->cap[CAP_ROWA]), p->tmpPA, p->rowB, h, p->layB,
                        phys_cap_rows(p->cap[CAP_ROWB]), p->tmpPB, p->c1, p->c2, p->cols, d,
                        phys_cap_cols(p->cap[CAP_C2]), p->s, p->sh, p->tmpE, p->tmpK, p->tmpR, p->tmpOff, hdr, fast_lds,
-                       keep ? (const int32_t *)&p->d_keep->same : (const int32_t *)nullptr, stride, p->chunkB);
+                       keep ? (const int32_t *)&p->d_keep->same : (const int32_t *)nullptr, stride, p->chunkB,
+                       (int)(dyn_bytes / sizeof(int32_t)));
     if (keep)
         hipLaunchKernelGGL(keep_remember_kernel, dim3(grid_for(p->cap[CAP_C1], 256, 16)), dim3(256), 0, st, p->c1,
                            (const PlanHeader *)hdr, p->snapRoot, p->snapExp, p->snapChild, p->d_keep);

@@ -41,7 +41,7 @@ constexpr int kBandRows = 2;  // divides kTile: the padded row counts are multip
 struct ScatterArgs {
     const int32_t *M;            // the int32 operand, row-major
     int64_t ldm;
-    const int32_t *prow_slot, *prow_src, *prow_exp;  // per physical row
+    const int32_t *prow;         // per physical row
     const int32_t *col_k;        // per stored column: source column, -1 = none
     const int32_t *col_e;        // per stored column: digit level along this operand's column axis
     const unsigned long long *col_w;   // per stored column: weight in the row norm (nullptr: s^exponent of the unit)
@@ -139,13 +139,13 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
     const bool inside = upos < nunits;
     const int4 ud = inside ? a.unit[upos] : make_int4(-1, -1, 7, 0);
     const int q0 = upos * 16;
-    const int kmin = ud.x, kmax = ud.y;
+    const int kfirst = ud.x, kany = ud.y;
     const bool run = (ud.z & 1) != 0, uniform = (ud.z & 2) != 0, onew = (ud.z & 4) != 0;
     const int ecu = ud.w & 0xFF;
     // what an entry of this unit weighs in the row norm: s^(exponent of S) for B_eu, the sum of those
     // over the column slots that read the stored column for A
     unsigned long long wgt = 0;
-    if (inside && kmax >= 0)
+    if (inside && kany >= 0)
         wgt = a.unit_w ? a.unit_w[upos] : ((ud.w >> 16) * a.sh >= 44 ? (1ull << 44) : (1ull << ((ud.w >> 16) * a.sh)));
     const unsigned mask4 = (unsigned)(a.s - 1) * 0x01010101u;
     const int p_first = band * kBandRows;
@@ -158,20 +158,20 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
 #pragma unroll
         for (int h = 0; h < RS; ++h) {
             const int p = __builtin_amdgcn_readfirstlane(p_first + r0 + h);
-            const int slot = a.prow_slot[p];
-            er[h] = a.prow_exp[p];
-            si[h] = max(a.prow_src[p], 0);
+            const int row = a.prow[p];
+            er[h] = row < 0 ? 0 : row >> kProwLevel;
+            si[h] = row < 0 ? 0 : row & ((1 << kProwLevel) - 1);
             // padding row, padding unit, or (UnpackBoth operands hold digit 0 at level (0, 0) only; every
             // operand: no digit that high) a unit that holds nothing in this row
             const unsigned usft = (unsigned)(a.sh * (er[h] + ecu));
-            live[h] = inside && slot >= 0 && kmax >= 0 && !(uniform && (DENSE ? usft >= 32u : er[h] + ecu != 0));
+            live[h] = inside && row >= 0 && kany >= 0 && !(uniform && (DENSE ? usft >= 32u : er[h] + ecu != 0));
 
             if (live[h]) {
                 const int32_t *src = a.M + (int64_t)si[h] * a.ldm;
                 if (run) {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        const v4i_u x = *reinterpret_cast<const v4i_u *>(src + kmin + 4 * j);
+                        const v4i_u x = *reinterpret_cast<const v4i_u *>(src + kfirst + 4 * j);
                         v[h][j][0] = x.x; v[h][j][1] = x.y; v[h][j][2] = x.z; v[h][j][3] = x.w;
                     }
                 } else {  // gather through the column table
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_batch_kernel(ScatterA
     if (item >= a.items) return;
     const int64_t off = blockIdx.y * a.stride;
     a.M = item_at(a.M, blockIdx.y * a.m_stride);
-    a.prow_slot = item_at(a.prow_slot, off); a.prow_src = item_at(a.prow_src, off); a.prow_exp = item_at(a.prow_exp, off);
+    a.prow = item_at(a.prow, off);
     a.col_k = item_at(a.col_k, off); a.col_e = item_at(a.col_e, off); a.col_w = item_at(a.col_w, off);
     a.unit = item_at(a.unit, off); a.unit_w = item_at(a.unit_w, off);
     a.out = item_at(a.out, blockIdx.y * a.out_stride);
@@ -565,7 +565,7 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
         const bool both = (op ? p->sB : p->sA) == IMUNPACK_BOTH;
         ScatterArgs &a = sc[op];
         a.M = op ? B : A; a.ldm = op ? ldb : lda;
-        a.prow_slot = lay.prow_slot; a.prow_src = lay.prow_src; a.prow_exp = lay.prow_exp;
+        a.prow = lay.prow;
         a.col_k = op ? p->cols.colB_k : p->cols.colA_k;
         a.col_e = op ? p->cols.colB_e : p->cols.colA_e;
         a.col_w = op ? nullptr : p->cols.colA_w;

@@ -952,3 +952,25 @@ def test_gemm_tiles_of_either_size(imu, n, d, h, b, strategies):
         assert np.array_equal(C_int.cpu().numpy(), want)
         ref = want.astype(np.float64) * 0.125
         assert (np.abs(C_fp.cpu().numpy() - ref) <= REL_TOL * np.abs(ref)).all()
+
+
+@pytest.mark.parametrize("n,d,h,b,sa,sb,kind", [
+    (5, 8200, 7, 8, COL, COL, "every"),     # more column slots than one workgroup lays out
+    (5, 8190, 7, 8, COL, COL, "every"),     # just as many as it does
+    (9, 8192, 6, 4, COL, COL, "deep"),      # many pairs of levels
+    (40, 600, 33, 2, COL, COL, "deep"),
+    (30, 4100, 20, 8, BOTH, BOTH, "deep"),
+    (4097, 40, 9000, 8, ROW, ROW, "every"),  # rows shared by two and three workgroups
+    (16385, 8, 18000, 4, ROW, COL, "deep"),  # more rows than registers and LDS hold
+    (12300, 16, 4096, 3, BOTH, ROW, "few"),
+])
+def test_layouts_around_the_sizes_where_they_change(imu, n, d, h, b, sa, sb, kind):
+    rng = np.random.default_rng(n + d + h)
+    s = 1 << (b - 1)
+    if kind == "every":
+        Aq, Bq = (rng.integers(-(s * s - 1), s * s, size=(r, d)).astype(np.int32) for r in (n, h))
+    elif kind == "deep":
+        Aq, Bq = (rand_ints(rng, r, d, s, 0.3 if b != 8 else 0.002, 4 if b > 2 else 9) for r in (n, h))
+    else:
+        Aq, Bq = (rand_ints(rng, r, d, s, 0.001, 2) for r in (n, h))
+    check_against_oracle(imu, Aq, Bq, b, sa, sb)
