@@ -540,63 +540,79 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             // source rows of this chunk: cs0 .. cs0 + ns - 1; no source row straddles a chunk
             const int cs0 = chunk0[c], ns = chunk0[c + 1] - cs0;
             const int rs0 = cs0 - chunk0[0];  // index of the chunk's first source row in rowmeta
+            // Four columns side by side from column q on (of the source columns jcol ..), four source rows at a time per
+            // thread so that their LDS reads are in flight together (a wave works on one row at a time, so the level
+            // counts are uniform).
+            constexpr int RS = kGemmThreads / 64;
+            auto quad_at = [&](const int32_t *at, bool aligned) {
+                v4i x;
+                if (aligned) {
+                    x = *reinterpret_cast<const v4i *>(at);
+                } else {
+                    x[0] = at[0]; x[1] = at[1]; x[2] = at[2]; x[3] = at[3];
+                }
+                return x;
+            };
+            auto copy_rows = [&](int q, int jcol, bool aligned) {  // no split row in the tile: physical order = source order
+                for (int r0 = tid >> 6; r0 < ns; r0 += 4 * RS) {
+                    v4i x[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) x[u] = quad_at(fold + min(r0 + u * RS, ns - 1) * FLD + q, aligned);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (r0 + u * RS < ns)
+                            store4((int64_t)(cs0 + r0 + u * RS) * g.ldc + jsrc0 + jcol, nsrcB - jcol, x[u][0], x[u][1], x[u][2], x[u][3]);
+                }
+            };
+            // split rows: the digit levels of a source row are added up, in binary64 where every sum is exact in it
+            auto fold_rows = [&](auto zero, int q, int jcol, bool aligned) {
+                using T = decltype(zero);
+                for (int r0 = tid >> 6; r0 < ns; r0 += 4 * RS) {
+                    int prel[4], nl[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int m = r0 + u * RS < ns ? rowmeta[rs0 + r0 + u * RS] : 0;
+                        prel[u] = (m & 0xFFFF) - c * kChunk;
+                        nl[u] = m >> 16;  // 0 past the chunk's last source row
+                    }
+                    const int nlmax = max(max(nl[0], nl[1]), max(nl[2], nl[3]));
+                    T v[4][4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) v[u][k] = zero;
+                    for (int l = 0; l < nlmax; ++l) {
+                        v4i x[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            x[u] = l < nl[u] ? quad_at(fold + (prel[u] + l) * FLD + q, aligned) : v4i{0, 0, 0, 0};
+                        if constexpr (std::is_same<T, double>::value) {
+                            const double wl = (double)(1ull << (g.sh * l));
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) v[u][k] += (double)x[u][k] * wl;
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) v[u][k] += (int64_t)x[u][k] << (g.sh * l);
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (r0 + u * RS < ns)
+                            store4((int64_t)(cs0 + r0 + u * RS) * g.ldc + jsrc0 + jcol, nsrcB - jcol, v[u][0],
+                                   v[u][1], v[u][2], v[u][3]);
+                }
+            };
             if (flatB) {
                 // source columns = physical columns: work items are (source row, four columns)
                 const int col4 = (tid & 63) * 4;
-                if (col4 < nsrcB && flatA) {  // physical order = source order inside the chunk
-                    for (int r = tid >> 6; r < ns; r += kGemmThreads / 64) {
-                        const v4i x = *reinterpret_cast<const v4i *>(fold + r * FLD + col4);
-                        store4((int64_t)(cs0 + r) * g.ldc + jsrc0 + col4, nsrcB - col4, x[0], x[1], x[2], x[3]);
-                    }
-                } else if (col4 < nsrcB) {
-                    // split rows: the digit levels of a source row are added up, four source rows at a time
-                    // per thread so that their LDS reads are in flight together (a wave works on one row, so
-                    // the level counts are uniform); in binary64 where every sum is exact in it
-                    constexpr int RS = kGemmThreads / 64;
-                    auto fold_rows = [&](auto zero) {
-                        using T = decltype(zero);
-                        for (int r0 = tid >> 6; r0 < ns; r0 += 4 * RS) {
-                            int prel[4], nl[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                const int m = r0 + u * RS < ns ? rowmeta[rs0 + r0 + u * RS] : 0;
-                                prel[u] = (m & 0xFFFF) - c * kChunk;
-                                nl[u] = m >> 16;  // 0 past the chunk's last source row
-                            }
-                            const int nlmax = max(max(nl[0], nl[1]), max(nl[2], nl[3]));
-                            T v[4][4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                                for (int k = 0; k < 4; ++k) v[u][k] = zero;
-                            for (int l = 0; l < nlmax; ++l) {
-                                v4i x[4];
-#pragma unroll
-                                for (int u = 0; u < 4; ++u)
-                                    x[u] = l < nl[u] ? *reinterpret_cast<const v4i *>(fold + (prel[u] + l) * FLD + col4)
-                                                     : v4i{0, 0, 0, 0};
-                                if constexpr (std::is_same<T, double>::value) {
-                                    const double wl = (double)(1ull << (g.sh * l));
-#pragma unroll
-                                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                                        for (int k = 0; k < 4; ++k) v[u][k] += (double)x[u][k] * wl;
-                                } else {
-#pragma unroll
-                                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                                        for (int k = 0; k < 4; ++k) v[u][k] += (int64_t)x[u][k] << (g.sh * l);
-                                }
-                            }
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                if (r0 + u * RS < ns)
-                                    store4((int64_t)(cs0 + r0 + u * RS) * g.ldc + jsrc0 + col4, nsrcB - col4, v[u][0],
-                                           v[u][1], v[u][2], v[u][3]);
-                        }
-                    };
-                    if (fold_f64) fold_rows(0.0);
-                    else fold_rows((int64_t)0);
+                if (col4 < nsrcB) {
+                    if (flatA) copy_rows(col4, col4, true);
+                    else if (fold_f64) fold_rows(0.0, col4, col4, true);
+                    else fold_rows((int64_t)0, col4, col4, true);
                 }
             } else {
                 // split source columns: lane l owns source columns 4l .. 4l+3 of the tile (where they sit in
@@ -628,23 +644,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                 };
                 if (plain) {
                     const bool aligned = (q0[0] & 3) == 0;
-                    for (int r = tid >> 6; r < ns; r += kGemmThreads / 64) {
-                        int prel, nl;
-                        row_levels(r, prel, nl);
-                        int64_t v[4] = {0, 0, 0, 0};
-                        for (int a = 0; a < nl; ++a) {
-                            const int32_t *row = fold + (prel + a) * FLD + q0[0];
-                            v4i x;
-                            if (aligned) {
-                                x = *reinterpret_cast<const v4i *>(row);
-                            } else {
-                                x[0] = row[0]; x[1] = row[1]; x[2] = row[2]; x[3] = row[3];
-                            }
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) v[k] += (int64_t)x[k] << (g.sh * a);
-                        }
-                        store4((int64_t)(cs0 + r) * g.ldc + jsrc0 + j4, nsrcB - j4, v[0], v[1], v[2], v[3]);
-                    }
+                    if (flatA) copy_rows(q0[0], j4, aligned);
+                    else if (fold_f64) fold_rows(0.0, q0[0], j4, aligned);
+                    else fold_rows((int64_t)0, q0[0], j4, aligned);
                 }
                 const bool many = __popcll(others) > 8;  // mostly split columns: every lane works its own quad
                 if (many && !plain && j4 < nsrcB) {
