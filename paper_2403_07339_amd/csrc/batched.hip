@@ -19,6 +19,17 @@ namespace imu {
 __global__ void clear_flags_kernel(int32_t *flags, int count) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) flags[i] = 0;
 }
+
+// The flags of a group to the host, the word it waits for behind them; leaves them cleared for the next group.
+__global__ void tell_flags_kernel(int32_t *flags, int count, int32_t *host, int32_t *word, int32_t seq) {
+    for (int i = threadIdx.x; i < count; i += blockDim.x) {
+        __hip_atomic_store(host + i, flags[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        flags[i] = 0;
+    }
+    stores_done();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(word, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 }  // namespace imu
 
 struct imunpack_batch {
@@ -29,7 +40,10 @@ struct imunpack_batch {
     size_t ue_bytes;
     void *ws;              // int64 unpacked product for items that cannot take the fused launch
     size_t ws_bytes;
-    int32_t *pin_flags;    // pinned: [0] whether any item flagged NaN / Inf / overflow, [1 + i] item i was refused
+    int32_t *pin_flags;    // pinned: [0] whether any item flagged NaN / Inf / overflow, [1 + i] item i was refused; last: the
+                           // sequence number of the group that wrote them
+    int32_t seq;
+    int32_t *clean_flags;  // the device's flags as a call that went through left them: cleared
 };
 
 using namespace imu;
@@ -82,11 +96,12 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
         c = new (std::nothrow) imunpack_batch();
         if (!c) return IMUNPACK_ENOMEM;
         memset(c, 0, sizeof(*c));
-        if (hipHostMalloc((void **)&c->pin_flags, (1 + kMaxItems) * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc((void **)&c->pin_flags, (2 + kMaxItems) * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             delete c;
             return IMUNPACK_ENOMEM;
         }
+        memset(c->pin_flags, 0, (2 + kMaxItems) * sizeof(int32_t));
         *ctx = c;
     }
     // ---- one arena for everything whose size the shapes fix
@@ -105,8 +120,11 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
     const int64_t group = std::min<int64_t>(std::min<int64_t>(batch, kMaxItems), std::max<int64_t>(1, kGroupBytes / (int64_t)item));
     const size_t head = (size_t)(1 + kMaxItems) * sizeof(int32_t) + 252;
     const size_t base = head & ~(size_t)255;
+    if (c->arena_bytes < base + item * (size_t)group) c->clean_flags = nullptr;  // new memory, whatever its address
     IMU_TRY(grow((void **)&c->arena, &c->arena_bytes, base + item * (size_t)group));
     int32_t *flags = (int32_t *)c->arena;
+    if (c->clean_flags != flags) hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(256), 0, st, flags, 1 + kMaxItems);
+    c->clean_flags = nullptr;
     char *first = c->arena + base;
     int32_t *Qa = (int32_t *)(first + oQa), *Qb = (int32_t *)(first + oQb);
     int32_t *sA = (int32_t *)(first + oSa), *sB = (int32_t *)(first + oSb);
@@ -127,7 +145,6 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
         bt.a_stride = sa_b * 4; bt.b_stride = sb_b * 4;
         bt.out_stride = (int64_t)item;
         bt.flag = flags;
-        hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(256), 0, st, flags, 1 + items);
         // the steps stay on the device: percentile -> step -> division in the quantizer -> product in the epilogue
         IMU_TRY(rtn_step_pair(Ai, n, sa_r, sa_c, beta_A, Bi, h, sb_r, sb_c, beta_B, d, p, steps, pws, bt, st));
         IMU_TRY(quantize_pair(Ai, n, sa_r, sa_c, 1.0f, steps, Qa, d, &stA, Bi, h, sb_r, sb_c, 1.0f, steps + 1, Qb, d, &stB, d,
@@ -150,8 +167,10 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
         IMU_TRY(unpack_impl(c->plan, Qa, d, Qb, d, Aue, (int64_t)ba, Beu, (int64_t)bb, st));
         IMU_TRY(gemm_batch(c->plan, Aue, (int64_t)ba, Beu, (int64_t)bb, Ci, sc_b * 4, ldc, steps, steps + 1, (int64_t)item,
                            flags + 1, st));
-        IMU_HIP(hipMemcpyAsync(c->pin_flags, flags, (size_t)(1 + items) * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        IMU_HIP(hipStreamSynchronize(st));
+        ++c->seq;
+        hipLaunchKernelGGL(tell_flags_kernel, dim3(1), dim3(256), 0, st, flags, 1 + items, c->pin_flags, c->pin_flags + 1 + kMaxItems, c->seq);
+        IMU_TRY(launch_status());
+        IMU_TRY(wait_word((const int32_t *)(c->pin_flags + 1 + kMaxItems), c->seq, st));
         bad = bad || c->pin_flags[0] != 0;
         bool unfused = false;
         for (int i = 0; i < items; ++i) {  // the fused launch is not exact for this item: un-fused path
@@ -169,5 +188,6 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
         }
         if (unfused) IMU_HIP(hipStreamSynchronize(st));
     }
+    c->clean_flags = flags;
     return bad ? IMUNPACK_ERANGE : IMUNPACK_OK;
 }

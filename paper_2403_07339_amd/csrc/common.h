@@ -82,7 +82,8 @@ struct PlanHeader {
     uint32_t cols_done;              // column-layout workgroups that have finished (the last one orders the units)
     int32_t extras;                  // edges that the repeated columns of B_e add to B's OB entries (UnpackBoth on B)
     int32_t reusedB;                 // the second operand's unpacking was taken over from the plan before (keep-weights mode)
-    int32_t pad_[2];
+    int32_t pad_;
+    int32_t seq;                     // in the host's copy: which plan's header it holds
     unsigned long long bound[2];     // max over rows of sum_c s^e(c) |digit| for A_ue, B_eu
 };
 
@@ -212,6 +213,16 @@ __device__ __forceinline__ int half_wave_max_nonneg_last(int v) {
     v = max(v, IMU_DPP(v, 0x142, 0xa, false));
     return v;
 }
+// Waits until this wave's stores have arrived.  Between words stored to the host's pinned memory (system scope, not cached)
+// and the word that says they are there this is all the order it takes; a release at system scope would first write back
+// the L2 of the XCD, with megabytes of operands in it.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// An accumulator bound for the host (saturated: beyond 2^44 no path asks how far).  The word carries the low bits of the
+// sequence number, so that neither bound's store has to wait for the other.
+__device__ __forceinline__ void tell_bound(PlanHeader *host, int i, unsigned long long bound, int32_t seq) {
+    const unsigned long long v = bound < (1ull << 44) ? bound : (1ull << 44);
+    __hip_atomic_store(&host->bound[i], v | ((unsigned long long)(unsigned)seq << 48), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // 6-bit floating-point digits in memory.  The matrix instruction takes, per lane, 32 consecutive columns of a
 // row as one 192-bit string (column j of the fragment at bits 6j .. 6j+5).  A row stores its columns in
 // groups of 64 (48 bytes): the first 128 bits of the group's two fragments (16 bytes each), then their
@@ -244,18 +255,17 @@ struct imunpack_plan {
     // views into the arena (valid after a successful imunpack_plan)
     imu::PlanHeader *d_hdr;       // one per item
     imu::PlanHeader hdr;          // host mirror (of item 0)
-    imu::PlanHeader *pin_hdr;     // pinned copies of the headers (device-to-host copies land here)
+    imu::PlanHeader *pin_hdr;     // pinned copies of the headers, written by the kernels that complete them
     int pin_items;                // ... how many of them fit
     // batch: the plans of `nitems` products of one shape, made by the same launches (1: a plan of its own)
     int nitems;
     int64_t item_bytes;           // from the arrays of one item in the arena to those of the next
     int64_t op_stride;            // from item to item: the integer operands, their statistics and OB lists
     int chunkB;                   // no source row of B straddles that many physical rows: kTile, or kChunk for small products
-    hipEvent_t ready;             // recorded after such a copy; the host polls it
-    hipStream_t side;             // carries the copy of the accumulator bounds, so that the caller's stream
-                                  // can already hold the GEMM while the host waits for them
-    hipEvent_t scattered;         // recorded on the caller's stream after the scatter; `side` waits for it
-    int bound_pending;            // the bounds of the last imunpack_unpack have not been read back yet
+    int32_t seq;                  // of the last header or bounds that the host asked for (the kernel writes it behind them)
+    hipStream_t bound_stream;     // the stream of the last imunpack_unpack
+    int bound_pending;            // the bounds of the last imunpack_unpack have not been read back yet ...
+    int bound_told;               // ... but a kernel that hands them to the host is queued
     int guess_fusable;            // whether the fused GEMM was exact for this plan object the last time
     imu::SlotSet rowA, rowB, c1, c2;
     imu::RowLayout layA, layB;
@@ -297,9 +307,11 @@ inline bool small_tiles_possible(int64_t n, int64_t h, int nitems) {
     return ((n + kTile - 1) / kTile) * ((h + kTile - 1) / kTile) * nitems <= 128;
 }
 
-// Copies the device headers to the host and waits for them.  The wait polls an event instead of blocking in the driver: the wake-up of a blocking wait costs
-// tens of microseconds during which the GPU idles between two stages of the path.
-int fetch_headers(Plan *p, hipStream_t st);
+// Waits until a kernel on `st` has written `want` to a word of pinned memory (behind the data that goes with it).  The host
+// polls the word: a blocking wait costs tens of microseconds of wake-up during which the GPU idles between two stages of
+// the path, and a copy with an event behind it a launch and three calls.
+template <class T>
+int wait_word(const T *word, T want, hipStream_t st);
 // The entry points' inner forms, which also serve the items of a batch (p->nitems of them).
 int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t *B, int64_t h, int64_t ldb, int b,
               int strategy_A, int strategy_B, const imunpack_stats_t *stats_A, const imunpack_stats_t *stats_B,
@@ -322,7 +334,9 @@ int gemm_batch(imunpack_plan_t *p, const int8_t *A_ue, int64_t a_stride, const i
 // The RTN steps of both operands of every item of a batch (percentile.hip); ws: two workspaces side by side.
 int rtn_step_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float beta_A, const float *B, int64_t h, int64_t sb_r,
                   int64_t sb_c, float beta_B, int64_t d, double p, float *steps, void *ws, const QuantBatch &bt, hipStream_t st);
-// Waits for the bounds that imunpack_unpack left in flight and sets p->fusable.
+// The sequence number under which a kernel that is about to be queued hands the bounds over (tell_bound).
+int32_t ask_bounds(Plan *p);
+// Waits for the bounds of the last imunpack_unpack and sets p->fusable.
 int resolve_bound(Plan *p);
 // Bytes from one physical row to the next of the A store (op 0) / of B_eu (op 1) in the digit format in
 // effect.  6-bit digits: 96 bytes per k-tile of 128 columns, the same rule against power-of-two pitches.

@@ -20,6 +20,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cstddef>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -195,22 +196,9 @@ __global__ void identity_slots_kernel(SlotSet set, PlanHeader *hdr, const int32_
 // Base items x = 0..N-1 with largest magnitude maxabs[via ? via[x] : x] (via: the columns that A's unpacking
 // left, N read from the header); every level l >= 1 appends the items that still have a digit there, in
 // ascending x.  `which` names the set.
-__global__ __launch_bounds__(kPlanThreads) void level_major_kernel(
-    SlotSet set, const int32_t *maxabs, const int32_t *via, int n_host, int sh, int32_t *tmpL, int32_t *tmpCur,
-    PlanHeader *hdr, int which, const int32_t *skip, int64_t stride, int64_t stats_stride) {
-    __shared__ int lds[40];
-    hdr += blockIdx.y;
-    {
-        const int64_t off = blockIdx.y * stride;
-        move_to_item(set, off);
-        via = item_at(via, off);
-        tmpL = item_at(tmpL, off);
-        tmpCur = item_at(tmpCur, off);
-        maxabs = item_at(maxabs, blockIdx.y * stats_stride);
-    }
-    if (hdr->overflow) return;
-    if (skip && *skip) return;  // keep-weights mode: this set is taken over as it stands
-    const int N = via ? hdr->d1 : n_host;
+template <int kLevelItems>
+__device__ void level_major(const SlotSet &set, const int32_t *maxabs, const int32_t *via, int N, int sh, int32_t *tmpL,
+                            int32_t *tmpCur, PlanHeader *hdr, int which, int *lds /* >= 40 ints */) {
     int32_t *count_out = which == CAP_ROWA ? &hdr->n_u : which == CAP_ROWB ? &hdr->h_u : which == CAP_C1 ? &hdr->d1 : &hdr->d_u;
     if (N > set.cap) {
         if (threadIdx.x == 0) flag_overflow(hdr, which, N);
@@ -218,7 +206,6 @@ __global__ __launch_bounds__(kPlanThreads) void level_major_kernel(
     }
     // Up to kLevelItems items per thread: their levels and latest slots stay in registers (a wave owns a contiguous segment, as
     // in ordered_select), so that a level is ballots and stores.  12608 rows: 23 -> 16 us.
-    constexpr int kLevelItems = 16;
     if (N <= kLevelItems * kPlanThreads) {
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         const int seg = ((N + kPlanWaves - 1) / kPlanWaves + 63) & ~63, x0 = wave * seg + lane;
@@ -329,6 +316,24 @@ __global__ __launch_bounds__(kPlanThreads) void level_major_kernel(
     }
 }
 
+__global__ __launch_bounds__(kPlanThreads) void level_major_kernel(
+    SlotSet set, const int32_t *maxabs, const int32_t *via, int n_host, int sh, int32_t *tmpL, int32_t *tmpCur,
+    PlanHeader *hdr, int which, const int32_t *skip, int64_t stride, int64_t stats_stride) {
+    __shared__ int lds[40];
+    hdr += blockIdx.y;
+    {
+        const int64_t off = blockIdx.y * stride;
+        move_to_item(set, off);
+        via = item_at(via, off);
+        tmpL = item_at(tmpL, off);
+        tmpCur = item_at(tmpCur, off);
+        maxabs = item_at(maxabs, blockIdx.y * stats_stride);
+    }
+    if (hdr->overflow) return;
+    if (skip && *skip) return;  // keep-weights mode: this set is taken over as it stands
+    level_major<16>(set, maxabs, via, via ? hdr->d1 : n_host, sh, tmpL, tmpCur, hdr, which, lds);
+}
+
 // ---------------------------------------------------------------------------------------------
 // UnpackBoth (Alg. 4): the greedy
 // ---------------------------------------------------------------------------------------------
@@ -386,32 +391,29 @@ __device__ __forceinline__ unsigned long long pack_edge(int row, int col, int le
 // written, compacted, to the other of two lists.  The order inside a batch only decides the numbers of the appended slots; it is recorded as
 // a sort key (batch, count descending, split slot) and the appended slots are renumbered on the host
 // when the plan is exported.
+__device__ __forceinline__ void move_to_item(GreedyArgs &g) {
+    const int64_t off = blockIdx.y * g.stride, soff = blockIdx.y * g.stats_stride;
+    move_to_item(g.rows, off);
+    move_to_item(g.cols, off);
+    g.chain_child = item_at(g.chain_child, off);
+    g.chain_root = item_at(g.chain_root, off);
+    g.edges = item_at(g.edges, off);
+    g.extra_rows = item_at(g.extra_rows, off);
+    g.rcnt = item_at(g.rcnt, off);
+    g.ccnt = item_at(g.ccnt, off);
+    g.rowcnt = item_at(g.rowcnt, soff);
+    g.colcnt = item_at(g.colcnt, soff);
+    g.rowmax = item_at(g.rowmax, soff);
+    g.ob_count = item_at(g.ob_count, blockIdx.y * g.list_stride);
+}
+
 template <bool LDS>
-__global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g) {
-    extern __shared__ __attribute__((aligned(16))) int32_t lds_counts[];
+__device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_counts) {
     __shared__ int s_top[2], s_T[2][4];
     __shared__ int s_pick[kPlanWaves][256];  // per wave: the slots picked in one 256-slot step
     __shared__ int s_found[kPlanWaves], s_positive[kPlanWaves];
     __shared__ int lds[40];
     __shared__ int s_count;
-    PlanHeader *hdr = g.hdr + blockIdx.y;
-    {
-        const int64_t off = blockIdx.y * g.stride, soff = blockIdx.y * g.stats_stride;
-        move_to_item(g.rows, off);
-        move_to_item(g.cols, off);
-        g.chain_child = item_at(g.chain_child, off);
-        g.chain_root = item_at(g.chain_root, off);
-        g.edges = item_at(g.edges, off);
-        g.extra_rows = item_at(g.extra_rows, off);
-        g.rcnt = item_at(g.rcnt, off);
-        g.ccnt = item_at(g.ccnt, off);
-        g.rowcnt = item_at(g.rowcnt, soff);
-        g.colcnt = item_at(g.colcnt, soff);
-        g.rowmax = item_at(g.rowmax, soff);
-        g.ob_count = item_at(g.ob_count, blockIdx.y * g.list_stride);
-    }
-    if (hdr->overflow) return;
-    if (g.skip && *g.skip) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const unsigned long long below = (1ull << lane) - 1ull;
     int nr = g.second ? hdr->h_u : hdr->n_u, nc = hdr->d1;
@@ -448,7 +450,7 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g)
     // edges of repeated columns (second operand only; the rows they touch start with that many more OB
     // entries)
     unsigned long long *list0 = g.edges, *list1 = g.edges + ((g.ecap + 1) & ~1);  // both 16-byte aligned
-    if (g.chain_child && threadIdx.x == 0) s_count = hdr->extras;
+    if (g.chain_child && threadIdx.x == 0) s_count = load_agent(&hdr->extras);
     __syncthreads();
     deep = block_max(deep, lds);
     const int extras = s_count;
@@ -792,6 +794,16 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g)
     }
 }
 
+template <bool LDS>
+__global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g) {
+    extern __shared__ __attribute__((aligned(16))) int32_t lds_counts[];
+    PlanHeader *hdr = g.hdr + blockIdx.y;
+    move_to_item(g);
+    if (hdr->overflow) return;
+    if (g.skip && *g.skip) return;
+    greedy_both<LDS>(g, hdr, lds_counts);
+}
+
 // ---------------------------------------------------------------------------------------------
 // physical layouts
 // ---------------------------------------------------------------------------------------------
@@ -1045,23 +1057,24 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
     for (int i = 0; i < tiles_c && xb + i < 256; ++i) t.extra_e[xb + i] = (unsigned char)e;
 }
 
-// The same layout for unpackings whose tables fit the LDS of one workgroup (every product up to about 16000 column slots):
+// The same layout for unpackings whose tables fit the LDS of one workgroup (every product up to 12288 column slots):
 // the general path below is a chain of phases that hand arrays to one another through memory, a microsecond or more per
 // dependent read, and its workgroups end in a device-wide fence that writes back the L2 of their XCD (24 to 54 us for one
 // product, 70 to 170 us for the items of a batch; this one: 14 to 37 and 14 to 16).  Here every slot stays in the registers of its thread.  A column slot is
 // known by its original column k and its levels eA, eB along A and B, and no two slots share all three; so the slots are a
 // bit per k in a mask per (eA, eB), every rank is a count of bits below k, and the columns of both stores are put together
 // in LDS and written once.  Returns false, having written nothing but tables that are written again, if LDS is too small.
-constexpr int kColSlotsLds = 16;  // slots per thread
+constexpr int kColSlotsLds = 12;  // slots per thread: as many as the registers of a 1024-thread workgroup hold
+template <int kSlots>
 __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColLayout &cols, int d, int cap_phys, int s, int sh,
                                 PlanHeader *hdr, ColTables &t, int32_t *dyn, int dyn_words) {
     const int D = hdr->d_u, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (D > kColSlotsLds * kPlanThreads) return false;
+    if (D > kSlots * kPlanThreads) return false;
     for (int x = tid; x < kMaxGroups * kMaxLevelsA; x += kPlanThreads) t.hist2[x] = 0;
     if (tid == 0) t.la = t.lb = t.bad = 0;
-    int key[kColSlotsLds], lev[kColSlotsLds];  // original column; eA | eB << 16
+    int key[kSlots], lev[kSlots];  // original column; eA | eB << 16
 #pragma unroll
-    for (int u = 0; u < kColSlotsLds; ++u) {
+    for (int u = 0; u < kSlots; ++u) {
         const int c = tid + u * kPlanThreads;
         key[u] = -1;
         lev[u] = 0;
@@ -1071,7 +1084,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     }
     int ma = 0, mb = 0;
 #pragma unroll
-    for (int u = 0; u < kColSlotsLds; ++u) {
+    for (int u = 0; u < kSlots; ++u) {
         if (key[u] < 0) continue;
         const int r = key[u], ea = c1.exp[r];
         key[u] = c1.root[r];
@@ -1098,7 +1111,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
         for (int x = tid; x < LA * LB * W * 16; x += kPlanThreads) packB[x] = 0;
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kColSlotsLds; ++u)
+        for (int u = 0; u < kSlots; ++u)
             if (key[u] >= 0) seen[((lev[u] & 0xffff) * LB + (lev[u] >> 16)) * W * 64 + key[u]] = 1;
         __syncthreads();
         for (int x = wave; x < LA * LB * W; x += kPlanWaves) {
@@ -1109,7 +1122,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
         for (int x = tid; x < 2 * LA * LB * W; x += kPlanThreads) dyn[x] = 0;
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kColSlotsLds; ++u) {
+        for (int u = 0; u < kSlots; ++u) {
             if (key[u] < 0) continue;
             const int k = key[u], pair = (lev[u] & 0xffff) * LB + (lev[u] >> 16);
             atomicOr(reinterpret_cast<unsigned *>(mask) + 2 * pair * W + (k >> 5), 1u << (k & 31));
@@ -1148,7 +1161,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
         return pre[pair * W + (k >> 6)] + __popcll(mask[pair * W + (k >> 6)] & ((1ull << (k & 63)) - 1ull));
     };
 #pragma unroll
-    for (int u = 0; u < kColSlotsLds; ++u) {
+    for (int u = 0; u < kSlots; ++u) {
         if (key[u] < 0) continue;
         const int c = tid + u * kPlanThreads, k = key[u], a = lev[u] & 0xffff, eb = lev[u] >> 16, e = a + eb;
         const int stored = t.lvlbase[a] + rank(a * LB, k);  // where level a of A holds column k
@@ -1306,6 +1319,10 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
     __syncthreads();
     const int Kp = t.kp, KA = t.ka, ka_levels = t.ka_levels;
     if (Kp > cap_phys || t.bad) return;
+    if (nparts == 1) {  // (several workgroups add to weights that an earlier launch has cleared)
+        for (int q = threadIdx.x; q < KA; q += kPlanThreads) cols.colA_w[q] = 0;
+        __syncthreads();
+    }
     // ---- the stored levels of A (first part)
     if (part == 0) {
         for (int q = threadIdx.x; q < ka_levels; q += kPlanThreads) {
@@ -1512,6 +1529,22 @@ __host__ __device__ inline int row_slices(int rows) {
     return w < 1 ? 1 : w > 4 ? 4 : w;
 }
 
+// A completed header to the host: its words, then the sequence number that the host waits for.
+__device__ __forceinline__ void publish_header(const PlanHeader *hdr, PlanHeader *host, int32_t seq) {
+    constexpr int kWords = (int)(offsetof(PlanHeader, seq) / sizeof(int32_t));
+    const int32_t *src = reinterpret_cast<const int32_t *>(hdr);
+    int32_t *dst = reinterpret_cast<int32_t *>(host);
+    for (int i = threadIdx.x; i < kWords; i += blockDim.x)
+        __hip_atomic_store(dst + i, load_agent(src + i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    stores_done();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(&host->seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ __launch_bounds__(256) void publish_kernel(const PlanHeader *hdr, PlanHeader *host, int32_t seq) {
+    publish_header(hdr + blockIdx.y, host + blockIdx.y, seq);
+}
+
 // One to four workgroups for the rows of A, as many for the rows of B, one for the columns (kColBlocks where there may be more column
 // slots than that one holds).
 __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
@@ -1553,7 +1586,7 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
         const int part = bx - slA - slB;
         const bool in_lds = hdr->d_u <= kColSlotsLds * kPlanThreads;
         if (in_lds && part > 0) return;
-        if (!in_lds || !cols_layout_lds(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words)) {
+        if (!in_lds || !cols_layout_lds<kColSlotsLds>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words)) {
             __syncthreads();
             cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, part, in_lds ? 1 : (int)gridDim.x - slA - slB, tables);
         }
@@ -1720,24 +1753,10 @@ static inline int grid_for(int64_t items, int threads, int maxblocks = 2048) {
 // of B in every column slot of A's unpacking that descends from k, so an OB entry (j, k) of B is
 // also an OB entry (j, c) for every such slot c.  The pass also writes the greedy's first edge list:
 // entry t of the OB list packed at position t, the edges of repeated columns behind the last entry.
-__global__ __launch_bounds__(256) void ob_copy_kernel(const int32_t *__restrict__ ob, int ob_cap,
-                                                      const int32_t *ob_count, int32_t *__restrict__ keep, int keep_cap,
-                                                      const int32_t *chain_child, unsigned long long *edges, int ecap,
-                                                      PlanHeader *hdr, int32_t *extra_rows, int sh, const int32_t *skip,
-                                                      int64_t stride, int64_t list_stride) {
-    if (skip && *skip) return;  // keep-weights mode: this operand's unpacking is taken over as it stands
-    {
-        const int64_t off = blockIdx.y * stride, loff = blockIdx.y * list_stride;
-        ob = item_at(ob, loff);
-        ob_count = item_at(ob_count, loff);
-        keep = item_at(keep, off);
-        chain_child = item_at(chain_child, off);
-        edges = item_at(edges, off);
-        extra_rows = item_at(extra_rows, off);
-    }
-    int32_t *extras = &hdr[blockIdx.y].extras;
-    const int n = min(*ob_count, ob_cap);
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+__device__ __forceinline__ void ob_copy(const int32_t *ob, int ob_cap, int n, int32_t *keep, int keep_cap, const int32_t *chain_child,
+                                        unsigned long long *edges, int ecap, int32_t *extras, int32_t *extra_rows, int sh, int t0,
+                                        int step) {
+    for (int t = t0; t < n; t += step) {
         const int j = ob[t], k = ob[ob_cap + t], v = ob[2 * (size_t)ob_cap + t];
         if (t < keep_cap) {
             keep[t] = j;
@@ -1757,6 +1776,25 @@ __global__ __launch_bounds__(256) void ob_copy_kernel(const int32_t *__restrict_
     }
 }
 
+__global__ __launch_bounds__(256) void ob_copy_kernel(const int32_t *__restrict__ ob, int ob_cap,
+                                                      const int32_t *ob_count, int32_t *__restrict__ keep, int keep_cap,
+                                                      const int32_t *chain_child, unsigned long long *edges, int ecap,
+                                                      PlanHeader *hdr, int32_t *extra_rows, int sh, const int32_t *skip,
+                                                      int64_t stride, int64_t list_stride) {
+    if (skip && *skip) return;  // keep-weights mode: this operand's unpacking is taken over as it stands
+    {
+        const int64_t off = blockIdx.y * stride, loff = blockIdx.y * list_stride;
+        ob = item_at(ob, loff);
+        ob_count = item_at(ob_count, loff);
+        keep = item_at(keep, off);
+        chain_child = item_at(chain_child, off);
+        edges = item_at(edges, off);
+        extra_rows = item_at(extra_rows, off);
+    }
+    ob_copy(ob, ob_cap, min(*ob_count, ob_cap), keep, keep_cap, chain_child, edges, ecap, &hdr[blockIdx.y].extras, extra_rows, sh,
+            blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+
 // ---- keep-weights mode (Sec. 4.2: weights are unpacked once, when they are loaded).  The unpacking of the
 // second operand depends on the first only through the column slots of the first operand's unpacking
 // (which columns of B_e are repeats, and their exponents).  If those are what they were for the plan
@@ -1764,12 +1802,21 @@ __global__ __launch_bounds__(256) void ob_copy_kernel(const int32_t *__restrict_
 // One workgroup: compares the column slots with the remembered ones and acts on the verdict.  Same slots: the
 // header fields that the second operand's unpacking and the layouts of its rows and of the columns left are
 // put back.  Different: its rows start afresh and the column weights are cleared for the column layout to come.
-__global__ __launch_bounds__(kPlanThreads) void keep_decide_kernel(
-    SlotSet c1, const int32_t *sroot, const int32_t *sexp, const int32_t *schild, KeepState *ks, int host_valid,
-    PlanHeader *hdr, SlotSet rowB, int h /* rows that start as unsplit originals */, int32_t *extra_rows, int nextra,
-    int32_t *col_weights, int nweights) {
-    const int d1 = hdr->d1;
-    bool differs = !host_valid || !ks->valid || d1 != ks->d1 || d1 > c1.cap || hdr->overflow != 0;
+struct KeepArgs {
+    const int32_t *sroot, *sexp, *schild;
+    KeepState *ks;               // nullptr: not in this mode
+    int host_valid;
+    int h;                       // rows of B that start as unsplit originals
+    int32_t *extra_rows;
+    int nextra;
+    int32_t *col_weights;
+    int nweights;
+};
+__device__ bool keep_decide(const KeepArgs &k, const SlotSet &c1, PlanHeader *hdr, const SlotSet &rowB) {
+    KeepState *ks = k.ks;
+    const int32_t *sroot = k.sroot, *sexp = k.sexp, *schild = k.schild;
+    const int h = k.h, d1 = hdr->d1;
+    bool differs = !k.host_valid || !ks->valid || d1 != ks->d1 || d1 > c1.cap || load_agent(&hdr->overflow) != 0;
     if (!differs)
         for (int x = threadIdx.x; x < d1; x += kPlanThreads)
             differs = differs || c1.root[x] != sroot[x] || c1.exp[x] != sexp[x] || c1.child[x] != schild[x];
@@ -1793,11 +1840,16 @@ __global__ __launch_bounds__(kPlanThreads) void keep_decide_kernel(
         int32_t *dst = reinterpret_cast<int32_t *>(hdr);
         for (size_t i = g0 + threadIdx.x; i < g1; i += kPlanThreads) dst[i] = src[i];
         for (size_t i = r0 + threadIdx.x; i < r1; i += kPlanThreads) dst[i] = src[i];
-        return;
+        return true;
     }
     for (int x = threadIdx.x; x < h; x += kPlanThreads) identity_slot(rowB, x);
-    for (int x = threadIdx.x; x < nextra; x += kPlanThreads) extra_rows[x] = 0;
-    for (int x = threadIdx.x; x < nweights; x += kPlanThreads) col_weights[x] = 0;
+    for (int x = threadIdx.x; x < k.nextra; x += kPlanThreads) k.extra_rows[x] = 0;
+    for (int x = threadIdx.x; x < k.nweights; x += kPlanThreads) k.col_weights[x] = 0;
+    return false;
+}
+
+__global__ __launch_bounds__(kPlanThreads) void keep_decide_kernel(KeepArgs k, SlotSet c1, PlanHeader *hdr, SlotSet rowB) {
+    keep_decide(k, c1, hdr, rowB);
 }
 
 // After a plan that unpacked the second operand anew: remember the column slots it was unpacked for and the
@@ -1826,22 +1878,72 @@ __global__ void keep_remember_kernel(SlotSet c1, const PlanHeader *hdr, int32_t 
     }
 }
 
+// ---- keep-weights mode in one launch: what runs on every plan in this mode -- the first operand is unpacked, the verdict taken
+// and, if the second operand's unpacking is taken over, the first operand's rows laid out.  One by one these were seven
+// launches that mostly found nothing to do (16 rows against resident 11008 x 4096 weights: 42 us; 21 in one).  If the
+// unpacking is not taken over, the host, which reads the verdict in the header, launches the rest.
+// (The whole plan of a small product in one workgroup and launch took longer than its kernels one by one, 107 against 95 us
+// at 256 x 256 x 256 and 54 against 32 at 1000 x 1031 x 777: code that runs once is bound by its instruction fetch.)
+struct KeepPlan {
+    PlanHeader *hdr;
+    SlotSet rows, cols, rowsB;        // slots of the first operand's unpacking; row slots of the second
+    RowLayout lay;
+    const int32_t *rowmax, *colmax;
+    GreedyArgs greedy;                // UnpackBoth
+    int32_t *tmpL, *tmpCur, *tmpP;
+    int n, d, h, sh, strategy, strategyB, cap_phys;
+    KeepArgs keep;
+    PlanHeader *host;
+    int32_t seq;
+};
+
+__global__ __launch_bounds__(kPlanThreads) void keep_plan_kernel(KeepPlan f) {
+    __shared__ int lds[40];
+    extern __shared__ __attribute__((aligned(16))) int32_t dyn[];
+    PlanHeader *hdr = f.hdr;
+    for (size_t i = threadIdx.x; i < sizeof(PlanHeader) / sizeof(int32_t); i += kPlanThreads) reinterpret_cast<int32_t *>(hdr)[i] = 0;
+    if (f.strategy != IMUNPACK_COL)
+        for (int x = threadIdx.x; x < f.d; x += kPlanThreads) identity_slot(f.cols, x);
+    if (f.strategy != IMUNPACK_ROW)
+        for (int x = threadIdx.x; x < f.n; x += kPlanThreads) identity_slot(f.rows, x);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        f.keep.ks->diff = f.keep.ks->same = 0;
+        if (f.strategy != IMUNPACK_ROW) hdr->n_u = f.n;
+        if (f.strategy != IMUNPACK_COL) hdr->d1 = f.d;
+        if (f.strategyB != IMUNPACK_ROW) hdr->h_u = f.h;
+    }
+    __syncthreads();
+    if (f.strategy == IMUNPACK_BOTH) {
+        greedy_both<true>(f.greedy, hdr, dyn);
+    } else {
+        const bool by_row = f.strategy == IMUNPACK_ROW;
+        level_major<4>(by_row ? f.rows : f.cols, by_row ? f.rowmax : f.colmax, nullptr, by_row ? f.n : f.d, f.sh, f.tmpL, f.tmpCur, hdr,
+                       by_row ? CAP_ROWA : CAP_C1, lds);
+    }
+    __syncthreads();
+    if (keep_decide(f.keep, f.cols, hdr, f.rowsB)) {
+        __syncthreads();
+        rows_layout(f.rows, f.n, &hdr->n_u, f.lay, f.cap_phys, f.cap_phys / kTile + 2, f.tmpP, hdr, 0, kChunk, lds, dyn, 0, 1);
+    }
+    __syncthreads();
+    publish_header(hdr, f.host, f.seq);
+}
+
 static constexpr int kGreedyLdsMax = 136 * 1024;  // dynamic LDS the greedy may use for the two count vectors
+static constexpr int kKeepPlanCols = 16384;       // columns that keep_plan_kernel sets up and compares in one workgroup
 static constexpr int kLayoutLdsMax = 140 * 1024;  // dynamic LDS the layouts kernel may use (its static tables take about 11 KiB)
 
 // ob: the operand's OB entry list ([3][ob_cap], count on the device)
-static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const int32_t *ob_count, int64_t list_stride,
-                      int which_list, hipStream_t st, const int32_t *skip = nullptr) {
-    PlanHeader *hdr = p->d_hdr;
+static GreedyArgs greedy_args(const Plan *p, int phase, int ob_cap, const int32_t *ob_count, int64_t list_stride, int which_list,
+                              const int32_t *skip) {
     const bool first = phase == 1;
-    SlotSet &rows = first ? p->rowA : p->rowB;
-    SlotSet &cols = first ? p->c1 : p->c2;
     GreedyArgs g;
-    g.rows = rows; g.cols = cols;
+    g.rows = first ? p->rowA : p->rowB; g.cols = first ? p->c1 : p->c2;
     g.second = !first;
     g.chain_child = first ? nullptr : p->c1.child;
     g.chain_root = first ? nullptr : p->c1.root;
-    int32_t **stats = first ? p->statsA : p->statsB;
+    int32_t *const *stats = first ? p->statsA : p->statsB;
     g.rowcnt = stats[0]; g.colcnt = stats[1]; g.rowmax = stats[2];
     g.ob_cap = ob_cap; g.ob_count = ob_count; g.which_list = which_list;
     g.stride = p->item_bytes; g.stats_stride = p->op_stride; g.list_stride = list_stride;
@@ -1849,24 +1951,41 @@ static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const i
     g.ecap = std::min(p->cap[first ? CAP_EDGEA : CAP_EDGEB], p->edge_cap);
     g.rcnt = p->rcnt; g.ccnt = p->ccnt;
     g.extra_rows = first ? nullptr : p->extraRows;
-    g.hdr = hdr;
+    g.hdr = p->d_hdr;
     g.whichR = first ? CAP_ROWA : CAP_ROWB;
     g.whichC = first ? CAP_C1 : CAP_C2;
     g.whichE = first ? CAP_EDGEA : CAP_EDGEB;
     g.s = p->s; g.sh = p->sh;
     g.skip = skip;
-    const size_t lds_bytes = ((size_t)((rows.cap + 7) & ~3) + (size_t)((cols.cap + 7) & ~3)) * sizeof(int32_t);
+    return g;
+}
+
+// dynamic LDS of the greedy's two count vectors
+static size_t greedy_lds(const Plan *p, int phase) {
+    const SlotSet &rows = phase == 1 ? p->rowA : p->rowB, &cols = phase == 1 ? p->c1 : p->c2;
+    return ((size_t)((rows.cap + 7) & ~3) + (size_t)((cols.cap + 7) & ~3)) * sizeof(int32_t);
+}
+
+static void launch_ob_copy(const Plan *p, const GreedyArgs &g, int phase, const int32_t *ob, hipStream_t st) {
+    const bool first = phase == 1;
+    const int keep_cap = p->cap[first ? CAP_EDGEA : CAP_EDGEB];  // the stride the fix-up pass reads with
+    hipLaunchKernelGGL(ob_copy_kernel, dim3(grid_for(g.ob_cap, 256, 128), (unsigned)p->nitems), dim3(256), 0, st, ob, g.ob_cap, g.ob_count,
+                       first ? p->obcopyA : p->obcopyB, keep_cap, g.chain_child, g.edges, g.ecap,
+                       p->d_hdr, p->extraRows, p->sh, g.skip, p->item_bytes, g.list_stride);
+}
+
+static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const int32_t *ob_count, int64_t list_stride,
+                      int which_list, hipStream_t st, const int32_t *skip = nullptr) {
+    const GreedyArgs g = greedy_args(p, phase, ob_cap, ob_count, list_stride, which_list, skip);
+    const size_t lds_bytes = greedy_lds(p, phase);
     static std::atomic<int> opted_in{0};  // the attribute is idempotent: a race sets the same value twice
     if (!opted_in.load(std::memory_order_acquire)) {
         IMU_HIP(hipFuncSetAttribute((const void *)greedy_both_kernel<true>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGreedyLdsMax));
         opted_in.store(1, std::memory_order_release);
     }
-    const int keep_cap = p->cap[first ? CAP_EDGEA : CAP_EDGEB];  // the stride the fix-up pass reads with
     const unsigned items = (unsigned)p->nitems;
-    hipLaunchKernelGGL(ob_copy_kernel, dim3(grid_for(ob_cap, 256, 128), items), dim3(256), 0, st, ob, ob_cap, ob_count,
-                       first ? p->obcopyA : p->obcopyB, keep_cap, (const int32_t *)g.chain_child, g.edges, g.ecap,
-                       hdr, p->extraRows, p->sh, skip, p->item_bytes, list_stride);
+    launch_ob_copy(p, g, phase, ob, st);
     if (lds_bytes <= (size_t)kGreedyLdsMax)
         hipLaunchKernelGGL(greedy_both_kernel<true>, dim3(1, items), dim3(kPlanThreads), lds_bytes, st, g);
     else
@@ -1874,7 +1993,41 @@ static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const i
     return launch_status();
 }
 
-static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, int64_t ldb,
+static void destroy_handles(Plan *p) {
+    if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
+}
+
+template <class T>
+int wait_word(const T *word, T want, hipStream_t st) {
+    for (long spin = 1;; ++spin) {
+        if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == want) return IMUNPACK_OK;
+        if (spin & 0xFFFF) continue;
+        // still nothing: look whether the stream has come to an end without it; a very long plan stops burning the core
+        hipError_t e = spin < (1 << 24) ? hipStreamQuery(st) : hipStreamSynchronize(st);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        if (e == hipSuccess && __atomic_load_n(word, __ATOMIC_ACQUIRE) == want) return IMUNPACK_OK;
+        g_last_hip_error = (int)e;
+        (void)hipGetLastError();
+        return IMUNPACK_EHIP;
+    }
+}
+
+template int wait_word<int32_t>(const int32_t *, int32_t, hipStream_t);
+template int wait_word<uint16_t>(const uint16_t *, uint16_t, hipStream_t);
+
+// The headers that the last launch hands over.
+static int await_headers(Plan *p, hipStream_t st) {
+    IMU_TRY(launch_status());
+    for (int i = 0; i < p->nitems; ++i) IMU_TRY(wait_word(&p->pin_hdr[i].seq, p->seq, st));
+    p->hdr = p->pin_hdr[0];
+    return IMUNPACK_OK;
+}
+
+// Plans on the device and waits for the headers.
+static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, int64_t ldb,
                         const imunpack_stats_t *stA, const imunpack_stats_t *stB, bool own_statsA,
                         bool own_statsB, hipStream_t st) {
     PlanHeader *hdr = p->d_hdr;
@@ -1890,10 +2043,19 @@ static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B
     const bool keep = p->keep_B != 0;
     const unsigned items = (unsigned)p->nitems;
     const int64_t stride = p->item_bytes, sstride = p->op_stride;
-    hipLaunchKernelGGL(setup_kernel, dim3(grid_for(std::max(std::max(idA, idC1), std::max(idB, kcA)), 256, 64), items),
-                       dim3(256), 0, st, hdr, p->rowA, idA, p->c1, idC1, p->rowB, keep ? 0 : idB,
-                       p->extraRows, (p->sB == IMUNPACK_BOTH && !keep) ? h : 0,
-                       reinterpret_cast<int32_t *>(p->cols.colA_w), keep ? 0 : 2 * kcA, keep ? p->d_keep : nullptr, stride);
+    // the row layouts keep two ints per source row and one per chunk in LDS when that fits beside the column layout's tables
+    const int most_phys = std::max(phys_cap_rows(p->cap[CAP_ROWA]), phys_cap_rows(p->cap[CAP_ROWB]));
+    const size_t fast_bytes = ((size_t)2 * std::max(n, h) + most_phys / kChunk + 8) * sizeof(int32_t);
+    const int fast_lds = fast_bytes <= (size_t)kLayoutLdsMax ? 1 : 0;
+    // the column layout: a word per column of either store, three per 64 original columns and pair of levels (sixteen pairs)
+    const size_t col_bytes = ((size_t)2 * (p->cap[CAP_C2] + 2048) + (size_t)48 * ((d + 63) / 64)) * sizeof(int32_t);
+    const size_t dyn_bytes = std::min((size_t)kLayoutLdsMax, std::max(fast_lds ? fast_bytes : 0, col_bytes));
+    static std::atomic<int> opted_in{0};  // the attributes are idempotent: a race sets the same values twice
+    if (!opted_in.load(std::memory_order_acquire)) {
+        IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
+        IMU_HIP(hipFuncSetAttribute((const void *)keep_plan_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kGreedyLdsMax));
+        opted_in.store(1, std::memory_order_release);
+    }
     // OB entry lists for UnpackBoth: the caller's (from the fused quantize pass) if complete, else
     // this call's own scan produces one.  The two operands are planned one after the other, so one
     // own buffer serves both.
@@ -1909,25 +2071,54 @@ static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B
         if (list) { sx.ob = p->ob; sx.ob_cap = p->cap[CAP_OB]; sx.ob_count = p->obcnt; }
         return scan_i32(M, rows, d, ld, p->b, &sx, p->nitems, sstride, stride, st);
     };
-    if (scanA) IMU_TRY(scan_operand(A, n, lda, p->statsA, own_statsA, listA && !callerA));
+    KeepArgs keep_args = {p->snapRoot, p->snapExp, p->snapChild, keep ? p->d_keep : nullptr, p->keep_valid, idB, p->extraRows,
+                          listB ? h : 0, reinterpret_cast<int32_t *>(p->cols.colA_w), 2 * kcA};
+    const int32_t *skip = nullptr;
+    // keep-weights mode: up to 4096 rows, which one workgroup lays out as fast as the layout kernel would
+    const size_t keep_lds = std::max(((size_t)2 * n + phys_cap_rows(p->cap[CAP_ROWA]) / kChunk + 8) * sizeof(int32_t), listA ? greedy_lds(p, 1) : 0);
+    const bool at_once = keep && items == 1 && !scanA && n <= kRowSlice && d <= kKeepPlanCols && keep_lds <= (size_t)kGreedyLdsMax;
+    if (at_once) {
+        KeepPlan f;
+        memset((void *)&f, 0, sizeof(f));
+        f.hdr = hdr;
+        f.rows = p->rowA; f.cols = p->c1; f.rowsB = p->rowB;
+        f.lay = p->layA;
+        f.rowmax = p->statsA[2]; f.colmax = p->statsA[3];
+        if (listA) {
+            f.greedy = greedy_args(p, 1, (int)stA->ob_cap, stA->ob_count, sstride, CAP_LISTA, nullptr);
+            launch_ob_copy(p, f.greedy, 1, stA->ob, st);
+        }
+        f.tmpL = p->tmpL; f.tmpCur = p->tmpCur; f.tmpP = p->tmpPA;
+        f.n = n; f.d = d; f.h = h; f.sh = p->sh; f.strategy = p->sA; f.strategyB = p->sB;
+        f.cap_phys = phys_cap_rows(p->cap[CAP_ROWA]);
+        f.keep = keep_args;
+        f.host = p->pin_hdr; f.seq = ++p->seq;
+        hipLaunchKernelGGL(keep_plan_kernel, dim3(1), dim3(kPlanThreads), keep_lds, st, f);
+        IMU_TRY(await_headers(p, st));
+        if (p->hdr.reusedB || p->hdr.overflow || p->hdr.err) return IMUNPACK_OK;
+    }
+    if (!at_once) {
+        hipLaunchKernelGGL(setup_kernel, dim3(grid_for(std::max(std::max(idA, idC1), std::max(idB, kcA)), 256, 64), items),
+                           dim3(256), 0, st, hdr, p->rowA, idA, p->c1, idC1, p->rowB, keep ? 0 : idB,
+                           p->extraRows, (p->sB == IMUNPACK_BOTH && !keep) ? h : 0,
+                           reinterpret_cast<int32_t *>(p->cols.colA_w), keep ? 0 : 2 * kcA, keep ? p->d_keep : nullptr, stride);
+        if (scanA) IMU_TRY(scan_operand(A, n, lda, p->statsA, own_statsA, listA && !callerA));
+    }
     // ---- phase 1: Unpack(A, B, I, b, strategy_A)
     auto closed_form = [&](const SlotSet &set, const int32_t *maxabs, const int32_t *via, int count, int which,
                            const int32_t *skip) {
         hipLaunchKernelGGL(level_major_kernel, dim3(1, items), dim3(kPlanThreads), 0, st, set, maxabs, via, count, p->sh,
                            p->tmpL, p->tmpCur, hdr, which, skip, stride, sstride);
     };
-    if (p->sA == IMUNPACK_ROW) closed_form(p->rowA, p->statsA[2], nullptr, n, CAP_ROWA, nullptr);
+    if (at_once) {}  // the first operand is unpacked, the second is to be unpacked anew
+    else if (p->sA == IMUNPACK_ROW) closed_form(p->rowA, p->statsA[2], nullptr, n, CAP_ROWA, nullptr);
     else if (p->sA == IMUNPACK_COL) closed_form(p->c1, p->statsA[3], nullptr, d, CAP_C1, nullptr);
     else if (callerA) IMU_TRY(run_greedy(p, 1, stA->ob, (int)stA->ob_cap, stA->ob_count, sstride, CAP_LISTA, st));
     else IMU_TRY(run_greedy(p, 1, p->ob, p->cap[CAP_OB], p->obcnt, stride, CAP_OB, st));
     if (scanB) IMU_TRY(scan_operand(B, h, ldb, p->statsB, own_statsB, listB && !callerB));
     // ---- phase 2: Unpack(B_e, A_u, S_u, b, strategy_B); B_e has d1 columns
-    const int32_t *skip = nullptr;
-    if (keep) {
-        hipLaunchKernelGGL(keep_decide_kernel, dim3(1), dim3(kPlanThreads), 0, st, p->c1, (const int32_t *)p->snapRoot,
-                           (const int32_t *)p->snapExp, (const int32_t *)p->snapChild, p->d_keep, p->keep_valid, hdr, p->rowB,
-                           idB, p->extraRows, p->sB == IMUNPACK_BOTH ? h : 0, reinterpret_cast<int32_t *>(p->cols.colA_w),
-                           2 * kcA);
+    if (keep && !at_once) {
+        hipLaunchKernelGGL(keep_decide_kernel, dim3(1), dim3(kPlanThreads), 0, st, keep_args, p->c1, hdr, p->rowB);
         skip = &p->d_keep->same;
     }
     if (p->sB == IMUNPACK_ROW) {
@@ -1942,60 +2133,20 @@ static int enqueue_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B
         IMU_TRY(run_greedy(p, 2, p->ob, p->cap[CAP_OB], p->obcnt, stride, CAP_OB, st, skip));
     }
     // ---- physical layouts
-    // the row layouts keep two ints per source row and one per chunk in LDS when that fits beside the column layout's tables
-    const int most_phys = std::max(phys_cap_rows(p->cap[CAP_ROWA]), phys_cap_rows(p->cap[CAP_ROWB]));
-    const size_t fast_bytes = ((size_t)2 * std::max(n, h) + most_phys / kChunk + 8) * sizeof(int32_t);
-    const int fast_lds = fast_bytes <= (size_t)kLayoutLdsMax ? 1 : 0;
-    // the column layout: a word per column of either store, three per 64 original columns and pair of levels (sixteen pairs)
-    const size_t col_bytes = ((size_t)2 * (p->cap[CAP_C2] + 2048) + (size_t)48 * ((d + 63) / 64)) * sizeof(int32_t);
-    const size_t dyn_bytes = std::min((size_t)kLayoutLdsMax, std::max(fast_lds ? fast_bytes : 0, col_bytes));
     const int col_blocks = p->cap[CAP_C2] <= kColSlotsLds * kPlanThreads ? 1 : kColBlocks;
     const int slices = fast_lds ? row_slices(n) + row_slices(h) : 2;
-    static std::atomic<int> layouts_opted_in{0};  // the attribute is idempotent: a race sets the same value twice
-    if (!layouts_opted_in.load(std::memory_order_acquire)) {
-        IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
-        layouts_opted_in.store(1, std::memory_order_release);
-    }
     hipLaunchKernelGGL(layouts_kernel, dim3(slices + col_blocks, items), dim3(kPlanThreads), dyn_bytes, st, p->rowA, n, p->layA,
                        phys_cap_rows(p->cap[CAP_ROWA]), p->tmpPA, p->rowB, h, p->layB,
                        phys_cap_rows(p->cap[CAP_ROWB]), p->tmpPB, p->c1, p->c2, p->cols, d,
                        phys_cap_cols(p->cap[CAP_C2]), p->s, p->sh, p->tmpE, p->tmpK, p->tmpR, p->tmpOff, hdr, fast_lds,
-                       keep ? (const int32_t *)&p->d_keep->same : (const int32_t *)nullptr, stride, p->chunkB,
+                       skip, stride, p->chunkB,
                        (int)(dyn_bytes / sizeof(int32_t)));
     if (keep)
         hipLaunchKernelGGL(keep_remember_kernel, dim3(grid_for(p->cap[CAP_C1], 256, 16)), dim3(256), 0, st, p->c1,
                            (const PlanHeader *)hdr, p->snapRoot, p->snapExp, p->snapChild, p->d_keep);
-    return launch_status();
-}
-
-static void destroy_handles(Plan *p) {
-    if (p->side) (void)hipStreamDestroy(p->side);
-    if (p->scattered) (void)hipEventDestroy(p->scattered);
-    if (p->ready) (void)hipEventDestroy(p->ready);
-    if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
-}
-
-int poll_ready(Plan *p) {
-    hipError_t e = hipErrorNotReady;
-    for (long spin = 0; spin < 20000000 && e == hipErrorNotReady; ++spin) e = hipEventQuery(p->ready);
-    if (e == hipErrorNotReady) {  // a very long plan: stop burning the core
-        (void)hipGetLastError();
-        e = hipEventSynchronize(p->ready);
-    }
-    if (e != hipSuccess) {
-        g_last_hip_error = (int)e;
-        (void)hipGetLastError();
-        return IMUNPACK_EHIP;
-    }
-    return IMUNPACK_OK;
-}
-
-int fetch_headers(Plan *p, hipStream_t st) {
-    IMU_HIP(hipMemcpyAsync(p->pin_hdr, p->d_hdr, (size_t)p->nitems * sizeof(PlanHeader), hipMemcpyDeviceToHost, st));
-    IMU_HIP(hipEventRecord(p->ready, st));
-    IMU_TRY(poll_ready(p));
-    p->hdr = p->pin_hdr[0];
-    return IMUNPACK_OK;
+    ++p->seq;
+    hipLaunchKernelGGL(publish_kernel, dim3(1, items), dim3(256), 0, st, (const PlanHeader *)hdr, p->pin_hdr, p->seq);
+    return await_headers(p, st);
 }
 
 // The plan of one product (nitems = 1), or of every product of a batch of one shape: A, B, the statistics and
@@ -2013,17 +2164,10 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         p = new (std::nothrow) Plan();
         if (!p) return IMUNPACK_ENOMEM;
         memset(p, 0, sizeof(*p));
-        if (hipEventCreateWithFlags(&p->ready, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&p->scattered, hipEventDisableTiming) != hipSuccess ||
-            hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking) != hipSuccess) {
-            (void)hipGetLastError();
-            destroy_handles(p);
-            delete p;
-            return IMUNPACK_ENOMEM;
-        }
         p->guess_fusable = 1;
     }
-    if (p->bound_pending) (void)resolve_bound(p);  // a copy into the header mirror is still in flight
+    if (p->bound_pending && p->bound_told) (void)resolve_bound(p);  // bounds on their way into the header mirror
+    p->bound_pending = 0;
     const bool same = p->valid && p->nitems == nitems && p->n == n && p->d == d && p->h == h && p->b == b && p->sA == strategy_A &&
                       p->sB == strategy_B;
     p->valid = 0;
@@ -2057,6 +2201,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
             p->pin_hdr = nullptr;
             rc = IMUNPACK_ENOMEM;
         } else {
+            memset(p->pin_hdr, 0, (size_t)nitems * sizeof(PlanHeader));
             p->pin_items = nitems;
         }
     }
@@ -2085,9 +2230,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         }
         if (!ownA) { p->statsA[0] = stats_A->rowcnt; p->statsA[1] = stats_A->colcnt; p->statsA[2] = stats_A->rowmax; p->statsA[3] = stats_A->colmax; }
         if (!ownB) { p->statsB[0] = stats_B->rowcnt; p->statsB[1] = stats_B->colcnt; p->statsB[2] = stats_B->rowmax; p->statsB[3] = stats_B->colmax; }
-        rc = enqueue_plan(p, A, lda, B, ldb, stats_A, stats_B, ownA, ownB, st);
-        if (rc != IMUNPACK_OK) break;
-        rc = fetch_headers(p, st);
+        rc = run_plan(p, A, lda, B, ldb, stats_A, stats_B, ownA, ownB, st);
         if (rc != IMUNPACK_OK) break;
         int err = 0, overflow = 0, needed[10] = {};
         for (int i = 0; i < nitems; ++i) {
@@ -2357,11 +2500,11 @@ extern "C" int imunpack_plan_export(imunpack_plan_t *p, int32_t *rowA_src, int32
 extern "C" int imunpack_plan_destroy(imunpack_plan_t *p) {
     if (!p) return IMUNPACK_OK;
     int rc = IMUNPACK_OK;
+    if (p->bound_pending && p->bound_told) (void)resolve_bound(p);
     if (p->arena) {
         hipError_t e = hipFree(p->arena);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = IMUNPACK_EHIP; }
     }
-    if (p->bound_pending) (void)resolve_bound(p);
     destroy_handles(p);
     delete p;
     return rc;

@@ -17,8 +17,6 @@
 //     former, fixup_kernel then places the higher digits of the listed OB entries.
 #include "common.h"
 
-namespace imu { int poll_ready(Plan *p); }
-
 #include <algorithm>
 #include <cstddef>
 #include <cstring>
@@ -464,6 +462,11 @@ __global__ void bound_kernel(const unsigned long long *rowsum_a, const unsigned 
     }
 }
 
+// The bounds to the host, where no GEMM launch hands them over.
+__global__ void tell_bounds_kernel(const unsigned long long *bound, PlanHeader *host, int32_t seq) {
+    if (threadIdx.x < 2) tell_bound(host, threadIdx.x, bound[threadIdx.x], seq);
+}
+
 // A repeated unpack of one plan: clears what the planner left cleared for the first.
 __global__ void reset_bound_kernel(PlanHeader *hdr, unsigned long long *rowsum_a, int rows_a,
                                    unsigned long long *rowsum_b, int rows_b) {
@@ -544,7 +547,7 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     const PlanHeader &h = p->hdr;
     const bool batch = p->nitems > 1;
     const unsigned nitems = (unsigned)p->nitems;
-    if (p->bound_pending) IMU_TRY(resolve_bound(p));  // of an earlier unpack of this plan
+    if (p->bound_pending && p->bound_told) IMU_TRY(resolve_bound(p));  // of an earlier unpack of this plan
     // the planner leaves the bounds and the row norms cleared; a repeated unpack of the same plan clears them again
     if (p->unpacked) {
         if (batch) return IMUNPACK_EINVAL;
@@ -638,15 +641,11 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     IMU_TRY(launch_status());
     p->unpacked = 1;
     if (a_stride) return IMUNPACK_OK;
-    // The bounds travel to the host on the plan's side stream, behind the scatter: the caller's stream is
-    // free to take the GEMM at once (imunpack_gemm launches it guarded and then waits for the bounds).
-    IMU_HIP(hipEventRecord(p->scattered, st));
-    IMU_HIP(hipStreamWaitEvent(p->side, p->scattered, 0));
-    IMU_HIP(hipMemcpyAsync(reinterpret_cast<char *>(p->pin_hdr) + offsetof(PlanHeader, bound),
-                           reinterpret_cast<const char *>(p->d_hdr) + offsetof(PlanHeader, bound),
-                           sizeof(p->hdr.bound), hipMemcpyDeviceToHost, p->side));
-    IMU_HIP(hipEventRecord(p->ready, p->side));
+    // The bounds stay on the device until somebody asks: imunpack_gemm launches the fused kernel at once, guarded, and it is
+    // that kernel which hands them over.
+    p->bound_stream = st;
     p->bound_pending = 1;
+    p->bound_told = 0;
     p->kept_Beu = p->keep_B ? B_eu : nullptr;
     p->kept_Beu_fp6 = p->fp6;
     return IMUNPACK_OK;
@@ -658,11 +657,26 @@ extern "C" int imunpack_unpack(imunpack_plan_t *p, const int32_t *A, int64_t lda
 }
 
 namespace imu {
+int32_t ask_bounds(Plan *p) {
+    ++p->seq;
+    p->bound_told = 1;
+    p->pin_hdr->bound[0] = p->pin_hdr->bound[1] = (unsigned long long)(uint16_t)~p->seq << 48;  // not there yet
+    return p->seq;
+}
+
 int resolve_bound(Plan *p) {
     if (!p->bound_pending) return IMUNPACK_OK;
     p->bound_pending = 0;
-    IMU_TRY(poll_ready(p));
-    memcpy(p->hdr.bound, p->pin_hdr->bound, sizeof(p->hdr.bound));
+    if (!p->bound_told) {
+        const int32_t seq = ask_bounds(p);
+        hipLaunchKernelGGL(tell_bounds_kernel, dim3(1), dim3(64), 0, p->bound_stream, (const unsigned long long *)p->d_hdr->bound, p->pin_hdr, seq);
+        IMU_TRY(launch_status());
+    }
+    for (int i = 0; i < 2; ++i) {  // the upper sixteen bits name the unpack
+        const uint16_t *tag = reinterpret_cast<const uint16_t *>(&p->pin_hdr->bound[i]) + 3;
+        IMU_TRY(wait_word(tag, (uint16_t)p->seq, p->bound_stream));
+        p->hdr.bound[i] = p->pin_hdr->bound[i] & ((1ull << 48) - 1);
+    }
     // |sum_c s^e(c) a_c b_c| <= (s - 1) * min(bound_A, bound_B): the shifted sum of all groups
     // fits int32 iff that is below 2^31.
     const unsigned long long m = p->hdr.bound[0] < p->hdr.bound[1] ? p->hdr.bound[0] : p->hdr.bound[1];

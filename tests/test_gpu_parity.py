@@ -956,7 +956,7 @@ def test_gemm_tiles_of_either_size(imu, n, d, h, b, strategies):
 
 @pytest.mark.parametrize("n,d,h,b,sa,sb,kind", [
     (5, 8200, 7, 8, COL, COL, "every"),     # more column slots than one workgroup lays out
-    (5, 8190, 7, 8, COL, COL, "every"),     # just as many as it does
+    (5, 6140, 7, 8, COL, COL, "every"),     # just as many as it does
     (9, 8192, 6, 4, COL, COL, "deep"),      # many pairs of levels
     (40, 600, 33, 2, COL, COL, "deep"),
     (30, 4100, 20, 8, BOTH, BOTH, "deep"),
