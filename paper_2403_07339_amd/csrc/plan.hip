@@ -356,6 +356,7 @@ struct GreedyArgs {
     int whichR, whichC, whichE;
     int s, sh;
     const int32_t *skip;           // keep-weights mode: non-zero there = nothing to do
+    int lds_words;                 // dynamic LDS of the launch
 };
 
 // An edge of the greedy: an OB entry's current row slot, column slot and the number of base-s digits
@@ -407,13 +408,30 @@ __device__ __forceinline__ void move_to_item(GreedyArgs &g) {
     g.ob_count = item_at(g.ob_count, blockIdx.y * g.list_stride);
 }
 
-template <bool LDS>
-__device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_counts) {
-    __shared__ int s_top[2], s_T[2][4];
-    __shared__ int s_pick[kPlanWaves][256];  // per wave: the slots picked in one 256-slot step
-    __shared__ int s_found[kPlanWaves], s_positive[kPlanWaves];
-    __shared__ int lds[40];
-    __shared__ int s_count;
+//
+// If they fit the LDS that the counts leave, the edges stay there from the first batch to the last (one that is finished
+// becomes 0): nothing the workgroup waits for between batches is in memory then, and its barriers need not wait for the
+// stores of the new slots.  With the edges in the two lists, which every pass reads and rewrites, a batch of a small operand
+// took 3 us and more, mostly round trips to memory.  (Edges in registers, 40 a thread, would reach further; the compiler
+// spills them.)
+struct GreedyShared {
+    int top[2], T[2][4];
+    int pick[kPlanWaves][256];  // per wave: the slots picked in one 256-slot step
+    int found[kPlanWaves], positive[kPlanWaves];
+    int lds[40];
+    int count;
+};
+
+template <bool LDS, bool RES>  // LDS: the counts are in LDS; RES: the edges too
+__device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_counts, GreedyShared &sh, int nob, int extras, const int deep) {
+    constexpr int UE = 4;  // edges in LDS that a thread looks at together
+    auto &s_top = sh.top;
+    auto &s_T = sh.T;
+    auto &s_pick = sh.pick;
+    auto &s_found = sh.found;
+    auto &s_positive = sh.positive;
+    auto &lds = sh.lds;
+    int &s_count = sh.count;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const unsigned long long below = (1ull << lane) - 1ull;
     int nr = g.second ? hdr->h_u : hdr->n_u, nc = hdr->d1;
@@ -424,36 +442,10 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
         }
         for (int x = threadIdx.x; x < nc; x += kPlanThreads) identity_slot(g.cols, x);
     }
-    const int nob = *g.ob_count;
     if (nob > g.ob_cap) {
         if (threadIdx.x == 0) flag_overflow(hdr, g.which_list, nob);
         return;
     }
-    const int rpad = (g.rows.cap + 7) & ~3, cpad = (g.cols.cap + 7) & ~3;  // int4 reads may run past the last slot
-    int32_t *rc = LDS ? lds_counts : g.rcnt;
-    int32_t *cc = LDS ? lds_counts + rpad : g.ccnt;
-    // ---- starting counts
-    int deep = 0;
-    const int s2 = g.s * g.s;
-    for (int x = threadIdx.x; x < rpad; x += kPlanThreads) {
-        rc[x] = x < nr ? g.rowcnt[x] + (g.extra_rows ? g.extra_rows[x] : 0) : 0;
-        if (x < nr && g.rowmax[x] >= s2) deep = 1;
-    }
-    for (int x = threadIdx.x; x < cpad; x += kPlanThreads)
-        cc[x] = x < nc ? g.colcnt[g.chain_root ? g.chain_root[x] : x] : 0;
-    if (threadIdx.x == 0) {
-        s_count = 0;
-        s_top[0] = s_top[1] = 0;
-    }
-    __syncthreads();
-    // ---- the first edge list was written by ob_copy_kernel: one packed edge per OB entry, then the extra
-    // edges of repeated columns (second operand only; the rows they touch start with that many more OB
-    // entries)
-    unsigned long long *list0 = g.edges, *list1 = g.edges + ((g.ecap + 1) & ~1);  // both 16-byte aligned
-    if (g.chain_child && threadIdx.x == 0) s_count = load_agent(&hdr->extras);
-    __syncthreads();
-    deep = block_max(deep, lds);
-    const int extras = s_count;
     const long long Etotal = (long long)nob + extras;
     if (threadIdx.x == 0) {
         *(g.second ? &hdr->edgesB : &hdr->edgesA) = (int)min(Etotal, 2147483647ll);
@@ -463,6 +455,59 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
         if (threadIdx.x == 0) flag_overflow(hdr, g.whichE, (int)min(Etotal, 1ll << 30));
         return;
     }
+    // ---- the first edge list was written by ob_copy_kernel: one packed edge per OB entry, then the extra
+    // edges of repeated columns (second operand only; the rows they touch start with that many more OB
+    // entries)
+    unsigned long long *list0 = g.edges, *list1 = g.edges + ((g.ecap + 1) & ~1);  // both 16-byte aligned
+    // between the phases of a batch: what the threads hand to one another is in LDS if the edges are in registers
+    auto sync = [] {
+        if constexpr (RES) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else __syncthreads();
+    };
+    const int rpad = (g.rows.cap + 7) & ~3, cpad = (g.cols.cap + 7) & ~3;  // int4 reads may run past the last slot
+    int32_t *rc = LDS ? lds_counts : g.rcnt;
+    int32_t *cc = LDS ? lds_counts + rpad : g.ccnt;
+    unsigned long long *held = reinterpret_cast<unsigned long long *>(lds_counts + rpad + cpad);
+    if constexpr (RES)
+        for (int e = threadIdx.x; e < Etotal; e += kPlanThreads) held[e] = list0[e];
+    // ---- starting counts
+    auto start_counts = [&]() __attribute__((always_inline)) {
+        for (int x = threadIdx.x; x < rpad; x += kPlanThreads)
+            rc[x] = x < nr ? g.rowcnt[x] + (g.extra_rows ? g.extra_rows[x] : 0) : 0;
+        for (int x = threadIdx.x; x < cpad; x += kPlanThreads)
+            cc[x] = x < nc ? g.colcnt[g.chain_root ? g.chain_root[x] : x] : 0;
+    };
+    start_counts();
+    if (threadIdx.x == 0) {
+        s_count = 0;
+        s_top[0] = s_top[1] = 0;
+    }
+    __syncthreads();
+    // If there are entries of three or more digits: the most that any row, any column holds.  The slot that a split appends
+    // starts with those of the split slot that are left (entries only lose digits), so its count never exceeds this, and
+    // slots with a larger count are taken before it whatever is split in between.
+    int deep_row = 0x7fffffff, deep_col = 0x7fffffff;
+    if (RES && deep) {
+        for (int x = threadIdx.x; x < rpad; x += kPlanThreads) rc[x] = 0;
+        for (int x = threadIdx.x; x < cpad; x += kPlanThreads) cc[x] = 0;
+        __syncthreads();
+        for (int e = threadIdx.x; e < Etotal; e += kPlanThreads) {
+            const unsigned lo = (unsigned)held[e], hi = (unsigned)(held[e] >> 32);
+            if (((lo >> kEdgeSlotBits) | ((hi >> kEdgeSlotBits) << 3)) > 2u) {
+                atomicAdd(&rc[lo & kEdgeSlotMask], 1);
+                atomicAdd(&cc[hi & kEdgeSlotMask], 1);
+            }
+        }
+        __syncthreads();
+        int mr = 0, mc = 0;
+        for (int x = threadIdx.x; x < nr; x += kPlanThreads) mr = max(mr, rc[x]);
+        for (int x = threadIdx.x; x < nc; x += kPlanThreads) mc = max(mc, cc[x]);
+        deep_row = block_max(mr, lds);
+        deep_col = block_max(mc, lds);
+        start_counts();
+        __syncthreads();
+    }
+    const int nr0 = nr, nc0 = nc;  // the slots below are unsplit originals
     int E = (int)Etotal, cur = 0;  // live edges; they are in list `cur`
     int prev_kind = -1;            // 1: the batch before split rows, 0: columns
     const long long max_batches = 32ll * Etotal + 64;  // every batch retires >= one digit of one entry
@@ -503,7 +548,8 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
             atomicMax(&s_top[0], m0);
             atomicMax(&s_top[1], m1);
         }
-        __syncthreads();
+        if (deep) __syncthreads();  // slots appended by an earlier batch are read from memory when they are split in turn
+        else sync();
         const int c0 = s_top[0], c1 = s_top[1];  // cleared again in step 3, past the next barrier
         if (c0 <= 0 && c1 <= 0) break;
         const bool isrow = c0 >= c1;  // rows win ties (Alg. 4: "else if c0 >= c1")
@@ -512,7 +558,8 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
         const int N = isrow ? nr : nc;
         // (2) slots with lo <= count <= hi are split in this batch, numbered in index order
         const int hi = isrow ? c0 : c1;
-        int lo = deep ? hi : (isrow ? max(c1, 1) : c0 + 1);
+        int lo = isrow ? max(c1, 1) : c0 + 1;
+        if (deep) lo = min(hi, max(lo, isrow ? deep_row < hi ? deep_row + 1 : hi : deep_col < hi ? deep_col + 1 : hi));
         // (1b) While the sequential algorithm stays on one side, the counts of that side do not change (no
         // entry has three digits) and only the top count of the other side falls, so the next batch would
         // be of the same kind with a lower bound: rows with count >= G(lo), G(lo) = top column count once
@@ -531,11 +578,29 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
                 int32_t *tmp = other + No4;  // zero on entry (slots that do not exist yet) and on exit
                 const unsigned long long *__restrict__ src = cur ? list1 : list0;
                 if (threadIdx.x < 8) (&s_T[0][0])[threadIdx.x] = 0;
-                __syncthreads();
+                sync();
                 for (int round = 0; round < 256; ++round) {
                     int *T = s_T[round & 1];  // cleared above or during the round before
-                    auto count_pass = [&](auto isrow_c) {
+                    auto count_pass = [&](auto isrow_c) __attribute__((always_inline)) {
                         constexpr bool IR = decltype(isrow_c)::value;
+                        auto outlives = [&](unsigned xs, unsigned os, bool present) __attribute__((always_inline)) {
+                            const int c = cnt[xs];  // slot 0's count is harmless for an absent entry ...
+                            const int k = present ? min(4, max(0, lo - c)) : 0;  // the entry outlives the bounds lo, .., lo - k + 1
+                            if (k) atomicAdd(reinterpret_cast<unsigned *>(&tmp[os]), 0x01010101u >> (8 * (4 - k)));
+                        };
+                        if constexpr (RES) {
+                            for (int e0 = threadIdx.x; e0 < E; e0 += kPlanThreads * UE) {
+                                unsigned long long ed[UE];
+#pragma unroll
+                                for (int u = 0; u < UE; ++u) ed[u] = e0 + u * kPlanThreads < E ? held[e0 + u * kPlanThreads] : 0ull;
+#pragma unroll
+                                for (int u = 0; u < UE; ++u) {
+                                    const unsigned el = (unsigned)ed[u] & kEdgeSlotMask, eh = (unsigned)(ed[u] >> 32) & kEdgeSlotMask;
+                                    outlives(IR ? el : eh, IR ? eh : el, ed[u] != 0ull);
+                                }
+                            }
+                            return;
+                        }
                         constexpr int UW = 8;  // 16-byte loads (two entries each) per thread in flight
                         for (int e0 = 0; e0 < E; e0 += kPlanThreads * 2 * UW) {
                             unsigned long long ed[2 * UW];
@@ -553,17 +618,14 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
                             }
 #pragma unroll
                             for (int u = 0; u < 2 * UW; ++u) {
-                                const unsigned elo = (unsigned)ed[u], ehi = (unsigned)(ed[u] >> 32);
-                                const unsigned xw = IR ? elo : ehi, ow = IR ? ehi : elo;
-                                const int c = cnt[xw & kEdgeSlotMask];  // slot 0's count is harmless for an absent entry ...
-                                const int k = (elo | ehi) ? min(4, max(0, lo - c)) : 0;  // the entry outlives the bounds lo, .., lo - k + 1
-                                if (k) atomicAdd(reinterpret_cast<unsigned *>(&tmp[ow & kEdgeSlotMask]), 0x01010101u >> (8 * (4 - k)));
+                                const unsigned el = (unsigned)ed[u] & kEdgeSlotMask, eh = (unsigned)(ed[u] >> 32) & kEdgeSlotMask;
+                                outlives(IR ? el : eh, IR ? eh : el, ed[u] != 0ull);
                             }
                         }
                     };
                     if (isrow) count_pass(std::true_type{});
                     else count_pass(std::false_type{});
-                    __syncthreads();
+                    sync();
                     int m0 = 0, m1 = 0, m2 = 0, m3 = 0;
                     if (threadIdx.x < 4) s_T[(round & 1) ^ 1][threadIdx.x] = 0;
                     for (int x = threadIdx.x * 4; x < No4; x += kPlanThreads * 4) {  // read and clear
@@ -588,7 +650,7 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
                         atomicMax(&T[2], m2);
                         atomicMax(&T[3], m3);
                     }
-                    __syncthreads();
+                    sync();
                     int now = lo;
                     bool stable = false;
                     for (int j = 0; j < 4; j = lo - now) {  // T[j]: the other side's top count with the bound lo - j
@@ -607,7 +669,7 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
                     lo = now;
                     if (stable) break;
                 }
-                __syncthreads();  // the cleared counters and the last reads of T, before anything else touches them
+                sync();  // the cleared counters and the last reads of T, before anything else touches them
             }
         }
         const int seg = isrow ? segR : segC;
@@ -625,7 +687,7 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
             s_found[wave] = found;
             s_positive[wave] = positive;
         }
-        __syncthreads();
+        sync();
         int run = 0, nb = 0, npos = 0;
 #pragma unroll
         for (int w = 0; w < kPlanWaves; ++w) {
@@ -673,7 +735,8 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
             for (int j = lane; j < all; j += 64) {
                 const int pk = s_pick[wave][j];
                 const int X = x0 + (pk & 0xFF), newX = N + run + j;
-                const int root = mine.root[X], ex = mine.exp[X];
+                const bool orig = X < (isrow ? nr0 : nc0);
+                const int root = orig ? X : mine.root[X], ex = orig ? 0 : mine.exp[X];
                 mine.time[X] = (uint32_t)bid;
                 mine.child[X] = newX;
                 mine.root[newX] = root;
@@ -689,33 +752,71 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
             s_count = 0;
             s_top[0] = s_top[1] = 0;
         }
-        __syncthreads();
+        sync();
         if (finishes) {
             for (int x = threadIdx.x; x < rpad; x += kPlanThreads) rc[x] = 0;
             for (int x = threadIdx.x; x < cpad; x += kPlanThreads) cc[x] = 0;
             if (isrow) nr += nb; else nc += nb;
             break;
         }
-        // (4) the pass.  The survivors of U entries per lane are appended with one counter update per wave.
+        // (4) the pass
+        if constexpr (RES) {
+            auto pass = [&](auto isrow_c) __attribute__((always_inline)) {
+                constexpr bool IR = decltype(isrow_c)::value;
+                for (int e0 = threadIdx.x; e0 < E; e0 += kPlanThreads * UE) {
+                    unsigned el[UE], eh[UE];
+                    int c[UE];
+#pragma unroll
+                    for (int u = 0; u < UE; ++u) {
+                        const unsigned long long ed = e0 + u * kPlanThreads < E ? held[e0 + u * kPlanThreads] : 0ull;
+                        el[u] = (unsigned)ed;
+                        eh[u] = (unsigned)(ed >> 32);
+                    }
+#pragma unroll
+                    for (int u = 0; u < UE; ++u) c[u] = cnt[(IR ? el[u] : eh[u]) & kEdgeSlotMask];  // slot 0's is harmless for an absent edge
+#pragma unroll
+                    for (int u = 0; u < UE; ++u) {
+                        if ((el[u] | eh[u]) == 0u || c[u] >= 0 || ~c[u] >= nb) continue;  // the mark -(k + 1) names new slot N + k
+                        unsigned long long left = 0;  // finished
+                        const unsigned levels = (el[u] >> kEdgeSlotBits) | ((eh[u] >> kEdgeSlotBits) << 3);
+                        if (levels > 2u) {  // still OB in the new slot: move on, one digit fewer
+                            const int newX = N + ~c[u];
+                            atomicAdd(&cnt[newX], 1);
+                            left = IR ? pack_edge(newX, (int)(eh[u] & kEdgeSlotMask), (int)levels - 1)
+                                      : pack_edge((int)(el[u] & kEdgeSlotMask), newX, (int)levels - 1);
+                        } else {
+                            atomicSub(&other[(IR ? eh[u] : el[u]) & kEdgeSlotMask], 1);
+                        }
+                        held[e0 + u * kPlanThreads] = left;
+                    }
+                }
+            };
+            if (isrow) pass(std::true_type{});
+            else pass(std::false_type{});
+            sync();
+            if (isrow) nr += nb; else nc += nb;
+            continue;
+        }
+        // The survivors of a lane's entries are appended with one counter update per wave.
         unsigned long long *dst = cur ? list0 : list1;
         // One CU's vector ALU bounds this pass, so it is written for few instructions: the side of the batch
         // and whether entries can move on (three or more digits) are compile-time cases, the common case
         // (two digits: an entry of a split slot is simply finished) has one predicated LDS update per entry.
-        auto process = [&](auto &e, auto isrow_c, auto deep_c) {  // e[u]: packed edge, 0 if absent
+        auto process = [&](auto &e, auto isrow_c, auto deep_c) __attribute__((always_inline)) {  // e[u]: packed edge, 0 if absent
             constexpr bool IR = decltype(isrow_c)::value, DP = decltype(deep_c)::value;
-            constexpr int U = sizeof(e) / sizeof(unsigned long long);
-            unsigned xw[U], ow[U];  // the word that names the slot on the batch's side, and the other one
-            int c[U];
+            constexpr int UE = sizeof(e) / sizeof(unsigned long long);
+            unsigned xw[UE], ow[UE];  // the word that names the slot on the batch's side, and the other one
+            int c[UE];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {  // marks do not change during a pass; slot 0's count is harmless for absent edges
+            for (int u = 0; u < UE; ++u) {  // marks do not change during a pass; slot 0's count is harmless for absent edges
                 const unsigned lo = (unsigned)e[u], hi = (unsigned)(e[u] >> 32);
                 xw[u] = IR ? lo : hi;
                 ow[u] = IR ? hi : lo;
                 c[u] = cnt[xw[u] & kEdgeSlotMask];
             }
-            int off[U], all = 0;  // survivors are packed edge by edge: the lanes of a store write side by side
+            int off[UE], all = 0;  // survivors are packed edge by edge: the lanes of a store write side by side
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < UE; ++u) {
                 bool live = (xw[u] | ow[u]) != 0u;
                 const bool split = live && c[u] < 0 && ~c[u] < nb;  // the mark -(k + 1) names new slot N + k
                 if constexpr (DP) {
@@ -746,13 +847,13 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
             if (lane == 0) base = atomicAdd(&s_count, all);
             base = __builtin_amdgcn_readfirstlane(base);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < UE; ++u)
                 if (off[u] >= 0) dst[base + off[u]] = e[u];
         };
-        auto run_pass = [&](auto isrow_c, auto deep_c) {  // the list of packed edges, two per load
+        auto run_pass = [&](auto isrow_c, auto deep_c) __attribute__((always_inline)) {  // the list of packed edges, two per load
             constexpr int U2 = 8;
             const unsigned long long *__restrict__ src = cur ? list1 : list0;
-            auto fetch = [&](int e0, unsigned long long (&fe)[U2]) {
+            auto fetch = [&](int e0, unsigned long long (&fe)[U2]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int u = 0; u < U2; u += 2) {
                     const int idx = e0 + (u * kPlanThreads + (int)threadIdx.x * 2);
@@ -792,6 +893,20 @@ __device__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_c
         *(g.second ? &hdr->h_u : &hdr->n_u) = nr;
         *(g.second ? &hdr->d_u : &hdr->d1) = nc;
     }
+}
+
+template <bool LDS, bool MAY_HOLD = LDS>
+__device__ __forceinline__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_counts) {
+    __shared__ GreedyShared sh;
+    const int nob = *g.ob_count, extras = g.chain_child ? load_agent(&hdr->extras) : 0;
+    const int nr = g.second ? hdr->h_u : hdr->n_u;
+    int deep = 0;
+    for (int x = threadIdx.x; x < nr; x += kPlanThreads) deep |= g.rowmax[x] >= g.s * g.s;
+    deep = __syncthreads_or(deep);
+    const long long E = (long long)nob + extras;
+    const long long room = ((long long)g.lds_words - ((g.rows.cap + 7) & ~3) - ((g.cols.cap + 7) & ~3)) / 2;
+    if (MAY_HOLD && E <= room) greedy_run<LDS, MAY_HOLD>(g, hdr, lds_counts, sh, nob, extras, deep);
+    else greedy_run<LDS, false>(g, hdr, lds_counts, sh, nob, extras, deep);
 }
 
 template <bool LDS>
@@ -1915,7 +2030,7 @@ __global__ __launch_bounds__(kPlanThreads) void keep_plan_kernel(KeepPlan f) {
     }
     __syncthreads();
     if (f.strategy == IMUNPACK_BOTH) {
-        greedy_both<true>(f.greedy, hdr, dyn);
+        greedy_both<true, false>(f.greedy, hdr, dyn);  // (the edges stay in memory: this kernel has no registers to spare)
     } else {
         const bool by_row = f.strategy == IMUNPACK_ROW;
         level_major<4>(by_row ? f.rows : f.cols, by_row ? f.rowmax : f.colmax, nullptr, by_row ? f.n : f.d, f.sh, f.tmpL, f.tmpCur, hdr,
@@ -1933,6 +2048,12 @@ __global__ __launch_bounds__(kPlanThreads) void keep_plan_kernel(KeepPlan f) {
 static constexpr int kGreedyLdsMax = 136 * 1024;  // dynamic LDS the greedy may use for the two count vectors
 static constexpr int kKeepPlanCols = 16384;       // columns that keep_plan_kernel sets up and compares in one workgroup
 static constexpr int kLayoutLdsMax = 140 * 1024;  // dynamic LDS the layouts kernel may use (its static tables take about 11 KiB)
+
+// dynamic LDS of the greedy's two count vectors
+static size_t greedy_lds(const Plan *p, int phase) {
+    const SlotSet &rows = phase == 1 ? p->rowA : p->rowB, &cols = phase == 1 ? p->c1 : p->c2;
+    return ((size_t)((rows.cap + 7) & ~3) + (size_t)((cols.cap + 7) & ~3)) * sizeof(int32_t);
+}
 
 // ob: the operand's OB entry list ([3][ob_cap], count on the device)
 static GreedyArgs greedy_args(const Plan *p, int phase, int ob_cap, const int32_t *ob_count, int64_t list_stride, int which_list,
@@ -1957,13 +2078,10 @@ static GreedyArgs greedy_args(const Plan *p, int phase, int ob_cap, const int32_
     g.whichE = first ? CAP_EDGEA : CAP_EDGEB;
     g.s = p->s; g.sh = p->sh;
     g.skip = skip;
+    // the counts, and room for edges: a workgroup per CU as long as there are CUs for the items
+    const size_t counts = greedy_lds(p, phase), room = p->nitems <= 256 ? 96 * 1024 : 32 * 1024;
+    g.lds_words = (int)(std::min(counts + std::min(room, (size_t)g.ecap * 8), std::max(counts, (size_t)kGreedyLdsMax)) / sizeof(int32_t));
     return g;
-}
-
-// dynamic LDS of the greedy's two count vectors
-static size_t greedy_lds(const Plan *p, int phase) {
-    const SlotSet &rows = phase == 1 ? p->rowA : p->rowB, &cols = phase == 1 ? p->c1 : p->c2;
-    return ((size_t)((rows.cap + 7) & ~3) + (size_t)((cols.cap + 7) & ~3)) * sizeof(int32_t);
 }
 
 static void launch_ob_copy(const Plan *p, const GreedyArgs &g, int phase, const int32_t *ob, hipStream_t st) {
@@ -1987,7 +2105,7 @@ static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const i
     const unsigned items = (unsigned)p->nitems;
     launch_ob_copy(p, g, phase, ob, st);
     if (lds_bytes <= (size_t)kGreedyLdsMax)
-        hipLaunchKernelGGL(greedy_both_kernel<true>, dim3(1, items), dim3(kPlanThreads), lds_bytes, st, g);
+        hipLaunchKernelGGL(greedy_both_kernel<true>, dim3(1, items), dim3(kPlanThreads), (size_t)g.lds_words * sizeof(int32_t), st, g);
     else
         hipLaunchKernelGGL(greedy_both_kernel<false>, dim3(1, items), dim3(kPlanThreads), 0, st, g);
     return launch_status();
@@ -2086,6 +2204,7 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
         f.rowmax = p->statsA[2]; f.colmax = p->statsA[3];
         if (listA) {
             f.greedy = greedy_args(p, 1, (int)stA->ob_cap, stA->ob_count, sstride, CAP_LISTA, nullptr);
+            f.greedy.lds_words = (int)(keep_lds / sizeof(int32_t));
             launch_ob_copy(p, f.greedy, 1, stA->ob, st);
         }
         f.tmpL = p->tmpL; f.tmpCur = p->tmpCur; f.tmpP = p->tmpPA;
