@@ -71,6 +71,9 @@ struct GemmArgs {
     const PlanHeader *hdr;    // nullptr: not a batch
     int64_t a_stride, b_stride, c_stride, plan_stride, scale_stride;  // bytes from item to item
     int32_t *refused;
+    // split: two words per meeting point (arrivals, how many have left their sums), and the sums of those that came first
+    int32_t *meet, *sums;
+    int most_parts;
     int lmaxA;                // largest number of digit levels of a row of A
     int kwaves;               // gemm_small_kernel: waves that share the contraction
     // benchmark reporting: if set, workgroup 0 writes {shader clock ticks, 100 MHz wall ticks} of its K loop
@@ -80,11 +83,15 @@ struct GemmArgs {
 // XCD-aware tile order: workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2,
 // so ids that land on one XCD are given one contiguous run of tiles; inside a run the tiles walk
 // bands of 4 tile-rows so that an XCD's resident workgroups share A and B panels.
+__device__ __forceinline__ void place_tile(int logical, int mtiles, int ntiles, int &tm, int &tn);
 __device__ __forceinline__ void tile_of(int wg, int mtiles, int ntiles, int &tm, int &tn) {
     const int total = mtiles * ntiles;
     const int xcd = wg & 7, idx = wg >> 3;
     const int per = total >> 3, rem = total & 7;
     const int logical = xcd * per + min(xcd, rem) + idx;
+    place_tile(logical, mtiles, ntiles, tm, tn);
+}
+__device__ __forceinline__ void place_tile(int logical, int mtiles, int ntiles, int &tm, int &tn) {
     constexpr int kBand = 4;
     const int band_sz = kBand * ntiles;
     const int band = logical / band_sz;
@@ -93,6 +100,38 @@ __device__ __forceinline__ void tile_of(int wg, int mtiles, int ntiles, int &tm,
     const int in_band = logical - band * band_sz;
     tm = first_m + in_band % rows_in_band;
     tn = in_band / rows_in_band;
+}
+
+// A launch of whole tiles ends in a round that leaves CUs idle (561 tiles on 256 CUs are 2.2 rounds, paid as 3).  Here the
+// tiles of that round are cut along the contraction into as many equal parts as there are CUs for (up to `most`), one
+// workgroup each.  All workgroups of an XCD still walk the contraction side by side, which is what lets its L2 serve them:
+// dealing tiles x k-tiles out in equal stretches, every CU at a k-tile of its own, left no CU idle and was slower for all
+// that (344 -> 411 us at 4096 x 8228 x 11013).
+constexpr int kXcdCus = 32;
+struct Piece {
+    int tile, ka, kb;  // tile of the XCD's order, its k-tiles [ka, kb)
+    int parts, slot;   // parts of the tile; where they meet (slot, slot + 1, ... for the sums of all but the last)
+};
+__device__ __forceinline__ bool piece_of(int wg, int mtiles, int ntiles, int K, int most, Piece &pc) {
+    const int total = mtiles * ntiles, xcd = wg & 7, idx = wg >> 3;
+    const int per = total >> 3, rem = total & 7;
+    const int T = per + (xcd < rem ? 1 : 0), first = xcd * per + min(xcd, rem);
+    const int whole = T / kXcdCus * kXcdCus, m = T - whole;
+    pc.ka = 0;
+    pc.kb = K;
+    pc.parts = 1;
+    pc.slot = 0;
+    pc.tile = first + idx;
+    if (idx < whole) return true;
+    if (m == 0) return false;
+    pc.parts = min(kXcdCus / m, most);
+    const int t = idx - whole, part = t / m;
+    if (part >= pc.parts) return false;
+    pc.tile = first + whole + t % m;
+    pc.slot = xcd * kXcdCus + (t % m) * pc.parts;
+    pc.ka = K * part / pc.parts;
+    pc.kb = K * (part + 1) / pc.parts;
+    return true;
 }
 
 // One direct-to-LDS load: every lane fetches 16 bytes from gbase + voff and the wave's 1 KiB lands
@@ -124,7 +163,7 @@ __device__ __forceinline__ const int8_t *uniform_ptr(const int8_t *p) {
 // BATCH: the items of a batch (blockIdx.y) in one launch; what the plan decides comes from the item's header.  A
 // variant of its own: read through a run-time choice, those values cost the one-product kernel its last
 // registers (101 spilled; 348 -> 460 us on a 4096 x 8228 x 11013 unpacked product).
-template <int MODE, bool FP6, bool BATCH = false>  // MODE 0: fused epilogue, 1: int64 segment into C_u
+template <int MODE, bool FP6, bool BATCH = false, bool SPLIT = false>  // SPLIT: pieces (see piece_of); MODE 0: fused epilogue, 1: int64 segment into C_u
 __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     constexpr int kRowB = FP6 ? 96 : BK;           // bytes of a row of the operand per k-tile
     constexpr int kPitch = FP6 ? 112 : BK;         // bytes from row to row in LDS
@@ -154,7 +193,18 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     int tm, tn;
-    tile_of(blockIdx.x, mtiles, ntiles, tm, tn);
+    Piece pc;
+    const int ktiles = kt1;
+    if constexpr (SPLIT) {
+        if (!piece_of(blockIdx.x, mtiles, ntiles, ktiles, g.most_parts, pc)) return;
+        place_tile(pc.tile, mtiles, ntiles, tm, tn);
+        kt0 = __builtin_amdgcn_readfirstlane(pc.ka);
+        kt1 = __builtin_amdgcn_readfirstlane(pc.kb);
+        tm = __builtin_amdgcn_readfirstlane(tm);
+        tn = __builtin_amdgcn_readfirstlane(tn);
+    } else {
+        tile_of(blockIdx.x, mtiles, ntiles, tm, tn);
+    }
     const int m0 = tm * BM, n0 = tn * BN;
     const unsigned lds0 = (unsigned)(size_t)smem;
 
@@ -195,10 +245,13 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         v_delta = hdr->run_blk0[r] - hdr->run_kt0[r];
         v_shift = g.sh * (hdr->grp_exp[hdr->run_grp[r]] - hdr->grp_exp[hdr->run_grp[r1]]);
     } else {
-        v_end = lane < nbound ? g.bound_kt[lane] + 1 : kt1;
+        v_end = lane < nbound ? g.bound_kt[lane] + 1 : ktiles;
         v_delta = g.seg_delta[min(lane, nbound)];
     }
-    int la_seg = 0, la_end = __builtin_amdgcn_readlane(v_end, 0), la_delta = __builtin_amdgcn_readlane(v_delta, 0);
+    int seg0 = 0;  // the segment of the first k-tile
+    if constexpr (SPLIT)
+        while (kt0 >= __builtin_amdgcn_readlane(v_end, seg0) && seg0 < nbound) ++seg0;
+    int la_seg = seg0, la_end = __builtin_amdgcn_readlane(v_end, seg0), la_delta = __builtin_amdgcn_readlane(v_delta, seg0);
     auto ring = [](int slot, int k) { slot += k; return slot >= kRing ? slot - kRing : slot; };
     const int8_t *pg = nullptr;
     unsigned dl = 0;
@@ -318,8 +371,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     // loads); past the barrier that holds for all waves, so step 4 may prefetch fragments of k-tile
     // kt+1 and stream B(kt+2) into the slot of A(kt).
     int kt = kt0;
-    for (int seg = 0; seg <= nbound; ++seg) {
-        const int shv = seg == 0 ? 0 : BATCH ? __builtin_amdgcn_readlane(v_shift, seg - 1) : g.bound_sh[seg - 1];
+    int seg = seg0;
+    for (; seg <= nbound && (!SPLIT || kt < kt1); ++seg) {
+        const int shv = seg == seg0 ? 0 : BATCH ? __builtin_amdgcn_readlane(v_shift, seg - 1) : g.bound_sh[seg - 1];
         if (shv != 0) {  // start of the next exponent group: Horner step
             // The accumulators fill the whole accumulation register file (a0..a255), so shifting every
             // one of those registers shifts every accumulator, whichever block sits where.  Written
@@ -372,7 +426,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                   "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
                 : [sh] "s"(shv));
         }
-        const int kend = BATCH ? __builtin_amdgcn_readlane(v_end, seg) : seg < nbound ? g.bound_kt[seg] + 1 : kt1;
+        int kend = BATCH ? __builtin_amdgcn_readlane(v_end, seg) : seg < nbound ? g.bound_kt[seg] + 1 : kt1;
+        if constexpr (SPLIT) kend = min(kend, kt1);
         for (; kt < kend; ++kt) {
             const int8_t *stA = smem + sa * kHalfBytes, *stB = smem + ring(sa, 1) * kHalfBytes;
             const int8_t *stA1 = smem + ring(sa, 2) * kHalfBytes, *stB1 = smem + ring(sa, 3) * kHalfBytes;
@@ -401,6 +456,52 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // drain the clamped tail loads before LDS is reused
     __syncthreads();  // all fragment reads done: the buffers may be reused by the epilogue
+
+    // A part of a tile.  All but the last to arrive leave their sums and are done; the last adds them to its own and goes on to
+    // the epilogue (it may have to wait for the end of their stores, from workgroups that are running: never for one that has
+    // yet to start).  The accumulators count in units of the segment they ended in: `rest` brings a part that ends before
+    // the last group to the units of that group.
+    int rest = 0, partners = 0;
+    const int32_t *partner = nullptr;
+    if constexpr (SPLIT) {
+        if (pc.parts > 1) {
+            for (int x = seg - 1; x < nbound; ++x) rest += g.bound_sh[x];
+            int32_t *meet = g.meet + 2 * pc.slot, *sums = g.sums + (size_t)pc.slot * (BM * BN) + 4 * tid;
+            int32_t *turn = reinterpret_cast<int32_t *>(smem);
+            if (tid == 0) *turn = __hip_atomic_fetch_add(meet, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            const int came = __builtin_amdgcn_readfirstlane(*turn);
+            if (came < pc.parts - 1) {
+                sums += (size_t)came * (BM * BN);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        int32_t *q = sums + ((i * 4 + j) * 16) * kGemmThreads;
+#pragma unroll
+                        for (int r = 0; r < 16; r += 4, q += 4 * kGemmThreads) {
+                            const v4i x = {(int32_t)acc[i][j][r] << rest, (int32_t)acc[i][j][r + 1] << rest, (int32_t)acc[i][j][r + 2] << rest,
+                                           (int32_t)acc[i][j][r + 3] << rest};
+                            // through to where every XCD reads it (and no overwriting of x in the next cycles: the compiler does not
+                            // know that this is a store of four words)
+                            asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 3" : : "v"(q), "v"(x) : "memory");
+                        }
+                    }
+                stores_done();
+                __syncthreads();
+                if (tid == 0) __hip_atomic_fetch_add(meet + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return;
+            }
+            if (tid == 0) {
+                while (__hip_atomic_load(meet + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < pc.parts - 1) __builtin_amdgcn_s_sleep(2);
+                __hip_atomic_store(meet + 1, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+                __hip_atomic_store(meet, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __syncthreads();
+            partner = sums;
+            partners = pc.parts - 1;
+        }
+    }
 
     if (MODE == 1) {
         // un-fused: the int32 partial product of this exponent group goes, shifted, into the int64
@@ -528,13 +629,31 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     for (int half = 0; half < 2; ++half) {
         __syncthreads();
 #pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
+        for (int ii = 0; ii < 2; ++ii) {
+            // 64 sums of a partner at a time: the loads have to be many to be fast, 256 KiB a partner
+            v4i other[16];
+            if (SPLIT && partner) {
+#pragma unroll
+                for (int t = 0; t < 16; ++t) other[t] = v4i{0, 0, 0, 0};
+                const int32_t *q = partner + (half * 2 + ii) * 4 * 16 * kGemmThreads;
+#pragma unroll 1
+                for (int w = 0; w < partners; ++w, q += BM * BN) {
+                    v4i x[16];
+#pragma unroll
+                    for (int t = 0; t < 16; ++t) x[t] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(q + t * 4 * kGemmThreads));
+#pragma unroll
+                    for (int t = 0; t < 16; ++t) other[t] += x[t];
+                }
+            }
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    foldbuf[(wm * kChunk + ii * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3)) * FLD + wn * 128 + jj * 32 + lrow] =
-                        (int32_t)acc[half * 2 + ii][jj][r];
+                for (int r = 0; r < 16; ++r) {
+                    int32_t v = (int32_t)acc[half * 2 + ii][jj][r];
+                    if (SPLIT && partner) v = (v << rest) + other[jj * 4 + (r >> 2)][r & 3];
+                    foldbuf[(wm * kChunk + ii * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3)) * FLD + wn * 128 + jj * 32 + lrow] = v;
+                }
+        }
         __syncthreads();
 #pragma unroll 1
         for (int reg = 0; reg < 2; ++reg) {
@@ -711,6 +830,12 @@ template <bool FP6>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_batch_kernel(const GemmArgs g) {
     extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
     gemm_body<0, FP6, true>(g, smem);
+}
+
+template <bool FP6>
+__global__ __launch_bounds__(kGemmThreads, 1) void gemm_split_kernel(const GemmArgs g) {
+    extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
+    gemm_body<0, FP6, false, true>(g, smem);
 }
 
 template <int MODE>
@@ -993,6 +1118,10 @@ __global__ __launch_bounds__(256) void recombine_kernel(const int64_t *__restric
     }
 }
 
+__global__ void clear_words_kernel(int32_t *p, int count) {
+    for (int i = threadIdx.x; i < count; i += blockDim.x) p[i] = 0;
+}
+
 // Register-resident back-to-back int8 MFMAs (no memory traffic): what the matrix cores sustain on
 // this chip, for the measured-peak line of the benchmark.  Eight independent accumulators per wave.
 __global__ __launch_bounds__(256) void mfma_peak_kernel(int iters, int *sink) {
@@ -1037,6 +1166,8 @@ static int gemm_lds_opt_in() {
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_f6_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_batch_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_batch_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         constexpr int kSmallLds = kSmallMeta + kSmallWaves * small_stage_bytes(false);
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
@@ -1099,15 +1230,27 @@ static void fused_args(GemmArgs &g, const Plan *p) {
     g.fold_f64 = 31 + p->sh * ((h.lmaxA - 1) + (h.lmaxB - 1)) <= 52;
 }
 
+// Into how many parts the tiles of the last round are cut (1: not at all): where at most half of the CUs would work on it and
+// the contraction is long enough.  Cut in four, the round is not four times as fast (CUs that share L2 and power walk
+// slower, and 256 KiB of sums change hands per part): 4096 x 8448 by 8448 rows, 66 k-tiles: 402 -> 381 us; 17408 rows,
+// 96 k-tiles of six-bit digits: 518 -> 493; 2048 x 15104 by 2048, 118 k-tiles: 140 -> 81; 3072 x 6144 by 6400, 48: 138 -> 125;
+// but 32 k-tiles: 430 -> 434, 19: 37 -> 42.  In eight parts none was faster than in four.
+static int split_parts(int64_t tiles, int64_t ktiles) {
+    const int64_t m = (tiles + 7) / 8 % kXcdCus;
+    if (m == 0 || m > kXcdCus / 2 || ktiles < 48) return 1;
+    return (int)std::min<int64_t>(kXcdCus / m, 4);
+}
+
 // Whether 64 x 64 tiles are the better ones for `tiles` tiles of 256 x 256, of which `pairs` chunk pairs hold anything, with
 // `ktiles` k-tiles each, from what either kernel measured (nanoseconds): a 256 x 256 tile takes 12 us and 1.2 us per k-tile, 256
-// of them at a time; the small tiles take 0.2 us and 10 ns per k-tile for each sixteen of them, and no less than 0.3 us per
-// k-tile.  (1024 x 6528 by 2304 rows, 36 tiles: 70 and 38 us; 2048 x 1920 by 4352, 136 tiles: 34 and 51;
-// 2048 x 1152 by 2048, 64 tiles: 32 and 24; 2048 x 15104 by 2048: 142 and 101.)
+// of them at a time (one round of tiles in parts: 20 us and 0.52 us per k-tile); the small tiles take 0.2 us and 10 ns per
+// k-tile for each sixteen of them, and no less than 0.3 us per k-tile.  (1024 x 6528 by 2304 rows, 36 tiles: 70 (52 in parts) and
+// 38 us; 2048 x 1920 by 4352, 136 tiles: 34 and 51; 2048 x 1152 by 2048, 64 tiles: 32 and 24; 2048 x 15104 by 2048: 142 (81) and 97.)
 static bool small_tiles(const Plan *p, int64_t tiles, int64_t pairs, int64_t ktiles) {
     if (p->chunkB != kChunk) return false;
     const int64_t small = 6000 + std::max(300 * ktiles, pairs * (200 + 10 * ktiles) / kChunkPairs);
-    const int64_t large = (tiles + 255) / 256 * (12000 + 1200 * ktiles);
+    const bool parts = p->nitems == 1 && tiles <= 256 && split_parts(tiles, ktiles) > 1;
+    const int64_t large = parts ? 20000 + 520 * ktiles : (tiles + 255) / 256 * (12000 + 1200 * ktiles);
     return small < large;
 }
 // The chunk pairs of an unpacked product that hold source rows.
@@ -1129,10 +1272,47 @@ static int launch_small(const Plan *p, GemmArgs g, int chunks, int ktiles, bool 
     return launch_status();
 }
 
+// What the parts of a tile meet in (64 MiB): made when the plan's first product that is cut is multiplied, freed with the plan.
+// Two launches that share it must not overlap.  Returns whether it can be used on this stream (never under capture).
+static bool prepare_split(Plan *p, hipStream_t st) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    constexpr int kMeets = 8 * kXcdCus;
+    if (!p->split_ws) {
+        if (hipMalloc(&p->split_ws, (size_t)kMeets * (BM * BN + 2) * sizeof(int32_t)) != hipSuccess ||
+            hipEventCreateWithFlags(&p->split_done, hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            if (p->split_ws) (void)hipFree(p->split_ws);
+            p->split_ws = nullptr;
+            return false;
+        }
+        hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(256), 0, st, (int32_t *)p->split_ws, 2 * kMeets);
+    } else if (p->split_stream != st && hipStreamWaitEvent(st, p->split_done, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    p->split_stream = st;
+    return true;
+}
+
 // The fused launch of one product.
-static int launch_fused(const Plan *p, const GemmArgs &g, hipStream_t st) {
+static int launch_fused(Plan *p, GemmArgs &g, hipStream_t st) {
     const int tiles = g.mtiles * g.ntiles;
     if (small_tiles(p, tiles, chunk_pairs(p->hdr), g.kt1)) return launch_small(p, g, tiles * kChunkPairs, g.kt1, false, st);
+    const int parts = split_parts(tiles, g.kt1);
+    if (parts > 1 && prepare_split(p, st)) {
+        g.meet = (int32_t *)p->split_ws;
+        g.sums = g.meet + 2 * 8 * kXcdCus;
+        g.most_parts = parts;
+        const dim3 grid((unsigned)(8 * (((tiles + 7) / 8 + kXcdCus - 1) / kXcdCus * kXcdCus)));
+        if (p->fp6) hipLaunchKernelGGL(gemm_split_kernel<true>, grid, dim3(kGemmThreads), kGemmLds, st, g);
+        else hipLaunchKernelGGL(gemm_split_kernel<false>, grid, dim3(kGemmThreads), kGemmLds, st, g);
+        IMU_HIP(hipEventRecord(p->split_done, st));
+        return launch_status();
+    }
     if (p->fp6) hipLaunchKernelGGL(gemm_f6_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
     else hipLaunchKernelGGL(gemm_i8_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
     return launch_status();

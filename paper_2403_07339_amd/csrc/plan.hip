@@ -2113,6 +2113,10 @@ static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const i
 
 static void destroy_handles(Plan *p) {
     if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
+    if (p->split_ws) {
+        (void)hipFree(p->split_ws);
+        (void)hipEventDestroy(p->split_done);
+    }
 }
 
 template <class T>

@@ -974,3 +974,37 @@ def test_layouts_around_the_sizes_where_they_change(imu, n, d, h, b, sa, sb, kin
     else:
         Aq, Bq = (rand_ints(rng, r, d, s, 0.001, 2) for r in (n, h))
     check_against_oracle(imu, Aq, Bq, b, sa, sb)
+
+
+@pytest.mark.parametrize("n,d,h,b,strategies", [(4600, 4400, 4800, 8, (COL, COL)), (2400, 6200, 2300, 8, (ROW, COL)),
+                                                (1100, 4200, 2300, 4, (ROW, COL)), (700, 8200, 2000, 8, (BOTH, BOTH))])
+def test_gemm_whose_last_round_is_cut_along_the_contraction(imu, n, d, h, b, strategies):
+    """Products whose last round of tiles would leave CUs idle: tiles in two to four parts, exponent groups that end
+    inside a part, launches in a row on two streams.  Rows from every band of tiles against the oracle."""
+    s = 1 << (b - 1)
+    rng = np.random.default_rng(n + d + h)
+    Aq = rng.integers(-(s - 1), s, size=(n, d)).astype(np.int32)
+    Bq = rng.integers(-(s - 1), s, size=(h, d)).astype(np.int32)
+    Aq[:, rng.integers(0, d, 9)] *= s
+    if strategies[0] == ROW:
+        Aq[rng.random(n) < 0.7] *= s
+    if strategies[1] == COL:
+        Bq[:, rng.integers(0, d, d // 40)] *= s
+    rows = np.unique(np.concatenate([np.arange(0, n, 61), np.arange(0, n, 256), [n - 1]]))
+    want = oracle.int_gemm(Aq[rows], Bq)
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    plan = imu.imunpack_plan(Qa, Qb, b, *strategies)
+    if b <= 4:
+        plan.set_digits(imu.DIGITS_FP6)
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    assert plan.fusable()
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream()]
+    outs = [torch.full((n, h), -1, dtype=torch.int64, device="cuda") for _ in range(4)]
+    streams[1].wait_stream(streams[0])
+    for i, C_int in enumerate(outs):
+        with torch.cuda.stream(streams[i % 2]):
+            imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None, fuse=True)
+    torch.cuda.synchronize()
+    for C_int in outs:
+        assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), want)
+        assert torch.equal(C_int, outs[0])
