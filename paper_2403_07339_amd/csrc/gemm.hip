@@ -163,7 +163,7 @@ __device__ __forceinline__ const int8_t *uniform_ptr(const int8_t *p) {
 // BATCH: the items of a batch (blockIdx.y) in one launch; what the plan decides comes from the item's header.  A
 // variant of its own: read through a run-time choice, those values cost the one-product kernel its last
 // registers (101 spilled; 348 -> 460 us on a 4096 x 8228 x 11013 unpacked product).
-template <int MODE, bool FP6, bool BATCH = false, bool SPLIT = false>  // SPLIT: pieces (see piece_of); MODE 0: fused epilogue, 1: int64 segment into C_u
+template <int MODE, bool FP6, bool BATCH = false, bool SPLIT = false>  // SPLIT: parts of tiles (see piece_of); MODE 0: fused epilogue, 1: int64 segment into C_u
 __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     constexpr int kRowB = FP6 ? 96 : BK;           // bytes of a row of the operand per k-tile
     constexpr int kPitch = FP6 ? 112 : BK;         // bytes from row to row in LDS
@@ -1242,7 +1242,7 @@ static int split_parts(int64_t tiles, int64_t ktiles) {
 }
 
 // Whether 64 x 64 tiles are the better ones for `tiles` tiles of 256 x 256, of which `pairs` chunk pairs hold anything, with
-// `ktiles` k-tiles each, from what either kernel measured (nanoseconds): a 256 x 256 tile takes 12 us and 1.2 us per k-tile, 256
+// `ktiles` k-tiles each, from what either kernel measured (nanoseconds): a 256 x 256 tile takes 16 us and 1.15 us per k-tile, 256
 // of them at a time (one round of tiles in parts: 20 us and 0.52 us per k-tile); the small tiles take 0.2 us and 10 ns per
 // k-tile for each sixteen of them, and no less than 0.3 us per k-tile.  (1024 x 6528 by 2304 rows, 36 tiles: 70 (52 in parts) and
 // 38 us; 2048 x 1920 by 4352, 136 tiles: 34 and 51; 2048 x 1152 by 2048, 64 tiles: 32 and 24; 2048 x 15104 by 2048: 142 (81) and 97.)
@@ -1250,7 +1250,7 @@ static bool small_tiles(const Plan *p, int64_t tiles, int64_t pairs, int64_t kti
     if (p->chunkB != kChunk) return false;
     const int64_t small = 6000 + std::max(300 * ktiles, pairs * (200 + 10 * ktiles) / kChunkPairs);
     const bool parts = p->nitems == 1 && tiles <= 256 && split_parts(tiles, ktiles) > 1;
-    const int64_t large = parts ? 20000 + 520 * ktiles : (tiles + 255) / 256 * (12000 + 1200 * ktiles);
+    const int64_t large = parts ? 20000 + 520 * ktiles : (tiles + 255) / 256 * (16000 + 1150 * ktiles);
     return small < large;
 }
 // The chunk pairs of an unpacked product that hold source rows.
