@@ -35,12 +35,21 @@ static inline int launch_status() {
     return IMUNPACK_OK;
 }
 
+// Whether what is queued on the stream goes into a graph (or cannot be queued, because another stream's capture forbids it).
+static inline bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // ---- geometry shared by planner, scatter and GEMM ----------------------------------------------
 constexpr int kTile = 256;       // GEMM output tile edge in unpacked rows (both operands)
 constexpr int kChunk = 64;       // physical rows the GEMM epilogue holds at a time; no source row straddles a chunk
 constexpr int kKPad = 128;       // every exponent group is padded to a multiple of this many columns
 constexpr int kMaxGroups = 64;   // distinct diagonal entries of S the planner supports
 constexpr int kMaxItems = 1024;  // products of a batch that are planned together
+constexpr int kBoundBlocks = 256;  // workgroups that measure the accumulator bounds, at most
 constexpr int kMaxRuns = 128;    // stretches of consecutive k-tiles that read consecutive blocks of the A store
 constexpr int kProwLevel = 24;   // dimensions are at most 2^24, digit levels fewer than 64
 constexpr uint32_t kNever = 0xFFFFFFFFu;  // split time of a row/column that is never split
@@ -218,10 +227,10 @@ __device__ __forceinline__ int half_wave_max_nonneg_last(int v) {
 // the L2 of the XCD, with megabytes of operands in it.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // An accumulator bound for the host (saturated: beyond 2^44 no path asks how far).  The word carries the low bits of the
-// sequence number, so that neither bound's store has to wait for the other.
-__device__ __forceinline__ void tell_bound(PlanHeader *host, int i, unsigned long long bound, int32_t seq) {
+// sequence number, so that no store has to wait for another.
+__device__ __forceinline__ void tell_bound(unsigned long long *word, unsigned long long bound, int32_t seq) {
     const unsigned long long v = bound < (1ull << 44) ? bound : (1ull << 44);
-    __hip_atomic_store(&host->bound[i], v | ((unsigned long long)(unsigned)seq << 48), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(word, v | ((unsigned long long)(unsigned)seq << 48), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 // 6-bit floating-point digits in memory.  The matrix instruction takes, per lane, 32 consecutive columns of a
 // row as one 192-bit string (column j of the fragment at bits 6j .. 6j+5).  A row stores its columns in
@@ -265,10 +274,11 @@ struct imunpack_plan {
     hipEvent_t split_done;        // recorded behind the launch that used it last ...
     hipStream_t split_stream;     // ... on this stream
     int chunkB;                   // no source row of B straddles that many physical rows: kTile, or kChunk for small products
-    int32_t seq;                  // of the last header or bounds that the host asked for (the kernel writes it behind them)
-    hipStream_t bound_stream;     // the stream of the last imunpack_unpack
-    int bound_pending;            // the bounds of the last imunpack_unpack have not been read back yet ...
-    int bound_told;               // ... but a kernel that hands them to the host is queued
+    int32_t seq;                  // of the last header or bounds that the host asked for (the kernel writes it with them)
+    unsigned long long *pin_bounds;  // pinned, behind the headers: two words per workgroup that measured the bounds
+    int bound_pending;            // the bounds of the last imunpack_unpack have not been read back yet
+    int32_t bound_seq;            // ... and carry this number
+    int bound_words;              // ... in that many pinned words (0: the unpack was captured into a graph, none are written)
     int guess_fusable;            // whether the fused GEMM was exact for this plan object the last time
     imu::SlotSet rowA, rowB, c1, c2;
     imu::RowLayout layA, layB;
@@ -337,8 +347,6 @@ int gemm_batch(imunpack_plan_t *p, const int8_t *A_ue, int64_t a_stride, const i
 // The RTN steps of both operands of every item of a batch (percentile.hip); ws: two workspaces side by side.
 int rtn_step_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float beta_A, const float *B, int64_t h, int64_t sb_r,
                   int64_t sb_c, float beta_B, int64_t d, double p, float *steps, void *ws, const QuantBatch &bt, hipStream_t st);
-// The sequence number under which a kernel that is about to be queued hands the bounds over (tell_bound).
-int32_t ask_bounds(Plan *p);
 // Waits for the bounds of the last imunpack_unpack and sets p->fusable.
 int resolve_bound(Plan *p);
 // Bytes from one physical row to the next of the A store (op 0) / of B_eu (op 1) in the digit format in

@@ -63,8 +63,6 @@ struct GemmArgs {
     // and writes nothing if the shifted group sum could leave int32
     const unsigned long long *guard;
     int guard_mul;            // s - 1
-    PlanHeader *host;         // ... and the first workgroup hands the bounds to the host, which waits for them
-    int32_t host_seq;
     int fold_f64;             // no int64 output wanted and every sum over digit levels is exact in binary64
     // batch (blockIdx.y is the item): everything above that the plan decides comes from the item's header;
     // an item that may not be fused writes nothing and sets refused[item]
@@ -184,7 +182,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         const unsigned long long *guard = BATCH ? hdr->bound : g.guard;
         const unsigned long long b0 = guard[0], b1 = guard[1];
         const unsigned long long m = b0 < b1 ? b0 : b1;
-        if (!BATCH && g.host && blockIdx.x == 0 && tid < 2) tell_bound(g.host, tid, tid ? b1 : b0, g.host_seq);
         if (!(m < (1ull << 40) && m * (unsigned long long)g.guard_mul < (1ull << (FP6 ? 24 : 31))) || (BATCH && nbound >= 63)) {
             if (g.refused && blockIdx.x == 0 && tid == 0) g.refused[blockIdx.y] = 1;
             return;
@@ -892,7 +889,6 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
         const unsigned long long *guard = BATCH ? hdr->bound : g.guard;
         const unsigned long long b0 = guard[0], b1 = guard[1];
         const unsigned long long m = b0 < b1 ? b0 : b1;
-        if (!BATCH && g.host && blockIdx.x == 0 && tid < 2) tell_bound(g.host, tid, tid ? b1 : b0, g.host_seq);
         if (!(m < (1ull << 40) && m * (unsigned long long)g.guard_mul < (1ull << (FP6 ? 24 : 31))) || (BATCH && nbound >= 63)) {
             if (g.refused && blockIdx.x == 0 && tid == 0) g.refused[blockIdx.y] = 1;
             return;
@@ -1275,11 +1271,7 @@ static int launch_small(const Plan *p, GemmArgs g, int chunks, int ktiles, bool 
 // What the parts of a tile meet in (64 MiB): made when the plan's first product that is cut is multiplied, freed with the plan.
 // Two launches that share it must not overlap.  Returns whether it can be used on this stream (never under capture).
 static bool prepare_split(Plan *p, hipStream_t st) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return false;
-    }
+    if (capturing(st)) return false;
     constexpr int kMeets = 8 * kXcdCus;
     if (!p->split_ws) {
         if (hipMalloc(&p->split_ws, (size_t)kMeets * (BM * BN + 2) * sizeof(int32_t)) != hipSuccess ||
@@ -1357,10 +1349,6 @@ int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *
         if ((!C_int && !C_fp) || ldc < p->h) return IMUNPACK_EINVAL;
         fused_args(g, p);
         g.guard = speculate ? p->d_hdr->bound : nullptr;
-        if (speculate) {
-            g.host = p->pin_hdr;
-            g.host_seq = ask_bounds(p);
-        }
         g.C_int = C_int; g.C_fp = C_fp; g.ldc = ldc;
         g.scale = (double)scale_A * (double)scale_B;
         g.scale_a_dev = scale_a_dev; g.scale_b_dev = scale_b_dev;
@@ -1372,7 +1360,6 @@ int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *
         if (p->fusable) return IMUNPACK_OK;
         if (!workspace) return IMUNPACK_ERANGE;  // the guarded launch wrote nothing
         g.guard = nullptr;
-        g.host = nullptr;
     }
     if (!workspace) return IMUNPACK_EINVAL;
     g.C_u = (int64_t *)workspace;

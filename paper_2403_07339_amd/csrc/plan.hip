@@ -2138,7 +2138,6 @@ int wait_word(const T *word, T want, hipStream_t st) {
 }
 
 template int wait_word<int32_t>(const int32_t *, int32_t, hipStream_t);
-template int wait_word<uint16_t>(const uint16_t *, uint16_t, hipStream_t);
 
 // The headers that the last launch hands over.
 static int await_headers(Plan *p, hipStream_t st) {
@@ -2289,7 +2288,6 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         memset(p, 0, sizeof(*p));
         p->guess_fusable = 1;
     }
-    if (p->bound_pending && p->bound_told) (void)resolve_bound(p);  // bounds on their way into the header mirror
     p->bound_pending = 0;
     const bool same = p->valid && p->nitems == nitems && p->n == n && p->d == d && p->h == h && p->b == b && p->sA == strategy_A &&
                       p->sB == strategy_B;
@@ -2319,12 +2317,14 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
         p->pin_hdr = nullptr;
         p->pin_items = 0;
-        if (hipHostMalloc((void **)&p->pin_hdr, (size_t)nitems * sizeof(PlanHeader), hipHostMallocDefault) != hipSuccess) {
+        const size_t bytes = (size_t)nitems * sizeof(PlanHeader) + 2 * kBoundBlocks * sizeof(unsigned long long);
+        if (hipHostMalloc((void **)&p->pin_hdr, bytes, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             p->pin_hdr = nullptr;
             rc = IMUNPACK_ENOMEM;
         } else {
-            memset(p->pin_hdr, 0, (size_t)nitems * sizeof(PlanHeader));
+            memset(p->pin_hdr, 0, bytes);
+            p->pin_bounds = reinterpret_cast<unsigned long long *>(p->pin_hdr + nitems);
             p->pin_items = nitems;
         }
     }
@@ -2623,7 +2623,6 @@ extern "C" int imunpack_plan_export(imunpack_plan_t *p, int32_t *rowA_src, int32
 extern "C" int imunpack_plan_destroy(imunpack_plan_t *p) {
     if (!p) return IMUNPACK_OK;
     int rc = IMUNPACK_OK;
-    if (p->bound_pending && p->bound_told) (void)resolve_bound(p);
     if (p->arena) {
         hipError_t e = hipFree(p->arena);
         if (e != hipSuccess) { g_last_hip_error = (int)e; rc = IMUNPACK_EHIP; }

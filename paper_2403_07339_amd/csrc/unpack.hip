@@ -18,8 +18,10 @@
 #include "common.h"
 
 #include <algorithm>
+#include <chrono>
 #include <cstddef>
 #include <cstring>
+#include <thread>
 
 namespace imu {
 
@@ -432,12 +434,17 @@ __global__ void fixup_kernel(FixupArgs fa, FixupArgs fb, int blocks_a, int block
 }
 
 // The accumulator bounds: the largest row norm of either operand (the scatter kernel's parts per wave
-// plus what the fix-up pass placed).
+// plus what the fix-up pass placed).  One update of the device's words per workgroup, and one pair of words per workgroup
+// for the host.  (A step of 12608 x 768 by 3072: 248 us with the GEMM's first workgroup handing the bounds over, which the host
+// could only wait for on the GEMM's stream; 235 us so.  256 x 256 x 256: 146 and 136.)
 __global__ void bound_kernel(const unsigned long long *rowsum_a, const unsigned long long *wavesum_a, int rows_a,
                              unsigned long long *bound_a, const unsigned long long *rowsum_b,
                              const unsigned long long *wavesum_b, int rows_b, unsigned long long *bound_b, int wpr_a,
                              int wpr_b, const PlanHeader *hdr /* batch: the sizes come from the item's header */,
-                             int64_t stride) {
+                             int64_t stride, unsigned long long *host /* nullptr: stay on the device */, int32_t seq) {
+    __shared__ unsigned long long s_bound[2];
+    if (threadIdx.x < 2) s_bound[threadIdx.x] = 0;
+    __syncthreads();
     unsigned long long ma = 0, mb = 0;
     if (hdr) {
         hdr += blockIdx.y;
@@ -456,15 +463,18 @@ __global__ void bound_kernel(const unsigned long long *rowsum_a, const unsigned 
         ma = max(ma, (unsigned long long)__shfl_xor((long long)ma, off, 64));
         mb = max(mb, (unsigned long long)__shfl_xor((long long)mb, off, 64));
     }
-    if ((threadIdx.x & 63) == 0) {  // the bound only grows: a plain (possibly stale) read filters most of the updates
-        if (ma > __hip_atomic_load(bound_a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(bound_a, ma);
-        if (mb > __hip_atomic_load(bound_b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(bound_b, mb);
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(&s_bound[0], ma);
+        atomicMax(&s_bound[1], mb);
     }
-}
-
-// The bounds to the host, where no GEMM launch hands them over.
-__global__ void tell_bounds_kernel(const unsigned long long *bound, PlanHeader *host, int32_t seq) {
-    if (threadIdx.x < 2) tell_bound(host, threadIdx.x, bound[threadIdx.x], seq);
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const unsigned long long m = s_bound[threadIdx.x];
+        unsigned long long *bound = threadIdx.x ? bound_b : bound_a;
+        // the bound only grows: a plain (possibly stale) read filters most of the updates
+        if (m > __hip_atomic_load(bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(bound, m);
+        if (host) tell_bound(host + 2 * blockIdx.x + threadIdx.x, m, seq);
+    }
 }
 
 // A repeated unpack of one plan: clears what the planner left cleared for the first.
@@ -547,7 +557,8 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     const PlanHeader &h = p->hdr;
     const bool batch = p->nitems > 1;
     const unsigned nitems = (unsigned)p->nitems;
-    if (p->bound_pending && p->bound_told) IMU_TRY(resolve_bound(p));  // of an earlier unpack of this plan
+    p->bound_pending = 0;
+    p->fusable = 0;  // until the bounds say otherwise
     // the planner leaves the bounds and the row norms cleared; a repeated unpack of the same plan clears them again
     if (p->unpacked) {
         if (batch) return IMUNPACK_EINVAL;
@@ -633,19 +644,23 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
             hipLaunchKernelGGL(fixup_kernel, dim3(fblocks[0] + fblocks[1], nitems), dim3(256), 0, st, fx[0], fx[1], fblocks[0],
                                fblocks[1]);
         }
-        const int nscan = std::min(256, (most_rows + 255) / 256);
+        const int nscan = std::min(kBoundBlocks, (most_rows + 255) / 256);
+        // a workgroup hands what it found to the host itself, in words of its own: the host needs no stream (the caller may use
+        // another for the GEMM, or destroy this one) and no event to learn the bounds, and no workgroup waits for another.  Not
+        // from a graph, whose replays nobody waits for.
+        p->bound_words = a_stride || capturing(st) ? 0 : 2 * nscan;
+        p->bound_seq = ++p->seq;
+        for (int i = 0; i < p->bound_words; ++i)  // not there yet
+            __atomic_store_n(&p->pin_bounds[i], (unsigned long long)(uint16_t)~p->bound_seq << 48, __ATOMIC_RELEASE);
         hipLaunchKernelGGL(bound_kernel, dim3(nscan, nitems), dim3(256), 0, st, p->layA.rowsum, p->layA.wavesum, h.Mp,
                            &p->d_hdr->bound[0], p->layB.rowsum, p->layB.wavesum, h.Np, &p->d_hdr->bound[1],
-                           sc[0].nwin, sc[1].nwin, batch ? p->d_hdr : nullptr, p->item_bytes);
+                           sc[0].nwin, sc[1].nwin, batch ? p->d_hdr : nullptr, p->item_bytes,
+                           p->bound_words ? p->pin_bounds : nullptr, p->bound_seq);
     }
     IMU_TRY(launch_status());
     p->unpacked = 1;
     if (a_stride) return IMUNPACK_OK;
-    // The bounds stay on the device until somebody asks: imunpack_gemm launches the fused kernel at once, guarded, and it is
-    // that kernel which hands them over.
-    p->bound_stream = st;
     p->bound_pending = 1;
-    p->bound_told = 0;
     p->kept_Beu = p->keep_B ? B_eu : nullptr;
     p->kept_Beu_fp6 = p->fp6;
     return IMUNPACK_OK;
@@ -657,26 +672,31 @@ extern "C" int imunpack_unpack(imunpack_plan_t *p, const int32_t *A, int64_t lda
 }
 
 namespace imu {
-int32_t ask_bounds(Plan *p) {
-    ++p->seq;
-    p->bound_told = 1;
-    p->pin_hdr->bound[0] = p->pin_hdr->bound[1] = (unsigned long long)(uint16_t)~p->seq << 48;  // not there yet
-    return p->seq;
-}
-
 int resolve_bound(Plan *p) {
     if (!p->bound_pending) return IMUNPACK_OK;
+    unsigned long long bound[2] = {0, 0};
+    if (p->bound_words == 0) {  // a captured unpack: nobody knows on which stream its graph ran
+        IMU_HIP(hipDeviceSynchronize());
+        IMU_HIP(hipMemcpy(bound, p->d_hdr->bound, sizeof(bound), hipMemcpyDeviceToHost));
+    }
+    long spin = 0;
+    for (int i = 0; i < p->bound_words; ++i) {  // the upper sixteen bits name the unpack
+        unsigned long long w;
+        while ((w = __atomic_load_n(&p->pin_bounds[i], __ATOMIC_ACQUIRE)) >> 48 != (uint16_t)p->bound_seq) {
+            if (++spin < (1 << 24)) continue;
+            // queued behind a lot of other work; if some ten seconds do not bring it, look whether it comes at all
+            if (spin < (1 << 24) + 150000) {
+                std::this_thread::sleep_for(std::chrono::microseconds(20));
+                continue;
+            }
+            IMU_HIP(hipDeviceSynchronize());
+            if (__atomic_load_n(&p->pin_bounds[i], __ATOMIC_ACQUIRE) >> 48 != (uint16_t)p->bound_seq) return IMUNPACK_EHIP;
+        }
+        bound[i & 1] = std::max(bound[i & 1], w & ((1ull << 48) - 1));
+    }
+    p->hdr.bound[0] = bound[0];
+    p->hdr.bound[1] = bound[1];
     p->bound_pending = 0;
-    if (!p->bound_told) {
-        const int32_t seq = ask_bounds(p);
-        hipLaunchKernelGGL(tell_bounds_kernel, dim3(1), dim3(64), 0, p->bound_stream, (const unsigned long long *)p->d_hdr->bound, p->pin_hdr, seq);
-        IMU_TRY(launch_status());
-    }
-    for (int i = 0; i < 2; ++i) {  // the upper sixteen bits name the unpack
-        const uint16_t *tag = reinterpret_cast<const uint16_t *>(&p->pin_hdr->bound[i]) + 3;
-        IMU_TRY(wait_word(tag, (uint16_t)p->seq, p->bound_stream));
-        p->hdr.bound[i] = p->pin_hdr->bound[i] & ((1ull << 48) - 1);
-    }
     // |sum_c s^e(c) a_c b_c| <= (s - 1) * min(bound_A, bound_B): the shifted sum of all groups
     // fits int32 iff that is below 2^31.
     const unsigned long long m = p->hdr.bound[0] < p->hdr.bound[1] ? p->hdr.bound[0] : p->hdr.bound[1];

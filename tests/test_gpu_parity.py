@@ -1008,3 +1008,90 @@ def test_gemm_whose_last_round_is_cut_along_the_contraction(imu, n, d, h, b, str
     for C_int in outs:
         assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), want)
         assert torch.equal(C_int, outs[0])
+
+
+def _long_work(ms=20):
+    """Queues some milliseconds of library work on the current stream."""
+    x = torch.ones((4096, 4096), device="cuda")
+    for _ in range(ms):
+        x = torch.mm(x, x)
+
+
+def _deep_in_both(rng, n, d, h, s, deep):
+    """Integers for UnpackColumn on both sides; `deep`: a column of four-digit entries in both operands, whose shifted
+    sum leaves int32."""
+    Aq, Bq = (rng.integers(-(s - 1), s, size=(r, d)).astype(np.int32) for r in (n, h))
+    if deep:
+        Aq[:, 7] = Bq[:, 7] = (s - 1) * s ** 3
+    return Aq, Bq
+
+
+def test_gemm_on_another_stream_than_the_unpack(imu):
+    """Plan and unpack on one stream, other work and then the GEMM on a second one that waits for an event of the
+    first, nothing asked in between: the accumulator bounds arrive whatever the second stream is busy with.  First
+    operands that the fused launch takes, then (on the same plan object, which expects the same again) operands that it
+    must refuse: without a workspace on every try, with one exactly."""
+    b, s = 8, 128
+    n, d, h = 300, 520, 260
+    rng = np.random.default_rng(5)
+    first, second = torch.cuda.Stream(), torch.cuda.Stream()
+    plan = imu.Plan()
+    for deep in (False, True, False):
+        Aq, Bq = _deep_in_both(rng, n, d, h, s, deep)
+        want = oracle.int_gemm(Aq, Bq)
+        Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+        C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(first):
+            imu.imunpack_plan(Qa, Qb, b, COL, COL, plan=plan)
+            A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+            unpacked = torch.cuda.Event()
+            unpacked.record()
+        with torch.cuda.stream(second):
+            second.wait_event(unpacked)
+            _long_work()
+            if deep:
+                for _ in range(2):
+                    with pytest.raises(imu.ImunpackError) as e:
+                        imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None, fuse=True)
+                    assert e.value.code == imu.ERANGE
+                second.synchronize()
+                assert int((C_int != -1).sum().item()) == 0
+                assert not plan.fusable() and min(plan.bounds()) * (s - 1) >= 2 ** 31
+            ws = torch.empty(plan.unpacked_bytes()[2] // 8, dtype=torch.int64, device="cuda") if deep else None
+            imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, ws, fuse=True)
+        second.synchronize()
+        assert np.array_equal(C_int.cpu().numpy(), want)
+        assert plan.fusable() == (not deep)
+
+
+def test_bounds_do_not_need_the_stream_of_the_unpack(imu):
+    """The bounds of an unpack on a stream that the caller has destroyed since, and of an unpack that ran in a graph."""
+    import ctypes
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    rng = np.random.default_rng(6)
+    Aq, Bq = (rand_ints(rng, r, 400, 128, 0.003, 2) for r in (130, 200))
+    want = oracle.int_gemm(Aq, Bq)
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    plan = imu.imunpack_plan(Qa, Qb, 8, BOTH, BOTH)
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    bounds = plan.bounds()
+    torch.cuda.synchronize()
+    handle = ctypes.c_void_p()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(handle), 1) == 0
+    with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
+        imu.imunpack_unpack(plan, Qa, Qb, A_ue, B_eu)
+    assert hip.hipStreamSynchronize(handle) == 0 and hip.hipStreamDestroy(handle) == 0
+    assert plan.bounds() == bounds
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        imu.imunpack_unpack(plan, Qa, Qb, A_ue, B_eu)
+    for _ in range(3):
+        A_ue.zero_()
+        graph.replay()
+        C_int = torch.full(want.shape, -1, dtype=torch.int64, device="cuda")
+        torch.cuda.synchronize()
+        assert plan.bounds() == bounds
+        imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None, fuse=True)
+        assert np.array_equal(C_int.cpu().numpy(), want)
