@@ -277,7 +277,10 @@ int imunpack_unpack_canonical(imunpack_plan_t *plan, const int8_t *A_ue, const i
  *   C_int (n x h int64, device, may be NULL) and/or C_fp (n x h fp32, device, may be NULL) are
  *   written directly.  This needs the shifted sum of all groups to fit int32 for this plan's
  *   operands (bound measured by imunpack_unpack); if it does not, the call falls back to the
- *   un-fused path when workspace != NULL and returns ERANGE otherwise.
+ *   un-fused path when workspace != NULL and returns ERANGE otherwise.  Products whose tiles are cut along the
+ *   contraction meet in a buffer of 64 MiB that the first of them allocates (without it, and under stream
+ *   capture, the tiles stay whole) and that stays with the plan object; calls that share it are ordered,
+ *   whatever streams they are on.
  * fuse == 0: writes the unpacked product C_u = A_ue S_uu B_eu^T as int64 into workspace
  *   (imunpack_unpacked_bytes) for imunpack_recombine; C_int / C_fp are ignored.
  * ldc: row stride of C_int and C_fp in elements (>= h).  scale_A, scale_B: the RTN steps. */
@@ -345,6 +348,11 @@ int imunpack_diag_mfma_peak(int workgroups, int iters, int64_t *ops, imunpack_st
  * from src to dst (device, 16-byte aligned, not overlapping) in the access pattern of the quantize pass,
  * with non-temporal loads and stores.  The caller times the stream; the traffic is 2 * bytes. */
 int imunpack_diag_copy(const void *src, void *dst, int64_t bytes, imunpack_stream_t stream);
+
+/* How the plan's last fused imunpack_gemm was launched (tests and benchmark reporting only): 0 = in tiles of
+ * 64 x 64 unpacked rows, 1 = of 256 x 256, 2 to 4 = of 256 x 256, those of the last round cut into that many parts
+ * along the contraction.  Errors: EINVAL (null plan). */
+int imunpack_diag_gemm_parts(const imunpack_plan_t *plan);
 
 /* Shader clock under the GEMM's own load (benchmark reporting only).  While `ticks` (device, two
  * elements, owned by the caller) is set, every fused imunpack_gemm launch of this process has its

@@ -29,7 +29,7 @@ EXPORTS = [
     "imunpack_plan_fusable", "imunpack_plan_bounds", "imunpack_diag_mfma_peak", "imunpack_diag_clock_probe", "imunpack_diag_copy", "imunpack_price",
     "imunpack_percentile", "imunpack_percentile_static", "imunpack_plan_layout", "imunpack_rtn_step",
     "imunpack_gemm_batched", "imunpack_batch_destroy", "imunpack_quantize_pair", "imunpack_plan_set_digits",
-    "imunpack_plan_digits", "imunpack_plan_keep_weights", "imunpack_plan_weights_reused",
+    "imunpack_plan_digits", "imunpack_plan_keep_weights", "imunpack_plan_weights_reused", "imunpack_diag_gemm_parts",
 ]
 DIGITS_INT8, DIGITS_FP6 = 0, 1
 
@@ -58,6 +58,7 @@ _lib.imunpack_plan_layout.argtypes = [_vp, C.POINTER(_i64)]
 _lib.imunpack_plan_set_digits.argtypes = [_vp, _i32]
 _lib.imunpack_plan_digits.argtypes = [_vp]
 _lib.imunpack_plan_keep_weights.argtypes = [_vp, _i32]
+_lib.imunpack_diag_gemm_parts.argtypes = [_vp]
 _lib.imunpack_plan_weights_reused.argtypes = [_vp]
 _lib.imunpack_unpack.argtypes = [_vp, _vp, _i64, _vp, _i64, _vp, _vp, _vp]
 _lib.imunpack_unpack_canonical.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp]
@@ -302,6 +303,12 @@ class Plan:
         out = (C.c_uint64 * 2)()
         _check(_lib.imunpack_plan_bounds(self._h, out), "imunpack_plan_bounds")
         return int(out[0]), int(out[1])
+
+
+def imunpack_diag_gemm_parts(plan: Plan) -> int:
+    """How the plan's last fused GEMM was launched: 0 in small tiles, 1 in whole large ones, 2 to 4 those of the last
+    round cut into that many parts."""
+    return int(_lib.imunpack_diag_gemm_parts(plan.handle))
 
 
 def imunpack_plan(A: torch.Tensor, B: torch.Tensor, b: int, strategy_a: int, strategy_b: int,

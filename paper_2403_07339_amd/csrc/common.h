@@ -271,8 +271,8 @@ struct imunpack_plan {
     int64_t item_bytes;           // from the arrays of one item in the arena to those of the next
     int64_t op_stride;            // from item to item: the integer operands, their statistics and OB lists
     void *split_ws;               // where the parts of a GEMM tile meet (gemm.hip), if a product needed it
-    hipEvent_t split_done;        // recorded behind the launch that used it last ...
-    hipStream_t split_stream;     // ... on this stream
+    hipEvent_t split_done;        // recorded behind the launch that used it last
+    int gemm_parts;               // parts of a tile in the last fused launch (0: 64 x 64 tiles; imunpack_diag_gemm_parts)
     int chunkB;                   // no source row of B straddles that many physical rows: kTile, or kChunk for small products
     int32_t seq;                  // of the last header or bounds that the host asked for (the kernel writes it with them)
     unsigned long long *pin_bounds;  // pinned, behind the headers: two words per workgroup that measured the bounds

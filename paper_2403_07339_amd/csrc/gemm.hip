@@ -1282,29 +1282,33 @@ static bool prepare_split(Plan *p, hipStream_t st) {
             return false;
         }
         hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(256), 0, st, (int32_t *)p->split_ws, 2 * kMeets);
-    } else if (p->split_stream != st && hipStreamWaitEvent(st, p->split_done, 0) != hipSuccess) {
+    } else {  // (not by comparing stream handles: one handle may stand for a stream per thread, or be used again)
+        hipError_t e = hipEventQuery(p->split_done);
+        if (e == hipErrorNotReady) e = hipStreamWaitEvent(st, p->split_done, 0);
         (void)hipGetLastError();
-        return false;
+        if (e != hipSuccess) return false;
     }
-    p->split_stream = st;
     return true;
 }
 
 // The fused launch of one product.
 static int launch_fused(Plan *p, GemmArgs &g, hipStream_t st) {
     const int tiles = g.mtiles * g.ntiles;
+    p->gemm_parts = 0;
     if (small_tiles(p, tiles, chunk_pairs(p->hdr), g.kt1)) return launch_small(p, g, tiles * kChunkPairs, g.kt1, false, st);
     const int parts = split_parts(tiles, g.kt1);
     if (parts > 1 && prepare_split(p, st)) {
         g.meet = (int32_t *)p->split_ws;
         g.sums = g.meet + 2 * 8 * kXcdCus;
         g.most_parts = parts;
+        p->gemm_parts = parts;
         const dim3 grid((unsigned)(8 * (((tiles + 7) / 8 + kXcdCus - 1) / kXcdCus * kXcdCus)));
         if (p->fp6) hipLaunchKernelGGL(gemm_split_kernel<true>, grid, dim3(kGemmThreads), kGemmLds, st, g);
         else hipLaunchKernelGGL(gemm_split_kernel<false>, grid, dim3(kGemmThreads), kGemmLds, st, g);
         IMU_HIP(hipEventRecord(p->split_done, st));
         return launch_status();
     }
+    p->gemm_parts = 1;
     if (p->fp6) hipLaunchKernelGGL(gemm_f6_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
     else hipLaunchKernelGGL(gemm_i8_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
     return launch_status();
@@ -1426,6 +1430,8 @@ extern "C" int imunpack_gemm(imunpack_plan_t *p, const int8_t *A_ue, const int8_
                              float scale_B, int fuse, imunpack_stream_t stream) {
     return gemm_impl(p, A_ue, B_eu, workspace, C_int, C_fp, ldc, scale_A, scale_B, nullptr, nullptr, fuse, (hipStream_t)stream);
 }
+
+extern "C" int imunpack_diag_gemm_parts(const imunpack_plan_t *p) { return p ? p->gemm_parts : IMUNPACK_EINVAL; }
 
 extern "C" int imunpack_diag_clock_probe(uint64_t *ticks) {
     g_clock_probe.store(reinterpret_cast<unsigned long long *>(ticks), std::memory_order_relaxed);

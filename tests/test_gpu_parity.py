@@ -976,21 +976,39 @@ def test_layouts_around_the_sizes_where_they_change(imu, n, d, h, b, sa, sb, kin
     check_against_oracle(imu, Aq, Bq, b, sa, sb)
 
 
-@pytest.mark.parametrize("n,d,h,b,strategies", [(4600, 4400, 4800, 8, (COL, COL)), (2400, 6200, 2300, 8, (ROW, COL)),
-                                                (1100, 4200, 2300, 4, (ROW, COL)), (700, 8200, 2000, 8, (BOTH, BOTH))])
-def test_gemm_whose_last_round_is_cut_along_the_contraction(imu, n, d, h, b, strategies):
-    """Products whose last round of tiles would leave CUs idle: tiles in two to four parts, exponent groups that end
-    inside a part, launches in a row on two streams.  Rows from every band of tiles against the oracle."""
+def _product_in_parts(n, d, h, b, strategies, every):
+    """Operands of a product with a long contraction: `every` splits each column of A (two exponent groups of the same
+    width), else a few columns and, under UnpackRow, most rows."""
     s = 1 << (b - 1)
     rng = np.random.default_rng(n + d + h)
     Aq = rng.integers(-(s - 1), s, size=(n, d)).astype(np.int32)
     Bq = rng.integers(-(s - 1), s, size=(h, d)).astype(np.int32)
-    Aq[:, rng.integers(0, d, 9)] *= s
-    if strategies[0] == ROW:
-        Aq[rng.random(n) < 0.7] *= s
-    if strategies[1] == COL:
-        Bq[:, rng.integers(0, d, d // 40)] *= s
-    rows = np.unique(np.concatenate([np.arange(0, n, 61), np.arange(0, n, 256), [n - 1]]))
+    if every:
+        Aq[n // 2] = s
+    else:
+        Aq[:, rng.integers(0, d, 9)] *= s
+        if strategies[0] == ROW:
+            Aq[rng.random(n) < 0.7] *= s
+        if strategies[1] == COL:
+            Bq[:, rng.integers(0, d, d // 40)] *= s
+    return Aq, Bq
+
+
+@pytest.mark.parametrize("n,d,h,b,strategies,every,parts", [
+    (1000, 6100, 2500, 8, (ROW, COL), False, 2),    # fewer tiles than CUs; groups that end inside a part
+    (2560, 3072, 2560, 8, (COL, COL), True, 2),     # a group that ends where a part does
+    (2200, 3072, 2000, 8, (COL, ROW), True, 3),     # ... and inside a part
+    (2048, 6400, 2048, 4, (COL, COL), False, 4),    # six-bit digits, groups inside parts
+    (2048, 3072, 2048, 4, (COL, COL), True, 4),     # six-bit digits, a group that ends where a part does
+    (4352, 6144, 4352, 8, (BOTH, COL), False, 4),   # a round of whole tiles before
+    (2560, 5900, 2560, 8, (ROW, ROW), False, 1),    # a contraction that is too short for it
+    (300, 8200, 600, 8, (COL, COL), False, 0),      # few tiles
+])
+def test_gemm_whose_last_round_is_cut_along_the_contraction(imu, n, d, h, b, strategies, every, parts):
+    """Products whose last round of tiles would leave CUs idle: tiles in two to four parts, exponent groups that end
+    inside a part and at its end, launches in a row on two streams.  Rows from every band of tiles against the oracle."""
+    Aq, Bq = _product_in_parts(n, d, h, b, strategies, every)
+    rows = np.unique(np.concatenate([np.arange(0, n, 61), np.arange(0, n, 256), [n // 2, n - 1]]))
     want = oracle.int_gemm(Aq[rows], Bq)
     Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
     plan = imu.imunpack_plan(Qa, Qb, b, *strategies)
@@ -1004,7 +1022,49 @@ def test_gemm_whose_last_round_is_cut_along_the_contraction(imu, n, d, h, b, str
     for i, C_int in enumerate(outs):
         with torch.cuda.stream(streams[i % 2]):
             imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None, fuse=True)
+            assert imu.imunpack_diag_gemm_parts(plan) == parts
     torch.cuda.synchronize()
+    for C_int in outs:
+        assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), want)
+        assert torch.equal(C_int, outs[0])
+
+
+def test_products_in_parts_from_two_threads(imu):
+    """A plan handed from one thread to another, each with its own per-thread default stream (one handle for both): the
+    launches share the buffer that the parts meet in and must not overlap."""
+    import threading
+    n, d, h = 2560, 3072, 2560
+    Aq, Bq = _product_in_parts(n, d, h, 8, (COL, COL), True)
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    plan = imu.imunpack_plan(Qa, Qb, 8, COL, COL)
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    assert plan.fusable()
+    outs = [torch.full((n, h), -1, dtype=torch.int64, device="cuda") for _ in range(6)]
+    torch.cuda.synchronize()
+    per_thread = 2  # hipStreamPerThread
+    turn, done, codes = [threading.Event() for _ in range(7)], threading.Event(), []
+
+    def work(me):
+        torch.cuda.set_device(0)
+        for i in range(me, 6, 2):
+            turn[i].wait()
+            codes.append(imu._lib.imunpack_gemm(plan.handle, A_ue.data_ptr(), B_eu.data_ptr(), None, outs[i].data_ptr(), None, h,
+                                                1.0, 1.0, 1, per_thread))
+            turn[i + 1].set()
+        done.wait()  # neither stream ends before the other thread has launched
+
+    threads = [threading.Thread(target=work, args=(me,)) for me in (0, 1)]
+    for t in threads:
+        t.start()
+    turn[0].set()
+    turn[6].wait()
+    done.set()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert codes == [0] * 6 and imu.imunpack_diag_gemm_parts(plan) == 2
+    rows = np.arange(0, n, 97)
+    want = oracle.int_gemm(Aq[rows], Bq)
     for C_int in outs:
         assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), want)
         assert torch.equal(C_int, outs[0])
