@@ -495,6 +495,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                 __hip_atomic_store(meet, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             __syncthreads();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the sums as their workgroups left them, whichever XCD those ran on
             partner = sums;
             partners = pc.parts - 1;
         }
