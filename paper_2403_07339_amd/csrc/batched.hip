@@ -96,7 +96,7 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
         c = new (std::nothrow) imunpack_batch();
         if (!c) return IMUNPACK_ENOMEM;
         memset(c, 0, sizeof(*c));
-        if (hipHostMalloc((void **)&c->pin_flags, (2 + kMaxItems) * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc((void **)&c->pin_flags, (2 + kMaxItems) * sizeof(int32_t), hipHostMallocCoherent) != hipSuccess) {
             (void)hipGetLastError();
             delete c;
             return IMUNPACK_ENOMEM;

@@ -322,7 +322,8 @@ inline bool small_tiles_possible(int64_t n, int64_t h, int nitems) {
 
 // Waits until a kernel on `st` has written `want` to a word of pinned memory (behind the data that goes with it).  The host
 // polls the word: a blocking wait costs tens of microseconds of wake-up during which the GPU idles between two stages of
-// the path, and a copy with an event behind it a launch and three calls.
+// the path, and a copy with an event behind it a launch and three calls.  (All pinned memory that kernels write while the host
+// polls it is allocated as coherent, whatever the environment's default.)
 template <class T>
 int wait_word(const T *word, T want, hipStream_t st);
 // The entry points' inner forms, which also serve the items of a batch (p->nitems of them).

@@ -2318,7 +2318,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         p->pin_hdr = nullptr;
         p->pin_items = 0;
         const size_t bytes = (size_t)nitems * sizeof(PlanHeader) + 2 * kBoundBlocks * sizeof(unsigned long long);
-        if (hipHostMalloc((void **)&p->pin_hdr, bytes, hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc((void **)&p->pin_hdr, bytes, hipHostMallocCoherent) != hipSuccess) {
             (void)hipGetLastError();
             p->pin_hdr = nullptr;
             rc = IMUNPACK_ENOMEM;
