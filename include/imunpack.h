@@ -297,7 +297,7 @@ int imunpack_gemm(imunpack_plan_t *plan, const int8_t *A_ue, const int8_t *B_eu,
  * *ctx == NULL creates a context; passing it again reuses its buffers (Q_A, Q_B, statistics, the unpacked
  * operands, a plan: they only grow), so steady-state calls allocate nothing.  The library owns the context;
  * release it with imunpack_batch_destroy.  The steps never leave the device.  The items share every launch (up to
- * 1024 at a time, fewer if they are large) and the host waits twice per such group: for the sizes of the
+ * 1024 at a time, fewer if they are large or device memory runs short) and the host waits twice per such group: for the sizes of the
  * unpacked problems and at the end.  Synchronises the stream before returning.
  * Errors: EINVAL; ERANGE if any operand held a NaN or Inf or a quotient beyond 32 bits (the outputs of
  * that item are then undefined); ENOMEM; EHIP.

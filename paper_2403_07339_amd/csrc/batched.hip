@@ -48,7 +48,8 @@ struct imunpack_batch {
 
 using namespace imu;
 
-static constexpr int64_t kGroupBytes = 1ll << 30;  // operands of the items that go through the launches together
+// Device memory of the items that go through the launches together: operands, plans and stores.
+static constexpr int64_t kGroupBytes = 2ll << 30;
 
 static int grow(void **ptr, size_t *have, size_t want) {
     if (*have >= want) return IMUNPACK_OK;
@@ -65,13 +66,25 @@ static int grow(void **ptr, size_t *have, size_t want) {
     return IMUNPACK_OK;
 }
 
-extern "C" int imunpack_batch_destroy(imunpack_batch_t *c) {
-    if (!c) return IMUNPACK_OK;
+// Gives all device memory of a context back.
+static int release(imunpack_batch *c) {
     int rc = IMUNPACK_OK;
     if (c->plan) rc = imunpack_plan_destroy(c->plan);
     if (c->arena) (void)hipFree(c->arena);
     if (c->ue) (void)hipFree(c->ue);
     if (c->ws) (void)hipFree(c->ws);
+    c->plan = nullptr;
+    c->arena = nullptr;
+    c->ue = nullptr;
+    c->ws = nullptr;
+    c->arena_bytes = c->ue_bytes = c->ws_bytes = 0;
+    c->clean_flags = nullptr;
+    return rc;
+}
+
+extern "C" int imunpack_batch_destroy(imunpack_batch_t *c) {
+    if (!c) return IMUNPACK_OK;
+    const int rc = release(c);
     if (c->pin_flags) (void)hipHostFree(c->pin_flags);
     delete c;
     return rc;
@@ -104,7 +117,7 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
         memset(c->pin_flags, 0, (2 + kMaxItems) * sizeof(int32_t));
         *ctx = c;
     }
-    // ---- one arena for everything whose size the shapes fix
+    // ---- what the shapes fix of an item: everything but its plan and its unpacked operands
     const int64_t capA = strategy_A == IMUNPACK_BOTH ? std::max<int64_t>(4096, n * d / 64) : 0;
     const int64_t capB = strategy_B == IMUNPACK_BOTH ? std::max<int64_t>(4096, h * d / 64) : 0;
     size_t off = 0;
@@ -115,29 +128,33 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
     const size_t oSmall = take(256);   // steps (2 floats), OB counts (2)
     const size_t oWs = take(2 * IMUNPACK_PERCENTILE_WORKSPACE_BYTES);
     const size_t item = off;
-    // Items that go through together: all of them while their operands and what is unpacked from them stay small
-    // beside the memory of the GPU (a group of large products fills the chip by itself).
-    const int64_t group = std::min<int64_t>(std::min<int64_t>(batch, kMaxItems), std::max<int64_t>(1, kGroupBytes / (int64_t)item));
     const size_t head = (size_t)(1 + kMaxItems) * sizeof(int32_t) + 252;
     const size_t base = head & ~(size_t)255;
-    if (c->arena_bytes < base + item * (size_t)group) c->clean_flags = nullptr;  // new memory, whatever its address
-    IMU_TRY(grow((void **)&c->arena, &c->arena_bytes, base + item * (size_t)group));
-    int32_t *flags = (int32_t *)c->arena;
-    if (c->clean_flags != flags) hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(256), 0, st, flags, 1 + kMaxItems);
-    c->clean_flags = nullptr;
-    char *first = c->arena + base;
-    int32_t *Qa = (int32_t *)(first + oQa), *Qb = (int32_t *)(first + oQb);
-    int32_t *sA = (int32_t *)(first + oSa), *sB = (int32_t *)(first + oSb);
-    float *steps = (float *)(first + oSmall);
-    int32_t *obcnt = (int32_t *)(first + oSmall) + 2;
-    void *pws = first + oWs;
-    imunpack_stats_t stA = {sA, sA + n, sA + n + d, sA + 2 * n + d, capA ? (int32_t *)(first + oLa) : nullptr, capA,
-                            capA ? obcnt : nullptr};
-    imunpack_stats_t stB = {sB, sB + h, sB + h + d, sB + 2 * h + d, capB ? (int32_t *)(first + oLb) : nullptr, capB,
-                            capB ? obcnt + 1 : nullptr};
-    bool bad = false;
-    for (int64_t i0 = 0; i0 < batch; i0 += group) {
-        const int items = (int)std::min<int64_t>(group, batch - i0);
+    // Items that go through together: all of them while their operands, their plans and what is unpacked from them (as much
+    // as without a split row or column) stay small beside the memory of the GPU: a group of large products fills the chip by
+    // itself.  (600 products of 1 x 65536 by 1 x 65536, some 50 MB each, nearly all of it plans and padding:
+    // 37.8 GB and 19 ms when only operands were counted, 2.4 GB and 25 ms so; one at a time 0.07 GB and 554 ms.)
+    auto padded = [](int64_t rows, int64_t cols) { return (rows + kTile - 1) / kTile * kTile * ((cols + kKPad - 1) / kKPad * kKPad); };
+    const int64_t whole = (int64_t)item + plan_item_bytes(n, d, h, b, strategy_A, strategy_B) + padded(n, d) + padded(h, d);
+    int64_t group = std::min<int64_t>(std::min<int64_t>(batch, kMaxItems), std::max<int64_t>(1, kGroupBytes / whole));
+    group = (batch + (batch + group - 1) / group - 1) / ((batch + group - 1) / group);  // as many groups, of equal size
+
+    auto run_group = [&](int64_t i0, int items, bool &bad) -> int {
+        if (c->arena_bytes < base + item * (size_t)items) c->clean_flags = nullptr;  // new memory, whatever its address
+        IMU_TRY(grow((void **)&c->arena, &c->arena_bytes, base + item * (size_t)items));
+        int32_t *flags = (int32_t *)c->arena;
+        if (c->clean_flags != flags) hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(256), 0, st, flags, 1 + kMaxItems);
+        c->clean_flags = nullptr;
+        char *first = c->arena + base;
+        int32_t *Qa = (int32_t *)(first + oQa), *Qb = (int32_t *)(first + oQb);
+        int32_t *sA = (int32_t *)(first + oSa), *sB = (int32_t *)(first + oSb);
+        float *steps = (float *)(first + oSmall);
+        int32_t *obcnt = (int32_t *)(first + oSmall) + 2;
+        void *pws = first + oWs;
+        imunpack_stats_t stA = {sA, sA + n, sA + n + d, sA + 2 * n + d, capA ? (int32_t *)(first + oLa) : nullptr, capA,
+                                capA ? obcnt : nullptr};
+        imunpack_stats_t stB = {sB, sB + h, sB + h + d, sB + 2 * h + d, capB ? (int32_t *)(first + oLb) : nullptr, capB,
+                                capB ? obcnt + 1 : nullptr};
         const float *Ai = A + i0 * sa_b, *Bi = B + i0 * sb_b;
         float *Ci = C + i0 * sc_b;
         QuantBatch bt;
@@ -187,7 +204,20 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
                               step + 1, 1, st));
         }
         if (unfused) IMU_HIP(hipStreamSynchronize(st));
+        c->clean_flags = flags;
+        return IMUNPACK_OK;
+    };
+    bool bad = false;
+    for (int64_t i0 = 0; i0 < batch;) {
+        const int items = (int)std::min<int64_t>(group, batch - i0);
+        const int rc = run_group(i0, items, bad);
+        if (rc == IMUNPACK_ENOMEM && items > 1) {  // their plans or their unpacked operands grew too large: fewer at a time
+            group = (items + 1) / 2;
+            IMU_TRY(release(c));
+            continue;
+        }
+        IMU_TRY(rc);
+        i0 += items;
     }
-    c->clean_flags = flags;
     return bad ? IMUNPACK_ERANGE : IMUNPACK_OK;
 }

@@ -331,6 +331,8 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
               int strategy_A, int strategy_B, const imunpack_stats_t *stats_A, const imunpack_stats_t *stats_B,
               imunpack_plan_t **plan, int nitems, int64_t op_stride, hipStream_t st);
 Plan item_view(const Plan &batch, int i);
+// Device memory that the plan of one item of a batch takes (before anything overflows its first guesses).
+int64_t plan_item_bytes(int64_t n, int64_t d, int64_t h, int b, int strategy_A, int strategy_B);
 int unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const int32_t *B, int64_t ldb, int8_t *A_ue,
                 int64_t a_stride, int8_t *B_eu, int64_t b_stride, hipStream_t st);
 int quantize_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float scale_A, const float *scale_A_dev,

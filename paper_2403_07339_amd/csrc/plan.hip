@@ -2271,6 +2271,28 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
     return await_headers(p, st);
 }
 
+// First guesses of the capacities; every one of them is grown after a run that reports it too small.
+static void guess_capacities(Plan *p) {
+    const int64_t n = p->n, d = p->d, h = p->h;
+    p->cap[CAP_ROWA] = std::max(p->cap[CAP_ROWA], (int)(p->sA == IMUNPACK_COL ? n : 2 * n + 256));
+    p->cap[CAP_ROWB] = std::max(p->cap[CAP_ROWB], (int)(p->sB == IMUNPACK_COL ? h : 2 * h + 256));
+    p->cap[CAP_C1] = std::max(p->cap[CAP_C1], (int)(p->sA == IMUNPACK_ROW ? d : 2 * d + 256));
+    p->cap[CAP_C2] = std::max(p->cap[CAP_C2], (int)(2 * d + 512));
+    p->cap[CAP_EDGEA] = std::max(p->cap[CAP_EDGEA], (int)std::min<int64_t>(n * d, std::max<int64_t>(n * d / 64, 4096)));
+    p->cap[CAP_EDGEB] = std::max(p->cap[CAP_EDGEB], (int)std::min<int64_t>(2 * h * d, std::max<int64_t>(h * d / 64, 4096)));
+    p->cap[CAP_OB] = std::max(p->cap[CAP_OB], (int)std::min<int64_t>(std::max(n, h) * d, std::max<int64_t>(std::max(n, h) * d / 64, 4096)));
+}
+
+int64_t plan_item_bytes(int64_t n, int64_t d, int64_t h, int b, int strategy_A, int strategy_B) {
+    Plan p;
+    memset((void *)&p, 0, sizeof(p));
+    p.n = n; p.d = d; p.h = h; p.b = b; p.sA = strategy_A; p.sB = strategy_B;
+    p.nitems = 1;
+    guess_capacities(&p);
+    (void)carve(&p, nullptr, false, false);
+    return p.item_bytes;
+}
+
 // The plan of one product (nitems = 1), or of every product of a batch of one shape: A, B, the statistics and
 // the OB lists of item i lie i * op_stride bytes behind those of item 0.
 int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t *B, int64_t h, int64_t ldb, int b,
@@ -2300,14 +2322,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
     p->op_stride = op_stride;
     p->chunkB = small_tiles_possible(n, h, nitems) ? kChunk : kTile;
     if (!same) {
-        // first guesses; every one of them is grown after a run that reports it too small
-        p->cap[CAP_ROWA] = std::max(p->cap[CAP_ROWA], (int)(strategy_A == IMUNPACK_COL ? n : 2 * n + 256));
-        p->cap[CAP_ROWB] = std::max(p->cap[CAP_ROWB], (int)(strategy_B == IMUNPACK_COL ? h : 2 * h + 256));
-        p->cap[CAP_C1] = std::max(p->cap[CAP_C1], (int)(strategy_A == IMUNPACK_ROW ? d : 2 * d + 256));
-        p->cap[CAP_C2] = std::max(p->cap[CAP_C2], (int)(2 * d + 512));
-        p->cap[CAP_EDGEA] = std::max(p->cap[CAP_EDGEA], (int)std::min<int64_t>(n * d, std::max<int64_t>(n * d / 64, 4096)));
-        p->cap[CAP_EDGEB] = std::max(p->cap[CAP_EDGEB], (int)std::min<int64_t>(2 * h * d, std::max<int64_t>(h * d / 64, 4096)));
-        p->cap[CAP_OB] = std::max(p->cap[CAP_OB], (int)std::min<int64_t>(std::max(n, h) * d, std::max<int64_t>(std::max(n, h) * d / 64, 4096)));
+        guess_capacities(p);
         p->ignore_listA = p->ignore_listB = 0;
     }
     const bool ownA = !(stats_A && stats_A->rowcnt && stats_A->colcnt && stats_A->rowmax && stats_A->colmax);
