@@ -298,7 +298,8 @@ int imunpack_gemm(imunpack_plan_t *plan, const int8_t *A_ue, const int8_t *B_eu,
  * operands, a plan: they only grow), so steady-state calls allocate nothing.  The library owns the context;
  * release it with imunpack_batch_destroy.  The steps never leave the device.  The items share every launch (up to
  * 1024 at a time, fewer if they are large or device memory runs short) and the host waits twice per such group: for the sizes of the
- * unpacked problems and at the end.  Synchronises the stream before returning.
+ * unpacked problems and at the end; items that write where another one reads or writes (C_i = A_(i+1), sc_b = 0)
+ * go one after the other in the order of i.  Synchronises the stream before returning.
  * Errors: EINVAL; ERANGE if any operand held a NaN or Inf or a quotient beyond 32 bits (the outputs of
  * that item are then undefined); ENOMEM; EHIP.
  * For b <= 4 the digits are stored as six-bit floating-point codes (imunpack_plan_set_digits); the

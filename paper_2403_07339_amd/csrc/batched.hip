@@ -137,6 +137,16 @@ extern "C" int imunpack_gemm_batched(const float *A, int64_t sa_b, int64_t sa_r,
     auto padded = [](int64_t rows, int64_t cols) { return (rows + kTile - 1) / kTile * kTile * ((cols + kKPad - 1) / kKPad * kKPad); };
     const int64_t whole = (int64_t)item + plan_item_bytes(n, d, h, b, strategy_A, strategy_B) + padded(n, d) + padded(h, d);
     int64_t group = std::min<int64_t>(std::min<int64_t>(batch, kMaxItems), std::max<int64_t>(1, kGroupBytes / whole));
+    // Items whose outputs lie on one another's outputs or operands (all but an output in the place of its own item's operand)
+    // go one after the other: C_i may be A_(i+1).
+    const int64_t ext_c = (n - 1) * ldc + h;
+    auto crosses = [&](const float *X, int64_t rows, int64_t sr, int64_t sc, int64_t sb) {
+        const int64_t ext = (rows - 1) * sr + (d - 1) * sc + 1;
+        if (C + (batch - 1) * sc_b + ext_c <= X || X + (batch - 1) * sb + ext <= C) return false;
+        return !(C == X && sc_b == sb && ext <= sb && ext_c <= sc_b);
+    };
+    const bool c_apart = sc_b >= ext_c || (sc_b >= h && ldc >= (batch - 1) * sc_b + h);  // side by side, or row by row in turn
+    if (!c_apart || crosses(A, n, sa_r, sa_c, sa_b) || crosses(B, h, sb_r, sb_c, sb_b)) group = 1;
     group = (batch + (batch + group - 1) / group - 1) / ((batch + group - 1) / group);  // as many groups, of equal size
 
     auto run_group = [&](int64_t i0, int items, bool &bad) -> int {

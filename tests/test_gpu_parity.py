@@ -891,6 +891,36 @@ def test_batched_memory_follows_what_an_item_takes(imu):
         assert (np.abs(out[i] - want) <= REL_TOL * np.abs(want)).all(), i
 
 
+def test_batched_items_that_write_over_one_another(imu):
+    """A chain (C_i is A_(i+1)), outputs all in one place, and outputs in the place of their own operands: as the items
+    one by one, in order."""
+    g = torch.Generator().manual_seed(33)
+    batch, n, d = 3, 40, 64
+    w = torch.randn((batch, d, d), generator=g).to("cuda")
+    x = torch.randn((batch + 1, n, d), generator=g).to("cuda")
+
+    def call(a, sa_b, c, sc_b, first, items, ctx):
+        step = 4 * first
+        code = imu._lib.imunpack_gemm_batched(a.data_ptr() + sa_b * step, sa_b, d, 1, w.data_ptr() + d * d * step, d * d, d, 1, items, n,
+                                              d, d, 95.0, 31.0, 31.0, 8, ROW, COL, c + sc_b * step, sc_b, d, imu.C.byref(ctx._h),
+                                              torch.cuda.current_stream().cuda_stream)
+        assert code == imu.OK
+
+    for where in ("chain", "one place", "own place"):
+        got = []
+        for one_by_one in (True, False):
+            buf = x.clone()
+            out = torch.zeros((n, d), device="cuda")
+            c, sc_b = {"chain": (buf.data_ptr() + 4 * n * d, n * d), "one place": (out.data_ptr(), 0),
+                       "own place": (buf.data_ptr(), n * d)}[where]
+            ctx = imu.BatchContext()
+            for i in range(batch) if one_by_one else (0,):
+                call(buf, n * d, c, sc_b, i, 1 if one_by_one else batch, ctx)
+            got.append((buf.cpu(), out.cpu()))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), where
+        assert not torch.equal(got[0][0], x.cpu()) or where == "one place"
+
+
 def _sampled_entries(total, count=4096):
     """The entries of a matrix that the percentile's sample looks at (a hash of the sample number)."""
     x = np.arange(count, dtype=np.uint64)
