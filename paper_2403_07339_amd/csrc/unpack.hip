@@ -559,8 +559,12 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     const unsigned nitems = (unsigned)p->nitems;
     p->bound_pending = 0;
     p->fusable = 0;  // until the bounds say otherwise
-    // the planner leaves the bounds and the row norms cleared; a repeated unpack of the same plan clears them again
-    if (p->unpacked) {
+    // keep-weights mode: the plan took the second operand's unpacking over, and the caller's buffer still holds
+    // what the unpack before wrote for exactly that unpacking (same buffer, same format, row norms in place)
+    const bool keepB = p->keep_B && h.reusedB && !p->unpacked && p->kept_Beu == B_eu && p->kept_Beu_fp6 == p->fp6;
+    // the planner leaves the bounds and the row norms cleared, but for the norms of an unpacking it took over; a repeated
+    // unpack of the same plan clears them again
+    if (p->unpacked || (h.reusedB && !keepB)) {
         if (batch) return IMUNPACK_EINVAL;
         hipLaunchKernelGGL(reset_bound_kernel, dim3(64), dim3(256), 0, st, p->d_hdr, p->layA.rowsum, h.Mp,
                            p->layB.rowsum, h.Np);
@@ -571,9 +575,6 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     memset(sc, 0, sizeof(sc));
     bool launch[2] = {false, false}, dense[2] = {false, false};
     int most_rows = 0;  // physical rows of both operands, in the largest item
-    // keep-weights mode: the plan took the second operand's unpacking over, and the caller's buffer still holds
-    // what the unpack before wrote for exactly that unpacking (same buffer, same format, row norms in place)
-    const bool keepB = p->keep_B && h.reusedB && !p->unpacked && p->kept_Beu == B_eu && p->kept_Beu_fp6 == p->fp6;
     for (int op = 0; op < 2; ++op) {
         const RowLayout &lay = op ? p->layB : p->layA;
         const bool both = (op ? p->sB : p->sA) == IMUNPACK_BOTH;

@@ -430,6 +430,26 @@ def test_keep_weights_takes_the_second_operand_over_only_when_it_may(imu, sa, sb
     assert not plan.weights_reused()
 
 
+def test_keep_weights_with_other_buffers(imu):
+    """A plan that took B's unpacking over, unpacked into another B_eu buffer than before: B is written again and its row
+    norms are measured afresh, not on top of the old ones."""
+    rng = np.random.default_rng(77)
+    Aq, Bq = (rand_ints(rng, r, 400, 128, 0.004, 2) for r in (60, 150))
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    want = oracle.int_gemm(Aq, Bq)
+    plan, bounds, held = imu.Plan(), None, []
+    for i in range(4):
+        imu.imunpack_plan(Qa, Qb, 8, ROW, BOTH, plan=plan)
+        plan.keep_weights(True)
+        assert plan.weights_reused() == (i > 1)
+        held.append(imu.imunpack_unpack(plan, Qa, Qb))
+        bounds = bounds or plan.bounds()
+        assert plan.bounds() == bounds, i
+        C_int = torch.full(want.shape, -1, dtype=torch.int64, device="cuda")
+        imu.imunpack_gemm(plan, *held[-1], 1.0, 1.0, C_int, None, None, fuse=True)
+        assert np.array_equal(C_int.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("b", [3, 5, 6, 7])
 def test_other_bit_widths(imu, b):
     w = workloads.small(11, 130, 200, 140, kind="scattered", b=b)
