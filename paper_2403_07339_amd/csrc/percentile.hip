@@ -33,20 +33,30 @@ constexpr int kHold = 48;                          // entries a thread of the on
 constexpr int64_t kSmall = kSelThreads * kHold;
 constexpr int kSample = 4096;                      // entries of the sample
 constexpr int kItems = 8;                          // 16-byte pieces per thread and step, loaded side by side
-constexpr int kBins0 = 2048, kBins1 = 1024, kBins2 = 512;  // of the three passes
+// Bins of the three passes: together they tell all 2^31 magnitudes apart, whatever the window (no workgroup is ever left to
+// finish alone: the last bit of the window above the 99.9th percentile of 8192 x 8190 weights took it 6.8 ms).  The first pass
+// needs no more than 2041: (infinity's bit pattern >> 20) + 1.
+constexpr int kBins0 = 2041, kBins1 = 1024, kBins2 = 1024;
 constexpr unsigned kInf = 0x7f800000u;             // above it: NaN
 
-// What the launches of one selection leave each other, behind the three histograms in the workspace.
+// What the launches of one selection leave each other: the words between the first pass's histogram and the second's.
 struct SelState {
-    unsigned lo, top, shift0;     // the window [lo, lo + top], the first pass's bin width 1 << shift0
+    unsigned lo, top;             // the window [lo, lo + top]
     unsigned below;               // entries below it (first pass)
-    unsigned maxbits, nan;        // largest magnitude (as its bit pattern); whether there is a NaN
-    unsigned base1, k1, shift1;   // the second pass's window, the rank wanted inside it, its bin width
-    unsigned found, missed;       // after the first pass: base1 is the answer / the rank was outside the window
-    unsigned arrived;             // workgroups of the third pass that are done
+    unsigned maxbits;             // largest magnitude (as its bit pattern; a NaN's is beyond infinity's)
+    unsigned base1, k1;           // the second pass's window and the rank wanted inside it
+    unsigned after;               // after the first pass: kFound: base1 is the answer, kMissed: the rank was outside the
+                                  // window, else the second pass's bin width << 16; below them the workgroups of the third pass that are done
 };
-static_assert(IMUNPACK_PERCENTILE_WORKSPACE_BYTES >= (kBins0 + kBins1 + kBins2) * sizeof(unsigned) + sizeof(SelState),
-              "workspace");
+constexpr unsigned kFound = 1u << 30, kMissed = 1u << 31;
+constexpr int kState0 = kBins0, kHist1 = kState0 + (int)(sizeof(SelState) / sizeof(unsigned)), kHist2 = kHist1 + kBins1;
+constexpr int kSelWords = kHist2 + kBins2;
+static_assert(IMUNPACK_PERCENTILE_WORKSPACE_BYTES >= kSelWords * sizeof(unsigned), "workspace");
+// the first pass's bin width (as a shift) for a window of top + 1 values: the smallest that kBins0 bins cover it with
+__device__ __forceinline__ unsigned sel_shift0(unsigned top) {
+    unsigned s = top >= 2048u ? 32 - __clz(top) - 11 : 0;
+    return (top >> s) < (unsigned)kBins0 ? s : s + 1;
+}
 
 // One matrix: nslow lines of nfast entries, entry (l, f) at X[l * sslow + f * sfast].
 struct SelOperand {
@@ -82,7 +92,7 @@ __device__ __forceinline__ SelOperand sel_operand(const SelArgs &a) {
 }
 __device__ __forceinline__ unsigned *sel_hist(void *ws) { return reinterpret_cast<unsigned *>(ws); }
 __device__ __forceinline__ SelState *sel_state(void *ws) {
-    return reinterpret_cast<SelState *>(reinterpret_cast<unsigned *>(ws) + kBins0 + kBins1 + kBins2);
+    return reinterpret_cast<SelState *>(reinterpret_cast<unsigned *>(ws) + kState0);
 }
 __device__ __forceinline__ unsigned sel_line(const SelOperand &o, unsigned e) {
     return o.nfast > 1 ? (unsigned)__umul64hi(e, o.magic) : e;
@@ -177,7 +187,7 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(SelArgs args)
     if (threadIdx.x == 0) s_max = 0;
     if (!whole) {  // a clean workspace for the passes
         unsigned *w = sel_hist(o.ws);
-        for (int i = threadIdx.x; i < kBins0 + kBins1 + kBins2 + (int)(sizeof(SelState) / 4); i += kSelThreads) w[i] = 0;
+        for (int i = threadIdx.x; i < kSelWords; i += kSelThreads) w[i] = 0;
         if (threadIdx.x == 0 && o.status && o.clear_status) *o.status = 0;
     }
     __syncthreads();
@@ -228,7 +238,6 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(SelArgs args)
     const unsigned lo = ok[0] ? min(prefix[0], kInf) : 0u, hi = ok[1] ? min(prefix[1] | 0x3ffu, kInf) : kInf;
     st->lo = lo;
     st->top = hi - lo;
-    st->shift0 = hi - lo >= (unsigned)kBins0 ? 32 - __clz(hi - lo) - 11 : 0;
 }
 
 // Calls take(bits of the magnitude) for every entry that this workgroup of `blocks` is responsible for.
@@ -286,8 +295,7 @@ __device__ __forceinline__ void sel_stream(const SelOperand &o, unsigned block, 
 }
 
 // The rank k inside the window [base, base + top], by one workgroup on its own: a radix select of 11 bits per
-// pass over the whole matrix.  (A window that missed, or the last bit of one of more than 2^30 values: the
-// passes below resolve everything else.)
+// pass over the whole matrix (a window that missed).
 __device__ __forceinline__ unsigned sel_alone(const SelOperand &o, unsigned base, unsigned top, unsigned k, unsigned *lh,
                                               unsigned *lds) {
     for (;;) {  // the window shrinks by eleven bits a pass
@@ -311,49 +319,49 @@ __device__ __forceinline__ unsigned sel_alone(const SelOperand &o, unsigned base
 // ---- a pass over the matrix (PASS 0, 1, 2) -----------------------------------------------------------------
 template <int PASS>
 __global__ __launch_bounds__(kSelThreads) void select_count_kernel(SelArgs args) {
-    __shared__ unsigned lh[kBins0];
+    __shared__ unsigned lh[2048];
     __shared__ unsigned lds[20], s_below, s_max, s_last;
     const SelOperand o = sel_operand(args);
     if (o.N <= (unsigned)kSmall) return;  // the one-workgroup launch has done it
     SelState *st = sel_state(o.ws);
-    unsigned *hist = sel_hist(o.ws) + (PASS == 0 ? 0 : PASS == 1 ? kBins0 : kBins0 + kBins1);
+    unsigned *hist = sel_hist(o.ws) + (PASS == 0 ? 0 : PASS == 1 ? kHist1 : kHist2);
     const bool lead = blockIdx.x == 0;
-    unsigned base = st->lo, top = st->top, shift = st->shift0, k = o.k, bin, before;
+    unsigned base = st->lo, top = st->top, shift = sel_shift0(top), k = o.k, bin, before;
     if (PASS == 1) {  // what the first pass has narrowed the window to
         const unsigned below = st->below, kw = k > below ? k - below : 0u;
         const bool got = sel_pick(sel_hist(o.ws), kBins0, kw, bin, before, lds);
         const unsigned nshift = shift > 10 ? shift - 10 : 0;
         if (lead && threadIdx.x == 0) {
-            st->missed = !got;
-            st->found = got && shift == 0;
+            st->after = !got ? kMissed : shift == 0 ? kFound : nshift << 16;
             st->base1 = base + (bin << shift);
             st->k1 = kw - before;
-            st->shift1 = nshift;
         }
         if (!got || shift == 0) return;
         base += bin << shift;
         top = (1u << shift) - 1u;
         shift = nshift;
     } else if (PASS == 2) {
-        if (st->missed) {
+        const unsigned after = st->after;
+        if (after & kMissed) {
             if (!lead) return;
-            const unsigned a = st->nan ? 0x7fffffffu : sel_alone(o, 0, kInf, k, lh, lds);
+            const unsigned a = st->maxbits > kInf ? 0x7fffffffu : sel_alone(o, 0, kInf, k, lh, lds);
             if (threadIdx.x == 0) sel_result(o, a, st->maxbits);
             return;
         }
         base = st->base1;
-        if (!st->found) {
-            shift = st->shift1;
-            if (!sel_pick(sel_hist(o.ws) + kBins0, kBins1, st->k1, bin, before, lds)) return;  // cannot be: counted before
+        shift = 0;
+        if (!(after & kFound)) {
+            shift = after >> 16;
+            if (!sel_pick(sel_hist(o.ws) + kHist1, kBins1, st->k1, bin, before, lds)) return;  // cannot be: counted before
             base += bin << shift;
             k = st->k1 - before;
         }
-        if (st->found || shift == 0) {
+        if (shift == 0) {
             if (lead && threadIdx.x == 0) sel_result(o, base, st->maxbits);
             return;
         }
-        top = (1u << shift) - 1u;
-        shift = shift > 9 ? shift - 9 : 0;
+        top = (1u << shift) - 1u;  // at most ten bits are left
+        shift = 0;
     }
     const int nbins = PASS == 0 ? kBins0 : PASS == 1 ? kBins1 : kBins2;
     for (int i = threadIdx.x; i < nbins; i += kSelThreads) lh[i] = 0;
@@ -381,10 +389,7 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(SelArgs args)
     if (PASS == 0 && threadIdx.x == 0) {
         if (s_below) atomicAdd(&st->below, s_below);
         atomicMax(&st->maxbits, s_max);
-        if (s_max > kInf) {
-            st->nan = 1;
-            if (o.status) atomicOr(o.status, 1);
-        }
+        if (s_max > kInf && o.status) atomicOr(o.status, 1);
     }
     if (PASS == 2) {  // rare: the workgroup that finishes last picks
         // (what the workgroups hand over are device-wide atomics: they only have to have arrived.  A fence to release them writes
@@ -392,14 +397,12 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(SelArgs args)
         // pass 110 us in all; so: 56, 41 without the pass)
         stores_done();
         __syncthreads();
-        if (threadIdx.x == 0) s_last = atomicAdd(&st->arrived, 1u) == gridDim.x - 1u;
+        if (threadIdx.x == 0) s_last = (atomicAdd(&st->after, 1u) & 0xffffu) == gridDim.x - 1u;
         __syncthreads();
         if (!s_last) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         if (!sel_pick(hist, kBins2, k, bin, before, lds)) return;
-        base += bin << shift;
-        if (shift) base = sel_alone(o, base, (1u << shift) - 1u, k - before, lh, lds);
-        if (threadIdx.x == 0) sel_result(o, base, st->maxbits);
+        if (threadIdx.x == 0) sel_result(o, base + bin, st->maxbits);
     }
 }
 

@@ -953,11 +953,12 @@ def _sampled_entries(total, count=4096):
 
 
 @pytest.mark.parametrize("rows,cols", [(256, 192), (1, 49153), (257, 1031), (1024, 768)])
-@pytest.mark.parametrize("kind", ["normal", "ties", "gap", "sparse", "misled"])
+@pytest.mark.parametrize("kind", ["normal", "ties", "gap", "sparse", "misled", "wide"])
 def test_percentile_windows(imu, rows, cols, kind):
     """Around the size where the selection leaves one workgroup, and what its window can meet: ties (values of eight
-    significant bits), two far modes with the rank at the edge between them (the third pass), mostly zeros, and a
-    sample that shows something else than the matrix (the window misses).  Contiguous, transposed and strided."""
+    significant bits), two far modes with the rank at the edge between them (the third pass), mostly zeros, a
+    sample that shows something else than the matrix (the window misses), and magnitudes of every exponent, zero and
+    infinity among them (windows of up to 2^31 values).  Contiguous, transposed and strided."""
     rng = np.random.default_rng(rows * 31 + cols)
     x = rng.standard_normal((rows, cols)).astype(np.float32)
     flat = x.reshape(-1)
@@ -969,6 +970,10 @@ def test_percentile_windows(imu, rows, cols, kind):
         flat[rng.random(flat.size) < 0.9995] = 0.0
     elif kind == "misled":
         flat[_sampled_entries(flat.size).astype(np.int64)] = np.float32(1e6)
+    elif kind == "wide":
+        flat[:] = (rng.integers(0, 1 << 32, flat.size, dtype=np.uint64).astype(np.uint32) & np.uint32(0xff7fffff)).view(np.float32)
+        flat[rng.random(flat.size) < 0.4] = 0.0
+        flat[rng.random(flat.size) < 0.001] = np.float32("inf")
     xt = torch.from_numpy(x)
     wide = torch.zeros((rows, cols + 4), device="cuda")
     wide[:, :cols] = xt.to("cuda")
