@@ -8,16 +8,17 @@
 // Up to kSmall entries: one workgroup holds the whole matrix in registers and selects there, one launch.
 //
 // More: one workgroup first selects two ranks of a random sample that enclose the wanted one (five standard
-// deviations of the sample's rank and a little to either side), which leaves a window of about 1 % of the
-// entries.  Two passes over the matrix then count the entries below the window and, per value of the
+// deviations of the sample's rank and a little to either side), which leaves a window of a few per cent of the
+// entries (3.6 at p = 95).  Two passes over the matrix then count the entries below the window and, per value of the
 // next 11 (10) bits inside it, the entries in it (a histogram in LDS per workgroup, merged with one atomic per
 // non-empty bin); a workgroup finds the bin that the pass before it narrowed the window to by itself, from the
-// merged histogram.  A window of more than 2^21 values takes a third pass; a window that missed (the sample was
-// that unlucky) is left to one workgroup's own radix select over the whole matrix.
-// The passes are bound by reading the matrix: with the window, one entry in a hundred goes to the histogram.  Three
+// merged histogram.  A window of more than 2^21 values (normal entries at p = 95: every other time; heavy tails: always) takes
+// a third pass of 10 bits; a window that missed (the sample was that unlucky) is left to one workgroup's own radix select over
+// the whole matrix.
+// The passes are bound by reading the matrix: with the window, few entries go to the histogram.  Three
 // passes with a histogram of every entry, each followed by a launch that picked the bin, took 53 us each
-// on 11008 x 4096 (180 MB), 3.4 TB/s, 175 us in all; now 16 us for the sample, 35 and 31 us
-// for the passes and 6 us for the launch that closes: 88.  1576 x 768 and 3072 x 768 together: 150 -> 35 us.  Everything stays on the stream; the caller reads *alpha when it
+// on 11008 x 4096 (180 MB), 3.4 TB/s, 175 us in all; now 9 us for the sample, 34 and 31 us for the passes (5.4 TB/s) and 5 us
+// for the launch that closes: 79, or 108 with the third pass.  Everything stays on the stream; the caller reads *alpha when it
 // needs the number.
 #include "common.h"
 
@@ -28,7 +29,6 @@
 namespace imu {
 
 constexpr int kSelThreads = 1024;
-constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kHold = 48;                          // entries a thread of the one-workgroup selection holds, at most
 constexpr int64_t kSmall = kSelThreads * kHold;
 constexpr int kSample = 4096;                      // entries of the sample
@@ -101,6 +101,20 @@ __device__ __forceinline__ float sel_entry(const SelOperand &o, unsigned e) {
     if (o.kind == 0) return o.X[e];
     const unsigned l = sel_line(o, e);
     return o.X[(int64_t)l * o.sslow + (int64_t)(e - l * o.nfast) * o.sfast];
+}
+
+// One more in a bin of a histogram in LDS.  `crowded`: lanes that name the bin of the first of them share an update, for
+// matrices that are full of one value (zeros behind a ReLU, ones), of which a wave would queue up 64.  (Where values
+// differ it costs 5 of 24 us, so the callers look first.)
+__device__ __forceinline__ void sel_count(unsigned *hist, unsigned bin, bool crowded) {
+    if (!crowded) {
+        atomicAdd(&hist[bin], 1u);
+        return;
+    }
+    const unsigned first = __builtin_amdgcn_readfirstlane(bin);
+    const unsigned long long same = __ballot(bin == first);
+    if (bin != first) atomicAdd(&hist[bin], 1u);
+    else if ((int)(threadIdx.x & 63) == __builtin_ctzll(same)) atomicAdd(&hist[first], (unsigned)__popcll(same));
 }
 
 // Workgroup-wide: the bin of hist[0..nbins) in which the cumulative count reaches k (1-based) and the count
@@ -201,11 +215,13 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(SelArgs args)
     for (int pass = 0; pass < passes; ++pass) {
         const int shift = pass == 0 ? 20 : pass == 1 ? 10 : 0, nbins = pass == 0 ? 2048 : 1024;
         const unsigned bmask = (unsigned)nbins - 1u, pmask = pass == 0 ? 0u : 0xffffffffu << (shift + 10);
+        // whether a quarter of the wave's first entries are the same (192 x 255, 94 % zeros: 56 -> 27 us, ones 133 -> 38)
+        const bool crowded = __popcll(__ballot(u[0] == __builtin_amdgcn_readfirstlane(u[0]) && u[0] != 0xffffffffu)) >= 16;
 #pragma unroll
         for (int j = 0; j < HOLD; ++j) {
             if (u[j] == 0xffffffffu) continue;
-            if ((u[j] & pmask) == prefix[0]) atomicAdd(&hist[0][(u[j] >> shift) & bmask], 1u);
-            if (!whole && pass > 0 && (u[j] & pmask) == prefix[1]) atomicAdd(&hist[1][(u[j] >> shift) & bmask], 1u);
+            if ((u[j] & pmask) == prefix[0]) sel_count(hist[0], (u[j] >> shift) & bmask, crowded);
+            if (!whole && pass > 0 && (u[j] & pmask) == prefix[1]) sel_count(hist[1], (u[j] >> shift) & bmask, crowded);
         }
         __syncthreads();
         const unsigned p0 = prefix[0], p1 = prefix[1];
@@ -303,7 +319,7 @@ __device__ __forceinline__ unsigned sel_alone(const SelOperand &o, unsigned base
         for (int i = threadIdx.x; i < 2048; i += kSelThreads) lh[i] = 0;
         __syncthreads();
         sel_stream<2>(o, 0, 1, [&](unsigned u) {
-            if (u - base <= top) atomicAdd(&lh[(u - base) >> shift], 1u);
+            if (u - base <= top) sel_count(lh, (u - base) >> shift, true);
         });
         __syncthreads();
         unsigned bin, before;
@@ -326,6 +342,8 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(SelArgs args)
     SelState *st = sel_state(o.ws);
     unsigned *hist = sel_hist(o.ws) + (PASS == 0 ? 0 : PASS == 1 ? kHist1 : kHist2);
     const bool lead = blockIdx.x == 0;
+    // a window with zero in it, or of next to nothing (4096 x 4095, 94 % zeros: 107 -> 66 us, ones 84 -> 33)
+    const bool crowded = st->lo == 0 || st->top < 2048u;
     unsigned base = st->lo, top = st->top, shift = sel_shift0(top), k = o.k, bin, before;
     if (PASS == 1) {  // what the first pass has narrowed the window to
         const unsigned below = st->below, kw = k > below ? k - below : 0u;
@@ -373,7 +391,7 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(SelArgs args)
             below += u < base ? 1u : 0u;
             umax = max(umax, u);
         }
-        if (u - base <= top) atomicAdd(&lh[(u - base) >> shift], 1u);
+        if (u - base <= top) sel_count(lh, (u - base) >> shift, crowded);
     });
     if (PASS == 0) {
         below = wave_sum_lane63(below);
