@@ -217,7 +217,8 @@ int imunpack_plan_destroy(imunpack_plan_t *plan);
  * every imunpack_plan on this plan object: a plan call then compares, on the device, the column slots of
  * A's unpacking with those of the call before and, if they are the same, takes the second operand's
  * unpacking (for UnpackBoth: without running Alg. 4 on it again) and the layouts of B's rows and of the
- * columns over as they stand (no extra host wait; the result is the same plan either way); the first
+ * columns over as they stand (the result is the same plan either way; if they differ, the host may wait a
+ * second time); the first
  * imunpack_unpack after such a plan call writes only the A store if it is given the B_eu buffer that the
  * unpack before wrote (same address, same digit format): B_eu and its row norms are already what they
  * would become.  Otherwise, and in the first call after keep was set, B is unpacked as usual.

@@ -2197,7 +2197,8 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
     const int32_t *skip = nullptr;
     // keep-weights mode: up to 4096 rows, which one workgroup lays out as fast as the layout kernel would
     const size_t keep_lds = std::max(((size_t)2 * n + phys_cap_rows(p->cap[CAP_ROWA]) / kChunk + 8) * sizeof(int32_t), listA ? greedy_lds(p, 1) : 0);
-    const bool at_once = keep && items == 1 && !scanA && n <= kRowSlice && d <= kKeepPlanCols && keep_lds <= (size_t)kGreedyLdsMax;
+    // (and only if there is something to take over: otherwise it would end in a wait for a verdict that is known)
+    const bool at_once = keep && p->keep_valid && items == 1 && !scanA && n <= kRowSlice && d <= kKeepPlanCols && keep_lds <= (size_t)kGreedyLdsMax;
     if (at_once) {
         KeepPlan f;
         memset((void *)&f, 0, sizeof(f));
