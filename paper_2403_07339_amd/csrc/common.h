@@ -46,6 +46,8 @@ static inline bool capturing(hipStream_t st) {
 // ---- geometry shared by planner, scatter and GEMM ----------------------------------------------
 constexpr int kTile = 256;       // GEMM output tile edge in unpacked rows (both operands)
 constexpr int kChunk = 64;       // physical rows the GEMM epilogue holds at a time; no source row straddles a chunk
+constexpr int kChunkPairs = (kTile / kChunk) * (kTile / kChunk);  // 64 x 64 tiles in one of 256 x 256
+constexpr int kXcdCus = 32;      // CUs of an XCD
 constexpr int kKPad = 128;       // every exponent group is padded to a multiple of this many columns
 constexpr int kMaxGroups = 64;   // distinct diagonal entries of S the planner supports
 constexpr int kMaxItems = 1024;  // products of a batch that are planned together
@@ -91,7 +93,7 @@ struct PlanHeader {
     uint32_t cols_done;              // column-layout workgroups that have finished (the last one orders the units)
     int32_t extras;                  // edges that the repeated columns of B_e add to B's OB entries (UnpackBoth on B)
     int32_t reusedB;                 // the second operand's unpacking was taken over from the plan before (keep-weights mode)
-    int32_t pad_;
+    int32_t chunkB;                  // no source row of B straddles that many physical rows: kTile, or kChunk for small products
     int32_t seq;                     // in the host's copy: which plan's header it holds
     unsigned long long bound[2];     // max over rows of sum_c s^e(c) |digit| for A_ue, B_eu
 };
@@ -273,7 +275,7 @@ struct imunpack_plan {
     void *split_ws;               // where the parts of a GEMM tile meet (gemm.hip), if a product needed it
     hipEvent_t split_done;        // recorded behind the launch that used it last
     int gemm_parts;               // parts of a tile in the last fused launch (0: 64 x 64 tiles; imunpack_diag_gemm_parts)
-    int chunkB;                   // no source row of B straddles that many physical rows: kTile, or kChunk for small products
+    int chunkB;                   // kChunk if the rows of B may be laid out for the small-tile GEMM (PlanHeader::chunkB: whether they are)
     int32_t seq;                  // of the last header or bounds that the host asked for (the kernel writes it with them)
     unsigned long long *pin_bounds;  // pinned, behind the headers: two words per workgroup that measured the bounds
     int bound_pending;            // the bounds of the last imunpack_unpack have not been read back yet
@@ -318,6 +320,31 @@ using Plan = struct ::imunpack_plan;  // the C function imunpack_plan() hides th
 // above about 120 tiles of unpacked rows).
 inline bool small_tiles_possible(int64_t n, int64_t h, int nitems) {
     return ((n + kTile - 1) / kTile) * ((h + kTile - 1) / kTile) * nitems <= 128;
+}
+
+// Into how many parts the tiles of the last round are cut (1: not at all): where at most half of the CUs would work on it and
+// the contraction is long enough.  Cut in four, the round is not four times as fast (CUs that share L2 and power walk
+// slower, and 256 KiB of sums change hands per part): 4096 x 8448 by 8448 rows, 66 k-tiles: 402 -> 381 us; 17408 rows,
+// 96 k-tiles of six-bit digits: 518 -> 493; 2048 x 15104 by 2048, 118 k-tiles: 140 -> 81; 3072 x 6144 by 6400, 48: 138 -> 125;
+// but 32 k-tiles: 430 -> 434, 19: 37 -> 42.  In eight parts none was faster than in four.
+__host__ __device__ inline int split_parts(int64_t tiles, int64_t ktiles) {
+    const int m = (int)((tiles + 7) / 8 % kXcdCus);
+    if (m == 0 || m > kXcdCus / 2 || ktiles < 48) return 1;
+    return kXcdCus / m < 4 ? kXcdCus / m : 4;
+}
+
+// Whether 64 x 64 tiles are the better ones for `tiles` tiles of 256 x 256, of which `pairs` chunk pairs hold anything, with
+// `ktiles` k-tiles each, from what either kernel measured (nanoseconds): a 256 x 256 tile takes 16 us and 1.15 us per k-tile, 256
+// of them at a time (one round of tiles in parts: 20 us and 0.52 us per k-tile); the small tiles take 0.2 us and 10 ns per
+// k-tile for each sixteen of them, and no less than 0.3 us per k-tile.  (1024 x 6528 by 2304 rows, 36 tiles: 70 (52 in parts) and
+// 38 us; 2048 x 1920 by 4352, 136 tiles: 34 and 51; 2048 x 1152 by 2048, 64 tiles: 32 and 24; 2048 x 15104 by 2048: 142 (81) and 97.)
+// `single`: a product of its own, whose last round may be cut.  margin: percent by which the large tiles have to be better.
+__host__ __device__ inline bool small_tiles_win(int64_t tiles, int64_t pairs, int64_t ktiles, bool single, int margin) {
+    const int64_t walk = 300 * ktiles, work = pairs * (200 + 10 * ktiles) / kChunkPairs;
+    const int64_t small = 6000 + (walk > work ? walk : work);
+    const bool parts = single && tiles <= 256 && split_parts(tiles, ktiles) > 1;
+    const int64_t large = parts ? 20000 + 520 * ktiles : (tiles + 255) / 256 * (16000 + 1150 * ktiles);
+    return small * 100 < large * (100 + margin);
 }
 
 // Waits until a kernel on `st` has written `want` to a word of pinned memory (behind the data that goes with it).  The host

@@ -105,7 +105,6 @@ __device__ __forceinline__ void place_tile(int logical, int mtiles, int ntiles, 
 // workgroup each.  All workgroups of an XCD still walk the contraction side by side, which is what lets its L2 serve them:
 // dealing tiles x k-tiles out in equal stretches, every CU at a k-tile of its own, left no CU idle and was slower for all
 // that (344 -> 411 us at 4096 x 8228 x 11013).
-constexpr int kXcdCus = 32;
 struct Piece {
     int tile, ka, kb;  // tile of the XCD's order, its k-tiles [ka, kb)
     int parts, slot;   // parts of the tile; where they meet (slot, slot + 1, ... for the sums of all but the last)
@@ -850,9 +849,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_f6_kernel(const GemmArgs
 // per CU cover it better than two stages per wave and one workgroup (21 -> 13 us at 1000 x 1031 x 777, b = 6), and fragments
 // loaded straight into registers, 64 bytes per lane and row, took twice as long (every load touches 64 lines).
 // 256 x 256 x 256: 90 -> 10 us; 16 rows against 11008 x 4096 weights 83 -> 35; 1000 x 1031 x 777, b = 6: 75 -> 14.
-// The planner lays rows of B out in chunks of 64 for products that may come here (Plan::chunkB).
+// The planner lays rows of B out in chunks of 64 for products that it expects here (PlanHeader::chunkB).
 constexpr int kSmallWaves = 4, kSmallThreads = 64 * kSmallWaves;
-constexpr int kChunkPairs = (kTile / kChunk) * (kTile / kChunk);  // 64 x 64 tiles in one of 256 x 256
 constexpr int kSmallPitch = 72;  // the two half-waves of an accumulator register sit four rows apart: 32 banks
 constexpr int kSmallMeta = 2 * kChunk * (int)sizeof(int32_t);  // a word per source row and per source column of the chunk pair
 constexpr int kSmallFold = kChunk * kSmallPitch * (int)sizeof(int32_t);
@@ -1227,28 +1225,9 @@ static void fused_args(GemmArgs &g, const Plan *p) {
     g.fold_f64 = 31 + p->sh * ((h.lmaxA - 1) + (h.lmaxB - 1)) <= 52;
 }
 
-// Into how many parts the tiles of the last round are cut (1: not at all): where at most half of the CUs would work on it and
-// the contraction is long enough.  Cut in four, the round is not four times as fast (CUs that share L2 and power walk
-// slower, and 256 KiB of sums change hands per part): 4096 x 8448 by 8448 rows, 66 k-tiles: 402 -> 381 us; 17408 rows,
-// 96 k-tiles of six-bit digits: 518 -> 493; 2048 x 15104 by 2048, 118 k-tiles: 140 -> 81; 3072 x 6144 by 6400, 48: 138 -> 125;
-// but 32 k-tiles: 430 -> 434, 19: 37 -> 42.  In eight parts none was faster than in four.
-static int split_parts(int64_t tiles, int64_t ktiles) {
-    const int64_t m = (tiles + 7) / 8 % kXcdCus;
-    if (m == 0 || m > kXcdCus / 2 || ktiles < 48) return 1;
-    return (int)std::min<int64_t>(kXcdCus / m, 4);
-}
-
-// Whether 64 x 64 tiles are the better ones for `tiles` tiles of 256 x 256, of which `pairs` chunk pairs hold anything, with
-// `ktiles` k-tiles each, from what either kernel measured (nanoseconds): a 256 x 256 tile takes 16 us and 1.15 us per k-tile, 256
-// of them at a time (one round of tiles in parts: 20 us and 0.52 us per k-tile); the small tiles take 0.2 us and 10 ns per
-// k-tile for each sixteen of them, and no less than 0.3 us per k-tile.  (1024 x 6528 by 2304 rows, 36 tiles: 70 (52 in parts) and
-// 38 us; 2048 x 1920 by 4352, 136 tiles: 34 and 51; 2048 x 1152 by 2048, 64 tiles: 32 and 24; 2048 x 15104 by 2048: 142 (81) and 97.)
+// Whether the small tiles are the better ones for this plan (and B's rows are laid out for them).
 static bool small_tiles(const Plan *p, int64_t tiles, int64_t pairs, int64_t ktiles) {
-    if (p->chunkB != kChunk) return false;
-    const int64_t small = 6000 + std::max(300 * ktiles, pairs * (200 + 10 * ktiles) / kChunkPairs);
-    const bool parts = p->nitems == 1 && tiles <= 256 && split_parts(tiles, ktiles) > 1;
-    const int64_t large = parts ? 20000 + 520 * ktiles : (tiles + 255) / 256 * (16000 + 1150 * ktiles);
-    return small < large;
+    return p->hdr.chunkB == kChunk && small_tiles_win(tiles, pairs, ktiles, p->nitems == 1, 0);
 }
 // The chunk pairs of an unpacked product that hold source rows.
 static int64_t chunk_pairs(const PlanHeader &h) {

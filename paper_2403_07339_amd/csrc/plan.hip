@@ -1037,7 +1037,7 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
     }
     if (threadIdx.x == 0 && slice == 0) {
         if (operand == 0) { hdr->Mp = Mp; hdr->mtiles = ntiles; hdr->lmaxA = lmax; }
-        else { hdr->Np = Mp; hdr->ntiles = ntiles; hdr->lmaxB = lmax; }
+        else { hdr->Np = Mp; hdr->ntiles = ntiles; hdr->lmaxB = lmax; hdr->chunkB = chunk; }
     }
 }
 
@@ -1695,9 +1695,17 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     // where the small-tile GEMM may be the one to run
     if (bx < slA)
         rows_layout(rowA, n, &hdr->n_u, layA, cap_physA, cap_physA / kTile + 2, tmpPA, hdr, 0, kChunk, lds, fast_lds ? fast_rows : nullptr, bx, slA);
-    else if (bx < slA + slB)
+    else if (bx < slA + slB) {
+        // (chunk by chunk a few more rows of B are padding, which may cost a round of the large tiles: 2000 x 2000 x 2000 with
+        // entries of three digits, un-fused: 272 tiles instead of 256, 944 us, 682 so.  Only the unpacked sizes tell: rows and k-tiles
+        // without their padding, and a margin for it.)
+        if (chunkB == kChunk && gridDim.y == 1) {
+            auto up = [](int x, int by) { return (int64_t)((x + by - 1) / by); };
+            const int nu = hdr->n_u, hu = hdr->h_u;
+            if (!small_tiles_win(up(nu, kTile) * up(hu, kTile), up(nu, kChunk) * up(hu, kChunk), up(hdr->d_u, kKPad), true, 25)) chunkB = kTile;
+        }
         rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr, bx - slA, slB);
-    else {
+    } else {
         const int part = bx - slA - slB;
         const bool in_lds = hdr->d_u <= kColSlotsLds * kPlanThreads;
         if (in_lds && part > 0) return;
@@ -1943,7 +1951,7 @@ __device__ bool keep_decide(const KeepArgs &k, const SlotSet &c1, PlanHeader *hd
             const PlanHeader &o = ks->saved;
             hdr->h_u = o.h_u; hdr->d_u = o.d_u; hdr->nobB = o.nobB; hdr->edgesB = o.edgesB; hdr->extras = o.extras;
             hdr->Np = o.Np; hdr->Kp = o.Kp; hdr->KA = o.KA; hdr->ldA = o.ldA; hdr->ldB = o.ldB;
-            hdr->ntiles = o.ntiles; hdr->lmaxB = o.lmaxB; hdr->ngroups = o.ngroups; hdr->nruns = o.nruns;
+            hdr->ntiles = o.ntiles; hdr->lmaxB = o.lmaxB; hdr->chunkB = o.chunkB; hdr->ngroups = o.ngroups; hdr->nruns = o.nruns;
         } else if (h) {
             hdr->h_u = h;
         }

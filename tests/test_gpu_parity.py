@@ -1049,6 +1049,24 @@ def test_layouts_around_the_sizes_where_they_change(imu, n, d, h, b, sa, sb, kin
     check_against_oracle(imu, Aq, Bq, b, sa, sb)
 
 
+@pytest.mark.parametrize("n,d,h,tiles_b,parts", [(2000, 600, 2000, 24, 1), (300, 600, 300, 4, 0)])
+def test_rows_of_b_are_laid_out_for_the_tiles_that_run(imu, n, d, h, tiles_b, parts):
+    """Three digit levels in every row of both operands: 6000 unpacked rows of B fill 24 tiles of 256 (25 if no row may
+    straddle 64), which the large tiles take; 900 rows go to the small ones."""
+    rng = np.random.default_rng(n)
+    Aq, Bq = (rng.integers(-127, 128, size=(r, d)).astype(np.int32) for r in (n, h))
+    Aq[np.arange(n), rng.integers(0, d, n)] = 128 * 128 + 5
+    Bq[np.arange(h), rng.integers(0, d, h)] = -128 * 128 - 7
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    plan = imu.imunpack_plan(Qa, Qb, 8, ROW, ROW)
+    assert plan.layout()[1][0] == tiles_b * 256
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+    imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None, fuse=True)
+    assert imu.imunpack_diag_gemm_parts(plan) == parts
+    assert np.array_equal(C_int.cpu().numpy(), oracle.int_gemm(Aq, Bq))
+
+
 def _product_in_parts(n, d, h, b, strategies, every):
     """Operands of a product with a long contraction: `every` splits each column of A (two exponent groups of the same
     width), else a few columns and, under UnpackRow, most rows."""
