@@ -471,9 +471,9 @@ static int sel_launch(const SelArgs &a, int nops, hipStream_t st) {
     if (most > (unsigned)kSmall) {
         // one workgroup per CU at most (every workgroup merges its histogram with atomics on the same counters); a piece is one
         // entry where four cannot be loaded together
-        unsigned pieces = 0;
-        for (int q = 0; q < nops; ++q) pieces = std::max(pieces, a.op[q].kind <= 1 ? a.op[q].N / 4 : a.op[q].N);
-        const unsigned blocks = std::min(256u, (pieces + kSelThreads * kItems - 1) / (kSelThreads * kItems));
+        int64_t pieces = 0;
+        for (int q = 0; q < nops; ++q) pieces = std::max<int64_t>(pieces, a.op[q].kind <= 1 ? a.op[q].N / 4 : a.op[q].N);
+        const unsigned blocks = (unsigned)std::min<int64_t>(256, (pieces + kSelThreads * kItems - 1) / (kSelThreads * kItems));
         hipLaunchKernelGGL(select_count_kernel<0>, dim3(blocks, y), dim3(kSelThreads), 0, st, a);
         hipLaunchKernelGGL(select_count_kernel<1>, dim3(blocks, y), dim3(kSelThreads), 0, st, a);
         hipLaunchKernelGGL(select_count_kernel<2>, dim3(blocks, y), dim3(kSelThreads), 0, st, a);

@@ -990,6 +990,18 @@ def test_percentile_windows(imu, rows, cols, kind):
     assert int(status.item()) == 1
 
 
+def test_percentile_of_nearly_four_billion_entries(imu):
+    """Just below the 2^32 entries that the call takes, read one by one: three rows that overlap but for an entry."""
+    cols = (2 ** 32 - 1) // 3 - 3
+    x = torch.arange(cols + 2, dtype=torch.int32, device="cuda").remainder_(1000).to(torch.float32)
+    view = torch.as_strided(x, (3, cols), (1, 1))
+    alpha, status = imu.imunpack_percentile(view, 95.0)
+    k = int(np.ceil(95.0 * 3 * cols / 100.0))
+    upto = lambda i: i // 1000 * np.arange(1, 1001) + np.minimum(np.arange(1, 1001), i % 1000)   # entries <= 0 .. 999 of the first i
+    counts = sum(upto(r + cols) - upto(r) for r in range(3))
+    assert int(status.item()) == 0 and int(alpha.item()) == int(np.searchsorted(counts, k))
+
+
 @pytest.mark.parametrize("b,strategies", [(8, (ROW, ROW)), (8, (COL, BOTH)), (4, (ROW, COL)), (3, (COL, ROW)), (8, (BOTH, BOTH))])
 @pytest.mark.parametrize("n,d,h", [(1, 1, 1), (33, 127, 65), (64, 513, 64), (257, 640, 31), (300, 1500, 250), (2050, 130, 1990)])
 def test_gemm_tiles_of_either_size(imu, n, d, h, b, strategies):
