@@ -101,9 +101,9 @@ struct PlanHeader {
 // What a plan in keep-weights mode remembers of the plan before it, on the device: the column unpacking of
 // the first operand that the second operand's unpacking was computed for, and the header fields that unpacking left.
 struct KeepState {
-    int32_t valid, d1, diff, same;
+    int32_t valid, d1, same;
     int32_t h_u, d_u, nobB, edgesB, extras;
-    int32_t pad_[7];
+    int32_t pad_[8];
     PlanHeader saved;  // the header as that plan left it: the layout of the second operand and of the columns
 };
 

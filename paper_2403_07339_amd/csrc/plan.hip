@@ -161,7 +161,7 @@ __global__ void setup_kernel(PlanHeader *hdr, SlotSet a, int na, SlotSet c, int 
             reinterpret_cast<int32_t *>(hdr)[i] = 0;
         __syncthreads();
         if (threadIdx.x == 0) {
-            if (ks) ks->diff = ks->same = 0;
+            if (ks) ks->same = 0;
             if (na) hdr->n_u = na;
             if (nb) hdr->h_u = nb;
             if (nc) hdr->d1 = nc;
@@ -380,7 +380,8 @@ __device__ __forceinline__ unsigned long long pack_edge(int row, int col, int le
 // digits), whose count then competes.  Hence:
 //   - if no entry has three or more digits, one batch takes all rows with count >= top column count
 //     (or all columns with count > top row count);
-//   - otherwise a batch takes only the slots that share the top count.
+//   - otherwise a batch takes the slots that share the top count; with the edges in LDS, where the most such entries that any
+//     slot of either side holds are counted once, every slot whose count exceeds that (greedy_run: deep_row, deep_col).
 // The starting counts are the operand's scan statistics.  After UnpackA the matrix B_e repeats column
 // k of B once per column slot that descends from k (Alg. 2 line 6 / Alg. 4 line 13): such a slot
 // starts with the count of column k, and every OB entry (j, k) adds one to row j per extra slot
@@ -2031,7 +2032,7 @@ __global__ __launch_bounds__(kPlanThreads) void keep_plan_kernel(KeepPlan f) {
         for (int x = threadIdx.x; x < f.n; x += kPlanThreads) identity_slot(f.rows, x);
     __syncthreads();
     if (threadIdx.x == 0) {
-        f.keep.ks->diff = f.keep.ks->same = 0;
+        f.keep.ks->same = 0;
         if (f.strategy != IMUNPACK_ROW) hdr->n_u = f.n;
         if (f.strategy != IMUNPACK_COL) hdr->d1 = f.d;
         if (f.strategyB != IMUNPACK_ROW) hdr->h_u = f.h;
