@@ -44,6 +44,17 @@ def profiled_traffic(workload: int, digits: str = "int8"):
     return out, os.path.relpath(path, ROOT)
 
 
+def gemm_kernel(imu, plan):
+    """The kernel that the plan's last GEMM ran."""
+    fp6 = plan.digits() == imu.DIGITS_FP6
+    if not plan.fusable():
+        return "gemm_f6_kernel<1>" if fp6 else "gemm_i8_kernel<1>"
+    parts = imu.imunpack_diag_gemm_parts(plan)
+    if parts == 1:
+        return "gemm_f6_kernel<0>" if fp6 else "gemm_i8_kernel<0>"
+    return f"gemm_small_kernel<{str(fp6).lower()}, false>" if parts == 0 else f"gemm_split_kernel<{str(fp6).lower()}>"
+
+
 def cpu_baseline(w, budget_rows: int = 4096):
     """The CPU oracle (unchanged, untuned) on a bounded sample of the same workload: RTN of both
     operands, the unpack of the full operands (Alg. 5), then the naive int64 GEMM and the fp64
@@ -292,6 +303,7 @@ def main():
     achieved = gemm_ops / (gemm_ms * 1e-3) / 1e12
     value = w.ops / (ms_step * 1e-3) / 1e12
     traffic, traffic_file = profiled_traffic(args.workload, args.digits)
+    kernel = gemm_kernel(imu, plan)
     # algorithmic bytes per launch of the memory-bound passes: quantize + scan moves 4 B in and 4 B out
     # per element; the scatter reads 4 B per source element and owes 1 B per element of the unpacked
     # operands (n' d' + h' d'), of which it stores fewer (repeated columns of A_ue are not stored)
@@ -321,9 +333,9 @@ def main():
         "stage_ms": {"quantize+scan": stage_ms[0], "plan": stage_ms[1], "scatter": stage_ms[2],
                      "gemm+recombine+dequant": gemm_ms, "host_gap": ms_step_marked - sum(stage_ms),
                      "step_with_event_marks": ms_step_marked},
-        "roofline": {"bound": "mfma", "kernel": "gemm_f6_kernel<0>" if fp6 else "gemm_i8_kernel<0>", "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": kernel, "achieved": achieved,
                      "peak": mfma_peak, "unit": "TOP/s", "frac": achieved / mfma_peak,
-                     "traffic": traffic.get("gemm_f6_kernel" if fp6 else "gemm_i8_kernel"), "ms": gemm_ms, "ops": gemm_ops,
+                     "traffic": traffic.get(kernel.split("<")[0]), "ms": gemm_ms, "ops": gemm_ops,
                      "algorithmic_bytes": float(ba + bb + 4 * n * h + (8 * n * h if args.with_int64 else 0))},
         "roofline_passes": {
             "quantize+scan": hbm_entry(["qscan_vec_pair_kernel", "qscan_vec_kernel", "qscan_tr_kernel", "qscan_tile_kernel", "zero_lists_kernel"],
@@ -409,7 +421,7 @@ def main():
         ms6 = (time.perf_counter() - t0) * 1e3 / args.steps
         gemm6 = sum(e[4].elapsed_time(e[5]) for e in ev6) / args.steps
         out["fp6_digits_step"] = {"ms_per_step": ms6, "value": w.ops / (ms6 * 1e-3) / 1e12, "unit": "TOPS",
-                                  "gemm_ms": gemm6, "gemm_kernel": "gemm_f6_kernel<0>",
+                                  "gemm_ms": gemm6, "gemm_kernel": gemm_kernel(imu, plan),
                                   "gemm_frac_of_fp6_peak": gemm_ops / (gemm6 * 1e-3) / 1e12 / FP6_PEAK_TOPS,
                                   "stored_bytes": dict(zip(("A_store", "B_eu"), plan.unpacked_bytes()[:2])),
                                   "note": "same step, digits as e2m3 codes (96 bytes per 128 columns) on "
