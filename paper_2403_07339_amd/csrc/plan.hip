@@ -263,8 +263,14 @@ __device__ void level_major(const SlotSet &set, const int32_t *maxabs, const int
                 const unsigned long long m = __ballot(f);
                 const int slot = run + __popcll(m & below);
                 run += __popcll(m);
-                if (!f || slot >= set.cap) continue;
+                if (!f) continue;
                 const int prev = last[u];
+                if (slot >= set.cap) {  // the plan is made again with more room; until then the chain ends here (ob_copy walks it
+                                        // before the host hears of it: no link may be left unwritten)
+                    set.time[prev] = kNever;
+                    set.child[prev] = -1;
+                    continue;
+                }
                 set.root[slot] = x0 + 64 * u;
                 set.exp[slot] = l;
                 set.key[slot] = ((unsigned long long)l << 48) | (unsigned)prev;

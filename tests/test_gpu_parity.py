@@ -1061,6 +1061,33 @@ def test_layouts_around_the_sizes_where_they_change(imu, n, d, h, b, sa, sb, kin
     check_against_oracle(imu, Aq, Bq, b, sa, sb)
 
 
+@pytest.mark.parametrize("b,depth", [(6, 3), (8, 2), (2, 5)])
+def test_columns_that_outgrow_their_room_before_an_unpack_both(imu, b, depth):
+    """UnpackColumn on A appends more columns than the plan has room for at first, UnpackBoth on B follows the links from a
+    column to its copies before the plan is made again; in an arena that other plans have written all over."""
+    s = 1 << (b - 1)
+    rng = np.random.default_rng(b)
+    plan = imu.Plan()
+    for n, d, h in ((900, 300, 800), (40, 460, 39)):
+        Aq, Bq = (rand_ints(rng, r, d, s, 0.01, 2) for r in (n, h))
+        big = d == 460
+        if big:
+            Aq[3] = s ** depth * rng.choice([-1, 1], d)         # every column has depth + 1 levels
+        Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+        sa = COL if big else BOTH
+        imu.imunpack_plan(Qa, Qb, b, sa, BOTH, plan=plan)
+        hnd = oracle.unpack_pair_handle(Aq, Bq, b, sa, BOTH)
+        assert plan.dims()[:3] == (hnd.n_u, hnd.d_u, hnd.h_u)
+        if big:
+            assert plan.dims()[1] > 2 * d + 256                 # more than the first guess
+        hnd.close()
+        A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+        C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+        ws = torch.empty(plan.unpacked_bytes()[2] // 8, dtype=torch.int64, device="cuda")
+        imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, ws, fuse=True)
+        assert np.array_equal(C_int.cpu().numpy(), oracle.int_gemm(Aq, Bq))
+
+
 @pytest.mark.parametrize("n,d,h,tiles_b,parts", [(2000, 600, 2000, 24, 1), (300, 600, 300, 4, 0)])
 def test_rows_of_b_are_laid_out_for_the_tiles_that_run(imu, n, d, h, tiles_b, parts):
     """Three digit levels in every row of both operands: 6000 unpacked rows of B fill 24 tiles of 256 (25 if no row may
