@@ -1185,11 +1185,13 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
 // product, 70 to 170 us for the items of a batch; this one: 14 to 37 and 14 to 16).  Here every slot stays in the registers of its thread.  A column slot is
 // known by its original column k and its levels eA, eB along A and B, and no two slots share all three; so the slots are a
 // bit per k in a mask per (eA, eB), every rank is a count of bits below k, and the columns of both stores are put together
-// in LDS and written once.  Returns false, having written nothing but tables that are written again, if LDS is too small.
+// in LDS and written once, by part 0.  Returns false, having written nothing but tables that are written again, if LDS is too
+// small: the same in every part, so that all of them take the general path (many pairs of levels: 300 x 9000 by 300 at b = 2
+// with eight levels on either side, a plan of 204 us in eight parts, 312 in one).
 constexpr int kColSlotsLds = 12;  // slots per thread: as many as the registers of a 1024-thread workgroup hold
 template <int kSlots>
 __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColLayout &cols, int d, int cap_phys, int s, int sh,
-                                PlanHeader *hdr, ColTables &t, int32_t *dyn, int dyn_words) {
+                                PlanHeader *hdr, ColTables &t, int32_t *dyn, int dyn_words, int part) {
     const int D = hdr->d_u, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (D > kSlots * kPlanThreads) return false;
     for (int x = tid; x < kMaxGroups * kMaxLevelsA; x += kPlanThreads) t.hist2[x] = 0;
@@ -1224,6 +1226,11 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     __syncthreads();
     const int LA = t.la + 1, LB = t.lb + 1, W = (d + 63) / 64;
     if (LA > kMaxLevelsA || LA + LB - 1 > kMaxGroups || (long long)LA * LB * W * 3 > dyn_words) return false;
+    if (part > 0) {  // where it is certain to fit (see below for what has to), the other parts need not find out
+        const int appended = D - d, pads = kKPad * (LA * LB + LA + LB);
+        const int kp = d + appended + appended / 7 + pads, ka = hdr->d1 + appended + pads;
+        if (kp <= 256 * kKPad && appended + pads <= 256 * kKPad && LA * LB * W * 3 + kp + ka <= dyn_words) return true;
+    }
     unsigned long long *mask = reinterpret_cast<unsigned long long *>(dyn);  // [LA * LB][W]
     int32_t *pre = dyn + 2 * LA * LB * W;                                     // [LA * LB][W] slots of the pair below the word
     int32_t *packB = pre + LA * LB * W;                                       // k | eB << 24 per column of B_eu, -1: none
@@ -1270,11 +1277,12 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     __syncthreads();
     if (tid == 0) level_bases(t);
     __syncthreads();
-    column_tables(t, cap_phys, D, s, sh, hdr, true);
+    column_tables(t, cap_phys, D, s, sh, hdr, part == 0);
     __syncthreads();
     const int Kp = t.kp, KA = t.ka, ka_levels = t.ka_levels;
     if (Kp > cap_phys) return true;  // reported: the plan is made again with more room
     if (Kp > 256 * kKPad || KA - ka_levels > 256 * kKPad || (long long)LA * LB * W * 3 + Kp + KA > dyn_words) return false;
+    if (part > 0) return true;
     int32_t *packA = packB + Kp;  // k | eA << 24 per stored column of A, -1: none
     for (int x = tid; x < Kp + KA; x += kPlanThreads) packB[x] = -1;
     __syncthreads();
@@ -1667,8 +1675,8 @@ __global__ __launch_bounds__(256) void publish_kernel(const PlanHeader *hdr, Pla
     publish_header(hdr + blockIdx.y, host + blockIdx.y, seq);
 }
 
-// One to four workgroups for the rows of A, as many for the rows of B, one for the columns (kColBlocks where there may be more column
-// slots than that one holds).
+// One to four workgroups for the rows of A, as many for the rows of B, kColBlocks for the columns (all but one of them idle unless
+// there are more column slots or pairs of levels than that one can hold; one for each item of a batch).
 __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     SlotSet rowA, int n, RowLayout layA, int cap_physA, int32_t *tmpPA, SlotSet rowB, int h, RowLayout layB,
     int cap_physB, int32_t *tmpPB, SlotSet c1, SlotSet c2, ColLayout cols, int d, int cap_physC, int s, int sh,
@@ -1714,11 +1722,9 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
         rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr, bx - slA, slB);
     } else {
         const int part = bx - slA - slB;
-        const bool in_lds = hdr->d_u <= kColSlotsLds * kPlanThreads;
-        if (in_lds && part > 0) return;
-        if (!in_lds || !cols_layout_lds<kColSlotsLds>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words)) {
+        if (!cols_layout_lds<kColSlotsLds>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part)) {
             __syncthreads();
-            cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, part, in_lds ? 1 : (int)gridDim.x - slA - slB, tables);
+            cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, part, (int)gridDim.x - slA - slB, tables);
         }
         if (part == 0 && threadIdx.x == 0) hdr->bound[0] = hdr->bound[1] = 0;
     }
@@ -2185,7 +2191,8 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
     const int fast_lds = fast_bytes <= (size_t)kLayoutLdsMax ? 1 : 0;
     // the column layout: a word per column of either store, three per 64 original columns and pair of levels (sixteen pairs)
     const size_t col_bytes = ((size_t)2 * (p->cap[CAP_C2] + 2048) + (size_t)48 * ((d + 63) / 64)) * sizeof(int32_t);
-    const size_t dyn_bytes = std::min((size_t)kLayoutLdsMax, std::max(fast_lds ? fast_bytes : 0, col_bytes));
+    // (a batch leaves LDS to the items beside it)
+    const size_t dyn_bytes = items == 1 ? (size_t)kLayoutLdsMax : std::min((size_t)kLayoutLdsMax, std::max(fast_lds ? fast_bytes : 0, col_bytes));
     static std::atomic<int> opted_in{0};  // the attributes are idempotent: a race sets the same values twice
     if (!opted_in.load(std::memory_order_acquire)) {
         IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
@@ -2271,7 +2278,7 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
         IMU_TRY(run_greedy(p, 2, p->ob, p->cap[CAP_OB], p->obcnt, stride, CAP_OB, st, skip));
     }
     // ---- physical layouts
-    const int col_blocks = p->cap[CAP_C2] <= kColSlotsLds * kPlanThreads ? 1 : kColBlocks;
+    const int col_blocks = items > 1 && p->cap[CAP_C2] <= kColSlotsLds * kPlanThreads ? 1 : kColBlocks;
     const int slices = fast_lds ? row_slices(n) + row_slices(h) : 2;
     hipLaunchKernelGGL(layouts_kernel, dim3(slices + col_blocks, items), dim3(kPlanThreads), dyn_bytes, st, p->rowA, n, p->layA,
                        phys_cap_rows(p->cap[CAP_ROWA]), p->tmpPA, p->rowB, h, p->layB,

@@ -1044,6 +1044,8 @@ def test_gemm_tiles_of_either_size(imu, n, d, h, b, strategies):
     (5, 6140, 7, 8, COL, COL, "every"),     # just as many as it does
     (9, 8192, 6, 4, COL, COL, "deep"),      # many pairs of levels
     (40, 600, 33, 2, COL, COL, "deep"),
+    (20, 9000, 30, 2, COL, COL, "pairs"),   # few column slots, but more pairs of levels than LDS holds masks for
+    (20, 4096, 30, 2, COL, COL, "pairs"),   # ... and just not too many
     (30, 4100, 20, 8, BOTH, BOTH, "deep"),
     (4097, 40, 9000, 8, ROW, ROW, "every"),  # rows shared by two and three workgroups
     (16385, 8, 18000, 4, ROW, COL, "deep"),  # more rows than registers and LDS hold
@@ -1056,6 +1058,11 @@ def test_layouts_around_the_sizes_where_they_change(imu, n, d, h, b, sa, sb, kin
         Aq, Bq = (rng.integers(-(s * s - 1), s * s, size=(r, d)).astype(np.int32) for r in (n, h))
     elif kind == "deep":
         Aq, Bq = (rand_ints(rng, r, d, s, 0.3 if b != 8 else 0.002, 4 if b > 2 else 9) for r in (n, h))
+    elif kind == "pairs":
+        Aq, Bq = (rng.integers(-(s - 1), s, size=(r, d)).astype(np.int32) for r in (n, h))
+        for M in (Aq, Bq):  # columns of one to eight levels
+            cols = rng.permutation(d)[:24]
+            M[3, cols] = s ** (np.arange(24) % 8)
     else:
         Aq, Bq = (rand_ints(rng, r, d, s, 0.001, 2) for r in (n, h))
     check_against_oracle(imu, Aq, Bq, b, sa, sb)
