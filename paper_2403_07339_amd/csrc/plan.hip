@@ -1702,7 +1702,8 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
         tmpR = item_at(tmpR, off);
         tmpOff = item_at(tmpOff, off);
     }
-    if (hdr->overflow) return;
+    // (asked once for all waves: another workgroup of this launch may be reporting an overflow of its own just now)
+    if (__syncthreads_or(load_agent(&hdr->overflow))) return;
     const int slA = fast_lds ? row_slices(n) : 1, slB = fast_lds ? row_slices(h) : 1;
     const int bx = (int)blockIdx.x;
     if (bx >= slA && skipB && *skipB) return;  // keep-weights mode: these layouts stand as they are
