@@ -47,6 +47,7 @@ static inline bool capturing(hipStream_t st) {
 constexpr int kTile = 256;       // GEMM output tile edge in unpacked rows (both operands)
 constexpr int kChunk = 64;       // physical rows the GEMM epilogue holds at a time; no source row straddles a chunk
 constexpr int kChunkPairs = (kTile / kChunk) * (kTile / kChunk);  // 64 x 64 tiles in one of 256 x 256
+constexpr int kEvenStep = 32;    // from level to level of an evenly laid out row of B: a column block of the matrix instruction
 constexpr int kXcdCus = 32;      // CUs of an XCD
 constexpr int kKPad = 128;       // every exponent group is padded to a multiple of this many columns
 constexpr int kMaxGroups = 64;   // distinct diagonal entries of S the planner supports
@@ -94,6 +95,9 @@ struct PlanHeader {
     int32_t extras;                  // edges that the repeated columns of B_e add to B's OB entries (UnpackBoth on B)
     int32_t reusedB;                 // the second operand's unpacking was taken over from the plan before (keep-weights mode)
     int32_t chunkB;                  // no source row of B straddles that many physical rows: kTile, or kChunk for small products
+    int32_t evenA;                   // 2, 4: every source row of A has that many physical rows side by side (some of them padding)
+    int32_t evenB;                   // 2, 4: every source row of B has that many physical rows (some of them padding), kEvenStep apart;
+                                     // 0: its levels lie one behind the other
     int32_t seq;                     // in the host's copy: which plan's header it holds
     unsigned long long bound[2];     // max over rows of sum_c s^e(c) |digit| for A_ue, B_eu
 };
@@ -119,6 +123,7 @@ struct RowLayout {
     int32_t *tile_src0;   // [tiles+1] first source row of each tile
     int32_t *chunk_src0;  // [4 tiles+1] first source row of each chunk of kChunk physical rows
     int32_t *tile_flat;   // [tiles]   1 if every source row of the tile has a single level
+    int32_t *chunk_lev;   // [4 tiles] (A) how many levels every source row of the chunk has, 0 if they differ
     // weighted L1 norm  sum_c s^e(c) |digit|  per physical row, in pieces: what the fix-up pass placed
     // (cleared by the planner) and one partial sum per wave of the scatter kernel
     unsigned long long *rowsum;   // [Mp]
@@ -169,6 +174,7 @@ __host__ __device__ __forceinline__ void move_to_item(RowLayout &l, int64_t off)
     l.prow = item_at(l.prow, off);
     l.row_phys = item_at(l.row_phys, off); l.src_pstart = item_at(l.src_pstart, off); l.src_nlev = item_at(l.src_nlev, off);
     l.tile_src0 = item_at(l.tile_src0, off); l.chunk_src0 = item_at(l.chunk_src0, off); l.tile_flat = item_at(l.tile_flat, off);
+    l.chunk_lev = item_at(l.chunk_lev, off);
     l.rowsum = item_at(l.rowsum, off); l.wavesum = item_at(l.wavesum, off);
 }
 __host__ __device__ __forceinline__ void move_to_item(ColLayout &c, int64_t off) {
@@ -334,16 +340,19 @@ __host__ __device__ inline int split_parts(int64_t tiles, int64_t ktiles) {
 }
 
 // Whether 64 x 64 tiles are the better ones for `tiles` tiles of 256 x 256, of which `pairs` chunk pairs hold anything, with
-// `ktiles` k-tiles each, from what either kernel measured (nanoseconds): a 256 x 256 tile takes 16 us and 1.15 us per k-tile, 256
+// `ktiles` k-tiles each, from what either kernel measured (nanoseconds): a 256 x 256 tile takes 14 us and 1.05 us per k-tile, 256
 // of them at a time (one round of tiles in parts: 20 us and 0.52 us per k-tile); the small tiles take 0.2 us and 10 ns per
-// k-tile for each sixteen of them, and no less than 0.3 us per k-tile.  (1024 x 6528 by 2304 rows, 36 tiles: 70 (52 in parts) and
-// 38 us; 2048 x 1920 by 4352, 136 tiles: 34 and 51; 2048 x 1152 by 2048, 64 tiles: 32 and 24; 2048 x 15104 by 2048: 142 (81) and 97.)
+// k-tile for each sixteen of them, and no less than 0.3 us per k-tile.  (1024 x 1664 by 2048 rows, 32 tiles: 27 and 12 us;
+// 2048 x 1152 by 2048, 64 tiles: 28 and 24; 3072 x 1920 by 2048, 96 tiles: 29 and 32; 3840 x 1024 by 2048, 120 tiles: 22 and 30;
+// 4096 x 1920 by 2048, 128 tiles: 31 and 42; 2048 x 15104 by 2048: 81 in parts and 96; 3328 x 4608 by 768, 39 tiles: 51 and 29.)
 // `single`: a product of its own, whose last round may be cut.  margin: percent by which the large tiles have to be better.
-__host__ __device__ inline bool small_tiles_win(int64_t tiles, int64_t pairs, int64_t ktiles, bool single, int margin) {
+// tile_ns: what a tile takes besides its walk, kTileNs where its results go out from the registers.
+constexpr int kTileNs = 14000;
+__host__ __device__ inline bool small_tiles_win(int64_t tiles, int64_t pairs, int64_t ktiles, bool single, int margin, int tile_ns = kTileNs) {
     const int64_t walk = 300 * ktiles, work = pairs * (200 + 10 * ktiles) / kChunkPairs;
     const int64_t small = 6000 + (walk > work ? walk : work);
     const bool parts = single && tiles <= 256 && split_parts(tiles, ktiles) > 1;
-    const int64_t large = parts ? 20000 + 520 * ktiles : (tiles + 255) / 256 * (16000 + 1150 * ktiles);
+    const int64_t large = parts ? tile_ns + 6000 + 520 * ktiles : (tiles + 255) / 256 * (tile_ns + 1050 * ktiles);
     return small * 100 < large * (100 + margin);
 }
 

@@ -26,8 +26,6 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef long v2l __attribute__((ext_vector_type(2)));
 typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any float boundary
 typedef long v2l_u __attribute__((ext_vector_type(2), aligned(8)));
 
@@ -72,6 +70,7 @@ struct GemmArgs {
     // split: two words per meeting point (arrivals, how many have left their sums), and the sums of those that came first
     int32_t *meet, *sums;
     int most_parts;
+    int evenB;                // PlanHeader::evenB
     int lmaxA;                // largest number of digit levels of a row of A
     int kwaves;               // gemm_small_kernel: waves that share the contraction
     // benchmark reporting: if set, workgroup 0 writes {shader clock ticks, 100 MHz wall ticks} of its K loop
@@ -139,6 +138,22 @@ __device__ __forceinline__ void dma16(unsigned lds_addr, unsigned voff, const in
                  : "s"(lds_addr), "v"(voff), "s"(gbase)
                  : "memory");
 }
+
+// (double)x by way of its bits: a conversion takes four times as long as an addition in binary64.
+__device__ __forceinline__ double exact_f64(int x) { return __hiloint2double(0x43300000, x ^ (int)0x80000000) - 4503601774854144.0 /* 2^52 + 2^31 */; }
+// One word at `off` bytes from the base, dropped by the hardware if that is not below the resource's size.
+template <bool NT>
+__device__ __forceinline__ void store_inside(float v, __amdgpu_buffer_rsrc_t to, unsigned off) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), to, (int)off, 0, NT ? 2 : 0);
+}
+// The same for four, 16 bytes at any boundary; non-temporal: a wave writes a contiguous kilobyte.
+__device__ __forceinline__ void store_inside4(const float (&f)[4], __amdgpu_buffer_rsrc_t to, unsigned off) {
+    v4i x;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = __float_as_int(f[k]);
+    __builtin_amdgcn_raw_buffer_store_b128(x, to, (int)off, 0, 2);
+}
+constexpr unsigned kOutside = 0x80000000u;  // an offset that stays outside with the offset of a row (below 2^30) added
 
 __device__ __forceinline__ const int8_t *uniform_ptr(const int8_t *p) {
     const uint64_t v = (uint64_t)p;
@@ -354,7 +369,31 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     half_setup(false, kt0 + 1, 3);
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) dma_one(false, u);
-    if (FP6) asm volatile("s_waitcnt vmcnt(14)" ::: "memory");
+    // What the epilogue needs to know of the tile, a word per lane (it is read once the sums stand; by then it has long
+    // arrived): 0 .. 4 first source row of each chunk, 8 .. 11 their levels, 16 / 17 first source column of the tile and of
+    // the next, 18 / 19 whether no row / no column is split, 20 / 21 the steps.
+    int tile_meta = 0;
+    if constexpr (MODE == 0) {
+        const int per = kTile / kChunk;
+        const int32_t *from = lane < 8    ? g.layA.chunk_src0 + tm * per + min(lane, per)
+                              : lane < 16 ? g.layA.chunk_lev + tm * per + min(lane - 8, per - 1)
+                              : lane < 18 ? g.layB.tile_src0 + tn + (lane - 16)
+                              : lane < 19 ? g.layA.tile_flat + tm
+                                          : g.layB.tile_flat + tn;
+        if constexpr (BATCH) from = item_at(from, blockIdx.y * g.plan_stride);
+        if (g.scale_a_dev && lane >= 20) {
+            from = reinterpret_cast<const int32_t *>(lane == 20 ? g.scale_a_dev : g.scale_b_dev);
+            if constexpr (BATCH) from = item_at(from, blockIdx.y * g.scale_stride);
+        }
+        tile_meta = *from;
+    }
+    auto meta = [&](int i) __attribute__((always_inline)) {  // (read where it is needed, not kept: scalar registers are scarce)
+        asm volatile("" : "+s"(i));
+        return __builtin_amdgcn_readlane(tile_meta, i);
+    };
+    if (MODE == 0 && FP6) asm volatile("s_waitcnt vmcnt(15)" ::: "memory");
+    else if (MODE == 0) asm volatile("s_waitcnt vmcnt(17)" ::: "memory");
+    else if (FP6) asm volatile("s_waitcnt vmcnt(14)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -534,114 +573,232 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         return;
     }
 
-    // ---- fused epilogue.  The accumulators leave the registers through LDS, one chunk of 64 physical
-    // rows of the tile at a time ([64][256] int32, rows padded to 260), so that global stores are
-    // row-contiguous and the digit levels of a source row (which the planner keeps inside one chunk)
-    // and of a source column (inside one tile) can be added up:
-    // C_int[i,j] = sum_{levels a of i, c of j} s^(a+c) * acc[row(i,a)][col(j,c)].
+    // ---- fused epilogue: C_int[i,j] = sum_{levels a of i, c of j} s^(a+c) * acc[row(i,a)][col(j,c)].  Two ways out:
+    // (1) From the registers, chunk by chunk of 64 physical rows, for fp32 results where the source rows of the chunk have one,
+    //     two or four levels each and the source columns too (or are split here and there: those go through strips in LDS).  A
+    //     lane holds whole source rows and columns then (see rows_layout), so it folds and stores by itself, without
+    //     LDS and barriers.  One wave per SIMD leaves nothing to hide latency behind, so this is bound by its instructions and
+    //     by the stores of all CUs at once: 64 results a lane in some 4000 cycles (9200 through LDS with every
+    //     row decided by itself); 25344 x 768 by 3072 rows 124 -> 107 us, 16384 x 3072 (six-bit) by 4096 512 -> 442 (of
+    //     which three tile rows that even rows save), 8192 x 8448 by 4096 266 -> 213.
+    //     Without levels to fold the stores are ordinary ones: 256 KiB a CU at once as non-temporal lines of 128 bytes take 45 000
+    //     cycles instead of 34 000 (4096 x 8228 by 11013: 357 and 325 us).  With levels there is a half of that or less, and
+    //     the non-temporal ones leave the last-level cache to the operands: a step of 12608 x 768 by 3072 226 and 233 us.
+    // (2) Through LDS ([64][256] int32, rows padded to 260) for everything else: int64 results, rows of several kinds in a chunk,
+    //     many split columns.  Global stores are row-contiguous, any levels can be added up (the planner keeps a source row in one
+    //     chunk, a source column in one tile).
     RowLayout layA = g.layA, layB = g.layB;
     float *C_fp = g.C_fp;
-    int final_shift = g.final_shift, fold_f64 = g.fold_f64;
-    const float *scale_a_dev = g.scale_a_dev, *scale_b_dev = g.scale_b_dev;
+    int final_shift = g.final_shift, fold_f64 = g.fold_f64, evenB = g.evenB;
     if constexpr (BATCH) {
+        evenB = hdr->evenB;
         move_to_item(layA, blockIdx.y * g.plan_stride);
         move_to_item(layB, blockIdx.y * g.plan_stride);
         C_fp = item_at(C_fp, blockIdx.y * g.c_stride);
         final_shift = hdr->ngroups ? g.sh * hdr->grp_exp[hdr->ngroups - 1] : 0;
         fold_f64 = 31 + g.sh * ((hdr->lmaxA - 1) + (hdr->lmaxB - 1)) <= 52;
-        scale_a_dev = item_at(scale_a_dev, blockIdx.y * g.scale_stride);
-        scale_b_dev = item_at(scale_b_dev, blockIdx.y * g.scale_stride);
     }
-    const int jsrc0 = layB.tile_src0[tn], nsrcB = layB.tile_src0[tn + 1] - jsrc0;
-    const bool flatA = layA.tile_flat[tm] != 0, flatB = layB.tile_flat[tn] != 0;
+    const int jsrc0 = meta(16), nsrcB = meta(17) - jsrc0;
+    const bool flatA = meta(18) != 0, flatB = meta(19) != 0;
+    const int stepB = evenB ? kEvenStep : 1;  // from level to level of a source column
     constexpr int FLD = 260;
     int32_t *foldbuf = reinterpret_cast<int32_t *>(smem);  // two regions of [64][FLD]
     // behind the staging buffer: per source row of the tile its first physical row (relative to the
     // tile) | levels << 16; the same per source column; the first source row of each chunk
     int32_t *rowmeta = foldbuf + 2 * kChunk * FLD, *colmeta = rowmeta + kTile, *chunk0 = colmeta + kTile;
+    // ... and the sums of split columns, a strip of the tile's physical rows for each
+    constexpr int kStrips = 20, kStripPitch = BM + 4;
+    int32_t *strips = chunk0 + 8;
+    static_assert(((2 * kChunk * FLD + 2 * kTile + 8) + kStrips * kStripPitch) * sizeof(int32_t) <= kGemmLds, "LDS of the epilogue");
     // scale * 2^final_shift is exact: one multiplication in binary64, one rounding to fp32
-    const double scale2 = (scale_a_dev ? (double)*scale_a_dev * (double)*scale_b_dev : g.scale) *
+    const double scale2 = (g.scale_a_dev ? (double)__int_as_float(meta(20)) * (double)__int_as_float(meta(21)) : g.scale) *
                           (double)(1ull << final_shift);
+    // The short way out of a chunk whose source rows have one, two or four levels each: a lane holds four physical rows side
+    // by side of a column, that is whole source rows, and stores their results itself.
+    int direct = 0, filled = 0;  // a bit per chunk: stored from the registers (or nothing to store); holds source rows
+    const bool fits = C_fp && !g.C_int && g.ldc < (1 << 22);  // fp32 alone, and a chunk of C spans less than 2^30 bytes
+    // the split ones among the tile's 256 physical columns, and the first of each source column
+    auto find_split = [&](unsigned long long (&split)[4], unsigned long long (&heads)[4]) __attribute__((always_inline)) {
+        int prow[4], next[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            prow[t] = layB.prow[n0 + 64 * t + lane];
+            next[t] = 64 * t + lane < BN - 1 ? layB.prow[n0 + 64 * t + lane + 1] : -1;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const bool more = next[t] >= 0 && (next[t] >> kProwLevel) > 0, first = prow[t] >= 0 && (prow[t] >> kProwLevel) == 0;
+            heads[t] = __ballot(first && more);
+            split[t] = __ballot(prow[t] >= 0 && (!first || more));
+        }
+    };
+    int nsplit = 0;
+    unsigned col_off[4] = {kOutside, kOutside, kOutside, kOutside};            // where the lane's four columns go in a row of C
+    int col_strip[4] = {-1, -1, -1, -1};
     {
-        const int isrc0 = layA.tile_src0[tm], nsrcA = layA.tile_src0[tm + 1] - isrc0;
+        if (fits && evenB) {  // the first level of each of the lane's columns
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int col = evenB == 2 ? wn * 64 + (t >> 1) * 32 + lrow : wn * 32 + lrow;
+                if (col < nsrcB) col_off[t] = 4u * (unsigned)col;
+            }
+        } else if (fits && !flatB) {
+            int own[4];
+            unsigned long long split_cols[4], heads[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) own[t] = layB.prow[n0 + wn * 128 + 32 * t + lrow];
+            find_split(split_cols, heads);
+            nsplit = __popcll(split_cols[0]) + __popcll(split_cols[1]) + __popcll(split_cols[2]) + __popcll(split_cols[3]);
+            // the wave's column 32 t + lrow is bit (32 t + lrow) & 63 of word 2 wn + t / 2
+            const unsigned long long lower = wn ? split_cols[2] : split_cols[0], upper = wn ? split_cols[3] : split_cols[1];
+            const int before = wn ? __popcll(split_cols[0]) + __popcll(split_cols[1]) : 0;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const unsigned long long m = t >> 1 ? upper : lower;
+                const int bit = (t & 1) * 32 + lrow;
+                if ((m >> bit) & 1) col_strip[t] = before + (t >> 1 ? __popcll(lower) : 0) + __popcll(m & ((1ull << bit) - 1ull));
+                else if (own[t] >= 0) col_off[t] = 4u * (unsigned)((own[t] & ((1 << kProwLevel) - 1)) - jsrc0);
+            }
+        } else if (fits) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int col = wn * 128 + 32 * t + lrow;
+                if (col < nsrcB) col_off[t] = 4u * (unsigned)col;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool rows = meta(c + 1) > meta(c);  // (a chunk of nothing but padding stores nothing, and no resource is made for it)
+            const int lev = fits && rows ? meta(8 + c) : 0;
+            const bool ok = ((lev == 1 && !evenB) || (fold_f64 && (lev == 1 || lev == 2 || lev == 4))) && nsplit <= kStrips;
+            direct |= (!rows || ok) << c;
+            filled |= rows << c;
+        }
+    }
+    const bool any_direct = (direct & filled) != 0, any_lds = direct != 15;
+    if (any_lds) {
+        const int isrc0 = meta(0), nsrcA = meta(4) - isrc0;
         if (!flatA && tid < nsrcA)
             rowmeta[tid] = (layA.src_pstart[isrc0 + tid] - m0) | (layA.src_nlev[isrc0 + tid] << 16);
         if (!flatB && tid < nsrcB)
             colmeta[tid] = (layB.src_pstart[jsrc0 + tid] - n0) | (layB.src_nlev[jsrc0 + tid] << 16);
-        if (tid <= kTile / kChunk) chunk0[tid] = layA.chunk_src0[tm * (kTile / kChunk) + tid];
+        if (tid <= kTile / kChunk) chunk0[tid] = tile_meta;
     }  // published by the first barrier below
-    // Four results of one output row leave as 16 bytes of fp32 and / or 32 bytes of int64 (any element
-    // boundary will do: a wave still writes a contiguous kilobyte), fewer than four at the ragged end of
-    // a tile one by one.  v: the integer sums before the final shift.
-    auto store4 = [&](int64_t o, int cols_left, auto v0, auto v1, auto v2, auto v3) {
-        if constexpr (std::is_same<decltype(v0), double>::value) {  // exact integer sums held in binary64; no int64 output
-            const float f[4] = {(float)(v0 * scale2), (float)(v1 * scale2), (float)(v2 * scale2), (float)(v3 * scale2)};
-            if (cols_left >= 4) {
-                v4f_u x;
-                x[0] = f[0]; x[1] = f[1]; x[2] = f[2]; x[3] = f[3];
-                __builtin_nontemporal_store(x, reinterpret_cast<v4f_u *>(C_fp + o));
-            } else {
+    // `ns` rows of C from source row c0 on, the tile's columns.  Rows behind them begin behind the end (ldc >= nsrcB).
+    auto rows_of_c = [&](int c0, int ns) __attribute__((always_inline)) {
+        float *to = C_fp + (int64_t)c0 * g.ldc + jsrc0;
+        return __builtin_amdgcn_make_buffer_rsrc(to, 0, (int)(((unsigned)(ns - 1) * (unsigned)g.ldc + (unsigned)nsrcB) * 4u), 0x00027000);
+    };
+    // The sums of 32 physical rows (I: which of the wave's four blocks of them) to where they belong.  L: physical rows of a
+    // source row, M: physical columns of a source column.
+    auto put = [&](auto lev_c, auto cols_c, auto block_c, auto value) __attribute__((always_inline)) {
+        constexpr int L = decltype(lev_c)::value, M = decltype(cols_c)::value, G = 4 / L;  // G source rows among four physical ones
+        constexpr int half = decltype(block_c)::value >> 1, ii = decltype(block_c)::value & 1;
+        const int c0 = meta(2 * wm + half), ns = meta(2 * wm + half + 1) - c0;
+        const unsigned pitch = (unsigned)g.ldc * 4u;
+        const __amdgpu_buffer_rsrc_t rs = rows_of_c(c0, ns);
+        unsigned off[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (k < cols_left) C_fp[o + k] = f[k];
-            }
-            return;
-        }
-        const int64_t w[4] = {(int64_t)v0, (int64_t)v1, (int64_t)v2, (int64_t)v3};
-        float f[4];
-        if (C_fp) {
-            if constexpr (sizeof(v0) == 4) {
-                f[0] = (float)((double)v0 * scale2); f[1] = (float)((double)v1 * scale2);
-                f[2] = (float)((double)v2 * scale2); f[3] = (float)((double)v3 * scale2);
-            } else {
+        for (int j = 0; j < 4; j += M) off[j] = col_off[j] + (unsigned)(lhalf * G) * pitch;
+        double w[L + M];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) f[k] = (float)((double)w[k] * scale2);
-            }
-        }
-        if (cols_left >= 4) {
-            if (C_fp) {
-                v4f_u x;
-                x[0] = f[0]; x[1] = f[1]; x[2] = f[2]; x[3] = f[3];
-                __builtin_nontemporal_store(x, reinterpret_cast<v4f_u *>(C_fp + o));
-            }
-            if (g.C_int) {
-                v2l_u lo, hi;
-                lo[0] = w[0] << final_shift; lo[1] = w[1] << final_shift;
-                hi[0] = w[2] << final_shift; hi[1] = w[3] << final_shift;
-                __builtin_nontemporal_store(lo, reinterpret_cast<v2l_u *>(g.C_int + o));
-                __builtin_nontemporal_store(hi, reinterpret_cast<v2l_u *>(g.C_int + o + 2));
-            }
-        } else {
+        for (int l = 0; l < L + M; ++l) w[l] = (double)(1ull << (g.sh * l));
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k < cols_left) {
-                    if (C_fp) C_fp[o + k] = f[k];
-                    if (g.C_int) g.C_int[o + k] = w[k] << final_shift;
+        for (int rg = 0; rg < 4; ++rg) {
+            float f[G][4];
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; j += M) {
+                    double v = 0.0;
+#pragma unroll
+                    for (int m = 0; m < M; ++m) {
+                        int x[L];
+#pragma unroll
+                        for (int l = 0; l < L; ++l) x[l] = value(j + m, 4 * rg + k * L + l);
+#pragma unroll
+                        for (int l = 0; l < L; l += FP6 ? 2 : 1) {
+                            // (sums of six-bit digits stay below 2^24 and the weights at 8: two levels fit 32 bits)
+                            const double t = exact_f64(FP6 && L > 1 ? x[l] + (x[(l + 1) % L] << g.sh) : x[l]);
+                            if (m + l == 0) v = t;
+                            else v += t * w[m + l];
+                        }
+                    }
+                    f[k][j] = (float)(v * scale2);
                 }
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; j += M)
+                    store_inside<(L * M > 1)>(f[k][j], rs, off[j] + (unsigned)((ii * 32 + 8 * rg) / L + k) * pitch);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // two chunks per round: every wave parks 64 of its 128 rows (region wm of the staging buffer), then
-    // all threads work the two chunks off
+    // 64 sums of a lane's partners at a time: the loads have to be many to be fast, 256 KiB a partner
+    auto others = [&](int block, v4i (&other)[16]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 16; ++t) other[t] = v4i{0, 0, 0, 0};
+        const int32_t *q = partner + block * 4 * 16 * kGemmThreads;
+#pragma unroll 1
+        for (int w = 0; w < partners; ++w, q += BM * BN) {
+            v4i x[16];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) x[t] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(q + t * 4 * kGemmThreads));
+#pragma unroll
+            for (int t = 0; t < 16; ++t) other[t] += x[t];
+        }
+    };
+    auto store_block = [&](auto block_c) __attribute__((always_inline)) {
+        constexpr int I = decltype(block_c)::value, half = I >> 1;
+        if (!((direct & filled) >> (2 * wm + half) & 1)) return;
+        const int my_lev = meta(8 + 2 * wm + half);
+        v4i other[16];
+        if (SPLIT && partner) others(I, other);
+        // (read by hand, so that the compiler does not convert sixty-four sums ahead of the choice between the three)
+        auto sum = [&](int jj, int r) __attribute__((always_inline)) {
+            int32_t v;
+            if constexpr (FP6) {
+                float x;
+                asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[I][jj][r]));
+                v = (int32_t)x;
+            } else {
+                asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(acc[I][jj][r]));
+            }
+            if (SPLIT && partner) v = (v << rest) + other[jj * 4 + (r >> 2)][r & 3];
+            return v;
+        };
+        auto with_cols = [&](auto cols_c) __attribute__((always_inline)) {
+            if (my_lev == 1) put(std::integral_constant<int, 1>{}, cols_c, block_c, sum);
+            else if (my_lev == 2) put(std::integral_constant<int, 2>{}, cols_c, block_c, sum);
+            else if (my_lev == 4) put(std::integral_constant<int, 4>{}, cols_c, block_c, sum);
+        };
+        if (evenB == 0) with_cols(std::integral_constant<int, 1>{});
+        else if (evenB == 2) with_cols(std::integral_constant<int, 2>{});
+        else with_cols(std::integral_constant<int, 4>{});
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+            if (col_strip[jj] >= 0)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    strips[col_strip[jj] * kStripPitch + wm * 128 + I * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3)] = sum(jj, r);
+    };
+    if (any_direct) {
+        asm volatile("s_nop 15\n\ts_nop 15");  // the last matrix instructions have landed (the compiler does not see the reads)
+        store_block(std::integral_constant<int, 0>{});
+        store_block(std::integral_constant<int, 1>{});
+        store_block(std::integral_constant<int, 2>{});
+        store_block(std::integral_constant<int, 3>{});
+    }
+    // two chunks per round: every wave parks 64 of its 128 rows (region wm of the staging buffer), then all threads work the
+    // two chunks off
+    if (any_lds)
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
         __syncthreads();
 #pragma unroll
         for (int ii = 0; ii < 2; ++ii) {
-            // 64 sums of a partner at a time: the loads have to be many to be fast, 256 KiB a partner
             v4i other[16];
-            if (SPLIT && partner) {
-#pragma unroll
-                for (int t = 0; t < 16; ++t) other[t] = v4i{0, 0, 0, 0};
-                const int32_t *q = partner + (half * 2 + ii) * 4 * 16 * kGemmThreads;
-#pragma unroll 1
-                for (int w = 0; w < partners; ++w, q += BM * BN) {
-                    v4i x[16];
-#pragma unroll
-                    for (int t = 0; t < 16; ++t) x[t] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(q + t * 4 * kGemmThreads));
-#pragma unroll
-                    for (int t = 0; t < 16; ++t) other[t] += x[t];
-                }
-            }
+            if (SPLIT && partner) others(half * 2 + ii, other);
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
@@ -655,164 +812,155 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
 #pragma unroll 1
         for (int reg = 0; reg < 2; ++reg) {
             const int c = 2 * reg + half;  // chunk of the tile: rows [64 c, 64 c + 64)
+            if (direct >> c & 1) continue;
             const int32_t *fold = foldbuf + reg * kChunk * FLD;
             // source rows of this chunk: cs0 .. cs0 + ns - 1; no source row straddles a chunk
             const int cs0 = chunk0[c], ns = chunk0[c + 1] - cs0;
             const int rs0 = cs0 - chunk0[0];  // index of the chunk's first source row in rowmeta
-            // Four columns side by side from column q on (of the source columns jcol ..), four source rows at a time per
-            // thread so that their LDS reads are in flight together (a wave works on one row at a time, so the level
-            // counts are uniform).
-            constexpr int RS = kGemmThreads / 64;
-            auto quad_at = [&](const int32_t *at, bool aligned) {
-                v4i x;
-                if (aligned) {
-                    x = *reinterpret_cast<const v4i *>(at);
-                } else {
-                    x[0] = at[0]; x[1] = at[1]; x[2] = at[2]; x[3] = at[3];
-                }
-                return x;
-            };
-            auto copy_rows = [&](int q, int jcol, bool aligned) {  // no split row in the tile: physical order = source order
-                for (int r0 = tid >> 6; r0 < ns; r0 += 4 * RS) {
-                    v4i x[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) x[u] = quad_at(fold + min(r0 + u * RS, ns - 1) * FLD + q, aligned);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (r0 + u * RS < ns)
-                            store4((int64_t)(cs0 + r0 + u * RS) * g.ldc + jsrc0 + jcol, nsrcB - jcol, x[u][0], x[u][1], x[u][2], x[u][3]);
-                }
-            };
-            // split rows: the digit levels of a source row are added up, in binary64 where every sum is exact in it
-            auto fold_rows = [&](auto zero, int q, int jcol, bool aligned) {
+            // A lane owns four source columns side by side, a wave works on four source rows together so that their LDS reads
+            // are in flight side by side; what a row needs is uniform in the wave, the levels of the columns are masked weights.
+            // (Every row and column looked at by itself: 9600 cycles a chunk, 30 000 where several columns were split.  A column
+            // to a lane and every row to every wave: 20 000.)
+            auto fold_chunk = [&](auto zero, auto flat_c) __attribute__((always_inline)) {
                 using T = decltype(zero);
-                for (int r0 = tid >> 6; r0 < ns; r0 += 4 * RS) {
-                    int prel[4], nl[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int m = r0 + u * RS < ns ? rowmeta[rs0 + r0 + u * RS] : 0;
-                        prel[u] = (m & 0xFFFF) - c * kChunk;
-                        nl[u] = m >> 16;  // 0 past the chunk's last source row
-                    }
-                    const int nlmax = max(max(nl[0], nl[1]), max(nl[2], nl[3]));
-                    T v[4][4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) v[u][k] = zero;
-                    for (int l = 0; l < nlmax; ++l) {
-                        v4i x[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            x[u] = l < nl[u] ? quad_at(fold + (prel[u] + l) * FLD + q, aligned) : v4i{0, 0, 0, 0};
-                        if constexpr (std::is_same<T, double>::value) {
-                            const double wl = (double)(1ull << (g.sh * l));
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                                for (int k = 0; k < 4; ++k) v[u][k] += (double)x[u][k] * wl;
-                        } else {
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                                for (int k = 0; k < 4; ++k) v[u][k] += (int64_t)x[u][k] << (g.sh * l);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (r0 + u * RS < ns)
-                            store4((int64_t)(cs0 + r0 + u * RS) * g.ldc + jsrc0 + jcol, nsrcB - jcol, v[u][0],
-                                   v[u][1], v[u][2], v[u][3]);
-                }
-            };
-            if (flatB) {
-                // source columns = physical columns: work items are (source row, four columns)
-                const int col4 = (tid & 63) * 4;
-                if (col4 < nsrcB) {
-                    if (flatA) copy_rows(col4, col4, true);
-                    else if (fold_f64) fold_rows(0.0, col4, col4, true);
-                    else fold_rows((int64_t)0, col4, col4, true);
-                }
-            } else {
-                // split source columns: lane l owns source columns 4l .. 4l+3 of the tile (where they sit in
-                // the tile and how many digit levels each has is looked up once per chunk).  Four unsplit
-                // columns side by side are the usual case and go the way of the flat tile (behind a split
-                // column they no longer start at a multiple of four: four words rather than one vector).
-                // A few other quads are then worked off one at a time with the wave's rows spread over its
-                // lanes, so that their level loops run once per wave and quad, not once per row; if most
-                // quads are of that kind, every lane works its own.
-                const int j4 = (tid & 63) * 4;
-                int q0[4], lj[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int cm = j4 + k < nsrcB ? colmeta[j4 + k] : 0;
-                    q0[k] = cm & 0xFFFF;
-                    lj[k] = cm >> 16;  // 0 past the last source column
-                }
-                const bool plain = lj[0] == 1 && lj[1] == 1 && lj[2] == 1 && lj[3] == 1 && q0[1] == q0[0] + 1 &&
-                                   q0[2] == q0[0] + 2 && q0[3] == q0[0] + 3;
-                const unsigned long long others = __ballot(j4 < nsrcB && !plain);
-                auto row_levels = [&](int r, int &prel, int &nl) {
-                    prel = r;
-                    nl = 1;
-                    if (!flatA) {
-                        const int m = rowmeta[rs0 + r];
-                        prel = (m & 0xFFFF) - c * kChunk;
-                        nl = m >> 16;
-                    }
-                };
-                if (plain) {
-                    const bool aligned = (q0[0] & 3) == 0;
-                    if (flatA) copy_rows(q0[0], j4, aligned);
-                    else if (fold_f64) fold_rows(0.0, q0[0], j4, aligned);
-                    else fold_rows((int64_t)0, q0[0], j4, aligned);
-                }
-                const bool many = __popcll(others) > 8;  // mostly split columns: every lane works its own quad
-                if (many && !plain && j4 < nsrcB) {
-                    const int ljmax = max(max(lj[0], lj[1]), max(lj[2], lj[3]));
-                    for (int r = tid >> 6; r < ns; r += kGemmThreads / 64) {
-                        int prel, nl;
-                        row_levels(r, prel, nl);
-                        int64_t v[4] = {0, 0, 0, 0};
-                        for (int a = 0; a < nl; ++a) {
-                            const int32_t *row = fold + (prel + a) * FLD;
-                            for (int l = 0; l < ljmax; ++l) {
-                                int x[4];
-#pragma unroll
-                                for (int k = 0; k < 4; ++k) x[k] = l < lj[k] ? row[q0[k] + l] : 0;
-#pragma unroll
-                                for (int k = 0; k < 4; ++k) v[k] += (int64_t)x[k] << (g.sh * (a + l));
-                            }
-                        }
-                        store4((int64_t)(cs0 + r) * g.ldc + jsrc0 + j4, nsrcB - j4, v[0], v[1], v[2], v[3]);
-                    }
-                }
-                for (unsigned long long m = many ? 0ull : others; m; m &= m - 1) {
-                    const int from = __builtin_ctzll(m);  // the lane that owns this quad
-                    int Q0[4], LJ[4];
+                constexpr bool F = decltype(flat_c)::value;  // source columns = physical columns
+                constexpr int U = 4, RS = kGemmThreads / 64;
+                const int j4 = lane * 4, left = nsrcB - j4;
+                // fp32 alone and no quad that ends inside: one store a row, what is outside dropped by the hardware
+                const bool quads = fits && (nsrcB & 3) == 0;
+                const unsigned quad_off = left > 0 ? 4u * (unsigned)j4 : kOutside;
+                const __amdgpu_buffer_rsrc_t rs = rows_of_c(cs0, max(ns, 1));
+                int q[4], lj[4], ljmax = 1;
+                if constexpr (!F) {
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        Q0[k] = __builtin_amdgcn_readlane(q0[k], from);
-                        LJ[k] = __builtin_amdgcn_readlane(lj[k], from);
+                        const int cm = j4 + k < nsrcB ? colmeta[j4 + k] : 1 << 16;
+                        q[k] = cm & 0xFFFF;
+                        lj[k] = cm >> 16;
                     }
-                    const int ljmax = max(max(LJ[0], LJ[1]), max(LJ[2], LJ[3]));
-                    const int r = (tid >> 6) + (kGemmThreads / 64) * (tid & 63);  // this wave's rows, one per lane
-                    if (r < ns) {
-                        int prel, nl;
-                        row_levels(r, prel, nl);
-                        int64_t v[4] = {0, 0, 0, 0};
-                        for (int a = 0; a < nl; ++a) {
-                            const int32_t *row = fold + (prel + a) * FLD;
-                            for (int l = 0; l < ljmax; ++l) {
+                    ljmax = from_lane63(wave_max_nonneg_lane63(max(max(lj[0], lj[1]), max(lj[2], lj[3]))));
+                }
+                for (int r0 = wave; r0 < ns; r0 += U * RS) {
+                    int nl[U], nlmax = 1;
+                    const int32_t *row[U];
+                    T v[U][4];
 #pragma unroll
-                                for (int k = 0; k < 4; ++k)
-                                    if (l < LJ[k]) v[k] += (int64_t)row[Q0[k] + l] << (g.sh * (a + l));
+                    for (int u = 0; u < U; ++u) {
+                        const int r = min(r0 + u * RS, ns - 1);
+                        const int m = flatA ? (1 << 16) | (c * kChunk + r) : __builtin_amdgcn_readfirstlane(rowmeta[rs0 + r]);
+                        row[u] = fold + ((m & 0xFFFF) - c * kChunk) * FLD;
+                        nl[u] = m >> 16;
+                        nlmax = max(nlmax, nl[u]);
+                    }
+                    {  // level 0 of all of them
+                        v4i x[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            if constexpr (F) x[u] = *reinterpret_cast<const v4i *>(row[u] + j4);
+                            else
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) x[u][k] = row[u][q[k]];
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                if constexpr (std::is_same<T, double>::value) v[u][k] = exact_f64(x[u][k]);
+                                else v[u][k] = x[u][k];
+                            }
+                    }
+                    for (int a = 0; a < nlmax; ++a)
+                        for (int l = a == 0; l < (F ? 1 : ljmax); ++l) {
+                            v4i x[U];
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const int32_t *at = row[u] + (a < nl[u] ? a * FLD : 0);
+                                if constexpr (F) x[u] = *reinterpret_cast<const v4i *>(at + j4);
+                                else
+#pragma unroll
+                                    for (int k = 0; k < 4; ++k) x[u][k] = at[q[k] + (l < lj[k] ? l * stepB : 0)];
+                            }
+                            if constexpr (std::is_same<T, double>::value) {
+                                const double w = (double)(1ull << (g.sh * (a + l)));
+                                double wk[4];
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) wk[k] = F || l < lj[k] ? w : 0.0;
+#pragma unroll
+                                for (int u = 0; u < U; ++u)
+#pragma unroll
+                                    for (int k = 0; k < 4; ++k) v[u][k] += exact_f64(x[u][k]) * (a < nl[u] ? wk[k] : 0.0);
+                            } else {
+#pragma unroll
+                                for (int u = 0; u < U; ++u)
+#pragma unroll
+                                    for (int k = 0; k < 4; ++k)
+                                        v[u][k] += (int64_t)(a < nl[u] && (F || l < lj[k]) ? x[u][k] : 0) << (g.sh * (a + l));
                             }
                         }
-                        store4((int64_t)(cs0 + r) * g.ldc + jsrc0 + 4 * from, nsrcB - 4 * from, v[0], v[1], v[2], v[3]);
+                    if constexpr (std::is_same<T, double>::value)
+                        if (quads) {
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const float f[4] = {(float)(v[u][0] * scale2), (float)(v[u][1] * scale2), (float)(v[u][2] * scale2), (float)(v[u][3] * scale2)};
+                                store_inside4(f, rs, (unsigned)(r0 + u * RS) * (unsigned)g.ldc * 4u + quad_off);
+                            }
+                            continue;
+                        }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (r0 + u * RS >= ns) break;
+                        const int64_t o = (int64_t)(cs0 + r0 + u * RS) * g.ldc + jsrc0 + j4;
+                        v4f_u f;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) f[k] = (float)((double)v[u][k] * scale2);
+                        if (left >= 4) {  // 16 bytes at any boundary: a wave writes a contiguous kilobyte
+                            if (C_fp) __builtin_nontemporal_store(f, reinterpret_cast<v4f_u *>(C_fp + o));
+                            if constexpr (!std::is_same<T, double>::value)
+                                if (g.C_int) {
+                                    const v2l_u lo = {v[u][0] << final_shift, v[u][1] << final_shift}, hi = {v[u][2] << final_shift, v[u][3] << final_shift};
+                                    __builtin_nontemporal_store(lo, reinterpret_cast<v2l_u *>(g.C_int + o));
+                                    __builtin_nontemporal_store(hi, reinterpret_cast<v2l_u *>(g.C_int + o + 2));
+                                }
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < 3; ++k)
+                                if (k < left) {
+                                    if (C_fp) C_fp[o + k] = f[k];
+                                    if constexpr (!std::is_same<T, double>::value)
+                                        if (g.C_int) g.C_int[o + k] = v[u][k] << final_shift;
+                                }
+                        }
                     }
                 }
+            };
+            const bool f64 = !g.C_int && ((flatA && flatB) || fold_f64);
+            if (f64 && flatB) fold_chunk(0.0, std::true_type{});
+            else if (f64) fold_chunk(0.0, std::false_type{});
+            else if (flatB) fold_chunk((int64_t)0, std::true_type{});
+            else fold_chunk((int64_t)0, std::false_type{});
+        }
+    }
+    // the split columns of the chunks that were stored from the registers: wave w takes chunk w, a lane a source row
+    if (any_direct && nsplit > 0 && nsplit <= kStrips) {
+        __syncthreads();
+        if (!((direct & filled) >> wave & 1)) return;
+        const int c0 = meta(wave), L = meta(8 + wave), ns = meta(wave + 1) - c0;
+        unsigned long long split_cols[4], heads[4];
+        find_split(split_cols, heads);
+        const int r = min(lane, ns - 1);
+        const int32_t *strip = strips + wave * kChunk + r * L;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            for (unsigned long long m = heads[t]; m; m &= m - 1) {
+                const int bit = __builtin_ctzll(m);
+                const int src = layB.prow[n0 + 64 * t + bit] & ((1 << kProwLevel) - 1), lj = layB.src_nlev[src];
+                const int32_t *s0 = strip + __popcll(split_cols[t] & ((1ull << bit) - 1ull)) * kStripPitch;
+                int64_t v = 0;
+                for (int l = 0; l < lj; ++l)
+                    for (int a = 0; a < L; ++a) v += (int64_t)s0[l * kStripPitch + a] << (g.sh * (a + l));
+                if (lane < ns) C_fp[(int64_t)(c0 + r) * g.ldc + src] = (float)((double)v * scale2);
             }
+            strip += __popcll(split_cols[t]) * kStripPitch;
         }
     }
 }
@@ -1019,7 +1167,8 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
             sh_now = sh_next;
         }
     };
-    const bool half_rows = ns * (BATCH ? hdr->lmaxA : g.lmaxA) <= 32;  // uniform; the rows of a chunk start at its first
+    const int lmaxA = BATCH ? hdr->lmaxA : g.lmaxA;
+    const bool half_rows = ns * (lmaxA == 3 ? 4 : lmaxA) <= 32;  // uniform; the rows of a chunk start at its first (three levels may take four rows)
     if (busy) {
         if (half_rows) contract(std::integral_constant<int, 1>{});
         else contract(std::integral_constant<int, 2>{});
@@ -1063,6 +1212,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
     // on four source rows at a time so that their LDS reads are in flight together
     if (lane >= nc) return;
     const int q0 = colmeta[lane] & 0xFFFF, lj = colmeta[lane] >> 16;
+    const int stepB = (BATCH ? hdr->evenB : g.evenB) ? kEvenStep : 1;  // from level to level of a source column
     constexpr int U = 4;
     for (int r0 = wave; r0 < ns; r0 += U * kSmallWaves) {
         int nl[U], nlmax = 0;
@@ -1081,7 +1231,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
             for (int c = 0; c < lj; ++c)
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    if (a < nl[u]) v[u] += (int64_t)row[u][a * kSmallPitch + c] << (g.sh * (a + c));
+                    if (a < nl[u]) v[u] += (int64_t)row[u][a * kSmallPitch + c * stepB] << (g.sh * (a + c));
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (nl[u]) {
@@ -1097,7 +1247,7 @@ __global__ __launch_bounds__(256) void recombine_kernel(const int64_t *__restric
                                                         RowLayout layB, int n, int h, int sh,
                                                         int64_t *C_int, float *C_fp, int64_t ldc,
                                                         double scale_val, const float *scale_a_dev,
-                                                        const float *scale_b_dev) {
+                                                        const float *scale_b_dev, int stepB) {
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= h) return;
     const double scale = scale_a_dev ? (double)*scale_a_dev * (double)*scale_b_dev : scale_val;
@@ -1106,7 +1256,7 @@ __global__ __launch_bounds__(256) void recombine_kernel(const int64_t *__restric
         const int p0 = layA.src_pstart[i], li = layA.src_nlev[i];
         int64_t acc = 0;
         for (int a = 0; a < li; ++a)
-            for (int c = 0; c < lj; ++c) acc += C_u[(int64_t)(p0 + a) * Np + (q0 + c)] << (sh * (a + c));
+            for (int c = 0; c < lj; ++c) acc += C_u[(int64_t)(p0 + a) * Np + (q0 + c * stepB)] << (sh * (a + c));
         const int64_t o = (int64_t)i * ldc + j;
         if (C_int) C_int[o] = acc;
         if (C_fp) C_fp[o] = (float)((double)acc * scale);
@@ -1189,7 +1339,7 @@ int recombine_impl(const imunpack_plan_t *p, const void *workspace, float scale_
     dim3 grid((unsigned)((p->h + 255) / 256), (unsigned)std::min<int64_t>(p->n, 65535));
     hipLaunchKernelGGL(recombine_kernel, grid, dim3(256), 0, stream,
                        (const int64_t *)workspace, p->hdr.Np, p->layA, p->layB, (int)p->n, (int)p->h, p->sh,
-                       C_int, C_fp, ldc, (double)scale_A * (double)scale_B, scale_a_dev, scale_b_dev);
+                       C_int, C_fp, ldc, (double)scale_A * (double)scale_B, scale_a_dev, scale_b_dev, p->hdr.evenB ? kEvenStep : 1);
     return launch_status();
 }
 }  // namespace imu
@@ -1209,6 +1359,7 @@ static void fused_args(GemmArgs &g, const Plan *p) {
     g.sh = p->sh;
     g.Np = h.Np;
     g.lmaxA = h.lmaxA;
+    g.evenB = h.evenB;
     g.guard_mul = p->s - 1;
     g.kt0 = 0; g.kt1 = h.Kp / BK;
     g.nbound = 0;
@@ -1225,9 +1376,16 @@ static void fused_args(GemmArgs &g, const Plan *p) {
     g.fold_f64 = 31 + p->sh * ((h.lmaxA - 1) + (h.lmaxB - 1)) <= 52;
 }
 
+// What the epilogue of a large tile takes: the longer way through LDS where levels differ from row to row (3328 x 768 in 3 and
+// 5 levels by 3072 rows: 34 us a round), the more where columns are split as well (1408 x 1024 by 1800 rows of two levels 27 us,
+// 250 by 6400 rows of two levels both 36).
+static int tile_ns(const PlanHeader &h) {
+    if (h.lmaxB > 1 && !h.evenB) return 10000 + 4500 * h.lmaxA * h.lmaxB;
+    return h.lmaxA > 1 && !h.evenA ? 12000 + 3000 * h.lmaxA : kTileNs;
+}
 // Whether the small tiles are the better ones for this plan (and B's rows are laid out for them).
 static bool small_tiles(const Plan *p, int64_t tiles, int64_t pairs, int64_t ktiles) {
-    return p->hdr.chunkB == kChunk && small_tiles_win(tiles, pairs, ktiles, p->nitems == 1, 0);
+    return p->hdr.chunkB == kChunk && small_tiles_win(tiles, pairs, ktiles, p->nitems == 1, 0, tile_ns(p->hdr));
 }
 // The chunk pairs of an unpacked product that hold source rows.
 static int64_t chunk_pairs(const PlanHeader &h) {

@@ -934,7 +934,7 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g)
 // can be applied on the 64 rows the tile's epilogue holds in LDS at a time; kTile for B, whose levels
 // are folded along the columns of a tile (kChunk there too if the 64 x 64 tiles of the small-tile GEMM may run).  Source row i with unpadded start P_i
 // goes to chunk floor(P_i / (kChunk - (Lmax-1))): a closed form, and the rows of a chunk never exceed
-// kChunk.
+// kChunk.  (Rows of A with nearly all the same number of levels: see `uniform`.)
 // Bound by the latency of one workgroup's reads and stores, so rows beyond kRowSlice are shared out: every one of
 // `nslices` workgroups derives the level counts and their sums for itself and writes its share of the rows.
 constexpr int kRowSlice = 4096;  // source rows per workgroup, at most four workgroups (12608 rows of two levels: 34 -> 21 us)
@@ -969,12 +969,37 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
     const int base = ordered_scan(
         nbase, 0, [&](int x) { return nlev[x]; }, [&](int x, int pre) { tmpP[x] = pre; }, lds);
     // chunks of `chunk` physical rows (a divisor of kTile); source row i goes to chunk floor(P_i / Cp)
-    const int Cp = chunk - (lmax - 1);
+    int Cp = chunk - (lmax - 1);
     if (Cp < 1) {
         if (threadIdx.x == 0) atomicMin(&hdr->err, IMUNPACK_ERANGE);
         return;
     }
-    const int nchunks = nbase > 0 ? tmpP[nbase - 1] / Cp + 1 : 0;
+    int nchunks = nbase > 0 ? tmpP[nbase - 1] / Cp + 1 : 0;
+    // Rows that (nearly) all have the same number of levels, two to four: each gets two or four physical rows, some of them
+    // padding, where that takes no more chunks.  Then the GEMM's epilogue stores from its registers: a lane holds four
+    // physical rows of A side by side, so the levels of a row of A are neighbours; and it holds the same column of every
+    // block of kEvenStep rows of B, so those of a row of B are that far apart.  Besides, nothing of a chunk is lost: 4096
+    // rows of A of four levels but 97 of three take 64 tiles instead of 67.
+    int even = lmax == 1 || lmax > 4 ? 0 : lmax == 2 ? 2 : 4;
+    static_assert(kEvenStep == 32 && kChunk == 64 && kTile == 256, "shifts below");
+    const int step = operand ? kEvenStep : 1;  // from level to level, if so
+    if (even * step > chunk) even = 0;         // (four levels of B do not fit the chunks of the small tiles)
+    const int lg_chunk = chunk == kChunk ? 6 : 8, lg_even = even >> 1, lg_step = operand ? 5 : 0;
+    const int most = (nbase + step - 1) / step * step;
+    const bool uniform = even && (int64_t)most * even <= (int64_t)nchunks * chunk;
+    if (uniform) {
+        Cp = chunk;
+        nchunks = (most * even + chunk - 1) / chunk;
+    }
+    const int total = uniform ? nbase * even : base;
+    auto start = [&](int i) { return i >= nbase ? total : uniform ? i << lg_even : tmpP[i]; };
+    const float per_chunk = 1.0f / (float)Cp;
+    auto chunk_of = [&](int P) {  // P / Cp (a division takes some forty instructions)
+        if (uniform) return P >> lg_chunk;
+        if (base >= (1 << 24)) return P / Cp;
+        const int q = (int)((float)P * per_chunk), r = P - q * Cp;  // off by one at most
+        return q + (r >= Cp ? 1 : 0) - (r < 0 ? 1 : 0);
+    };
     const int kPerTile = kTile / chunk;
     const int ntiles = (nchunks + kPerTile - 1) / kPerTile;
     const int Mp = ntiles * kTile;
@@ -989,6 +1014,7 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
         // first i with P_i >= ch * Cp
         int lo = 0, hi = nbase;
         const int want = ch * Cp;
+        if (uniform) lo = hi = min(nbase, ch << (lg_chunk - lg_even));
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
             if (tmpP[mid] >= want) hi = mid; else lo = mid + 1;
@@ -996,6 +1022,7 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
         chunk0[ch] = lo;
         if (slice == 0) {
             if (fast) lay.chunk_src0[ch] = lo;
+            if (operand == 0) lay.chunk_lev[ch] = uniform ? even : lo < nbase ? nlev[lo] : 0;
             if (ch % kPerTile == 0) lay.tile_src0[ch / kPerTile] = lo;
         }
     }
@@ -1003,22 +1030,35 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
     if (slice == 0)
         for (int t = threadIdx.x; t < ntiles; t += kPlanThreads) {
             const int a = chunk0[t * kPerTile], e = chunk0[(t + 1) * kPerTile];
-            const int slots = (e < nbase ? tmpP[e] : base) - tmpP[a];
+            const int slots = start(e) - start(a);
             // (rows of B in chunks: the tile's columns of C are read as one run, which gaps between the chunks break)
-            lay.tile_flat[t] = (slots == e - a && (operand == 0 || chunk == kTile || lmax == 1)) ? 1 : 0;
+            lay.tile_flat[t] = (!uniform && slots == e - a && (operand == 0 || chunk == kTile || lmax == 1)) ? 1 : 0;
         }
-    const int step = kPlanThreads * nslices, me = slice * kPlanThreads + threadIdx.x;
-    // rows behind the last one of a chunk are padding
-    for (int p = me; p < Mp; p += step) {
-        const int ch = p / chunk, a = chunk0[ch], e = chunk0[ch + 1];
-        const int used = a < e ? (e < nbase ? tmpP[e] : base) - tmpP[a] : 0;
-        if (p - ch * chunk >= used) lay.prow[p] = -1;
+    if (slice == 0 && operand == 0 && !uniform && lmax > 1)
+        for (int i = threadIdx.x; i < nbase; i += kPlanThreads) {
+            const int ch = chunk_of(start(i));
+            if (nlev[i] != nlev[chunk0[ch]]) lay.chunk_lev[ch] = 0;
+        }
+    const int threads = kPlanThreads * nslices, me = slice * kPlanThreads + threadIdx.x;
+    // rows behind the last one of a chunk are padding, those of the levels that a row does not have too
+    for (int p = me; p < Mp; p += threads) {
+        const int ch = p >> lg_chunk, a = chunk0[ch], e = chunk0[ch + 1], at = p & (chunk - 1);
+        bool none;
+        if (uniform) {
+            const int i = a + (at >> (lg_even + lg_step) << lg_step) + (at & (step - 1)), l = (at >> lg_step) & (even - 1);
+            none = i >= e || l >= nlev[i];
+        } else {
+            none = at >= (a < e ? start(e) - start(a) : 0);
+        }
+        if (none) lay.prow[p] = -1;
         lay.rowsum[p] = 0;
     }
+    if (lmax > 1) __syncthreads();  // the level counts have been looked at
     // where a source row starts takes the place of its level count (without LDS: of its own entry in the layout)
     int32_t *pstart = fast ? nlev : lay.src_pstart;
     for (int i = threadIdx.x; i < nbase; i += kPlanThreads) {
-        const int P = tmpP[i], ch = P / Cp, at = ch * chunk + (P - tmpP[chunk0[ch]]);
+        const int P = start(i), ch = chunk_of(P);
+        const int at = uniform ? (i >> lg_step << (lg_step + lg_even)) + (i & (step - 1)) : (ch << lg_chunk) + (P - start(chunk0[ch]));
         if (fast && slice == 0) {
             lay.src_nlev[i] = nlev[i];  // the GEMM epilogue reads both from memory
             lay.src_pstart[i] = at;
@@ -1026,25 +1066,25 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
         pstart[i] = at;
     }
     __syncthreads();
-    for (int R0 = me; R0 < count; R0 += step * V) {
+    for (int R0 = me; R0 < count; R0 += threads * V) {
         int root[V], ex[V];
 #pragma unroll
         for (int u = 0; u < V; ++u) {
-            const int R = R0 + u * step;
+            const int R = R0 + u * threads;
             root[u] = R < nbase ? R : R < count ? rows.root[R] : -1;
             ex[u] = R >= nbase && R < count ? rows.exp[R] : 0;
         }
 #pragma unroll
         for (int u = 0; u < V; ++u) {
             if (root[u] < 0) continue;
-            const int at = pstart[root[u]] + ex[u];
+            const int at = pstart[root[u]] + ex[u] * (uniform ? step : 1);
             lay.prow[at] = root[u] | (ex[u] << kProwLevel);
-            lay.row_phys[R0 + u * step] = at;
+            lay.row_phys[R0 + u * threads] = at;
         }
     }
     if (threadIdx.x == 0 && slice == 0) {
-        if (operand == 0) { hdr->Mp = Mp; hdr->mtiles = ntiles; hdr->lmaxA = lmax; }
-        else { hdr->Np = Mp; hdr->ntiles = ntiles; hdr->lmaxB = lmax; hdr->chunkB = chunk; }
+        if (operand == 0) { hdr->Mp = Mp; hdr->mtiles = ntiles; hdr->lmaxA = lmax; hdr->evenA = uniform ? even : 0; }
+        else { hdr->Np = Mp; hdr->ntiles = ntiles; hdr->lmaxB = lmax; hdr->chunkB = chunk; hdr->evenB = uniform ? even : 0; }
     }
 }
 
@@ -1815,6 +1855,7 @@ static size_t carve(Plan *p, char *base, bool own_statsA, bool own_statsB) {
         l.tile_src0 = cv.take<int32_t>(pc / kTile + 2);
         l.chunk_src0 = cv.take<int32_t>(pc / kChunk + 8);
         l.tile_flat = cv.take<int32_t>(pc / kTile + 2);
+        l.chunk_lev = cv.take<int32_t>(pc / kChunk + 8);
         l.rowsum = cv.take<unsigned long long>(pc);
         l.wavesum = cv.take<unsigned long long>((size_t)pc * ((phys_cap_cols(p->cap[CAP_C2]) + 1023) / 1024));
     }
@@ -1965,7 +2006,7 @@ __device__ bool keep_decide(const KeepArgs &k, const SlotSet &c1, PlanHeader *hd
             const PlanHeader &o = ks->saved;
             hdr->h_u = o.h_u; hdr->d_u = o.d_u; hdr->nobB = o.nobB; hdr->edgesB = o.edgesB; hdr->extras = o.extras;
             hdr->Np = o.Np; hdr->Kp = o.Kp; hdr->KA = o.KA; hdr->ldA = o.ldA; hdr->ldB = o.ldB;
-            hdr->ntiles = o.ntiles; hdr->lmaxB = o.lmaxB; hdr->chunkB = o.chunkB; hdr->ngroups = o.ngroups; hdr->nruns = o.nruns;
+            hdr->ntiles = o.ntiles; hdr->lmaxB = o.lmaxB; hdr->chunkB = o.chunkB; hdr->evenB = o.evenB; hdr->ngroups = o.ngroups; hdr->nruns = o.nruns;
         } else if (h) {
             hdr->h_u = h;
         }

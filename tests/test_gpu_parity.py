@@ -1039,6 +1039,55 @@ def test_gemm_tiles_of_either_size(imu, n, d, h, b, strategies):
         assert (np.abs(C_fp.cpu().numpy() - ref) <= REL_TOL * np.abs(ref)).all()
 
 
+@pytest.mark.parametrize("b,levels,few,splits,blev,fp6", [
+    (8, 1, 0, 0, 1, False),       # no row split, columns in place
+    (8, 1, 0, 30, 2, False),      # ... a few split rows of B in every tile
+    (8, 1, 40, 300, 2, False),    # rows of one and of two levels; more split columns in a tile than have strips
+    (8, 2, 5, 30, 2, False),      # nearly every row has two levels: two physical rows each
+    (8, 2, 900, 0, 1, False),     # too many have one: rows one behind the other, chunks of both kinds
+    (8, 3, 10, 0, 1, False),      # three levels in four physical rows
+    (8, 4, 100, 30, 2, False),    # four levels, with split columns too high for binary64
+    (8, 1, 0, 2885, 2, False), (8, 2, 2, 2890, 2, False), (8, 2, 1000, 2880, 2, False),  # the rows of B evenly laid out too
+    (8, 4, 9, 2890, 2, False), (8, 1, 0, 2890, 3, False), (6, 2, 0, 2800, 4, False),
+    (4, 4, 100, 30, 2, True), (4, 2, 3, 0, 1, True), (4, 3, 2900, 7, 2, True), (4, 6, 0, 3, 2, False),
+    (4, 4, 0, 2890, 4, True), (4, 2, 1, 2888, 3, True), (4, 1, 0, 2890, 2, True), (4, 3, 1500, 2890, 5, True),
+])
+def test_results_of_the_large_tiles_for_every_number_of_levels(imu, b, levels, few, splits, blev, fp6):
+    """The 256 x 256 tiles store from their registers where the source rows of a chunk have one, two or four levels each (and
+    those of B few splits, or two or four each), and through LDS elsewhere.  Odd sizes: the last tile has chunks without rows,
+    its columns end inside a quad.  The fp32 output has to be that of the call that also writes int64, bit for bit, and
+    nothing around C may be touched."""
+    n, d, h = 3003, 70, 2890
+    s = 1 << (b - 1)
+    rng = np.random.default_rng(b * 100 + levels * 10 + few)
+    Aq = rng.integers(-(s - 1), s, size=(n, d)).astype(np.int32)
+    Bq = rng.integers(-(s - 1), s, size=(h, d)).astype(np.int32)
+    deep = np.setdiff1d(np.arange(n), rng.choice(n, few, replace=False)) if levels > 1 else rng.choice(n, few, replace=False)
+    top = (s if levels > 1 else 1) if levels < 3 else s ** (levels - 1)
+    Aq[deep, rng.integers(0, d, deep.size)] = max(top, s) + rng.integers(0, s, deep.size)
+    if levels > 2:  # the few have a level less
+        rest = np.setdiff1d(np.arange(n), deep)
+        Aq[rest, 3] = s ** (levels - 2) + 1
+    if splits:
+        Bq[rng.choice(h, splits, replace=False), 5] = -3 * s ** (blev - 1) if blev > 1 else 0
+    want = oracle.int_gemm(Aq, Bq)
+    plan = imu.imunpack_plan(torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda(), b, ROW, ROW)
+    if fp6:
+        plan.set_digits(imu.DIGITS_FP6)
+    A_ue, B_eu = imu.imunpack_unpack(plan, torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda())
+    C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+    C_both = torch.full((n, h), -1.0, device="cuda")
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, C_int, C_both, None, fuse=True)
+    assert imu.imunpack_diag_gemm_parts(plan) == 1 and np.array_equal(C_int.cpu().numpy(), want)
+    around = torch.full((n * h + 2 * 4096,), -1.0, device="cuda")
+    C = around[4096:-4096].view(n, h)
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, None, C, None, fuse=True)
+    assert torch.equal(C, C_both)
+    assert bool((around[:4096] == -1).all()) and bool((around[-4096:] == -1).all())
+    ref = oracle.dequantize(want, 0.013, 0.0021)
+    assert (np.abs(C.cpu().numpy() - ref) <= REL_TOL * np.abs(ref)).all()
+
+
 @pytest.mark.parametrize("n,d,h,b,sa,sb,kind", [
     (5, 8200, 7, 8, COL, COL, "every"),     # more column slots than one workgroup lays out
     (5, 6140, 7, 8, COL, COL, "every"),     # just as many as it does
