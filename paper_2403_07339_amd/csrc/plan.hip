@@ -493,16 +493,23 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
     // If there are entries of three or more digits: the most that any row, any column holds.  The slot that a split appends
     // starts with those of the split slot that are left (entries only lose digits), so its count never exceeds this, and
     // slots with a larger count are taken before it whatever is split in between.
-    int deep_row = 0x7fffffff, deep_col = 0x7fffffff;
-    if (RES && deep) {
+    int deep_row = 0, deep_col = 0;
+    if (deep) {
         for (int x = threadIdx.x; x < rpad; x += kPlanThreads) rc[x] = 0;
         for (int x = threadIdx.x; x < cpad; x += kPlanThreads) cc[x] = 0;
         __syncthreads();
-        for (int e = threadIdx.x; e < Etotal; e += kPlanThreads) {
-            const unsigned lo = (unsigned)held[e], hi = (unsigned)(held[e] >> 32);
-            if (((lo >> kEdgeSlotBits) | ((hi >> kEdgeSlotBits) << 3)) > 2u) {
-                atomicAdd(&rc[lo & kEdgeSlotMask], 1);
-                atomicAdd(&cc[hi & kEdgeSlotMask], 1);
+        constexpr int UD = 8;
+        for (int e0 = threadIdx.x; e0 < Etotal; e0 += kPlanThreads * UD) {
+            unsigned long long ed[UD];
+#pragma unroll
+            for (int u = 0; u < UD; ++u) ed[u] = e0 + u * kPlanThreads < Etotal ? (RES ? held : list0)[e0 + u * kPlanThreads] : 0ull;
+#pragma unroll
+            for (int u = 0; u < UD; ++u) {
+                const unsigned lo = (unsigned)ed[u], hi = (unsigned)(ed[u] >> 32);
+                if (((lo >> kEdgeSlotBits) | ((hi >> kEdgeSlotBits) << 3)) > 2u) {
+                    atomicAdd(&rc[lo & kEdgeSlotMask], 1);
+                    atomicAdd(&cc[hi & kEdgeSlotMask], 1);
+                }
             }
         }
         __syncthreads();
@@ -566,7 +573,8 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
         // (2) slots with lo <= count <= hi are split in this batch, numbered in index order
         const int hi = isrow ? c0 : c1;
         int lo = isrow ? max(c1, 1) : c0 + 1;
-        if (deep) lo = min(hi, max(lo, isrow ? deep_row < hi ? deep_row + 1 : hi : deep_col < hi ? deep_col + 1 : hi));
+        const int least = (isrow ? deep_row : deep_col) + 1;  // appended slots hold fewer
+        lo = min(hi, max(lo, least));
         // (1b) While the sequential algorithm stays on one side, the counts of that side do not change (no
         // entry has three digits) and only the top count of the other side falls, so the next batch would
         // be of the same kind with a lower bound: rows with count >= G(lo), G(lo) = top column count once
@@ -574,11 +582,12 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
         // point of that recursion is split before the other side gets a turn, in (count descending, index)
         // order: one batch.  A read-only pass over the live entries evaluates G at lo, lo-1, lo-2, lo-3 at
         // once (four 8-bit counters per slot of the other side, kept in the unused upper half of that
-        // side's count vector), which usually covers several steps of the recursion.
+        // side's count vector), which usually covers several steps of the recursion.  (With entries of three digits the
+        // same holds down to `least`; such an entry outlives every bound.)
         // Tried only when the batch before was of the same kind: a side's first batch often is its only one.
         const bool again = prev_kind == (isrow ? 1 : 0);
         prev_kind = isrow ? 1 : 0;
-        if (LDS && !deep && E > 0 && lo > 1 && again) {
+        if (LDS && E > 0 && lo > max(least, 1) && again) {
             const int No = isrow ? nc : nr, No4 = (No + 3) & ~3;
             const int top_o = isrow ? c1 : c0;
             if (2 * No4 <= (isrow ? cpad : rpad) - 4 && top_o <= 255) {
@@ -588,11 +597,11 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
                 sync();
                 for (int round = 0; round < 256; ++round) {
                     int *T = s_T[round & 1];  // cleared above or during the round before
-                    auto count_pass = [&](auto isrow_c) __attribute__((always_inline)) {
-                        constexpr bool IR = decltype(isrow_c)::value;
-                        auto outlives = [&](unsigned xs, unsigned os, bool present) __attribute__((always_inline)) {
+                    auto count_pass = [&](auto isrow_c, auto deep_c) __attribute__((always_inline)) {
+                        constexpr bool IR = decltype(isrow_c)::value, DP = decltype(deep_c)::value;
+                        auto outlives = [&](unsigned xs, unsigned os, unsigned levels, bool present) __attribute__((always_inline)) {
                             const int c = cnt[xs];  // slot 0's count is harmless for an absent entry ...
-                            const int k = present ? min(4, max(0, lo - c)) : 0;  // the entry outlives the bounds lo, .., lo - k + 1
+                            const int k = !present ? 0 : DP && levels > 2u ? 4 : min(4, max(0, lo - c));  // the entry outlives the bounds lo, .., lo - k + 1
                             if (k) atomicAdd(reinterpret_cast<unsigned *>(&tmp[os]), 0x01010101u >> (8 * (4 - k)));
                         };
                         if constexpr (RES) {
@@ -602,8 +611,8 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
                                 for (int u = 0; u < UE; ++u) ed[u] = e0 + u * kPlanThreads < E ? held[e0 + u * kPlanThreads] : 0ull;
 #pragma unroll
                                 for (int u = 0; u < UE; ++u) {
-                                    const unsigned el = (unsigned)ed[u] & kEdgeSlotMask, eh = (unsigned)(ed[u] >> 32) & kEdgeSlotMask;
-                                    outlives(IR ? el : eh, IR ? eh : el, ed[u] != 0ull);
+                                    const unsigned wl = (unsigned)ed[u], wh = (unsigned)(ed[u] >> 32), el = wl & kEdgeSlotMask, eh = wh & kEdgeSlotMask;
+                                    outlives(IR ? el : eh, IR ? eh : el, (wl >> kEdgeSlotBits) | (wh >> kEdgeSlotBits << 3), ed[u] != 0ull);
                                 }
                             }
                             return;
@@ -625,13 +634,18 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
                             }
 #pragma unroll
                             for (int u = 0; u < 2 * UW; ++u) {
-                                const unsigned el = (unsigned)ed[u] & kEdgeSlotMask, eh = (unsigned)(ed[u] >> 32) & kEdgeSlotMask;
-                                outlives(IR ? el : eh, IR ? eh : el, ed[u] != 0ull);
+                                const unsigned wl = (unsigned)ed[u], wh = (unsigned)(ed[u] >> 32), el = wl & kEdgeSlotMask, eh = wh & kEdgeSlotMask;
+                                outlives(IR ? el : eh, IR ? eh : el, (wl >> kEdgeSlotBits) | (wh >> kEdgeSlotBits << 3), ed[u] != 0ull);
                             }
                         }
                     };
-                    if (isrow) count_pass(std::true_type{});
-                    else count_pass(std::false_type{});
+                    if (deep) {
+                        if (isrow) count_pass(std::true_type{}, std::true_type{});
+                        else count_pass(std::false_type{}, std::true_type{});
+                    } else {
+                        if (isrow) count_pass(std::true_type{}, std::false_type{});
+                        else count_pass(std::false_type{}, std::false_type{});
+                    }
                     sync();
                     int m0 = 0, m1 = 0, m2 = 0, m3 = 0;
                     if (threadIdx.x < 4) s_T[(round & 1) ^ 1][threadIdx.x] = 0;
@@ -662,13 +676,13 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
                     bool stable = false;
                     for (int j = 0; j < 4; j = lo - now) {  // T[j]: the other side's top count with the bound lo - j
                         const int t = T[j];
-                        const int next = isrow ? max(t, 1) : t + 1;
+                        const int next = max(isrow ? max(t, 1) : t + 1, least);
                         if (next >= now) {
                             stable = true;
                             break;
                         }
                         now = next;
-                        if (now <= 1) {  // nothing below: every slot that holds an entry is taken
+                        if (now <= max(least, 1)) {  // nothing below that may be taken (without longer entries: every slot that holds one is)
                             stable = true;
                             break;
                         }

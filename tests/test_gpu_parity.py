@@ -295,6 +295,29 @@ def rand_ints(rng, rows, cols, s, p_ob, depth):
     return np.where(mask, big, M).astype(np.int32)
 
 
+@pytest.mark.parametrize("n,d,h,share_a,share_b,longer,digits", [
+    (900, 1200, 80, 0.04, 0.01, 0.0, 3),      # more heavy hitters than LDS holds, none of three digits
+    (900, 1200, 80, 0.04, 0.01, 0.00002, 3),  # ... a few of three digits
+    (900, 1200, 80, 0.04, 0.01, 0.004, 4),    # ... several of up to four in one row and column
+    (60, 1500, 1100, 0.01, 0.03, 0.001, 3),   # the second operand, with repeated columns
+    (2500, 700, 40, 0.02, 0.02, 0.0005, 3),
+    (400, 300, 200, 0.05, 0.05, 0.002, 3),    # all of them in LDS
+])
+def test_greedy_with_entries_of_three_digits_and_many_heavy_hitters(imu, n, d, h, share_a, share_b, longer, digits):
+    """UnpackBoth takes many slots in one batch also where some entries keep heavy hitters in the slots that a split appends:
+    every split, in order, against Alg. 4 step by step.  Uneven rows and columns, so that both sides are split in turn."""
+    s = 128
+    rng = np.random.default_rng(n + d + digits)
+
+    def draw(rows, share):
+        M = rng.integers(-(s - 1), s, size=(rows, d))
+        uneven = (rng.random(d) ** 3 * 3)[None, :] * (rng.random(rows) ** 2 * 2)[:, None]
+        M = np.where(rng.random((rows, d)) < share * uneven, rng.integers(s, s * s, size=(rows, d)), M)
+        return np.where(rng.random((rows, d)) < longer, rng.integers(s * s, s ** digits, size=(rows, d)), M).astype(np.int32)
+
+    check_against_oracle(imu, draw(n, share_a), draw(h, share_b), 8, BOTH, BOTH)
+
+
 @pytest.mark.parametrize("sa,sb", list(itertools.product(STRATS, STRATS)))
 @pytest.mark.parametrize("b", [8, 4, 2])
 def test_small_random_all_strategies(imu, sa, sb, b):
