@@ -429,7 +429,7 @@ struct GreedyShared {
     int count;
 };
 
-template <bool LDS, bool RES>  // LDS: the counts are in LDS; RES: the edges too
+template <bool LDS, bool RES, bool SHORT>  // LDS: the counts are in LDS; RES: the edges too; SHORT: fewer variants of the passes
 __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_counts, GreedyShared &sh, int nob, int extras, const int deep) {
     constexpr int UE = 4;  // edges in LDS that a thread looks at together
     auto &s_top = sh.top;
@@ -502,7 +502,11 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
         for (int e0 = threadIdx.x; e0 < Etotal; e0 += kPlanThreads * UD) {
             unsigned long long ed[UD];
 #pragma unroll
-            for (int u = 0; u < UD; ++u) ed[u] = e0 + u * kPlanThreads < Etotal ? (RES ? held : list0)[e0 + u * kPlanThreads] : 0ull;
+            for (int u = 0; u < UD; ++u) {
+                const int e = e0 + u * kPlanThreads;
+                if constexpr (RES) ed[u] = e < Etotal ? held[e] : 0ull;
+                else ed[u] = e < Etotal ? list0[e] : 0ull;
+            }
 #pragma unroll
             for (int u = 0; u < UD; ++u) {
                 const unsigned lo = (unsigned)ed[u], hi = (unsigned)(ed[u] >> 32);
@@ -639,7 +643,7 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
                             }
                         }
                     };
-                    if (deep) {
+                    if (SHORT || deep) {
                         if (isrow) count_pass(std::true_type{}, std::true_type{});
                         else count_pass(std::false_type{}, std::true_type{});
                     } else {
@@ -926,8 +930,8 @@ __device__ __forceinline__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr
     deep = __syncthreads_or(deep);
     const long long E = (long long)nob + extras;
     const long long room = ((long long)g.lds_words - ((g.rows.cap + 7) & ~3) - ((g.cols.cap + 7) & ~3)) / 2;
-    if (MAY_HOLD && E <= room) greedy_run<LDS, MAY_HOLD>(g, hdr, lds_counts, sh, nob, extras, deep);
-    else greedy_run<LDS, false>(g, hdr, lds_counts, sh, nob, extras, deep);
+    if (MAY_HOLD && E <= room) greedy_run<LDS, MAY_HOLD, false>(g, hdr, lds_counts, sh, nob, extras, deep);
+    else greedy_run<LDS, false, LDS && !MAY_HOLD>(g, hdr, lds_counts, sh, nob, extras, deep);
 }
 
 template <bool LDS>
