@@ -26,9 +26,10 @@ __device__ __forceinline__ int32_t rtn_one(float x, float scale, int &bad) {
     return (int32_t)r;
 }
 
-// 16 bytes that are read exactly once
+// 16 bytes that are read exactly once (rows may start at any word: a wave reads a contiguous kilobyte either way)
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ int4 load_nt16(const int32_t *p) {
-    typedef int v4i_nt __attribute__((ext_vector_type(4)));
+    typedef v4i_any v4i_nt;
     const v4i_nt t = __builtin_nontemporal_load(reinterpret_cast<const v4i_nt *>(p));
     return make_int4(t[0], t[1], t[2], t[3]);
 }
@@ -67,34 +68,86 @@ __device__ __forceinline__ void flush_columns(int (&ccnt)[COLS_PER_LANE], int (&
 
 // OB entries found by a workgroup are staged in LDS and appended to the global list with a single
 // atomic per workgroup (one atomic per wave-row would serialise on the list's counter).
+// A list that is full only counts on: where most entries are heavy hitters (a weight at b = 6 whose step is fit to 255
+// levels: three quarters) the stage fills at once, and an atomic per entry behind it took 1.1 ms for 9688 x 576.
 constexpr int kObStage = 1024;
 struct ObStage {
     int count;
     int base;
+    int full;   // the list has no room left: its counter is at ob_cap or beyond
+    int extra;  // entries counted since, added to the counter at the end
     int32_t row[kObStage], col[kObStage], val[kObStage];
 };
 
-__device__ __forceinline__ void ob_push(ObStage *sg, int pos, int32_t r, int32_t c, int32_t v, int32_t *ob,
-                                        int ob_cap, int32_t *ob_count) {
+__device__ __forceinline__ void ob_begin(ObStage *sg) { sg->count = sg->full = sg->extra = 0; }
+
+__device__ __forceinline__ bool ob_full(const ObStage *sg) { return __hip_atomic_load(&sg->full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0; }
+
+// `count` entries of a wave take the positions from `base` on: those behind the stage go to the list itself, from this
+// position on (beyond ob_cap: nowhere).  All lanes of the wave, count > 0.
+__device__ __forceinline__ int ob_behind_stage(ObStage *sg, int base, int count, int ob_cap, int32_t *ob_count) {
+    const int n = base + count - max(base, kObStage);
+    int at = 0;
+    if (n > 0) {
+        const int lane = threadIdx.x & 63;
+        if (ob_full(sg)) {
+            if (lane == 0) atomicAdd(&sg->extra, n);
+            return ob_cap;
+        }
+        if (lane == 0) at = atomicAdd(ob_count, n);
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (lane == 0 && at + n >= ob_cap) __hip_atomic_store(&sg->full, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    return at;
+}
+
+// Entry at position `pos` of those that start at `base`; at: ob_behind_stage.
+__device__ __forceinline__ void ob_put(ObStage *sg, int pos, int base, int at, int32_t r, int32_t c, int32_t v, int32_t *ob, int ob_cap) {
     if (pos < kObStage) {
         sg->row[pos] = r;
         sg->col[pos] = c;
         sg->val[pos] = v;
-    } else {  // stage full (an almost entirely OB tile): append directly
-        const int g = atomicAdd(ob_count, 1);
-        if (g < ob_cap) {
-            ob[g] = r;
-            ob[ob_cap + g] = c;
-            ob[2 * ob_cap + g] = v;
-        }
+        return;
     }
+    const int g = at + pos - max(base, kObStage);
+    if (g < ob_cap) {
+        ob[g] = r;
+        ob[ob_cap + g] = c;
+        ob[2 * ob_cap + g] = v;
+    }
+}
+
+// One entry, at a position of the stage or behind it (the lanes that are here together share what that takes).
+__device__ __forceinline__ void ob_push(ObStage *sg, int pos, int32_t r, int32_t c, int32_t v, int32_t *ob, int ob_cap, int32_t *ob_count) {
+    if (pos < kObStage) {
+        sg->row[pos] = r;
+        sg->col[pos] = c;
+        sg->val[pos] = v;
+        return;
+    }
+    const unsigned long long here = __ballot(1);
+    const int lane = threadIdx.x & 63, lead = __builtin_ctzll(here), n = __popcll(here);
+    if (ob_full(sg)) {
+        if (lane == lead) atomicAdd(&sg->extra, n);
+        return;
+    }
+    int base = 0;
+    if (lane == lead) base = atomicAdd(ob_count, n);
+    base = __builtin_amdgcn_readlane(base, lead);
+    const int g = base + __popcll(here & ((1ull << lane) - 1ull));
+    if (g < ob_cap) {
+        ob[g] = r;
+        ob[ob_cap + g] = c;
+        ob[2 * ob_cap + g] = v;
+    }
+    if (lane == lead && base + n >= ob_cap) __hip_atomic_store(&sg->full, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 __device__ __forceinline__ void ob_flush(ObStage *sg, int32_t *ob, int ob_cap, int32_t *ob_count) {
     __syncthreads();
     const int n = min(sg->count, kObStage);
     if (n == 0) return;  // uniform
-    if (threadIdx.x == 0) sg->base = atomicAdd(ob_count, n);
+    if (threadIdx.x == 0) sg->base = atomicAdd(ob_count, n + sg->extra);  // (`extra` is only ever counted behind a full list)
     __syncthreads();
     const int base = sg->base;
     for (int t = threadIdx.x; t < n; t += blockDim.x) {
@@ -107,8 +160,8 @@ __device__ __forceinline__ void ob_flush(ObStage *sg, int32_t *ob, int ob_cap, i
     }
 }
 
-// Fast path: unit column stride, 16-byte aligned rows.  Workgroup = rows_per_wg rows x 256 columns;
-// a wave reads one 1 KiB row segment per instruction (float4 per lane).
+// Fast path: unit column stride.  Workgroup = rows_per_wg rows x 256 columns; a wave reads one 1 KiB row segment per
+// instruction (float4 per lane).  RAGGED: the last lane of a row may hold fewer than four columns.
 struct VecOperand {
     const void *X;
     int64_t rows, ldx;
@@ -133,7 +186,7 @@ __device__ __forceinline__ void move_to_item(VecOperand &a) {
     to_item(blockIdx.z * a.out_stride, a.scale_ptr, a.Q, a.rowcnt, a.colcnt, a.rowmax, a.colmax, a.ob, a.ob_count);
 }
 
-template <bool FROM_FLOAT>
+template <bool FROM_FLOAT, bool RAGGED>
 __device__ __forceinline__ void qscan_vec_body(const VecOperand &a, int64_t cols, int s, int by, int *lds, ObStage &stage) {
     const void *__restrict__ Xv = a.X;
     int32_t *__restrict__ Q = a.Q;
@@ -142,7 +195,7 @@ __device__ __forceinline__ void qscan_vec_body(const VecOperand &a, int64_t cols
     int32_t *ob = a.ob, *ob_count = a.ob_count;
     const int ob_cap = a.ob_cap, rows_per_wg = a.rows_per_wg;
     if (ob) {
-        if (threadIdx.x == 0) stage.count = 0;
+        if (threadIdx.x == 0) ob_begin(&stage);
         __syncthreads();
     }
     const float scale = step_of(a.scale_val, a.scale_ptr);
@@ -156,7 +209,8 @@ __device__ __forceinline__ void qscan_vec_body(const VecOperand &a, int64_t cols
     const int64_t r_end = min(rows, r_base + rows_per_wg);
     int ccnt[4] = {0, 0, 0, 0}, cmax[4] = {0, 0, 0, 0};
     int bad = 0;
-    const bool in_cols = c0 < cols;  // cols % 4 == 0 on this path
+    const bool in_cols = c0 < cols;
+    const int left = RAGGED ? (int)min((int64_t)4, cols - c0) : 4;
     // four rows per step: their loads are issued together, before any of them is used (keeping the next
     // step's loads in flight as well was slower: 0.113 against 0.105 ms for both operands of the benchmark)
     for (int64_t rb = r_base + wave; rb < r_end; rb += 16) {  // uniform per wave
@@ -165,8 +219,16 @@ __device__ __forceinline__ void qscan_vec_body(const VecOperand &a, int64_t cols
         for (int v = 0; v < 4; ++v) {
             const int64_t r = rb + 4 * v;
             raw[v] = make_int4(0, 0, 0, 0);
-            if (in_cols && r < r_end)  // read once: non-temporal (0.125 -> 0.109 ms)
-                raw[v] = load_nt16(reinterpret_cast<const int32_t *>(Xv) + r * ldx + c0);
+            if (in_cols && r < r_end) {  // read once: non-temporal (0.125 -> 0.109 ms)
+                const int32_t *at = reinterpret_cast<const int32_t *>(Xv) + r * ldx + c0;
+                if (!RAGGED || left == 4) {
+                    raw[v] = load_nt16(at);
+                } else {
+                    raw[v].x = at[0];
+                    if (left > 1) raw[v].y = at[1];
+                    if (left > 2) raw[v].z = at[2];
+                }
+            }
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -178,7 +240,14 @@ __device__ __forceinline__ void qscan_vec_body(const VecOperand &a, int64_t cols
                 q.y = rtn_one(__int_as_float(raw[v].y), scale, bad);
                 q.z = rtn_one(__int_as_float(raw[v].z), scale, bad);
                 q.w = rtn_one(__int_as_float(raw[v].w), scale, bad);
-                *reinterpret_cast<int4 *>(Q + r * ldq + c0) = q;
+                int32_t *to = Q + r * ldq + c0;
+                if (!RAGGED || left == 4) {
+                    *reinterpret_cast<v4i_any *>(to) = v4i_any{q.x, q.y, q.z, q.w};
+                } else {
+                    to[0] = q.x;
+                    if (left > 1) to[1] = q.y;
+                    if (left > 2) to[2] = q.z;
+                }
             }
             const int a0 = iabs_sat(q.x), a1 = iabs_sat(q.y), a2 = iabs_sat(q.z), a3 = iabs_sat(q.w);
             const int o0 = a0 >= s, o1 = a1 >= s, o2 = a2 >= s, o3 = a3 >= s;
@@ -200,13 +269,14 @@ __device__ __forceinline__ void qscan_vec_body(const VecOperand &a, int64_t cols
                 int base = 0;
                 if (lane == 0) base = atomicAdd(&stage.count, rc);
                 base = __builtin_amdgcn_readfirstlane(base);
+                const int at = ob_behind_stage(&stage, base, rc, ob_cap, ob_count);
                 const unsigned long long below = (1ull << lane) - 1ull;
                 const int p0 = base + __popcll(b0 & below), p1 = base + n0 + __popcll(b1 & below),
                           p2 = base + n0 + n1 + __popcll(b2 & below), p3 = base + n0 + n1 + n2 + __popcll(b3 & below);
-                if (o0) ob_push(&stage, p0, (int32_t)r, (int32_t)c0, q.x, ob, ob_cap, ob_count);
-                if (o1) ob_push(&stage, p1, (int32_t)r, (int32_t)(c0 + 1), q.y, ob, ob_cap, ob_count);
-                if (o2) ob_push(&stage, p2, (int32_t)r, (int32_t)(c0 + 2), q.z, ob, ob_cap, ob_count);
-                if (o3) ob_push(&stage, p3, (int32_t)r, (int32_t)(c0 + 3), q.w, ob, ob_cap, ob_count);
+                if (o0) ob_put(&stage, p0, base, at, (int32_t)r, (int32_t)c0, q.x, ob, ob_cap);
+                if (o1) ob_put(&stage, p1, base, at, (int32_t)r, (int32_t)(c0 + 1), q.y, ob, ob_cap);
+                if (o2) ob_put(&stage, p2, base, at, (int32_t)r, (int32_t)(c0 + 2), q.z, ob, ob_cap);
+                if (o3) ob_put(&stage, p3, base, at, (int32_t)r, (int32_t)(c0 + 3), q.w, ob, ob_cap);
             }
         }
     }
@@ -216,26 +286,27 @@ __device__ __forceinline__ void qscan_vec_body(const VecOperand &a, int64_t cols
     if (FROM_FLOAT && status && __ballot(bad) && lane == 0) atomicOr(status, 1);
 }
 
-template <bool FROM_FLOAT>
+template <bool FROM_FLOAT, bool RAGGED>
 __global__ __launch_bounds__(256) void qscan_vec_kernel(VecOperand a, int64_t cols, int s) {
     __shared__ int lds[2 * 4 * 256];
     __shared__ ObStage stage;
     move_to_item(a);
-    qscan_vec_body<FROM_FLOAT>(a, cols, s, blockIdx.y, lds, stage);
+    qscan_vec_body<FROM_FLOAT, RAGGED>(a, cols, s, blockIdx.y, lds, stage);
 }
 
 // Both operands of a product (same inner dimension) in one launch: the row blocks of the second follow
 // those of the first, so that the end of the one overlaps the start of the other.
+template <bool RAGGED>
 __global__ __launch_bounds__(256) void qscan_vec_pair_kernel(VecOperand a, VecOperand b, int64_t cols, int s) {
     __shared__ int lds[2 * 4 * 256];
     __shared__ ObStage stage;
     const int by = blockIdx.y;
     if (by < a.row_blocks) {
         move_to_item(a);
-        qscan_vec_body<true>(a, cols, s, by, lds, stage);
+        qscan_vec_body<true, RAGGED>(a, cols, s, by, lds, stage);
     } else {
         move_to_item(b);
-        qscan_vec_body<true>(b, cols, s, by - a.row_blocks, lds, stage);
+        qscan_vec_body<true, RAGGED>(b, cols, s, by - a.row_blocks, lds, stage);
     }
 }
 
@@ -256,23 +327,23 @@ __global__ __launch_bounds__(256) void qscan_tile_kernel(const void *Xv, int64_t
     __shared__ int lds[2 * 4 * 64];
     __shared__ ObStage stage;
     const float scale = step_of(scale_val, scale_ptr);
-    if (ob && threadIdx.x == 0) stage.count = 0;  // published by the barrier after the tile is filled
+    if (ob && threadIdx.x == 0) ob_begin(&stage);  // published by the barrier after the tile is filled
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
     int bad = 0;
     const bool along_rows = (sx_r == 1 && sx_c != 1);  // unit stride runs down the rows
+    int32_t raw[16];  // all sixteen loads of a lane in flight (one after the other: 17 us for 1000 x 1031)
+#pragma unroll
     for (int it = 0; it < 16; ++it) {
         const int a = wave + 4 * it;  // slow index of this pass
-        const int rr = along_rows ? lane : a;
-        const int cc = along_rows ? a : lane;
-        const int64_t r = r0 + rr, c = c0 + cc;
-        int32_t q = 0;
-        if (r < rows && c < cols) {
-            if (FROM_FLOAT)
-                q = rtn_one(reinterpret_cast<const float *>(Xv)[r * sx_r + c * sx_c], scale, bad);
-            else
-                q = reinterpret_cast<const int32_t *>(Xv)[r * sx_r + c * sx_c];
-        }
+        const int64_t r = r0 + (along_rows ? lane : a), c = c0 + (along_rows ? a : lane);
+        raw[it] = r < rows && c < cols ? reinterpret_cast<const int32_t *>(Xv)[r * sx_r + c * sx_c] : 0;
+    }
+#pragma unroll
+    for (int it = 0; it < 16; ++it) {
+        const int a = wave + 4 * it, rr = along_rows ? lane : a, cc = along_rows ? a : lane;
+        int32_t q = raw[it];
+        if (FROM_FLOAT) q = r0 + rr < rows && c0 + cc < cols ? rtn_one(__int_as_float(q), scale, bad) : 0;
         tile[rr][cc] = q;
     }
     __syncthreads();
@@ -298,8 +369,8 @@ __global__ __launch_bounds__(256) void qscan_tile_kernel(const void *Xv, int64_t
             int base = 0;
             if (lane == 0) base = atomicAdd(&stage.count, rc);
             base = __builtin_amdgcn_readfirstlane(base);
-            const int pos = base + __popcll(bo & ((1ull << lane) - 1ull));
-            if (o) ob_push(&stage, pos, (int32_t)r, (int32_t)c, q, ob, ob_cap, ob_count);
+            const int at = ob_behind_stage(&stage, base, rc, ob_cap, ob_count), pos = base + __popcll(bo & ((1ull << lane) - 1ull));
+            if (o) ob_put(&stage, pos, base, at, (int32_t)r, (int32_t)c, q, ob, ob_cap);
         }
     }
     if (ob) ob_flush(&stage, ob, ob_cap, ob_count);
@@ -327,7 +398,7 @@ __global__ __launch_bounds__(kTrThreads) void qscan_tr_kernel(const void *Xv, in
     __shared__ int32_t tile[kTrTile * kTrPitch];  // [column][row]
     __shared__ ObStage stage;
     const float scale = step_of(scale_val, scale_ptr);
-    if (ob && threadIdx.x == 0) stage.count = 0;  // published by the barrier after the tile is filled
+    if (ob && threadIdx.x == 0) ob_begin(&stage);  // published by the barrier after the tile is filled
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int half = lane >> 5, l32 = lane & 31;
     const int64_t r0 = (int64_t)blockIdx.x * kTrTile, c0 = (int64_t)blockIdx.y * kTrTile;
@@ -383,12 +454,10 @@ __global__ __launch_bounds__(kTrThreads) void qscan_tr_kernel(const void *Xv, in
                 if (rowmax && rm) atomicMax(&rowmax[r], rm);
             }
         }
-        if (ob && any) {
+        if (ob && any) {  // (a position at a time: with the positions of a wave's entries taken together 57 -> 80 us at 4096 x 8192)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (o[i])
-                    ob_push(&stage, atomicAdd(&stage.count, 1), (int32_t)r, (int32_t)(cl + i), q[i], ob, ob_cap,
-                            ob_count);
+                if (o[i]) ob_push(&stage, atomicAdd(&stage.count, 1), (int32_t)r, (int32_t)(cl + i), q[i], ob, ob_cap, ob_count);
         }
     }
     if (ob) ob_flush(&stage, ob, ob_cap, ob_count);
@@ -490,16 +559,15 @@ static int zero_stats(const imunpack_stats_t *st, int64_t rows, int64_t cols, in
     return zero_listed(z, list_stats(z, 0, st, rows, cols, bt.flag ? nullptr : status), bt.nitems, stream);
 }
 
-// The operand's description for the fast path, if it qualifies (unit column stride, rows and pointers
-// aligned to 16 bytes).
+// The operand's description for the fast path, if it qualifies (unit column stride).
 template <bool FROM_FLOAT>
 static bool vec_operand(VecOperand &o, const void *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, float scale,
                         const float *scale_dev, int32_t *Q, int64_t ldq, const imunpack_stats_t *st, int32_t *status,
                         int64_t x_stride, const QuantBatch &bt) {
-    const bool vec = sx_c == 1 && (cols % 4) == 0 && (sx_r % 4) == 0 && ((uintptr_t)X % 16) == 0 && (x_stride % 16) == 0 &&
-                     (!FROM_FLOAT || ((ldq % 4) == 0 && ((uintptr_t)Q % 16) == 0));
-    if (!vec) return false;
-    int64_t rpw = 64;  // 16, 32 and 128 rows per workgroup were all slower
+    if (sx_c != 1) return false;
+    // 64 rows to a workgroup (16, 32 and 128 were all slower), but 16, one step of its waves, where there would be fewer than
+    // two workgroups per CU: what a step waits for comes one after the other then (both operands of 256 x 256: 16 -> 9 us)
+    int64_t rpw = (rows + 63) / 64 * ((cols + 255) / 256) * bt.nitems < 512 ? 16 : 64;
     if ((rows + rpw - 1) / rpw > 32767) rpw = ((rows + 32766) / 32767 + 3) / 4 * 4;
     int32_t *ob = (st && st->ob && st->ob_count && st->ob_cap > 0) ? st->ob : nullptr;
     o = VecOperand{X, rows, sx_r, scale, scale_dev, Q, ldq,
@@ -522,9 +590,9 @@ static int check_qscan_args(const void *X, int64_t rows, int64_t cols, int64_t s
 template <bool FROM_FLOAT>
 int run_qscan(const void *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t sx_c, float scale,
               const float *scale_dev, int b, int32_t *Q, int64_t ldq, const imunpack_stats_t *st, int32_t *status,
-              int64_t x_stride, const QuantBatch &bt, hipStream_t stream) {
+              int64_t x_stride, const QuantBatch &bt, hipStream_t stream, bool cleared = false) {
     IMU_TRY(check_qscan_args<FROM_FLOAT>(X, rows, cols, sx_r, sx_c, scale, scale_dev, b, Q, ldq, st));
-    IMU_TRY(zero_stats(st, rows, cols, FROM_FLOAT ? status : nullptr, bt, stream));
+    if (!cleared) IMU_TRY(zero_stats(st, rows, cols, FROM_FLOAT ? status : nullptr, bt, stream));
     if (rows == 0 || cols == 0) return IMUNPACK_OK;
     const unsigned items = (unsigned)bt.nitems;
     if (bt.flag) status = bt.flag;
@@ -538,7 +606,8 @@ int run_qscan(const void *X, int64_t rows, int64_t cols, int64_t sx_r, int64_t s
     VecOperand vo;
     if (vec_operand<FROM_FLOAT>(vo, X, rows, cols, sx_r, sx_c, scale, scale_dev, Q, ldq, st, status, x_stride, bt)) {
         dim3 grid((unsigned)((cols + 255) / 256), (unsigned)vo.row_blocks, items);
-        hipLaunchKernelGGL(qscan_vec_kernel<FROM_FLOAT>, grid, dim3(256), 0, stream, vo, cols, s);
+        if (cols % 4) hipLaunchKernelGGL((qscan_vec_kernel<FROM_FLOAT, true>), grid, dim3(256), 0, stream, vo, cols, s);
+        else hipLaunchKernelGGL((qscan_vec_kernel<FROM_FLOAT, false>), grid, dim3(256), 0, stream, vo, cols, s);
     } else if (sx_r == 1 && (rows % 4) == 0 && (cols % 4) == 0 && (sx_c % 4) == 0 && ((uintptr_t)X % 16) == 0 && (x_stride % 16) == 0 &&
                (!FROM_FLOAT || ((ldq % 4) == 0 && ((uintptr_t)Q % 16) == 0)) && (cols + kTrTile - 1) / kTrTile <= 65535) {
         dim3 grid((unsigned)((rows + kTrTile - 1) / kTrTile), (unsigned)((cols + kTrTile - 1) / kTrTile), items);
@@ -567,19 +636,19 @@ int quantize_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float s
     const bool paired = n > 0 && h > 0 && d > 0 &&
                         vec_operand<true>(va, A, n, d, sa_r, sa_c, scale_A, scale_A_dev, QA, ldqa, stA, stat_a, bt.a_stride, bt) &&
                         vec_operand<true>(vb, B, h, d, sb_r, sb_c, scale_B, scale_B_dev, QB, ldqb, stB, stat_b, bt.b_stride, bt);
-    if (!paired) {
-        IMU_TRY(run_qscan<true>(A, n, d, sa_r, sa_c, scale_A, scale_A_dev, b, QA, ldqa, stA, stat_a, bt.a_stride, bt, stream));
-        return run_qscan<true>(B, h, d, sb_r, sb_c, scale_B, scale_B_dev, b, QB, ldqb, stB, stat_b, bt.b_stride, bt, stream);
-    }
     ZeroList z;
     z.stride = bt.out_stride;
-    if (bt.flag) stat_a = stat_b = nullptr;
-    const int64_t la = list_stats(z, 0, stA, n, d, stat_a), lb = list_stats(z, 6, stB, h, d, stat_b);
+    const int64_t la = list_stats(z, 0, stA, n, d, bt.flag ? nullptr : stat_a), lb = list_stats(z, 6, stB, h, d, bt.flag ? nullptr : stat_b);
     IMU_TRY(zero_listed(z, std::max(la, lb), bt.nitems, stream));
+    if (!paired) {
+        IMU_TRY(run_qscan<true>(A, n, d, sa_r, sa_c, scale_A, scale_A_dev, b, QA, ldqa, stA, stat_a, bt.a_stride, bt, stream, true));
+        return run_qscan<true>(B, h, d, sb_r, sb_c, scale_B, scale_B_dev, b, QB, ldqb, stB, stat_b, bt.b_stride, bt, stream, true);
+    }
     const bool b_first = vb.row_blocks > va.row_blocks;  // the longer operand first: the shorter one fills its tail
     const VecOperand &first = b_first ? vb : va, &second = b_first ? va : vb;
     dim3 grid((unsigned)((d + 255) / 256), (unsigned)(first.row_blocks + second.row_blocks), (unsigned)bt.nitems);
-    hipLaunchKernelGGL(qscan_vec_pair_kernel, grid, dim3(256), 0, stream, first, second, d, 1 << (b - 1));
+    if (d % 4) hipLaunchKernelGGL(qscan_vec_pair_kernel<true>, grid, dim3(256), 0, stream, first, second, d, 1 << (b - 1));
+    else hipLaunchKernelGGL(qscan_vec_pair_kernel<false>, grid, dim3(256), 0, stream, first, second, d, 1 << (b - 1));
     return launch_status();
 }
 

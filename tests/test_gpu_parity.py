@@ -154,6 +154,53 @@ def test_ob_entry_list_for_every_input_layout(imu, shape, b, frac):
         assert sorted(zip(ob[0].tolist(), ob[1].tolist(), ob[2].tolist())) == want_set
 
 
+@pytest.mark.parametrize("shape,pitch", [((37, 1031), 1031), ((700, 261), 263), ((5, 3), 7), ((1100, 1), 5), ((64, 514), 514), ((2100, 258), 259)])
+def test_quantize_rows_that_start_anywhere(imu, shape, pitch):
+    """Rows of a length and a pitch that are no multiples of four, from an odd address, in blocks of 16 and of 64 rows, into
+    rows of integers like that: integers, statistics, the list, and nothing beside them."""
+    rows, cols = shape
+    g = torch.Generator().manual_seed(rows + cols)
+    x = torch.randn(shape, generator=g)
+    x[torch.rand(shape, generator=g) < 0.02] *= 300.0
+    buf = torch.full((rows * pitch + 9,), float("nan"), device="cuda")
+    view = buf[3:3 + rows * pitch].view(rows, pitch)[:, :cols]
+    view.copy_(dev(x))
+    want = oracle_quant(x, np.float32(0.021))
+    around = torch.full((rows * cols + 10,), 77, dtype=torch.int32, device="cuda")
+    Q = around[5:5 + rows * cols].view(rows, cols)
+    st = imu.Stats.empty(rows, cols, view.device, ob_cap=rows * cols)
+    _, st, status = imu.imunpack_quantize(view, 0.021, 8, Q, st)
+    assert int(status.item()) == 0 and np.array_equal(Q.cpu().numpy(), want)
+    assert bool((around[:5] == 77).all()) and bool((around[-5:] == 77).all())
+    rc, cc, rm, cm = np_stats(want, 128)
+    assert np.array_equal(st.rowcnt.cpu().numpy(), rc) and np.array_equal(st.colcnt.cpu().numpy(), cc)
+    assert np.array_equal(st.rowmax.cpu().numpy(), rm) and np.array_equal(st.colmax.cpu().numpy(), cm)
+    n_ob = int(st.ob_count.item())
+    ii, jj = np.nonzero(np.abs(want.astype(np.int64)) >= 128)
+    ob = st.ob[:, :n_ob].cpu().numpy()
+    assert sorted(zip(ob[0].tolist(), ob[1].tolist(), ob[2].tolist())) == sorted(zip(ii.tolist(), jj.tolist(), want[ii, jj].tolist()))
+
+
+@pytest.mark.parametrize("cap", [1, 1000, 70000, 229632, 229633, 400000])
+@pytest.mark.parametrize("layout", ["rows", "columns", "neither"])
+def test_list_of_an_operand_of_nothing_but_heavy_hitters(imu, layout, cap):
+    """Far more entries than a workgroup stages, with no room, some, just enough and plenty: all are counted, the list holds as
+    many as it has room for, each once."""
+    rows, cols = 897, 256
+    x = torch.arange(rows * cols, dtype=torch.float32).view(rows, cols) + 200.0  # every entry is one, all different
+    view = dev(x) if layout == "rows" else dev(x.t().contiguous()).t()
+    if layout == "neither":
+        view = torch.zeros(rows, 2 * cols, device="cuda")
+        view[:, ::2] = dev(x)
+        view = view[:, ::2]
+    st = imu.Stats.empty(rows, cols, view.device, ob_cap=cap)
+    st.ob.fill_(-1)
+    Q, st, _ = imu.imunpack_quantize(view, 1.0, 8, stats=st)
+    assert int(st.ob_count.item()) == rows * cols
+    ob = st.ob[:, :min(cap, rows * cols)].cpu().numpy()
+    assert len(set(ob[2].tolist())) == ob.shape[1] and np.array_equal(ob[2], ob[0] * cols + ob[1] + 200)
+
+
 @pytest.mark.parametrize("scale,lo_exp,negate", [(1.0, 21, False), (0.75, 21, True), (0.0371, -3, False)])
 def test_quantize_every_float_of_two_binades(imu, scale, lo_exp, negate):
     """Every binary32 value of two adjacent binades (2 x 2^23 bit patterns) through the quantizer: the
