@@ -17,6 +17,8 @@
 //     former, fixup_kernel then places the higher digits of the listed OB entries.
 #include "common.h"
 
+#include <type_traits>
+
 #include <algorithm>
 #include <chrono>
 #include <cstddef>
@@ -37,6 +39,17 @@ namespace imu {
 constexpr int kScatterThreads = 256;
 constexpr int kScatterWaves = kScatterThreads / 64;
 constexpr int kBandRows = 2;  // divides kTile: the padded row counts are multiples of it
+// Stores of at most 512 columns leave half of such a wave's lanes or more without a unit.  NARROW: 8, 16, 32 or 64 lanes to a band,
+// as many as it has units for, and so up to eight bands to a wave (the two products of attention on 48 heads of 197 tokens,
+// six-bit: 33 + 38 us with a wave to every band).
+constexpr int kNarrow = 512;
+__host__ __device__ inline int lg_band_lanes(int W) { return W <= 128 ? 3 : W <= 256 ? 4 : W <= 512 ? 5 : 6; }
+__host__ __device__ inline int scatter_items(int rows, int W, bool narrow) {
+    const int bands = rows / kBandRows;
+    if (!narrow) return bands * ((W + 1023) / 1024);
+    const int per = 64 >> lg_band_lanes(W);
+    return (bands + per - 1) / per;
+}
 
 struct ScatterArgs {
     const int32_t *M;            // the int32 operand, row-major
@@ -50,7 +63,7 @@ struct ScatterArgs {
     int rows, W, ld, s, sh;      // physical rows, stored columns, bytes from one row of `out` to the next
     int nwin;                    // windows of 1024 stored columns
     int fp6;                     // store 6-bit floating-point codes (12 bytes per unit) instead of int8 digits
-    int items;                   // waves that serve this operand: (rows / kBandRows) * nwin
+    int items;                   // waves that serve this operand
     int8_t *out;
     unsigned long long *wavesum; // [rows][nwin]: every wave leaves its part of the row norm
     // batch (blockIdx.y is the item): the sizes above differ from item to item and come from its header
@@ -59,6 +72,7 @@ struct ScatterArgs {
     int64_t m_stride, stride, out_stride;  // bytes from item to item: M, the plan's arrays, `out`
 };
 
+template <bool NARROW>
 __device__ __forceinline__ void sizes_of_item(ScatterArgs &a) {
     if (!a.out) {  // nothing to do for this operand
         a.items = 0;
@@ -69,7 +83,7 @@ __device__ __forceinline__ void sizes_of_item(ScatterArgs &a) {
     a.W = a.op ? h.Kp : h.KA;
     a.ld = header_pitch(h, a.fp6, a.op);
     a.nwin = (a.W + 1023) / 1024;
-    a.items = (a.rows / kBandRows) * a.nwin;
+    a.items = scatter_items(a.rows, a.W, NARROW);
 }
 
 typedef int v4i_u __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any int boundary
@@ -130,13 +144,15 @@ __device__ __forceinline__ unsigned long long sat44(unsigned long long m, unsign
     return t < (1ull << 44) ? t : (1ull << 44);
 }
 
-// One wave's work: band and window `item` of operand a.
-template <bool DENSE>
+// One wave's work: band and window `item` of operand a (NARROW: the bands of group `item`).
+template <bool DENSE, bool NARROW>
 __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int lane) {
-    const int band = item / a.nwin, win = item - band * a.nwin;
     const int nunits = a.W >> 4;
-    const int upos = win * 64 + lane;
-    const bool inside = upos < nunits;
+    const int lg = NARROW ? lg_band_lanes(a.W) : 6;
+    const int band = NARROW ? (item << (6 - lg)) + (lane >> lg) : item / a.nwin, win = NARROW ? 0 : item - band * a.nwin;
+    const int upos = NARROW ? lane & ((1 << lg) - 1) : win * 64 + lane;
+    const bool there = !NARROW || band * kBandRows < a.rows;
+    const bool inside = upos < nunits && there;
     const int4 ud = inside ? a.unit[upos] : make_int4(-1, -1, 7, 0);
     const int q0 = upos * 16;
     const int kfirst = ud.x, kany = ud.y;
@@ -157,8 +173,8 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
         // ---- both rows' loads first
 #pragma unroll
         for (int h = 0; h < RS; ++h) {
-            const int p = __builtin_amdgcn_readfirstlane(p_first + r0 + h);
-            const int row = a.prow[p];
+            const int p = NARROW ? p_first + r0 + h : __builtin_amdgcn_readfirstlane(p_first + r0 + h);
+            const int row = there ? a.prow[p] : -1;
             er[h] = row < 0 ? 0 : row >> kProwLevel;
             si[h] = row < 0 ? 0 : row & ((1 << kProwLevel) - 1);
             // padding row, padding unit, or (UnpackBoth operands hold digit 0 at level (0, 0) only; every
@@ -251,6 +267,12 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
                 }
             }
             // ---- the wave's part of the row norm
+            if constexpr (NARROW) {  // over the lanes of the band
+                unsigned long long sum = wsum + sat44(mag, wgt);
+                for (int off = 1; off < 1 << lg; off <<= 1) sum += (unsigned long long)__shfl_xor((long long)sum, off, 64);
+                if (there && upos == 0) a.wavesum[p] = sum < (1ull << 44) ? sum : 1ull << 44;
+                continue;
+            }
             const unsigned long long nz = __ballot(mag != 0 || wsum != 0);
             unsigned long long total = 0;
             if (nz != 0) {
@@ -273,7 +295,7 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
 }
 
 // Two operands in one launch when they take the same variant: waves below a0.items serve a0, the rest a1.
-template <bool DENSE>
+template <bool DENSE, bool NARROW>
 __global__ __launch_bounds__(kScatterThreads) void scatter_kernel(ScatterArgs a0, ScatterArgs a1) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int item = (int)blockIdx.x * kScatterWaves + wave;
@@ -281,17 +303,17 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_kernel(ScatterArgs a0
     const ScatterArgs &a = second ? a1 : a0;
     if (second) item -= a0.items;
     if (item >= a.items) return;  // uniform per wave; no barriers anywhere
-    scatter_item<DENSE>(a, item, (int)(threadIdx.x & 63));
+    scatter_item<DENSE, NARROW>(a, item, (int)(threadIdx.x & 63));
 }
 
 // The same for the items of a batch, whose sizes come from their headers (a kernel of its own: the waves are too
 // short to hide a further dependent read where it is not needed).
-template <bool DENSE>
+template <bool DENSE, bool NARROW>
 __global__ __launch_bounds__(kScatterThreads) void scatter_batch_kernel(ScatterArgs a0, ScatterArgs a1) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int item = (int)blockIdx.x * kScatterWaves + wave;
-    sizes_of_item(a0);
-    sizes_of_item(a1);
+    sizes_of_item<NARROW>(a0);
+    sizes_of_item<NARROW>(a1);
     const bool second = item >= a0.items;
     ScatterArgs a = second ? a1 : a0;
     if (second) item -= a0.items;
@@ -303,7 +325,7 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_batch_kernel(ScatterA
     a.unit = item_at(a.unit, off); a.unit_w = item_at(a.unit_w, off);
     a.out = item_at(a.out, blockIdx.y * a.out_stride);
     a.wavesum = item_at(a.wavesum, off);
-    scatter_item<DENSE>(a, item, (int)(threadIdx.x & 63));
+    scatter_item<DENSE, NARROW>(a, item, (int)(threadIdx.x & 63));
 }
 
 // Places the digits above digit 0 of the listed OB entries of an operand unpacked by UnpackBoth.
@@ -575,6 +597,13 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     memset(sc, 0, sizeof(sc));
     bool launch[2] = {false, false}, dense[2] = {false, false};
     int most_rows = 0;  // physical rows of both operands, in the largest item
+    int least = 1 << 30, widest = 0;  // stored columns of either operand
+    for (unsigned i = 0; i < nitems; ++i) {
+        const PlanHeader &hi = batch ? p->pin_hdr[i] : h;
+        least = std::min(least, std::min((int)hi.Kp, (int)hi.KA));
+        widest = std::max(widest, std::max((int)hi.Kp, (int)hi.KA));
+    }
+    const bool narrow = least <= kNarrow && widest <= 1024;
     for (int op = 0; op < 2; ++op) {
         const RowLayout &lay = op ? p->layB : p->layA;
         const bool both = (op ? p->sB : p->sA) == IMUNPACK_BOTH;
@@ -595,7 +624,7 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
         int nob = 0;
         for (unsigned i = 0; i < nitems; ++i) {  // the launch covers the largest item
             const PlanHeader &hi = batch ? p->pin_hdr[i] : h;
-            a.items = std::max(a.items, ((op ? hi.Np : hi.Mp) / kBandRows) * (((op ? hi.Kp : hi.KA) + 1023) / 1024));
+            a.items = std::max(a.items, scatter_items(op ? hi.Np : hi.Mp, op ? hi.Kp : hi.KA, narrow));
             nob = std::max(nob, (int)(op ? hi.nobB : hi.nobA));
             most_rows = std::max(most_rows, hi.Mp + hi.Np);
         }
@@ -624,10 +653,15 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     }
     auto scatter = [&](const ScatterArgs &x, const ScatterArgs &y, int items, bool dns) {
         const dim3 grid((unsigned)((items + kScatterWaves - 1) / kScatterWaves), nitems);
-        if (batch && dns) hipLaunchKernelGGL(scatter_batch_kernel<true>, grid, dim3(kScatterThreads), 0, st, x, y);
-        else if (batch) hipLaunchKernelGGL(scatter_batch_kernel<false>, grid, dim3(kScatterThreads), 0, st, x, y);
-        else if (dns) hipLaunchKernelGGL(scatter_kernel<true>, grid, dim3(kScatterThreads), 0, st, x, y);
-        else hipLaunchKernelGGL(scatter_kernel<false>, grid, dim3(kScatterThreads), 0, st, x, y);
+        auto go = [&](auto dense_c, auto narrow_c) {
+            constexpr bool D = decltype(dense_c)::value, N = decltype(narrow_c)::value;
+            if (batch) hipLaunchKernelGGL((scatter_batch_kernel<D, N>), grid, dim3(kScatterThreads), 0, st, x, y);
+            else hipLaunchKernelGGL((scatter_kernel<D, N>), grid, dim3(kScatterThreads), 0, st, x, y);
+        };
+        if (dns && narrow) go(std::true_type{}, std::true_type{});
+        else if (dns) go(std::true_type{}, std::false_type{});
+        else if (narrow) go(std::false_type{}, std::true_type{});
+        else go(std::false_type{}, std::false_type{});
     };
     ScatterArgs none;
     memset(&none, 0, sizeof(none));

@@ -365,6 +365,15 @@ def test_greedy_with_entries_of_three_digits_and_many_heavy_hitters(imu, n, d, h
     check_against_oracle(imu, draw(n, share_a), draw(h, share_b), 8, BOTH, BOTH)
 
 
+@pytest.mark.parametrize("d", [1, 120, 128, 250, 380, 512, 640, 1000, 1030])
+@pytest.mark.parametrize("sa,sb", [(ROW, ROW), (COL, ROW), (BOTH, ROW)])
+def test_stores_of_every_width(imu, d, sa, sb):
+    """Stores of one to eight blocks of 128 columns, where a wave of the scatter takes eight bands to half a band, and operands
+    of different widths in one launch: digits, padding, norms and the product."""
+    rng = np.random.default_rng(d)
+    check_against_oracle(imu, rand_ints(rng, 150, d, 128, 0.004, 2), rand_ints(rng, 90, d, 128, 0.004, 3), 8, sa, sb)
+
+
 @pytest.mark.parametrize("sa,sb", list(itertools.product(STRATS, STRATS)))
 @pytest.mark.parametrize("b", [8, 4, 2])
 def test_small_random_all_strategies(imu, sa, sb, b):
