@@ -130,7 +130,11 @@ __device__ __forceinline__ bool sel_pick(const unsigned *hist, int nbins, unsign
     if (threadIdx.x == 0) lds[16] = 0xffffffffu;
     __syncthreads();
     unsigned run = incl - (c0 + c1);
-    for (int w = 0; w < wave; ++w) run += lds[w];
+#pragma unroll
+    for (int w = 0; w < kSelThreads / 64 - 1; ++w) {  // all read at once, not one behind the other
+        const unsigned c = lds[w];
+        if (w < wave) run += c;
+    }
     if (k > run && k <= run + c0 + c1) {  // at most one thread
         const bool first = k <= run + c0;
         lds[16] = (unsigned)b0 + (first ? 0u : 1u);
@@ -236,6 +240,7 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(SelArgs args)
                 prefix[q] = (q ? p1 : p0) | (bin << shift);
             }
         }
+        if (pass + 1 == passes) break;
         __syncthreads();
         for (int i = threadIdx.x; i < 2 * 2048; i += kSelThreads) (&hist[0][0])[i] = 0;
         __syncthreads();
