@@ -340,6 +340,56 @@ __global__ __launch_bounds__(kPlanThreads) void level_major_kernel(
     level_major<16>(set, maxabs, via, via ? hdr->d1 : n_host, sh, tmpL, tmpCur, hdr, which, lds);
 }
 
+// Both operands in one launch, where neither is unpacked by UnpackBoth.  Workgroup 0 takes the first operand and what needs
+// its columns, workgroup 1, beside it, a second operand that does not: its rows, or its columns where the first operand
+// leaves the columns as they are.  (One behind the other: 17 + 5 us for 12608 rows and 768 columns, 6 + 5 + 3 for 1031 columns
+// and 777 rows; most of a launch this short is its start.)
+struct LevelPair {
+    SlotSet a, b, c1, c2;              // c1, c2: column slots of A's unpacking, of the second one
+    const int32_t *max_a, *max_b;
+    int strategyA, strategyB, n, d, h, sh;
+    int32_t *tmpL, *tmpCur;
+    PlanHeader *hdr;
+    int64_t stride, stats_stride;
+};
+constexpr int kPairItems = 8;  // items a thread holds: more, and what chooses between the operands no longer fits the registers
+__global__ __launch_bounds__(kPlanThreads) void level_major_pair_kernel(LevelPair f) {
+    __shared__ int lds[40];
+    PlanHeader *hdr = f.hdr + blockIdx.y;
+    const int64_t off = blockIdx.y * f.stride, soff = blockIdx.y * f.stats_stride;
+    move_to_item(f.a, off);
+    move_to_item(f.b, off);
+    move_to_item(f.c1, off);
+    move_to_item(f.c2, off);
+    f.max_a = item_at(f.max_a, soff);
+    f.max_b = item_at(f.max_b, soff);
+    f.tmpL = item_at(f.tmpL, off);
+    f.tmpCur = item_at(f.tmpCur, off);
+    const bool by_row = f.strategyA == IMUNPACK_ROW, b_by_row = f.strategyB == IMUNPACK_ROW;
+    // workgroup 0: A, then what of B needs A's columns; workgroup 1: what does not (one call of level_major: with several the
+    // compiler leaves it out of line and its arguments in scratch memory, 17 -> 52 us)
+    bool second = blockIdx.x == 1;
+    for (;; second = true) {
+        SlotSet set = second ? (b_by_row ? f.b : f.c2) : by_row ? f.a : f.c1;
+        const bool via = second && blockIdx.x == 0;
+        const int N = via ? hdr->d1 : second ? (b_by_row ? f.h : f.d) : by_row ? f.n : f.d;
+        level_major<kPairItems>(set, second ? f.max_b : f.max_a, via ? f.c1.root : nullptr, N, f.sh, f.tmpL, f.tmpCur, hdr,
+                                second ? (b_by_row ? CAP_ROWB : CAP_C2) : by_row ? CAP_ROWA : CAP_C1, lds);
+        if (second || (by_row && !b_by_row)) return;
+        __syncthreads();
+        if (hdr->d1 > f.c1.cap) return;  // reported: the plan is made again
+        if (b_by_row) break;
+    }
+    // the second unpacking splits no column: its column slots are those that A's left
+    const int N = hdr->d1;
+    if (N > f.c2.cap) {
+        if (threadIdx.x == 0) flag_overflow(hdr, CAP_C2, N);
+        return;
+    }
+    for (int x = threadIdx.x; x < N; x += kPlanThreads) identity_slot(f.c2, x);
+    if (threadIdx.x == 0) hdr->d_u = N;
+}
+
 // ---------------------------------------------------------------------------------------------
 // UnpackBoth (Alg. 4): the greedy
 // ---------------------------------------------------------------------------------------------
@@ -2320,7 +2370,20 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
         hipLaunchKernelGGL(level_major_kernel, dim3(1, items), dim3(kPlanThreads), 0, st, set, maxabs, via, count, p->sh,
                            p->tmpL, p->tmpCur, hdr, which, skip, stride, sstride);
     };
-    if (at_once) {}  // the first operand is unpacked, the second is to be unpacked anew
+    const bool pair = !keep && !listA && !listB && !scanA && !scanB && std::max(std::max(n, h), d) <= kPairItems * kPlanThreads;
+    if (pair) {
+        LevelPair f;
+        f.a = p->rowA; f.b = p->rowB; f.c1 = p->c1; f.c2 = p->c2;
+        f.max_a = p->statsA[p->sA == IMUNPACK_ROW ? 2 : 3]; f.max_b = p->statsB[p->sB == IMUNPACK_ROW ? 2 : 3];
+        f.strategyA = p->sA; f.strategyB = p->sB;
+        f.n = n; f.d = d; f.h = h; f.sh = p->sh;
+        f.tmpL = p->tmpL; f.tmpCur = p->tmpCur;
+        f.hdr = hdr;
+        f.stride = stride; f.stats_stride = sstride;
+        const bool beside = p->sB == IMUNPACK_ROW || p->sA == IMUNPACK_ROW;
+        hipLaunchKernelGGL(level_major_pair_kernel, dim3(beside ? 2 : 1, items), dim3(kPlanThreads), 0, st, f);
+    }
+    else if (at_once) {}  // the first operand is unpacked, the second is to be unpacked anew
     else if (p->sA == IMUNPACK_ROW) closed_form(p->rowA, p->statsA[2], nullptr, n, CAP_ROWA, nullptr);
     else if (p->sA == IMUNPACK_COL) closed_form(p->c1, p->statsA[3], nullptr, d, CAP_C1, nullptr);
     else if (callerA) IMU_TRY(run_greedy(p, 1, stA->ob, (int)stA->ob_cap, stA->ob_count, sstride, CAP_LISTA, st));
@@ -2331,7 +2394,8 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
         hipLaunchKernelGGL(keep_decide_kernel, dim3(1), dim3(kPlanThreads), 0, st, keep_args, p->c1, hdr, p->rowB);
         skip = &p->d_keep->same;
     }
-    if (p->sB == IMUNPACK_ROW) {
+    if (pair) {
+    } else if (p->sB == IMUNPACK_ROW) {
         closed_form(p->rowB, p->statsB[2], nullptr, h, CAP_ROWB, skip);
         hipLaunchKernelGGL(identity_slots_kernel, dim3(grid_for(p->cap[CAP_C2], 256, 64), items), dim3(256), 0, st,
                            p->c2, hdr, skip, stride);
