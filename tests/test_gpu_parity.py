@@ -374,6 +374,15 @@ def test_stores_of_every_width(imu, d, sa, sb):
     check_against_oracle(imu, rand_ints(rng, 150, d, 128, 0.004, 2), rand_ints(rng, 90, d, 128, 0.004, 3), 8, sa, sb)
 
 
+@pytest.mark.parametrize("n,d,h", [(1, 1, 1), (40, 8191, 24), (24, 8192, 24), (40, 8193, 24), (8192, 40, 16), (16, 40, 8193)])
+@pytest.mark.parametrize("sa,sb", list(itertools.product([ROW, COL], [ROW, COL])))
+def test_rows_and_columns_planned_in_one_launch(imu, n, d, h, sa, sb):
+    """On either side of the 8192 rows and columns up to which one launch unpacks both operands; the second one splits the
+    columns that the first one left, which are more than 8192 where the first one split some."""
+    rng = np.random.default_rng(n + d + h)
+    check_against_oracle(imu, rand_ints(rng, n, d, 128, 0.0005, 2), rand_ints(rng, h, d, 128, 0.0005, 3), 8, sa, sb)
+
+
 @pytest.mark.parametrize("sa,sb", list(itertools.product(STRATS, STRATS)))
 @pytest.mark.parametrize("b", [8, 4, 2])
 def test_small_random_all_strategies(imu, sa, sb, b):
