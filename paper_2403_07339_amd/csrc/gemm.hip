@@ -71,6 +71,7 @@ struct GemmArgs {
     int32_t *meet, *sums;
     int most_parts;
     int evenB;                // PlanHeader::evenB
+    int whole_rows;           // results without levels to fold leave row by row (see whole_rows_win)
     int lmaxA;                // largest number of digit levels of a row of A
     int kwaves;               // gemm_small_kernel: waves that share the contraction
     // benchmark reporting: if set, workgroup 0 writes {shader clock ticks, 100 MHz wall ticks} of its K loop
@@ -585,7 +586,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     //     cycles instead of 34 000 (4096 x 8228 by 11013: 357 and 325 us).  With levels there is a half of that or less, and
     //     the non-temporal ones leave the last-level cache to the operands: a step of 12608 x 768 by 3072 226 and 233 us.
     // (2) Through LDS ([64][256] int32, rows padded to 260) for everything else: int64 results, rows of several kinds in a chunk,
-    //     many split columns.  Global stores are row-contiguous, any levels can be added up (the planner keeps a source row in one
+    //     many split columns, results without levels of large products (whole_rows_win).  Global stores are row-contiguous, any levels can be added up (the planner keeps a source row in one
     //     chunk, a source column in one tile).
     RowLayout layA = g.layA, layB = g.layB;
     float *C_fp = g.C_fp;
@@ -670,7 +671,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         for (int c = 0; c < 4; ++c) {
             const bool rows = meta(c + 1) > meta(c);  // (a chunk of nothing but padding stores nothing, and no resource is made for it)
             const int lev = fits && rows ? meta(8 + c) : 0;
-            const bool ok = ((lev == 1 && !evenB) || (fold_f64 && (lev == 1 || lev == 2 || lev == 4))) && nsplit <= kStrips;
+            // (with nothing to fold, one by one only where the stores may stay in the caches)
+            const bool plain = lev == 1 && !evenB;
+            const bool ok = (plain ? !g.whole_rows || nsplit > 0 : fold_f64 && (lev == 1 || lev == 2 || lev == 4)) && nsplit <= kStrips;
             direct |= (!rows || ok) << c;
             filled |= rows << c;
         }
@@ -1351,6 +1354,17 @@ extern "C" int imunpack_recombine(const imunpack_plan_t *p, const void *workspac
 }
 
 namespace imu {
+// Whether results that have no levels to fold go through LDS and out as non-temporal rows of a kilobyte.  From the registers they
+// are ordinary stores (non-temporal lines of 128 bytes are slow), the faster way for the kernel (4096 x 8228 by 11013: 310 and
+// 322 us), but they stay in the last-level cache of 256 MB, and what a step reads again, the operands and their integers, does
+// not: the scatter and quantise behind that product 90 and 98 us instead of 83 and 93.  The line lies between what was measured,
+// in bytes of operands, integers and results (rows by columns of A by rows of B, a step through the registers and through LDS):
+// 235 MB 182 and 188 us (4096 x 1024 by 8192), 251 MB 186 and 188 (12608 x 768 by 3072), 402 MB 275 and 265 (8192 x 1024 by 8192),
+// 439 MB 340 and 326 (1024 x 4096 by 11008), 675 MB 753 and 752, 450 and 444 with resident weights (4096 x 4096 by 11008).
+static bool whole_rows_win(const Plan *p) {
+    const double d = (double)p->d, rows = (double)p->n + (double)p->h;
+    return 8.0 * rows * d + 4.0 * (double)p->n * (double)p->h > 320e6;
+}
 // What the fused launch of one plan takes from its header.
 static void fused_args(GemmArgs &g, const Plan *p) {
     const PlanHeader &h = p->hdr;
@@ -1360,6 +1374,7 @@ static void fused_args(GemmArgs &g, const Plan *p) {
     g.Np = h.Np;
     g.lmaxA = h.lmaxA;
     g.evenB = h.evenB;
+    g.whole_rows = whole_rows_win(p);
     g.guard_mul = p->s - 1;
     g.kt0 = 0; g.kt1 = h.Kp / BK;
     g.nbound = 0;

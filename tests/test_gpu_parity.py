@@ -374,6 +374,28 @@ def test_stores_of_every_width(imu, d, sa, sb):
     check_against_oracle(imu, rand_ints(rng, 150, d, 128, 0.004, 2), rand_ints(rng, 90, d, 128, 0.004, 3), 8, sa, sb)
 
 
+@pytest.mark.parametrize("h", [6000, 6001])
+@pytest.mark.parametrize("split_rows", [0, 40])
+def test_large_products_without_levels_leave_by_rows(imu, h, split_rows):
+    """Products whose operands outgrow the last-level cache: results go out row by row, ragged ends and some rows of two
+    levels on either side among them.  The integer product is exact in binary64 (below 2^31), so the result is too but for its
+    one rounding."""
+    n, d = 4140, 4100
+    g = torch.Generator(device="cuda").manual_seed(h + split_rows)
+    A = torch.randint(-127, 128, (n, d), generator=g, device="cuda", dtype=torch.int32)
+    B = torch.randint(-127, 128, (h, d), generator=g, device="cuda", dtype=torch.int32)
+    for X in (A, B):
+        at = torch.randperm(X.shape[0], generator=g, device="cuda")[:split_rows]
+        X[at, at % d] = 700
+    plan = imu.imunpack_plan(A, B, 8, ROW, ROW)
+    A_ue, B_eu = imu.imunpack_unpack(plan, A, B)
+    C = torch.full((n + 1, h), 3.5, device="cuda")
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, None, C[:n], None)
+    scale = float(np.float32(0.013)) * float(np.float32(0.0021))
+    assert torch.equal(C[:n], ((A.double() @ B.double().t()) * scale).float())
+    assert (C[n] == 3.5).all()
+
+
 @pytest.mark.parametrize("n,d,h", [(1, 1, 1), (40, 8191, 24), (24, 8192, 24), (40, 8193, 24), (8192, 40, 16), (16, 40, 8193)])
 @pytest.mark.parametrize("sa,sb", list(itertools.product([ROW, COL], [ROW, COL])))
 def test_rows_and_columns_planned_in_one_launch(imu, n, d, h, sa, sb):
