@@ -1103,7 +1103,7 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
         }
     if (operand == 0) {  // a slice looks at the rows of its share of the chunks (all in one: 20 -> 24 us at 8880 rows of two and three levels)
         const int each = (nchunks + nslices - 1) / nslices, c0 = min(slice * each, nchunks), c1 = min(c0 + each, nchunks);
-        for (int ch = c0 + threadIdx.x; ch < c1; ch += kPlanThreads) lay.chunk_lev[ch] = uniform ? even : nlev[chunk0[ch]];
+        for (int ch = c0 + threadIdx.x; ch < c1; ch += kPlanThreads) lay.chunk_lev[ch] = uniform ? even : lmax == 1 ? 1 : nlev[chunk0[ch]];
         if (!uniform && lmax > 1 && c0 < c1) {
             __syncthreads();
             for (int i = chunk0[c0] + threadIdx.x; i < chunk0[c1]; i += kPlanThreads) {
@@ -1126,7 +1126,7 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
         if (none) lay.prow[p] = -1;
         lay.rowsum[p] = 0;
     }
-    if (lmax > 1) __syncthreads();  // the level counts have been looked at
+    if (lmax > 1) __syncthreads();  // the level counts have been looked at (where no row is split, nobody does)
     // where a source row starts takes the place of its level count (without LDS: of its own entry in the layout)
     int32_t *pstart = fast ? nlev : lay.src_pstart;
     for (int i = threadIdx.x; i < nbase; i += kPlanThreads) {
