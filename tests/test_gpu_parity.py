@@ -992,6 +992,39 @@ def test_batched_items_that_differ(imu, b, strategies):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("b,beta", [(8, 31.0), (4, 5.0)])
+@pytest.mark.parametrize("n,d,h,kinds", [
+    # levels of most rows and how many rows have one (of one level: two), of A and of B
+    (1030, 70, 1027, [((1, 0), (1, 12)), ((2, 4), (2, 0)), ((4, 0), (1, 0)), ((2, 500), (1, 0)), ((1, 0), (4, 3)), ((3, 0), (2, 300))]),
+    # rows so few that three levels take four physical rows as well
+    (16, 40, 21, [((la, 0), (lb, 0)) for la in (1, 2, 3, 4) for lb in (1, 2, 3, 4)] * 9),
+])
+def test_batched_items_of_large_tiles_that_differ(imu, n, d, h, kinds, b, beta):
+    """Batches of more than 128 tiles of 256 x 256 (up to which the small ones run): rows of one to four levels, evenly laid out
+    or not, of several kinds, a few split rows of B and many, from item to item, int8 and six-bit digits.  Items against
+    the oracle chain, and bit for bit what they give in a batch of their own."""
+    s = 1 << (b - 1)
+    g = torch.Generator().manual_seed(n + b)
+    assert -(-n // 256) * -(-h // 256) * len(kinds) > 128
+    a, bt = (torch.randn((len(kinds), rows, d), generator=g).clamp_(-2.5, 2.5) for rows in (n, h))
+    for i, sides in enumerate(kinds):
+        for x, (levels, few) in zip((a[i], bt[i]), sides):
+            others = torch.randperm(x.shape[0], generator=g)
+            deep, digits = (others[few:], levels) if levels > 1 else (others[:few], 2)
+            if deep.numel():
+                x[deep, torch.randint(0, d, (deep.numel(),), generator=g)] = 2.0 * 1.96 / (beta / 2) * s ** (digits - 1)
+            q = oracle_quant(x, oracle.rtn_step(oracle.percentile_alpha(x.numpy(), 95.0), beta))
+            top = np.abs(q.astype(np.int64)).max(1)
+            own = 1 + sum((top >= s ** l).astype(int) for l in range(1, 6))
+            assert (own[deep.numpy()] == digits).all() and (own == 1).sum() == x.shape[0] - deep.numel()
+    out = imu.imunpack_gemm_batched(dev(a), dev(bt), 95.0, beta, beta, b, ROW, ROW, ctx=imu.BatchContext())
+    for i in range(min(len(kinds), 32)):
+        alone = imu.imunpack_gemm_batched(dev(a[i:i + 1]), dev(bt[i:i + 1]), 95.0, beta, beta, b, ROW, ROW, ctx=imu.BatchContext())
+        assert torch.equal(out[i], alone[0]), i
+        want = _oracle_matmul(a[i].numpy(), bt[i].numpy(), 95.0, beta, beta)
+        assert (np.abs(out[i].cpu().numpy().astype(np.float64) - want) <= REL_TOL * np.abs(want)).all(), i
+
+
 def test_batched_more_items_than_one_group(imu):
     """A batch of more items than share one set of launches, of the smallest shapes."""
     g = torch.Generator().manual_seed(31)
@@ -1155,7 +1188,7 @@ def test_gemm_tiles_of_either_size(imu, n, d, h, b, strategies):
     (8, 1, 40, 300, 2, False),    # rows of one and of two levels; more split columns in a tile than have strips
     (8, 2, 5, 30, 2, False),      # nearly every row has two levels: two physical rows each
     (8, 2, 900, 0, 1, False),     # too many have one: rows one behind the other, chunks of both kinds
-    (8, 3, 10, 0, 1, False),      # three levels in four physical rows
+    (8, 3, 10, 0, 1, False),      # three levels: four physical rows each would take more chunks
     (8, 4, 100, 30, 2, False),    # four levels, with split columns too high for binary64
     (8, 1, 0, 2885, 2, False), (8, 2, 2, 2890, 2, False), (8, 2, 1000, 2880, 2, False),  # the rows of B evenly laid out too
     (8, 4, 9, 2890, 2, False), (8, 1, 0, 2890, 3, False), (6, 2, 0, 2800, 4, False),
@@ -1323,6 +1356,68 @@ def test_gemm_whose_last_round_is_cut_along_the_contraction(imu, n, d, h, b, str
     for C_int in outs:
         assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), want)
         assert torch.equal(C_int, outs[0])
+
+
+def _rows_of_levels(rng, rows, d, s, levels, few):
+    """In-Bound integers, one entry of `levels` digits in every row but in `few`, which have a digit less (levels == 1: more)."""
+    M = rng.integers(-(s - 1), s, size=(rows, d)).astype(np.int32)
+    others = rng.choice(rows, few, replace=False)
+    own = np.full(rows, levels)
+    own[others] = levels - 1 if levels > 1 else 2
+    deep = np.flatnonzero(own > 1)
+    M[deep, rng.integers(0, d, deep.size)] = s ** (own[deep] - 1) + rng.integers(0, s, deep.size)
+    return M
+
+
+@pytest.mark.parametrize("n,d,h,b,lev_a,few_a,lev_b,few_b,every", [
+    (2001, 7000, 2000, 8, 1, 0, 1, 0, False),     # nothing split
+    (2001, 7000, 2000, 8, 1, 0, 1, 30, False),    # a few split rows of B in every tile
+    (1001, 7000, 2003, 8, 2, 3, 1, 0, False),     # rows of A of two levels, evenly laid out
+    (501, 7000, 2003, 8, 4, 9, 1, 0, False),      # ... of four and a few of three
+    (1500, 7000, 2003, 8, 1, 500, 1, 0, False),   # chunks of rows of one and of two levels
+    (2003, 7000, 1001, 8, 1, 0, 2, 0, False),     # rows of B of two levels, evenly laid out
+    (2003, 7000, 1001, 8, 1, 0, 4, 2, False),     # ... of four
+    (1003, 7000, 1001, 8, 2, 0, 2, 1, False),     # ... on either side
+    (2001, 3500, 2000, 8, 1, 0, 1, 0, True),      # two exponent groups of one width: a part ends before the last group
+    (2001, 3500, 1001, 8, 1, 0, 2, 0, True),
+    (2001, 12000, 2000, 4, 1, 0, 1, 0, False),    # six-bit digits
+    (2001, 12000, 2000, 4, 1, 0, 1, 30, False),
+    (501, 12000, 2003, 4, 4, 9, 1, 0, False),
+    (1003, 12000, 1001, 4, 2, 0, 2, 1, False),
+    (2003, 12000, 1001, 4, 1, 0, 4, 2, False),
+    (2001, 6000, 1001, 4, 1, 0, 2, 0, True),
+])
+def test_fp32_results_of_tiles_in_parts(imu, n, d, h, b, lev_a, few_a, lev_b, few_b, every):
+    """The last part of a tile adds the sums of the others and stores fp32 results from its registers where the levels of the
+    tile's rows allow it: rows of one, two and four levels on either side, split columns, both digit formats, parts that end
+    before the last exponent group.  Bit for bit what the call gives that also writes int64 (through LDS); nothing
+    around C is touched."""
+    s = 1 << (b - 1)
+    rng = np.random.default_rng(n + d + h + b + few_b)
+    Aq, Bq = _rows_of_levels(rng, n, d, s, lev_a, few_a), _rows_of_levels(rng, h, d, s, lev_b, few_b)
+    if every:
+        Aq[n // 2] = s
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    plan = imu.imunpack_plan(Qa, Qb, b, COL if every else ROW, ROW)
+    if b <= 4:
+        plan.set_digits(imu.DIGITS_FP6)
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    assert plan.fusable()
+    C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+    C_both = torch.full((n, h), -1.0, device="cuda")
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, C_int, C_both, None, fuse=True)
+    assert imu.imunpack_diag_gemm_parts(plan) > 1
+    around = torch.full((n * h + 2 * 4096,), -1.0, device="cuda")
+    C = around[4096:-4096].view(n, h)
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, None, C, None, fuse=True)
+    assert imu.imunpack_diag_gemm_parts(plan) > 1
+    assert torch.equal(C, C_both)
+    assert bool((around[:4096] == -1).all()) and bool((around[-4096:] == -1).all())
+    rows = np.unique(np.concatenate([np.arange(0, n, 61), [n // 2, n - 1]]))
+    want = oracle.int_gemm(Aq[rows], Bq)
+    assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), want)
+    ref = oracle.dequantize(want, 0.013, 0.0021)
+    assert (np.abs(C[torch.from_numpy(rows).cuda()].cpu().numpy() - ref) <= REL_TOL * np.abs(ref)).all()
 
 
 def test_products_in_parts_from_two_threads(imu):
