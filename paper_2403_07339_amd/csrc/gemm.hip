@@ -154,7 +154,12 @@ __device__ __forceinline__ void store_inside4(const float (&f)[4], __amdgpu_buff
     for (int k = 0; k < 4; ++k) x[k] = __float_as_int(f[k]);
     __builtin_amdgcn_raw_buffer_store_b128(x, to, (int)off, 0, 2);
 }
-constexpr unsigned kOutside = 0x80000000u;  // an offset that stays outside with the offset of a row (below 2^30) added
+// An offset that stays outside with the offset of a row added: a chunk of C ends below 2^31 bytes and no row is asked for further
+// than kRowsAhead behind a chunk, so that the sum stays below 2^32 and at 2^31 or beyond.
+constexpr unsigned kOutside = 0x80000000u;
+constexpr int64_t kDirectPitch = 1 << 22;  // results leave by 32-bit offsets where a row of C is shorter (in elements)
+constexpr int kRowsAhead = 16;
+static_assert((kChunk + kRowsAhead) * kDirectPitch * (int64_t)sizeof(float) < (int64_t)kOutside, "offsets of rows");
 
 __device__ __forceinline__ const int8_t *uniform_ptr(const int8_t *p) {
     const uint64_t v = (uint64_t)p;
@@ -583,11 +588,14 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     //     row decided by itself); 25344 x 768 by 3072 rows 124 -> 107 us, 16384 x 3072 (six-bit) by 4096 512 -> 442 (of
     //     which three tile rows that even rows save), 8192 x 8448 by 4096 266 -> 213.
     //     Without levels to fold the stores are ordinary ones: 256 KiB a CU at once as non-temporal lines of 128 bytes take 45 000
-    //     cycles instead of 34 000 (4096 x 8228 by 11013: 357 and 325 us).  With levels there is a half of that or less, and
+    //     cycles instead of 34 000 (4096 x 8228 by 11013, one run: 344 and 317 us).  With levels there is a half of that or less, and
     //     the non-temporal ones leave the last-level cache to the operands: a step of 12608 x 768 by 3072 226 and 233 us.
+    //     The price is code: nine pairs of levels times four blocks of rows, straight down, make this kernel 170 kB (50 with the
+    //     ways through LDS alone) and spill 5 vector registers (31 six-bit, 49 and 35 in parts, 10 and 45 in a batch), all of them
+    //     behind the walk along the contraction.
     // (2) Through LDS ([64][256] int32, rows padded to 260) for everything else: int64 results, rows of several kinds in a chunk,
-    //     many split columns, results without levels of large products (whole_rows_win).  Global stores are row-contiguous, any levels can be added up (the planner keeps a source row in one
-    //     chunk, a source column in one tile).
+    //     many split columns, results without levels of large products (whole_rows_win).  Global stores are row-contiguous, any
+    //     levels can be added up (the planner keeps a source row in one chunk, a source column in one tile).
     RowLayout layA = g.layA, layB = g.layB;
     float *C_fp = g.C_fp;
     int final_shift = g.final_shift, fold_f64 = g.fold_f64, evenB = g.evenB;
@@ -617,7 +625,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     // The short way out of a chunk whose source rows have one, two or four levels each: a lane holds four physical rows side
     // by side of a column, that is whole source rows, and stores their results itself.
     int direct = 0, filled = 0;  // a bit per chunk: stored from the registers (or nothing to store); holds source rows
-    const bool fits = C_fp && !g.C_int && g.ldc < (1 << 22);  // fp32 alone, and a chunk of C spans less than 2^30 bytes
+    const bool fits = C_fp && !g.C_int && g.ldc < kDirectPitch;  // fp32 alone, and a chunk of C spans no more than 2^30 bytes
     // the split ones among the tile's 256 physical columns, and the first of each source column
     auto find_split = [&](unsigned long long (&split)[4], unsigned long long (&heads)[4]) __attribute__((always_inline)) {
         int prow[4], next[4];
@@ -828,6 +836,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                 using T = decltype(zero);
                 constexpr bool F = decltype(flat_c)::value;  // source columns = physical columns
                 constexpr int U = 4, RS = kGemmThreads / 64;
+                static_assert((U - 1) * RS <= kRowsAhead, "rows asked for behind a chunk");
                 const int j4 = lane * 4, left = nsrcB - j4;
                 // fp32 alone and no quad that ends inside: one store a row, what is outside dropped by the hardware
                 const bool quads = fits && (nsrcB & 3) == 0;
@@ -1355,12 +1364,15 @@ extern "C" int imunpack_recombine(const imunpack_plan_t *p, const void *workspac
 
 namespace imu {
 // Whether results that have no levels to fold go through LDS and out as non-temporal rows of a kilobyte.  From the registers they
-// are ordinary stores (non-temporal lines of 128 bytes are slow), the faster way for the kernel (4096 x 8228 by 11013: 310 and
-// 322 us), but they stay in the last-level cache of 256 MB, and what a step reads again, the operands and their integers, does
-// not: the scatter and quantise behind that product 90 and 98 us instead of 83 and 93.  The line lies between what was measured,
-// in bytes of operands, integers and results (rows by columns of A by rows of B, a step through the registers and through LDS):
-// 235 MB 182 and 188 us (4096 x 1024 by 8192), 251 MB 186 and 188 (12608 x 768 by 3072), 402 MB 275 and 265 (8192 x 1024 by 8192),
-// 439 MB 340 and 326 (1024 x 4096 by 11008), 675 MB 753 and 752, 450 and 444 with resident weights (4096 x 4096 by 11008).
+// are ordinary stores (non-temporal lines of 128 bytes are slow), the faster way for the kernel (4096 x 8228 by 11013: 309 and
+// 320 us, in a run of few steps 327 and 338), but they stay in the last-level cache of 256 MB, and what a step reads again, the
+// operands and their integers, does not: the scatter and quantise behind that product 90 and 97 us instead of 84 and 93.  The line
+// lies where the two meet, in bytes of operands, integers and results (rows by columns of A by rows of B, a step through the registers and through LDS, means of
+// three turns that differ by 1 to 3 %): 235 MB 184 and 188 us (4096 x 1024 by 8192), 251 MB 184 and 187 (12608 x 768 by 3072),
+// 302 MB 236 and 238 (4096 x 2048 by 7168), 319 MB 219 and 216 (8192 x 1024 by 6144), 341 MB 281 and 281 (6000 x 2048 by 6000),
+// 361 MB 257 and 258 (8192 x 1024 by 7168), 403 MB 273 and 267 (8192 x 1024 by 8192), 439 MB 343 and 327 (1024 x 4096 by 11008),
+// 675 MB 754 and 753, 450 and 440 with resident weights (4096 x 4096 by 11008).  Batches of several items, whose products are
+// small beside that cache one by one, were not measured and stay with the registers.
 static bool whole_rows_win(const Plan *p) {
     const double d = (double)p->d, rows = (double)p->n + (double)p->h;
     return 8.0 * rows * d + 4.0 * (double)p->n * (double)p->h > 320e6;
@@ -1393,7 +1405,9 @@ static void fused_args(GemmArgs &g, const Plan *p) {
 
 // What the epilogue of a large tile takes: the longer way through LDS where levels differ from row to row (3328 x 768 in 3 and
 // 5 levels by 3072 rows: 34 us a round), the more where columns are split as well (1408 x 1024 by 1800 rows of two levels 27 us,
-// 250 by 6400 rows of two levels both 36).
+// 250 by 6400 rows of two levels both 36).  The planner, which lays out B's rows before the levels are known, asks with kTileNs and
+// a margin of 25 % instead: where splits make the large tiles dearer than that, a product between the two costs takes them all the
+// same.
 static int tile_ns(const PlanHeader &h) {
     if (h.lmaxB > 1 && !h.evenB) return 10000 + 4500 * h.lmaxA * h.lmaxB;
     return h.lmaxA > 1 && !h.evenA ? 12000 + 3000 * h.lmaxA : kTileNs;

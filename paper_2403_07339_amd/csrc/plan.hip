@@ -1043,11 +1043,11 @@ __device__ void rows_layout(const SlotSet &rows, int nbase, const int32_t *count
         return;
     }
     int nchunks = nbase > 0 ? tmpP[nbase - 1] / Cp + 1 : 0;
-    // Rows that (nearly) all have the same number of levels, two to four: each gets two or four physical rows, some of them
-    // padding, where that takes no more chunks.  Then the GEMM's epilogue stores from its registers: a lane holds four
-    // physical rows of A side by side, so the levels of a row of A are neighbours; and it holds the same column of every
-    // block of kEvenStep rows of B, so those of a row of B are that far apart.  Besides, nothing of a chunk is lost: 4096
-    // rows of A of four levels but 97 of three take 64 tiles instead of 67.
+    // Rows that (nearly) all have the same number of levels, two or four (three only where a chunk has the room): each gets two
+    // or four physical rows, some of them padding, where that takes no more chunks.  Then the GEMM's epilogue stores from its
+    // registers: a lane holds four physical rows of A side by side, so the levels of a row of A are neighbours; and it holds the
+    // same column of every block of kEvenStep rows of B, so those of a row of B are that far apart.  Besides, nothing of a
+    // chunk is lost: 4096 rows of A of four levels but 97 of three take 64 tiles instead of 67.
     int even = lmax == 1 || lmax > 4 ? 0 : lmax == 2 ? 2 : 4;
     static_assert(kEvenStep == 32 && kChunk == 64 && kTile == 256, "shifts below");
     const int step = operand ? kEvenStep : 1;  // from level to level, if so
