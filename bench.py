@@ -50,9 +50,12 @@ def gemm_kernel(imu, plan):
     if not plan.fusable():
         return "gemm_f6_kernel<1>" if fp6 else "gemm_i8_kernel<1>"
     parts = imu.imunpack_diag_gemm_parts(plan)
+    if parts == 1 and imu.imunpack_diag_list_columns(plan):
+        return "gemm_lists_kernel"
     if parts == 1:
         return "gemm_f6_kernel<0>" if fp6 else "gemm_i8_kernel<0>"
-    return f"gemm_small_kernel<{str(fp6).lower()}, false>" if parts == 0 else f"gemm_split_kernel<{str(fp6).lower()}>"
+    return f"gemm_small_kernel<{str(fp6).lower()}, false>" if parts == 0 else \
+        f"gemm_split_kernel<{str(fp6).lower()}, {str(imu.imunpack_diag_list_columns(plan) > 0).lower()}>"
 
 
 def cpu_baseline(w, budget_rows: int = 4096):
@@ -299,7 +302,8 @@ def main():
     ba, bb, _ = plan.unpacked_bytes()
     (_, wa, _), (_, wb, _) = plan.layout()
     gemm_ms = stage_ms[4]
-    gemm_ops = 2.0 * n_u * d_u * h_u
+    # what the fused GEMM multiplies: not the columns whose few digits it takes from lists
+    gemm_ops = 2.0 * n_u * (d_u - (imu.imunpack_diag_list_columns(plan) if plan.fusable() else 0)) * h_u
     achieved = gemm_ops / (gemm_ms * 1e-3) / 1e12
     value = w.ops / (ms_step * 1e-3) / 1e12
     traffic, traffic_file = profiled_traffic(args.workload, args.digits)

@@ -276,7 +276,8 @@ int imunpack_unpack_canonical(imunpack_plan_t *plan, const int8_t *A_ue, const i
  * accumulation of integers below 2^24 on v_mfma_f32_32x32x64_f8f6f4, the bound below is 2^24 then).
  * fuse != 0: one launch; the recombination (6) and the dequantisation run in the epilogue and
  *   C_int (n x h int64, device, may be NULL) and/or C_fp (n x h fp32, device, may be NULL) are
- *   written directly.  This needs the shifted sum of all groups to fit int32 for this plan's
+ *   written directly (columns that UnpackBoth appended to B for a few heavy hitters each are not multiplied as columns: their digits,
+ *   which the plan holds too, meet a transposed copy of A's columns that the plan keeps).  This needs the shifted sum of all groups to fit int32 for this plan's
  *   operands (bound measured by imunpack_unpack); if it does not, the call falls back to the
  *   un-fused path when workspace != NULL and returns ERANGE otherwise.  Products whose tiles are cut along the
  *   contraction meet in a buffer of 64 MiB that the first of them allocates (without it, and under stream
@@ -355,6 +356,11 @@ int imunpack_diag_copy(const void *src, void *dst, int64_t bytes, imunpack_strea
  * 64 x 64 unpacked rows, 1 = of 256 x 256, 2 to 4 = of 256 x 256, those of the last round cut into that many parts
  * along the contraction.  Errors: EINVAL (null plan). */
 int imunpack_diag_gemm_parts(const imunpack_plan_t *plan);
+
+/* How many of the d' columns the fused imunpack_gemm of this plan does not multiply as columns (tests and benchmark reporting
+ * only): columns that UnpackBoth appended to B for a few heavy hitters each, whose digits it takes one by one
+ * (B_eu holds them like any other).  Errors: EINVAL (no valid plan). */
+int imunpack_diag_list_columns(const imunpack_plan_t *plan);
 
 /* Shader clock under the GEMM's own load (benchmark reporting only).  While `ticks` (device, two
  * elements, owned by the caller) is set, every fused imunpack_gemm launch of this process has its

@@ -88,6 +88,10 @@ struct PlanHeader {
     int32_t run_grp[kMaxRuns];       // the group the run belongs to
     int32_t edgesA, edgesB;          // OB entry lists built for UnpackBoth
     int32_t nobA, nobB;              // OB entries of A / B kept for the scatter (UnpackBoth operands)
+    int32_t nsparse;                 // columns that the fused GEMM takes from lists (see SparseLists) ...
+    int32_t list_kt0;                // ... instead of the k-tiles of B_eu from this one on, the last run
+    int32_t lists_refused;           // ... which this plan cannot have: it has to be made again without
+    int32_t sparse_room;             // places that their lists of digits take
     int32_t overflow;                // bit set: which capacity was too small
     int32_t need[10];                // size that would have been needed, per capacity
     int32_t err;                     // IMUNPACK_ERANGE conditions found on the device
@@ -112,7 +116,7 @@ struct KeepState {
 };
 
 enum CapIndex { CAP_ROWA = 0, CAP_ROWB = 1, CAP_C1 = 2, CAP_C2 = 3, CAP_EDGEA = 4, CAP_EDGEB = 5, CAP_OB = 6,
-                CAP_LISTA = 7, CAP_LISTB = 8 };  // the last two: a caller's OB list was too short
+                CAP_LISTA = 7, CAP_LISTB = 8, CAP_SPARSE = 9 };  // the last two: a caller's OB list was too short
 
 // Physical-row description used by scatter and by the GEMM epilogue.
 struct RowLayout {
@@ -154,6 +158,27 @@ struct ColLayout {
                                   // entry of it weighs in the row norm behind the accumulator bound)
     int4 *unitA;          // [KA/16] as unitB (w = level only)
     unsigned long long *unitA_w;  // [KA/16] the weight of the unit's columns if they share one
+};
+
+// Columns that UnpackBoth appends to B for a few heavy hitters hold next to nothing but zeros (on a 11008 x 4096 weight with
+// 0.1 % of them 9 digits in 11008 places, and there is one for nearly every original column), yet multiplied as columns they double the
+// contraction.  Those that carry digit 1 along the columns of an original column (level 0 along A, exponent 1) and few enough
+// digits come last in B_eu, in a run of their own that the fused GEMM leaves out: their digits go into a list for every kSparseRows
+// physical rows of B as well, and the GEMM multiplies a list's digits, 32 at a time, with the columns of A that they meet, which it
+// reads from a transposed copy of level 0 of the A store.  Every product of two digits other than zero is still the low-bit GEMM's.
+// 4096 x 4096 by 11008: GEMM 331 -> 257 us and a step 446 -> 388 on resident weights; 754 -> 729 where the weights are unpacked in
+// every step (planner 7 us more, the copy 5); 16 rows against resident weights that no cache holds 115 -> 88.
+//
+// An entry: physical row inside the kSparseRows | original column << 7 | digit << 24 (in no particular order: the sums are integers).
+// The copy: column k of the store in rows 128 g .. 128 g + 127 is the line of 128 bytes at (g d + k) * 128, row p at its byte
+// (p % 32) * 4 + p / 32 % 4, so that one word is what a lane of the matrix instruction needs of the four row blocks of a wave.
+constexpr int kSparseRows = 32;
+constexpr uint32_t kSparseLine = 0x00ffff80u;  // of an entry: its line in the copy (the column layout in LDS takes 12288 slots, so k < 2^17)
+struct SparseLists {
+    int32_t *off;       // [Np / kSparseRows + 1] where a list begins (a multiple of 32)
+    int32_t *cnt;       // [Np / kSparseRows] entries it holds
+    uint32_t *ent;
+    int32_t cap;        // places in ent
 };
 
 // ---- batches.  The items of a batch (products of one shape) are planned, unpacked and multiplied by the
@@ -291,6 +316,10 @@ struct imunpack_plan {
     imu::SlotSet rowA, rowB, c1, c2;
     imu::RowLayout layA, layB;
     imu::ColLayout cols;
+    imu::SparseLists sparse;          // ent == nullptr: the fused GEMM multiplies every column of B_eu
+    int no_sparse;                    // there is no room for lists
+    int8_t *at;                       // the transposed copy of level 0 of the A store
+    int at_rows;                      // ... physical rows of A that it has room for
     int32_t *statsA[4], *statsB[4];   // rowcnt, colcnt, rowmax, colmax actually used
     // greedy scratch
     unsigned long long *edges;        // two lists of edge_cap packed edges each

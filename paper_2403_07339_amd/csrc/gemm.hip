@@ -74,6 +74,12 @@ struct GemmArgs {
     int whole_rows;           // results without levels to fold leave row by row (see whole_rows_win)
     int lmaxA;                // largest number of digit levels of a row of A
     int kwaves;               // gemm_small_kernel: waves that share the contraction
+    // columns of B that are taken from lists (SparseLists): they come in before k-tile sp_kt (-1: there are none), where the accumulators
+    // count in units of s, and are followed by a shift of sp_after bits
+    SparseLists sparse;
+    const int8_t *at;         // the transposed copy of level 0 of the A store
+    int at_cols;              // ... lines of 128 bytes to a block of 128 rows
+    int sp_kt, sp_after;
     // benchmark reporting: if set, workgroup 0 writes {shader clock ticks, 100 MHz wall ticks} of its K loop
     unsigned long long *clock_probe;
 };
@@ -168,6 +174,62 @@ __device__ __forceinline__ const int8_t *uniform_ptr(const int8_t *p) {
     return (const int8_t *)(((uint64_t)hi << 32) | lo);
 }
 
+// c += a b on accumulation registers, by hand: with the builtin in a second place the compiler moves accumulators between the two
+// register files on the way (253 registers spilled).  The operands may have been written just before (two wait states); what
+// reads c next has to wait for it.
+__device__ __forceinline__ void mfma_in_place(const v4i &a, const v4i &b, v16i &c) {
+    asm volatile("s_nop 1\n\tv_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+
+// 32 S entries of a list of SparseLists as the operands of S matrix instructions, entry 32 s + 16 h + i at byte i of lane half h of
+// instruction s, by way of list_lds(S) bytes of LDS that the wave has to itself: the digits of instruction s in fragment order at byte
+// 1024 s, behind them the entries.  (Digits put together in registers, every lane comparing sixteen rows: 20 000 cycles of the vector
+// ALU for the four lists of a wave at 4096 columns of 9 digits in 11008 rows, 11 000 so; 8 000 more for what the loads of A's copy,
+// from the last-level cache, leave uncovered.  More of them in flight, beside more registers held, were slower.)
+constexpr int list_lds(int S) { return S * (1024 + 128); }
+template <int S>
+struct ListWords {
+    unsigned w[(S + 1) / 2];
+    __device__ __forceinline__ void load(const uint32_t *ent, int lane) {
+#pragma unroll
+        for (int j = 0; j < (S + 1) / 2; ++j) w[j] = ent[64 * j + lane];
+    }
+    // the first `left` (at least one) are entries
+    __device__ __forceinline__ void stage(int8_t *lds, int left, int lane) const {
+#pragma unroll
+        for (int s = 0; s < S; ++s) *reinterpret_cast<v4i *>(lds + 1024 * s + 16 * lane) = v4i{0, 0, 0, 0};
+        const unsigned none = (unsigned)__builtin_amdgcn_readfirstlane((int)w[0]) & kSparseLine;  // what is not there meets the first one's column
+#pragma unroll
+        for (int j = 0; j < (S + 1) / 2; ++j) {
+            const int t = 64 * j + lane;
+            if (S < 2 && t >= 32) continue;
+            *reinterpret_cast<unsigned *>(lds + 1024 * S + 4 * t) = t < left ? w[j] : none;
+            if (t < left) lds[1024 * (t >> 5) + 16 * ((int)(w[j] & (kSparseRows - 1)) + 2 * (t & 16)) + (t & 15)] = (int8_t)(w[j] >> 24);
+        }
+    }
+};
+// the words of A's copy that the entries of instruction s meet, one byte per block of 32 rows of A
+__device__ __forceinline__ void list_columns(unsigned (&x)[16], const int8_t *entries, int s, int lhalf, const int8_t *at, unsigned row_off) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const v4i e = *reinterpret_cast<const v4i *>(entries + 128 * s + 64 * lhalf + 16 * q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[4 * q + i] = *reinterpret_cast<const unsigned *>(at + (((unsigned)e[i] & kSparseLine) | row_off));
+    }
+}
+// f[rb]: sixteen columns in row block rb
+__device__ __forceinline__ void list_rows(const unsigned (&x)[16], v4i (&f)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const unsigned a = __builtin_amdgcn_perm(x[4 * q + 1], x[4 * q], 0x05010400u), b = __builtin_amdgcn_perm(x[4 * q + 1], x[4 * q], 0x07030602u);
+        const unsigned c = __builtin_amdgcn_perm(x[4 * q + 3], x[4 * q + 2], 0x05010400u), d = __builtin_amdgcn_perm(x[4 * q + 3], x[4 * q + 2], 0x07030602u);
+        f[0][q] = (int)__builtin_amdgcn_perm(c, a, 0x05040100u);
+        f[1][q] = (int)__builtin_amdgcn_perm(c, a, 0x07060302u);
+        f[2][q] = (int)__builtin_amdgcn_perm(d, b, 0x05040100u);
+        f[3][q] = (int)__builtin_amdgcn_perm(d, b, 0x07060302u);
+    }
+}
+
 // LDS half-stage: [256 rows][128 B] of one operand; the eight 16-byte chunks of a row are XOR-swizzled
 // with bits 1..3 of the row (chunk kc of row r lives at r*128 + ((kc ^ ((r >> 1) & 7)) << 4)), which
 // makes the 64-lane ds_read_b128 of an MFMA operand (32 rows x 2 chunks) conflict-free.
@@ -181,7 +243,8 @@ __device__ __forceinline__ const int8_t *uniform_ptr(const int8_t *p) {
 // BATCH: the items of a batch (blockIdx.y) in one launch; what the plan decides comes from the item's header.  A
 // variant of its own: read through a run-time choice, those values cost the one-product kernel its last
 // registers (101 spilled; 348 -> 460 us on a 4096 x 8228 x 11013 unpacked product).
-template <int MODE, bool FP6, bool BATCH = false, bool SPLIT = false>  // SPLIT: parts of tiles (see piece_of); MODE 0: fused epilogue, 1: int64 segment into C_u
+// LISTS: some columns of B are taken from lists (int8, a product of its own); a variant of its own for the registers' sake too.
+template <int MODE, bool FP6, bool BATCH = false, bool SPLIT = false, bool LISTS = false>  // SPLIT: parts of tiles (see piece_of); MODE 0: fused epilogue, 1: int64 segment into C_u
 __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     constexpr int kRowB = FP6 ? 96 : BK;           // bytes of a row of the operand per k-tile
     constexpr int kPitch = FP6 ? 112 : BK;         // bytes from row to row in LDS
@@ -413,48 +476,66 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     // kt+1 and stream B(kt+2) into the slot of A(kt).
     int kt = kt0;
     int seg = seg0;
-    for (; seg <= nbound && (!SPLIT || kt < kt1); ++seg) {
-        const int shv = seg == seg0 ? 0 : BATCH ? __builtin_amdgcn_readlane(v_shift, seg - 1) : g.bound_sh[seg - 1];
-        if (shv != 0) {  // start of the next exponent group: Horner step
-            // The accumulators fill the whole accumulation register file (a0..a255), so shifting every
-            // one of those registers shifts every accumulator, whichever block sits where.  Written
-            // out by hand: left to the compiler, this step spills three blocks to scratch memory.
-            int t0, t1, t2, t3;
-            if constexpr (FP6) {  // binary32 accumulators: times 2^shift, exact
-                asm volatile(
-                    "s_nop 15\n\ts_nop 7\n\t"
-                    ".irp n," IMU_ACC_QUADS "\n\t"
-                    "v_accvgpr_read_b32 %[t0], a[\\n]\n\t"
-                    "v_accvgpr_read_b32 %[t1], a[\\n+1]\n\t"
-                    "v_accvgpr_read_b32 %[t2], a[\\n+2]\n\t"
-                    "v_accvgpr_read_b32 %[t3], a[\\n+3]\n\t"
-                    "v_ldexp_f32 %[t0], %[t0], %[sh]\n\t"
-                    "v_ldexp_f32 %[t1], %[t1], %[sh]\n\t"
-                    "v_ldexp_f32 %[t2], %[t2], %[sh]\n\t"
-                    "v_ldexp_f32 %[t3], %[t3], %[sh]\n\t"
-                    "v_accvgpr_write_b32 a[\\n], %[t0]\n\t"
-                    "v_accvgpr_write_b32 a[\\n+1], %[t1]\n\t"
-                    "v_accvgpr_write_b32 a[\\n+2], %[t2]\n\t"
-                    "v_accvgpr_write_b32 a[\\n+3], %[t3]\n\t"
-                    ".endr\n\t"
-                    "s_nop 7"
-                    : [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), "+a"(acc[0][0]), "+a"(acc[0][1]),
-                      "+a"(acc[0][2]), "+a"(acc[0][3]), "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]),
-                      "+a"(acc[1][3]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
-                      "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
-                    : [sh] "s"(shv));
-            } else
+    // The columns that are taken from lists: the wave's four blocks of 32 physical rows of B in turn, 128 entries at a time, through what
+    // the wave itself will fill of the slot of the ring that is free now (the waves are at different places here).
+    auto lists = [&]() __attribute__((always_inline)) {
+        const int8_t *at = uniform_ptr(g.at + (int64_t)(tm * 2 + wm) * g.at_cols * 128);
+        const unsigned row_off = (unsigned)lrow * 4u;
+        const int block0 = (n0 + wn * 128) / kSparseRows;
+        int8_t *lds = smem + ring(sa, 4) * kHalfBytes + wave * kWaveBytes;
+        static_assert(list_lds(4) <= kWaveBytes, "LDS of the lists");
+        // lane 0 .. 4: where the lists of the wave's blocks begin and the last one ends; 8 .. 11: their lengths
+        const int bounds = lane < 8 ? g.sparse.off[block0 + min(lane, 4)] : g.sparse.cnt[block0 + min(lane - 8, 3)];
+        ListWords<4> words;  // the next 128 entries, or the first of the list behind
+        words.load(g.sparse.ent + __builtin_amdgcn_readlane(bounds, 0), lane);
+        auto block = [&](auto cb_c) __attribute__((always_inline)) {
+            constexpr int CB = decltype(cb_c)::value;
+            const int from = __builtin_amdgcn_readlane(bounds, CB), after = __builtin_amdgcn_readlane(bounds, CB + 1);
+            const int len = min(__builtin_amdgcn_readlane(bounds, CB + 8), after - from);
+            if (len <= 0) words.load(g.sparse.ent + after, lane);  // (there are none of this list)
+            for (int t = 0; t < len; t += 128) {
+                words.stage(lds, len - t, lane);
+                unsigned x[4][16];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) list_columns(x[s], lds + 4096, s, lhalf, at, row_off);
+                words.load(g.sparse.ent + (t + 128 < len ? from + t + 128 : after), lane);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    if (t + 32 * s >= len) break;  // uniform
+                    const v4i fd = *reinterpret_cast<const v4i *>(lds + 1024 * s + 16 * lane);
+                    v4i fr[4];
+                    list_rows(x[s], fr);
+#pragma unroll
+                    for (int rb = 0; rb < 4; ++rb)
+                        if constexpr (LISTS) mfma_in_place(fr[rb], fd, acc[rb][CB]);
+                }
+            }
+        };
+        block(std::integral_constant<int, 0>{});
+        block(std::integral_constant<int, 1>{});
+        block(std::integral_constant<int, 2>{});
+        block(std::integral_constant<int, 3>{});
+        asm volatile("s_nop 15");  // (the matrix instructions behind do not know of these)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read: it may be filled
+    };
+    // Horner step
+    auto horner = [&](const int shv) __attribute__((always_inline)) {
+        // The accumulators fill the whole accumulation register file (a0..a255), so shifting every
+        // one of those registers shifts every accumulator, whichever block sits where.  Written
+        // out by hand: left to the compiler, this step spills three blocks to scratch memory.
+        int t0, t1, t2, t3;
+        if constexpr (FP6) {  // binary32 accumulators: times 2^shift, exact
             asm volatile(
-                "s_nop 15\n\ts_nop 7\n\t"  // the last MFMA results must have landed
+                "s_nop 15\n\ts_nop 7\n\t"
                 ".irp n," IMU_ACC_QUADS "\n\t"
                 "v_accvgpr_read_b32 %[t0], a[\\n]\n\t"
                 "v_accvgpr_read_b32 %[t1], a[\\n+1]\n\t"
                 "v_accvgpr_read_b32 %[t2], a[\\n+2]\n\t"
                 "v_accvgpr_read_b32 %[t3], a[\\n+3]\n\t"
-                "v_lshlrev_b32 %[t0], %[sh], %[t0]\n\t"
-                "v_lshlrev_b32 %[t1], %[sh], %[t1]\n\t"
-                "v_lshlrev_b32 %[t2], %[sh], %[t2]\n\t"
-                "v_lshlrev_b32 %[t3], %[sh], %[t3]\n\t"
+                "v_ldexp_f32 %[t0], %[t0], %[sh]\n\t"
+                "v_ldexp_f32 %[t1], %[t1], %[sh]\n\t"
+                "v_ldexp_f32 %[t2], %[t2], %[sh]\n\t"
+                "v_ldexp_f32 %[t3], %[t3], %[sh]\n\t"
                 "v_accvgpr_write_b32 a[\\n], %[t0]\n\t"
                 "v_accvgpr_write_b32 a[\\n+1], %[t1]\n\t"
                 "v_accvgpr_write_b32 a[\\n+2], %[t2]\n\t"
@@ -466,7 +547,38 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                   "+a"(acc[1][3]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
                   "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
                 : [sh] "s"(shv));
-        }
+        } else
+        asm volatile(
+            "s_nop 15\n\ts_nop 7\n\t"  // the last MFMA results must have landed
+            ".irp n," IMU_ACC_QUADS "\n\t"
+            "v_accvgpr_read_b32 %[t0], a[\\n]\n\t"
+            "v_accvgpr_read_b32 %[t1], a[\\n+1]\n\t"
+            "v_accvgpr_read_b32 %[t2], a[\\n+2]\n\t"
+            "v_accvgpr_read_b32 %[t3], a[\\n+3]\n\t"
+            "v_lshlrev_b32 %[t0], %[sh], %[t0]\n\t"
+            "v_lshlrev_b32 %[t1], %[sh], %[t1]\n\t"
+            "v_lshlrev_b32 %[t2], %[sh], %[t2]\n\t"
+            "v_lshlrev_b32 %[t3], %[sh], %[t3]\n\t"
+            "v_accvgpr_write_b32 a[\\n], %[t0]\n\t"
+            "v_accvgpr_write_b32 a[\\n+1], %[t1]\n\t"
+            "v_accvgpr_write_b32 a[\\n+2], %[t2]\n\t"
+            "v_accvgpr_write_b32 a[\\n+3], %[t3]\n\t"
+            ".endr\n\t"
+            "s_nop 7"
+            : [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), "+a"(acc[0][0]), "+a"(acc[0][1]),
+              "+a"(acc[0][2]), "+a"(acc[0][3]), "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]),
+              "+a"(acc[1][3]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
+              "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
+            : [sh] "s"(shv));
+    };
+    for (; seg <= nbound && (!SPLIT || kt < kt1); ++seg) {
+        const int shv = seg == seg0 ? 0 : BATCH ? __builtin_amdgcn_readlane(v_shift, seg - 1) : g.bound_sh[seg - 1];
+        if (shv != 0) horner(shv);  // start of the next exponent group
+        if constexpr (LISTS)
+            if (kt == g.sp_kt) {  // (the first k-tile of a segment)
+                lists();
+                if (g.sp_after != 0) horner(g.sp_after);
+            }
         int kend = BATCH ? __builtin_amdgcn_readlane(v_end, seg) : seg < nbound ? g.bound_kt[seg] + 1 : kt1;
         if constexpr (SPLIT) kend = min(kend, kt1);
         for (; kt < kend; ++kt) {
@@ -507,6 +619,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     if constexpr (SPLIT) {
         if (pc.parts > 1) {
             for (int x = seg - 1; x < nbound; ++x) rest += g.bound_sh[x];
+            if (LISTS && g.sp_kt >= kt1) rest += g.sp_after;
             int32_t *meet = g.meet + 2 * pc.slot, *sums = g.sums + (size_t)pc.slot * (BM * BN) + 4 * tid;
             int32_t *turn = reinterpret_cast<int32_t *>(smem);
             if (tid == 0) *turn = __hip_atomic_fetch_add(meet, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -989,10 +1102,15 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_batch_kernel(const GemmA
     gemm_body<0, FP6, true>(g, smem);
 }
 
-template <bool FP6>
+template <bool FP6, bool LISTS>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_split_kernel(const GemmArgs g) {
     extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
-    gemm_body<0, FP6, false, true>(g, smem);
+    gemm_body<0, FP6, false, true, LISTS>(g, smem);
+}
+
+__global__ __launch_bounds__(kGemmThreads, 1) void gemm_lists_kernel(const GemmArgs g) {
+    extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
+    gemm_body<0, false, false, false, true>(g, smem);
 }
 
 template <int MODE>
@@ -1185,6 +1303,42 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
         if (half_rows) contract(std::integral_constant<int, 1>{});
         else contract(std::integral_constant<int, 2>{});
     }
+    // The columns that are taken from lists: a wave takes 32 entries in turn, through its stage.  Sums of their own: the accumulators may
+    // be counting in units of a higher group, and by `rest` they are brought to those of the lowest, which is exponent 0 here.
+    AccT list_acc[2][2];
+    const bool lists = !FP6 && !BATCH && g.sp_kt >= 0 && busy;
+    if constexpr (!FP6 && !BATCH) {
+        if (lists) {
+            static_assert(list_lds(1) <= small_stage_bytes(FP6), "LDS of the lists");
+            const int8_t *at = uniform_ptr(g.at + (int64_t)(cm / 2) * g.at_cols * 128);
+            int8_t *lds = const_cast<int8_t *>(sa);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) list_acc[i][j][r] = 0;
+                const int block = 2 * cn + j, from = g.sparse.off[block], to = g.sparse.off[block + 1], len = min(g.sparse.cnt[block], to - from);
+                for (int t = wave * 32; t < len; t += step * 32) {
+                    ListWords<1> words;
+                    unsigned x[16];
+                    words.load(g.sparse.ent + from + t, lane);
+                    words.stage(lds, len - t, lane);
+                    list_columns(x, lds + 1024, 0, lhalf, at, (unsigned)lrow * 4u);
+                    const v4i fd = *reinterpret_cast<const v4i *>(lds + 16 * lane);
+                    v4i fr[4];
+                    list_rows(x, fr);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        v4i a;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) a[q] = cm & 1 ? fr[2 + i][q] : fr[i][q];
+                        list_acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, fd, list_acc[i][j], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
     if (tid < ns) rowmeta[tid] = (layA.src_pstart[isrc0 + tid] - m0) | (layA.src_nlev[isrc0 + tid] << 16);
     if (tid >= 64 && tid - 64 < nc) colmeta[tid - 64] = (layB.src_pstart[jsrc0 + tid - 64] - n0) | (layB.src_nlev[jsrc0 + tid - 64] << 16);
     __syncthreads();  // every stage has been read
@@ -1199,7 +1353,8 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    put(&fold[(i * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3)) * kSmallPitch + j * 32 + lrow], (int32_t)acc[i][j][r] << rest);
+                    put(&fold[(i * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3)) * kSmallPitch + j * 32 + lrow],
+                        ((int32_t)acc[i][j][r] << rest) + (lists ? (int32_t)list_acc[i][j][r] << g.sh : 0));
         }
     };
     if (wave == 0) each([](int32_t *p, int32_t x) { *p = x; });  // (wave 0 always has a k-tile)
@@ -1323,8 +1478,10 @@ static int gemm_lds_opt_in() {
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_f6_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_batch_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_batch_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
-        IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
-        IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_lists_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         constexpr int kSmallLds = kSmallMeta + kSmallWaves * small_stage_bytes(false);
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
@@ -1377,6 +1534,8 @@ static bool whole_rows_win(const Plan *p) {
     const double d = (double)p->d, rows = (double)p->n + (double)p->h;
     return 8.0 * rows * d + 4.0 * (double)p->n * (double)p->h > 320e6;
 }
+// The runs that the fused GEMM walks: what is taken from lists is a run of B_eu's own, the last.
+static int fused_runs(const PlanHeader &h) { return h.nruns - (h.nsparse ? 1 : 0); }
 // What the fused launch of one plan takes from its header.
 static void fused_args(GemmArgs &g, const Plan *p) {
     const PlanHeader &h = p->hdr;
@@ -1388,17 +1547,32 @@ static void fused_args(GemmArgs &g, const Plan *p) {
     g.evenB = h.evenB;
     g.whole_rows = whole_rows_win(p);
     g.guard_mul = p->s - 1;
-    g.kt0 = 0; g.kt1 = h.Kp / BK;
+    g.kt0 = 0; g.kt1 = h.nsparse ? h.list_kt0 : h.Kp / BK;
     g.nbound = 0;
-    for (int r = 0; r < h.nruns; ++r) {
+    const int runs = fused_runs(h);
+    for (int r = 0; r < runs; ++r) {
         g.seg_delta[r] = h.run_blk0[r] - h.run_kt0[r];
-        if (r + 1 < h.nruns) {
+        if (r + 1 < runs) {
             g.bound_kt[g.nbound] = h.run_kt0[r + 1] - 1;
             g.bound_sh[g.nbound] = p->sh * (h.grp_exp[h.run_grp[r]] - h.grp_exp[h.run_grp[r + 1]]);
             ++g.nbound;
         }
     }
     g.final_shift = h.ngroups ? p->sh * h.grp_exp[h.ngroups - 1] : 0;
+    g.sp_kt = -1;
+    if (h.nsparse) {
+        g.sparse = p->sparse;
+        g.at = p->at;
+        g.at_cols = (int)p->d;
+        // before the first group of exponent 1 or, if no column of that exponent is stored, 0 (there always is that one)
+        int r = 0;
+        while (h.grp_exp[h.run_grp[r]] > 1) ++r;
+        g.sp_kt = h.run_kt0[r];
+        if (h.grp_exp[h.run_grp[r]] == 0) {
+            g.sp_after = p->sh;
+            if (r > 0) g.bound_sh[r - 1] -= p->sh;
+        }
+    }
     // |accumulator| < 2^31, weights up to s^(levels of a row - 1 + levels of a column - 1)
     g.fold_f64 = 31 + p->sh * ((h.lmaxA - 1) + (h.lmaxB - 1)) <= 52;
 }
@@ -1470,13 +1644,15 @@ static int launch_fused(Plan *p, GemmArgs &g, hipStream_t st) {
         g.most_parts = parts;
         p->gemm_parts = parts;
         const dim3 grid((unsigned)(8 * (((tiles + 7) / 8 + kXcdCus - 1) / kXcdCus * kXcdCus)));
-        if (p->fp6) hipLaunchKernelGGL(gemm_split_kernel<true>, grid, dim3(kGemmThreads), kGemmLds, st, g);
-        else hipLaunchKernelGGL(gemm_split_kernel<false>, grid, dim3(kGemmThreads), kGemmLds, st, g);
+        if (p->fp6) hipLaunchKernelGGL((gemm_split_kernel<true, false>), grid, dim3(kGemmThreads), kGemmLds, st, g);
+        else if (g.sp_kt >= 0) hipLaunchKernelGGL((gemm_split_kernel<false, true>), grid, dim3(kGemmThreads), kGemmLds, st, g);
+        else hipLaunchKernelGGL((gemm_split_kernel<false, false>), grid, dim3(kGemmThreads), kGemmLds, st, g);
         IMU_HIP(hipEventRecord(p->split_done, st));
         return launch_status();
     }
     p->gemm_parts = 1;
     if (p->fp6) hipLaunchKernelGGL(gemm_f6_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
+    else if (g.sp_kt >= 0) hipLaunchKernelGGL(gemm_lists_kernel, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
     else hipLaunchKernelGGL(gemm_i8_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
     return launch_status();
 }
@@ -1499,7 +1675,7 @@ int gemm_impl(imunpack_plan_t *p, const int8_t *A_ue, const int8_t *B_eu, void *
     g.Np = h.Np;
     const int grid = h.mtiles * h.ntiles;
     bool fused = fuse != 0;
-    const bool too_many_runs = h.nruns > 63;  // more segments than the lanes of a wave can hold the tables of
+    const bool too_many_runs = fused_runs(h) > 63;  // more segments than the lanes of a wave can hold the tables of
     // The bounds of the last imunpack_unpack may still be on their way to the host.  If the fused
     // launch was exact for this plan object the last time, it goes out now with a guard (the kernel
     // checks the bounds on the device and writes nothing if they are too large), and only then does
@@ -1573,11 +1749,12 @@ int gemm_batch(imunpack_plan_t *p, const int8_t *A_ue, int64_t a_stride, const i
     g.C_fp = C_fp; g.ldc = ldc;
     g.scale_a_dev = scale_a_dev; g.scale_b_dev = scale_b_dev;
     g.refused = refused;
-    if (p->nitems == 1 && p->pin_hdr[0].nruns <= 63) {  // a batch of one: the one-product kernel, its tables in the launch
+    if (p->nitems == 1 && fused_runs(p->pin_hdr[0]) <= 63) {  // a batch of one: the one-product kernel, its tables in the launch
         fused_args(g, p);
         g.guard = p->d_hdr->bound;
         return launch_fused(p, g, st);
     }
+    g.sp_kt = -1;
     g.layA = p->layA; g.layB = p->layB;
     g.sh = p->sh;
     g.guard_mul = p->s - 1;
@@ -1599,6 +1776,8 @@ extern "C" int imunpack_gemm(imunpack_plan_t *p, const int8_t *A_ue, const int8_
 }
 
 extern "C" int imunpack_diag_gemm_parts(const imunpack_plan_t *p) { return p ? p->gemm_parts : IMUNPACK_EINVAL; }
+
+extern "C" int imunpack_diag_list_columns(const imunpack_plan_t *p) { return p && p->valid ? p->hdr.nsparse : IMUNPACK_EINVAL; }
 
 extern "C" int imunpack_diag_clock_probe(uint64_t *ticks) {
     g_clock_probe.store(reinterpret_cast<unsigned long long *>(ticks), std::memory_order_relaxed);

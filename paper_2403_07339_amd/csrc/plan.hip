@@ -1189,8 +1189,21 @@ struct ColTables {
     int gk0[kMaxGroups], gext[kMaxGroups];                 // first column of a group and its extent
     int cbase[kMaxGroups], xbase[kMaxGroups], ccount[kMaxGroups];  // gathered: first column, first extra block, how many
     int kp, ka, ka_levels, bad, la;
-    int lb, scratch;                                       // (of the path in LDS)
+    int lb, nsparse, list_col;                             // (of the path in LDS) columns taken from lists, the first of their run
     unsigned char tile_e[256], extra_e[256];               // group of every k-tile of B_eu / of every extra block of A
+};
+
+// Which appended columns the fused GEMM takes from lists (SparseLists).  A digit costs a wave of the large tiles some 44 cycles (18 700
+// for the 430 digits that 4096 columns of 9 in 11008 rows leave in its 128 rows of B), a stored column 17: the two meet where a
+// column holds one digit in 330 rows, and kSparseShare is a little beyond it.  Fewer than kSparseLeast of them (four k-tiles) are not
+// worth the copy of the A store, nor are those of a small B; and their run in B_eu has a place for every original column, so that
+// they have to be half of these.
+constexpr int kSparseShare = 384, kSparseLeast = 512;
+constexpr int64_t kSparseEntries = 1 << 22;  // of B
+struct SparseArgs {
+    const int32_t *colcnt, *rowcnt, *rowmax;  // statistics of B
+    int h;
+    SparseLists lists;
 };
 
 __device__ __forceinline__ void level_bases(ColTables &t) {
@@ -1219,6 +1232,8 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
         if (shared) tiles_sh += (t.cntA[a] + kKPad - 1) / kKPad;
         else ccount += m;
     }
+    const int tiles_l = t.nsparse ? (t.cntA[0] + kKPad - 1) / kKPad : 0;  // the run that the fused GEMM leaves out
+    if (e == 1) members += t.nsparse;
     const int tiles_c = (ccount + kKPad - 1) / kKPad;
     const int tiles = tiles_sh + tiles_c;
     int nrun = tiles_c > 0 ? 1 : 0;  // stretches of k-tiles that walk consecutive blocks of the A store
@@ -1250,10 +1265,15 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
             hdr->run_blk0[ri] = t.ka_levels / kKPad + xb;
             hdr->run_grp[ri] = g;
         }
-        const int total_r = __shfl(above_r, 0, 64);
+        const int total_r = __shfl(above_r, 0, 64), dense = __shfl(above, 0, 64);
         if (e == 0) {
-            hdr->nruns = total_r;
-            if (total_r > kMaxRuns) atomicMin(&hdr->err, IMUNPACK_ERANGE);
+            hdr->nruns = total_r + (tiles_l ? 1 : 0);
+            if (hdr->nruns > kMaxRuns) atomicMin(&hdr->err, IMUNPACK_ERANGE);
+        }
+        if (e == 1 && tiles_l && total_r < kMaxRuns) {  // behind all groups, beside level 0
+            hdr->run_kt0[total_r] = dense;
+            hdr->run_blk0[total_r] = 0;
+            hdr->run_grp[total_r] = g;
         }
     }
     for (int a = 0; a < kMaxLevelsA; ++a)
@@ -1263,14 +1283,16 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
     t.ccount[e] = ccount;
     t.gk0[e] = k0;
     t.gext[e] = tiles * kKPad;
-    const int total_tiles = __shfl(above, 0, 64), total_c = __shfl(above_c, 0, 64), ngroups = __shfl(above_n, 0, 64);
+    const int dense_tiles = __shfl(above, 0, 64), total_c = __shfl(above_c, 0, 64), ngroups = __shfl(above_n, 0, 64);
+    const int total_tiles = dense_tiles + tiles_l;
     if (e == 0) {
+        t.list_col = dense_tiles * kKPad;
         t.kp = total_tiles * kKPad;
         t.ka = t.ka_levels + total_c * kKPad;
     }
     if (members > 0) {
         const long long lim = 2147483647ll / ((long long)(s - 1) * (s - 1));
-        if (e * sh > 62 || tiles * kKPad > lim) atomicMin(&hdr->err, IMUNPACK_ERANGE);
+        if (e * sh > 62 || (tiles + (e == 1 ? tiles_l : 0)) * kKPad > lim) atomicMin(&hdr->err, IMUNPACK_ERANGE);
         if (report) {
             hdr->grp_exp[g] = e;
             hdr->grp_k0[g] = k0;
@@ -1279,6 +1301,8 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
     }
     if (report && e == 0) {
         hdr->ngroups = ngroups;
+        hdr->nsparse = t.nsparse;
+        hdr->list_kt0 = dense_tiles;
         hdr->Kp = total_tiles * kKPad;
         hdr->KA = t.ka_levels + total_c * kKPad;
         // row pitches: wide rows get an odd multiple of 256 bytes (power-of-two strides put the rows
@@ -1290,6 +1314,8 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
     }
     for (int i = 0; i < tiles && k0 / kKPad + i < 256; ++i) t.tile_e[k0 / kKPad + i] = (unsigned char)e;
     for (int i = 0; i < tiles_c && xb + i < 256; ++i) t.extra_e[xb + i] = (unsigned char)e;
+    if (e == 1)
+        for (int i = 0; i < tiles_l && dense_tiles + i < 256; ++i) t.tile_e[dense_tiles + i] = 1;
 }
 
 // The same layout for unpackings whose tables fit the LDS of one workgroup (every product up to 12288 column slots):
@@ -1301,14 +1327,15 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
 // in LDS and written once, by part 0.  Returns false, having written nothing but tables that are written again, if LDS is too
 // small: the same in every part, so that all of them take the general path (many pairs of levels: 300 x 9000 by 300 at b = 2
 // with eight levels on either side, a plan of 204 us in eight parts, 312 in one).
+constexpr int kListed = 1 << 30;   // (of a slot's levels) its column is taken from lists
 constexpr int kColSlotsLds = 12;  // slots per thread: as many as the registers of a 1024-thread workgroup hold
-template <int kSlots>
+template <int kSlots, bool LISTS>
 __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColLayout &cols, int d, int cap_phys, int s, int sh,
-                                PlanHeader *hdr, ColTables &t, int32_t *dyn, int dyn_words, int part) {
+                                PlanHeader *hdr, ColTables &t, int32_t *dyn, int dyn_words, int part, const SparseArgs &sp) {
     const int D = hdr->d_u, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (D > kSlots * kPlanThreads) return false;
     for (int x = tid; x < kMaxGroups * kMaxLevelsA; x += kPlanThreads) t.hist2[x] = 0;
-    if (tid == 0) t.la = t.lb = t.bad = 0;
+    if (tid == 0) t.la = t.lb = t.bad = t.nsparse = 0;
     int key[kSlots], lev[kSlots];  // original column; eA | eB << 16
 #pragma unroll
     for (int u = 0; u < kSlots; ++u) {
@@ -1338,35 +1365,57 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     }
     __syncthreads();
     const int LA = t.la + 1, LB = t.lb + 1, W = (d + 63) / 64;
-    if (LA > kMaxLevelsA || LA + LB - 1 > kMaxGroups || (long long)LA * LB * W * 3 > dyn_words) return false;
+    if (LISTS && LB > 1) {
+        const int most = sp.h / kSparseShare;
+        int found = 0;
+#pragma unroll
+        for (int u = 0; u < kSlots; ++u)
+            if (key[u] >= 0 && lev[u] == 1 << 16 && sp.colcnt[key[u]] <= most) {
+                lev[u] |= kListed;
+                ++found;
+            }
+        const unsigned sum = wave_sum_lane63((unsigned)found);
+        if (lane == 63) atomicAdd(&t.nsparse, (int)sum);
+        __syncthreads();
+        if (t.nsparse < kSparseLeast || t.nsparse * 2 < d) {  // uniform
+#pragma unroll
+            for (int u = 0; u < kSlots; ++u) lev[u] &= ~kListed;
+            __syncthreads();
+            if (tid == 0) t.nsparse = 0;
+            __syncthreads();
+        }
+    }
+    const int lists = LA * LB, pairs = lists + (LISTS && t.nsparse ? 1 : 0);  // the columns taken from lists have a mask of their own
+    if (LA > kMaxLevelsA || LA + LB - 1 > kMaxGroups || (long long)pairs * W * 3 > dyn_words) return false;
     if (part > 0) {  // where it is certain to fit (see below for what has to), the other parts need not find out
         const int appended = D - d, pads = kKPad * (LA * LB + LA + LB);
-        const int kp = d + appended + appended / 7 + pads, ka = hdr->d1 + appended + pads;
-        if (kp <= 256 * kKPad && appended + pads <= 256 * kKPad && LA * LB * W * 3 + kp + ka <= dyn_words) return true;
+        const int kp = d + appended + appended / 7 + pads + (pairs > lists ? d : 0), ka = hdr->d1 + appended + pads;
+        if (kp <= 256 * kKPad && appended + pads <= 256 * kKPad && pairs * W * 3 + kp + ka <= dyn_words) return true;
     }
-    unsigned long long *mask = reinterpret_cast<unsigned long long *>(dyn);  // [LA * LB][W]
-    int32_t *pre = dyn + 2 * LA * LB * W;                                     // [LA * LB][W] slots of the pair below the word
-    int32_t *packB = pre + LA * LB * W;                                       // k | eB << 24 per column of B_eu, -1: none
-    if (LA * LB * W * (3 + 16) <= dyn_words) {  // a byte per k first, where the stores will be put together (atomics on the
+    unsigned long long *mask = reinterpret_cast<unsigned long long *>(dyn);  // [pairs][W]
+    int32_t *pre = dyn + 2 * pairs * W;                                       // [pairs][W] slots of the pair below the word
+    int32_t *packB = pre + pairs * W;                                         // k | eB << 24 per column of B_eu, -1: none
+    auto pair_of = [=](int l) { return LISTS && l & kListed ? lists : (l & 0xffff) * LB + (l >> 16); };
+    if (pairs * W * (3 + 16) <= dyn_words) {  // a byte per k first, where the stores will be put together (atomics on the
                                                 // masks would queue up 32 to a word)
         unsigned char *seen = reinterpret_cast<unsigned char *>(packB);
-        for (int x = tid; x < LA * LB * W * 16; x += kPlanThreads) packB[x] = 0;
+        for (int x = tid; x < pairs * W * 16; x += kPlanThreads) packB[x] = 0;
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kSlots; ++u)
-            if (key[u] >= 0) seen[((lev[u] & 0xffff) * LB + (lev[u] >> 16)) * W * 64 + key[u]] = 1;
+            if (key[u] >= 0) seen[pair_of(lev[u]) * W * 64 + key[u]] = 1;
         __syncthreads();
-        for (int x = wave; x < LA * LB * W; x += kPlanWaves) {
+        for (int x = wave; x < pairs * W; x += kPlanWaves) {
             const unsigned long long m = __ballot(seen[x * 64 + lane] != 0);
             if (lane == 0) mask[x] = m;
         }
     } else {
-        for (int x = tid; x < 2 * LA * LB * W; x += kPlanThreads) dyn[x] = 0;
+        for (int x = tid; x < 2 * pairs * W; x += kPlanThreads) dyn[x] = 0;
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kSlots; ++u) {
             if (key[u] < 0) continue;
-            const int k = key[u], pair = (lev[u] & 0xffff) * LB + (lev[u] >> 16);
+            const int k = key[u], pair = pair_of(lev[u]);
             atomicOr(reinterpret_cast<unsigned *>(mask) + 2 * pair * W + (k >> 5), 1u << (k & 31));
         }
     }
@@ -1394,7 +1443,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     __syncthreads();
     const int Kp = t.kp, KA = t.ka, ka_levels = t.ka_levels;
     if (Kp > cap_phys) return true;  // reported: the plan is made again with more room
-    if (Kp > 256 * kKPad || KA - ka_levels > 256 * kKPad || (long long)LA * LB * W * 3 + Kp + KA > dyn_words) return false;
+    if (Kp > 256 * kKPad || KA - ka_levels > 256 * kKPad || (long long)pairs * W * 3 + Kp + KA > dyn_words) return false;
     if (part > 0) return true;
     int32_t *packA = packB + Kp;  // k | eA << 24 per stored column of A, -1: none
     for (int x = tid; x < Kp + KA; x += kPlanThreads) packB[x] = -1;
@@ -1407,6 +1456,13 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     for (int u = 0; u < kSlots; ++u) {
         if (key[u] < 0) continue;
         const int c = tid + u * kPlanThreads, k = key[u], a = lev[u] & 0xffff, eb = lev[u] >> 16, e = a + eb;
+        if (LISTS && lev[u] & kListed) {  // beside level 0 of A, which holds column k in place
+            packB[t.list_col + k] = k | (1 << 24);
+            cols.pcol_slot[t.list_col + k] = c;
+            cols.col_phys[c] = t.list_col + k;
+            cols.acol_phys[c] = k;
+            continue;
+        }
         const int stored = t.lvlbase[a] + rank(a * LB, k);  // where level a of A holds column k
         const int kb = t.kbase[e * kMaxLevelsA + a];
         int q, qa;
@@ -1457,6 +1513,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
             } else {
                 for (int eb = 0; eb < LB; ++eb)
                     if (t.kbase[(a + eb) * kMaxLevelsA + a] >= 0 && bit(a * LB + eb, k)) w += weight_of(a + eb, sh);
+                if (LISTS && a == 0 && pairs > lists && bit(lists, k)) w += weight_of(1, sh);
             }
         }
         cols.colA_k[q] = k;
@@ -1493,7 +1550,7 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
     int32_t *tmpOff = tmpOffAll + (size_t)part * (d + 1);
     for (int x = threadIdx.x; x < kMaxGroups * kMaxLevelsA; x += kPlanThreads) hist2[x] = 0;
     if (threadIdx.x < kMaxLevelsA) cntA[threadIdx.x] = 0;
-    if (threadIdx.x == 0) t.bad = 0;
+    if (threadIdx.x == 0) t.bad = t.nsparse = 0;  // (every column is stored here)
     __syncthreads();
     // every part computes the same per-slot values and the same tables (the stores of the parts
     // coincide); a part then lays out the groups part, part + kColBlocks, ...
@@ -1767,6 +1824,45 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
     }
 }
 
+// Room for the lists of SparseLists: the heavy hitters of a row of B, for every further digit, in each block that holds one of its
+// physical rows.  One workgroup, behind the layout of the rows; `room`: Np / kSparseRows words of LDS.  Lists that do not fit
+// are not begun: the host sees from sparse_room that the plan has to be made again, if any column is kept that way.
+__device__ __forceinline__ void sparse_rooms(const int32_t *src_pstart, const int32_t *src_nlev, int h, int sh, const SparseArgs &sp, PlanHeader *hdr, int *lds, int32_t *room) {
+    __shared__ unsigned long long s_total;
+    __syncthreads();
+    if (__syncthreads_or(load_agent(&hdr->overflow) | load_agent(&hdr->err))) return;  // (as the waves of this workgroup see it together)
+    const int nblocks = load_agent(&hdr->Np) / kSparseRows, step = load_agent(&hdr->evenB) ? kEvenStep : 1;
+    for (int x = threadIdx.x; x < nblocks; x += kPlanThreads) room[x] = 0;
+    if (threadIdx.x == 0) s_total = 0;
+    __syncthreads();
+    unsigned long long mine = 0;
+    for (int i = threadIdx.x; i < h; i += kPlanThreads) {
+        const int cnt = sp.rowcnt[i];
+        if (cnt == 0) continue;
+        const int digits = cnt * (digit_levels(sp.rowmax[i], sh) - 1), at = src_pstart[i], lev = src_nlev[i];
+        for (int l = 0; l < lev; ++l) atomicAdd(&room[(at + l * step) / kSparseRows], digits);
+        mine += (unsigned long long)digits * (unsigned)lev;
+    }
+    if (mine) atomicAdd(&s_total, mine);
+    __syncthreads();
+    const unsigned long long need = s_total + 32ull * nblocks;
+    if (need > (unsigned long long)sp.lists.cap) {
+        if (threadIdx.x == 0) hdr->sparse_room = (int32_t)min(need, 1ull << 30);
+        return;
+    }
+    const int total = ordered_scan(
+        nblocks, 0, [&](int x) { return (room[x] + 31) & ~31; },
+        [&](int x, int pre) {
+            sp.lists.off[x] = pre;
+            sp.lists.cnt[x] = 0;
+        },
+        lds);
+    if (threadIdx.x == 0) {
+        sp.lists.off[nblocks] = total;
+        hdr->sparse_room = (int32_t)need;
+    }
+}
+
 __host__ __device__ inline int row_slices(int rows) {
     const int w = (rows + kRowSlice - 1) / kRowSlice;
     return w < 1 ? 1 : w > 4 ? 4 : w;
@@ -1790,11 +1886,15 @@ __global__ __launch_bounds__(256) void publish_kernel(const PlanHeader *hdr, Pla
 
 // One to four workgroups for the rows of A, as many for the rows of B, kColBlocks for the columns (all but one of them idle unless
 // there are more column slots or pairs of levels than that one can hold; one for each item of a batch).
+// LISTS: columns of B may be taken from lists (see SparseArgs); then there is no other layout of the columns than the one in LDS, and the
+// host makes the plan again, without lists, if that is refused.  A variant of its own: 20 -> 36 us for a product without lists in one
+// kernel with them.
+template <bool LISTS>
 __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     SlotSet rowA, int n, RowLayout layA, int cap_physA, int32_t *tmpPA, SlotSet rowB, int h, RowLayout layB,
     int cap_physB, int32_t *tmpPB, SlotSet c1, SlotSet c2, ColLayout cols, int d, int cap_physC, int s, int sh,
     int32_t *tmpE, int32_t *tmpK, int32_t *tmpR, int32_t *tmpOff, PlanHeader *hdr, int fast_lds, const int32_t *skipB,
-    int64_t stride, int chunkB, int dyn_words) {
+    int64_t stride, int chunkB, int dyn_words, SparseArgs sparse) {
     __shared__ int lds[40];
     __shared__ ColTables tables;
     extern __shared__ __attribute__((aligned(16))) int32_t fast_rows[];  // what rows_layout asks for if fast_lds; dyn_words in all
@@ -1834,9 +1934,14 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
             if (!small_tiles_win(up(nu, kTile) * up(hu, kTile), up(nu, kChunk) * up(hu, kChunk), up(hdr->d_u, kKPad), true, 25)) chunkB = kTile;
         }
         rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr, bx - slA, slB);
+        if (LISTS && bx == slA) sparse_rooms(layB.src_pstart, layB.src_nlev, h, sh, sparse, hdr, lds, fast_rows);
     } else {
         const int part = bx - slA - slB;
-        if (!cols_layout_lds<kColSlotsLds>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part)) {
+        if (LISTS) {
+            if (!cols_layout_lds<kColSlotsLds, true>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part, sparse) && part == 0 &&
+                threadIdx.x == 0)
+                hdr->lists_refused = 1;
+        } else if (!cols_layout_lds<kColSlotsLds, false>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part, sparse)) {
             __syncthreads();
             cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, part, (int)gridDim.x - slA - slB, tables);
         }
@@ -1904,6 +2009,16 @@ static void carve_slots(Carver &cv, SlotSet &s, int cap) {
 
 static inline int phys_cap_rows(int cap) { return (int)((int64_t)cap * kChunk / (kChunk - 8) + 2 * kTile); }
 static inline int phys_cap_cols(int cap) { return cap + kMaxGroups * kKPad; }
+
+static constexpr int kLayoutLdsMax = 140 * 1024;  // dynamic LDS the layouts kernel may use (its static tables take about 11 KiB)
+
+// Whether appended columns of B may be taken from lists: those of UnpackBoth, whose heavy hitters the plan holds one by one; a product of
+// its own; digits that stay int8 (the six-bit format may be asked for once the plan is made); a word of LDS per list; B large enough
+// for its unpacked columns to be worth more than the lists' share of the planner.
+static inline bool sparse_possible(const Plan *p) {
+    return p->d >= kSparseLeast && p->h * p->d >= kSparseEntries && p->sB == IMUNPACK_BOTH && p->nitems == 1 && p->b > 4 && !p->no_sparse && 2 * p->d + 512 <= kColSlotsLds * kPlanThreads &&
+           phys_cap_rows(p->cap[CAP_ROWB]) / kSparseRows <= kLayoutLdsMax / (int)sizeof(int32_t);
+}
 
 // Lays every device array out in the arena for the current capacities: the headers of all items, then the
 // arrays of item 0, those of item 1 (p->item_bytes further), and so on.  Returns the bytes needed.
@@ -1982,6 +2097,15 @@ static size_t carve(Plan *p, char *base, bool own_statsA, bool own_statsB) {
         p->ccnt = cv.take<int32_t>(ccap + 8);
         p->ob = cv.take<int32_t>((size_t)3 * p->cap[CAP_OB]);
         p->obcnt = cv.take<int32_t>(1);
+    }
+    p->sparse = SparseLists{};
+    if (sparse_possible(p)) {
+        const int blocks = phys_cap_rows(p->cap[CAP_ROWB]) / kSparseRows;
+        p->sparse.off = cv.take<int32_t>(blocks + 1);
+        p->sparse.cnt = cv.take<int32_t>(blocks);
+        p->sparse.ent = cv.take<uint32_t>(p->cap[CAP_SPARSE] + 256);  // (the GEMM asks for 128 at a time, and once more behind a list)
+        p->sparse.cap = p->cap[CAP_SPARSE];
+        p->at = cv.take<int8_t>((size_t)p->at_rows * (size_t)d);
     }
     p->snapRoot = cv.take<int32_t>(p->cap[CAP_C1]);
     p->snapExp = cv.take<int32_t>(p->cap[CAP_C1]);
@@ -2080,6 +2204,7 @@ __device__ bool keep_decide(const KeepArgs &k, const SlotSet &c1, PlanHeader *hd
             hdr->h_u = o.h_u; hdr->d_u = o.d_u; hdr->nobB = o.nobB; hdr->edgesB = o.edgesB; hdr->extras = o.extras;
             hdr->Np = o.Np; hdr->Kp = o.Kp; hdr->KA = o.KA; hdr->ldA = o.ldA; hdr->ldB = o.ldB;
             hdr->ntiles = o.ntiles; hdr->lmaxB = o.lmaxB; hdr->chunkB = o.chunkB; hdr->evenB = o.evenB; hdr->ngroups = o.ngroups; hdr->nruns = o.nruns;
+            hdr->nsparse = o.nsparse; hdr->list_kt0 = o.list_kt0; hdr->sparse_room = o.sparse_room;
         } else if (h) {
             hdr->h_u = h;
         }
@@ -2183,8 +2308,6 @@ __global__ __launch_bounds__(kPlanThreads) void keep_plan_kernel(KeepPlan f) {
 
 static constexpr int kGreedyLdsMax = 136 * 1024;  // dynamic LDS the greedy may use for the two count vectors
 static constexpr int kKeepPlanCols = 16384;       // columns that keep_plan_kernel sets up and compares in one workgroup
-static constexpr int kLayoutLdsMax = 140 * 1024;  // dynamic LDS the layouts kernel may use (its static tables take about 11 KiB)
-
 // dynamic LDS of the greedy's two count vectors
 static size_t greedy_lds(const Plan *p, int phase) {
     const SlotSet &rows = phase == 1 ? p->rowA : p->rowB, &cols = phase == 1 ? p->c1 : p->c2;
@@ -2310,7 +2433,8 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
     const size_t dyn_bytes = items == 1 ? (size_t)kLayoutLdsMax : std::min((size_t)kLayoutLdsMax, std::max(fast_lds ? fast_bytes : 0, col_bytes));
     static std::atomic<int> opted_in{0};  // the attributes are idempotent: a race sets the same values twice
     if (!opted_in.load(std::memory_order_acquire)) {
-        IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
+        IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
+        IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
         IMU_HIP(hipFuncSetAttribute((const void *)keep_plan_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kGreedyLdsMax));
         opted_in.store(1, std::memory_order_release);
     }
@@ -2409,12 +2533,17 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
     // ---- physical layouts
     const int col_blocks = items > 1 && p->cap[CAP_C2] <= kColSlotsLds * kPlanThreads ? 1 : kColBlocks;
     const int slices = fast_lds ? row_slices(n) + row_slices(h) : 2;
-    hipLaunchKernelGGL(layouts_kernel, dim3(slices + col_blocks, items), dim3(kPlanThreads), dyn_bytes, st, p->rowA, n, p->layA,
-                       phys_cap_rows(p->cap[CAP_ROWA]), p->tmpPA, p->rowB, h, p->layB,
-                       phys_cap_rows(p->cap[CAP_ROWB]), p->tmpPB, p->c1, p->c2, p->cols, d,
-                       phys_cap_cols(p->cap[CAP_C2]), p->s, p->sh, p->tmpE, p->tmpK, p->tmpR, p->tmpOff, hdr, fast_lds,
-                       skip, stride, p->chunkB,
-                       (int)(dyn_bytes / sizeof(int32_t)));
+    const SparseArgs sparse = {p->statsB[1], p->statsB[0], p->statsB[2], h, p->sparse};
+    auto lay_out = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(slices + col_blocks, items), dim3(kPlanThreads), dyn_bytes, st, p->rowA, n, p->layA,
+                           phys_cap_rows(p->cap[CAP_ROWA]), p->tmpPA, p->rowB, h, p->layB,
+                           phys_cap_rows(p->cap[CAP_ROWB]), p->tmpPB, p->c1, p->c2, p->cols, d,
+                           phys_cap_cols(p->cap[CAP_C2]), p->s, p->sh, p->tmpE, p->tmpK, p->tmpR, p->tmpOff, hdr, fast_lds,
+                           skip, stride, p->chunkB,
+                           (int)(dyn_bytes / sizeof(int32_t)), sparse);
+    };
+    if (p->sparse.ent) lay_out(layouts_kernel<true>);
+    else lay_out(layouts_kernel<false>);
     if (keep)
         hipLaunchKernelGGL(keep_remember_kernel, dim3(grid_for(p->cap[CAP_C1], 256, 16)), dim3(256), 0, st, p->c1,
                            (const PlanHeader *)hdr, p->snapRoot, p->snapExp, p->snapChild, p->d_keep);
@@ -2432,6 +2561,8 @@ static void guess_capacities(Plan *p) {
     p->cap[CAP_C2] = std::max(p->cap[CAP_C2], (int)(2 * d + 512));
     p->cap[CAP_EDGEA] = std::max(p->cap[CAP_EDGEA], (int)std::min<int64_t>(n * d, std::max<int64_t>(n * d / 64, 4096)));
     p->cap[CAP_EDGEB] = std::max(p->cap[CAP_EDGEB], (int)std::min<int64_t>(2 * h * d, std::max<int64_t>(h * d / 64, 4096)));
+    p->cap[CAP_SPARSE] = std::max(p->cap[CAP_SPARSE], (int)std::min<int64_t>(h * d / 64 + h + 8192, 1 << 26));
+    p->at_rows = std::max(p->at_rows, (int)((n + kTile - 1) / kTile * kTile));
     p->cap[CAP_OB] = std::max(p->cap[CAP_OB], (int)std::min<int64_t>(std::max(n, h) * d, std::max<int64_t>(std::max(n, h) * d / 64, 4096)));
 }
 
@@ -2476,6 +2607,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
     if (!same) {
         guess_capacities(p);
         p->ignore_listA = p->ignore_listB = 0;
+        p->no_sparse = 0;
     }
     const bool ownA = !(stats_A && stats_A->rowcnt && stats_A->colcnt && stats_A->rowmax && stats_A->colmax);
     const bool ownB = !(stats_B && stats_B->rowcnt && stats_B->colcnt && stats_B->rowmax && stats_B->colmax);
@@ -2512,7 +2644,8 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         carve(p, p->arena, ownA, ownB);
         {  // what is kept of the plan before is only good for the same arrays at the same addresses
             unsigned long long sig = (unsigned long long)(uintptr_t)p->arena * 1000003ull + (unsigned long long)(uintptr_t)p->d_keep;
-            const long long parts[] = {n, d, h, b, strategy_A, strategy_B, ownA, ownB, (long long)(uintptr_t)B, (long long)ldb};
+            const long long parts[] = {n, d, h, b, strategy_A, strategy_B, ownA, ownB, (long long)(uintptr_t)B, (long long)ldb,
+                                       p->cap[CAP_SPARSE], p->at_rows, p->no_sparse};
             for (long long v : parts) sig = sig * 1099511628211ull + (unsigned long long)v;
             for (int c = 0; c <= CAP_OB; ++c) sig = sig * 1099511628211ull + (unsigned long long)p->cap[c];
             if (sig != p->keep_sig) p->keep_valid = 0;
@@ -2531,6 +2664,25 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
                 if (hi.overflow & (1 << c)) needed[c] = std::max(needed[c], (int)hi.need[c]);
         }
         if (err) { rc = err; p->keep_valid = 0; break; }
+        if (!overflow && p->hdr.lists_refused) {
+            p->no_sparse = 1;
+            p->keep_valid = 0;
+            continue;
+        }
+        if (!overflow && p->hdr.nsparse) {  // columns taken from lists: room for these and for the copy of the A store that they meet
+            const int64_t room = p->hdr.sparse_room;
+            bool again = room > p->sparse.cap;
+            if (again && room < (1 << 26)) p->cap[CAP_SPARSE] = (int)(room + room / 8);
+            else if (again) p->no_sparse = 1;
+            if (p->hdr.Mp > p->at_rows) {
+                p->at_rows = p->hdr.Mp;
+                again = true;
+            }
+            if (again) {
+                p->keep_valid = 0;
+                continue;
+            }
+        }
         if (!overflow) {
             p->valid = 1;
             p->canon_valid = 0;

@@ -354,6 +354,8 @@ struct FixupArgs {
     int fp6;                    // `out` holds 6-bit floating-point codes
     int8_t *out;
     unsigned long long *rowsum; // per physical row: what the digits placed here add to the row norm
+    SparseLists sparse;         // second == 1: the digits in stored columns from list_col on go there as well
+    int list_col;
 };
 
 // The whole norm of physical row p as far as it is known: the scatter kernel's parts plus `placed`.
@@ -390,6 +392,27 @@ __device__ __forceinline__ void add_to_row(unsigned long long *rowsum, int p, un
         pending &= ~same;
     }
     if (mine) atomicAdd(&rowsum[p], sum);
+}
+
+// A place in the list of `block` for every lane that gets here together: one atomic per list named, all of them in flight together (the
+// entries of a block of rows sit side by side in the OB list; an atomic to each lane: 36 us for 37 000 entries).
+__device__ __forceinline__ int list_place(int32_t *cnt, int block) {
+    const int lane = threadIdx.x & 63;
+    unsigned long long pending = __ballot(1);
+    int lead = lane, before = 0, count = 0;
+    while (pending) {
+        const int first = __builtin_ctzll(pending);
+        const unsigned long long same = __ballot(block == __builtin_amdgcn_readlane(block, first));
+        if ((same >> lane) & 1) {
+            lead = first;
+            before = __popcll(same & ((1ull << lane) - 1ull));
+            count = __popcll(same);
+        }
+        pending &= ~same;
+    }
+    int base = 0;
+    if (lane == lead) base = atomicAdd(&cnt[block], count);
+    return __shfl(base, lead, 64) + before;
 }
 
 // Both operands in one launch: blocks [0, blocks_a) serve fa, the next blocks_b serve fb.  What a digit
@@ -435,16 +458,22 @@ __global__ void fixup_kernel(FixupArgs fa, FixupArgs fb, int blocks_a, int block
                 const int p = f.row_phys[R];
                 const int8_t dg = (int8_t)(v < 0 ? -m : m);
                 for (int c = C, hops = 0; c >= 0 && hops < 4096; c = f.second ? -1 : f.c2_child[c], ++hops) {
+                    const int at = f.out_col[c];
+                    if (f.second && at >= f.list_col) {
+                        const int block = p / kSparseRows, from = f.sparse.off[block], to = f.sparse.off[block + 1];
+                        const int pos = from + list_place(f.sparse.cnt, block);
+                        if (pos < to) f.sparse.ent[pos] = (uint32_t)(p % kSparseRows) | (uint32_t)(at - f.list_col) << 7 | (uint32_t)(uint8_t)dg << 24;
+                    }
                     if (f.fp6) {  // the position holds 0 (the scatter wrote it): OR the code in, 6 bits at bit 6 * column
                         const unsigned code = (fp6_codes4((unsigned)(uint8_t)dg) & 0x3fu);
-                        const int col = f.out_col[c];
+                        const int col = at;
                         const unsigned bit = 6u * (unsigned)(col & 31);  // inside the 32-column fragment
                         unsigned *row = reinterpret_cast<unsigned *>(f.out + (int64_t)p * f.W);
                         const int grp = col >> 6, frag = (col >> 5) & 1, i = (int)(bit >> 5);
                         atomicOr(row + fp6_dword(p, grp, frag, i), code << (bit & 31u));
                         if ((bit & 31u) > 26u) atomicOr(row + fp6_dword(p, grp, frag, i + 1), code >> (32u - (bit & 31u)));
                     } else {
-                        f.out[(int64_t)p * f.W + f.out_col[c]] = dg;
+                        f.out[(int64_t)p * f.W + at] = dg;
                     }
                     const unsigned nsft = (unsigned)(f.sh * f.col_sexp[f.col_phys[c]]);
                     const unsigned long long term = nsft >= 40u ? (1ull << 44) : ((unsigned long long)m << nsft);
@@ -452,6 +481,47 @@ __global__ void fixup_kernel(FixupArgs fa, FixupArgs fb, int blocks_a, int block
                 }
             }
         }
+    }
+}
+
+// The copy of level 0 of the A store that SparseLists describes, 128 x 128 at a time: 16 bytes a lane in, four rows by four columns a lane
+// turned in registers, 16 bytes a lane (eight lanes to a line of 128 bytes) out.
+struct TransposeArgs {
+    const int8_t *A;   // the A store, ldA bytes from row to row
+    int8_t *out;
+    int ldA, d, blocks_k, blocks;  // blocks of 128 columns, blocks in all (0: nothing to do)
+};
+__device__ __forceinline__ void transpose_block(const TransposeArgs &t, int block, int8_t *lds /* 128 * kTrPitch */) {
+    constexpr int kTrPitch = 132;
+    const int g = block / t.blocks_k, k0 = (block - g * t.blocks_k) * 128, tid = threadIdx.x;
+    int4 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)  // the stores' widths are multiples of 128
+        x[u] = *reinterpret_cast<const int4 *>(t.A + (int64_t)(g * 128 + 32 * u + (tid >> 3)) * t.ldA + k0 + 16 * (tid & 7));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        int *to = reinterpret_cast<int *>(lds + (32 * u + (tid >> 3)) * kTrPitch + 16 * (tid & 7));
+        to[0] = x[u].x; to[1] = x[u].y; to[2] = x[u].z; to[3] = x[u].w;
+    }
+    __syncthreads();
+    const int l4 = (tid & 7) * 4, kq = tid >> 3;  // rows l4 .. l4 + 3 of each block of 32, columns 4 kq .. 4 kq + 3
+    unsigned o[4][4];                              // [column][row]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned r[4];
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) r[rb] = *reinterpret_cast<const unsigned *>(lds + (32 * rb + l4 + i) * kTrPitch + 4 * kq);
+        const unsigned a = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u), b = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
+        const unsigned c = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u), e = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
+        o[0][i] = __builtin_amdgcn_perm(c, a, 0x05040100u);
+        o[1][i] = __builtin_amdgcn_perm(c, a, 0x07060302u);
+        o[2][i] = __builtin_amdgcn_perm(e, b, 0x05040100u);
+        o[3][i] = __builtin_amdgcn_perm(e, b, 0x07060302u);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = k0 + 4 * kq + j;
+        if (k < t.d) *reinterpret_cast<uint4 *>(t.out + ((int64_t)g * t.d + k) * 128 + 4 * l4) = make_uint4(o[j][0], o[j][1], o[j][2], o[j][3]);
     }
 }
 
@@ -463,8 +533,14 @@ __global__ void bound_kernel(const unsigned long long *rowsum_a, const unsigned 
                              unsigned long long *bound_a, const unsigned long long *rowsum_b,
                              const unsigned long long *wavesum_b, int rows_b, unsigned long long *bound_b, int wpr_a,
                              int wpr_b, const PlanHeader *hdr /* batch: the sizes come from the item's header */,
-                             int64_t stride, unsigned long long *host /* nullptr: stay on the device */, int32_t seq) {
-    __shared__ unsigned long long s_bound[2];
+                             int64_t stride, unsigned long long *host /* nullptr: stay on the device */, int32_t seq,
+                             int nscan /* workgroups behind these make the transposed copy */, TransposeArgs tr) {
+    __shared__ __attribute__((aligned(16))) int8_t s_rows[128 * 132];
+    if ((int)blockIdx.x >= nscan) {  // uniform
+        transpose_block(tr, (int)blockIdx.x - nscan, s_rows);
+        return;
+    }
+    unsigned long long *s_bound = reinterpret_cast<unsigned long long *>(s_rows);
     if (threadIdx.x < 2) s_bound[threadIdx.x] = 0;
     __syncthreads();
     unsigned long long ma = 0, mb = 0;
@@ -476,7 +552,7 @@ __global__ void bound_kernel(const unsigned long long *rowsum_a, const unsigned 
         rows_a = hdr->Mp; rows_b = hdr->Np;
         wpr_a = (hdr->KA + 1023) / 1024; wpr_b = (hdr->Kp + 1023) / 1024;
     }
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < rows_a + rows_b; t += gridDim.x * blockDim.x) {
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < rows_a + rows_b; t += nscan * blockDim.x) {
         if (t < rows_a) ma = max(ma, row_norm(wavesum_a, wpr_a, t, rowsum_a[t]));
         else mb = max(mb, row_norm(wavesum_b, wpr_b, t - rows_a, rowsum_b[t - rows_a]));
     }
@@ -501,11 +577,12 @@ __global__ void bound_kernel(const unsigned long long *rowsum_a, const unsigned 
 
 // A repeated unpack of one plan: clears what the planner left cleared for the first.
 __global__ void reset_bound_kernel(PlanHeader *hdr, unsigned long long *rowsum_a, int rows_a,
-                                   unsigned long long *rowsum_b, int rows_b) {
+                                   unsigned long long *rowsum_b, int rows_b, int32_t *list_len, int lists) {
     const int t0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
     if (t0 == 0) hdr->bound[0] = hdr->bound[1] = 0;
     for (int t = t0; t < rows_a; t += stride) rowsum_a[t] = 0;
     for (int t = t0; t < rows_b; t += stride) rowsum_b[t] = 0;
+    for (int t = t0; t < lists; t += stride) list_len[t] = 0;
 }
 
 // canon[R][c] = phys[row_phys[R]][col_phys[c]]; Kp: stored columns per physical row
@@ -589,7 +666,7 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     if (p->unpacked || (h.reusedB && !keepB)) {
         if (batch) return IMUNPACK_EINVAL;
         hipLaunchKernelGGL(reset_bound_kernel, dim3(64), dim3(256), 0, st, p->d_hdr, p->layA.rowsum, h.Mp,
-                           p->layB.rowsum, h.Np);
+                           p->layB.rowsum, h.Np, p->sparse.cnt, h.nsparse ? h.Np / kSparseRows : 0);
     }
     FixupArgs fx[2] = {};
     int fblocks[2] = {0, 0};
@@ -648,6 +725,8 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
             f.col_phys = p->cols.col_phys; f.col_sexp = p->cols.col_sexp;
             f.W = a.ld; f.s = p->s; f.sh = p->sh; f.fp6 = p->fp6;
             f.out = a.out; f.rowsum = lay.rowsum;
+            f.sparse = p->sparse;
+            f.list_col = h.nsparse ? h.list_kt0 * kKPad : 0x7fffffff;
             fblocks[op] = (nob + 255) / 256;
         }
     }
@@ -687,10 +766,12 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
         p->bound_seq = ++p->seq;
         for (int i = 0; i < p->bound_words; ++i)  // not there yet
             __atomic_store_n(&p->pin_bounds[i], (unsigned long long)(uint16_t)~p->bound_seq << 48, __ATOMIC_RELEASE);
-        hipLaunchKernelGGL(bound_kernel, dim3(nscan, nitems), dim3(256), 0, st, p->layA.rowsum, p->layA.wavesum, h.Mp,
+        TransposeArgs tr = {A_ue, p->at, sc[0].ld, (int)p->d, (int)((p->d + 127) / 128), 0};
+        if (h.nsparse) tr.blocks = h.Mp / 128 * tr.blocks_k;
+        hipLaunchKernelGGL(bound_kernel, dim3(nscan + tr.blocks, nitems), dim3(256), 0, st, p->layA.rowsum, p->layA.wavesum, h.Mp,
                            &p->d_hdr->bound[0], p->layB.rowsum, p->layB.wavesum, h.Np, &p->d_hdr->bound[1],
                            sc[0].nwin, sc[1].nwin, batch ? p->d_hdr : nullptr, p->item_bytes,
-                           p->bound_words ? p->pin_bounds : nullptr, p->bound_seq);
+                           p->bound_words ? p->pin_bounds : nullptr, p->bound_seq, nscan, tr);
     }
     IMU_TRY(launch_status());
     p->unpacked = 1;

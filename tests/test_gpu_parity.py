@@ -1546,3 +1546,43 @@ def test_bounds_do_not_need_the_stream_of_the_unpack(imu):
         assert plan.bounds() == bounds
         imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None, fuse=True)
         assert np.array_equal(C_int.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,d,h,sa,longer,parts", [
+    (20, 1100, 4100, ROW, 0.0, 0),         # 64 x 64 tiles, one half of a row block; every column of exponent 1 comes from lists
+    (150, 1070, 4165, COL, 0.00002, 0),    # ... columns of exponents 1 and 2 beside them, entries of three digits
+    (2000, 1060, 4100, ROW, 0.0, 1),       # 256 x 256 tiles
+    (3300, 1100, 4000, COL, 0.00002, 1),
+    (400, 5800, 8000, COL, 0.0, 2),        # ... cut along the contraction (2: in two parts or more), the lists in one of them
+])
+def test_appended_columns_of_few_digits(imu, n, d, h, sa, longer, parts):
+    """UnpackBoth appends a column for nearly every original one, each for a few heavy hitters: the fused GEMM takes their digits from
+    lists, the un-fused one from B_eu.  Some columns are full of heavy hitters and are multiplied as columns."""
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    A = torch.randint(-127, 128, (n, d), generator=g, device="cuda", dtype=torch.int32)
+    B = torch.randint(-127, 128, (h, d), generator=g, device="cuda", dtype=torch.int32)
+    A[:, ::97] += 3000
+    sign = torch.randint(0, 2, (h, d), generator=g, device="cuda", dtype=torch.int32) * 2 - 1
+    for share, lo, hi in ((4 / h, 128, 128 ** 2), (longer, 128 ** 2, 128 ** 3)):
+        at = torch.rand((h, d), generator=g, device="cuda") < share
+        B = torch.where(at, sign * torch.randint(lo, hi, (h, d), generator=g, device="cuda", dtype=torch.int32), B)
+    B[:, 5::211] += 200
+    want = A.double() @ B.double().t()      # exact: below 2^53
+    plan = imu.Plan()
+    for rows in (n, max(1, n - 3)):         # the plan object again, its buffers and lists reused
+        imu.imunpack_plan(A[:rows], B, 8, sa, BOTH, plan=plan)
+        assert imu.imunpack_diag_list_columns(plan) > d // 2
+        A_ue, B_eu = imu.imunpack_unpack(plan, A[:rows], B)
+        for again in range(2):              # a second unpack of the plan starts the lists afresh
+            C = torch.full((rows, h), 3.5, device="cuda")
+            C_int = torch.full((rows, h), -1, dtype=torch.int64, device="cuda")
+            imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, None, C, None)
+            assert min(imu.imunpack_diag_gemm_parts(plan), 2) == parts
+            imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
+            scale = float(np.float32(0.013)) * float(np.float32(0.0021))
+            assert torch.equal(C_int.double(), want[:rows]) and torch.equal(C, (want[:rows] * scale).float())
+            imu.imunpack_unpack(plan, A[:rows], B, A_ue, B_eu)
+    ws = torch.empty(plan.unpacked_bytes()[2] // 8, dtype=torch.int64, device="cuda")
+    imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, None, None, ws, fuse=False)
+    imu.imunpack_recombine(plan, ws, 1.0, 1.0, C_int, None)
+    assert torch.equal(C_int.double(), want[:rows])
