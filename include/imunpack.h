@@ -236,7 +236,9 @@ int imunpack_plan_weights_reused(const imunpack_plan_t *plan);
  * IMUNPACK_DIGITS_INT8 (default): one int8 per digit.  IMUNPACK_DIGITS_FP6: 96 bytes per 128 columns; a
  * group of 64 columns takes 48 bytes: the 32 columns of each half form a 192-bit string (column j at
  * bits 6j .. 6j+5), stored as the first 16 bytes of both strings followed by the last 8 bytes of both
- * (those two in the other order in physical rows whose index has bit 4 set).  The request stays with the plan object
+ * (those two in the other order in physical rows whose index has bit 4 set).  Physical rows 2i and 2i + 1 share their bytes: row 2i
+ * holds the 96 bytes of both for every even group of 128 columns, row 2i + 1 for every odd one (none behind
+ * a last group without a partner).  The request stays with the plan object
  * across re-planning and is in effect whenever the plan's b <= 4 (a plan with b > 4 keeps int8);
  * imunpack_plan_digits returns the format in effect.  Call after imunpack_plan and before
  * imunpack_unpacked_bytes / imunpack_unpack: the format changes the sizes and the row pitches.
@@ -260,7 +262,7 @@ int imunpack_unpacked_bytes(const imunpack_plan_t *plan, size_t *bytes_A, size_t
                             size_t *bytes_workspace);
 /* The shape of the two buffers (host output, six values): physical rows, stored columns and bytes from
  * one row to the next, of the A store and then of B_eu.  bytes_A = rows * pitch.  The bytes of a row
- * behind its stored columns are neither written nor read. */
+ * behind its stored columns (six-bit digits: behind those of an even number of groups of 128) are neither written nor read. */
 int imunpack_plan_layout(const imunpack_plan_t *plan, int64_t *shape);
 int imunpack_unpack(imunpack_plan_t *plan, const int32_t *A, int64_t lda,
                     const int32_t *B, int64_t ldb, int8_t *A_ue, int8_t *B_eu,

@@ -270,11 +270,19 @@ __device__ __forceinline__ void tell_bound(unsigned long long *word, unsigned lo
 // groups of 64 (48 bytes): the first 128 bits of the group's two fragments (16 bytes each), then their
 // last 64 bits (8 bytes each), so that a lane reads its fragment as one aligned 16-byte and one aligned
 // 8-byte piece.  The two 8-byte pieces change places in the rows whose index has bit 4 set: the thirty-two
-// rows that an 8-byte LDS read serves together then fall on different banks (rows 112 bytes apart).
-// Returns the position, in 32-bit words from the start of the row, of word i (0..5) of fragment `frag`
-// (0, 1) of group `grp` in physical row `row`.
+// rows that an 8-byte LDS read serves together then fall on different banks (see fp6_piece in gemm.hip).
+// Returns the position, in 32-bit words from the start of the row's 96 bytes of a k-tile, of word i (0..5) of fragment
+// `frag` (0, 1) of group `grp` (0, 1) in physical row `row`.
 __host__ __device__ __forceinline__ int fp6_dword(int row, int grp, int frag, int i) {
     return 12 * grp + (i < 4 ? 4 * frag + i : 8 + 2 * (frag ^ ((row >> 4) & 1)) + (i - 4));
+}
+// Where the 96 bytes of k-tile kt of a row begin.  The caches hand 64 bytes at a time to a CU, so that 96 of a row cost 128; the rows
+// 2i and 2i + 1 therefore share their bytes: row 2i of the store holds the even k-tiles of both, 192 bytes each, row 2i + 1 the odd
+// ones.  A last k-tile without a partner leaves its place in row 2i + 1 to nothing (zeros); a single one is two rows side by side
+// all the same.  12288 stored columns, 16384 rows by 4096: GEMM 451 -> 388 us, the
+// scatter that writes them 67 -> 71.
+__host__ __device__ __forceinline__ int64_t fp6_ktile(int row, int kt, int64_t ld) {
+    return ((row & ~1) + (kt & 1)) * ld + (kt >> 1) * 192 + (row & 1) * 96;
 }
 // Lane 63's value in every lane (a scalar register).
 __device__ __forceinline__ int from_lane63(int v) { return __builtin_amdgcn_readlane(v, 63); }
@@ -418,10 +426,11 @@ int rtn_step_pair(const float *A, int64_t n, int64_t sa_r, int64_t sa_c, float b
 // Waits for the bounds of the last imunpack_unpack and sets p->fusable.
 int resolve_bound(Plan *p);
 // Bytes from one physical row to the next of the A store (op 0) / of B_eu (op 1) in the digit format in
-// effect.  6-bit digits: 96 bytes per k-tile of 128 columns, the same rule against power-of-two pitches.
+// effect.  6-bit digits: 96 bytes per k-tile of 128 columns, pairs of k-tiles (see fp6_ktile), the same rule against power-of-two
+// pitches.
 __host__ __device__ inline int header_pitch(const PlanHeader &h, int fp6, int op) {
     if (!fp6) return op ? h.ldB : h.ldA;
-    const int bytes = (op ? h.Kp : h.KA) / 4 * 3;
+    const int tiles = (op ? h.Kp : h.KA) / kKPad, bytes = (tiles + (tiles > 1 ? tiles & 1 : 0)) * 96;
     return bytes >= 2048 ? (((bytes + 255) / 256) | 1) * 256 : bytes;
 }
 inline int64_t store_pitch(const Plan *p, int op) { return header_pitch(p->hdr, p->fp6, op); }

@@ -235,21 +235,26 @@ __device__ __forceinline__ void list_rows(const unsigned (&x)[16], v4i (&f)[4]) 
 // makes the 64-lane ds_read_b128 of an MFMA operand (32 rows x 2 chunks) conflict-free.
 //
 // FP6 = true: the digits are 6-bit floating-point codes (b <= 4).  A k-tile is still 128 columns, now 96
-// bytes of a row; LDS rows are 112 bytes apart (seven 16-byte slots, the seventh a repeat of the sixth:
-// with 96 the rows that a wave reads together would share banks two by two); a lane's fragment of
-// v_mfma_f32_32x32x64_f8f6f4 is one 16-byte and one 8-byte read (see fp6_dword); a k-tile is two k-steps
-// of 16 matrix instructions; the accumulators are binary32 and hold integers below 2^24, exactly.
+// bytes of a row, in LDS as in memory, but for the six 16-byte pieces of a row changing places two by two in
+// rows whose index has bit 3 set (fp6_piece); a lane's fragment of v_mfma_f32_32x32x64_f8f6f4 is one 16-byte and one 8-byte
+// read (see fp6_dword); a k-tile is two k-steps of 16 matrix instructions; the accumulators are binary32 and hold integers
+// below 2^24, exactly.
 //
 // BATCH: the items of a batch (blockIdx.y) in one launch; what the plan decides comes from the item's header.  A
 // variant of its own: read through a run-time choice, those values cost the one-product kernel its last
 // registers (101 spilled; 348 -> 460 us on a 4096 x 8228 x 11013 unpacked product).
 // LISTS: some columns of B are taken from lists (int8, a product of its own); a variant of its own for the registers' sake too.
+//
+// fp6_piece: rows 96 bytes apart begin at eight multiples of eight of the 64 banks, rows 8 apart at the same one; with pieces
+// moved by one in every second eight rows the sixteen that a 16-byte read serves per cycle have four banks each and, with the
+// swap of fp6_dword, the 32 of an 8-byte read two.  (Rows 112 bytes apart did the same with a seventh load that brought nothing.)
+__device__ __forceinline__ int fp6_piece(int row, int piece) { return piece ^ ((row >> 3) & 1); }
 template <int MODE, bool FP6, bool BATCH = false, bool SPLIT = false, bool LISTS = false>  // SPLIT: parts of tiles (see piece_of); MODE 0: fused epilogue, 1: int64 segment into C_u
 __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     constexpr int kRowB = FP6 ? 96 : BK;           // bytes of a row of the operand per k-tile
-    constexpr int kPitch = FP6 ? 112 : BK;         // bytes from row to row in LDS
+    constexpr int kPitch = kRowB;                  // bytes from row to row in LDS
     constexpr int kHalfBytes = BM * kPitch;        // the A tile or the B tile of one k-tile in LDS
-    constexpr int kLoads = FP6 ? 7 : 8;            // direct-to-LDS loads per wave and half-stage
+    constexpr int kLoads = FP6 ? 6 : 8;            // direct-to-LDS loads per wave and half-stage
     constexpr int kWaveBytes = 64 * kPitch;        // a wave's 64 rows of a half-stage
     const int tid = threadIdx.x, lane = tid & 63;
     const PlanHeader *hdr = BATCH ? g.hdr + blockIdx.y : nullptr;
@@ -295,12 +300,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     unsigned voffA[8], voffB[8];
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
-        if (FP6) {  // slot u * 64 + lane of the wave's 64 x 7 slots: row slot / 7, piece slot % 7 (6 repeats 5)
+        if (FP6) {  // slot u * 64 + lane of the wave's 64 x 6 slots: six to a row
             const int slot = u * 64 + lane;
-            const int r = slot / 7, piece = min(slot - 7 * r, 5);
+            const int r = slot / 6, piece = fp6_piece(r, slot - 6 * r);
             const int row = 64 * wave + r;
-            voffA[u] = (unsigned)row * (unsigned)ldA + (unsigned)(piece * 16);
-            voffB[u] = (unsigned)row * (unsigned)ldB + (unsigned)(piece * 16);
+            voffA[u] = (unsigned)fp6_ktile(row, 0, ldA) + (unsigned)(piece * 16);
+            voffB[u] = (unsigned)fp6_ktile(row, 0, ldB) + (unsigned)(piece * 16);
         } else {
             const int row = 64 * wave + 8 * u + (lane >> 3);
             const int kc = (lane & 7) ^ ((row >> 1) & 7);
@@ -345,7 +350,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             la_delta = __builtin_amdgcn_readlane(v_delta, la_seg);
             blk = ktc + la_delta;
         }
-        pg = uniform_ptr((isA ? gA : gB) + (int64_t)blk * kRowB);
+        pg = uniform_ptr((isA ? gA : gB) + (FP6 ? fp6_ktile(0, blk, isA ? ldA : ldB) : (int64_t)blk * kRowB));
         dl = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)(slot * kHalfBytes) + (unsigned)(wave * kWaveBytes));
     };
     auto dma_one = [&](bool isA, int u) {  // u = 0..kLoads-1: the u-th KiB of the wave's rows of the half-stage set up last
@@ -358,9 +363,11 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     const int swz = (lrow >> 1) & 7;
     const unsigned fa_base = (unsigned)((wm * 128 + lrow) * kPitch);
     const unsigned fb_base = (unsigned)((wn * 128 + lrow) * kPitch);
-    unsigned kc_off[4];
+    unsigned kc_off[4], hi_off[2];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) kc_off[ks] = FP6 ? (unsigned)(48 * ks + 16 * lhalf) : (unsigned)(((2 * ks + lhalf) ^ swz) << 4);
+    for (int ks = 0; ks < 4; ++ks) kc_off[ks] = FP6 ? (unsigned)(16 * fp6_piece(lrow, 3 * ks + lhalf)) : (unsigned)(((2 * ks + lhalf) ^ swz) << 4);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) hi_off[ks] = (unsigned)(16 * fp6_piece(lrow, 3 * ks + 2) + 8 * (lhalf ^ ((lrow >> 4) & 1)));
     using FragT = std::conditional_t<FP6, v8i, v4i>;
     using AccT = std::conditional_t<FP6, v16f, v16i>;
     FragT fa[2][4], fb[2][4];
@@ -381,7 +388,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         FragT &dst = isA[q] ? fa[buf][idx[q]] : fb[buf][idx[q]];
         if constexpr (FP6) {
             const v4i lo = *reinterpret_cast<const v4i *>(src + kc_off[ks]);
-            const v2i hi = *reinterpret_cast<const v2i *>(src + 48 * ks + 32 + 8 * (lhalf ^ ((lrow >> 4) & 1)));
+            const v2i hi = *reinterpret_cast<const v2i *>(src + hi_off[ks & 1]);
             dst[0] = lo[0]; dst[1] = lo[1]; dst[2] = lo[2]; dst[3] = lo[3];
             dst[4] = hi[0]; dst[5] = hi[1];
         } else {
@@ -460,9 +467,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         asm volatile("" : "+s"(i));
         return __builtin_amdgcn_readlane(tile_meta, i);
     };
-    if (MODE == 0 && FP6) asm volatile("s_waitcnt vmcnt(15)" ::: "memory");
+    if (MODE == 0 && FP6) asm volatile("s_waitcnt vmcnt(13)" ::: "memory");
     else if (MODE == 0) asm volatile("s_waitcnt vmcnt(17)" ::: "memory");
-    else if (FP6) asm volatile("s_waitcnt vmcnt(14)" ::: "memory");
+    else if (FP6) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -587,8 +594,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             half_setup(true, kt + 2, ring(sa, 4));
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (FP6) {  // two k-steps of 64 columns: the first streams A(kt+2), the second B(kt+2)
-                step(0, stA, stB, 1, true, 0, 7);
-                asm volatile("s_waitcnt vmcnt(7) lgkmcnt(0)" ::: "memory");
+                step(0, stA, stB, 1, true, 0, kLoads);
+                asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)" ::: "memory");
             } else {
                 step(0, stA, stB, 1, true, 0, 3);
                 step(1, stA, stB, 2, true, 3, 3);
@@ -1132,11 +1139,11 @@ constexpr int kSmallWaves = 4, kSmallThreads = 64 * kSmallWaves;
 constexpr int kSmallPitch = 72;  // the two half-waves of an accumulator register sit four rows apart: 32 banks
 constexpr int kSmallMeta = 2 * kChunk * (int)sizeof(int32_t);  // a word per source row and per source column of the chunk pair
 constexpr int kSmallFold = kChunk * kSmallPitch * (int)sizeof(int32_t);
-__host__ __device__ constexpr int small_stage_bytes(bool fp6) { return 2 * kChunk * (fp6 ? 112 : BK); }
+__host__ __device__ constexpr int small_stage_bytes(bool fp6) { return 2 * kChunk * (fp6 ? 96 : BK); }
 
 template <bool FP6, bool BATCH>
 __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const GemmArgs g) {
-    constexpr int kRowB = FP6 ? 96 : BK, kPitch = FP6 ? 112 : BK, kLoads = FP6 ? 7 : 8;  // as in gemm_body
+    constexpr int kRowB = FP6 ? 96 : BK, kPitch = kRowB, kLoads = FP6 ? 6 : 8;  // as in gemm_body
     constexpr int kSteps = FP6 ? 2 : 4;                                                  // matrix instructions along a k-tile
     extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
     int32_t *rowmeta = reinterpret_cast<int32_t *>(smem), *colmeta = rowmeta + kChunk;
@@ -1196,17 +1203,15 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
     unsigned voffA[kLoads], voffB[kLoads];
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
-        int row, byte;
         if (FP6) {
-            const int slot = u * 64 + lane;
-            row = slot / 7;
-            byte = min(slot - 7 * row, 5) * 16;
+            const int slot = u * 64 + lane, row = slot / 6, byte = fp6_piece(row, slot - 6 * row) * 16;
+            voffA[u] = (unsigned)fp6_ktile(row, 0, ldA) + (unsigned)byte;
+            voffB[u] = (unsigned)fp6_ktile(row, 0, ldB) + (unsigned)byte;
         } else {
-            row = 8 * u + (lane >> 3);
-            byte = ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+            const int row = 8 * u + (lane >> 3), byte = ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+            voffA[u] = (unsigned)row * (unsigned)ldA + (unsigned)byte;
+            voffB[u] = (unsigned)row * (unsigned)ldB + (unsigned)byte;
         }
-        voffA[u] = (unsigned)row * (unsigned)ldA + (unsigned)byte;
-        voffB[u] = (unsigned)row * (unsigned)ldB + (unsigned)byte;
     }
     const int8_t *sa = stages + wave * small_stage_bytes(FP6), *sb = sa + kChunk * kPitch;  // the wave's stage
     const int step = g.kwaves;
@@ -1232,7 +1237,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
     // decoded tokens fills one).
     auto contract = [&](auto ra_c) {
         constexpr int RA = decltype(ra_c)::value;
-        constexpr int kLoadsA = RA == 2 ? kLoads : 4;
+        constexpr int kLoadsA = RA == 2 ? kLoads : kLoads / 2;
         // starts the loads of k-tile kt; returns the Horner shift between the wave's k-tile before and this one
         auto fetch = [&](int kt) {
             int sh = 0;
@@ -1240,8 +1245,9 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
                 sh += __builtin_amdgcn_readlane(v_shift, seg);
                 ++seg;
             }
-            const int8_t *pa = uniform_ptr(gA + (int64_t)(kt + __builtin_amdgcn_readlane(v_delta, seg)) * kRowB);
-            const int8_t *pb = uniform_ptr(gB + (int64_t)kt * kRowB);
+            const int blk = kt + __builtin_amdgcn_readlane(v_delta, seg);
+            const int8_t *pa = uniform_ptr(gA + (FP6 ? fp6_ktile(0, blk, ldA) : (int64_t)blk * kRowB));
+            const int8_t *pb = uniform_ptr(gB + (FP6 ? fp6_ktile(0, kt, ldB) : (int64_t)kt * kRowB));
             const unsigned dst = __builtin_amdgcn_readfirstlane((unsigned)(size_t)sa);
 #pragma unroll
             for (int u = 0; u < kLoadsA; ++u) dma16(dst + u * 1024, voffA[u], pa);
@@ -1256,8 +1262,8 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
             auto load_frag = [&](const int8_t *half, int k) {
                 const int8_t *row = half + lrow * kPitch;
                 if constexpr (FP6) {
-                    const v4i lo = *reinterpret_cast<const v4i *>(row + 48 * k + 16 * lhalf);
-                    const v2i hi = *reinterpret_cast<const v2i *>(row + 48 * k + 32 + 8 * (lhalf ^ ((lrow >> 4) & 1)));
+                    const v4i lo = *reinterpret_cast<const v4i *>(row + 16 * fp6_piece(lrow, 3 * k + lhalf));
+                    const v2i hi = *reinterpret_cast<const v2i *>(row + 16 * fp6_piece(lrow, 3 * k + 2) + 8 * (lhalf ^ ((lrow >> 4) & 1)));
                     return v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], 0, 0};
                 } else {
                     return *reinterpret_cast<const v4i *>(row + (((2 * k + lhalf) ^ ((lrow >> 1) & 7)) << 4));

@@ -250,8 +250,8 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
                                    t3 = fp6_pack4((unsigned)o.w);
                     // the unit is the lower or the upper half of a 32-column fragment (see fp6_dword in common.h)
                     const int d0 = (int)(t0 | (t1 << 24)), d1 = (int)((t1 >> 8) | (t2 << 16)), d2 = (int)((t2 >> 16) | (t3 << 8));
-                    int8_t *row = a.out + (int64_t)p * a.ld;
-                    const int grp = upos >> 2, frag = (upos >> 1) & 1;
+                    int8_t *row = a.out + fp6_ktile(p, upos >> 3, a.ld);
+                    const int grp = (upos >> 2) & 1, frag = (upos >> 1) & 1;
                     if ((upos & 1) == 0) {
                         v3i_u w3;
                         w3.x = d0; w3.y = d1; w3.z = d2;
@@ -261,6 +261,10 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
                         v2i_u w2;
                         w2.x = d1; w2.y = d2;
                         *reinterpret_cast<v2i_u *>(row + 4 * fp6_dword(p, grp, frag, 4)) = w2;
+                    }
+                    if ((p & 1) && upos >= 8 && (upos >> 3) % 2 == 0 && (upos >> 3) + 1 == a.W / kKPad) {  // the place of no k-tile
+                        int *none = reinterpret_cast<int *>(a.out + (int64_t)p * a.ld + 12 * upos);
+                        none[0] = none[1] = none[2] = 0;
                     }
                 } else {
                     *reinterpret_cast<int4 *>(a.out + (int64_t)p * a.ld + q0) = o;
@@ -468,8 +472,8 @@ __global__ void fixup_kernel(FixupArgs fa, FixupArgs fb, int blocks_a, int block
                         const unsigned code = (fp6_codes4((unsigned)(uint8_t)dg) & 0x3fu);
                         const int col = at;
                         const unsigned bit = 6u * (unsigned)(col & 31);  // inside the 32-column fragment
-                        unsigned *row = reinterpret_cast<unsigned *>(f.out + (int64_t)p * f.W);
-                        const int grp = col >> 6, frag = (col >> 5) & 1, i = (int)(bit >> 5);
+                        unsigned *row = reinterpret_cast<unsigned *>(f.out + fp6_ktile(p, col >> 7, f.W));
+                        const int grp = (col >> 6) & 1, frag = (col >> 5) & 1, i = (int)(bit >> 5);
                         atomicOr(row + fp6_dword(p, grp, frag, i), code << (bit & 31u));
                         if ((bit & 31u) > 26u) atomicOr(row + fp6_dword(p, grp, frag, i + 1), code >> (32u - (bit & 31u)));
                     } else {
@@ -585,20 +589,20 @@ __global__ void reset_bound_kernel(PlanHeader *hdr, unsigned long long *rowsum_a
     for (int t = t0; t < lists; t += stride) list_len[t] = 0;
 }
 
-// canon[R][c] = phys[row_phys[R]][col_phys[c]]; Kp: stored columns per physical row
-__global__ void canonical_kernel(const int8_t *__restrict__ phys, int Kp, const int32_t *row_phys,
+// canon[R][c] = phys[row_phys[R]][col_phys[c]]; ld: bytes from one physical row to the next
+__global__ void canonical_kernel(const int8_t *__restrict__ phys, int ld, const int32_t *row_phys,
                                  const int32_t *col_phys, int nrows, int ncols, int8_t *__restrict__ canon, int fp6) {
     const int R = blockIdx.x;
     if (R >= nrows) return;
-    const int8_t *src = phys + (int64_t)row_phys[R] * Kp;
+    const int8_t *src = phys + (int64_t)row_phys[R] * ld;
     for (int c = threadIdx.x; c < ncols; c += blockDim.x) {
         int8_t v;
         if (fp6) {  // e2m3 code at bit 6 * column -> the integer it stands for (digits are integers)
             const int col = col_phys[c];
             const unsigned bit = 6u * (unsigned)(col & 31);
-            const unsigned *row = reinterpret_cast<const unsigned *>(src);
-            const int grp = col >> 6, frag = (col >> 5) & 1, i = (int)(bit >> 5);
             const int pr = row_phys[R];
+            const unsigned *row = reinterpret_cast<const unsigned *>(phys + fp6_ktile(pr, col >> 7, ld));
+            const int grp = (col >> 6) & 1, frag = (col >> 5) & 1, i = (int)(bit >> 5);
             unsigned long long two = row[fp6_dword(pr, grp, frag, i)];
             if ((bit & 31u) > 26u) two |= (unsigned long long)row[fp6_dword(pr, grp, frag, i + 1)] << 32;
             const unsigned code = (unsigned)(two >> (bit & 31u)) & 0x3fu;

@@ -439,6 +439,30 @@ def test_six_bit_floating_point_digits(imu, sa, sb, b):
     check_against_oracle(imu, Aq, Bq, b, sa, sb, fp6=True)
 
 
+@pytest.mark.parametrize("sa,sb", [(ROW, COL), (BOTH, BOTH)])
+@pytest.mark.parametrize("n,h,d", [(70, 40, 100), (70, 300, 257), (300, 520, 300), (290, 330, 2810)])
+def test_six_bit_rows_that_share_their_bytes(imu, n, h, d, sa, sb):
+    """One, two, an odd number of k-tiles, and rows wide enough to be padded: the last k-tile of an odd number has no partner, and its
+    place in the odd row holds zeros.  The buffers hold other bytes before."""
+    rng = np.random.default_rng(d)
+    Aq, Bq = rand_ints(rng, n, d, 8, 0.01, 2), rand_ints(rng, h, d, 8, 0.01, 2)
+    A_d, B_d = dev(torch.from_numpy(Aq)), dev(torch.from_numpy(Bq))
+    plan = imu.imunpack_plan(A_d, B_d, 4, sa, sb)
+    plan.set_digits(imu.DIGITS_FP6)
+    ba, bb, _ = plan.unpacked_bytes()
+    A6, B6 = torch.full((ba,), 0x55, dtype=torch.int8, device="cuda"), torch.full((bb,), 0x55, dtype=torch.int8, device="cuda")
+    imu.imunpack_unpack(plan, A_d, B_d, A6, B6)
+    for got, want in zip(imu.imunpack_unpack_canonical(plan, A6, B6), oracle.unpack_pair_handle(Aq, Bq, 4, sa, sb).operands_i8()):
+        assert np.array_equal(got.cpu().numpy(), want)
+    for buf, (rows, width, pitch) in zip((A6, B6), plan.layout()):
+        if width // 128 % 2 and width > 128:
+            assert not buf.view(rows, pitch)[1::2, width * 3 // 4 - 96:width * 3 // 4].any()
+    C = torch.empty((n, h), dtype=torch.float32, device="cuda")
+    imu.imunpack_gemm(plan, A6, B6, 1.0, 1.0, None, C, torch.empty(plan.unpacked_bytes()[2] // 8, dtype=torch.int64, device="cuda"))
+    want = oracle.dequantize(oracle.int_gemm(Aq, Bq), 1.0, 1.0)
+    assert (np.abs(C.cpu().numpy() - want) <= 1e-6 * np.abs(want)).all()
+
+
 def test_six_bit_digits_fused_path_and_format_rules(imu):
     """A case whose accumulator bound stays below 2^24 runs the fused 6-bit kernel (Horner step as a
     multiplication by a power of two in binary32); the format is refused for b > 4, and a plan object
