@@ -1324,14 +1324,15 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
 // product, 70 to 170 us for the items of a batch; this one: 14 to 37 and 14 to 16).  Here every slot stays in the registers of its thread.  A column slot is
 // known by its original column k and its levels eA, eB along A and B, and no two slots share all three; so the slots are a
 // bit per k in a mask per (eA, eB), every rank is a count of bits below k, and the columns of both stores are put together
-// in LDS and written once, by part 0.  Returns false, having written nothing but tables that are written again, if LDS is too
+// in LDS and written once, 1024 at a time by the parts in turn (every part puts all of them together; by one workgroup alone the
+// layouts of 4096 x 8192 by 4096 took 40 us instead of 28, of 12288 slots 36 instead of 28).  Returns false, having written nothing but tables that are written again, if LDS is too
 // small: the same in every part, so that all of them take the general path (many pairs of levels: 300 x 9000 by 300 at b = 2
 // with eight levels on either side, a plan of 204 us in eight parts, 312 in one).
 constexpr int kListed = 1 << 30;   // (of a slot's levels) its column is taken from lists
 constexpr int kColSlotsLds = 12;  // slots per thread: as many as the registers of a 1024-thread workgroup hold
 template <int kSlots, bool LISTS>
 __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColLayout &cols, int d, int cap_phys, int s, int sh,
-                                PlanHeader *hdr, ColTables &t, int32_t *dyn, int dyn_words, int part, const SparseArgs &sp) {
+                                PlanHeader *hdr, ColTables &t, int32_t *dyn, int dyn_words, int part, int parts, const SparseArgs &sp) {
     const int D = hdr->d_u, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (D > kSlots * kPlanThreads) return false;
     for (int x = tid; x < kMaxGroups * kMaxLevelsA; x += kPlanThreads) t.hist2[x] = 0;
@@ -1387,10 +1388,10 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     }
     const int lists = LA * LB, pairs = lists + (LISTS && t.nsparse ? 1 : 0);  // the columns taken from lists have a mask of their own
     if (LA > kMaxLevelsA || LA + LB - 1 > kMaxGroups || (long long)pairs * W * 3 > dyn_words) return false;
-    if (part > 0) {  // where it is certain to fit (see below for what has to), the other parts need not find out
+    if (part > 0) {  // where it is certain to fit (see below for what has to), parts that will have nothing to write need not find out
         const int appended = D - d, pads = kKPad * (LA * LB + LA + LB);
         const int kp = d + appended + appended / 7 + pads + (pairs > lists ? d : 0), ka = hdr->d1 + appended + pads;
-        if (kp <= 256 * kKPad && appended + pads <= 256 * kKPad && pairs * W * 3 + kp + ka <= dyn_words) return true;
+        if (part * kPlanThreads >= kp + ka + kPlanThreads && kp <= 256 * kKPad && appended + pads <= 256 * kKPad && pairs * W * 3 + kp + ka <= dyn_words) return true;
     }
     unsigned long long *mask = reinterpret_cast<unsigned long long *>(dyn);  // [pairs][W]
     int32_t *pre = dyn + 2 * pairs * W;                                       // [pairs][W] slots of the pair below the word
@@ -1444,7 +1445,6 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     const int Kp = t.kp, KA = t.ka, ka_levels = t.ka_levels;
     if (Kp > cap_phys) return true;  // reported: the plan is made again with more room
     if (Kp > 256 * kKPad || KA - ka_levels > 256 * kKPad || (long long)pairs * W * 3 + Kp + KA > dyn_words) return false;
-    if (part > 0) return true;
     int32_t *packA = packB + Kp;  // k | eA << 24 per stored column of A, -1: none
     for (int x = tid; x < Kp + KA; x += kPlanThreads) packB[x] = -1;
     __syncthreads();
@@ -1456,11 +1456,15 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     for (int u = 0; u < kSlots; ++u) {
         if (key[u] < 0) continue;
         const int c = tid + u * kPlanThreads, k = key[u], a = lev[u] & 0xffff, eb = lev[u] >> 16, e = a + eb;
+        auto placed = [&](int q, int qa) {
+            if (u % parts != part) return;  // uniform
+            cols.pcol_slot[q] = c;
+            cols.col_phys[c] = q;
+            cols.acol_phys[c] = qa;
+        };
         if (LISTS && lev[u] & kListed) {  // beside level 0 of A, which holds column k in place
             packB[t.list_col + k] = k | (1 << 24);
-            cols.pcol_slot[t.list_col + k] = c;
-            cols.col_phys[c] = t.list_col + k;
-            cols.acol_phys[c] = k;
+            placed(t.list_col + k, k);
             continue;
         }
         const int stored = t.lvlbase[a] + rank(a * LB, k);  // where level a of A holds column k
@@ -1482,16 +1486,15 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
         }
         packB[q] = k | (eb << 24);
         if (eb == 0) packA[stored] = k | (a << 24);
-        cols.pcol_slot[q] = c;
-        cols.col_phys[c] = q;
-        cols.acol_phys[c] = qa;
+        placed(q, qa);
     }
     __syncthreads();
     // ---- out: sixteen lanes side by side hold a unit (both widths are multiples of 128); its first lane with a column
     // describes it (the first of all if none has)
+    const int step = parts * kPlanThreads, firstA = (part + parts - (Kp + kPlanThreads - 1) / kPlanThreads % parts) % parts;
     auto in_unit = [&](bool f) { return (unsigned)(__ballot(f) >> (lane & 48)) & 0xffffu; };
     auto from = [&](int v, int l) { return __shfl(v, l, 64); };
-    for (int q = tid; q < Kp; q += kPlanThreads) {
+    for (int q = tid + part * kPlanThreads; q < Kp; q += step) {
         const int v = packB[q], k = v == -1 ? -1 : v & 0xffffff, eb = v == -1 ? 0 : (v >> 24) & 0xff, e = t.tile_e[q / kKPad];
         cols.colB_k[q] = k;
         cols.colB_e[q] = eb;
@@ -1504,7 +1507,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
         const bool uniform = in_unit(k < 0 || eb == from(eb, first)) == 0xffffu;
         if (lane == first) cols.unitB[q / 16] = make_int4(k, k, (run ? 1 : 0) | (uniform ? 2 : 0) | 4, eb | (e << 16));
     }
-    for (int q = tid; q < KA; q += kPlanThreads) {
+    for (int q = tid + firstA * kPlanThreads; q < KA; q += step) {
         const int v = packA[q], k = v == -1 ? -1 : v & 0xffffff, a = v == -1 ? 0 : (v >> 24) & 0xff;
         unsigned long long w = 0;  // what an entry of the column weighs: s^e over the slots that read it
         if (k >= 0) {
@@ -1884,8 +1887,8 @@ __global__ __launch_bounds__(256) void publish_kernel(const PlanHeader *hdr, Pla
     publish_header(hdr + blockIdx.y, host + blockIdx.y, seq);
 }
 
-// One to four workgroups for the rows of A, as many for the rows of B, kColBlocks for the columns (all but one of them idle unless
-// there are more column slots or pairs of levels than that one can hold; one for each item of a batch).
+// One to four workgroups for the rows of A, as many for the rows of B, kColBlocks for the columns (those idle that have nothing to write;
+// one for each item of a batch).
 // LISTS: columns of B may be taken from lists (see SparseArgs); then there is no other layout of the columns than the one in LDS, and the
 // host makes the plan again, without lists, if that is refused.  A variant of its own: 20 -> 36 us for a product without lists in one
 // kernel with them.
@@ -1936,14 +1939,14 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
         rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr, bx - slA, slB);
         if (LISTS && bx == slA) sparse_rooms(layB.src_pstart, layB.src_nlev, h, sh, sparse, hdr, lds, fast_rows);
     } else {
-        const int part = bx - slA - slB;
+        const int part = bx - slA - slB, parts = (int)gridDim.x - slA - slB;
         if (LISTS) {
-            if (!cols_layout_lds<kColSlotsLds, true>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part, sparse) && part == 0 &&
+            if (!cols_layout_lds<kColSlotsLds, true>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part, parts, sparse) && part == 0 &&
                 threadIdx.x == 0)
                 hdr->lists_refused = 1;
-        } else if (!cols_layout_lds<kColSlotsLds, false>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part, sparse)) {
+        } else if (!cols_layout_lds<kColSlotsLds, false>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part, parts, sparse)) {
             __syncthreads();
-            cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, part, (int)gridDim.x - slA - slB, tables);
+            cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, part, parts, tables);
         }
         if (part == 0 && threadIdx.x == 0) hdr->bound[0] = hdr->bound[1] = 0;
     }

@@ -439,6 +439,14 @@ def test_six_bit_floating_point_digits(imu, sa, sb, b):
     check_against_oracle(imu, Aq, Bq, b, sa, sb, fp6=True)
 
 
+@pytest.mark.parametrize("sa,sb", [(COL, COL), (ROW, BOTH)])
+@pytest.mark.parametrize("d", [890, 1025, 4100, 9000])
+def test_columns_laid_out_by_several_workgroups(imu, d, sa, sb):
+    """Stored columns from just one step of 1024 to more steps than workgroups that take them in turn."""
+    rng = np.random.default_rng(d)
+    check_against_oracle(imu, rand_ints(rng, 33, d, 16, 0.01, 2), rand_ints(rng, 20, d, 16, 0.002, 2), 5, sa, sb)
+
+
 @pytest.mark.parametrize("sa,sb", [(ROW, COL), (BOTH, BOTH)])
 @pytest.mark.parametrize("n,h,d", [(70, 40, 100), (70, 300, 257), (300, 520, 300), (290, 330, 2810)])
 def test_six_bit_rows_that_share_their_bytes(imu, n, h, d, sa, sb):
