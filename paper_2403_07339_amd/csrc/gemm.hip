@@ -74,8 +74,9 @@ struct GemmArgs {
     int whole_rows;           // results without levels to fold leave row by row (see whole_rows_win)
     int lmaxA;                // largest number of digit levels of a row of A
     int kwaves;               // gemm_small_kernel: waves that share the contraction
-    // columns of B that are taken from lists (SparseLists): they come in before k-tile sp_kt (-1: there are none), where the accumulators
-    // count in units of s, and are followed by a shift of sp_after bits
+    // columns of B that are taken from lists (SparseLists): they come in before k-tile sp_kt (-1: there are none), where the large tiles'
+    // accumulators count in units of s, and are followed by a shift of sp_after bits (which the shift in front of that k-tile, if there is
+    // a group before it, contains: the small tiles, which keep the lists' sums apart, know nothing of sp_after)
     SparseLists sparse;
     const int8_t *at;         // the transposed copy of level 0 of the A store
     int at_cols;              // ... lines of 128 bytes to a block of 128 rows
@@ -579,7 +580,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             : [sh] "s"(shv));
     };
     for (; seg <= nbound && (!SPLIT || kt < kt1); ++seg) {
-        const int shv = seg == seg0 ? 0 : BATCH ? __builtin_amdgcn_readlane(v_shift, seg - 1) : g.bound_sh[seg - 1];
+        int shv = seg == seg0 ? 0 : BATCH ? __builtin_amdgcn_readlane(v_shift, seg - 1) : g.bound_sh[seg - 1];
+        if (LISTS && seg != seg0 && kt == g.sp_kt) shv -= g.sp_after;  // (that much of it comes behind the lists)
         if (shv != 0) horner(shv);  // start of the next exponent group
         if constexpr (LISTS)
             if (kt == g.sp_kt) {  // (the first k-tile of a segment)
@@ -626,7 +628,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     if constexpr (SPLIT) {
         if (pc.parts > 1) {
             for (int x = seg - 1; x < nbound; ++x) rest += g.bound_sh[x];
-            if (LISTS && g.sp_kt >= kt1) rest += g.sp_after;
             int32_t *meet = g.meet + 2 * pc.slot, *sums = g.sums + (size_t)pc.slot * (BM * BN) + 4 * tid;
             int32_t *turn = reinterpret_cast<int32_t *>(smem);
             if (tid == 0) *turn = __hip_atomic_fetch_add(meet, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1574,10 +1575,7 @@ static void fused_args(GemmArgs &g, const Plan *p) {
         int r = 0;
         while (h.grp_exp[h.run_grp[r]] > 1) ++r;
         g.sp_kt = h.run_kt0[r];
-        if (h.grp_exp[h.run_grp[r]] == 0) {
-            g.sp_after = p->sh;
-            if (r > 0) g.bound_sh[r - 1] -= p->sh;
-        }
+        if (h.grp_exp[h.run_grp[r]] == 0) g.sp_after = p->sh;
     }
     // |accumulator| < 2^31, weights up to s^(levels of a row - 1 + levels of a column - 1)
     g.fold_f64 = 31 + p->sh * ((h.lmaxA - 1) + (h.lmaxB - 1)) <= 52;

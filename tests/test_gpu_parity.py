@@ -1618,3 +1618,44 @@ def test_appended_columns_of_few_digits(imu, n, d, h, sa, longer, parts):
     imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, None, None, ws, fuse=False)
     imu.imunpack_recombine(plan, ws, 1.0, 1.0, C_int, None)
     assert torch.equal(C_int.double(), want[:rows])
+
+
+def _few_digits(rng, n, d, h, deep, deep_cols=24):
+    """In-Bound integers but for four entries of two digits in every column of B and, if `deep`, five of three in some of
+    them, no two of those in one row; a few rows of A have two levels."""
+    A = rng.integers(-127, 128, (n, d)).astype(np.int32)
+    B = rng.integers(-127, 128, (h, d)).astype(np.int32)
+    A[::7, rng.integers(0, d)] = 3000
+    for k in range(d):
+        B[rng.choice(h, 4, replace=False), k] = rng.integers(128, 128 ** 2, 4) * rng.choice([-1, 1], 4)
+    if deep:
+        cols = np.arange(deep_cols) * (d // deep_cols)
+        at = rng.choice(h, (deep_cols, 5), replace=False)
+        B[at, cols[:, None]] = rng.integers(128 ** 2, 128 ** 3, at.shape) * rng.choice([-1, 1], at.shape)
+    return torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+
+
+@pytest.mark.parametrize("n,d,h,deep,parts", [
+    (20, 1100, 4100, False, 0),    # 64 x 64 tiles: a single exponent group beside the lists
+    (20, 1100, 4100, True, 0),     # ... columns of exponent 2 before them
+    (150, 1070, 4165, True, 0),
+    (2000, 1060, 4100, False, 1),  # 256 x 256 tiles
+    (2000, 1060, 4100, True, 1),
+    (400, 5800, 13000, True, 2),   # ... cut along the contraction (2: in two parts or more)
+])
+def test_no_stored_column_has_the_exponent_of_the_lists(imu, n, d, h, deep, parts):
+    """Every column of exponent 1 is taken from lists: the shift from the groups above to the lowest one is that over two
+    exponents, with the lists in between."""
+    A, B = _few_digits(np.random.default_rng(n + d), n, d, h, deep, 200 if parts == 2 else 24)
+    want = A.double() @ B.double().t()      # exact: below 2^53
+    plan = imu.imunpack_plan(A, B, 8, ROW, BOTH)
+    col_exp = plan.export()[5].numpy()
+    assert int((col_exp == 1).sum()) == imu.imunpack_diag_list_columns(plan) > d // 2 and (int(col_exp.max()) == 2) == deep
+    A_ue, B_eu = imu.imunpack_unpack(plan, A, B)
+    C = torch.full((n, h), 3.5, device="cuda")
+    C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, None, C, None)
+    assert min(imu.imunpack_diag_gemm_parts(plan), 2) == parts
+    imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
+    scale = float(np.float32(0.013)) * float(np.float32(0.0021))
+    assert torch.equal(C_int.double(), want) and torch.equal(C, (want * scale).float())
