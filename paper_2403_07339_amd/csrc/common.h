@@ -91,7 +91,7 @@ struct PlanHeader {
     int32_t nsparse;                 // columns that the fused GEMM takes from lists (see SparseLists) ...
     int32_t list_kt0;                // ... instead of the k-tiles of B_eu from this one on, the last run
     int32_t lists_refused;           // ... which this plan cannot have: it has to be made again without
-    int32_t sparse_room;             // places that their lists of digits take
+    int32_t sparse_room;             // places that the longest list of digits would have needed, if one was too short (else 0)
     int32_t overflow;                // bit set: which capacity was too small
     int32_t need[10];                // size that would have been needed, per capacity
     int32_t err;                     // IMUNPACK_ERANGE conditions found on the device
@@ -116,7 +116,8 @@ struct KeepState {
 };
 
 enum CapIndex { CAP_ROWA = 0, CAP_ROWB = 1, CAP_C1 = 2, CAP_C2 = 3, CAP_EDGEA = 4, CAP_EDGEB = 5, CAP_OB = 6,
-                CAP_LISTA = 7, CAP_LISTB = 8, CAP_SPARSE = 9 };  // the last two: a caller's OB list was too short
+                CAP_LISTA = 7, CAP_LISTB = 8,  // (a caller's OB list was too short)
+                CAP_SPARSE = 9 };              // places in a list of SparseLists
 
 // Physical-row description used by scatter and by the GEMM epilogue.
 struct RowLayout {
@@ -163,9 +164,11 @@ struct ColLayout {
 // Columns that UnpackBoth appends to B for a few heavy hitters hold next to nothing but zeros (on a 11008 x 4096 weight with
 // 0.1 % of them 9 digits in 11008 places, and there is one for nearly every original column), yet multiplied as columns they double the
 // contraction.  Those that carry digit 1 along the columns of an original column (level 0 along A, exponent 1) and few enough
-// digits come last in B_eu, in a run of their own that the fused GEMM leaves out: their digits go into a list for every kSparseRows
-// physical rows of B as well, and the GEMM multiplies a list's digits, 32 at a time, with the columns of A that they meet, which it
+// digits come last in B_eu, in a run of their own that the fused GEMM leaves out: the plan holds their digits in a list for every kSparseRows
+// physical rows of B, and the GEMM multiplies a list's digits, 32 at a time, with the columns of A that they meet, which it
 // reads from a transposed copy of level 0 of the A store.  Every product of two digits other than zero is still the low-bit GEMM's.
+// The lists are written once, by the launch that completes the plan (lists_kernel): an unpack, which may come again, from a graph or
+// beside a GEMM on another stream, leaves them alone.
 // 4096 x 4096 by 11008: GEMM 331 -> 257 us and a step 446 -> 388 on resident weights; 754 -> 729 where the weights are unpacked in
 // every step (planner 7 us more, the copy 5); 16 rows against resident weights that no cache holds 115 -> 88.
 //
@@ -175,10 +178,9 @@ struct ColLayout {
 constexpr int kSparseRows = 32;
 constexpr uint32_t kSparseLine = 0x00ffff80u;  // of an entry: its line in the copy (the column layout in LDS takes 12288 slots, so k < 2^17)
 struct SparseLists {
-    int32_t *off;       // [Np / kSparseRows + 1] where a list begins (a multiple of 32)
-    int32_t *cnt;       // [Np / kSparseRows] entries it holds
-    uint32_t *ent;
-    int32_t cap;        // places in ent
+    int32_t *cnt;       // [Np / kSparseRows] entries in a list
+    uint32_t *ent;      // list x begins at entry x * cap
+    int32_t cap;        // places in a list (a multiple of 32)
 };
 
 // ---- batches.  The items of a batch (products of one shape) are planned, unpacked and multiplied by the
@@ -283,6 +285,24 @@ __host__ __device__ __forceinline__ int fp6_dword(int row, int grp, int frag, in
 // scatter that writes them 67 -> 71.
 __host__ __device__ __forceinline__ int64_t fp6_ktile(int row, int kt, int64_t ld) {
     return ((row & ~1) + (kt & 1)) * ld + (kt >> 1) * 192 + (row & 1) * 96;
+}
+// The digits above digit 0 of an OB entry of magnitude av at row slot R and column slot C of an operand unpacked by UnpackBoth,
+// emit(row slot, column slot, digit) for those that are not zero: the remainder floor(av / s) moves to the child of whichever of R
+// and C was split first (Alg. 4 lines 7-9 / 11-14).
+template <class E>
+__device__ __forceinline__ void digits_above(const SlotSet &rows, const SlotSet &cols, int R, int C, unsigned av, int sh, E emit) {
+    unsigned rem = av;
+    for (int step = 0; step < 40; ++step) {
+        rem >>= sh;
+        if (rem == 0) break;
+        const uint32_t tr = rows.time[R], tc = cols.time[C];
+        if (tr < tc) R = rows.child[R];
+        else if (tc != kNever) C = cols.child[C];
+        else break;  // an OB remainder nothing splits: not a complete plan
+        if (R < 0 || C < 0) break;
+        const int m = (int)(rem & ((1u << sh) - 1u));
+        if (m != 0) emit(R, C, m);
+    }
 }
 // Lane 63's value in every lane (a scalar register).
 __device__ __forceinline__ int from_lane63(int v) { return __builtin_amdgcn_readlane(v, 63); }

@@ -492,21 +492,21 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         const int block0 = (n0 + wn * 128) / kSparseRows;
         int8_t *lds = smem + ring(sa, 4) * kHalfBytes + wave * kWaveBytes;
         static_assert(list_lds(4) <= kWaveBytes, "LDS of the lists");
-        // lane 0 .. 4: where the lists of the wave's blocks begin and the last one ends; 8 .. 11: their lengths
-        const int bounds = lane < 8 ? g.sparse.off[block0 + min(lane, 4)] : g.sparse.cnt[block0 + min(lane - 8, 3)];
+        const int lens = min(g.sparse.cnt[block0 + min(lane, 3)], g.sparse.cap);  // lane 0 .. 3: how long the lists of the wave's blocks are
+        int list = block0 * g.sparse.cap;  // (no more than kSparsePlaces)
         ListWords<4> words;  // the next 128 entries, or the first of the list behind
-        words.load(g.sparse.ent + __builtin_amdgcn_readlane(bounds, 0), lane);
+        words.load(g.sparse.ent + list, lane);
         auto block = [&](auto cb_c) __attribute__((always_inline)) {
             constexpr int CB = decltype(cb_c)::value;
-            const int from = __builtin_amdgcn_readlane(bounds, CB), after = __builtin_amdgcn_readlane(bounds, CB + 1);
-            const int len = min(__builtin_amdgcn_readlane(bounds, CB + 8), after - from);
-            if (len <= 0) words.load(g.sparse.ent + after, lane);  // (there are none of this list)
+            const int len = __builtin_amdgcn_readlane(lens, CB);
+            const int next = list + g.sparse.cap;
+            if (len <= 0) words.load(g.sparse.ent + next, lane);  // (there are none of this list)
             for (int t = 0; t < len; t += 128) {
                 words.stage(lds, len - t, lane);
                 unsigned x[4][16];
 #pragma unroll
                 for (int s = 0; s < 4; ++s) list_columns(x[s], lds + 4096, s, lhalf, at, row_off);
-                words.load(g.sparse.ent + (t + 128 < len ? from + t + 128 : after), lane);
+                words.load(g.sparse.ent + (t + 128 < len ? list + t + 128 : next), lane);
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     if (t + 32 * s >= len) break;  // uniform
@@ -518,6 +518,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                         if constexpr (LISTS) mfma_in_place(fr[rb], fd, acc[rb][CB]);
                 }
             }
+            list = next;
         };
         block(std::integral_constant<int, 0>{});
         block(std::integral_constant<int, 1>{});
@@ -1325,11 +1326,12 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) list_acc[i][j][r] = 0;
-                const int block = 2 * cn + j, from = g.sparse.off[block], to = g.sparse.off[block + 1], len = min(g.sparse.cnt[block], to - from);
+                const int block = 2 * cn + j, len = min(g.sparse.cnt[block], g.sparse.cap);
+                const uint32_t *list = g.sparse.ent + (size_t)block * g.sparse.cap;
                 for (int t = wave * 32; t < len; t += step * 32) {
                     ListWords<1> words;
                     unsigned x[16];
-                    words.load(g.sparse.ent + from + t, lane);
+                    words.load(list + t, lane);
                     words.stage(lds, len - t, lane);
                     list_columns(x, lds + 1024, 0, lhalf, at, (unsigned)lrow * 4u);
                     const v4i fd = *reinterpret_cast<const v4i *>(lds + 16 * lane);

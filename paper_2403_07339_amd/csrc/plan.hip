@@ -1200,10 +1200,11 @@ struct ColTables {
 // they have to be half of these.
 constexpr int kSparseShare = 384, kSparseLeast = 512;
 constexpr int64_t kSparseEntries = 1 << 22;  // of B
+constexpr int64_t kSparsePlaces = 1 << 26;   // in all lists
 struct SparseArgs {
-    const int32_t *colcnt, *rowcnt, *rowmax;  // statistics of B
+    const int32_t *colcnt;  // of B
     int h;
-    SparseLists lists;
+    int32_t *cnt;           // the lengths of the lists, cleared
 };
 
 __device__ __forceinline__ void level_bases(ColTables &t) {
@@ -1827,42 +1828,57 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
     }
 }
 
-// Room for the lists of SparseLists: the heavy hitters of a row of B, for every further digit, in each block that holds one of its
-// physical rows.  One workgroup, behind the layout of the rows; `room`: Np / kSparseRows words of LDS.  Lists that do not fit
-// are not begun: the host sees from sparse_room that the plan has to be made again, if any column is kept that way.
-__device__ __forceinline__ void sparse_rooms(const int32_t *src_pstart, const int32_t *src_nlev, int h, int sh, const SparseArgs &sp, PlanHeader *hdr, int *lds, int32_t *room) {
-    __shared__ unsigned long long s_total;
-    __syncthreads();
-    if (__syncthreads_or(load_agent(&hdr->overflow) | load_agent(&hdr->err))) return;  // (as the waves of this workgroup see it together)
-    const int nblocks = load_agent(&hdr->Np) / kSparseRows, step = load_agent(&hdr->evenB) ? kEvenStep : 1;
-    for (int x = threadIdx.x; x < nblocks; x += kPlanThreads) room[x] = 0;
-    if (threadIdx.x == 0) s_total = 0;
-    __syncthreads();
-    unsigned long long mine = 0;
-    for (int i = threadIdx.x; i < h; i += kPlanThreads) {
-        const int cnt = sp.rowcnt[i];
-        if (cnt == 0) continue;
-        const int digits = cnt * (digit_levels(sp.rowmax[i], sh) - 1), at = src_pstart[i], lev = src_nlev[i];
-        for (int l = 0; l < lev; ++l) atomicAdd(&room[(at + l * step) / kSparseRows], digits);
-        mine += (unsigned long long)digits * (unsigned)lev;
+// A place in the list of `block` for every lane that gets here together: one atomic per list named, all of them in flight together (the
+// entries of a block of rows sit side by side in the OB list; an atomic to each lane: 36 us for 37 000 entries).
+__device__ __forceinline__ int list_place(int32_t *cnt, int block) {
+    const int lane = threadIdx.x & 63;
+    unsigned long long pending = __ballot(1);
+    int lead = lane, before = 0, count = 0;
+    while (pending) {
+        const int first = __builtin_ctzll(pending);
+        const unsigned long long same = __ballot(block == __builtin_amdgcn_readlane(block, first));
+        if ((same >> lane) & 1) {
+            lead = first;
+            before = __popcll(same & ((1ull << lane) - 1ull));
+            count = __popcll(same);
+        }
+        pending &= ~same;
     }
-    if (mine) atomicAdd(&s_total, mine);
-    __syncthreads();
-    const unsigned long long need = s_total + 32ull * nblocks;
-    if (need > (unsigned long long)sp.lists.cap) {
-        if (threadIdx.x == 0) hdr->sparse_room = (int32_t)min(need, 1ull << 30);
-        return;
-    }
-    const int total = ordered_scan(
-        nblocks, 0, [&](int x) { return (room[x] + 31) & ~31; },
-        [&](int x, int pre) {
-            sp.lists.off[x] = pre;
-            sp.lists.cnt[x] = 0;
-        },
-        lds);
-    if (threadIdx.x == 0) {
-        sp.lists.off[nblocks] = total;
-        hdr->sparse_room = (int32_t)need;
+    int base = 0;
+    if (lane == lead) base = atomicAdd(&cnt[block], count);
+    return __shfl(base, lead, 64) + before;
+}
+
+// The digits of the columns that the fused GEMM takes from lists, into the lists: level by level like the fix-up behind the scatter, which
+// writes the same digits to B_eu.  The digits of a list stand in no particular order; one that is too short is reported.  Bound by the
+// latency of an entry's dependent reads: 45 000 entries of 11008 x 4096 weights 7.7 us.  (Places counted row by row ahead of them, in the
+// layouts' launch, and the lists filled by the fix-up: layouts 41 us instead of 27, fix-up 15 instead of 12.)
+struct ListsArgs {
+    const int32_t *ob;       // [3][ob_cap] the OB entries of B, kept by the plan
+    int ob_cap, sh;
+    SlotSet rows, cols;      // of the second unpacking
+    const int32_t *row_phys, *col_phys;
+    const int32_t *skip;     // keep-weights mode: set if they stand as they are
+    PlanHeader *hdr;
+    SparseLists lists;
+};
+__global__ __launch_bounds__(256) void lists_kernel(ListsArgs f) {
+    PlanHeader *hdr = f.hdr;
+    if (hdr->nsparse == 0 || hdr->overflow || hdr->err || (f.skip && *f.skip)) return;
+    const int n = min(hdr->nobB, f.ob_cap), list_col = hdr->list_kt0 * kKPad;
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+        const int v = f.ob[2 * (size_t)f.ob_cap + t];
+        const unsigned av = v < 0 ? 0u - (unsigned)v : (unsigned)v;
+        // (the copies of a column that A's unpacking repeats belong to higher levels along A, which are not listed)
+        digits_above(f.rows, f.cols, f.ob[t], f.ob[f.ob_cap + t], av, f.sh, [&](int R, int C, int m) {
+            const int k = f.col_phys[C] - list_col;
+            if (k < 0) return;
+            const int p = f.row_phys[R], block = p / kSparseRows, pos = list_place(f.lists.cnt, block);
+            if (pos < f.lists.cap)
+                f.lists.ent[(size_t)block * f.lists.cap + pos] = (uint32_t)(p % kSparseRows) | (uint32_t)k << 7 | (uint32_t)(uint8_t)(int8_t)(v < 0 ? -m : m) << 24;
+            else
+                atomicMax(&hdr->sparse_room, pos + 1);
+        });
     }
 }
 
@@ -1937,7 +1953,8 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
             if (!small_tiles_win(up(nu, kTile) * up(hu, kTile), up(nu, kChunk) * up(hu, kChunk), up(hdr->d_u, kKPad), true, 25)) chunkB = kTile;
         }
         rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr, bx - slA, slB);
-        if (LISTS && bx == slA) sparse_rooms(layB.src_pstart, layB.src_nlev, h, sh, sparse, hdr, lds, fast_rows);
+        if (LISTS && bx == slA)
+            for (int x = threadIdx.x; x < cap_physB / kSparseRows; x += kPlanThreads) sparse.cnt[x] = 0;
     } else {
         const int part = bx - slA - slB, parts = (int)gridDim.x - slA - slB;
         if (LISTS) {
@@ -2015,12 +2032,13 @@ static inline int phys_cap_cols(int cap) { return cap + kMaxGroups * kKPad; }
 
 static constexpr int kLayoutLdsMax = 140 * 1024;  // dynamic LDS the layouts kernel may use (its static tables take about 11 KiB)
 
+static inline int list_count(const Plan *p) { return phys_cap_rows(p->cap[CAP_ROWB]) / kSparseRows; }
 // Whether appended columns of B may be taken from lists: those of UnpackBoth, whose heavy hitters the plan holds one by one; a product of
-// its own; digits that stay int8 (the six-bit format may be asked for once the plan is made); a word of LDS per list; B large enough
-// for its unpacked columns to be worth more than the lists' share of the planner.
+// its own; digits that stay int8 (the six-bit format may be asked for once the plan is made); B large enough
+// for its unpacked columns to be worth more than the lists' share of the planner, and lists that stay within 256 MiB.
 static inline bool sparse_possible(const Plan *p) {
     return p->d >= kSparseLeast && p->h * p->d >= kSparseEntries && p->sB == IMUNPACK_BOTH && p->nitems == 1 && p->b > 4 && !p->no_sparse && 2 * p->d + 512 <= kColSlotsLds * kPlanThreads &&
-           phys_cap_rows(p->cap[CAP_ROWB]) / kSparseRows <= kLayoutLdsMax / (int)sizeof(int32_t);
+           (int64_t)list_count(p) * p->cap[CAP_SPARSE] <= kSparsePlaces;
 }
 
 // Lays every device array out in the arena for the current capacities: the headers of all items, then the
@@ -2103,10 +2121,8 @@ static size_t carve(Plan *p, char *base, bool own_statsA, bool own_statsB) {
     }
     p->sparse = SparseLists{};
     if (sparse_possible(p)) {
-        const int blocks = phys_cap_rows(p->cap[CAP_ROWB]) / kSparseRows;
-        p->sparse.off = cv.take<int32_t>(blocks + 1);
-        p->sparse.cnt = cv.take<int32_t>(blocks);
-        p->sparse.ent = cv.take<uint32_t>(p->cap[CAP_SPARSE] + 256);  // (the GEMM asks for 128 at a time, and once more behind a list)
+        p->sparse.cnt = cv.take<int32_t>(list_count(p));
+        p->sparse.ent = cv.take<uint32_t>((size_t)list_count(p) * p->cap[CAP_SPARSE] + 256);  // (the GEMM asks for 128 at a time, and once more behind a list)
         p->sparse.cap = p->cap[CAP_SPARSE];
         p->at = cv.take<int8_t>((size_t)p->at_rows * (size_t)d);
     }
@@ -2207,7 +2223,7 @@ __device__ bool keep_decide(const KeepArgs &k, const SlotSet &c1, PlanHeader *hd
             hdr->h_u = o.h_u; hdr->d_u = o.d_u; hdr->nobB = o.nobB; hdr->edgesB = o.edgesB; hdr->extras = o.extras;
             hdr->Np = o.Np; hdr->Kp = o.Kp; hdr->KA = o.KA; hdr->ldA = o.ldA; hdr->ldB = o.ldB;
             hdr->ntiles = o.ntiles; hdr->lmaxB = o.lmaxB; hdr->chunkB = o.chunkB; hdr->evenB = o.evenB; hdr->ngroups = o.ngroups; hdr->nruns = o.nruns;
-            hdr->nsparse = o.nsparse; hdr->list_kt0 = o.list_kt0; hdr->sparse_room = o.sparse_room;
+            hdr->nsparse = o.nsparse; hdr->list_kt0 = o.list_kt0;
         } else if (h) {
             hdr->h_u = h;
         }
@@ -2536,7 +2552,7 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
     // ---- physical layouts
     const int col_blocks = items > 1 && p->cap[CAP_C2] <= kColSlotsLds * kPlanThreads ? 1 : kColBlocks;
     const int slices = fast_lds ? row_slices(n) + row_slices(h) : 2;
-    const SparseArgs sparse = {p->statsB[1], p->statsB[0], p->statsB[2], h, p->sparse};
+    const SparseArgs sparse = {p->statsB[1], h, p->sparse.cnt};
     auto lay_out = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(slices + col_blocks, items), dim3(kPlanThreads), dyn_bytes, st, p->rowA, n, p->layA,
                            phys_cap_rows(p->cap[CAP_ROWA]), p->tmpPA, p->rowB, h, p->layB,
@@ -2545,8 +2561,13 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
                            skip, stride, p->chunkB,
                            (int)(dyn_bytes / sizeof(int32_t)), sparse);
     };
-    if (p->sparse.ent) lay_out(layouts_kernel<true>);
-    else lay_out(layouts_kernel<false>);
+    if (p->sparse.ent) {
+        lay_out(layouts_kernel<true>);
+        const ListsArgs f = {p->obcopyB, p->cap[CAP_EDGEB], p->sh, p->rowB, p->c2, p->layB.row_phys, p->cols.col_phys, skip, hdr, p->sparse};
+        hipLaunchKernelGGL(lists_kernel, dim3(grid_for(p->cap[CAP_EDGEB], 256, 256)), dim3(256), 0, st, f);
+    } else {
+        lay_out(layouts_kernel<false>);
+    }
     if (keep)
         hipLaunchKernelGGL(keep_remember_kernel, dim3(grid_for(p->cap[CAP_C1], 256, 16)), dim3(256), 0, st, p->c1,
                            (const PlanHeader *)hdr, p->snapRoot, p->snapExp, p->snapChild, p->d_keep);
@@ -2564,7 +2585,9 @@ static void guess_capacities(Plan *p) {
     p->cap[CAP_C2] = std::max(p->cap[CAP_C2], (int)(2 * d + 512));
     p->cap[CAP_EDGEA] = std::max(p->cap[CAP_EDGEA], (int)std::min<int64_t>(n * d, std::max<int64_t>(n * d / 64, 4096)));
     p->cap[CAP_EDGEB] = std::max(p->cap[CAP_EDGEB], (int)std::min<int64_t>(2 * h * d, std::max<int64_t>(h * d / 64, 4096)));
-    p->cap[CAP_SPARSE] = std::max(p->cap[CAP_SPARSE], (int)std::min<int64_t>(h * d / 64 + h + 8192, 1 << 26));
+    // (a listed column holds a digit in kSparseShare rows at most, so that a list holds d / 12 on average; and Alg. 4 splits the longest row or column
+    // first: behind a column of so few no row has more, h / 12 in all rows of a list)
+    p->cap[CAP_SPARSE] = (int)std::min((h + 11) / 12, (d + 5) / 6) / kSparseRows * kSparseRows + 2 * kSparseRows;
     p->at_rows = std::max(p->at_rows, (int)((n + kTile - 1) / kTile * kTile));
     p->cap[CAP_OB] = std::max(p->cap[CAP_OB], (int)std::min<int64_t>(std::max(n, h) * d, std::max<int64_t>(std::max(n, h) * d / 64, 4096)));
 }
@@ -2673,10 +2696,8 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
             continue;
         }
         if (!overflow && p->hdr.nsparse) {  // columns taken from lists: room for these and for the copy of the A store that they meet
-            const int64_t room = p->hdr.sparse_room;
-            bool again = room > p->sparse.cap;
-            if (again && room < (1 << 26)) p->cap[CAP_SPARSE] = (int)(room + room / 8);
-            else if (again) p->no_sparse = 1;
+            bool again = p->hdr.sparse_room > p->sparse.cap;
+            if (again) p->cap[CAP_SPARSE] = (p->hdr.sparse_room + p->hdr.sparse_room / 8 + kSparseRows) / kSparseRows * kSparseRows;
             if (p->hdr.Mp > p->at_rows) {
                 p->at_rows = p->hdr.Mp;
                 again = true;

@@ -333,8 +333,7 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_batch_kernel(ScatterA
 }
 
 // Places the digits above digit 0 of the listed OB entries of an operand unpacked by UnpackBoth.
-// The remainder floor(|v| / s) of an entry at (R, C) moves to the child of whichever of R and C was
-// split first (Alg. 4 lines 7-9 / 11-14) and leaves its own digit 0 there.
+// (digits_above finds them.)
 //   second == 0 (A): the entry's column chain lives in the column slots of A's unpacking; A_ue then
 //     repeats column r of A_u in every column slot of the second unpacking that descends from r
 //     (Alg. 2 line 6 / Alg. 4 line 13): the digit is stored wherever such a slot reads its column of A
@@ -354,12 +353,10 @@ struct FixupArgs {
     const int32_t *row_phys;
     const int32_t *out_col;     // per column slot of the second unpacking: the stored column that holds it
     const int32_t *col_phys, *col_sexp;  // its column of B_eu, and per such column the exponent of S
-    int W, s, sh;               // bytes from one row of `out` to the next
+    int W, sh;                  // bytes from one row of `out` to the next
     int fp6;                    // `out` holds 6-bit floating-point codes
     int8_t *out;
     unsigned long long *rowsum; // per physical row: what the digits placed here add to the row norm
-    SparseLists sparse;         // second == 1: the digits in stored columns from list_col on go there as well
-    int list_col;
 };
 
 // The whole norm of physical row p as far as it is known: the scatter kernel's parts plus `placed`.
@@ -398,27 +395,6 @@ __device__ __forceinline__ void add_to_row(unsigned long long *rowsum, int p, un
     if (mine) atomicAdd(&rowsum[p], sum);
 }
 
-// A place in the list of `block` for every lane that gets here together: one atomic per list named, all of them in flight together (the
-// entries of a block of rows sit side by side in the OB list; an atomic to each lane: 36 us for 37 000 entries).
-__device__ __forceinline__ int list_place(int32_t *cnt, int block) {
-    const int lane = threadIdx.x & 63;
-    unsigned long long pending = __ballot(1);
-    int lead = lane, before = 0, count = 0;
-    while (pending) {
-        const int first = __builtin_ctzll(pending);
-        const unsigned long long same = __ballot(block == __builtin_amdgcn_readlane(block, first));
-        if ((same >> lane) & 1) {
-            lead = first;
-            before = __popcll(same & ((1ull << lane) - 1ull));
-            count = __popcll(same);
-        }
-        pending &= ~same;
-    }
-    int base = 0;
-    if (lane == lead) base = atomicAdd(&cnt[block], count);
-    return __shfl(base, lead, 64) + before;
-}
-
 // Both operands in one launch: blocks [0, blocks_a) serve fa, the next blocks_b serve fb.  What a digit
 // placed here adds to its row's norm goes to rowsum; bound_kernel, launched behind this one, takes the
 // largest norm (a wait for the sum inside this kernel, to keep the bound current entry by entry, was
@@ -442,38 +418,20 @@ __global__ void fixup_kernel(FixupArgs fa, FixupArgs fb, int blocks_a, int block
         f.W = header_pitch(*f.hdr, f.fp6, f.second);
     }
     const int n = min(f.second ? f.hdr->nobB : f.hdr->nobA, f.ob_cap);
-    const unsigned mask = (unsigned)(f.s - 1);
     for (int t = block * blockDim.x + threadIdx.x; t < n; t += nblocks * blockDim.x) {
         const int i = f.ob[t], k = f.ob[f.ob_cap + t], v = f.ob[2 * (size_t)f.ob_cap + t];
         const unsigned av = v < 0 ? 0u - (unsigned)v : (unsigned)v;
         for (int croot = k, copies = 0; croot >= 0 && copies < 64; croot = f.second ? f.c1_child[croot] : -1, ++copies) {
-            int R = i, C = croot;
-            unsigned rem = av;
-            for (int step = 0; step < 40; ++step) {
-                rem >>= f.sh;
-                if (rem == 0) break;
-                const uint32_t tr = f.rows.time[R], tc = f.cset.time[C];
-                if (tr < tc) R = f.rows.child[R];
-                else if (tc != kNever) C = f.cset.child[C];
-                else break;  // an OB remainder nothing splits: not a complete plan
-                if (R < 0 || C < 0) break;
-                const int m = (int)(rem & mask);
-                if (m == 0) continue;
+            digits_above(f.rows, f.cset, i, croot, av, f.sh, [&](int R, int C, int m) {
                 const int p = f.row_phys[R];
                 const int8_t dg = (int8_t)(v < 0 ? -m : m);
                 for (int c = C, hops = 0; c >= 0 && hops < 4096; c = f.second ? -1 : f.c2_child[c], ++hops) {
                     const int at = f.out_col[c];
-                    if (f.second && at >= f.list_col) {
-                        const int block = p / kSparseRows, from = f.sparse.off[block], to = f.sparse.off[block + 1];
-                        const int pos = from + list_place(f.sparse.cnt, block);
-                        if (pos < to) f.sparse.ent[pos] = (uint32_t)(p % kSparseRows) | (uint32_t)(at - f.list_col) << 7 | (uint32_t)(uint8_t)dg << 24;
-                    }
                     if (f.fp6) {  // the position holds 0 (the scatter wrote it): OR the code in, 6 bits at bit 6 * column
                         const unsigned code = (fp6_codes4((unsigned)(uint8_t)dg) & 0x3fu);
-                        const int col = at;
-                        const unsigned bit = 6u * (unsigned)(col & 31);  // inside the 32-column fragment
-                        unsigned *row = reinterpret_cast<unsigned *>(f.out + fp6_ktile(p, col >> 7, f.W));
-                        const int grp = (col >> 6) & 1, frag = (col >> 5) & 1, i = (int)(bit >> 5);
+                        const unsigned bit = 6u * (unsigned)(at & 31);  // inside the 32-column fragment
+                        unsigned *row = reinterpret_cast<unsigned *>(f.out + fp6_ktile(p, at >> 7, f.W));
+                        const int grp = (at >> 6) & 1, frag = (at >> 5) & 1, i = (int)(bit >> 5);
                         atomicOr(row + fp6_dword(p, grp, frag, i), code << (bit & 31u));
                         if ((bit & 31u) > 26u) atomicOr(row + fp6_dword(p, grp, frag, i + 1), code >> (32u - (bit & 31u)));
                     } else {
@@ -483,7 +441,7 @@ __global__ void fixup_kernel(FixupArgs fa, FixupArgs fb, int blocks_a, int block
                     const unsigned long long term = nsft >= 40u ? (1ull << 44) : ((unsigned long long)m << nsft);
                     add_to_row(f.rowsum, p, term);
                 }
-            }
+            });
         }
     }
 }
@@ -581,12 +539,11 @@ __global__ void bound_kernel(const unsigned long long *rowsum_a, const unsigned 
 
 // A repeated unpack of one plan: clears what the planner left cleared for the first.
 __global__ void reset_bound_kernel(PlanHeader *hdr, unsigned long long *rowsum_a, int rows_a,
-                                   unsigned long long *rowsum_b, int rows_b, int32_t *list_len, int lists) {
+                                   unsigned long long *rowsum_b, int rows_b) {
     const int t0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
     if (t0 == 0) hdr->bound[0] = hdr->bound[1] = 0;
     for (int t = t0; t < rows_a; t += stride) rowsum_a[t] = 0;
     for (int t = t0; t < rows_b; t += stride) rowsum_b[t] = 0;
-    for (int t = t0; t < lists; t += stride) list_len[t] = 0;
 }
 
 // canon[R][c] = phys[row_phys[R]][col_phys[c]]; ld: bytes from one physical row to the next
@@ -670,7 +627,7 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     if (p->unpacked || (h.reusedB && !keepB)) {
         if (batch) return IMUNPACK_EINVAL;
         hipLaunchKernelGGL(reset_bound_kernel, dim3(64), dim3(256), 0, st, p->d_hdr, p->layA.rowsum, h.Mp,
-                           p->layB.rowsum, h.Np, p->sparse.cnt, h.nsparse ? h.Np / kSparseRows : 0);
+                           p->layB.rowsum, h.Np);
     }
     FixupArgs fx[2] = {};
     int fblocks[2] = {0, 0};
@@ -727,10 +684,8 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
             f.row_phys = lay.row_phys;
             f.out_col = op ? p->cols.col_phys : p->cols.acol_phys;
             f.col_phys = p->cols.col_phys; f.col_sexp = p->cols.col_sexp;
-            f.W = a.ld; f.s = p->s; f.sh = p->sh; f.fp6 = p->fp6;
+            f.W = a.ld; f.sh = p->sh; f.fp6 = p->fp6;
             f.out = a.out; f.rowsum = lay.rowsum;
-            f.sparse = p->sparse;
-            f.list_col = h.nsparse ? h.list_kt0 * kKPad : 0x7fffffff;
             fblocks[op] = (nob + 255) / 256;
         }
     }

@@ -1659,3 +1659,103 @@ def test_no_stored_column_has_the_exponent_of_the_lists(imu, n, d, h, deep, part
     imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
     scale = float(np.float32(0.013)) * float(np.float32(0.0021))
     assert torch.equal(C_int.double(), want) and torch.equal(C, (want * scale).float())
+
+
+@pytest.mark.parametrize("n,d,h,deep", [(20, 1100, 4100, True), (2000, 1060, 4100, False)])
+def test_first_unpack_of_a_plan_with_lists_in_a_graph(imu, n, d, h, deep):
+    """The graph holds the unpack that comes first after the plan; its replays, and an unpack outside it, leave the same operands, and
+    the fused GEMM behind each of them gives the same integers."""
+    A, B = _few_digits(np.random.default_rng(n), n, d, h, deep)
+    want = A.double() @ B.double().t()
+    plan = imu.imunpack_plan(A, B, 8, ROW, BOTH)
+    assert imu.imunpack_diag_list_columns(plan) > d // 2
+    ba, bb, _ = plan.unpacked_bytes()
+    A_ue, B_eu = (torch.zeros(x, dtype=torch.int8, device="cuda") for x in (ba, bb))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        imu.imunpack_unpack(plan, A, B, A_ue, B_eu)
+    ws = torch.empty(plan.unpacked_bytes()[2] // 8, dtype=torch.int64, device="cuda")
+    for turn in range(4):
+        A_ue.zero_()
+        if turn < 3:
+            graph.replay()
+        else:
+            imu.imunpack_unpack(plan, A, B, A_ue, B_eu)
+        torch.cuda.synchronize()
+        C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+        imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, ws)
+        assert torch.equal(C_int.double(), want)
+
+
+def test_unpack_beside_a_gemm_of_the_same_plan(imu):
+    """The plan's operands are unpacked into a second pair of buffers on one stream while GEMMs on the first pair run on another: neither
+    the lists nor the transposed copy of A's columns, which the plan holds, change under them."""
+    n, d, h = 2000, 1060, 4100
+    A, B = _few_digits(np.random.default_rng(1), n, d, h, True)
+    want = A.double() @ B.double().t()
+    plan = imu.imunpack_plan(A, B, 8, ROW, BOTH)
+    assert imu.imunpack_diag_list_columns(plan) > d // 2
+    A_ue, B_eu = imu.imunpack_unpack(plan, A, B)
+    A2, B2 = torch.zeros_like(A_ue), torch.zeros_like(B_eu)
+    outs = [torch.full((n, h), -1, dtype=torch.int64, device="cuda") for _ in range(8)]
+    first, second = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for C_int in outs:
+        with torch.cuda.stream(second):
+            imu.imunpack_unpack(plan, A, B, A2, B2)
+        with torch.cuda.stream(first):
+            imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
+    torch.cuda.synchronize()
+    for C_int in outs:
+        assert torch.equal(C_int.double(), want)
+    imu.imunpack_gemm(plan, A2, B2, 1.0, 1.0, outs[0].zero_(), None, None)
+    assert torch.equal(outs[0].double(), want)
+
+
+@pytest.mark.parametrize("n", [16, 1900])
+def test_lists_with_weights_that_stay_resident(imu, n):
+    """Keep-weights mode: the lists belong to the unpacking of B.  Taken over (into the same buffer, into another one), made anew when
+    other columns of A are split, taken over again; the statistics are the caller's."""
+    d, h, b = 1100, 4100, 8
+    A, B = _few_digits(np.random.default_rng(2), n, d, h, True)
+    other = torch.randint(-127, 128, (n, d), device="cuda", dtype=torch.int32)
+    other[:, 3] = 5000
+    st_b = imu.imunpack_scan(B, b, imu.Stats.empty(h, d, B.device, imu.Stats.default_ob_cap(h, d)))
+    plan = imu.imunpack_plan(A, B, b, COL, BOTH, imu.imunpack_scan(A, b), st_b)
+    plan.keep_weights()
+    B_eu = None
+    for X, buffer, reused in ((A, 0, False), (A.flip(0).contiguous(), 0, True), (A, 1, True), (other, 1, False), (other.flip(0).contiguous(), 1, True),
+                              (A, 0, False), (A, 0, True)):
+        imu.imunpack_plan(X, B, b, COL, BOTH, imu.imunpack_scan(X, b), st_b, plan)
+        assert plan.weights_reused() == reused and imu.imunpack_diag_list_columns(plan) > d // 2
+        ba, bb, bw = plan.unpacked_bytes()
+        if B_eu is None or B_eu[0].numel() < bb:
+            B_eu = [torch.zeros(bb + 2 ** 20, dtype=torch.int8, device="cuda") for _ in range(2)]
+        A_ue = torch.zeros(ba, dtype=torch.int8, device="cuda")
+        for _ in range(2):                  # the second unpack of a plan writes B_eu whatever was taken over
+            imu.imunpack_unpack(plan, X, B, A_ue, B_eu[buffer])
+            C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+            imu.imunpack_gemm(plan, A_ue, B_eu[buffer], 1.0, 1.0, C_int, None, None)
+            assert torch.equal(C_int.double(), X.double() @ B.double().t())
+
+
+def test_lists_that_outgrow_their_places(imu):
+    """Thirty heavy hitters in each of 32 rows side by side, forty in every column: the columns are split, and the list of those rows is
+    far longer than the average that the plan makes room for.  It is made again with more."""
+    n, d, h = 40, 1024, 24000
+    rng = np.random.default_rng(3)
+    A, B = (rng.integers(-127, 128, (r, d)).astype(np.int32) for r in (n, h))
+    for k in range(d):
+        B[64 + rng.choice(h - 64, 39, replace=False), k] = rng.integers(128, 128 ** 2, 39)
+    for r in range(32, 64):
+        B[r, rng.choice(d, 30, replace=False)] = -300
+    A, B = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    want = A.double() @ B.double().t()
+    plan = imu.Plan()
+    for _ in range(2):
+        imu.imunpack_plan(A, B, 8, ROW, BOTH, plan=plan)
+        assert imu.imunpack_diag_list_columns(plan) == d
+        A_ue, B_eu = imu.imunpack_unpack(plan, A, B)
+        C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+        imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
+        assert torch.equal(C_int.double(), want)
