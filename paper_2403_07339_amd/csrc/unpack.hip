@@ -623,11 +623,12 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     // what the unpack before wrote for exactly that unpacking (same buffer, same format, row norms in place)
     const bool keepB = p->keep_B && h.reusedB && !p->unpacked && p->kept_Beu == B_eu && p->kept_Beu_fp6 == p->fp6;
     // the planner leaves the bounds and the row norms cleared, but for the norms of an unpacking it took over; a repeated
-    // unpack of the same plan clears them again
-    if (p->unpacked || (h.reusedB && !keepB)) {
+    // unpack of the same plan clears them again, and so does every replay of a graph that holds one
+    const bool graph = a_stride == 0 && capturing(st);
+    if (p->unpacked || (h.reusedB && !keepB) || graph) {
         if (batch) return IMUNPACK_EINVAL;
         hipLaunchKernelGGL(reset_bound_kernel, dim3(64), dim3(256), 0, st, p->d_hdr, p->layA.rowsum, h.Mp,
-                           p->layB.rowsum, h.Np);
+                           p->layB.rowsum, keepB ? 0 : h.Np);
     }
     FixupArgs fx[2] = {};
     int fblocks[2] = {0, 0};
@@ -721,7 +722,7 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
         // a workgroup hands what it found to the host itself, in words of its own: the host needs no stream (the caller may use
         // another for the GEMM, or destroy this one) and no event to learn the bounds, and no workgroup waits for another.  Not
         // from a graph, whose replays nobody waits for.
-        p->bound_words = a_stride || capturing(st) ? 0 : 2 * nscan;
+        p->bound_words = a_stride || graph ? 0 : 2 * nscan;
         p->bound_seq = ++p->seq;
         for (int i = 0; i < p->bound_words; ++i)  // not there yet
             __atomic_store_n(&p->pin_bounds[i], (unsigned long long)(uint16_t)~p->bound_seq << 48, __ATOMIC_RELEASE);

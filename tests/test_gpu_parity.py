@@ -1759,3 +1759,35 @@ def test_lists_that_outgrow_their_places(imu):
         C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
         imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
         assert torch.equal(C_int.double(), want)
+
+
+def test_bounds_of_a_first_unpack_in_a_graph(imu):
+    """Every replay of a graph that holds a plan's first unpack measures the bounds afresh, also where it leaves the second operand's
+    unpacking, which a plan in keep-weights mode took over, as it is."""
+    rng = np.random.default_rng(8)
+    Aq, Bq = (rand_ints(rng, r, 400, 128, 0.003, 2) for r in (130, 200))
+    want = oracle.int_gemm(Aq, Bq)
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    plan = imu.imunpack_plan(Qa, Qb, 8, BOTH, BOTH)
+    plan.keep_weights()
+    imu.imunpack_plan(Qa, Qb, 8, BOTH, BOTH, plan=plan)
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    bounds = plan.bounds()
+    for taken_over in (False, True):
+        plan.keep_weights(taken_over)
+        imu.imunpack_plan(Qa, Qb, 8, BOTH, BOTH, plan=plan)
+        if taken_over:                      # the plan that the next one takes it over from
+            imu.imunpack_unpack(plan, Qa, Qb, A_ue, B_eu)
+            imu.imunpack_plan(Qa, Qb, 8, BOTH, BOTH, plan=plan)
+        assert plan.weights_reused() == taken_over
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            imu.imunpack_unpack(plan, Qa, Qb, A_ue, B_eu)
+        for _ in range(3):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert plan.bounds() == bounds
+        C_int = torch.full(want.shape, -1, dtype=torch.int64, device="cuda")
+        imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
+        assert np.array_equal(C_int.cpu().numpy(), want)
