@@ -346,8 +346,8 @@ struct imunpack_plan {
     imu::ColLayout cols;
     imu::SparseLists sparse;          // ent == nullptr: the fused GEMM multiplies every column of B_eu
     int no_sparse;                    // there is no room for lists
-    int8_t *at;                       // the transposed copy of level 0 of the A store
-    int at_rows;                      // ... physical rows of A that it has room for
+    int8_t *at;                       // the transposed copy of level 0 of the A store, if a plan of this object needed one
+    size_t at_bytes;                  // ... room for it (it only grows)
     int32_t *statsA[4], *statsB[4];   // rowcnt, colcnt, rowmax, colmax actually used
     // greedy scratch
     unsigned long long *edges;        // two lists of edge_cap packed edges each

@@ -2124,7 +2124,6 @@ static size_t carve(Plan *p, char *base, bool own_statsA, bool own_statsB) {
         p->sparse.cnt = cv.take<int32_t>(list_count(p));
         p->sparse.ent = cv.take<uint32_t>((size_t)list_count(p) * p->cap[CAP_SPARSE] + 256);  // (the GEMM asks for 128 at a time, and once more behind a list)
         p->sparse.cap = p->cap[CAP_SPARSE];
-        p->at = cv.take<int8_t>((size_t)p->at_rows * (size_t)d);
     }
     p->snapRoot = cv.take<int32_t>(p->cap[CAP_C1]);
     p->snapExp = cv.take<int32_t>(p->cap[CAP_C1]);
@@ -2391,6 +2390,7 @@ static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const i
 
 static void destroy_handles(Plan *p) {
     if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
+    if (p->at) (void)hipFree(p->at);
     if (p->split_ws) {
         (void)hipFree(p->split_ws);
         (void)hipEventDestroy(p->split_done);
@@ -2588,15 +2588,30 @@ static void guess_capacities(Plan *p) {
     // (a listed column holds a digit in kSparseShare rows at most, so that a list holds d / 12 on average; and Alg. 4 splits the longest row or column
     // first: behind a column of so few no row has more, h / 12 in all rows of a list)
     p->cap[CAP_SPARSE] = (int)std::min((h + 11) / 12, (d + 5) / 6) / kSparseRows * kSparseRows + 2 * kSparseRows;
-    p->at_rows = std::max(p->at_rows, (int)((n + kTile - 1) / kTile * kTile));
     p->cap[CAP_OB] = std::max(p->cap[CAP_OB], (int)std::min<int64_t>(std::max(n, h) * d, std::max<int64_t>(std::max(n, h) * d / 64, 4096)));
+}
+
+// Room for the transposed copy of the A store that the lists meet: made outside the arena once the number of physical rows is known, so
+// that neither a plan without lists holds it nor more rows of A have the plan made again.
+static bool room_for_copy(Plan *p, size_t bytes) {
+    if (bytes <= p->at_bytes) return true;
+    if (p->at) (void)hipFree(p->at);
+    p->at_bytes = 0;
+    const size_t want = bytes + bytes / 4;
+    if (hipMalloc((void **)&p->at, want) != hipSuccess) {
+        (void)hipGetLastError();
+        p->at = nullptr;
+        return false;
+    }
+    p->at_bytes = want;
+    return true;
 }
 
 int64_t plan_item_bytes(int64_t n, int64_t d, int64_t h, int b, int strategy_A, int strategy_B) {
     Plan p;
     memset((void *)&p, 0, sizeof(p));
     p.n = n; p.d = d; p.h = h; p.b = b; p.sA = strategy_A; p.sB = strategy_B;
-    p.nitems = 1;
+    p.nitems = 2;  // of several
     guess_capacities(&p);
     (void)carve(&p, nullptr, false, false);
     return p.item_bytes;
@@ -2671,7 +2686,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         {  // what is kept of the plan before is only good for the same arrays at the same addresses
             unsigned long long sig = (unsigned long long)(uintptr_t)p->arena * 1000003ull + (unsigned long long)(uintptr_t)p->d_keep;
             const long long parts[] = {n, d, h, b, strategy_A, strategy_B, ownA, ownB, (long long)(uintptr_t)B, (long long)ldb,
-                                       p->cap[CAP_SPARSE], p->at_rows, p->no_sparse};
+                                       p->cap[CAP_SPARSE], p->no_sparse};
             for (long long v : parts) sig = sig * 1099511628211ull + (unsigned long long)v;
             for (int c = 0; c <= CAP_OB; ++c) sig = sig * 1099511628211ull + (unsigned long long)p->cap[c];
             if (sig != p->keep_sig) p->keep_valid = 0;
@@ -2698,10 +2713,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         if (!overflow && p->hdr.nsparse) {  // columns taken from lists: room for these and for the copy of the A store that they meet
             bool again = p->hdr.sparse_room > p->sparse.cap;
             if (again) p->cap[CAP_SPARSE] = (p->hdr.sparse_room + p->hdr.sparse_room / 8 + kSparseRows) / kSparseRows * kSparseRows;
-            if (p->hdr.Mp > p->at_rows) {
-                p->at_rows = p->hdr.Mp;
-                again = true;
-            }
+            else again = p->no_sparse = !room_for_copy(p, (size_t)p->hdr.Mp * (size_t)d);
             if (again) {
                 p->keep_valid = 0;
                 continue;

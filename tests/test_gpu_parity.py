@@ -1791,3 +1791,21 @@ def test_bounds_of_a_first_unpack_in_a_graph(imu):
         C_int = torch.full(want.shape, -1, dtype=torch.int64, device="cuda")
         imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
         assert np.array_equal(C_int.cpu().numpy(), want)
+
+
+def test_lists_of_weights_survive_more_rows_of_activations(imu):
+    """The rows of A do not concern B's unpacking: an activation whose rows all split, twice the physical rows of the one before, takes it
+    over, lists and all."""
+    n, d, h, b = 700, 1100, 4100, 8
+    A, B = _few_digits(np.random.default_rng(4), n, d, h, False)
+    split = A.clone()
+    split[:, 11] = 4000
+    plan = imu.imunpack_plan(A, B, b, ROW, BOTH)
+    plan.keep_weights()
+    for X, reused in ((A, False), (split, True), (A, True)):
+        imu.imunpack_plan(X, B, b, ROW, BOTH, plan=plan)
+        assert plan.weights_reused() == reused and imu.imunpack_diag_list_columns(plan) > d // 2
+        A_ue, B_eu = imu.imunpack_unpack(plan, X, B)
+        C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+        imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
+        assert torch.equal(C_int.double(), X.double() @ B.double().t())
