@@ -90,7 +90,7 @@ struct PlanHeader {
     int32_t nobA, nobB;              // OB entries of A / B kept for the scatter (UnpackBoth operands)
     int32_t nsparse;                 // columns that the fused GEMM takes from lists (see SparseLists) ...
     int32_t list_kt0;                // ... instead of the k-tiles of B_eu from this one on, the last run
-    int32_t lists_refused;           // ... which this plan cannot have: it has to be made again without
+    int32_t cols_left;               // the layout that knows lists cannot hold the columns: the general one has yet to place them
     int32_t sparse_room;             // places that the longest list of digits would have needed, if one was too short (else 0)
     int32_t overflow;                // bit set: which capacity was too small
     int32_t need[10];                // size that would have been needed, per capacity
@@ -345,7 +345,7 @@ struct imunpack_plan {
     imu::RowLayout layA, layB;
     imu::ColLayout cols;
     imu::SparseLists sparse;          // ent == nullptr: the fused GEMM multiplies every column of B_eu
-    int no_sparse;                    // there is no room for lists
+    int no_sparse;                    // plans of this shape get no lists: no room for the copy of A, or more columns than their layout holds
     int8_t *at;                       // the transposed copy of level 0 of the A store, if a plan of this object needed one
     size_t at_bytes;                  // ... room for it (it only grows)
     int32_t *statsA[4], *statsB[4];   // rowcnt, colcnt, rowmax, colmax actually used

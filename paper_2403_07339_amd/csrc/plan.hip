@@ -1367,6 +1367,13 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     }
     __syncthreads();
     const int LA = t.la + 1, LB = t.lb + 1, W = (d + 63) / 64;
+    // what the stored columns of both operands cannot exceed, -1 if LDS and the tables may not hold them (see below for what has to)
+    auto most_columns = [&](bool listed) {
+        const int mine = LA * LB + (listed ? 1 : 0), appended = D - d, pads = kKPad * (LA * LB + LA + LB);
+        const int kp = d + appended + appended / 7 + pads + (listed ? d : 0), ka = hdr->d1 + appended + pads;
+        return LA <= kMaxLevelsA && LA + LB - 1 <= kMaxGroups && mine + LA + LB <= kMaxRuns && kp <= 256 * kKPad && appended + pads <= 256 * kKPad &&
+               (long long)mine * W * 3 + kp + ka <= dyn_words ? kp + ka : -1;
+    };
     if (LISTS && LB > 1) {
         const int most = sp.h / kSparseShare;
         int found = 0;
@@ -1379,7 +1386,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
         const unsigned sum = wave_sum_lane63((unsigned)found);
         if (lane == 63) atomicAdd(&t.nsparse, (int)sum);
         __syncthreads();
-        if (t.nsparse < kSparseLeast || t.nsparse * 2 < d) {  // uniform
+        if (t.nsparse < kSparseLeast || t.nsparse * 2 < d || most_columns(true) < 0) {  // uniform
 #pragma unroll
             for (int u = 0; u < kSlots; ++u) lev[u] &= ~kListed;
             __syncthreads();
@@ -1389,10 +1396,9 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     }
     const int lists = LA * LB, pairs = lists + (LISTS && t.nsparse ? 1 : 0);  // the columns taken from lists have a mask of their own
     if (LA > kMaxLevelsA || LA + LB - 1 > kMaxGroups || (long long)pairs * W * 3 > dyn_words) return false;
-    if (part > 0) {  // where it is certain to fit (see below for what has to), parts that will have nothing to write need not find out
-        const int appended = D - d, pads = kKPad * (LA * LB + LA + LB);
-        const int kp = d + appended + appended / 7 + pads + (pairs > lists ? d : 0), ka = hdr->d1 + appended + pads;
-        if (part * kPlanThreads >= kp + ka + kPlanThreads && kp <= 256 * kKPad && appended + pads <= 256 * kKPad && pairs * W * 3 + kp + ka <= dyn_words) return true;
+    if (part > 0) {  // where it is certain to fit, parts that will have nothing to write need not find out
+        const int most = most_columns(pairs > lists);
+        if (most >= 0 && part * kPlanThreads >= most + kPlanThreads) return true;
     }
     unsigned long long *mask = reinterpret_cast<unsigned long long *>(dyn);  // [pairs][W]
     int32_t *pre = dyn + 2 * pairs * W;                                       // [pairs][W] slots of the pair below the word
@@ -1905,9 +1911,8 @@ __global__ __launch_bounds__(256) void publish_kernel(const PlanHeader *hdr, Pla
 
 // One to four workgroups for the rows of A, as many for the rows of B, kColBlocks for the columns (those idle that have nothing to write;
 // one for each item of a batch).
-// LISTS: columns of B may be taken from lists (see SparseArgs); then there is no other layout of the columns than the one in LDS, and the
-// host makes the plan again, without lists, if that is refused.  A variant of its own: 20 -> 36 us for a product without lists in one
-// kernel with them.
+// LISTS: columns of B may be taken from lists (see SparseArgs).  A variant of its own (20 -> 36 us for a product without lists in one kernel with
+// them), without the general layout of the columns, which left it no registers (27 -> 36 us): the host launches the other one if it is needed.
 template <bool LISTS>
 __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     SlotSet rowA, int n, RowLayout layA, int cap_physA, int32_t *tmpPA, SlotSet rowB, int h, RowLayout layB,
@@ -1957,13 +1962,13 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
             for (int x = threadIdx.x; x < cap_physB / kSparseRows; x += kPlanThreads) sparse.cnt[x] = 0;
     } else {
         const int part = bx - slA - slB, parts = (int)gridDim.x - slA - slB;
-        if (LISTS) {
-            if (!cols_layout_lds<kColSlotsLds, true>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part, parts, sparse) && part == 0 &&
-                threadIdx.x == 0)
-                hdr->lists_refused = 1;
-        } else if (!cols_layout_lds<kColSlotsLds, false>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part, parts, sparse)) {
-            __syncthreads();
-            cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, part, parts, tables);
+        if (!cols_layout_lds<kColSlotsLds, LISTS>(c1, c2, cols, d, cap_physC, s, sh, hdr, tables, fast_rows, dyn_words, part, parts, sparse)) {
+            if (LISTS) {
+                if (part == 0 && threadIdx.x == 0) hdr->cols_left = 1;
+            } else {
+                __syncthreads();
+                cols_layout(c1, c2, cols, d, cap_physC, s, sh, tmpE, tmpK, tmpR, tmpOff, hdr, lds, part, parts, tables);
+            }
         }
         if (part == 0 && threadIdx.x == 0) hdr->bound[0] = hdr->bound[1] = 0;
     }
@@ -2037,7 +2042,7 @@ static inline int list_count(const Plan *p) { return phys_cap_rows(p->cap[CAP_RO
 // its own; digits that stay int8 (the six-bit format may be asked for once the plan is made); B large enough
 // for its unpacked columns to be worth more than the lists' share of the planner, and lists that stay within 256 MiB.
 static inline bool sparse_possible(const Plan *p) {
-    return p->d >= kSparseLeast && p->h * p->d >= kSparseEntries && p->sB == IMUNPACK_BOTH && p->nitems == 1 && p->b > 4 && !p->no_sparse && 2 * p->d + 512 <= kColSlotsLds * kPlanThreads &&
+    return p->d >= kSparseLeast && p->h * p->d >= kSparseEntries && p->sB == IMUNPACK_BOTH && p->nitems == 1 && p->b > 4 && 2 * p->d + 512 <= kColSlotsLds * kPlanThreads &&
            (int64_t)list_count(p) * p->cap[CAP_SPARSE] <= kSparsePlaces;
 }
 
@@ -2561,19 +2566,24 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
                            skip, stride, p->chunkB,
                            (int)(dyn_bytes / sizeof(int32_t)), sparse);
     };
-    if (p->sparse.ent) {
+    auto complete = [&]() {
+        if (keep)
+            hipLaunchKernelGGL(keep_remember_kernel, dim3(grid_for(p->cap[CAP_C1], 256, 16)), dim3(256), 0, st, p->c1,
+                               (const PlanHeader *)hdr, p->snapRoot, p->snapExp, p->snapChild, p->d_keep);
+        ++p->seq;
+        hipLaunchKernelGGL(publish_kernel, dim3(1, items), dim3(256), 0, st, (const PlanHeader *)hdr, p->pin_hdr, p->seq);
+        return await_headers(p, st);
+    };
+    if (p->sparse.ent && !p->no_sparse) {
         lay_out(layouts_kernel<true>);
         const ListsArgs f = {p->obcopyB, p->cap[CAP_EDGEB], p->sh, p->rowB, p->c2, p->layB.row_phys, p->cols.col_phys, skip, hdr, p->sparse};
         hipLaunchKernelGGL(lists_kernel, dim3(grid_for(p->cap[CAP_EDGEB], 256, 256)), dim3(256), 0, st, f);
-    } else {
-        lay_out(layouts_kernel<false>);
+        IMU_TRY(complete());
+        if (!p->hdr.cols_left || p->hdr.overflow || p->hdr.err) return IMUNPACK_OK;
+        p->no_sparse = 1;
     }
-    if (keep)
-        hipLaunchKernelGGL(keep_remember_kernel, dim3(grid_for(p->cap[CAP_C1], 256, 16)), dim3(256), 0, st, p->c1,
-                           (const PlanHeader *)hdr, p->snapRoot, p->snapExp, p->snapChild, p->d_keep);
-    ++p->seq;
-    hipLaunchKernelGGL(publish_kernel, dim3(1, items), dim3(256), 0, st, (const PlanHeader *)hdr, p->pin_hdr, p->seq);
-    return await_headers(p, st);
+    lay_out(layouts_kernel<false>);
+    return complete();
 }
 
 // First guesses of the capacities; every one of them is grown after a run that reports it too small.
@@ -2686,7 +2696,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         {  // what is kept of the plan before is only good for the same arrays at the same addresses
             unsigned long long sig = (unsigned long long)(uintptr_t)p->arena * 1000003ull + (unsigned long long)(uintptr_t)p->d_keep;
             const long long parts[] = {n, d, h, b, strategy_A, strategy_B, ownA, ownB, (long long)(uintptr_t)B, (long long)ldb,
-                                       p->cap[CAP_SPARSE], p->no_sparse};
+                                       p->cap[CAP_SPARSE]};
             for (long long v : parts) sig = sig * 1099511628211ull + (unsigned long long)v;
             for (int c = 0; c <= CAP_OB; ++c) sig = sig * 1099511628211ull + (unsigned long long)p->cap[c];
             if (sig != p->keep_sig) p->keep_valid = 0;
@@ -2705,11 +2715,6 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
                 if (hi.overflow & (1 << c)) needed[c] = std::max(needed[c], (int)hi.need[c]);
         }
         if (err) { rc = err; p->keep_valid = 0; break; }
-        if (!overflow && p->hdr.lists_refused) {
-            p->no_sparse = 1;
-            p->keep_valid = 0;
-            continue;
-        }
         if (!overflow && p->hdr.nsparse) {  // columns taken from lists: room for these and for the copy of the A store that they meet
             bool again = p->hdr.sparse_room > p->sparse.cap;
             if (again) p->cap[CAP_SPARSE] = (p->hdr.sparse_room + p->hdr.sparse_room / 8 + kSparseRows) / kSparseRows * kSparseRows;
@@ -2732,6 +2737,7 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
         p->keep_valid = 0;
         if (overflow & (1 << CAP_LISTA)) p->ignore_listA = 1;
         if (overflow & (1 << CAP_LISTB)) p->ignore_listB = 1;
+        if (needed[CAP_C2] > kColSlotsLds * kPlanThreads) p->no_sparse = 1;
         for (int c = 0; c <= CAP_OB; ++c)
             if (overflow & (1 << c)) {
                 int64_t nv = std::max<int64_t>((int64_t)needed[c] + needed[c] / 8 + 256, (int64_t)p->cap[c] * 2);

@@ -1809,3 +1809,26 @@ def test_lists_of_weights_survive_more_rows_of_activations(imu):
         C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
         imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
         assert torch.equal(C_int.double(), X.double() @ B.double().t())
+
+
+@pytest.mark.parametrize("keep", [False, True])
+@pytest.mark.parametrize("roomy", [False, True])
+def test_more_columns_than_the_layout_with_lists_holds(imu, keep, roomy):
+    """Every column of A in three levels: more column slots than the layout in LDS, which alone knows lists, has room for.  On a new plan
+    object, which learns of them by the room it lacks, and on one that has the room."""
+    n, d, h = 33, 4100, 1100
+    A, B = _few_digits(np.random.default_rng(5), n, d, h, False)
+    A[torch.arange(d, device="cuda") % n, torch.arange(d, device="cuda")] = 20000
+    want = A.double() @ B.double().t()
+    plan = imu.Plan()
+    if roomy:
+        imu.imunpack_plan(A, B[:1090], 8, COL, BOTH, plan=plan)
+    imu.imunpack_plan(A, B, 8, COL, BOTH, plan=plan)
+    plan.keep_weights(keep)
+    for turn in range(3):
+        assert imu.imunpack_diag_list_columns(plan) == 0 and plan.dims()[1] > 12288 and plan.weights_reused() == (keep and turn == 2)
+        A_ue, B_eu = imu.imunpack_unpack(plan, A, B)
+        C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+        imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, torch.empty(plan.unpacked_bytes()[2] // 8, dtype=torch.int64, device="cuda"))
+        assert torch.equal(C_int.double(), want)
+        imu.imunpack_plan(A, B, 8, COL, BOTH, plan=plan)
