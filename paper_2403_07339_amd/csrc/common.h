@@ -96,6 +96,7 @@ struct PlanHeader {
     int32_t need[10];                // size that would have been needed, per capacity
     int32_t err;                     // IMUNPACK_ERANGE conditions found on the device
     uint32_t cols_done;              // column-layout workgroups that have finished (the last one orders the units)
+    uint32_t lists_done;             // workgroups that have filled their share of the lists (the last one publishes the header)
     int32_t extras;                  // edges that the repeated columns of B_e add to B's OB entries (UnpackBoth on B)
     int32_t reusedB;                 // the second operand's unpacking was taken over from the plan before (keep-weights mode)
     int32_t chunkB;                  // no source row of B straddles that many physical rows: kTile, or kChunk for small products

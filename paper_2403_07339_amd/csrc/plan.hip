@@ -1190,16 +1190,25 @@ struct ColTables {
     int cbase[kMaxGroups], xbase[kMaxGroups], ccount[kMaxGroups];  // gathered: first column, first extra block, how many
     int kp, ka, ka_levels, bad, la;
     int lb, nsparse, list_col;                             // (of the path in LDS) columns taken from lists, the first of their run
+    int unlisted;                                          // ... that could have been but hold too much
+    unsigned digits;                                       // ... what those listed hold
     unsigned char tile_e[256], extra_e[256];               // group of every k-tile of B_eu / of every extra block of A
 };
 
-// Which appended columns the fused GEMM takes from lists (SparseLists).  A digit costs a wave of the large tiles some 44 cycles (18 700
-// for the 430 digits that 4096 columns of 9 in 11008 rows leave in its 128 rows of B), a stored column 17: the two meet where a
-// column holds one digit in 330 rows, and kSparseShare is a little beyond it.  Fewer than kSparseLeast of them (four k-tiles) are not
-// worth the copy of the A store, nor are those of a small B; and their run in B_eu has a place for every original column, so that
-// they have to be half of these.
-constexpr int kSparseShare = 384, kSparseLeast = 512;
-constexpr int64_t kSparseEntries = 1 << 22;  // of B
+// Which appended columns the fused GEMM takes from lists (SparseLists), from steps with and without them on weights of scattered heavy
+// hitters (columns x rows of B; us without -> with):
+// * All that could be: lists beside a k-tile's worth of columns that hold more and are gathered.  (3030 of 4096 x 11008 listed and 1066
+//   gathered: step of 4096 rows 526 -> 607.)  One column may hold a digit in kSparseMost rows.
+// * A digit in kSparseShare rows on average.  4096 x 11008, 4096 rows of A: one in 500 510 -> 485 (resident weights 365 -> 326), in 400 514 -> 502
+//   (365 -> 335), in 333 520 -> 514 (365 -> 342), in 250 528 -> 537 (370 -> 358); 1024 rows, resident: 145 -> 141, 145 -> 145, 145 -> 146.
+// * At least kSparseLeast of them, and half of the original columns, for each of which their run in B_eu has a place.  Resident, one digit
+//   in 1000 rows, 16 and 4096 rows of A: 1024 x 8192 59 -> 60 and 180 -> 183, 1280 62 -> 63 and 198 -> 197, 1536 66 -> 63 and 215 -> 211, 2048 68 -> 65 and
+//   253 -> 234, 4096 x 11008 81 -> 77 and 401 -> 347.
+// * Where B is unpacked in every step the lists and the copy of A cost the planner and the unpack some 10 us, which the GEMM has to save:
+//   kSparseWork multiplications or more.  2048 x 8192, 1024, 2048 and 4096 rows: 214 -> 218, 255 -> 256, 337 -> 326; 1536 x 12288, 2048 and 4096:
+//   217 -> 223, 348 -> 343; 4096 x 11008, 16, 1024, 4096: 232 -> 239, 304 -> 300, 575 -> 538.
+constexpr int kSparseShare = 384, kSparseMost = 96, kSparseLeast = 1536;
+constexpr int64_t kSparseWork = 1ll << 36;
 constexpr int64_t kSparsePlaces = 1 << 26;   // in all lists
 struct SparseArgs {
     const int32_t *colcnt;  // of B
@@ -1337,7 +1346,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     const int D = hdr->d_u, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (D > kSlots * kPlanThreads) return false;
     for (int x = tid; x < kMaxGroups * kMaxLevelsA; x += kPlanThreads) t.hist2[x] = 0;
-    if (tid == 0) t.la = t.lb = t.bad = t.nsparse = 0;
+    if (tid == 0) t.la = t.lb = t.bad = t.nsparse = t.unlisted = t.digits = 0;
     int key[kSlots], lev[kSlots];  // original column; eA | eB << 16
 #pragma unroll
     for (int u = 0; u < kSlots; ++u) {
@@ -1375,18 +1384,31 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
                (long long)mine * W * 3 + kp + ka <= dyn_words ? kp + ka : -1;
     };
     if (LISTS && LB > 1) {
-        const int most = sp.h / kSparseShare;
-        int found = 0;
+        const int most = sp.h / kSparseMost;
+        unsigned found = 0, rest = 0, digits = 0;
 #pragma unroll
-        for (int u = 0; u < kSlots; ++u)
-            if (key[u] >= 0 && lev[u] == 1 << 16 && sp.colcnt[key[u]] <= most) {
+        for (int u = 0; u < kSlots; ++u) {
+            if (key[u] < 0 || lev[u] != 1 << 16) continue;
+            const int cnt = sp.colcnt[key[u]];
+            if (cnt <= most) {
                 lev[u] |= kListed;
                 ++found;
+                digits += cnt;
+            } else {
+                ++rest;
             }
-        const unsigned sum = wave_sum_lane63((unsigned)found);
-        if (lane == 63) atomicAdd(&t.nsparse, (int)sum);
+        }
+        found = wave_sum_lane63(found);
+        rest = wave_sum_lane63(rest);
+        digits = wave_sum_lane63(digits);
+        if (lane == 63) {
+            atomicAdd(&t.nsparse, (int)found);
+            atomicAdd(&t.unlisted, (int)rest);
+            atomicAdd(&t.digits, digits);
+        }
         __syncthreads();
-        if (t.nsparse < kSparseLeast || t.nsparse * 2 < d || most_columns(true) < 0) {  // uniform
+        if (t.nsparse < kSparseLeast || t.nsparse * 2 < d || t.unlisted > kKPad || (unsigned long long)t.digits * kSparseShare > (unsigned long long)t.nsparse * sp.h ||
+            most_columns(true) < 0) {  // uniform
 #pragma unroll
             for (int u = 0; u < kSlots; ++u) lev[u] &= ~kListed;
             __syncthreads();
@@ -1855,44 +1877,6 @@ __device__ __forceinline__ int list_place(int32_t *cnt, int block) {
     return __shfl(base, lead, 64) + before;
 }
 
-// The digits of the columns that the fused GEMM takes from lists, into the lists: level by level like the fix-up behind the scatter, which
-// writes the same digits to B_eu.  The digits of a list stand in no particular order; one that is too short is reported.  Bound by the
-// latency of an entry's dependent reads: 45 000 entries of 11008 x 4096 weights 7.7 us.  (Places counted row by row ahead of them, in the
-// layouts' launch, and the lists filled by the fix-up: layouts 41 us instead of 27, fix-up 15 instead of 12.)
-struct ListsArgs {
-    const int32_t *ob;       // [3][ob_cap] the OB entries of B, kept by the plan
-    int ob_cap, sh;
-    SlotSet rows, cols;      // of the second unpacking
-    const int32_t *row_phys, *col_phys;
-    const int32_t *skip;     // keep-weights mode: set if they stand as they are
-    PlanHeader *hdr;
-    SparseLists lists;
-};
-__global__ __launch_bounds__(256) void lists_kernel(ListsArgs f) {
-    PlanHeader *hdr = f.hdr;
-    if (hdr->nsparse == 0 || hdr->overflow || hdr->err || (f.skip && *f.skip)) return;
-    const int n = min(hdr->nobB, f.ob_cap), list_col = hdr->list_kt0 * kKPad;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
-        const int v = f.ob[2 * (size_t)f.ob_cap + t];
-        const unsigned av = v < 0 ? 0u - (unsigned)v : (unsigned)v;
-        // (the copies of a column that A's unpacking repeats belong to higher levels along A, which are not listed)
-        digits_above(f.rows, f.cols, f.ob[t], f.ob[f.ob_cap + t], av, f.sh, [&](int R, int C, int m) {
-            const int k = f.col_phys[C] - list_col;
-            if (k < 0) return;
-            const int p = f.row_phys[R], block = p / kSparseRows, pos = list_place(f.lists.cnt, block);
-            if (pos < f.lists.cap)
-                f.lists.ent[(size_t)block * f.lists.cap + pos] = (uint32_t)(p % kSparseRows) | (uint32_t)k << 7 | (uint32_t)(uint8_t)(int8_t)(v < 0 ? -m : m) << 24;
-            else
-                atomicMax(&hdr->sparse_room, pos + 1);
-        });
-    }
-}
-
-__host__ __device__ inline int row_slices(int rows) {
-    const int w = (rows + kRowSlice - 1) / kRowSlice;
-    return w < 1 ? 1 : w > 4 ? 4 : w;
-}
-
 // A completed header to the host: its words, then the sequence number that the host waits for.
 __device__ __forceinline__ void publish_header(const PlanHeader *hdr, PlanHeader *host, int32_t seq) {
     constexpr int kWords = (int)(offsetof(PlanHeader, seq) / sizeof(int32_t));
@@ -1903,6 +1887,59 @@ __device__ __forceinline__ void publish_header(const PlanHeader *hdr, PlanHeader
     stores_done();
     __syncthreads();
     if (threadIdx.x == 0) __hip_atomic_store(&host->seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The digits of the columns that the fused GEMM takes from lists, into the lists: level by level like the fix-up behind the scatter, which
+// writes the same digits to B_eu.  The digits of a list stand in no particular order; one that is too short is reported.  Then the header to
+// the host (a launch of its own: 3 us more, which plans without lists would pay too).  Bound by the latency of an entry's dependent
+// reads: 45 000 entries of 11008 x 4096 weights 9.9 us.  (Places counted row by row ahead of them, in the
+// layouts' launch, and the lists filled by the fix-up: layouts 41 us instead of 27, fix-up 15 instead of 12.)
+struct ListsArgs {
+    const int32_t *ob;       // [3][ob_cap] the OB entries of B, kept by the plan
+    int ob_cap, sh;
+    SlotSet rows, cols;      // of the second unpacking
+    const int32_t *row_phys, *col_phys;
+    const int32_t *skip;     // keep-weights mode: set if they stand as they are
+    PlanHeader *hdr;
+    SparseLists lists;
+    PlanHeader *host;
+    int32_t seq;
+};
+__global__ __launch_bounds__(256) void lists_kernel(ListsArgs f) {
+    PlanHeader *hdr = f.hdr;
+    if (hdr->nsparse == 0 || hdr->overflow || hdr->err || (f.skip && *f.skip)) {
+        if (blockIdx.x == 0) publish_header(hdr, f.host, f.seq);
+        return;
+    }
+    const int n = min(hdr->nobB, f.ob_cap), list_col = hdr->list_kt0 * kKPad;
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+        const int v = f.ob[2 * (size_t)f.ob_cap + t];
+        const unsigned av = v < 0 ? 0u - (unsigned)v : (unsigned)v;
+        // (the copies of a column that A's unpacking repeats belong to higher levels along A, which are not listed)
+        digits_above(f.rows, f.cols, f.ob[t], f.ob[f.ob_cap + t], av, f.sh, [&](int R, int C, int m) {
+            const int k = f.col_phys[C] - list_col;
+            if (k < 0) return;
+            const int p = f.row_phys[R], block = p / kSparseRows, pos = list_place(f.lists.cnt, block);
+            // (through to where every XCD reads it: once the host has the header, a stream that does not wait for this launch may)
+            if (pos < f.lists.cap)
+                __hip_atomic_store(&f.lists.ent[(size_t)block * f.lists.cap + pos],
+                                   (uint32_t)(p % kSparseRows) | (uint32_t)k << 7 | (uint32_t)(uint8_t)(int8_t)(v < 0 ? -m : m) << 24, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            else
+                atomicMax(&hdr->sparse_room, pos + 1);
+        });
+    }
+    __shared__ unsigned s_before;
+    stores_done();
+    __syncthreads();
+    if (threadIdx.x == 0) s_before = atomicAdd(&hdr->lists_done, 1u);
+    __syncthreads();
+    if (s_before == gridDim.x - 1) publish_header(hdr, f.host, f.seq);
+}
+
+__host__ __device__ inline int row_slices(int rows) {
+    const int w = (rows + kRowSlice - 1) / kRowSlice;
+    return w < 1 ? 1 : w > 4 ? 4 : w;
 }
 
 __global__ __launch_bounds__(256) void publish_kernel(const PlanHeader *hdr, PlanHeader *host, int32_t seq) {
@@ -2039,11 +2076,11 @@ static constexpr int kLayoutLdsMax = 140 * 1024;  // dynamic LDS the layouts ker
 
 static inline int list_count(const Plan *p) { return phys_cap_rows(p->cap[CAP_ROWB]) / kSparseRows; }
 // Whether appended columns of B may be taken from lists: those of UnpackBoth, whose heavy hitters the plan holds one by one; a product of
-// its own; digits that stay int8 (the six-bit format may be asked for once the plan is made); B large enough
-// for its unpacked columns to be worth more than the lists' share of the planner, and lists that stay within 256 MiB.
+// its own; digits that stay int8 (the six-bit format may be asked for once the plan is made); a product that is worth the planner's
+// share (see kSparseWork), and lists that stay within 256 MiB.
 static inline bool sparse_possible(const Plan *p) {
-    return p->d >= kSparseLeast && p->h * p->d >= kSparseEntries && p->sB == IMUNPACK_BOTH && p->nitems == 1 && p->b > 4 && 2 * p->d + 512 <= kColSlotsLds * kPlanThreads &&
-           (int64_t)list_count(p) * p->cap[CAP_SPARSE] <= kSparsePlaces;
+    return p->sB == IMUNPACK_BOTH && p->nitems == 1 && p->b > 4 && p->d >= kSparseLeast && 2 * p->d + 512 <= kColSlotsLds * kPlanThreads &&
+           (p->keep_B || (double)p->n * (double)p->d * (double)p->h >= (double)kSparseWork) && (int64_t)list_count(p) * p->cap[CAP_SPARSE] <= kSparsePlaces;
 }
 
 // Lays every device array out in the arena for the current capacities: the headers of all items, then the
@@ -2566,24 +2603,25 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
                            skip, stride, p->chunkB,
                            (int)(dyn_bytes / sizeof(int32_t)), sparse);
     };
-    auto complete = [&]() {
+    auto remember = [&]() {
         if (keep)
             hipLaunchKernelGGL(keep_remember_kernel, dim3(grid_for(p->cap[CAP_C1], 256, 16)), dim3(256), 0, st, p->c1,
                                (const PlanHeader *)hdr, p->snapRoot, p->snapExp, p->snapChild, p->d_keep);
         ++p->seq;
-        hipLaunchKernelGGL(publish_kernel, dim3(1, items), dim3(256), 0, st, (const PlanHeader *)hdr, p->pin_hdr, p->seq);
-        return await_headers(p, st);
     };
     if (p->sparse.ent && !p->no_sparse) {
         lay_out(layouts_kernel<true>);
-        const ListsArgs f = {p->obcopyB, p->cap[CAP_EDGEB], p->sh, p->rowB, p->c2, p->layB.row_phys, p->cols.col_phys, skip, hdr, p->sparse};
+        remember();
+        const ListsArgs f = {p->obcopyB, p->cap[CAP_EDGEB], p->sh, p->rowB, p->c2, p->layB.row_phys, p->cols.col_phys, skip, hdr, p->sparse, p->pin_hdr, p->seq};
         hipLaunchKernelGGL(lists_kernel, dim3(grid_for(p->cap[CAP_EDGEB], 256, 256)), dim3(256), 0, st, f);
-        IMU_TRY(complete());
+        IMU_TRY(await_headers(p, st));
         if (!p->hdr.cols_left || p->hdr.overflow || p->hdr.err) return IMUNPACK_OK;
         p->no_sparse = 1;
     }
     lay_out(layouts_kernel<false>);
-    return complete();
+    remember();
+    hipLaunchKernelGGL(publish_kernel, dim3(1, items), dim3(256), 0, st, (const PlanHeader *)hdr, p->pin_hdr, p->seq);
+    return await_headers(p, st);
 }
 
 // First guesses of the capacities; every one of them is grown after a run that reports it too small.
@@ -2595,9 +2633,9 @@ static void guess_capacities(Plan *p) {
     p->cap[CAP_C2] = std::max(p->cap[CAP_C2], (int)(2 * d + 512));
     p->cap[CAP_EDGEA] = std::max(p->cap[CAP_EDGEA], (int)std::min<int64_t>(n * d, std::max<int64_t>(n * d / 64, 4096)));
     p->cap[CAP_EDGEB] = std::max(p->cap[CAP_EDGEB], (int)std::min<int64_t>(2 * h * d, std::max<int64_t>(h * d / 64, 4096)));
-    // (a listed column holds a digit in kSparseShare rows at most, so that a list holds d / 12 on average; and Alg. 4 splits the longest row or column
-    // first: behind a column of so few no row has more, h / 12 in all rows of a list)
-    p->cap[CAP_SPARSE] = (int)std::min((h + 11) / 12, (d + 5) / 6) / kSparseRows * kSparseRows + 2 * kSparseRows;
+    // (listed columns hold a digit in kSparseShare rows on average, so that a list holds d / 12; and Alg. 4 splits the longest row or column
+    // first: behind a column of h / kSparseMost digits no row has more, h / 3 in all rows of a list)
+    p->cap[CAP_SPARSE] = (int)std::min((h + 2) / 3, (d + 5) / 6) / kSparseRows * kSparseRows + 2 * kSparseRows;
     p->cap[CAP_OB] = std::max(p->cap[CAP_OB], (int)std::min<int64_t>(std::max(n, h) * d, std::max<int64_t>(std::max(n, h) * d / 64, 4096)));
 }
 

@@ -1581,10 +1581,10 @@ def test_bounds_do_not_need_the_stream_of_the_unpack(imu):
 
 
 @pytest.mark.parametrize("n,d,h,sa,longer,parts", [
-    (20, 1100, 4100, ROW, 0.0, 0),         # 64 x 64 tiles, one half of a row block; every column of exponent 1 comes from lists
-    (150, 1070, 4165, COL, 0.00002, 0),    # ... columns of exponents 1 and 2 beside them, entries of three digits
-    (2000, 1060, 4100, ROW, 0.0, 1),       # 256 x 256 tiles
-    (3300, 1100, 4000, COL, 0.00002, 1),
+    (20, 1700, 8200, ROW, 0.0, 0),         # 64 x 64 tiles, one half of a row block; the full columns are stored beside the lists
+    (150, 1670, 8265, COL, 0.00002, 0),    # ... columns of exponents 1 and 2 beside them, entries of three digits
+    (2000, 1660, 8200, ROW, 0.0, 1),       # 256 x 256 tiles
+    (3300, 1700, 8000, COL, 0.00002, 1),
     (400, 5800, 8000, COL, 0.0, 2),        # ... cut along the contraction (2: in two parts or more), the lists in one of them
 ])
 def test_appended_columns_of_few_digits(imu, n, d, h, sa, longer, parts):
@@ -1595,17 +1595,18 @@ def test_appended_columns_of_few_digits(imu, n, d, h, sa, longer, parts):
     B = torch.randint(-127, 128, (h, d), generator=g, device="cuda", dtype=torch.int32)
     A[:, ::97] += 3000
     sign = torch.randint(0, 2, (h, d), generator=g, device="cuda", dtype=torch.int32) * 2 - 1
-    for share, lo, hi in ((4 / h, 128, 128 ** 2), (longer, 128 ** 2, 128 ** 3)):
+    for share, lo, hi in (((4 if d > 5000 else 8) / h, 128, 128 ** 2), (longer, 128 ** 2, 128 ** 3)):
         at = torch.rand((h, d), generator=g, device="cuda") < share
         B = torch.where(at, sign * torch.randint(lo, hi, (h, d), generator=g, device="cuda", dtype=torch.int32), B)
     B[:, 5::211] += 200
     want = A.double() @ B.double().t()      # exact: below 2^53
-    plan = imu.Plan()
-    for rows in (n, max(1, n - 3)):         # the plan object again, its buffers and lists reused
+    plan = imu.imunpack_plan(A, B, 8, sa, BOTH)
+    plan.keep_weights()                     # (products of this size have lists where the weights stay resident)
+    for rows in (n, max(1, n - 3)):         # the plan object again, its buffers reused
         imu.imunpack_plan(A[:rows], B, 8, sa, BOTH, plan=plan)
         assert imu.imunpack_diag_list_columns(plan) > d // 2
         A_ue, B_eu = imu.imunpack_unpack(plan, A[:rows], B)
-        for again in range(2):              # a second unpack of the plan starts the lists afresh
+        for again in range(2):              # a second unpack of the plan leaves the lists as they are
             C = torch.full((rows, h), 3.5, device="cuda")
             C_int = torch.full((rows, h), -1, dtype=torch.int64, device="cuda")
             imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, None, C, None)
@@ -1635,12 +1636,19 @@ def _few_digits(rng, n, d, h, deep, deep_cols=24):
     return torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
 
 
+def _plan_of_resident_weights(imu, A, B, sa):
+    """The first plan in keep-weights mode, where products of any number of rows have lists."""
+    plan = imu.imunpack_plan(A, B, 8, sa, BOTH)
+    plan.keep_weights()
+    return imu.imunpack_plan(A, B, 8, sa, BOTH, plan=plan)
+
+
 @pytest.mark.parametrize("n,d,h,deep,parts", [
-    (20, 1100, 4100, False, 0),    # 64 x 64 tiles: a single exponent group beside the lists
-    (20, 1100, 4100, True, 0),     # ... columns of exponent 2 before them
-    (150, 1070, 4165, True, 0),
-    (2000, 1060, 4100, False, 1),  # 256 x 256 tiles
-    (2000, 1060, 4100, True, 1),
+    (20, 1700, 6400, False, 0),    # 64 x 64 tiles: a single exponent group beside the lists
+    (20, 1700, 6400, True, 0),     # ... columns of exponent 2 before them
+    (150, 1670, 6465, True, 0),
+    (2000, 1660, 6400, False, 1),  # 256 x 256 tiles
+    (2000, 1660, 6400, True, 1),
     (400, 5800, 13000, True, 2),   # ... cut along the contraction (2: in two parts or more)
 ])
 def test_no_stored_column_has_the_exponent_of_the_lists(imu, n, d, h, deep, parts):
@@ -1648,7 +1656,7 @@ def test_no_stored_column_has_the_exponent_of_the_lists(imu, n, d, h, deep, part
     exponents, with the lists in between."""
     A, B = _few_digits(np.random.default_rng(n + d), n, d, h, deep, 200 if parts == 2 else 24)
     want = A.double() @ B.double().t()      # exact: below 2^53
-    plan = imu.imunpack_plan(A, B, 8, ROW, BOTH)
+    plan = _plan_of_resident_weights(imu, A, B, ROW)
     col_exp = plan.export()[5].numpy()
     assert int((col_exp == 1).sum()) == imu.imunpack_diag_list_columns(plan) > d // 2 and (int(col_exp.max()) == 2) == deep
     A_ue, B_eu = imu.imunpack_unpack(plan, A, B)
@@ -1661,13 +1669,13 @@ def test_no_stored_column_has_the_exponent_of_the_lists(imu, n, d, h, deep, part
     assert torch.equal(C_int.double(), want) and torch.equal(C, (want * scale).float())
 
 
-@pytest.mark.parametrize("n,d,h,deep", [(20, 1100, 4100, True), (2000, 1060, 4100, False)])
+@pytest.mark.parametrize("n,d,h,deep", [(20, 1700, 6400, True), (2000, 1660, 6400, False)])
 def test_first_unpack_of_a_plan_with_lists_in_a_graph(imu, n, d, h, deep):
     """The graph holds the unpack that comes first after the plan; its replays, and an unpack outside it, leave the same operands, and
     the fused GEMM behind each of them gives the same integers."""
     A, B = _few_digits(np.random.default_rng(n), n, d, h, deep)
     want = A.double() @ B.double().t()
-    plan = imu.imunpack_plan(A, B, 8, ROW, BOTH)
+    plan = _plan_of_resident_weights(imu, A, B, ROW)
     assert imu.imunpack_diag_list_columns(plan) > d // 2
     ba, bb, _ = plan.unpacked_bytes()
     A_ue, B_eu = (torch.zeros(x, dtype=torch.int8, device="cuda") for x in (ba, bb))
@@ -1690,10 +1698,10 @@ def test_first_unpack_of_a_plan_with_lists_in_a_graph(imu, n, d, h, deep):
 def test_unpack_beside_a_gemm_of_the_same_plan(imu):
     """The plan's operands are unpacked into a second pair of buffers on one stream while GEMMs on the first pair run on another: neither
     the lists nor the transposed copy of A's columns, which the plan holds, change under them."""
-    n, d, h = 2000, 1060, 4100
+    n, d, h = 2000, 1660, 6400
     A, B = _few_digits(np.random.default_rng(1), n, d, h, True)
     want = A.double() @ B.double().t()
-    plan = imu.imunpack_plan(A, B, 8, ROW, BOTH)
+    plan = _plan_of_resident_weights(imu, A, B, ROW)
     assert imu.imunpack_diag_list_columns(plan) > d // 2
     A_ue, B_eu = imu.imunpack_unpack(plan, A, B)
     A2, B2 = torch.zeros_like(A_ue), torch.zeros_like(B_eu)
@@ -1716,7 +1724,7 @@ def test_unpack_beside_a_gemm_of_the_same_plan(imu):
 def test_lists_with_weights_that_stay_resident(imu, n):
     """Keep-weights mode: the lists belong to the unpacking of B.  Taken over (into the same buffer, into another one), made anew when
     other columns of A are split, taken over again; the statistics are the caller's."""
-    d, h, b = 1100, 4100, 8
+    d, h, b = 1700, 6400, 8
     A, B = _few_digits(np.random.default_rng(2), n, d, h, True)
     other = torch.randint(-127, 128, (n, d), device="cuda", dtype=torch.int32)
     other[:, 3] = 5000
@@ -1742,7 +1750,7 @@ def test_lists_with_weights_that_stay_resident(imu, n):
 def test_lists_that_outgrow_their_places(imu):
     """Thirty heavy hitters in each of 32 rows side by side, forty in every column: the columns are split, and the list of those rows is
     far longer than the average that the plan makes room for.  It is made again with more."""
-    n, d, h = 40, 1024, 24000
+    n, d, h = 40, 1600, 24000
     rng = np.random.default_rng(3)
     A, B = (rng.integers(-127, 128, (r, d)).astype(np.int32) for r in (n, h))
     for k in range(d):
@@ -1751,14 +1759,15 @@ def test_lists_that_outgrow_their_places(imu):
         B[r, rng.choice(d, 30, replace=False)] = -300
     A, B = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
     want = A.double() @ B.double().t()
-    plan = imu.Plan()
+    plan = _plan_of_resident_weights(imu, A, B, ROW)
     for _ in range(2):
-        imu.imunpack_plan(A, B, 8, ROW, BOTH, plan=plan)
         assert imu.imunpack_diag_list_columns(plan) == d
         A_ue, B_eu = imu.imunpack_unpack(plan, A, B)
         C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
         imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, None)
         assert torch.equal(C_int.double(), want)
+        imu.imunpack_plan(A, B, 8, ROW, BOTH, plan=plan)
+        assert plan.weights_reused()
 
 
 def test_bounds_of_a_first_unpack_in_a_graph(imu):
@@ -1796,7 +1805,7 @@ def test_bounds_of_a_first_unpack_in_a_graph(imu):
 def test_lists_of_weights_survive_more_rows_of_activations(imu):
     """The rows of A do not concern B's unpacking: an activation whose rows all split, twice the physical rows of the one before, takes it
     over, lists and all."""
-    n, d, h, b = 700, 1100, 4100, 8
+    n, d, h, b = 700, 1700, 6400, 8
     A, B = _few_digits(np.random.default_rng(4), n, d, h, False)
     split = A.clone()
     split[:, 11] = 4000
