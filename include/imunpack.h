@@ -237,8 +237,8 @@ int imunpack_plan_weights_reused(const imunpack_plan_t *plan);
  * group of 64 columns takes 48 bytes: the 32 columns of each half form a 192-bit string (column j at
  * bits 6j .. 6j+5), stored as the first 16 bytes of both strings followed by the last 8 bytes of both
  * (those two in the other order in physical rows whose index has bit 4 set).  Physical rows 2i and 2i + 1 share their bytes: row 2i
- * holds the 96 bytes of both for every even group of 128 columns, row 2i + 1 for every odd one (none behind
- * a last group without a partner).  The request stays with the plan object
+ * holds the 96 bytes of both for every even group of 128 columns, row 2i + 1 for every odd one (zeros behind
+ * a last group without a partner, unless it is the only one).  The request stays with the plan object
  * across re-planning and is in effect whenever the plan's b <= 4 (a plan with b > 4 keeps int8);
  * imunpack_plan_digits returns the format in effect.  Call after imunpack_plan and before
  * imunpack_unpacked_bytes / imunpack_unpack: the format changes the sizes and the row pitches.

@@ -281,7 +281,7 @@ __host__ __device__ __forceinline__ int fp6_dword(int row, int grp, int frag, in
 }
 // Where the 96 bytes of k-tile kt of a row begin.  The caches hand 64 bytes at a time to a CU, so that 96 of a row cost 128; the rows
 // 2i and 2i + 1 therefore share their bytes: row 2i of the store holds the even k-tiles of both, 192 bytes each, row 2i + 1 the odd
-// ones.  A last k-tile without a partner leaves its place in row 2i + 1 to nothing (zeros); a single one is two rows side by side
+// ones.  A last k-tile without a partner leaves 192 zeros in row 2i + 1; a single one is two rows side by side
 // all the same.  12288 stored columns, 16384 rows by 4096: GEMM 451 -> 388 us, the
 // scatter that writes them 67 -> 71.
 __host__ __device__ __forceinline__ int64_t fp6_ktile(int row, int kt, int64_t ld) {

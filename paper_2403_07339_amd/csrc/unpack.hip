@@ -263,8 +263,9 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
                         *reinterpret_cast<v2i_u *>(row + 4 * fp6_dword(p, grp, frag, 4)) = w2;
                     }
                     if ((p & 1) && upos >= 8 && (upos >> 3) % 2 == 0 && (upos >> 3) + 1 == a.W / kKPad) {  // the place of no k-tile
-                        int *none = reinterpret_cast<int *>(a.out + (int64_t)p * a.ld + 12 * upos);
+                        int *none = reinterpret_cast<int *>(a.out + (int64_t)p * a.ld + 12 * upos);  // (of this row and of the one before)
                         none[0] = none[1] = none[2] = 0;
+                        none[24] = none[25] = none[26] = 0;
                     }
                 } else {
                     *reinterpret_cast<int4 *>(a.out + (int64_t)p * a.ld + q0) = o;
