@@ -625,12 +625,13 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
     const bool keepB = p->keep_B && h.reusedB && !p->unpacked && p->kept_Beu == B_eu && p->kept_Beu_fp6 == p->fp6;
     // the planner leaves the bounds and the row norms cleared, but for the norms of an unpacking it took over; a repeated
     // unpack of the same plan clears them again, and so does every replay of a graph that holds one
-    const bool graph = a_stride == 0 && capturing(st);
-    if (p->unpacked || (h.reusedB && !keepB) || graph) {
-        if (batch) return IMUNPACK_EINVAL;
+    auto clear = [&]() {
         hipLaunchKernelGGL(reset_bound_kernel, dim3(64), dim3(256), 0, st, p->d_hdr, p->layA.rowsum, h.Mp,
                            p->layB.rowsum, keepB ? 0 : h.Np);
-    }
+    };
+    const bool again = p->unpacked || (h.reusedB && !keepB);
+    if (again && batch) return IMUNPACK_EINVAL;
+    if (again) clear();
     FixupArgs fx[2] = {};
     int fblocks[2] = {0, 0};
     ScatterArgs sc[2];
@@ -711,6 +712,9 @@ int imu::unpack_impl(imunpack_plan_t *p, const int32_t *A, int64_t lda, const in
         for (int op = 0; op < 2; ++op)
             if (launch[op]) scatter(sc[op], none, sc[op].items, dense[op]);
     }
+    // (asked while the scatter, which does not touch the norms, is under way)
+    const bool graph = a_stride == 0 && capturing(st);
+    if (graph && !again) clear();
     if (most_rows > 0) {
         // after both scatters: the fix-up overwrites zeros they wrote; then the bounds from the row norms
         if (fblocks[0] + fblocks[1] > 0) {
