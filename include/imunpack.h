@@ -257,7 +257,9 @@ int imunpack_plan_digits(const imunpack_plan_t *plan);
  * imunpack_unpacked_bytes gives the buffer sizes and the workspace an un-fused GEMM needs.
  * A, B: the int32 operands the plan was made from.  A_ue, B_eu: device, caller-allocated.
  * imunpack_unpack does not wait for the device: the accumulator bounds that select the GEMM path
- * reach the host later, and imunpack_gemm / imunpack_plan_fusable wait for them. */
+ * reach the host later, and imunpack_gemm / imunpack_plan_fusable wait for them.  A plan may be unpacked
+ * again, into the same or other buffers, also by the replays of a graph and beside an imunpack_gemm on other
+ * buffers: what the plan itself holds for the GEMM is written once or again with the same bytes. */
 int imunpack_unpacked_bytes(const imunpack_plan_t *plan, size_t *bytes_A, size_t *bytes_B,
                             size_t *bytes_workspace);
 /* The shape of the two buffers (host output, six values): physical rows, stored columns and bytes from

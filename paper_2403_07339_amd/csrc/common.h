@@ -170,8 +170,8 @@ struct ColLayout {
 // reads from a transposed copy of level 0 of the A store.  Every product of two digits other than zero is still the low-bit GEMM's.
 // The lists are written once, by the launch that completes the plan (lists_kernel): an unpack, which may come again, from a graph or
 // beside a GEMM on another stream, leaves them alone.
-// 4096 x 4096 by 11008: GEMM 331 -> 257 us and a step 446 -> 388 on resident weights; 754 -> 729 where the weights are unpacked in
-// every step (planner 7 us more, the copy 5); 16 rows against resident weights that no cache holds 115 -> 88.
+// 4096 x 4096 by 11008: GEMM 343 -> 289 us; a step 452 -> 408 on resident weights, 710 -> 683 where the weights are unpacked in
+// every step (planner 6 us more, the copy 5); 16 rows against resident weights that no cache holds 116 -> 84.
 //
 // An entry: physical row inside the kSparseRows | original column << 7 | digit << 24 (in no particular order: the sums are integers).
 // The copy: column k of the store in rows 128 g .. 128 g + 127 is the line of 128 bytes at (g d + k) * 128, row p at its byte

@@ -713,7 +713,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     //     cycles instead of 34 000 (4096 x 8228 by 11013, one run: 344 and 317 us).  With levels there is a half of that or less, and
     //     the non-temporal ones leave the last-level cache to the operands: a step of 12608 x 768 by 3072 226 and 233 us.
     //     The price is code: nine pairs of levels times four blocks of rows, straight down, make this kernel 170 kB (50 with the
-    //     ways through LDS alone) and spill 5 vector registers (31 six-bit, 49 and 35 in parts, 10 and 45 in a batch), all of them
+    //     ways through LDS alone) and spill 5 vector registers (17 six-bit, 49 and 16 in parts, 64 in parts beside lists, 10 and 26 in a batch), all of them
     //     behind the walk along the contraction.
     // (2) Through LDS ([64][256] int32, rows padded to 260) for everything else: int64 results, rows of several kinds in a chunk,
     //     many split columns, results without levels of large products (whole_rows_win).  Global stores are row-contiguous, any

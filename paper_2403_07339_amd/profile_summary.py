@@ -92,7 +92,7 @@ def main():
     total_us = sum(sum(v) for v in trace.values())
     for (name, grid), durs in sorted(trace.items(), key=lambda kv: -sum(kv[1])):
         if not (name.startswith(("gemm", "scatter", "qscan", "fixup", "bound", "greedy", "layouts", "level_major",
-                                 "setup", "ob_copy", "zero_lists", "identity", "recombine", "select", "reset", "publish", "keep"))):
+                                 "setup", "ob_copy", "lists", "zero_lists", "identity", "recombine", "select", "reset", "publish", "keep"))):
             continue
         row = {"kernel": name, "grid_threads": grid, "launches": len(durs), "avg_us": sum(durs) / len(durs),
                "min_us": min(durs), "max_us": max(durs), "share_of_gpu_time": sum(durs) / total_us}

@@ -1841,3 +1841,22 @@ def test_more_columns_than_the_layout_with_lists_holds(imu, keep, roomy):
         imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, torch.empty(plan.unpacked_bytes()[2] // 8, dtype=torch.int64, device="cuda"))
         assert torch.equal(C_int.double(), want)
         imu.imunpack_plan(A, B, 8, COL, BOTH, plan=plan)
+
+
+def test_batch_of_one_with_lists(imu):
+    """A batch of one product, and one large enough for lists on every call, takes the one-product launch with them: the same bits as the
+    calling sequence, and the exact product."""
+    n, d, h = 4100, 2100, 8200
+    g = torch.Generator(device="cuda").manual_seed(3)
+    A, B = torch.randn((n, d), generator=g, device="cuda"), torch.randn((h, d), generator=g, device="cuda") * 0.02
+    A[:, ::300] *= 100.0
+    B[torch.rand((h, d), generator=g, device="cuda") < 0.001] *= 20.0
+    got = imu.imunpack_gemm_batched(A[None], B[None], 95.0, 31.0, 31.0, 8, ROW, BOTH, ctx=imu.BatchContext())[0]
+    steps = [float(imu.imunpack_rtn_step(X, 95.0, 31.0)[0].item()) for X in (A, B)]
+    (Qa, *_), (Qb, *_) = (imu.imunpack_quantize(X, s, 8) for X, s in zip((A, B), steps))
+    plan = imu.imunpack_plan(Qa, Qb, 8, ROW, BOTH)
+    assert imu.imunpack_diag_list_columns(plan) > d // 2
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    C = torch.empty((n, h), device="cuda")
+    imu.imunpack_gemm(plan, A_ue, B_eu, steps[0], steps[1], None, C, None)
+    assert torch.equal(got, C) and torch.equal(C, (Qa.double() @ Qb.double().t() * (steps[0] * steps[1])).float())
