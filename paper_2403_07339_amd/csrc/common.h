@@ -346,9 +346,8 @@ struct imunpack_plan {
     imu::RowLayout layA, layB;
     imu::ColLayout cols;
     imu::SparseLists sparse;          // ent == nullptr: the fused GEMM multiplies every column of B_eu
-    int no_sparse;                    // plans of this shape get no lists: no room for the copy of A, or more columns than their layout holds
-    int8_t *at;                       // the transposed copy of level 0 of the A store, if a plan of this object needed one
-    size_t at_bytes;                  // ... room for it (it only grows)
+    int no_sparse;                    // plans of this shape get no lists: they have more columns than the layout of those holds
+    int8_t *at;                       // the transposed copy of level 0 of the A store (with lists: room for all physical rows there may be)
     int32_t *statsA[4], *statsB[4];   // rowcnt, colcnt, rowmax, colmax actually used
     // greedy scratch
     unsigned long long *edges;        // two lists of edge_cap packed edges each

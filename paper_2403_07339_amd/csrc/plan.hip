@@ -2162,10 +2162,14 @@ static size_t carve(Plan *p, char *base, bool own_statsA, bool own_statsB) {
         p->obcnt = cv.take<int32_t>(1);
     }
     p->sparse = SparseLists{};
+    p->at = nullptr;
     if (sparse_possible(p)) {
         p->sparse.cnt = cv.take<int32_t>(list_count(p));
         p->sparse.ent = cv.take<uint32_t>((size_t)list_count(p) * p->cap[CAP_SPARSE] + 256);  // (the GEMM asks for 128 at a time, and once more behind a list)
         p->sparse.cap = p->cap[CAP_SPARSE];
+        // (as many rows as the layout may have: how many it has is known only once the plan is made.  Allocated then, outside the arena, it
+        // cost a new plan object of 4096 x 4096 by 11008 some 40 us)
+        p->at = cv.take<int8_t>((size_t)phys_cap_rows(p->cap[CAP_ROWA]) * (size_t)d);
     }
     p->snapRoot = cv.take<int32_t>(p->cap[CAP_C1]);
     p->snapExp = cv.take<int32_t>(p->cap[CAP_C1]);
@@ -2432,7 +2436,6 @@ static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const i
 
 static void destroy_handles(Plan *p) {
     if (p->pin_hdr) (void)hipHostFree(p->pin_hdr);
-    if (p->at) (void)hipFree(p->at);
     if (p->split_ws) {
         (void)hipFree(p->split_ws);
         (void)hipEventDestroy(p->split_done);
@@ -2639,22 +2642,6 @@ static void guess_capacities(Plan *p) {
     p->cap[CAP_OB] = std::max(p->cap[CAP_OB], (int)std::min<int64_t>(std::max(n, h) * d, std::max<int64_t>(std::max(n, h) * d / 64, 4096)));
 }
 
-// Room for the transposed copy of the A store that the lists meet: made outside the arena once the number of physical rows is known, so
-// that neither a plan without lists holds it nor more rows of A have the plan made again.
-static bool room_for_copy(Plan *p, size_t bytes) {
-    if (bytes <= p->at_bytes) return true;
-    if (p->at) (void)hipFree(p->at);
-    p->at_bytes = 0;
-    const size_t want = bytes + bytes / 4;
-    if (hipMalloc((void **)&p->at, want) != hipSuccess) {
-        (void)hipGetLastError();
-        p->at = nullptr;
-        return false;
-    }
-    p->at_bytes = want;
-    return true;
-}
-
 int64_t plan_item_bytes(int64_t n, int64_t d, int64_t h, int b, int strategy_A, int strategy_B) {
     Plan p;
     memset((void *)&p, 0, sizeof(p));
@@ -2753,14 +2740,10 @@ int plan_impl(const int32_t *A, int64_t n, int64_t d, int64_t lda, const int32_t
                 if (hi.overflow & (1 << c)) needed[c] = std::max(needed[c], (int)hi.need[c]);
         }
         if (err) { rc = err; p->keep_valid = 0; break; }
-        if (!overflow && p->hdr.nsparse) {  // columns taken from lists: room for these and for the copy of the A store that they meet
-            bool again = p->hdr.sparse_room > p->sparse.cap;
-            if (again) p->cap[CAP_SPARSE] = (p->hdr.sparse_room + p->hdr.sparse_room / 8 + kSparseRows) / kSparseRows * kSparseRows;
-            else again = p->no_sparse = !room_for_copy(p, (size_t)p->hdr.Mp * (size_t)d);
-            if (again) {
-                p->keep_valid = 0;
-                continue;
-            }
+        if (!overflow && p->hdr.nsparse && p->hdr.sparse_room > p->sparse.cap) {  // a list that was too short
+            p->cap[CAP_SPARSE] = (p->hdr.sparse_room + p->hdr.sparse_room / 8 + kSparseRows) / kSparseRows * kSparseRows;
+            p->keep_valid = 0;
+            continue;
         }
         if (!overflow) {
             p->valid = 1;
