@@ -8,10 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libimunpack.so")
-# The order of the code objects sways in which of two states small products run, for a cause not found (a call of 176 x 281 by 88, whose kernels
-# take the same time by themselves in either: 75 us in 12 of 17 processes with this order, 81 to 97 in all of 17 with the planner in the
-# fourth place).
-SOURCES = ["plan.hip", "api.hip", "percentile.hip", "quantize.hip", "unpack.hip", "gemm.hip", "batched.hip"]
+SOURCES = ["api.hip", "percentile.hip", "quantize.hip", "plan.hip", "unpack.hip", "gemm.hip", "batched.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-fast-math",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
