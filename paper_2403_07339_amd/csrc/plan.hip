@@ -1949,7 +1949,7 @@ __global__ __launch_bounds__(256) void publish_kernel(const PlanHeader *hdr, Pla
 // One to four workgroups for the rows of A, as many for the rows of B, kColBlocks for the columns (those idle that have nothing to write;
 // one for each item of a batch).
 // LISTS: columns of B may be taken from lists (see SparseArgs).  A variant of its own (20 -> 36 us for a product without lists in one kernel with
-// them), without the general layout of the columns, which left it no registers (27 -> 36 us): the host launches the other one if it is needed.
+// them), without the general layout of the columns, which left it no registers (plans 7 to 13 us longer): the host launches the other one if it is needed.
 template <bool LISTS>
 __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     SlotSet rowA, int n, RowLayout layA, int cap_physA, int32_t *tmpPA, SlotSet rowB, int h, RowLayout layB,
