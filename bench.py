@@ -50,8 +50,8 @@ def gemm_kernel(imu, plan):
     if not plan.fusable():
         return "gemm_f6_kernel<1>" if fp6 else "gemm_i8_kernel<1>"
     parts = imu.imunpack_diag_gemm_parts(plan)
-    if parts == 1 and imu.imunpack_diag_list_columns(plan):
-        return "gemm_lists_kernel"
+    if imu.imunpack_diag_gemm_halves(plan):
+        return f"gemm_dual_kernel<{str(imu.imunpack_diag_list_columns(plan) > 0).lower()}>"
     if parts == 1:
         return "gemm_f6_kernel<0>" if fp6 else "gemm_i8_kernel<0>"
     return f"gemm_small_kernel<{str(fp6).lower()}, false>" if parts == 0 else \

@@ -250,7 +250,8 @@ int imunpack_plan_digits(const imunpack_plan_t *plan);
 /* ---- (4) digit scatter (Eq. (mod); Alg. 1 l.4-5, Alg. 2 l.4-6, Alg. 4 l.7-8, 11-13) -----------
  * Writes the unpacked operands as int8 in the plan's *physical* layout: rows grouped by source row (all
  * digit levels of a row of A inside one 64-row chunk of a GEMM tile, of a row of B inside one tile),
- * both padded to tile multiples.  B_eu is stored in full, its columns grouped by diagonal entry of S_uu
+ * both padded to tile multiples; physical rows 2i and 2i + 1 share their bytes: row 2i holds the columns 128 k .. 128 k + 63 of both (64
+ * of row 2i, 64 of row 2i + 1, and so on), row 2i + 1 the others.  B_eu is stored in full, its columns grouped by diagonal entry of S_uu
  * in whole k-tiles of 128.  Of A_ue only the columns of A_u are stored, each once ("A store"): where
  * column unpacking of the partner repeats a column (Alg. 2 line 6 / Alg. 4 line 13) the GEMM reads the
  * stored one again, so the copies cost neither memory nor traffic.
@@ -357,9 +358,11 @@ int imunpack_diag_mfma_peak(int workgroups, int iters, int64_t *ops, imunpack_st
 int imunpack_diag_copy(const void *src, void *dst, int64_t bytes, imunpack_stream_t stream);
 
 /* How the plan's last fused imunpack_gemm was launched (tests and benchmark reporting only): 0 = in tiles of
- * 64 x 64 unpacked rows, 1 = of 256 x 256, 2 to 4 = of 256 x 256, those of the last round cut into that many parts
- * along the contraction.  Errors: EINVAL (null plan). */
+ * 64 x 64 unpacked rows, 1 = of 256 x 256 or half tiles, 2 to 4 = of 256 x 256, those of the last round cut into that many parts
+ * along the contraction.  Errors: EINVAL (null plan).
+ * imunpack_diag_gemm_halves: 1 if it was in tiles of 128 x 256, two workgroups to a CU, else 0. */
 int imunpack_diag_gemm_parts(const imunpack_plan_t *plan);
+int imunpack_diag_gemm_halves(const imunpack_plan_t *plan);
 
 /* How many of the d' columns the fused imunpack_gemm of this plan does not multiply as columns (tests and benchmark reporting
  * only): columns that UnpackBoth appended to B for a few heavy hitters each, whose digits it takes one by one

@@ -29,7 +29,7 @@ EXPORTS = [
     "imunpack_plan_fusable", "imunpack_plan_bounds", "imunpack_diag_mfma_peak", "imunpack_diag_clock_probe", "imunpack_diag_copy", "imunpack_price",
     "imunpack_percentile", "imunpack_percentile_static", "imunpack_plan_layout", "imunpack_rtn_step",
     "imunpack_gemm_batched", "imunpack_batch_destroy", "imunpack_quantize_pair", "imunpack_plan_set_digits",
-    "imunpack_plan_digits", "imunpack_plan_keep_weights", "imunpack_plan_weights_reused", "imunpack_diag_gemm_parts", "imunpack_diag_list_columns",
+    "imunpack_plan_digits", "imunpack_plan_keep_weights", "imunpack_plan_weights_reused", "imunpack_diag_gemm_parts", "imunpack_diag_gemm_halves", "imunpack_diag_list_columns",
 ]
 DIGITS_INT8, DIGITS_FP6 = 0, 1
 
@@ -59,6 +59,7 @@ _lib.imunpack_plan_set_digits.argtypes = [_vp, _i32]
 _lib.imunpack_plan_digits.argtypes = [_vp]
 _lib.imunpack_plan_keep_weights.argtypes = [_vp, _i32]
 _lib.imunpack_diag_gemm_parts.argtypes = [_vp]
+_lib.imunpack_diag_gemm_halves.argtypes = [_vp]
 _lib.imunpack_diag_list_columns.argtypes = [_vp]
 _lib.imunpack_plan_weights_reused.argtypes = [_vp]
 _lib.imunpack_unpack.argtypes = [_vp, _vp, _i64, _vp, _i64, _vp, _vp, _vp]
@@ -310,6 +311,11 @@ def imunpack_diag_gemm_parts(plan: Plan) -> int:
     """How the plan's last fused GEMM was launched: 0 in small tiles, 1 in whole large ones, 2 to 4 those of the last
     round cut into that many parts."""
     return int(_lib.imunpack_diag_gemm_parts(plan.handle))
+
+
+def imunpack_diag_gemm_halves(plan: Plan) -> int:
+    """1 if the plan's last fused GEMM ran in tiles of 128 x 256, two workgroups to a CU, else 0."""
+    return int(_lib.imunpack_diag_gemm_halves(plan.handle))
 
 
 def imunpack_diag_list_columns(plan: Plan) -> int:

@@ -34,6 +34,9 @@ constexpr int kGemmThreads = 256;                // 4 waves, 2 x 2, each 128 x 1
 constexpr int kHalfBytes = BM * BK;              // 32 KiB: the A tile or the B tile of one k-tile
 constexpr int kRing = 5;                         // LDS ring of half-stages: A(k) in slot 2k mod 5, B(k) in slot 2k+1 mod 5
 constexpr int kGemmLds = kRing * kHalfBytes;     // all 160 KiB of the CU's LDS
+// Two workgroups to a CU: tiles of 128 x 256, three stages of a piece of 64 columns each, and 2 KiB for every wave beside them.
+constexpr int kDualRows = 128, kDualStages = 3, kDualStage = (kDualRows + BN) * 64, kDualSpare = 2048;
+constexpr int kDualLds = kDualStages * kDualStage + 4 * kDualSpare;  // 80 KiB
 
 struct GemmArgs {
     const int8_t *A, *B;      // the A store [Mp][ldA] and B_eu [Np][ldB] (row pitches in bytes)
@@ -88,16 +91,18 @@ struct GemmArgs {
 // XCD-aware tile order: workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2,
 // so ids that land on one XCD are given one contiguous run of tiles; inside a run the tiles walk
 // bands of 4 tile-rows so that an XCD's resident workgroups share A and B panels.
+template <int kBand = 4, bool DEAL = false>
 __device__ __forceinline__ void place_tile(int logical, int mtiles, int ntiles, int &tm, int &tn);
+template <int kBand = 4, bool DEAL = false>
 __device__ __forceinline__ void tile_of(int wg, int mtiles, int ntiles, int &tm, int &tn) {
     const int total = mtiles * ntiles;
     const int xcd = wg & 7, idx = wg >> 3;
     const int per = total >> 3, rem = total & 7;
     const int logical = xcd * per + min(xcd, rem) + idx;
-    place_tile(logical, mtiles, ntiles, tm, tn);
+    place_tile<kBand, DEAL>(logical, mtiles, ntiles, tm, tn);
 }
+template <int kBand, bool DEAL>
 __device__ __forceinline__ void place_tile(int logical, int mtiles, int ntiles, int &tm, int &tn) {
-    constexpr int kBand = 4;
     const int band_sz = kBand * ntiles;
     const int band = logical / band_sz;
     const int first_m = band * kBand;
@@ -105,6 +110,17 @@ __device__ __forceinline__ void place_tile(int logical, int mtiles, int ntiles, 
     const int in_band = logical - band * band_sz;
     tm = first_m + in_band % rows_in_band;
     tn = in_band / rows_in_band;
+    if constexpr (DEAL) {
+        // XCDs to a band.  They share its columns out one by one, not in stretches: the rows of B that were written last are still in the
+        // last-level cache, the ones before them are not, and the XCDs that had those were a third slower per k-tile (4096 x 4352 by 11013:
+        // kernel 266 -> 245 us in a step).
+        const int m = 8 * kBand / max(mtiles, kBand);
+        if (m > 1) {
+            const int q = ntiles / m, r = ntiles - q * m;  // the first r of them have q + 1 columns
+            const int k = tn < r * (q + 1) ? tn / (q + 1) : r + (q > 0 ? (tn - r * (q + 1)) / q : 0);
+            tn = (tn - k * q - min(k, r)) * m + k;
+        }
+    }
 }
 
 // A launch of whole tiles ends in a round that leaves CUs idle (561 tiles on 256 CUs are 2.2 rounds, paid as 3).  Here the
@@ -178,16 +194,20 @@ __device__ __forceinline__ const int8_t *uniform_ptr(const int8_t *p) {
 // c += a b on accumulation registers, by hand: with the builtin in a second place the compiler moves accumulators between the two
 // register files on the way (253 registers spilled).  The operands may have been written just before (two wait states); what
 // reads c next has to wait for it.
+template <bool VGPR>
 __device__ __forceinline__ void mfma_in_place(const v4i &a, const v4i &b, v16i &c) {
+    if constexpr (VGPR) asm volatile("s_nop 1\n\tv_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+    else
     asm volatile("s_nop 1\n\tv_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
 // 32 S entries of a list of SparseLists as the operands of S matrix instructions, entry 32 s + 16 h + i at byte i of lane half h of
-// instruction s, by way of list_lds(S) bytes of LDS that the wave has to itself: the digits of instruction s in fragment order at byte
-// 1024 s, behind them the entries.  (Digits put together in registers, every lane comparing sixteen rows: 20 000 cycles of the vector
+// instruction s, by way of list_lds(S) bytes of LDS that the wave has to itself: the digits of one instruction after the other in fragment order,
+// behind them the entries.  (Digits put together in registers, every lane comparing sixteen rows: 20 000 cycles of the vector
 // ALU for the four lists of a wave at 4096 columns of 9 digits in 11008 rows, 11 000 so; 8 000 more for what the loads of A's copy,
-// from the last-level cache, leave uncovered.  More of them in flight, beside more registers held, were slower.)
-constexpr int list_lds(int S) { return S * (1024 + 128); }
+// from the last-level cache, leave uncovered.  More of them in flight, beside more registers held, were slower; with
+// two workgroups to a CU two instructions at a time are the most that registers allow: one 20 000, two 15 000 cycles, four spill.)
+constexpr int list_lds(int S) { return 1024 + 128 * S; }
 template <int S>
 struct ListWords {
     unsigned w[(S + 1) / 2];
@@ -195,17 +215,25 @@ struct ListWords {
 #pragma unroll
         for (int j = 0; j < (S + 1) / 2; ++j) w[j] = ent[64 * j + lane];
     }
-    // the first `left` (at least one) are entries
-    __device__ __forceinline__ void stage(int8_t *lds, int left, int lane) const {
-#pragma unroll
-        for (int s = 0; s < S; ++s) *reinterpret_cast<v4i *>(lds + 1024 * s + 16 * lane) = v4i{0, 0, 0, 0};
+    // the first `left` (at least one) are entries; digits[s]: the operand of instruction s, put together in the same place as the ones
+    // before and behind it (a wave's LDS accesses are served in order)
+    __device__ __forceinline__ void stage(int8_t *lds, int left, int lane, v4i (&digits)[S]) const {
         const unsigned none = (unsigned)__builtin_amdgcn_readfirstlane((int)w[0]) & kSparseLine;  // what is not there meets the first one's column
 #pragma unroll
         for (int j = 0; j < (S + 1) / 2; ++j) {
             const int t = 64 * j + lane;
             if (S < 2 && t >= 32) continue;
-            *reinterpret_cast<unsigned *>(lds + 1024 * S + 4 * t) = t < left ? w[j] : none;
-            if (t < left) lds[1024 * (t >> 5) + 16 * ((int)(w[j] & (kSparseRows - 1)) + 2 * (t & 16)) + (t & 15)] = (int8_t)(w[j] >> 24);
+            *reinterpret_cast<unsigned *>(lds + 1024 + 4 * t) = t < left ? w[j] : none;
+        }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const unsigned e = w[s >> 1];
+            const int t = 64 * (s >> 1) + lane;
+            *reinterpret_cast<v4i *>(lds + 16 * lane) = v4i{0, 0, 0, 0};
+            if (lane >> 5 == (s & 1) && t < left) lds[16 * ((int)(e & (kSparseRows - 1)) + 2 * (t & 16)) + (t & 15)] = (int8_t)(e >> 24);
+            asm volatile("" ::: "memory");  // (other lanes' stores: what a lane put there itself is not what it reads)
+            digits[s] = *reinterpret_cast<const v4i *>(lds + 16 * lane);
         }
     }
 };
@@ -246,12 +274,22 @@ __device__ __forceinline__ void list_rows(const unsigned (&x)[16], v4i (&f)[4]) 
 // registers (101 spilled; 348 -> 460 us on a 4096 x 8228 x 11013 unpacked product).
 // LISTS: some columns of B are taken from lists (int8, a product of its own); a variant of its own for the registers' sake too.
 //
+// DUAL: two workgroups to a CU, each with a tile of 128 x 256 (a wave: 128 x 64, whose sums are ordinary vector registers: 128 of 256)
+// and half of the LDS.  A workgroup with a CU to itself leaves the matrix cores idle while its first k-tiles arrive, while it takes
+// columns from lists, shifts its sums and stores its results: 34 k-tiles of 4096 x 4352 by 11013 were 83 000 cycles of a tile's 190 000
+// (lists 26 000, results 41 000, what loads from beyond L2 take longer than the ring covers 25 000).  Here the other workgroup goes on
+// meanwhile; the two drift apart by themselves, since the older one's waves are served first.  Times stand at dual_wins.
+//
 // fp6_piece: rows 96 bytes apart begin at eight multiples of eight of the 64 banks, rows 8 apart at the same one; with pieces
 // moved by one in every second eight rows the sixteen that a 16-byte read serves per cycle have four banks each and, with the
 // swap of fp6_dword, the 32 of an 8-byte read two.  (Rows 112 bytes apart did the same with a seventh load that brought nothing.)
 __device__ __forceinline__ int fp6_piece(int row, int piece) { return piece ^ ((row >> 3) & 1); }
-template <int MODE, bool FP6, bool BATCH = false, bool SPLIT = false, bool LISTS = false>  // SPLIT: parts of tiles (see piece_of); MODE 0: fused epilogue, 1: int64 segment into C_u
+template <int MODE, bool FP6, bool BATCH = false, bool SPLIT = false, bool LISTS = false, bool DUAL = false>  // SPLIT: parts of tiles (see piece_of); MODE 0: fused epilogue, 1: int64 segment into C_u
 __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
+    static_assert(!DUAL || (MODE == 0 && !FP6 && !BATCH && !SPLIT), "variants with two workgroups to a CU");
+    constexpr int BM = DUAL ? kDualRows : imu::BM;
+    constexpr int kChunks = BM / kChunk;           // chunks of A in the tile
+    constexpr int NB = DUAL ? 2 : 4;               // blocks of 32 columns of a wave (and four of 32 rows)
     constexpr int kRowB = FP6 ? 96 : BK;           // bytes of a row of the operand per k-tile
     constexpr int kPitch = kRowB;                  // bytes from row to row in LDS
     constexpr int kHalfBytes = BM * kPitch;        // the A tile or the B tile of one k-tile in LDS
@@ -267,17 +305,22 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         kt0 = 0; kt1 = hdr->Kp / BK;
         nbound = hdr->nruns - 1;
     }
+    // (DUAL: checked behind the first loads, the bounds come from memory.)
+    unsigned long long bound0 = 0, bound1 = 0;
     if (MODE == 0 && (BATCH || g.guard)) {
         const unsigned long long *guard = BATCH ? hdr->bound : g.guard;
-        const unsigned long long b0 = guard[0], b1 = guard[1];
-        const unsigned long long m = b0 < b1 ? b0 : b1;
-        if (!(m < (1ull << 40) && m * (unsigned long long)g.guard_mul < (1ull << (FP6 ? 24 : 31))) || (BATCH && nbound >= 63)) {
-            if (g.refused && blockIdx.x == 0 && tid == 0) g.refused[blockIdx.y] = 1;
-            return;
-        }
+        bound0 = guard[0];
+        bound1 = guard[1];
     }
+    auto inexact = [&]() __attribute__((always_inline)) {
+        const unsigned long long m = bound0 < bound1 ? bound0 : bound1;
+        const bool bad = !(m < (1ull << 40) && m * (unsigned long long)g.guard_mul < (1ull << (FP6 ? 24 : 31))) || (BATCH && nbound >= 63);
+        if (bad && g.refused && blockIdx.x == 0 && tid == 0) g.refused[blockIdx.y] = 1;
+        return bad;
+    };
+    if (!DUAL && MODE == 0 && (BATCH || g.guard) && inexact()) return;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = DUAL ? 0 : wave >> 1, wn = DUAL ? wave : wave & 1;  // of the 128 rows and the 32 NB columns of the wave
     int tm, tn;
     Piece pc;
     const int ktiles = kt1;
@@ -289,7 +332,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         tm = __builtin_amdgcn_readfirstlane(tm);
         tn = __builtin_amdgcn_readfirstlane(tn);
     } else {
-        tile_of(blockIdx.x, mtiles, ntiles, tm, tn);
+        tile_of<DUAL ? 8 : 4, DUAL>(blockIdx.x, DUAL ? mtiles * (imu::BM / BM) : mtiles, ntiles, tm, tn);
     }
     const int m0 = tm * BM, n0 = tn * BN;
     const unsigned lds0 = (unsigned)(size_t)smem;
@@ -310,8 +353,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         } else {
             const int row = 64 * wave + 8 * u + (lane >> 3);
             const int kc = (lane & 7) ^ ((row >> 1) & 7);
-            voffA[u] = (unsigned)row * (unsigned)ldA + (unsigned)(kc * 16);
-            voffB[u] = (unsigned)row * (unsigned)ldB + (unsigned)(kc * 16);
+            voffA[u] = (unsigned)i8_at(row, kc * 16, ldA);
+            voffB[u] = (unsigned)i8_at(row, kc * 16, ldB);
         }
     }
     const int8_t *gA = g.A + (int64_t)m0 * ldA, *gB = g.B + (int64_t)n0 * ldB;
@@ -401,13 +444,57 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         else c = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
     };
 
-    AccT acc[4][4];
+    AccT acc[4][NB];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+    // DUAL: the contraction goes by pieces of 64 columns, three stages of 24 KiB: with k-tiles of 128 not even two would fit.  A k-tile is two pieces of 64 columns, a stage of LDS holds one: 128 rows of A, 256 of B, 64 bytes each, the four 16-byte
+    // chunks of a row swizzled with bits 2 and 3 of the row.  Wave w fills rows [32 w, 32 w + 32) of A and [64 w, 64 w + 64) of B, 16
+    // rows (1 KiB, eight whole lines) per load.
+    unsigned voffP[6] = {};
+    const int8_t *pgA = nullptr, *pgB = nullptr;
+    if constexpr (DUAL) {
+#pragma unroll
+        for (int u = 0; u < 6; ++u) {
+            const int row = (u < 2 ? 32 * wave + 16 * u : 64 * wave + 16 * (u - 2)) + (lane >> 2);
+            voffP[u] = (unsigned)i8_at(row, ((lane & 3) ^ ((row >> 2) & 3)) * 16, u < 2 ? ldA : ldB);
+        }
+    }
+    // piece kp of the contraction (asked for in ascending order) into stage `stage`
+    auto piece_setup = [&](int kp, int stage) {
+        const int kpc = min(kp, 2 * kt1 - 1), ktc = kpc >> 1;
+        la_seg += ktc >= la_end ? 1 : 0;
+        la_end = __builtin_amdgcn_readlane(v_end, la_seg);
+        la_delta = __builtin_amdgcn_readlane(v_delta, la_seg);
+        pgA = uniform_ptr(gA + (int64_t)(ktc + la_delta) * BK + (kpc & 1) * ldA);
+        pgB = uniform_ptr(gB + (int64_t)ktc * BK + (kpc & 1) * ldB);
+        dl = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)(stage * kDualStage) + (unsigned)(wave * 2048));
+    };
+    auto dma_piece = [&](int u) {
+        dma16(u < 2 ? dl + u * 1024 : dl + (unsigned)(kDualRows * 64 - 2048 * wave + 4096 * wave) + (u - 2) * 1024, voffP[u], u < 2 ? pgA : pgB);
+    };
+    // fragment q of a k-step: a0 b0 b1 a1 a2 a3
+    auto piece_frag = [&](const int8_t *st, int ks, int buf, int q) {
+        constexpr int isA[6] = {1, 0, 0, 1, 1, 1};
+        constexpr int idx[6] = {0, 0, 1, 1, 2, 3};
+        const int row = idx[q] * 32 + lrow + (isA[q] ? 0 : wn * 64);
+        const int8_t *src = st + (isA[q] ? 0 : kDualRows * 64) + row * 64 + (((2 * ks + lhalf) ^ ((lrow >> 2) & 3)) << 4);
+        if constexpr (DUAL) (isA[q] ? fa[buf][idx[q]] : fb[buf][idx[q]]) = *reinterpret_cast<const v4i *>(src);
+    };
+    // eight matrix instructions on the fragments in buffer `cur`, the next k-step's fragments and (if any) six loads on the way
+    auto piece_step = [&](int cur, const int8_t *next, int next_ks, bool load) {
+        if constexpr (DUAL)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (q < 6) piece_frag(next, next_ks, cur ^ 1, q);
+                mma(fa[cur][q >> 1], fb[cur][q & 1], acc[q >> 1][q & 1]);
+                if (load && q < 6) dma_piece(q);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
     // MFMA order: 2 x 2 sub-blocks, so that the fragments of the next k-step can trickle in
     constexpr int mi[16] = {0, 0, 1, 1, 0, 0, 1, 1, 2, 2, 3, 3, 2, 2, 3, 3};
     constexpr int mj[16] = {0, 1, 0, 1, 2, 3, 2, 3, 0, 1, 0, 1, 2, 3, 2, 3};
@@ -416,6 +503,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     // the next k-step into the other buffer and with `ndma` direct-to-LDS loads (starting at block
     // `dma0`) of the half-stage set up last.
     auto step = [&](int cur, const int8_t *sta, const int8_t *stb, int next_ks, bool isA, int dma0, int ndma) {
+        if constexpr (!DUAL)
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             load_frag(sta, stb, next_ks, cur ^ 1, q);
@@ -434,28 +522,37 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     }
     // ---- prologue: k-tile kt0 landed, k-tile kt0+1 in flight, first fragments loaded
     int sa = 0;  // ring slot of A(kt); B(kt) is sa+1, A(kt+1) sa+2, B(kt+1) sa+3, A(kt+2) sa+4, B(kt+2) sa
-    half_setup(true, kt0, 0);
+    if constexpr (DUAL) {
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) dma_one(true, u);
-    half_setup(false, kt0, 1);
+        for (int p = 0; p < kDualStages; ++p) {
+            piece_setup(2 * kt0 + p, p);
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) dma_one(false, u);
-    half_setup(true, kt0 + 1, 2);
+            for (int u = 0; u < 6; ++u) dma_piece(u);
+        }
+    } else {
+        half_setup(true, kt0, 0);
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) dma_one(true, u);
-    half_setup(false, kt0 + 1, 3);
+        for (int u = 0; u < kLoads; ++u) dma_one(true, u);
+        half_setup(false, kt0, 1);
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) dma_one(false, u);
+        for (int u = 0; u < kLoads; ++u) dma_one(false, u);
+        half_setup(true, kt0 + 1, 2);
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) dma_one(true, u);
+        half_setup(false, kt0 + 1, 3);
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) dma_one(false, u);
+    }
     // What the epilogue needs to know of the tile, a word per lane (it is read once the sums stand; by then it has long
     // arrived): 0 .. 4 first source row of each chunk, 8 .. 11 their levels, 16 / 17 first source column of the tile and of
     // the next, 18 / 19 whether no row / no column is split, 20 / 21 the steps.
     int tile_meta = 0;
     if constexpr (MODE == 0) {
-        const int per = kTile / kChunk;
+        constexpr int per = kChunks;
         const int32_t *from = lane < 8    ? g.layA.chunk_src0 + tm * per + min(lane, per)
                               : lane < 16 ? g.layA.chunk_lev + tm * per + min(lane - 8, per - 1)
                               : lane < 18 ? g.layB.tile_src0 + tn + (lane - 16)
-                              : lane < 19 ? g.layA.tile_flat + tm
+                              : lane < 19 ? g.layA.tile_flat + tm * per / (kTile / kChunk)
                                           : g.layB.tile_flat + tn;
         if constexpr (BATCH) from = item_at(from, blockIdx.y * g.plan_stride);
         if (g.scale_a_dev && lane >= 20) {
@@ -468,14 +565,24 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         asm volatile("" : "+s"(i));
         return __builtin_amdgcn_readlane(tile_meta, i);
     };
-    if (MODE == 0 && FP6) asm volatile("s_waitcnt vmcnt(13)" ::: "memory");
+    if (DUAL && inexact()) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may land in LDS behind the workgroup's end
+        return;
+    }
+    if (DUAL) asm volatile("s_waitcnt vmcnt(13)" ::: "memory");
+    else if (MODE == 0 && FP6) asm volatile("s_waitcnt vmcnt(13)" ::: "memory");
     else if (MODE == 0) asm volatile("s_waitcnt vmcnt(17)" ::: "memory");
     else if (FP6) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    if constexpr (DUAL) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) load_frag(smem, smem + kHalfBytes, 0, 0, q);
+        for (int q = 0; q < 6; ++q) piece_frag(smem, 0, 0, q);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) load_frag(smem, smem + kHalfBytes, 0, 0, q);
+    }
 
     // ---- main loop, one 128-byte k-tile (4 k-steps, 64 MFMAs) and one barrier per iteration.
     // Steps 1-3 stream A(kt+2) into the spare slot.  After step 3 every fragment of k-tile kt has been
@@ -487,44 +594,47 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     // The columns that are taken from lists: the wave's four blocks of 32 physical rows of B in turn, 128 entries at a time, through what
     // the wave itself will fill of the slot of the ring that is free now (the waves are at different places here).
     auto lists = [&]() __attribute__((always_inline)) {
-        const int8_t *at = uniform_ptr(g.at + (int64_t)(tm * 2 + wm) * g.at_cols * 128);
+        const int8_t *at = uniform_ptr(g.at + (int64_t)(tm * (BM / 128) + wm) * g.at_cols * 128);
         const unsigned row_off = (unsigned)lrow * 4u;
-        const int block0 = (n0 + wn * 128) / kSparseRows;
-        int8_t *lds = smem + ring(sa, 4) * kHalfBytes + wave * kWaveBytes;
-        static_assert(list_lds(4) <= kWaveBytes, "LDS of the lists");
-        const int lens = min(g.sparse.cnt[block0 + min(lane, 3)], g.sparse.cap);  // lane 0 .. 3: how long the lists of the wave's blocks are
+        const int block0 = (n0 + wn * 32 * NB) / kSparseRows;
+        constexpr int S = DUAL ? 2 : 4;  // matrix instructions at a time
+        int8_t *lds = DUAL ? smem + kDualStages * kDualStage + wave * kDualSpare : smem + ring(sa, 4) * kHalfBytes + wave * kWaveBytes;
+        static_assert(list_lds(S) <= kWaveBytes && list_lds(S) <= kDualSpare, "LDS of the lists");
+        const int lens = min(g.sparse.cnt[block0 + min(lane, NB - 1)], g.sparse.cap);  // lane 0 .. 3: how long the lists of the wave's blocks are
         int list = block0 * g.sparse.cap;  // (no more than kSparsePlaces)
-        ListWords<4> words;  // the next 128 entries, or the first of the list behind
+        ListWords<S> words;  // the next 32 S entries, or the first of the list behind
         words.load(g.sparse.ent + list, lane);
         auto block = [&](auto cb_c) __attribute__((always_inline)) {
             constexpr int CB = decltype(cb_c)::value;
             const int len = __builtin_amdgcn_readlane(lens, CB);
             const int next = list + g.sparse.cap;
             if (len <= 0) words.load(g.sparse.ent + next, lane);  // (there are none of this list)
-            for (int t = 0; t < len; t += 128) {
-                words.stage(lds, len - t, lane);
-                unsigned x[4][16];
+            for (int t = 0; t < len; t += 32 * S) {
+                v4i digits[S];
+                words.stage(lds, len - t, lane, digits);
+                unsigned x[S][16];
 #pragma unroll
-                for (int s = 0; s < 4; ++s) list_columns(x[s], lds + 4096, s, lhalf, at, row_off);
-                words.load(g.sparse.ent + (t + 128 < len ? list + t + 128 : next), lane);
+                for (int s = 0; s < S; ++s) list_columns(x[s], lds + 1024, s, lhalf, at, row_off);
+                words.load(g.sparse.ent + (t + 32 * S < len ? list + t + 32 * S : next), lane);
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
+                for (int s = 0; s < S; ++s) {
                     if (t + 32 * s >= len) break;  // uniform
-                    const v4i fd = *reinterpret_cast<const v4i *>(lds + 1024 * s + 16 * lane);
                     v4i fr[4];
                     list_rows(x[s], fr);
 #pragma unroll
                     for (int rb = 0; rb < 4; ++rb)
-                        if constexpr (LISTS) mfma_in_place(fr[rb], fd, acc[rb][CB]);
+                        if constexpr (LISTS) mfma_in_place<DUAL>(fr[rb], digits[s], acc[rb][CB]);
                 }
             }
             list = next;
         };
         block(std::integral_constant<int, 0>{});
         block(std::integral_constant<int, 1>{});
-        block(std::integral_constant<int, 2>{});
-        block(std::integral_constant<int, 3>{});
-        asm volatile("s_nop 15");  // (the matrix instructions behind do not know of these)
+        if constexpr (!DUAL) {
+            block(std::integral_constant<int, 2>{});
+            block(std::integral_constant<int, 3>{});
+        }
+        asm volatile("s_nop 15\n\ts_nop 3");  // (the matrix instructions behind do not know of these)
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read: it may be filled
     };
     // Horner step
@@ -533,7 +643,14 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         // one of those registers shifts every accumulator, whichever block sits where.  Written
         // out by hand: left to the compiler, this step spills three blocks to scratch memory.
         int t0, t1, t2, t3;
-        if constexpr (FP6) {  // binary32 accumulators: times 2^shift, exact
+        if constexpr (DUAL) {  // the accumulators are ordinary registers
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] = (int)((unsigned)acc[i][j][r] << shv);
+        } else if constexpr (FP6) {  // binary32 accumulators: times 2^shift, exact
             asm volatile(
                 "s_nop 15\n\ts_nop 7\n\t"
                 ".irp n," IMU_ACC_QUADS "\n\t"
@@ -552,9 +669,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                 ".endr\n\t"
                 "s_nop 7"
                 : [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), "+a"(acc[0][0]), "+a"(acc[0][1]),
-                  "+a"(acc[0][2]), "+a"(acc[0][3]), "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]),
-                  "+a"(acc[1][3]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
-                  "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
+                  "+a"(acc[0][NB - 2]), "+a"(acc[0][NB - 1]), "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][NB - 2]),
+                  "+a"(acc[1][NB - 1]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][NB - 2]), "+a"(acc[2][NB - 1]),
+                  "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][NB - 2]), "+a"(acc[3][NB - 1])
                 : [sh] "s"(shv));
         } else
         asm volatile(
@@ -575,9 +692,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             ".endr\n\t"
             "s_nop 7"
             : [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), "+a"(acc[0][0]), "+a"(acc[0][1]),
-              "+a"(acc[0][2]), "+a"(acc[0][3]), "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]),
-              "+a"(acc[1][3]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
-              "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
+              "+a"(acc[0][NB - 2]), "+a"(acc[0][NB - 1]), "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][NB - 2]),
+              "+a"(acc[1][NB - 1]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][NB - 2]), "+a"(acc[2][NB - 1]),
+              "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][NB - 2]), "+a"(acc[3][NB - 1])
             : [sh] "s"(shv));
     };
     for (; seg <= nbound && (!SPLIT || kt < kt1); ++seg) {
@@ -591,6 +708,23 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             }
         int kend = BATCH ? __builtin_amdgcn_readlane(v_end, seg) : seg < nbound ? g.bound_kt[seg] + 1 : kt1;
         if constexpr (SPLIT) kend = min(kend, kt1);
+        if constexpr (DUAL)
+            for (; kt < kend; ++kt)
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    const int8_t *st = smem + sa * kDualStage;
+                    piece_step(0, st, 1, false);
+                    // the piece has been read, and this wave's parts of the next one have landed (all but the 6 newest loads): past the
+                    // barrier that holds for all waves
+                    asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    piece_setup(2 * kt + half + kDualStages, sa);
+                    sa = sa + 1 == kDualStages ? 0 : sa + 1;
+                    __builtin_amdgcn_sched_barrier(0);
+                    piece_step(1, smem + sa * kDualStage, 0, true);
+                }
+        else
         for (; kt < kend; ++kt) {
             const int8_t *stA = smem + sa * kHalfBytes, *stB = smem + ring(sa, 1) * kHalfBytes;
             const int8_t *stA1 = smem + ring(sa, 2) * kHalfBytes, *stB1 = smem + ring(sa, 3) * kHalfBytes;
@@ -667,7 +801,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         }
     }
 
-    if (MODE == 1) {
+    if constexpr (MODE == 1) {
         // un-fused: the int32 partial product of this exponent group goes, shifted, into the int64
         // unpacked product C_u (physical coordinates, padded to tiles: no bounds to check)
         constexpr int FLD1 = 260;
@@ -733,14 +867,15 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     const bool flatA = meta(18) != 0, flatB = meta(19) != 0;
     const int stepB = evenB ? kEvenStep : 1;  // from level to level of a source column
     constexpr int FLD = 260;
-    int32_t *foldbuf = reinterpret_cast<int32_t *>(smem);  // two regions of [64][FLD]
+    constexpr int kRegions = DUAL ? 1 : 2;
+    int32_t *foldbuf = reinterpret_cast<int32_t *>(smem);  // kRegions of [64][FLD]
     // behind the staging buffer: per source row of the tile its first physical row (relative to the
     // tile) | levels << 16; the same per source column; the first source row of each chunk
-    int32_t *rowmeta = foldbuf + 2 * kChunk * FLD, *colmeta = rowmeta + kTile, *chunk0 = colmeta + kTile;
+    int32_t *rowmeta = foldbuf + kRegions * kChunk * FLD, *colmeta = rowmeta + kTile, *chunk0 = colmeta + kTile;
     // ... and the sums of split columns, a strip of the tile's physical rows for each
     constexpr int kStrips = 20, kStripPitch = BM + 4;
     int32_t *strips = chunk0 + 8;
-    static_assert(((2 * kChunk * FLD + 2 * kTile + 8) + kStrips * kStripPitch) * sizeof(int32_t) <= kGemmLds, "LDS of the epilogue");
+    static_assert((kRegions * kChunk * FLD + 2 * kTile + 8 + kStrips * kStripPitch) * sizeof(int32_t) <= (DUAL ? kDualLds : kGemmLds), "LDS of the epilogue");
     // scale * 2^final_shift is exact: one multiplication in binary64, one rounding to fp32
     const double scale2 = (g.scale_a_dev ? (double)__int_as_float(meta(20)) * (double)__int_as_float(meta(21)) : g.scale) *
                           (double)(1ull << final_shift);
@@ -764,58 +899,72 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         }
     };
     int nsplit = 0;
-    unsigned col_off[4] = {kOutside, kOutside, kOutside, kOutside};            // where the lane's four columns go in a row of C
-    int col_strip[4] = {-1, -1, -1, -1};
+    unsigned col_off[NB];  // where the lane's columns go in a row of C
+    int col_strip[NB];
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+        col_off[t] = kOutside;
+        col_strip[t] = -1;
+    }
     {
         if (fits && evenB) {  // the first level of each of the lane's columns
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int col = evenB == 2 ? wn * 64 + (t >> 1) * 32 + lrow : wn * 32 + lrow;
+            for (int t = 0; t < NB; ++t) {
+                const int col = evenB == 2 ? wn * (16 * NB) + (t >> 1) * 32 + lrow : wn * (8 * NB) + lrow;
                 if (col < nsrcB) col_off[t] = 4u * (unsigned)col;
             }
         } else if (fits && !flatB) {
-            int own[4];
+            int own[NB];
             unsigned long long split_cols[4], heads[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) own[t] = layB.prow[n0 + wn * 128 + 32 * t + lrow];
+            for (int t = 0; t < NB; ++t) own[t] = layB.prow[n0 + wn * (32 * NB) + 32 * t + lrow];
             find_split(split_cols, heads);
             nsplit = __popcll(split_cols[0]) + __popcll(split_cols[1]) + __popcll(split_cols[2]) + __popcll(split_cols[3]);
-            // the wave's column 32 t + lrow is bit (32 t + lrow) & 63 of word 2 wn + t / 2
-            const unsigned long long lower = wn ? split_cols[2] : split_cols[0], upper = wn ? split_cols[3] : split_cols[1];
-            const int before = wn ? __popcll(split_cols[0]) + __popcll(split_cols[1]) : 0;
+            // the wave's column 32 t + lrow is bit (32 t + lrow) & 63 of word wn NB / 2 + t / 2
+            unsigned long long mine[NB / 2];
+            int before = 0;
+            if constexpr (DUAL) {
+                mine[0] = wn < 2 ? (wn ? split_cols[1] : split_cols[0]) : wn == 2 ? split_cols[2] : split_cols[3];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const unsigned long long m = t >> 1 ? upper : lower;
+                for (int t = 0; t < 3; ++t) before += t < wn ? __popcll(split_cols[t]) : 0;
+            } else {
+                mine[0] = wn ? split_cols[2] : split_cols[0];
+                mine[NB / 2 - 1] = wn ? split_cols[3] : split_cols[1];
+                before = wn ? __popcll(split_cols[0]) + __popcll(split_cols[1]) : 0;
+            }
+#pragma unroll
+            for (int t = 0; t < NB; ++t) {
+                const unsigned long long m = mine[t >> 1];
                 const int bit = (t & 1) * 32 + lrow;
-                if ((m >> bit) & 1) col_strip[t] = before + (t >> 1 ? __popcll(lower) : 0) + __popcll(m & ((1ull << bit) - 1ull));
+                if ((m >> bit) & 1) col_strip[t] = before + (t >> 1 ? __popcll(mine[0]) : 0) + __popcll(m & ((1ull << bit) - 1ull));
                 else if (own[t] >= 0) col_off[t] = 4u * (unsigned)((own[t] & ((1 << kProwLevel) - 1)) - jsrc0);
             }
         } else if (fits) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int col = wn * 128 + 32 * t + lrow;
+            for (int t = 0; t < NB; ++t) {
+                const int col = wn * (32 * NB) + 32 * t + lrow;
                 if (col < nsrcB) col_off[t] = 4u * (unsigned)col;
             }
         }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < kChunks; ++c) {
             const bool rows = meta(c + 1) > meta(c);  // (a chunk of nothing but padding stores nothing, and no resource is made for it)
             const int lev = fits && rows ? meta(8 + c) : 0;
             // (with nothing to fold, one by one only where the stores may stay in the caches)
             const bool plain = lev == 1 && !evenB;
-            const bool ok = (plain ? !g.whole_rows || nsplit > 0 : fold_f64 && (lev == 1 || lev == 2 || lev == 4)) && nsplit <= kStrips;
+            const bool ok = (plain ? !g.whole_rows || nsplit > 0 : fold_f64 && (lev == 1 || lev == 2 || lev == 4) && evenB <= NB) && nsplit <= kStrips;
             direct |= (!rows || ok) << c;
             filled |= rows << c;
         }
     }
-    const bool any_direct = (direct & filled) != 0, any_lds = direct != 15;
+    const bool any_direct = (direct & filled) != 0, any_lds = direct != (1 << kChunks) - 1;
     if (any_lds) {
-        const int isrc0 = meta(0), nsrcA = meta(4) - isrc0;
+        const int isrc0 = meta(0), nsrcA = meta(kChunks) - isrc0;
         if (!flatA && tid < nsrcA)
             rowmeta[tid] = (layA.src_pstart[isrc0 + tid] - m0) | (layA.src_nlev[isrc0 + tid] << 16);
         if (!flatB && tid < nsrcB)
             colmeta[tid] = (layB.src_pstart[jsrc0 + tid] - n0) | (layB.src_nlev[jsrc0 + tid] << 16);
-        if (tid <= kTile / kChunk) chunk0[tid] = tile_meta;
+        if (tid <= kChunks) chunk0[tid] = tile_meta;
     }  // published by the first barrier below
     // `ns` rows of C from source row c0 on, the tile's columns.  Rows behind them begin behind the end (ldc >= nsrcB).
     auto rows_of_c = [&](int c0, int ns) __attribute__((always_inline)) {
@@ -830,19 +979,19 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         const int c0 = meta(2 * wm + half), ns = meta(2 * wm + half + 1) - c0;
         const unsigned pitch = (unsigned)g.ldc * 4u;
         const __amdgpu_buffer_rsrc_t rs = rows_of_c(c0, ns);
-        unsigned off[4];
+        unsigned off[NB];
 #pragma unroll
-        for (int j = 0; j < 4; j += M) off[j] = col_off[j] + (unsigned)(lhalf * G) * pitch;
+        for (int j = 0; j < NB; j += M) off[j] = col_off[j] + (unsigned)(lhalf * G) * pitch;
         double w[L + M];
 #pragma unroll
         for (int l = 0; l < L + M; ++l) w[l] = (double)(1ull << (g.sh * l));
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
-            float f[G][4];
+            float f[G][NB];
 #pragma unroll
             for (int k = 0; k < G; ++k)
 #pragma unroll
-                for (int j = 0; j < 4; j += M) {
+                for (int j = 0; j < NB; j += M) {
                     double v = 0.0;
 #pragma unroll
                     for (int m = 0; m < M; ++m) {
@@ -862,7 +1011,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
 #pragma unroll
             for (int k = 0; k < G; ++k)
 #pragma unroll
-                for (int j = 0; j < 4; j += M)
+                for (int j = 0; j < NB; j += M)
                     store_inside<(L * M > 1)>(f[k][j], rs, off[j] + (unsigned)((ii * 32 + 8 * rg) / L + k) * pitch);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -894,6 +1043,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                 float x;
                 asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[I][jj][r]));
                 v = (int32_t)x;
+            } else if constexpr (DUAL) {
+                asm volatile("v_mov_b32 %0, %1" : "=v"(v) : "v"(acc[I][jj][r]));
             } else {
                 asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(acc[I][jj][r]));
             }
@@ -907,9 +1058,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         };
         if (evenB == 0) with_cols(std::integral_constant<int, 1>{});
         else if (evenB == 2) with_cols(std::integral_constant<int, 2>{});
-        else with_cols(std::integral_constant<int, 4>{});
+        else if constexpr (NB == 4) with_cols(std::integral_constant<int, 4>{});
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
+        for (int jj = 0; jj < NB; ++jj)
             if (col_strip[jj] >= 0)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
@@ -933,17 +1084,17 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
             v4i other[16];
             if (SPLIT && partner) others(half * 2 + ii, other);
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj)
+            for (int jj = 0; jj < NB; ++jj)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     int32_t v = (int32_t)acc[half * 2 + ii][jj][r];
                     if (SPLIT && partner) v = (v << rest) + other[jj * 4 + (r >> 2)][r & 3];
-                    foldbuf[(wm * kChunk + ii * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3)) * FLD + wn * 128 + jj * 32 + lrow] = v;
+                    foldbuf[(wm * kChunk + ii * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3)) * FLD + wn * (32 * NB) + jj * 32 + lrow] = v;
                 }
         }
         __syncthreads();
 #pragma unroll 1
-        for (int reg = 0; reg < 2; ++reg) {
+        for (int reg = 0; reg < kRegions; ++reg) {
             const int c = 2 * reg + half;  // chunk of the tile: rows [64 c, 64 c + 64)
             if (direct >> c & 1) continue;
             const int32_t *fold = foldbuf + reg * kChunk * FLD;
@@ -1077,7 +1228,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     // the split columns of the chunks that were stored from the registers: wave w takes chunk w, a lane a source row
     if (any_direct && nsplit > 0 && nsplit <= kStrips) {
         __syncthreads();
-        if (!((direct & filled) >> wave & 1)) return;
+        if (wave >= kChunks || !((direct & filled) >> wave & 1)) return;
         const int c0 = meta(wave), L = meta(8 + wave), ns = meta(wave + 1) - c0;
         unsigned long long split_cols[4], heads[4];
         find_split(split_cols, heads);
@@ -1117,9 +1268,10 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_split_kernel(const GemmA
     gemm_body<0, FP6, false, true, LISTS>(g, smem);
 }
 
-__global__ __launch_bounds__(kGemmThreads, 1) void gemm_lists_kernel(const GemmArgs g) {
+template <bool LISTS>
+__global__ __launch_bounds__(kGemmThreads, 2) void gemm_dual_kernel(const GemmArgs g) {
     extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
-    gemm_body<0, false, false, false, true>(g, smem);
+    gemm_body<0, false, false, false, LISTS, true>(g, smem);
 }
 
 template <int MODE>
@@ -1211,8 +1363,8 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
             voffB[u] = (unsigned)fp6_ktile(row, 0, ldB) + (unsigned)byte;
         } else {
             const int row = 8 * u + (lane >> 3), byte = ((lane & 7) ^ ((row >> 1) & 7)) * 16;
-            voffA[u] = (unsigned)row * (unsigned)ldA + (unsigned)byte;
-            voffB[u] = (unsigned)row * (unsigned)ldB + (unsigned)byte;
+            voffA[u] = (unsigned)i8_at(row, byte, ldA);
+            voffB[u] = (unsigned)i8_at(row, byte, ldB);
         }
     }
     const int8_t *sa = stages + wave * small_stage_bytes(FP6), *sb = sa + kChunk * kPitch;  // the wave's stage
@@ -1332,9 +1484,9 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
                     ListWords<1> words;
                     unsigned x[16];
                     words.load(list + t, lane);
-                    words.stage(lds, len - t, lane);
+                    v4i fd[1];
+                    words.stage(lds, len - t, lane, fd);
                     list_columns(x, lds + 1024, 0, lhalf, at, (unsigned)lrow * 4u);
-                    const v4i fd = *reinterpret_cast<const v4i *>(lds + 16 * lane);
                     v4i fr[4];
                     list_rows(x, fr);
 #pragma unroll
@@ -1342,7 +1494,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Gemm
                         v4i a;
 #pragma unroll
                         for (int q = 0; q < 4; ++q) a[q] = cm & 1 ? fr[2 + i][q] : fr[i][q];
-                        list_acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, fd, list_acc[i][j], 0, 0, 0);
+                        list_acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, fd[0], list_acc[i][j], 0, 0, 0);
                     }
                 }
             }
@@ -1490,7 +1642,8 @@ static int gemm_lds_opt_in() {
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_split_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
-        IMU_HIP(hipFuncSetAttribute((const void *)gemm_lists_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_dual_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kDualLds));
+        IMU_HIP(hipFuncSetAttribute((const void *)gemm_dual_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kDualLds));
         constexpr int kSmallLds = kSmallMeta + kSmallWaves * small_stage_bytes(false);
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
         IMU_HIP(hipFuncSetAttribute((const void *)gemm_small_kernel<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds));
@@ -1594,7 +1747,7 @@ static int tile_ns(const PlanHeader &h) {
 }
 // Whether the small tiles are the better ones for this plan (and B's rows are laid out for them).
 static bool small_tiles(const Plan *p, int64_t tiles, int64_t pairs, int64_t ktiles) {
-    return p->hdr.chunkB == kChunk && small_tiles_win(tiles, pairs, ktiles, p->nitems == 1, 0, tile_ns(p->hdr));
+    return p->hdr.chunkB == kChunk && small_tiles_win(tiles, pairs, ktiles, p->nitems == 1, !p->fp6, 0, tile_ns(p->hdr));
 }
 // The chunk pairs of an unpacked product that hold source rows.
 static int64_t chunk_pairs(const PlanHeader &h) {
@@ -1638,10 +1791,23 @@ static bool prepare_split(Plan *p, hipStream_t st) {
     return true;
 }
 
+// Whether half tiles, two workgroups to a CU, are the better ones (int8 digits).  While one workgroup loads its first k-tiles, takes
+// columns from lists or stores its results the other one has the matrix cores, and a product that fills half the CUs with whole tiles
+// fills all of them; but a half tile takes half as many operand bytes again for its operations, so over a long contraction that is
+// all there is to it the whole tiles win.  Microseconds with k-tiles t (whole and half tiles, kernel alone): a full round 14 + 1.45 t and 12 +
+// 1.48 t, a round of at most 256 half tiles 9 + 0.8 t.  4096 x 4352 by 11013 with lists 259 and 248 (in a step 288 and 247), 12608 x
+// 896 by 3072, folded rows, 114 and 94; 5120 x 5120 by 4096 138 and 110; 2304 x 2304 by 2048 40 and 26; 10240 x 5760 by 8192 408
+// and 391; but 8192 x 8320 by 4096 222 and 233, 11776 x 11392 by 8192 816 and 835, 1024 x 8448 by 11264 (176 tiles) 100 and 103.
+static bool dual_wins(int64_t tiles, int64_t ktiles) {
+    const int64_t halves = tiles * (BM / kDualRows), full = 12000 + 1483 * ktiles, rem = halves % 512;
+    const int64_t dual = halves / 512 * full + (rem == 0 ? 0 : rem <= 256 ? 9000 + 800 * ktiles : full);
+    return dual < (tiles + 255) / 256 * (kTileNs + 1450 * ktiles);
+}
+
 // The fused launch of one product.
 static int launch_fused(Plan *p, GemmArgs &g, hipStream_t st) {
     const int tiles = g.mtiles * g.ntiles;
-    p->gemm_parts = 0;
+    p->gemm_parts = p->gemm_halves = 0;
     if (small_tiles(p, tiles, chunk_pairs(p->hdr), g.kt1)) return launch_small(p, g, tiles * kChunkPairs, g.kt1, false, st);
     const int parts = split_parts(tiles, g.kt1);
     if (parts > 1 && prepare_split(p, st)) {
@@ -1657,8 +1823,14 @@ static int launch_fused(Plan *p, GemmArgs &g, hipStream_t st) {
         return launch_status();
     }
     p->gemm_parts = 1;
+    if (!p->fp6 && (g.sp_kt >= 0 || dual_wins(tiles, g.kt1))) {  // (with lists the contraction is never so long that the whole tiles win)
+        p->gemm_halves = 1;
+        const dim3 halves((unsigned)(tiles * (BM / kDualRows)));
+        if (g.sp_kt >= 0) hipLaunchKernelGGL(gemm_dual_kernel<true>, halves, dim3(kGemmThreads), kDualLds, st, g);
+        else hipLaunchKernelGGL(gemm_dual_kernel<false>, halves, dim3(kGemmThreads), kDualLds, st, g);
+        return launch_status();
+    }
     if (p->fp6) hipLaunchKernelGGL(gemm_f6_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
-    else if (g.sp_kt >= 0) hipLaunchKernelGGL(gemm_lists_kernel, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
     else hipLaunchKernelGGL(gemm_i8_kernel<0>, dim3(tiles), dim3(kGemmThreads), kGemmLds, st, g);
     return launch_status();
 }
@@ -1782,6 +1954,8 @@ extern "C" int imunpack_gemm(imunpack_plan_t *p, const int8_t *A_ue, const int8_
 }
 
 extern "C" int imunpack_diag_gemm_parts(const imunpack_plan_t *p) { return p ? p->gemm_parts : IMUNPACK_EINVAL; }
+
+extern "C" int imunpack_diag_gemm_halves(const imunpack_plan_t *p) { return p ? p->gemm_halves : IMUNPACK_EINVAL; }
 
 extern "C" int imunpack_diag_list_columns(const imunpack_plan_t *p) { return p && p->valid ? p->hdr.nsparse : IMUNPACK_EINVAL; }
 

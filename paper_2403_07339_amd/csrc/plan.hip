@@ -1992,7 +1992,7 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
         if (chunkB == kChunk && gridDim.y == 1) {
             auto up = [](int x, int by) { return (int64_t)((x + by - 1) / by); };
             const int nu = hdr->n_u, hu = hdr->h_u;
-            if (!small_tiles_win(up(nu, kTile) * up(hu, kTile), up(nu, kChunk) * up(hu, kChunk), up(hdr->d_u, kKPad), true, 25)) chunkB = kTile;
+            if (!small_tiles_win(up(nu, kTile) * up(hu, kTile), up(nu, kChunk) * up(hu, kChunk), up(hdr->d_u, kKPad), true, sh > 3 /* b > 4: int8 digits */, 25)) chunkB = kTile;
         }
         rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr, bx - slA, slB);
         if (LISTS && bx == slA)

@@ -268,7 +268,7 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
                         none[24] = none[25] = none[26] = 0;
                     }
                 } else {
-                    *reinterpret_cast<int4 *>(a.out + (int64_t)p * a.ld + q0) = o;
+                    *reinterpret_cast<int4 *>(a.out + i8_at(p, q0, a.ld)) = o;
                 }
             }
             // ---- the wave's part of the row norm
@@ -436,7 +436,7 @@ __global__ void fixup_kernel(FixupArgs fa, FixupArgs fb, int blocks_a, int block
                         atomicOr(row + fp6_dword(p, grp, frag, i), code << (bit & 31u));
                         if ((bit & 31u) > 26u) atomicOr(row + fp6_dword(p, grp, frag, i + 1), code >> (32u - (bit & 31u)));
                     } else {
-                        f.out[(int64_t)p * f.W + at] = dg;
+                        f.out[i8_at(p, at, f.W)] = dg;
                     }
                     const unsigned nsft = (unsigned)(f.sh * f.col_sexp[f.col_phys[c]]);
                     const unsigned long long term = nsft >= 40u ? (1ull << 44) : ((unsigned long long)m << nsft);
@@ -460,7 +460,7 @@ __device__ __forceinline__ void transpose_block(const TransposeArgs &t, int bloc
     int4 x[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u)  // the stores' widths are multiples of 128
-        x[u] = *reinterpret_cast<const int4 *>(t.A + (int64_t)(g * 128 + 32 * u + (tid >> 3)) * t.ldA + k0 + 16 * (tid & 7));
+        x[u] = *reinterpret_cast<const int4 *>(t.A + i8_at(g * 128 + 32 * u + (tid >> 3), k0 + 16 * (tid & 7), t.ldA));
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         int *to = reinterpret_cast<int *>(lds + (32 * u + (tid >> 3)) * kTrPitch + 16 * (tid & 7));
@@ -552,7 +552,6 @@ __global__ void canonical_kernel(const int8_t *__restrict__ phys, int ld, const 
                                  const int32_t *col_phys, int nrows, int ncols, int8_t *__restrict__ canon, int fp6) {
     const int R = blockIdx.x;
     if (R >= nrows) return;
-    const int8_t *src = phys + (int64_t)row_phys[R] * ld;
     for (int c = threadIdx.x; c < ncols; c += blockDim.x) {
         int8_t v;
         if (fp6) {  // e2m3 code at bit 6 * column -> the integer it stands for (digits are integers)
@@ -569,7 +568,7 @@ __global__ void canonical_kernel(const int8_t *__restrict__ phys, int ld, const 
             const int mag = (int)(eighths >> 3);
             v = (int8_t)((code & 32u) ? -mag : mag);
         } else {
-            v = src[col_phys[c]];
+            v = phys[i8_at(row_phys[R], col_phys[c], ld)];
         }
         canon[(int64_t)R * ncols + c] = v;
     }

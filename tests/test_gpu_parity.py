@@ -1621,6 +1621,67 @@ def test_appended_columns_of_few_digits(imu, n, d, h, sa, longer, parts):
     assert torch.equal(C_int.double(), want[:rows])
 
 
+@pytest.mark.parametrize("n,d,h,b,levels,few,splits,blev,halves", [
+    (257, 128, 8200, 8, 1, 0, 0, 1, True),         # a single k-tile; the second half of a tile of rows is padding
+    (130, 129, 12100, 8, 1, 9, 40, 2, True),       # two k-tiles, rows of one and two levels, split columns
+    (4127, 380, 2049, 8, 2, 3, 0, 1, True),        # three k-tiles, more half tiles than two to a CU
+    (1000, 1300, 8193, 5, 4, 11, 8180, 2, True),   # four levels a row, columns evenly laid out
+    (1000, 1300, 2100, 5, 2, 11, 2095, 3, True),   # ... in four levels
+    (3003, 7700, 2890, 8, 1, 0, 0, 1, False),      # whole tiles: 61 k-tiles
+    (3003, 7700, 2890, 8, 1, 30, 25, 2, False),
+    (1502, 7700, 2890, 8, 2, 3, 0, 1, False),
+    (1502, 7700, 1440, 8, 2, 3, 1438, 2, False),
+])
+def test_half_tiles_and_whole_ones(imu, n, d, h, b, levels, few, splits, blev, halves):
+    """Tiles of 128 x 256, which most products take, and of 256 x 256, for long contractions: fp32 results, from registers or
+    through LDS, are those of the call that also writes int64, bit for bit, and nothing around C is touched; a product
+    whose sums might leave int32 is refused by the launch that has already begun to load it."""
+    s = 1 << (b - 1)
+    rng = np.random.default_rng(n + d + h + levels)
+    Aq, Bq = _rows_of_levels(rng, n, d, s, levels, few), rng.integers(-(s - 1), s, size=(h, d)).astype(np.int32)
+    if splits:
+        Bq[rng.choice(h, splits, replace=False), 5] = -3 * s ** (blev - 1)
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    plan = imu.imunpack_plan(Qa, Qb, b, ROW, ROW)
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+    C_both = torch.full((n, h), -1.0, device="cuda")
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, C_int, C_both, None, fuse=True)
+    assert imu.imunpack_diag_gemm_parts(plan) == 1 and imu.imunpack_diag_gemm_halves(plan) == int(halves)
+    around = torch.full((n * h + 2 * 4096,), -1.0, device="cuda")
+    C = around[4096:-4096].view(n, h)
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, None, C, None, fuse=True)
+    assert torch.equal(C, C_both)
+    assert bool((around[:4096] == -1).all()) and bool((around[-4096:] == -1).all())
+    rows = np.unique(np.concatenate([np.arange(0, n, 61), [n // 2, n - 1]]))
+    assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), oracle.int_gemm(Aq[rows], Bq))
+
+
+def test_half_tiles_refuse_what_may_overflow(imu):
+    """The fused launch goes out before the host knows the bounds: a second unpack of larger integers than the first had."""
+    n, d, h = 300, 400, 8200
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randint(-127, 128, (n, d), generator=g, device="cuda", dtype=torch.int32)
+    B = torch.randint(-127, 128, (h, d), generator=g, device="cuda", dtype=torch.int32)
+    plan = imu.Plan()
+    for top in (1, 128 ** 3):
+        A[:, 7] = 5 * top
+        B[:, 7] = 9 * top
+        imu.imunpack_plan(A, B, 8, COL, COL, plan=plan)
+        A_ue, B_eu = imu.imunpack_unpack(plan, A, B)
+        C = torch.full((n, h), -1.0, device="cuda")
+        if top == 1:
+            imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, None, C, None, fuse=True)
+            assert imu.imunpack_diag_gemm_halves(plan) == 1
+        else:
+            with pytest.raises(imu.ImunpackError):
+                imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, None, C, None, fuse=True)
+            assert bool((C == -1).all())
+            imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, None, C, torch.empty(plan.unpacked_bytes()[2] // 8, dtype=torch.int64, device="cuda"), fuse=True)
+        want = A.double() @ B.double().t()      # exact: below 2^53
+        assert torch.equal(C, want.float())
+
+
 def _few_digits(rng, n, d, h, deep, deep_cols=24):
     """In-Bound integers but for four entries of two digits in every column of B and, if `deep`, five of three in some of
     them, no two of those in one row; a few rows of A have two levels."""
