@@ -477,7 +477,198 @@ struct GreedyShared {
     int found[kPlanWaves], positive[kPlanWaves];
     int lds[40];
     int count;
+    alignas(16) unsigned long long split[32];  // greedy_bits
 };
+
+// What comes before the first batch: the second operand's columns become unsplit originals, the number of edges is reported.  Returns
+// it, or -1 where something has no room (uniform).
+__device__ __forceinline__ long long greedy_begin(const GreedyArgs &g, PlanHeader *hdr, int nc, int nob, int extras) {
+    if (g.second) {
+        if (nc > g.cols.cap) {
+            if (threadIdx.x == 0) flag_overflow(hdr, g.whichC, nc);
+            return -1;
+        }
+        for (int x = threadIdx.x; x < nc; x += kPlanThreads) identity_slot(g.cols, x);
+    }
+    if (nob > g.ob_cap) {
+        if (threadIdx.x == 0) flag_overflow(hdr, g.which_list, nob);
+        return -1;
+    }
+    const long long Etotal = (long long)nob + extras;
+    if (threadIdx.x == 0) {
+        *(g.second ? &hdr->edgesB : &hdr->edgesA) = (int)min(Etotal, 2147483647ll);
+        *(g.second ? &hdr->nobB : &hdr->nobA) = nob;  // the OB entries kept for the scatter
+    }
+    if (Etotal > g.ecap) {
+        if (threadIdx.x == 0) flag_overflow(hdr, g.whichE, (int)min(Etotal, 1ll << 30));
+        return -1;
+    }
+    return Etotal;
+}
+
+// The greedy of an operand of at most 32 W rows and columns whose entries have at most three digits, on bits.  All that is left of an
+// entry above digit 0 is always in the last slot of its row's and of its column's chain of splits, so the state is how often
+// each original row and column has been split, and a slot's count is that of the bits of
+//   (entries of two digits or more) & (other side not split)  |  (entries of three) & (other side split once)
+// in its row or column of the operand (the planes move down by one when the slot is split).  A thread has the bits of one row or of
+// one column in registers: a batch is some hundred instructions a wave and two
+// barriers, with the batches of greedy_run, one for each turn between the sides or bound.  In it, with the edges in LDS,
+// a batch takes 4 us.  24 heads, 197 x 197 gradients of a softmax, some entries of three digits: 160 us, 90 so; both operands of 256 x 256
+// with 330 heavy hitters each: 23 and 23 us, 10 and 13.
+// planes: 64 W W words of LDS.
+template <int W, bool DEEP>  // DEEP: there are entries of three digits
+__device__ __forceinline__ void greedy_bits(const GreedyArgs &g, PlanHeader *hdr, unsigned *planes, GreedyShared &sh, int nob, int extras) {
+    constexpr int S = 32 * W, kSideWaves = W / 2;
+    static_assert(2 * kSideWaves <= kPlanWaves && W <= 16, "a wave for every 64 slots of either side");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int nr = g.second ? hdr->h_u : hdr->n_u, nc = hdr->d1;
+    const int Etotal = (int)greedy_begin(g, hdr, nc, nob, extras);
+    if (Etotal < 0) return;
+    const bool is_col = wave >= kSideWaves;
+    const int own_wave = wave & (kSideWaves - 1), x = own_wave * 64 + lane;  // the thread's original row or column
+    constexpr int kPlanes = DEEP ? 2 : 1;
+    unsigned two[W], three[W];
+    auto load = [&](const unsigned *from) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            two[i] = from[x * W + i];
+            if constexpr (DEEP) three[i] = from[S * W + x * W + i];
+        }
+    };
+    // both sides at once where LDS holds them, else one after the other
+    const bool at_once = 2 * kPlanes * S * W <= g.lds_words;
+    for (int side = 0; side < 2; ++side) {
+        if (side && at_once) break;
+        const int words = (at_once ? 2 : 1) * kPlanes * S * W;
+        for (int t = threadIdx.x * 4; t < words; t += kPlanThreads * 4) *reinterpret_cast<int4 *>(planes + t) = make_int4(0, 0, 0, 0);
+        __syncthreads();
+        for (int e = threadIdx.x; e < Etotal; e += kPlanThreads) {
+            const unsigned long long ed = g.edges[e];
+            if (ed == 0ull) continue;
+            const unsigned lo = (unsigned)ed, hi = (unsigned)(ed >> 32), r = lo & kEdgeSlotMask, c = hi & kEdgeSlotMask;
+            const bool longer = DEEP && ((lo >> kEdgeSlotBits) | ((hi >> kEdgeSlotBits) << 3)) > 2u;
+            auto set = [&](unsigned *to, unsigned own, unsigned other) __attribute__((always_inline)) {
+                const unsigned at = own * W + (other >> 5), bit = 1u << (other & 31);
+                atomicOr(to + at, bit);
+                if (longer) atomicOr(to + S * W + at, bit);
+            };
+            if (at_once || side == 0) set(planes, r, c);
+            if (at_once) set(planes + kPlanes * S * W, c, r);
+            else if (side == 1) set(planes, c, r);
+        }
+        __syncthreads();
+        if (wave < 2 * kSideWaves) {
+            if (at_once) load(planes + (is_col ? kPlanes * S * W : 0));
+            else if (is_col == (side != 0)) load(planes);
+        }
+        if (!at_once) __syncthreads();
+    }
+    const bool serves = wave < 2 * kSideWaves;  // (the other waves only keep in step)
+    if (!serves)
+#pragma unroll
+        for (int i = 0; i < W; ++i) two[i] = three[i] = 0;
+    auto sync = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    // the largest value of either side
+    auto tops = [&](int v, int &rows, int &cols) __attribute__((always_inline)) {
+        v = wave_max_nonneg_lane63(v);
+        if (lane == 63 && serves) sh.found[wave] = v;
+        sync();
+        int m = lane < 2 * kSideWaves ? sh.found[lane] : 0;  // lanes [0, kSideWaves) the rows'
+        m = max(m, IMU_DPP(m, 0x111, 0xf, true));
+        m = max(m, IMU_DPP(m, 0x112, 0xf, true));
+        if constexpr (kSideWaves == 8) m = max(m, IMU_DPP(m, 0x114, 0xf, true));
+        rows = __builtin_amdgcn_readlane(m, kSideWaves - 1);
+        cols = __builtin_amdgcn_readlane(m, 2 * kSideWaves - 1);
+    };
+    int deep_row = 0, deep_col = 0;  // as in greedy_run
+    if constexpr (DEEP) {
+        int n3 = 0;
+#pragma unroll
+        for (int i = 0; i < W; ++i) n3 += __popc(three[i]);
+        tops(n3, deep_row, deep_col);
+        sync();
+    }
+    // a side's slots that are not split, and those that are split once, a word per wave of the side
+    auto masks = [&](bool col, int kind) __attribute__((always_inline)) { return sh.split + (col ? 16 : 0) + 8 * kind; };
+    unsigned long long whole = ~0ull, once = 0ull;  // (the wave's own)
+    if (lane == 0 && serves) {
+        masks(is_col, 0)[own_wave] = whole;
+        masks(is_col, 1)[own_wave] = once;
+    }
+    sync();
+    const SlotSet &mine = is_col ? g.cols : g.rows;
+    int slot = x, splits = 0;  // the last slot of the thread's chain
+    for (int bid = 0;; ++bid) {  // (every batch splits a slot, each original twice at most)
+        int cnt = 0;
+        if (serves)
+#pragma unroll
+            for (int i = 0; i < W; i += 4) {
+                const int4 a = *reinterpret_cast<const int4 *>(reinterpret_cast<const unsigned *>(masks(!is_col, 0)) + i);
+                const unsigned none[4] = {(unsigned)a.x, (unsigned)a.y, (unsigned)a.z, (unsigned)a.w};
+                unsigned one[4] = {0, 0, 0, 0};
+                if constexpr (DEEP) {
+                    const int4 c = *reinterpret_cast<const int4 *>(reinterpret_cast<const unsigned *>(masks(!is_col, 1)) + i);
+                    one[0] = c.x; one[1] = c.y; one[2] = c.z; one[3] = c.w;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) cnt += __popc(DEEP ? (two[i + k] & none[k]) | (three[i + k] & one[k]) : two[i + k] & none[k]);
+            }
+        int c0, c1;
+        tops(cnt, c0, c1);
+        if (c0 <= 0 && c1 <= 0) break;
+        const bool isrow = c0 >= c1;  // rows win ties
+        const int hi = isrow ? c0 : c1, least = (isrow ? deep_row : deep_col) + 1;
+        const int lo = min(hi, max(isrow ? max(c1, 1) : c0 + 1, least));
+        const bool turn = serves && isrow != is_col, pick = turn && cnt >= lo;
+        const unsigned long long picked = __ballot(pick);
+        if (turn) {
+            once = (once & ~picked) | (whole & picked);
+            whole &= ~picked;
+            if (lane == 0) {
+                masks(is_col, 0)[own_wave] = whole;
+                if constexpr (DEEP) masks(is_col, 1)[own_wave] = once;
+                sh.positive[own_wave] = __popcll(picked);
+            }
+        }
+        sync();
+        int nb = 0, before = 0;
+#pragma unroll
+        for (int w = 0; w < kSideWaves; ++w) {
+            if (w == own_wave) before = nb;
+            nb += sh.positive[w];
+        }
+        nb = __builtin_amdgcn_readfirstlane(nb);
+        const int N = isrow ? nr : nc;
+        if (N + nb > (isrow ? g.rows.cap : g.cols.cap)) {
+            if (threadIdx.x == 0) flag_overflow(hdr, isrow ? g.whichR : g.whichC, 2 * (N + nb));
+            return;
+        }
+        if (turn) {
+            if (pick) {
+                const int newX = N + before + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(picked >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)picked, 0u));
+                mine.time[slot] = (uint32_t)bid;
+                mine.child[slot] = newX;
+                mine.root[newX] = x;
+                mine.exp[newX] = ++splits;
+                mine.time[newX] = kNever;
+                mine.child[newX] = -1;
+                mine.key[newX] = ((unsigned long long)bid << 48) | ((unsigned long long)(0xFFFFFF - cnt) << 24) | (unsigned)slot;
+                slot = newX;
+#pragma unroll
+                for (int i = 0; i < W; ++i) {
+                    two[i] = DEEP ? three[i] : 0;
+                    if constexpr (DEEP) three[i] = 0;
+                }
+            }
+        }
+        if (isrow) nr += nb; else nc += nb;
+    }
+    if (threadIdx.x == 0) {
+        *(g.second ? &hdr->h_u : &hdr->n_u) = nr;
+        *(g.second ? &hdr->d_u : &hdr->d1) = nc;
+    }
+}
+constexpr int bits_words(int slots) { return slots <= 256 ? 64 * 8 * 8 : slots <= 512 ? 64 * 16 * 16 : 0; }  // LDS of greedy_bits (0: not for so many)
 
 template <bool LDS, bool RES, bool SHORT>  // LDS: the counts are in LDS; RES: the edges too; SHORT: fewer variants of the passes
 __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_counts, GreedyShared &sh, int nob, int extras, const int deep) {
@@ -492,26 +683,8 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const unsigned long long below = (1ull << lane) - 1ull;
     int nr = g.second ? hdr->h_u : hdr->n_u, nc = hdr->d1;
-    if (g.second) {
-        if (nc > g.cols.cap) {
-            if (threadIdx.x == 0) flag_overflow(hdr, g.whichC, nc);
-            return;
-        }
-        for (int x = threadIdx.x; x < nc; x += kPlanThreads) identity_slot(g.cols, x);
-    }
-    if (nob > g.ob_cap) {
-        if (threadIdx.x == 0) flag_overflow(hdr, g.which_list, nob);
-        return;
-    }
-    const long long Etotal = (long long)nob + extras;
-    if (threadIdx.x == 0) {
-        *(g.second ? &hdr->edgesB : &hdr->edgesA) = (int)min(Etotal, 2147483647ll);
-        *(g.second ? &hdr->nobB : &hdr->nobA) = nob;  // the OB entries kept for the scatter
-    }
-    if (Etotal > g.ecap) {
-        if (threadIdx.x == 0) flag_overflow(hdr, g.whichE, (int)min(Etotal, 1ll << 30));
-        return;
-    }
+    const long long Etotal = greedy_begin(g, hdr, nc, nob, extras);
+    if (Etotal < 0) return;
     // ---- the first edge list was written by ob_copy_kernel: one packed edge per OB entry, then the extra
     // edges of repeated columns (second operand only; the rows they touch start with that many more OB
     // entries)
@@ -970,7 +1143,7 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
     }
 }
 
-template <bool LDS, bool MAY_HOLD = LDS>
+template <bool LDS, bool MAY_HOLD = LDS, bool BITS = false>  // BITS: operands of few rows and columns
 __device__ __forceinline__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_counts) {
     __shared__ GreedyShared sh;
     const int nob = *g.ob_count, extras = g.chain_child ? load_agent(&hdr->extras) : 0;
@@ -978,20 +1151,41 @@ __device__ __forceinline__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr
     int deep = 0;
     for (int x = threadIdx.x; x < nr; x += kPlanThreads) deep |= g.rowmax[x] >= g.s * g.s;
     deep = __syncthreads_or(deep);
+    constexpr bool SHORT = BITS || (LDS && !MAY_HOLD);
+    if constexpr (BITS) {
+        const int words = bits_words(max(nr, hdr->d1));
+        if (words != 0 && words <= g.lds_words) {
+            int longer = 0;
+            if (deep) {
+                for (int x = threadIdx.x; x < nr; x += kPlanThreads) longer |= g.rowmax[x] >= g.s * g.s * g.s;
+                longer = __syncthreads_or(longer);
+            }
+            if (!longer) {
+                unsigned *planes = reinterpret_cast<unsigned *>(lds_counts);
+                const bool narrow = words == bits_words(256);
+                if (narrow && !deep) greedy_bits<8, false>(g, hdr, planes, sh, nob, extras);
+                else if (narrow) greedy_bits<8, true>(g, hdr, planes, sh, nob, extras);
+                else if (!deep) greedy_bits<16, false>(g, hdr, planes, sh, nob, extras);
+                else greedy_bits<16, true>(g, hdr, planes, sh, nob, extras);
+                return;
+            }
+        }
+    }
     const long long E = (long long)nob + extras;
     const long long room = ((long long)g.lds_words - ((g.rows.cap + 7) & ~3) - ((g.cols.cap + 7) & ~3)) / 2;
-    if (MAY_HOLD && E <= room) greedy_run<LDS, MAY_HOLD, false>(g, hdr, lds_counts, sh, nob, extras, deep);
-    else greedy_run<LDS, false, LDS && !MAY_HOLD>(g, hdr, lds_counts, sh, nob, extras, deep);
+    if (MAY_HOLD && E <= room) greedy_run<LDS, MAY_HOLD, SHORT>(g, hdr, lds_counts, sh, nob, extras, deep);
+    else greedy_run<LDS, false, SHORT>(g, hdr, lds_counts, sh, nob, extras, deep);
 }
 
-template <bool LDS>
+// (BITS: a variant of its own, for the registers' sake)
+template <bool LDS, bool BITS>
 __global__ __launch_bounds__(kPlanThreads) void greedy_both_kernel(GreedyArgs g) {
     extern __shared__ __attribute__((aligned(16))) int32_t lds_counts[];
     PlanHeader *hdr = g.hdr + blockIdx.y;
     move_to_item(g);
     if (hdr->overflow) return;
     if (g.skip && *g.skip) return;
-    greedy_both<LDS>(g, hdr, lds_counts);
+    greedy_both<LDS, LDS, BITS>(g, hdr, lds_counts);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2234,6 +2428,31 @@ __global__ __launch_bounds__(256) void ob_copy_kernel(const int32_t *__restrict_
             blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
+// UnpackBoth on both operands of a small product: copies of the lists and greedies, one after the other, by one workgroup.  (Four
+// launches otherwise, each of which waits for the one before, finds its arguments and fetches its instructions again: 256 x 256
+// by 256: 31 us and four launches, 26 and one.)
+constexpr int kGreedyPairSlots = 512;
+constexpr int64_t kGreedyPairList = 1 << 16;  // places in either list: several workgroups copy longer ones
+struct GreedyPair {
+    GreedyArgs g[2];
+    const int32_t *ob[2];
+    int32_t *keep[2];
+    int keep_cap[2];
+};
+__global__ __launch_bounds__(kPlanThreads) void greedy_pair_kernel(GreedyPair f) {
+    extern __shared__ __attribute__((aligned(16))) int32_t lds_counts[];
+    PlanHeader *hdr = f.g[0].hdr + blockIdx.y;
+    for (int op = 0; op < 2; ++op) {
+        if (__syncthreads_or(load_agent(&hdr->overflow))) return;
+        GreedyArgs g = f.g[op];
+        move_to_item(g);
+        ob_copy(item_at(f.ob[op], blockIdx.y * g.list_stride), g.ob_cap, min(*g.ob_count, g.ob_cap), item_at(f.keep[op], blockIdx.y * g.stride), f.keep_cap[op],
+                g.chain_child, g.edges, g.ecap, &hdr->extras, const_cast<int32_t *>(g.extra_rows), g.sh, threadIdx.x, kPlanThreads);
+        __syncthreads();
+        greedy_both<true, true, true>(g, hdr, lds_counts);
+    }
+}
+
 // ---- keep-weights mode (Sec. 4.2: weights are unpacked once, when they are loaded).  The unpacking of the
 // second operand depends on the first only through the column slots of the first operand's unpacking
 // (which columns of B_e are repeats, and their exponents).  If those are what they were for the plan
@@ -2373,6 +2592,9 @@ __global__ __launch_bounds__(kPlanThreads) void keep_plan_kernel(KeepPlan f) {
 static constexpr int kGreedyLdsMax = 136 * 1024;  // dynamic LDS the greedy may use for the two count vectors
 static constexpr int kKeepPlanCols = 16384;       // columns that keep_plan_kernel sets up and compares in one workgroup
 // dynamic LDS of the greedy's two count vectors
+// The larger side of an operand.
+static int greedy_slots(const Plan *p, int phase) { return (int)std::max(phase == 1 ? p->n : p->h, p->d); }
+
 static size_t greedy_lds(const Plan *p, int phase) {
     const SlotSet &rows = phase == 1 ? p->rowA : p->rowB, &cols = phase == 1 ? p->c1 : p->c2;
     return ((size_t)((rows.cap + 7) & ~3) + (size_t)((cols.cap + 7) & ~3)) * sizeof(int32_t);
@@ -2404,6 +2626,9 @@ static GreedyArgs greedy_args(const Plan *p, int phase, int ob_cap, const int32_
     // the counts, and room for edges: a workgroup per CU as long as there are CUs for the items
     const size_t counts = greedy_lds(p, phase), room = p->nitems <= 256 ? 96 * 1024 : 32 * 1024;
     g.lds_words = (int)(std::min(counts + std::min(room, (size_t)g.ecap * 8), std::max(counts, (size_t)kGreedyLdsMax)) / sizeof(int32_t));
+    // ... or for the bits of a small operand (B_e may have more columns than B)
+    const int slots = greedy_slots(p, phase), words = bits_words(slots);
+    if (words != 0) g.lds_words = std::max(g.lds_words, first || 2 * slots <= 256 || p->nitems > 256 ? words : bits_words(512));
     return g;
 }
 
@@ -2421,16 +2646,18 @@ static int run_greedy(Plan *p, int phase, const int32_t *ob, int ob_cap, const i
     const size_t lds_bytes = greedy_lds(p, phase);
     static std::atomic<int> opted_in{0};  // the attribute is idempotent: a race sets the same value twice
     if (!opted_in.load(std::memory_order_acquire)) {
-        IMU_HIP(hipFuncSetAttribute((const void *)greedy_both_kernel<true>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kGreedyLdsMax));
+        IMU_HIP(hipFuncSetAttribute((const void *)greedy_both_kernel<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, kGreedyLdsMax));
+        IMU_HIP(hipFuncSetAttribute((const void *)greedy_both_kernel<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, kGreedyLdsMax));
         opted_in.store(1, std::memory_order_release);
     }
     const unsigned items = (unsigned)p->nitems;
     launch_ob_copy(p, g, phase, ob, st);
-    if (lds_bytes <= (size_t)kGreedyLdsMax)
-        hipLaunchKernelGGL(greedy_both_kernel<true>, dim3(1, items), dim3(kPlanThreads), (size_t)g.lds_words * sizeof(int32_t), st, g);
+    if (lds_bytes <= (size_t)kGreedyLdsMax && bits_words(greedy_slots(p, phase)) != 0)
+        hipLaunchKernelGGL((greedy_both_kernel<true, true>), dim3(1, items), dim3(kPlanThreads), (size_t)g.lds_words * sizeof(int32_t), st, g);
+    else if (lds_bytes <= (size_t)kGreedyLdsMax)
+        hipLaunchKernelGGL((greedy_both_kernel<true, false>), dim3(1, items), dim3(kPlanThreads), (size_t)g.lds_words * sizeof(int32_t), st, g);
     else
-        hipLaunchKernelGGL(greedy_both_kernel<false>, dim3(1, items), dim3(kPlanThreads), 0, st, g);
+        hipLaunchKernelGGL((greedy_both_kernel<false, false>), dim3(1, items), dim3(kPlanThreads), 0, st, g);
     return launch_status();
 }
 
@@ -2503,6 +2730,7 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
     if (!opted_in.load(std::memory_order_acquire)) {
         IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
         IMU_HIP(hipFuncSetAttribute((const void *)layouts_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kLayoutLdsMax));
+        IMU_HIP(hipFuncSetAttribute((const void *)greedy_pair_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kGreedyLdsMax));
         IMU_HIP(hipFuncSetAttribute((const void *)keep_plan_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kGreedyLdsMax));
         opted_in.store(1, std::memory_order_release);
     }
@@ -2563,6 +2791,8 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
                            p->tmpL, p->tmpCur, hdr, which, skip, stride, sstride);
     };
     const bool pair = !keep && !listA && !listB && !scanA && !scanB && std::max(std::max(n, h), d) <= kPairItems * kPlanThreads;
+    const bool both = !keep && callerA && callerB && !scanA && !scanB && std::max(std::max(n, h), d) <= kGreedyPairSlots &&
+                      std::max(stA->ob_cap, stB->ob_cap) <= kGreedyPairList;
     if (pair) {
         LevelPair f;
         f.a = p->rowA; f.b = p->rowB; f.c1 = p->c1; f.c2 = p->c2;
@@ -2576,6 +2806,17 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
         hipLaunchKernelGGL(level_major_pair_kernel, dim3(beside ? 2 : 1, items), dim3(kPlanThreads), 0, st, f);
     }
     else if (at_once) {}  // the first operand is unpacked, the second is to be unpacked anew
+    else if (both) {
+        GreedyPair f;
+        f.g[0] = greedy_args(p, 1, (int)stA->ob_cap, stA->ob_count, sstride, CAP_LISTA, nullptr);
+        f.g[1] = greedy_args(p, 2, (int)stB->ob_cap, stB->ob_count, sstride, CAP_LISTB, nullptr);
+        f.ob[0] = stA->ob; f.ob[1] = stB->ob;
+        f.keep[0] = p->obcopyA; f.keep[1] = p->obcopyB;
+        f.keep_cap[0] = p->cap[CAP_EDGEA]; f.keep_cap[1] = p->cap[CAP_EDGEB];
+        const int words = std::max(f.g[0].lds_words, f.g[1].lds_words);
+        f.g[0].lds_words = f.g[1].lds_words = words;
+        hipLaunchKernelGGL(greedy_pair_kernel, dim3(1, items), dim3(kPlanThreads), (size_t)words * sizeof(int32_t), st, f);
+    }
     else if (p->sA == IMUNPACK_ROW) closed_form(p->rowA, p->statsA[2], nullptr, n, CAP_ROWA, nullptr);
     else if (p->sA == IMUNPACK_COL) closed_form(p->c1, p->statsA[3], nullptr, d, CAP_C1, nullptr);
     else if (callerA) IMU_TRY(run_greedy(p, 1, stA->ob, (int)stA->ob_cap, stA->ob_count, sstride, CAP_LISTA, st));
@@ -2586,7 +2827,7 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
         hipLaunchKernelGGL(keep_decide_kernel, dim3(1), dim3(kPlanThreads), 0, st, keep_args, p->c1, hdr, p->rowB);
         skip = &p->d_keep->same;
     }
-    if (pair) {
+    if (pair || both) {
     } else if (p->sB == IMUNPACK_ROW) {
         closed_form(p->rowB, p->statsB[2], nullptr, h, CAP_ROWB, skip);
         hipLaunchKernelGGL(identity_slots_kernel, dim3(grid_for(p->cap[CAP_C2], 256, 64), items), dim3(256), 0, st,

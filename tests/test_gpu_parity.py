@@ -1292,6 +1292,27 @@ def test_layouts_around_the_sizes_where_they_change(imu, n, d, h, b, sa, sb, kin
     check_against_oracle(imu, Aq, Bq, b, sa, sb)
 
 
+@pytest.mark.parametrize("n,d,h", [(1, 1, 1), (64, 65, 63), (197, 64, 197), (256, 256, 256), (257, 250, 130), (512, 400, 511), (300, 513, 200)])
+@pytest.mark.parametrize("b,digits,share", [(8, 2, 0.02), (8, 3, 0.01), (5, 4, 0.004), (4, 3, 0.2), (2, 2, 0.5)])
+def test_unpack_both_of_few_rows_and_columns(imu, n, d, h, b, digits, share):
+    """Up to 256 and 512 rows and columns, and just beyond, in-bound but for a share of the entries, of up to three digits or more (four are
+    left to the general greedy), spread evenly or crowded in a few rows and columns; columns of A that are split often enough for B_e to
+    have more than 256, or 512.  One operand alone, and both in one launch."""
+    s = 1 << (b - 1)
+    rng = np.random.default_rng(n + 3 * d + h + b + digits)
+
+    def draw(rows):
+        q = rng.integers(-(s - 1), s, size=(rows, d))
+        crowd = np.outer(rng.random(rows) ** 4, rng.random(d) ** 4) * 12
+        big = rng.random((rows, d)) < share * (crowd if rows % 2 else 1.0)
+        q[big] = rng.choice([-1, 1], int(big.sum())) * (s ** (rng.integers(1, digits, int(big.sum()))) + rng.integers(0, s, int(big.sum())))
+        return q.astype(np.int32)
+
+    Aq, Bq = draw(n), draw(h)
+    for sa, sb in ((BOTH, BOTH), (BOTH, COL), (COL, BOTH)):
+        check_against_oracle(imu, Aq, Bq, b, sa, sb)
+
+
 @pytest.mark.parametrize("b,depth", [(6, 3), (8, 2), (2, 5)])
 def test_columns_that_outgrow_their_room_before_an_unpack_both(imu, b, depth):
     """UnpackColumn on A appends more columns than the plan has room for at first, UnpackBoth on B follows the links from a
