@@ -1160,13 +1160,13 @@ __device__ __forceinline__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr
                 for (int x = threadIdx.x; x < nr; x += kPlanThreads) longer |= g.rowmax[x] >= g.s * g.s * g.s;
                 longer = __syncthreads_or(longer);
             }
-            if (!longer) {
+            if (!longer && (MAY_HOLD || !deep || words == bits_words(256))) {
                 unsigned *planes = reinterpret_cast<unsigned *>(lds_counts);
                 const bool narrow = words == bits_words(256);
                 if (narrow && !deep) greedy_bits<8, false>(g, hdr, planes, sh, nob, extras);
                 else if (narrow) greedy_bits<8, true>(g, hdr, planes, sh, nob, extras);
                 else if (!deep) greedy_bits<16, false>(g, hdr, planes, sh, nob, extras);
-                else greedy_bits<16, true>(g, hdr, planes, sh, nob, extras);
+                else if constexpr (MAY_HOLD) greedy_bits<16, true>(g, hdr, planes, sh, nob, extras);
                 return;
             }
         }
@@ -1410,25 +1410,29 @@ struct SparseArgs {
     int32_t *cnt;           // the lengths of the lists, cleared
 };
 
+// (the first wave)
 __device__ __forceinline__ void level_bases(ColTables &t) {
-    int run = 0, la = 1;
-    for (int a = 0; a < kMaxLevelsA; ++a) {
-        t.lvlbase[a] = run;
-        run += (t.cntA[a] + kKPad - 1) / kKPad * kKPad;
-        if (t.cntA[a]) la = a + 1;
+    const int a = threadIdx.x, cnt = a < kMaxLevelsA ? t.cntA[a] : 0, padded = (cnt + kKPad - 1) / kKPad * kKPad;
+    const int incl = wave_inclusive_sum(padded);
+    const unsigned long long any = __ballot(cnt > 0);
+    if (a <= kMaxLevelsA) t.lvlbase[a] = incl - padded;
+    if (a == 63) {
+        t.ka_levels = incl;
+        t.la = any ? 64 - __builtin_clzll(any) : 1;
     }
-    t.lvlbase[kMaxLevelsA] = run;
-    t.ka_levels = run;
-    t.la = la;
 }
 
 // The k-tiles of every group, from hist2, cntA and the level bases: lane e of the first wave takes exponent e.  `report`:
 // the workgroup that writes the run and group tables of the header.
 __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, PlanHeader *hdr, bool report) {
     if (threadIdx.x >= 64) return;
-    const int e = threadIdx.x;
+    const int e = threadIdx.x, la = t.la;  // (levels of A beyond it hold nothing)
     int tiles_sh = 0, ccount = 0, members = 0;
     for (int a = 0; a < kMaxLevelsA; ++a) {
+        if (a >= la) {
+            t.kbase[e * kMaxLevelsA + a] = -1;
+            continue;
+        }
         const int m = t.hist2[e * kMaxLevelsA + a];
         members += m;
         const bool shared = m > 0 && (long long)m * 8 >= (long long)t.cntA[a] * 7;
@@ -1441,7 +1445,7 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
     const int tiles_c = (ccount + kKPad - 1) / kKPad;
     const int tiles = tiles_sh + tiles_c;
     int nrun = tiles_c > 0 ? 1 : 0;  // stretches of k-tiles that walk consecutive blocks of the A store
-    for (int a = 0; a < kMaxLevelsA; ++a)
+    for (int a = 0; a < la; ++a)
         if (t.kbase[e * kMaxLevelsA + a] >= 0) ++nrun;
     // groups come highest exponent first: sums over the lanes above this one
     int above = tiles, above_c = tiles_c, above_n = members > 0 ? 1 : 0, above_r = nrun;
@@ -1480,7 +1484,7 @@ __device__ void column_tables(ColTables &t, int cap_phys, int D, int s, int sh, 
             hdr->run_grp[total_r] = g;
         }
     }
-    for (int a = 0; a < kMaxLevelsA; ++a)
+    for (int a = 0; a < la; ++a)
         if (t.kbase[e * kMaxLevelsA + a] >= 0) t.kbase[e * kMaxLevelsA + a] += k0;
     t.cbase[e] = k0 + tiles_sh * kKPad;
     t.xbase[e] = xb;
@@ -1661,7 +1665,7 @@ __device__ bool cols_layout_lds(const SlotSet &c1, const SlotSet &c2, const ColL
     }
     if (tid >= LA && tid < kMaxLevelsA) t.cntA[tid] = 0;
     __syncthreads();
-    if (tid == 0) level_bases(t);
+    if (tid < 64) level_bases(t);
     __syncthreads();
     column_tables(t, cap_phys, D, s, sh, hdr, part == 0);
     __syncthreads();
@@ -1794,7 +1798,7 @@ __device__ void cols_layout(const SlotSet &c1, const SlotSet &c2, const ColLayou
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) level_bases(t);
+    if (threadIdx.x < 64) level_bases(t);
     __syncthreads();
     const int la = t.la;
     // ---- stored column of every column slot of A's unpacking: level 0 in place, level a >= 1 by rank
@@ -2431,7 +2435,7 @@ __global__ __launch_bounds__(256) void ob_copy_kernel(const int32_t *__restrict_
 // UnpackBoth on both operands of a small product: copies of the lists and greedies, one after the other, by one workgroup.  (Four
 // launches otherwise, each of which waits for the one before, finds its arguments and fetches its instructions again: 256 x 256
 // by 256: 31 us and four launches, 26 and one.)
-constexpr int kGreedyPairSlots = 512;
+constexpr int kGreedyPairSlots = 256;
 constexpr int64_t kGreedyPairList = 1 << 16;  // places in either list: several workgroups copy longer ones
 struct GreedyPair {
     GreedyArgs g[2];
@@ -2449,7 +2453,7 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_pair_kernel(GreedyPair f)
         ob_copy(item_at(f.ob[op], blockIdx.y * g.list_stride), g.ob_cap, min(*g.ob_count, g.ob_cap), item_at(f.keep[op], blockIdx.y * g.stride), f.keep_cap[op],
                 g.chain_child, g.edges, g.ecap, &hdr->extras, const_cast<int32_t *>(g.extra_rows), g.sh, threadIdx.x, kPlanThreads);
         __syncthreads();
-        greedy_both<true, true, true>(g, hdr, lds_counts);
+        greedy_both<true, false, true>(g, hdr, lds_counts);  // (edges of what is not for bits stay in memory: no registers to spare)
     }
 }
 
