@@ -212,7 +212,7 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
             if (live[h]) {
                 int pk[4];
                 const unsigned usft = (unsigned)(a.sh * (er[h] + ecu));
-                if (uniform && onew) {
+                if (uniform) {
                     if (!DENSE || usft == 0u) {
 #pragma unroll
                         for (int j = 0; j < 4; ++j) pk[j] = digit0x4(v[h][j], mask4, mag);
@@ -220,26 +220,37 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
 #pragma unroll
                         for (int j = 0; j < 4; ++j) pk[j] = digits4(v[h][j], usft, a.sh, mag);
                     }
-                } else {  // a digit level and / or a weight per column
+                } else {  // a digit level per column
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const int4 ee = *reinterpret_cast<const int4 *>(a.col_e + q0 + 4 * j);
                         const int ec[4] = {ee.x, ee.y, ee.z, ee.w};
-                        int dg[4];
+                        pk[j] = 0;
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const int t = er[h] + ec[i];
-                            const unsigned sft = (unsigned)(a.sh * t);
-                            const int one[4] = {v[h][j][i], 0, 0, 0};
-                            unsigned m1 = 0;
-                            const bool holds = DENSE ? sft < 32u : t == 0;
-                            dg[i] = holds ? (digits4(one, sft, a.sh, m1) & 0xFF) : 0;
-                            if (holds && m1) {
-                                if (onew) mag += m1;
-                                else wsum += sat44(m1, a.col_w[q0 + 4 * j + i]);
-                            }
+                            const int level = er[h] + ec[i], x = v[h][j][i], sx = x >> 31;
+                            const unsigned sft = (unsigned)(a.sh * level), av = (unsigned)((x ^ sx) - sx);
+                            const int m = (DENSE ? sft < 32u : level == 0) ? (int)__builtin_amdgcn_ubfe(av, sft, (unsigned)a.sh) : 0;
+                            mag += (unsigned)m;
+                            pk[j] |= (((m ^ sx) - sx) & 0xFF) << (8 * i);
                         }
-                        pk[j] = dg[0] | (dg[1] << 8) | (dg[2] << 16) | (dg[3] << 24);
+                    }
+                }
+                // A weight per column (columns of A that the partner repeats beside others that it does not): the digits are those already
+                // made.  (Made once more, column by column, for the sake of the norm they kept a whole wave wherever one of its units is such:
+                // 4096 x 4096 by 11008 86 -> 79 us, against resident weights 30 -> 19 and with 16 rows 12.5 -> 7, 1576 x 768 by 3072 21 -> 19.)
+                if (!onew) {
+                    mag = 0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const ulonglong2 w01 = *reinterpret_cast<const ulonglong2 *>(a.col_w + q0 + 4 * j), w23 = *reinterpret_cast<const ulonglong2 *>(a.col_w + q0 + 4 * j + 2);
+                        const unsigned long long w[4] = {w01.x, w01.y, w23.x, w23.y};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int dg = (int8_t)(pk[j] >> (8 * i));
+                            // (terms below 2^51, 1024 of them in a wave: no saturation before the sum is)
+                            wsum += (unsigned long long)(unsigned)(dg < 0 ? -dg : dg) * min(w[i], 1ull << 44);
+                        }
                     }
                 }
                 o = make_int4(pk[0], pk[1], pk[2], pk[3]);
@@ -300,8 +311,10 @@ __device__ __forceinline__ void scatter_item(const ScatterArgs &a, int item, int
 }
 
 // Two operands in one launch when they take the same variant: waves below a0.items serve a0, the rest a1.
+// (DENSE: eight waves a SIMD, 61 registers; left to itself it takes 76: 12608 x 768 by 3072 28 and 30 us.  The other kind reads less and
+// computes less: held to 64 registers 4096 x 8192 by 4096 took 81 us instead of 76.)
 template <bool DENSE, bool NARROW>
-__global__ __launch_bounds__(kScatterThreads) void scatter_kernel(ScatterArgs a0, ScatterArgs a1) {
+__global__ __launch_bounds__(kScatterThreads, DENSE ? 8 : 1) void scatter_kernel(ScatterArgs a0, ScatterArgs a1) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int item = (int)blockIdx.x * kScatterWaves + wave;
     const bool second = item >= a0.items;
@@ -314,7 +327,7 @@ __global__ __launch_bounds__(kScatterThreads) void scatter_kernel(ScatterArgs a0
 // The same for the items of a batch, whose sizes come from their headers (a kernel of its own: the waves are too
 // short to hide a further dependent read where it is not needed).
 template <bool DENSE, bool NARROW>
-__global__ __launch_bounds__(kScatterThreads) void scatter_batch_kernel(ScatterArgs a0, ScatterArgs a1) {
+__global__ __launch_bounds__(kScatterThreads, DENSE ? 8 : 1) void scatter_batch_kernel(ScatterArgs a0, ScatterArgs a1) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int item = (int)blockIdx.x * kScatterWaves + wave;
     sizes_of_item<NARROW>(a0);
