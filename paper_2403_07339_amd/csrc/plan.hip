@@ -2595,10 +2595,10 @@ __global__ __launch_bounds__(kPlanThreads) void keep_plan_kernel(KeepPlan f) {
 
 static constexpr int kGreedyLdsMax = 136 * 1024;  // dynamic LDS the greedy may use for the two count vectors
 static constexpr int kKeepPlanCols = 16384;       // columns that keep_plan_kernel sets up and compares in one workgroup
-// dynamic LDS of the greedy's two count vectors
 // The larger side of an operand.
 static int greedy_slots(const Plan *p, int phase) { return (int)std::max(phase == 1 ? p->n : p->h, p->d); }
 
+// dynamic LDS of the greedy's two count vectors
 static size_t greedy_lds(const Plan *p, int phase) {
     const SlotSet &rows = phase == 1 ? p->rowA : p->rowB, &cols = phase == 1 ? p->c1 : p->c2;
     return ((size_t)((rows.cap + 7) & ~3) + (size_t)((cols.cap + 7) & ~3)) * sizeof(int32_t);
@@ -2795,8 +2795,11 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
                            p->tmpL, p->tmpCur, hdr, which, skip, stride, sstride);
     };
     const bool pair = !keep && !listA && !listB && !scanA && !scanB && std::max(std::max(n, h), d) <= kPairItems * kPlanThreads;
+    // (A plan that has held a large product has room for its slots: the counts of so many do not fit LDS, whatever the sizes are now, and
+    // the launches of run_greedy keep them in memory.)
     const bool both = !keep && callerA && callerB && !scanA && !scanB && std::max(std::max(n, h), d) <= kGreedyPairSlots &&
-                      std::max(stA->ob_cap, stB->ob_cap) <= kGreedyPairList;
+                      std::max(stA->ob_cap, stB->ob_cap) <= kGreedyPairList &&
+                      std::max(greedy_lds(p, 1), greedy_lds(p, 2)) <= (size_t)kGreedyLdsMax;
     if (pair) {
         LevelPair f;
         f.a = p->rowA; f.b = p->rowB; f.c1 = p->c1; f.c2 = p->c2;
@@ -2820,6 +2823,7 @@ static int run_plan(Plan *p, const int32_t *A, int64_t lda, const int32_t *B, in
         const int words = std::max(f.g[0].lds_words, f.g[1].lds_words);
         f.g[0].lds_words = f.g[1].lds_words = words;
         hipLaunchKernelGGL(greedy_pair_kernel, dim3(1, items), dim3(kPlanThreads), (size_t)words * sizeof(int32_t), st, f);
+        IMU_TRY(launch_status());
     }
     else if (p->sA == IMUNPACK_ROW) closed_form(p->rowA, p->statsA[2], nullptr, n, CAP_ROWA, nullptr);
     else if (p->sA == IMUNPACK_COL) closed_form(p->c1, p->statsA[3], nullptr, d, CAP_C1, nullptr);

@@ -1313,6 +1313,61 @@ def test_unpack_both_of_few_rows_and_columns(imu, n, d, h, b, digits, share):
         check_against_oracle(imu, Aq, Bq, b, sa, sb)
 
 
+def _listed(imu, M, b, cap=None):
+    """Integers on the device with their statistics and list of heavy hitters, as the quantizer hands them over."""
+    X = dev(torch.from_numpy(M)).float()
+    stats = imu.Stats.empty(*M.shape, X.device, cap or imu.Stats.default_ob_cap(*M.shape))
+    Q, _, status = imu.imunpack_quantize(X, 1.0, b, stats=stats)
+    assert int(status.item()) == 0 and np.array_equal(Q.cpu().numpy(), M)
+    return Q, stats
+
+
+@pytest.mark.parametrize("large", [(17000, 700, 32), (32, 700, 17000), (40, 17000, 24)])
+def test_small_products_on_a_plan_that_has_held_a_large_one(imu, large):
+    """UnpackBoth on both operands, a plan object whose rows of A, rows of B or columns once were so many that the greedy's counts of
+    as many do not fit LDS (capacities only grow): small products are planned as by a plan of their own."""
+    rng = np.random.default_rng(large[0])
+    plan = imu.Plan()
+    for n, d, h in (large, (256, 256, 256), (197, 64, 197), large, (1, 3, 2), (300, 280, 310)):
+        Aq, Bq = (rand_ints(rng, r, d, 128, 0.001 if n * d > 1 << 20 or h * d > 1 << 20 else 0.01, 2) for r in (n, h))
+        (Qa, st_a), (Qb, st_b) = _listed(imu, Aq, 8), _listed(imu, Bq, 8)
+        imu.imunpack_plan(Qa, Qb, 8, BOTH, BOTH, st_a, st_b, plan)
+        hnd = oracle.unpack_pair_handle(Aq, Bq, 8, BOTH, BOTH)
+        assert plan.dims()[:3] == (hnd.n_u, hnd.d_u, hnd.h_u)
+        A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+        if max(n, d, h) <= 310:
+            Ac, Bc = imu.imunpack_unpack_canonical(plan, A_ue, B_eu)
+            oa, ob = hnd.operands_i8()
+            assert np.array_equal(Ac.cpu().numpy(), oa) and np.array_equal(Bc.cpu().numpy(), ob)
+        hnd.close()
+        C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+        ws = torch.empty(plan.unpacked_bytes()[2] // 8, dtype=torch.int64, device="cuda")
+        imu.imunpack_gemm(plan, A_ue, B_eu, 1.0, 1.0, C_int, None, ws, fuse=True)
+        assert np.array_equal(C_int.cpu().numpy(), oracle.int_gemm(Aq, Bq))
+
+
+def test_attention_on_a_context_that_has_served_a_large_layer(imu):
+    """The three products of a layer's training step over many tokens, then an attention's, UnpackBoth throughout: one context, the
+    outputs of the small products bit for bit those of a context of their own and within tolerance of the oracle chain."""
+    g = torch.Generator().manual_seed(61)
+    tokens, d, h = 17000, 700, 32
+    x, w, gy = (torch.randn(shape, generator=g) for shape in ((tokens, d), (h, d), (tokens, h)))
+    x[:, 5] *= 30.0
+    w[torch.rand(w.shape, generator=g) < 0.001] *= 20.0
+    q, k = (torch.randn((6, 197, 64), generator=g) for _ in range(2))
+    k[..., 5] *= 12.0
+    p = torch.softmax(torch.randn((6, 197, 197), generator=g) * 3, -1)
+    v = torch.randn((6, 64, 197), generator=g)
+    ctx = imu.BatchContext()
+    for A, B in ((x, w), (gy, w.t()), (gy.t(), x.t()), (q, k), (p, v), (x, w), (q, k)):
+        got = imu.imunpack_gemm_batched(dev(A), dev(B), 95.0, 31.0, 31.0, 8, BOTH, BOTH, ctx=ctx)
+        assert torch.equal(got, imu.imunpack_gemm_batched(dev(A), dev(B), 95.0, 31.0, 31.0, 8, BOTH, BOTH, ctx=imu.BatchContext()))
+        for a_i, b_i, got_i in ((A, B, got),) if A.dim() == 2 else ((A[i], B[i], got[i]) for i in (0, 5)):
+            want = _oracle_matmul(a_i.contiguous().numpy(), b_i.contiguous().numpy(), 95.0, 31.0, 31.0)
+            assert (np.abs(got_i.cpu().numpy().astype(np.float64) - want) <= REL_TOL * np.abs(want)).all()
+    ctx.destroy()
+
+
 @pytest.mark.parametrize("b,depth", [(6, 3), (8, 2), (2, 5)])
 def test_columns_that_outgrow_their_room_before_an_unpack_both(imu, b, depth):
     """UnpackColumn on A appends more columns than the plan has room for at first, UnpackBoth on B follows the links from a
