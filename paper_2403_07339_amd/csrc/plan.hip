@@ -1143,7 +1143,8 @@ __device__ __forceinline__ void greedy_run(const GreedyArgs &g, PlanHeader *hdr,
     }
 }
 
-template <bool LDS, bool MAY_HOLD = LDS, bool BITS = false>  // BITS: operands of few rows and columns
+// BITS: operands of few rows and columns; DEEP: three digits go by bits of 512 slots too
+template <bool LDS, bool MAY_HOLD = LDS, bool BITS = false, bool DEEP = BITS>
 __device__ __forceinline__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr, int32_t *lds_counts) {
     __shared__ GreedyShared sh;
     const int nob = *g.ob_count, extras = g.chain_child ? load_agent(&hdr->extras) : 0;
@@ -1160,13 +1161,13 @@ __device__ __forceinline__ void greedy_both(const GreedyArgs &g, PlanHeader *hdr
                 for (int x = threadIdx.x; x < nr; x += kPlanThreads) longer |= g.rowmax[x] >= g.s * g.s * g.s;
                 longer = __syncthreads_or(longer);
             }
-            if (!longer && (MAY_HOLD || !deep || words == bits_words(256))) {
+            if (!longer && (DEEP || !deep || words == bits_words(256))) {
                 unsigned *planes = reinterpret_cast<unsigned *>(lds_counts);
                 const bool narrow = words == bits_words(256);
                 if (narrow && !deep) greedy_bits<8, false>(g, hdr, planes, sh, nob, extras);
                 else if (narrow) greedy_bits<8, true>(g, hdr, planes, sh, nob, extras);
                 else if (!deep) greedy_bits<16, false>(g, hdr, planes, sh, nob, extras);
-                else if constexpr (MAY_HOLD) greedy_bits<16, true>(g, hdr, planes, sh, nob, extras);
+                else if constexpr (DEEP) greedy_bits<16, true>(g, hdr, planes, sh, nob, extras);
                 return;
             }
         }
@@ -2453,7 +2454,11 @@ __global__ __launch_bounds__(kPlanThreads) void greedy_pair_kernel(GreedyPair f)
         ob_copy(item_at(f.ob[op], blockIdx.y * g.list_stride), g.ob_cap, min(*g.ob_count, g.ob_cap), item_at(f.keep[op], blockIdx.y * g.stride), f.keep_cap[op],
                 g.chain_child, g.edges, g.ecap, &hdr->extras, const_cast<int32_t *>(g.extra_rows), g.sh, threadIdx.x, kPlanThreads);
         __syncthreads();
-        greedy_both<true, false, true>(g, hdr, lds_counts);  // (edges of what is not for bits stay in memory: no registers to spare)
+        // What is not for bits of 256 slots, entries of four digits or more above all, has its edges in LDS (256 x 256 by 256, b = 5, four
+        // digits, 1 % of heavy hitters: planned in 300 us with the edges in memory, in 236 so; with 5 % at b = 4 451 and 360, where two
+        // launches of greedy_both_kernel and two copies by many workgroups took 336).  Three digits in a B_e of 257 to 512 columns go that way
+        // too (184 and 156 us): with bits for them as well the kernel spills.
+        greedy_both<true, true, true, false>(g, hdr, lds_counts);
     }
 }
 

@@ -243,16 +243,21 @@ def test_quantize_flags_bad_input(imu):
 
 
 # ------------------------------------------------------------------ plan + operands + product
-def check_against_oracle(imu, Aq, Bq, b, sa, sb, scale_a=0.013, scale_b=0.0021, full_product=True, fp6=False):
+def check_against_oracle(imu, Aq, Bq, b, sa, sb, scale_a=0.013, scale_b=0.0021, full_product=True, fp6=False, lists=None):
     """Aq, Bq: int32 numpy.  Compares plan, unpacked operands, int64 product (fused and un-fused)
-    and the fp32 output with the oracle.  fp6: the digits are stored as 6-bit floating-point codes."""
+    and the fp32 output with the oracle.  fp6: the digits are stored as 6-bit floating-point codes.  lists: the plan is made from
+    the caller's statistics and lists of heavy hitters, with so many places each, and not from scans of its own."""
     n, h = Aq.shape[0], Bq.shape[0]
     s = 1 << (b - 1)
     hnd = oracle.unpack_pair_handle(Aq, Bq, b, sa, sb)
     S, pas, paw, pbs, pbw = hnd.meta()
     assert hnd.max_abs() <= s - 1
-    A_d, B_d = dev(torch.from_numpy(Aq)), dev(torch.from_numpy(Bq))
-    plan = imu.imunpack_plan(A_d, B_d, b, sa, sb)
+    if lists is None:
+        A_d, B_d = dev(torch.from_numpy(Aq)), dev(torch.from_numpy(Bq))
+        plan = imu.imunpack_plan(A_d, B_d, b, sa, sb)
+    else:
+        (A_d, stats_a), (B_d, stats_b) = _listed(imu, Aq, b, lists[0]), _listed(imu, Bq, b, lists[1])
+        plan = imu.imunpack_plan(A_d, B_d, b, sa, sb, stats_a, stats_b)
     n_u, d_u, h_u, ng = plan.dims()
     assert (n_u, d_u, h_u) == (hnd.n_u, hnd.d_u, hnd.h_u)
     ra_s, ra_e, rb_s, rb_e, c_s, c_e, c_par, ops = [t.numpy().astype(np.int64) for t in plan.export_all()]
@@ -1311,6 +1316,56 @@ def test_unpack_both_of_few_rows_and_columns(imu, n, d, h, b, digits, share):
     Aq, Bq = draw(n), draw(h)
     for sa, sb in ((BOTH, BOTH), (BOTH, COL), (COL, BOTH)):
         check_against_oracle(imu, Aq, Bq, b, sa, sb)
+    # both in one launch, from lists of the caller: room for every entry; too little for A's, for B's (planned from scans then)
+    for lists in ((n * d, h * d), (7, h * d), (n * d, 7)):
+        check_against_oracle(imu, Aq, Bq, b, BOTH, BOTH, lists=lists)
+
+
+@pytest.mark.parametrize("deep_a,deep_b", [(True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("b,digits,share", [(2, 9, 0.3), (8, 3, 0.3), (4, 5, 0.12)])
+def test_sets_that_outgrow_their_room_in_one_launch(imu, b, digits, share, deep_a, deep_b):
+    """UnpackBoth on both operands of at most 256 rows and columns, from lists: rows, columns and edges of the first operand, of the second
+    or of both are more than a plan has room for at first."""
+    rng = np.random.default_rng(b + 2 * deep_a + deep_b)
+    s = 1 << (b - 1)
+    n, d, h = 256, 255, 250
+    Aq, Bq = (_wide_ints(rng, rows, d, s, digits, share) if deep else rng.integers(-(s - 1), s, size=(rows, d)).astype(np.int32)
+              for rows, deep in ((n, deep_a), (h, deep_b)))
+    check_against_oracle(imu, Aq, Bq, b, BOTH, BOTH, lists=(n * d, h * d))
+
+
+def _wide_ints(rng, rows, d, s, digits, share):
+    """In-Bound integers but for a share of 2 to `digits` digits."""
+    q = rng.integers(-(s - 1), s, size=(rows, d))
+    big = rng.random((rows, d)) < share
+    q[big] = rng.choice([-1, 1], int(big.sum())) * (s ** (rng.integers(1, digits, int(big.sum()))) + rng.integers(0, s, int(big.sum())))
+    return q.astype(np.int32)
+
+
+@pytest.mark.parametrize("n,d,h", [(256, 256, 255), (197, 64, 256), (255, 197, 64)])
+@pytest.mark.parametrize("b", [8, 5])
+def test_batched_unpack_both_whose_items_differ_in_digits(imu, n, d, h, b):
+    """A batch whose items hold no heavy hitters, some of two and of three digits (in B_e of up to 256 columns and of more) and of four or
+    more, in either operand or in both: each against the oracle chain, and bit for bit what it gives alone."""
+    g = torch.Generator().manual_seed(n + d + b)
+    s = float(1 << (b - 1))
+    # digits of the longest entries of A, of B (at b = 8 no weight may exceed 62 bits: eight digits above the first in all)
+    kinds = [(0, 0), (2, 2), (3, 0), (0, 3), (3, 3), (4, 0), (2, 4), (0, 5)]
+    a, bt = (torch.randn((len(kinds), rows, d), generator=g).clamp_(-2.5, 2.5) for rows in (n, h))
+    for i, digits in enumerate(kinds):
+        for x, k in zip((a[i], bt[i]), digits):
+            if k:
+                big = torch.rand(x.shape, generator=g) < 0.01
+                x[big] = 6.0 * 1.96 / s * s ** torch.randint(1, k, (int(big.sum()),), generator=g).float()   # 1.5 s^1 to 1.5 s^(k - 1)
+    out = imu.imunpack_gemm_batched(dev(a), dev(bt), 95.0, s / 2, s / 2, b, BOTH, BOTH, ctx=imu.BatchContext())
+    for i, digits in enumerate(kinds):
+        for x, k in zip((a[i], bt[i]), digits):
+            top = np.abs(oracle_quant(x, oracle.rtn_step(oracle.percentile_alpha(x.numpy(), 95.0), s / 2)).astype(np.int64)).max()
+            assert s ** max(k - 1, 0) <= top < s ** max(k, 1)
+        alone = imu.imunpack_gemm_batched(dev(a[i:i + 1]), dev(bt[i:i + 1]), 95.0, s / 2, s / 2, b, BOTH, BOTH, ctx=imu.BatchContext())
+        assert torch.equal(out[i], alone[0]), i
+        want = _oracle_matmul(a[i].numpy(), bt[i].numpy(), 95.0, s / 2, s / 2)
+        assert (np.abs(out[i].cpu().numpy().astype(np.float64) - want) <= REL_TOL * np.abs(want)).all(), i
 
 
 def _listed(imu, M, b, cap=None):
