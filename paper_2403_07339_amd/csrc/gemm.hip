@@ -193,11 +193,8 @@ __device__ __forceinline__ const int8_t *uniform_ptr(const int8_t *p) {
 
 // c += a b on accumulation registers, by hand: with the builtin in a second place the compiler moves accumulators between the two
 // register files on the way (253 registers spilled).  The operands may have been written just before (two wait states); what
-// reads c next has to wait for it.
-template <bool VGPR>
+// reads c next has to wait for it.  (Where the sums are ordinary registers the builtin does as well, and the compiler sees to the waits.)
 __device__ __forceinline__ void mfma_in_place(const v4i &a, const v4i &b, v16i &c) {
-    if constexpr (VGPR) asm volatile("s_nop 1\n\tv_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
-    else
     asm volatile("s_nop 1\n\tv_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
@@ -623,7 +620,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
                     list_rows(x[s], fr);
 #pragma unroll
                     for (int rb = 0; rb < 4; ++rb)
-                        if constexpr (LISTS) mfma_in_place<DUAL>(fr[rb], digits[s], acc[rb][CB]);
+                        if constexpr (LISTS && DUAL) mma(fr[rb], digits[s], acc[rb][CB]);
+                        else if constexpr (LISTS) mfma_in_place(fr[rb], digits[s], acc[rb][CB]);
+                    if constexpr (DUAL) __builtin_amdgcn_sched_barrier(0);  // (the next one's rows are put together behind: 4096 x 4352 by 11013 0.7 % of a step)
                 }
             }
             list = next;
@@ -633,8 +632,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         if constexpr (!DUAL) {
             block(std::integral_constant<int, 2>{});
             block(std::integral_constant<int, 3>{});
+            // What comes behind does not know of these matrix instructions: it takes the sums from here, once they stand.
+            asm volatile("s_nop 15\n\ts_nop 3"
+                         : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][NB - 2]), "+a"(acc[0][NB - 1]), "+a"(acc[1][0]), "+a"(acc[1][1]),
+                           "+a"(acc[1][NB - 2]), "+a"(acc[1][NB - 1]), "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][NB - 2]),
+                           "+a"(acc[2][NB - 1]), "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][NB - 2]), "+a"(acc[3][NB - 1]));
         }
-        asm volatile("s_nop 15\n\ts_nop 3");  // (the matrix instructions behind do not know of these)
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read: it may be filled
     };
     // Horner step
