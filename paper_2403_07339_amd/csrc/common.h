@@ -289,7 +289,7 @@ __host__ __device__ __forceinline__ int64_t fp6_ktile(int row, int kt, int64_t l
 }
 // int8 digits in memory: rows 2i and 2i + 1 of a store share their bytes, so that 64 columns of both are one line of 128 bytes: row 2i
 // holds the columns [128 k, 128 k + 64) of both, row 2i + 1 the other half.  A GEMM that walks the contraction 64 columns at a time
-// still fetches whole lines (64 bytes of a line at a time arrive at half the rate: 24 against 41 bytes per clock and CU).
+// still fetches whole lines (64 bytes of a line at a time arrive at some 25 bytes per clock and CU, whole lines at 41).
 // Where byte `col` of row `row` lies:
 __host__ __device__ __forceinline__ int64_t i8_at(int row, int col, int64_t ld) {
     return ((row & ~1) + ((col >> 6) & 1)) * ld + (col >> 7) * 128 + (row & 1) * 64 + (col & 63);

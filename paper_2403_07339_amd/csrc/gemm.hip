@@ -302,7 +302,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
         kt0 = 0; kt1 = hdr->Kp / BK;
         nbound = hdr->nruns - 1;
     }
-    // (DUAL: checked behind the first loads, the bounds come from memory.)
+    // (DUAL: the branch on them stands behind the first loads; the words themselves, read under a condition, are waited for here.)
     unsigned long long bound0 = 0, bound1 = 0;
     if (MODE == 0 && (BATCH || g.guard)) {
         const unsigned long long *guard = BATCH ? hdr->bound : g.guard;
@@ -589,7 +589,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     int kt = kt0;
     int seg = seg0;
     // The columns that are taken from lists: the wave's four blocks of 32 physical rows of B in turn, 128 entries at a time, through what
-    // the wave itself will fill of the slot of the ring that is free now (the waves are at different places here).
+    // the wave itself will fill of the slot of the ring that is free now (the waves are at different places here).  In half tiles two
+    // blocks, 64 entries at a time, through 2 KiB that the wave has for this alone: no stage is free.
     auto lists = [&]() __attribute__((always_inline)) {
         const int8_t *at = uniform_ptr(g.at + (int64_t)(tm * (BM / 128) + wm) * g.at_cols * 128);
         const unsigned row_off = (unsigned)lrow * 4u;
@@ -850,8 +851,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &g, int8_t *smem) {
     //     cycles instead of 34 000 (4096 x 8228 by 11013, one run: 344 and 317 us).  With levels there is a half of that or less, and
     //     the non-temporal ones leave the last-level cache to the operands: a step of 12608 x 768 by 3072 226 and 233 us.
     //     The price is code: nine pairs of levels times four blocks of rows, straight down, make this kernel 170 kB (50 with the
-    //     ways through LDS alone) and spill 5 vector registers (17 six-bit, 49 and 16 in parts, 64 in parts beside lists, 10 and 26 in a batch), all of them
-    //     behind the walk along the contraction.
+    //     ways through LDS alone) and spill 10 vector registers (17 six-bit, 17 and 16 in parts, 32 in parts beside lists, 10 and 26 in a batch; none in half tiles),
+    //     all of them behind the walk along the contraction.
     // (2) Through LDS ([64][256] int32, rows padded to 260) for everything else: int64 results, rows of several kinds in a chunk,
     //     many split columns, results without levels of large products (whole_rows_win).  Global stores are row-contiguous, any
     //     levels can be added up (the planner keeps a source row in one chunk, a source column in one tile).
@@ -1812,6 +1813,9 @@ static int launch_fused(Plan *p, GemmArgs &g, hipStream_t st) {
     const int tiles = g.mtiles * g.ntiles;
     p->gemm_parts = p->gemm_halves = 0;
     if (small_tiles(p, tiles, chunk_pairs(p->hdr), g.kt1)) return launch_small(p, g, tiles * kChunkPairs, g.kt1, false, st);
+    // (Parts are asked for before half tiles, by what they gain over whole tiles.  Half tiles against them, microseconds in parts and in half tiles:
+    // 64 tiles, 48 k-tiles 63 and 45, 118: 91 and 89; 128 tiles, 48: 75 and 54, 100: 112 and 98; 320 tiles, 48: 152 and 126, 96: 240 and 230;
+    // 528 tiles, 66: 284 and 271; but 272 tiles, 128: 278 and 292.  So below about a hundred k-tiles they would be the better ones.)
     const int parts = split_parts(tiles, g.kt1);
     if (parts > 1 && prepare_split(p, st)) {
         g.meet = (int32_t *)p->split_ws;
@@ -1826,7 +1830,7 @@ static int launch_fused(Plan *p, GemmArgs &g, hipStream_t st) {
         return launch_status();
     }
     p->gemm_parts = 1;
-    if (!p->fp6 && (g.sp_kt >= 0 || dual_wins(tiles, g.kt1))) {  // (with lists the contraction is never so long that the whole tiles win)
+    if (!p->fp6 && (g.sp_kt >= 0 || dual_wins(tiles, g.kt1))) {  // (lists hold up a whole tile for some 12 us more, which its k-tiles make up for only after hundreds)
         p->gemm_halves = 1;
         const dim3 halves((unsigned)(tiles * (BM / kDualRows)));
         if (g.sp_kt >= 0) hipLaunchKernelGGL(gemm_dual_kernel<true>, halves, dim3(kGemmThreads), kDualLds, st, g);
