@@ -1808,6 +1808,16 @@ static bool dual_wins(int64_t tiles, int64_t ktiles) {
     return dual < (tiles + 255) / 256 * (kTileNs + 1450 * ktiles);
 }
 
+// Rows of B in four places each, evenly laid out, and rows of A that are too, or have one level: a whole tile folds its results in the
+// registers (a lane has all four levels of a source column), a half tile, whose waves are two blocks of 32 columns wide, takes them through LDS.
+// Whole and half tiles, microseconds with b = 3, rows of B of four levels: 6392 x 256 by 4 x 9904 rows 171 and 330, x 1024 286 and 398; 1500 x
+// 512 by 4 x 1500 17 and 31, x 2048 31 and 44; 3000 x 1024 by 4 x 3000, rows of A of two levels 87 and 125, of four 154 and 230; over long
+// contractions the walk decides: 3000 x 6016 by 4 x 3000 181 and 182, x 9088 257 and 252; 1000 x 3072 by 4 x 2000 (128 tiles) 38 and 38.  Where
+// rows of A go through LDS in whole tiles too, 364 and 234 (three levels), 89 and 85 (five rows of 3000 have two), or int64 results, 148 and 88.
+static bool whole_tiles_fold(const GemmArgs &g, const PlanHeader &h, int64_t tiles) {
+    return h.evenB == 4 && (h.lmaxA == 1 || h.evenA) && g.fold_f64 && !g.C_int && g.ldc < kDirectPitch && g.kt1 <= (tiles <= 128 ? 24 : 48);
+}
+
 // The fused launch of one product.
 static int launch_fused(Plan *p, GemmArgs &g, hipStream_t st) {
     const int tiles = g.mtiles * g.ntiles;
@@ -1830,7 +1840,7 @@ static int launch_fused(Plan *p, GemmArgs &g, hipStream_t st) {
         return launch_status();
     }
     p->gemm_parts = 1;
-    if (!p->fp6 && (g.sp_kt >= 0 || dual_wins(tiles, g.kt1))) {  // (lists hold up a whole tile for some 12 us more, which its k-tiles make up for only after hundreds)
+    if (!p->fp6 && (g.sp_kt >= 0 || (dual_wins(tiles, g.kt1) && !whole_tiles_fold(g, p->hdr, tiles)))) {  // (lists hold up a whole tile for some 12 us more, which its k-tiles make up for only after hundreds)
         p->gemm_halves = 1;
         const dim3 halves((unsigned)(tiles * (BM / kDualRows)));
         if (g.sp_kt >= 0) hipLaunchKernelGGL(gemm_dual_kernel<true>, halves, dim3(kGemmThreads), kDualLds, st, g);

@@ -1788,6 +1788,37 @@ def test_half_tiles_and_whole_ones(imu, n, d, h, b, levels, few, splits, blev, h
     assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), oracle.int_gemm(Aq[rows], Bq))
 
 
+@pytest.mark.parametrize("n,d,h,b,levels,few,blev,halves", [
+    (1500, 130, 1499, 3, 1, 0, 4, 0),     # four levels of every row of B, two k-tiles: folded in the registers of whole tiles
+    (700, 300, 1500, 3, 2, 0, 4, 0),      # ... and two of every row of A
+    (400, 300, 1500, 3, 4, 3, 4, 0),      # ... and four, but three rows with three
+    (1500, 300, 1500, 3, 1, 9, 4, 1),     # rows of A of one and two levels in a chunk go through LDS
+    (700, 300, 1500, 3, 3, 0, 4, 1),      # so do three levels
+    (700, 300, 1500, 8, 2, 0, 4, 1),      # sums that binary64 does not hold
+    (1000, 3072, 2000, 3, 1, 0, 4, 0),    # 128 tiles, 24 k-tiles
+    (1000, 3073, 2000, 3, 1, 0, 4, 1),    # ... 25
+    (3000, 5889, 3000, 3, 1, 0, 4, 0),    # a little more than two rounds, 47 k-tiles
+])
+def test_four_levels_of_every_column_fold_in_whole_tiles(imu, n, d, h, b, levels, few, blev, halves):
+    """Rows of B of four levels each: in whole tiles a lane has them all, half tiles take them through LDS; either way the fp32
+    results are those of the call that also writes int64, bit for bit, which is the oracle's."""
+    s = 1 << (b - 1)
+    rng = np.random.default_rng(n + d + h + levels)
+    Aq, Bq = _rows_of_levels(rng, n, d, s, levels, few), _rows_of_levels(rng, h, d, s, blev, 0)
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    plan = imu.imunpack_plan(Qa, Qb, b, ROW, ROW)
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    C_int = torch.full((n, h), -1, dtype=torch.int64, device="cuda")
+    C_both, C = (torch.full((n, h), -1.0, device="cuda") for _ in range(2))
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, C_int, C_both, None, fuse=True)
+    assert imu.imunpack_diag_gemm_parts(plan) == 1 and imu.imunpack_diag_gemm_halves(plan) == 1
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, None, C, None, fuse=True)
+    assert imu.imunpack_diag_gemm_parts(plan) == 1 and imu.imunpack_diag_gemm_halves(plan) == halves
+    assert torch.equal(C, C_both)
+    rows = np.unique(np.concatenate([np.arange(0, n, 61), [n // 2, n - 1]]))
+    assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), oracle.int_gemm(Aq[rows], Bq))
+
+
 def test_half_tiles_refuse_what_may_overflow(imu):
     """The fused launch goes out before the host knows the bounds: a second unpack of larger integers than the first had."""
     n, d, h = 300, 400, 8200
