@@ -410,19 +410,14 @@ __host__ __device__ inline int split_parts(int64_t tiles, int64_t ktiles) {
 // k-tile for each sixteen of them, and no less than 0.3 us per k-tile.  (1024 x 1664 by 2048 rows, 32 tiles: 27 and 12 us;
 // 2048 x 1152 by 2048, 64 tiles: 28 and 24; 3072 x 1920 by 2048, 96 tiles: 29 and 32; 3840 x 1024 by 2048, 120 tiles: 22 and 30;
 // 4096 x 1920 by 2048, 128 tiles: 31 and 42; 2048 x 15104 by 2048: 81 in parts and 96; 3328 x 4608 by 768, 39 tiles: 51 and 29.)
-// Half tiles of int8 digits (dual_wins in gemm.hip) take 9 us and 0.8 us per k-tile where there are CUs for all of them.  (1024 x 1152 by
-// 1024, 16 tiles: 21 us, small tiles 19; 512 x 4992 by 4096, 48 tiles: 41 and 39; 1576 x 896 by 3072, 84 tiles: 20 and 36; 768 x 1024 by
-// 3072, 72 tiles: 18 and 29.)
-// `single`: a product of its own, whose last round may be cut.  halves: one that may run in half tiles.  margin: percent by which the large tiles have to be better.
+// `single`: a product of its own, whose last round may be cut.  margin: percent by which the large tiles have to be better.
 // tile_ns: what a tile takes besides its walk, kTileNs where its results go out from the registers.
 constexpr int kTileNs = 14000;
-__host__ __device__ inline bool small_tiles_win(int64_t tiles, int64_t pairs, int64_t ktiles, bool single, bool halves, int margin, int tile_ns = kTileNs) {
+__host__ __device__ inline bool small_tiles_win(int64_t tiles, int64_t pairs, int64_t ktiles, bool single, int margin, int tile_ns = kTileNs) {
     const int64_t walk = 300 * ktiles, work = pairs * (200 + 10 * ktiles) / kChunkPairs;
     const int64_t small = 6000 + (walk > work ? walk : work);
     const bool parts = single && tiles <= 256 && split_parts(tiles, ktiles) > 1;
-    const int64_t large = parts                                       ? tile_ns + 6000 + 520 * ktiles
-                          : single && halves && tiles <= 128 ? tile_ns / 2 + 2000 + 800 * ktiles
-                                                             : (tiles + 255) / 256 * (tile_ns + 1050 * ktiles);
+    const int64_t large = parts ? tile_ns + 6000 + 520 * ktiles : (tiles + 255) / 256 * (tile_ns + 1050 * ktiles);
     return small * 100 < large * (100 + margin);
 }
 

@@ -1749,9 +1749,29 @@ static int tile_ns(const PlanHeader &h) {
     if (h.lmaxB > 1 && !h.evenB) return 10000 + 4500 * h.lmaxA * h.lmaxB;
     return h.lmaxA > 1 && !h.evenA ? 12000 + 3000 * h.lmaxA : kTileNs;
 }
+// Where there are CUs for all half tiles (int8 digits, a product of its own, at most 128 tiles; see dual_wins) the choice is between those and the
+// small ones, by least-squares fits over 895 products of 8 to 128 tiles, 1 to 64 k-tiles and one to five levels on either side (nanoseconds, rms 1.2 to
+// 1.8 us and 3.3 us; what they choose takes 0.9 % more in all than the better one each time, 29 % at worst).  Half tiles: results that leave from
+// the registers take the least, and where they go through LDS it is the levels of B that cost (1576 x 896 by 3072, 84 tiles, 20 us and small tiles 36;
+// 459 x 256 by 2 x 3036 rows, rows of A of two and three levels, 22 and 12; 1047 x 1280 by 3 x 1257 29 and 37).  Small tiles: by the chunk
+// pairs that hold anything and, for their levels, by the rounds that all of them take, two to a CU.
+static bool small_tiles_beat_halves(const PlanHeader &h, int64_t tiles, int64_t pairs, int64_t ktiles) {
+    const bool unevenA = h.lmaxA > 1 && !h.evenA, unevenB = h.lmaxB > 1 && !h.evenB;
+    const int64_t results = unevenA && unevenB     ? 19400 + 3300 * h.lmaxB - 1800 * h.lmaxA
+                            : unevenB              ? 12300 + 2900 * h.lmaxB - 900 * h.lmaxA
+                            : unevenA && h.lmaxB > 1 ? 22400 - 1000 * h.lmaxA
+                            : unevenA              ? 16600 - 1200 * h.lmaxA
+                                                   : 10300;
+    const int64_t half = std::max<int64_t>(results, 10300) + 620 * ktiles + 18 * tiles;
+    const int64_t small = 8500 + 100 * ktiles + pairs * (2000 + 360 * ktiles) / 512 + (tiles * kChunkPairs + 511) / 512 * 1000 * h.lmaxB;
+    return small < half;
+}
 // Whether the small tiles are the better ones for this plan (and B's rows are laid out for them).
 static bool small_tiles(const Plan *p, int64_t tiles, int64_t pairs, int64_t ktiles) {
-    return p->hdr.chunkB == kChunk && small_tiles_win(tiles, pairs, ktiles, p->nitems == 1, !p->fp6, 0, tile_ns(p->hdr));
+    if (p->hdr.chunkB != kChunk) return false;
+    const bool single = p->nitems == 1;
+    if (single && !p->fp6 && tiles <= 128 && split_parts(tiles, ktiles) == 1) return small_tiles_beat_halves(p->hdr, tiles, pairs, ktiles);
+    return small_tiles_win(tiles, pairs, ktiles, single, 0, tile_ns(p->hdr));
 }
 // The chunk pairs of an unpacked product that hold source rows.
 static int64_t chunk_pairs(const PlanHeader &h) {

@@ -2187,13 +2187,14 @@ __global__ __launch_bounds__(kPlanThreads) void layouts_kernel(
     else if (bx < slA + slB) {
         // (chunk by chunk a few more rows of B are padding, which may cost a round of the large tiles: 2000 x 2000 x 2000 with
         // entries of three digits, un-fused: 272 tiles instead of 256, 944 us, 682 so.  Only the unpacked sizes tell: rows and k-tiles
-        // without their padding, and a margin for it.  For b <= 4 the digits may still be asked for in six bits, which have no half tiles: counted
-        // without them.  With them int8 products took the same times (1576 x 1537 by 6144 26.4 and 26.4 us, 2640 x 1031 by 1554 26.3 and 26.3), but the
-        // six-bit ones of a new plan lost their small tiles: 22 -> 40 and, 2092 x 768 by 1536, 19 -> 37 us.)
+        // without their padding, and a margin for it.  Half tiles are not counted: what they take goes by the
+        // levels, and for b <= 4 the digits may still be asked for in six bits, which have none.  Counted as for products without levels they
+        // brought nothing (1576 x 1537 by 6144 26.4 and 26.4 us, 2640 x 1031 by 1554 26.3 and 26.3) and took the small tiles from others: 954 x 64
+        // by 2405 14 -> 32 us, 148 x 76 by 7676 14 -> 30, six-bit digits in a new plan 22 -> 40 and 19 -> 37.)
         if (chunkB == kChunk && gridDim.y == 1) {
             auto up = [](int x, int by) { return (int64_t)((x + by - 1) / by); };
             const int nu = hdr->n_u, hu = hdr->h_u;
-            if (!small_tiles_win(up(nu, kTile) * up(hu, kTile), up(nu, kChunk) * up(hu, kChunk), up(hdr->d_u, kKPad), true, sh > 3, 25)) chunkB = kTile;
+            if (!small_tiles_win(up(nu, kTile) * up(hu, kTile), up(nu, kChunk) * up(hu, kChunk), up(hdr->d_u, kKPad), true, 25)) chunkB = kTile;
         }
         rows_layout(rowB, h, &hdr->h_u, layB, cap_physB, cap_physB / kTile + 2, tmpPB, hdr, 1, chunkB, lds, fast_lds ? fast_rows : nullptr, bx - slA, slB);
         if (LISTS && bx == slA)

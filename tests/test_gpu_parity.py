@@ -1754,7 +1754,8 @@ def test_appended_columns_of_few_digits(imu, n, d, h, sa, longer, parts):
 
 @pytest.mark.parametrize("n,d,h,b,levels,few,splits,blev,halves", [
     (257, 128, 8200, 8, 1, 0, 0, 1, True),         # a single k-tile; the second half of a tile of rows is padding
-    (130, 129, 12100, 8, 1, 9, 40, 2, True),       # two k-tiles, rows of one and two levels, split columns
+    # two k-tiles, rows of one and two levels, split columns (12100 rows of B, 48 tiles, are for the small tiles: 19.5 us, 25.8 in half tiles)
+    (130, 129, 24100, 8, 1, 9, 40, 2, True),
     (4127, 380, 2049, 8, 2, 3, 0, 1, True),        # three k-tiles, more half tiles than two to a CU
     (1000, 1300, 8193, 5, 4, 11, 8180, 2, True),   # four levels a row, columns evenly laid out
     (1000, 1300, 2100, 5, 2, 11, 2095, 3, True),   # ... in four levels
@@ -1786,6 +1787,32 @@ def test_half_tiles_and_whole_ones(imu, n, d, h, b, levels, few, splits, blev, h
     assert bool((around[:4096] == -1).all()) and bool((around[-4096:] == -1).all())
     rows = np.unique(np.concatenate([np.arange(0, n, 61), [n // 2, n - 1]]))
     assert np.array_equal(C_int[torch.from_numpy(rows).cuda()].cpu().numpy(), oracle.int_gemm(Aq[rows], Bq))
+
+
+@pytest.mark.parametrize("n,d,h,b,lev_a,few_a,lev_b,few_b,parts,halves", [
+    (338, 64, 481, 5, 3, 60, 5, 0, 0, 0),       # one k-tile, results through LDS in half tiles: small tiles
+    (148, 76, 1919, 5, 1, 60, 4, 0, 0, 0),
+    (173, 149, 3036, 3, 3, 60, 2, 7, 0, 0),     # the same where rows of B have two levels each
+    (130, 129, 12100, 8, 1, 9, 1, 40, 0, 0),    # a few rows of two levels on either side
+    (1576, 800, 3072, 8, 1, 0, 1, 0, 1, 1),     # 84 tiles without levels: half tiles
+    (776, 97, 972, 6, 3, 0, 3, 0, 1, 1),        # 120 with three levels a row on both sides: four rounds of small tiles
+])
+def test_small_tiles_and_half_tiles_of_few_large_ones(imu, n, d, h, b, lev_a, few_a, lev_b, few_b, parts, halves):
+    """At most 128 tiles, by levels of either side: which kernel runs, and its results."""
+    s = 1 << (b - 1)
+    rng = np.random.default_rng(n + d + h)
+    Aq, Bq = _rows_of_levels(rng, n, d, s, lev_a, few_a), _rows_of_levels(rng, h, d, s, lev_b, few_b)
+    Qa, Qb = torch.from_numpy(Aq).cuda(), torch.from_numpy(Bq).cuda()
+    plan = imu.imunpack_plan(Qa, Qb, b, ROW, ROW)
+    A_ue, B_eu = imu.imunpack_unpack(plan, Qa, Qb)
+    C_int, C = torch.full((n, h), -1, dtype=torch.int64, device="cuda"), torch.full((n, h), -1.0, device="cuda")
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, None, C, None, fuse=True)
+    assert imu.imunpack_diag_gemm_parts(plan) == parts and imu.imunpack_diag_gemm_halves(plan) == halves
+    imu.imunpack_gemm(plan, A_ue, B_eu, 0.013, 0.0021, C_int, None, None, fuse=True)
+    want = oracle.int_gemm(Aq, Bq)
+    assert np.array_equal(C_int.cpu().numpy(), want)
+    ref = oracle.dequantize(want, 0.013, 0.0021)
+    assert (np.abs(C.cpu().numpy().astype(np.float64) - ref) <= REL_TOL * np.abs(ref)).all()
 
 
 @pytest.mark.parametrize("n,d,h,b,levels,few,blev,halves", [
